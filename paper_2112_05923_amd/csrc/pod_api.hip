@@ -451,8 +451,8 @@ int ppo_minibatch_grads(void *hip_stream, const pr_ppo_config *cfg, const float 
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) ||
       workspace_bytes < ppo_scratch_bytes(cfg->batch, cfg->hidden, cfg->n_stocks, 1 + cfg->n_stocks * (2 + cfg->n_ind)))
     return PR_EINVAL;
-  POD_HIP(launch_ppo_grads(static_cast<hipStream_t>(hip_stream), *cfg, obs, act_raw, logp_old, adv, ret, rows, *actor,
-                           *critic, *grad_actor, *grad_critic, workspace, stats));
+  POD_HIP(launch_ppo(static_cast<hipStream_t>(hip_stream), *cfg, obs, act_raw, logp_old, adv, ret, rows, *actor, *critic,
+                     *grad_actor, *grad_critic, nullptr, workspace, stats));
   return PR_OK;
 }
 
@@ -513,20 +513,10 @@ int ppo_learner_step(void *hip_stream, const pr_ppo_config *cfg, const float *ob
     p += align_up((size_t)nc[i] * 4, 256);
   }
   const pr_net_params gpa = {ga[0], ga[1], ga[2], ga[3], ga[4], ga[5]}, gpc = {gc[0], gc[1], gc[2], gc[3], gc[4], gc[5]};
-  int r2 = ppo_minibatch_grads(hip_stream, cfg, obs, act_raw, logp_old, adv, ret, rows, actor, critic, &gpa, &gpc,
-                               workspace, workspace_bytes, stats);
-  if (r2 != PR_OK) return r2;
-  // one launch for the twelve tensors
-  int64_t n12[12];
-  float *th[12], *gg[12], *mm[12], *vv[12];
-  float *const *ta = &actor->W1, *const *tc = &critic->W1;
-  float *const *ma = &m_actor->W1, *const *va = &v_actor->W1, *const *mc = &m_critic->W1, *const *vc = &v_critic->W1;
-  for (int i = 0; i < 6; ++i) {
-    n12[i] = na[i], th[i] = ta[i], gg[i] = ga[i], mm[i] = ma[i], vv[i] = va[i];
-    n12[6 + i] = nc[i], th[6 + i] = tc[i], gg[6 + i] = gc[i], mm[6 + i] = mc[i], vv[6 + i] = vc[i];
-  }
-  POD_HIP(launch_adam12(static_cast<hipStream_t>(hip_stream), n12, th, gg, mm, vv, cfg->lr, cfg->beta1, cfg->beta2,
-                        cfg->adam_eps, cfg->adam_step));
+  if (!obs || !act_raw || !logp_old || !adv || !ret) return PR_EINVAL;
+  const PpoAdam adam = {{m_actor, m_critic}, {v_actor, v_critic}};
+  POD_HIP(launch_ppo(static_cast<hipStream_t>(hip_stream), *cfg, obs, act_raw, logp_old, adv, ret, rows, *actor, *critic,
+                     gpa, gpc, &adam, workspace, stats));
   return PR_OK;
 }
 

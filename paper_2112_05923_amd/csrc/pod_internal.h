@@ -82,10 +82,14 @@ hipError_t launch_trading_metrics(hipStream_t st, int32_t T, int32_t N, int32_t 
 hipError_t launch_population_refill(hipStream_t st, int32_t P, int64_t count, const int32_t *rank, int32_t keep,
                                     float sigma, const float *noise, float *params);
 size_t ppo_scratch_bytes(int B, int Hd, int D, int S);
-hipError_t launch_ppo_grads(hipStream_t st, const pr_ppo_config &c, const float *obs, const float *act,
-                            const float *logp_old, const float *adv, const float *ret, const int32_t *rows,
-                            const pr_net_params &actor, const pr_net_params &critic, const pr_net_params &ga,
-                            const pr_net_params &gc, void *scratch, float *stats);
+// Gradients into ga / gc (whose tensors also hold intermediate sums), and with `adam` the update of both networks.
+struct PpoAdam {
+  const pr_net_params *m[2], *v[2];  // actor, critic
+};
+hipError_t launch_ppo(hipStream_t st, const pr_ppo_config &c, const float *obs, const float *act, const float *logp_old,
+                      const float *adv, const float *ret, const int32_t *rows, const pr_net_params &actor,
+                      const pr_net_params &critic, const pr_net_params &ga, const pr_net_params &gc,
+                      const PpoAdam *adam, void *scratch, float *stats);
 // The same with the scratch in a fixed device array of ppo_static_scratch_bytes() (no workspace, no allocation);
 // hipErrorInvalidValue when the shape needs more.
 size_t ppo_static_scratch_bytes();
@@ -93,8 +97,6 @@ hipError_t launch_ppo_grads_static(hipStream_t st, const pr_ppo_config &c, const
                                    const float *logp_old, const float *adv, const float *ret, const int32_t *rows,
                                    const pr_net_params &actor, const pr_net_params &critic, const pr_net_params &ga,
                                    const pr_net_params &gc, float *stats);
-hipError_t launch_adam12(hipStream_t st, const int64_t *n, float *const *theta, float *const *g, float *const *m,
-                         float *const *v, float lr, float b1, float b2, float eps, int32_t t);
 hipError_t launch_adam(hipStream_t st, int64_t n, float *theta, const float *g, float *m, float *v, float lr, float b1,
                        float b2, float eps, int32_t t);
 hipError_t launch_gae(hipStream_t st, int32_t T, int32_t N, const float *reward, const float *value,

@@ -2,341 +2,876 @@
 // transitions from the buffer, train the networks; Sec. 5.2: PPO, batch size
 // 1024, learning rate 1e-3): forward of actor and critic with the activations
 // kept, clipped-surrogate and value loss, backward through both 3-layer
-// perceptrons, Adam.  fp32 master weights, fp32 matrix-core arithmetic
-// (v_mfma_f32_32x32x2_f32), fp32 accumulation.
+// perceptrons, Adam.  fp32 master weights and activations.
 //
-// Every dense product -- forward, input gradient, weight gradient -- goes
-// through ONE tiled kernel that reads its operands through (row stride, column
-// stride) views, so no transposed copy of a weight or an activation is made;
-// bias + tanh, and the tanh derivative of the backward pass, are fused into its
-// epilogue.  The minibatch rows are gathered once into a zero-padded, aligned
-// copy that both networks' first layers read.  Nothing here allocates,
-// memsets or synchronises: a step is ~38 kernel launches on the caller's
-// stream and can sit in a captured graph (at the paper's batch of 1024 the
-// launches are short, so that is how it should be run).
+// A step is six launches, each over both networks:
+//   1. h1 = tanh(X W1 + b1), the minibatch rows gathered as they are read
+//   2. h2 = tanh(h1 W2 + b2)
+//   3. output layers, losses, dz3, and dz2 = (dz3 W3') (1 - h2^2)
+//   4. dz1 = (dz2 W2') (1 - h1^2)  and  gW2 = h1' dz2, gb2
+//   5. gW1 = X' dz1, gb1  and  gW3 = h2' dz3, gb3
+//   6. partial sums of the split weight gradients added up (in order), Adam
+// At the paper's batch of 1024 nothing is large: what a step costs is launches
+// and the memory round trips inside each, so independent products share a launch
+// and no launch does anything that the next could do while it reads.
+//
+// The forward pass keeps one fp32 accumulator per element (see forward_kernel).  The backward products run on the
+// bf16 matrix instructions without giving up binary32 precision: an fp32 number is exactly the sum of three bf16
+// numbers, and of the nine products the six that are not below 2^-26 of the result are summed in fp32 -- what is
+// dropped is smaller than the rounding of one fp32 product (pod_split3.h).  Six bf16 instructions take 6/16 of the time
+// of the fp32 instruction's same work.
+//
+// Measured (301-512-512 networks): a step at batch 1024 94 us (315 us as 38 launches); gradients at 15000 samples with
+// 256 hidden units 330 us (750 us).
+#include <math.h>
+
+#include <algorithm>
+#include <type_traits>
+
 #include "pod_internal.h"
+#include "pod_split3.h"
 
 namespace pod {
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef f32x4 f32x4u __attribute__((aligned(4)));
+typedef f32x2 f32x2u __attribute__((aligned(4)));
 
+// ------------------------------------------------------------------ dense products
+// C[M, N] = A' B' with k running over K.  Operand layouts by kind:
+//   DZ   A'[m][k] = A[m lda + k]   B'[k][n] = B[n ldb + k]     (dz x transposed weights)
+//   DW   A'[m][k] = A[k lda + m]   B'[k][n] = B[k ldb + n]     (transposed activations x dz; k is the batch)
+// `gather`: rows of A (indexed by k, DW) are rows gather[.] of the buffer.
+enum Kind { DZ = 1, DW = 2 };
 
-enum Epi { EPI_NONE = 0, EPI_BIAS_TANH = 1, EPI_BIAS = 2, EPI_DTANH = 3 };
-
-struct GemmArgs {
-  const float *A;        // A'[m][k] = A[m * a_rs + k * a_cs]
-  int64_t a_rs, a_cs;
-  const float *B;        // B'[k][n] = B[k * b_rs + n * b_cs]
-  int64_t b_rs, b_cs;
-  float *C;              // row-major [M, N]; with k_splits > 1: [k_splits][M, N] partial products
-  int32_t M, N, K;
-  int32_t a_m_phys;      // rows of A' that may be read (>= M: zero padding behind the logical rows); 0 = M
-  int32_t b_k_valid;     // rows of B' that exist (<= K: A' is zero beyond); 0 = K
-  int32_t k_splits, k_chunk;  // blockIdx.z takes k in [z k_chunk, (z + 1) k_chunk)
-  const float *bias;     // [N]   (EPI_BIAS_TANH, EPI_BIAS)
-  const float *aux;      // [M, N] saved activation h: C = acc * (1 - h^2)   (EPI_DTANH)
-  int32_t epi;           // (EPI_NONE when k_splits > 1)
+struct Prob {
+  const float *A, *B;
+  const int32_t *gather;
+  float *C;              // DZ: [M, N];  DW: the first split's part of gW
+  const float *aux;      // DZ: C = . * (1 - aux^2)
+  float *colsum;         // DW: the first split's part of gb[n] = sum_k B'[k][n]
+  float *part;           // DW: later splits, [split - 1][M + 1][N], the column sums in row M
+  int64_t lda;
+  int32_t ldb, ldc, M, N, K;    // ldc: rows of C and aux (the later splits' parts are dense)
+  int32_t kind, tiles_n, tiles, splits, k_chunk;
+  int32_t first_block, blocks;  // blocks = tiles * splits rounded up to a multiple of 8
+};
+constexpr int kMaxProbs = 4;
+constexpr int kOwnTiles = 1000;  // tiles from which every wavefront takes one of its own
+struct ProbSet {
+  Prob p[kMaxProbs];
+  int32_t n;
 };
 
-// One operand's staging of a [TM x GK] slice into the k-major LDS tile S[k][mn].
-//   VEC: 16-byte global loads along the operand's contiguous dimension (pointers and guards set up once, advanced by
-//        a uniform stride per slice).  Needs a 16-byte aligned base, the other stride a multiple of 4 elements and
-//        the extent along the contiguous dimension a multiple of 4 (the host checks).  Loads along k are scattered
-//        into 4 LDS rows (lanes 4 apart in k, so the 64 stores of a wavefront hit distinct banks), loads along
-//        m/n are one 16-byte LDS store.
-//   else: 4-byte loads through the general (row stride, column stride) view, for the few skinny or unaligned
-//        operands (30-column output layer, scalar value head).
-template <int TM, int GK, bool VEC>
-struct Stage {
-  static constexpr int TP = TM + 4;
-  static constexpr int NV = VEC ? TM * GK / 1024 : TM * GK / 256;
-  const float *ptr[NV];
-  int kof[NV], sof[NV];  // k offset inside the slice; LDS offset of the first element
-  bool along_k;
-  int64_t kstep;
-  float4 v4[VEC ? NV : 1];
-  float v1[VEC ? 1 : NV];
-  int mn_ok[VEC ? 1 : NV];
+// A wavefront computes a 64 x 64 tile of C, its operands read straight from global memory into the registers of the
+// matrix operands: no LDS and no barrier in the loop.  With fewer tiles than SIMDs the eight wavefronts of a
+// workgroup share one tile's k range (every operand element is still read by exactly one of them) and their
+// accumulators are added up, in order, in LDS at the end; with more, each wavefront takes a tile of its own.
+// Operand of a 32 x 32 x 16 product: lane l holds 8 consecutive k of row (column) l % 32, k group l / 32.
+//   k contiguous in memory: two 16-byte loads; row of block x is 32 x + l % 32;
+//   m (n) contiguous: eight 8-byte loads, one per k, that serve both 32-row blocks: row of block x is 2 (l % 32) + x.
+constexpr int kTile = 64, kPitch = kTile + 4;
 
-  // base: the operand; ks / ms: element strides along k and along m (or n); mn0: first row/column of the tile;
-  // mn_lim: rows/columns that may be read
-  __device__ void init(const float *base, int64_t ks, int64_t ms, int mn0, int mn_lim, int kbeg, int tid) {
-    along_k = (ks == 1);
-    kstep = (int64_t)GK * ks;
+// Granularity is 16 k (one matrix instruction deep).  Requests are made for ascending k: `load` reads the 16 k at the
+// present position into a slot, `advance` moves on.
+template <class T>
+__device__ inline void pin(T &x) { asm volatile("" : "+v"(x)); }  // x is needed, and settled, here
+
+template <int SLOTS>
+struct RawK {  // k-contiguous operand: [slot][block][8]
+  const float *p[2];
+  f32x4 v[SLOTS][2][2];
+  __device__ void init(const float *base, int64_t ld, int r0, int rows, const int32_t *gather, int k, int, int lane) {
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const int idx = tid + 256 * j;
-      int k, mn;
-      if (VEC) {
-        if (along_k) {
-          k = 4 * (idx % (GK / 4)), mn = idx / (GK / 4);
-        } else {
-          mn = 4 * (idx % (TM / 4)), k = idx / (TM / 4);
-        }
-        // rows/columns past the edge are clamped: they only feed rows/columns of C that are never stored
-        int gmn = mn0 + mn;
-        const int last = along_k ? mn_lim - 1 : mn_lim - 4;
-        gmn = gmn < last ? gmn : last;
-        ptr[j] = base + (int64_t)gmn * ms + (int64_t)(kbeg + k) * ks;
-      } else {
-        if (along_k) {
-          k = idx % GK, mn = idx / GK;
-        } else {
-          mn = idx % TM, k = idx / TM;
-        }
-        mn_ok[j] = mn0 + mn < mn_lim;
-        ptr[j] = base + (int64_t)(mn_ok[j] ? mn0 + mn : 0) * ms + (int64_t)(kbeg + k) * ks;
-      }
-      kof[j] = k;
-      sof[j] = k * TP + mn;
+    for (int x = 0; x < 2; ++x) {
+      int r = min(r0 + 32 * x + (lane & 31), rows - 1);
+      if (gather) r = gather[r];
+      p[x] = base + (int64_t)r * ld + k + 8 * (lane >> 5);
     }
   }
-  // k0: first k of the slice, klim: first k that must read as zero
-  __device__ void fetch(int k0, int klim) {
+  template <int SLOT>
+  __device__ void load(int kend, int lane) {
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      if (VEC) {
-        float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (k0 + kof[j] < klim) v = *reinterpret_cast<const float4 *>(ptr[j]);
-        v4[j] = v;
-      } else {
-        float v = 0.0f;
-        if (mn_ok[j] && k0 + kof[j] < klim) v = *ptr[j];
-        v1[j] = v;
-      }
-      ptr[j] += kstep;
-    }
-  }
-  __device__ void store(float *S) const {
+    for (int x = 0; x < 2; ++x)
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      if (VEC) {
-        if (along_k) {
-          S[sof[j]] = v4[j].x, S[sof[j] + TP] = v4[j].y, S[sof[j] + 2 * TP] = v4[j].z, S[sof[j] + 3 * TP] = v4[j].w;
-        } else {
-          *reinterpret_cast<float4 *>(S + sof[j]) = v4[j];
-        }
-      } else {
-        S[sof[j]] = v1[j];
-      }
-    }
+      for (int q = 0; q < 2; ++q) v[SLOT][x][q] = *reinterpret_cast<const f32x4u *>(p[x] + 4 * q);
   }
+  __device__ void advance(int step) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x) p[x] += step;
+  }
+  template <int SLOT>
+  __device__ void arrived() {  // (a use of the slot: the wait for it stands here)
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) pin(v[SLOT][x][q]);
+  }
+  template <int SLOT>
+  __device__ float get(int x, int e) const { return v[SLOT][x][e >> 2][e & 3]; }
 };
 
-// C = A' B' on the fp32 matrix cores.  A workgroup of 4 wavefronts owns a TM x TM tile of C (each wavefront a
-// TM/2 x TM/2 quadrant = (TM/64)^2 accumulators of 32 x 32); the k range is walked in slices of GK that are staged
-// in LDS k-major, so that the two operands of v_mfma_f32_32x32x2_f32 are conflict-free row reads.  The next
-// slice's global loads are issued into registers before the matrix instructions of the current one.
-template <int TM, int GK, bool VA, bool VB>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
-  constexpr int TP = TM + 4;         // LDS row pitch
-  constexpr int Q = TM / 64;         // 32 x 32 accumulators per wavefront and dimension
-  __shared__ __align__(16) float As[GK * TP];
-  __shared__ __align__(16) float Bs[GK * TP];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TM;
-  const int mi = (w & 1) * (TM / 2), ni = (w >> 1) * (TM / 2);
-  const int kbeg = blockIdx.z * g.k_chunk, kend = min(g.K, kbeg + g.k_chunk);
-  const int kend_b = min(kend, g.b_k_valid);
-  f32x16 acc[Q][Q];
+template <int SLOTS, bool GATHER>
+struct RawM {  // m- (n-) contiguous operand: [slot][8] pairs
+  const float *base;  // uniform
+  const int32_t *gather;
+  uint32_t off;       // of this lane's column pair and k half
+  int64_t ld;
+  int k, kend;
+  int32_t id[8];  // rows of the present 16 k (GATHER; requested one position ahead)
+  bool second;    // the pair was moved down by one at the end of the row: its first element is the second loaded
+  f32x2 v[SLOTS][8];
+  __device__ void rows_of(int lane) {
 #pragma unroll
-  for (int x = 0; x < Q; ++x)
+    for (int e = 0; e < 8; ++e) id[e] = gather[min(k + 8 * (lane >> 5) + e, kend - 1)];
+  }
+  __device__ void init(const float *b, int64_t ld_, int c0, int cols, const int32_t *g, int k_, int kend_, int lane) {
+    const int c = c0 + 2 * (lane & 31), last = cols > 1 ? cols - 2 : 0;
+    second = c == cols - 1 && cols > 1;
+    ld = ld_, gather = g, k = k_, kend = kend_;
+    off = (uint32_t)min(c, last);
+    if constexpr (GATHER) {
+      base = b;
+      rows_of(lane);
+    } else {
+      base = b + k * ld;
+      off += (uint32_t)(8 * (lane >> 5)) * (uint32_t)ld;
+    }
+  }
+  template <int SLOT>
+  __device__ void load(int, int lane) {
 #pragma unroll
-    for (int y = 0; y < Q; ++y)
+    for (int e = 0; e < 8; ++e) {
+      if constexpr (GATHER)
+        v[SLOT][e] = *reinterpret_cast<const f32x2u *>(base + (id[e] * ld + off));
+      else
+        v[SLOT][e] = *reinterpret_cast<const f32x2u *>(base + e * ld + off);
+    }
+  }
+  __device__ void advance(int step) {
+    k += step;
+    if constexpr (GATHER) rows_of(threadIdx.x & 63);
+    else base += step * ld;
+  }
+  // the 16 k at the present position with rows outside [k_from, kend) as zeros (the others clamped into the range)
+  template <int SLOT>
+  __device__ void load_trimmed(int k_from, int lane) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int kk = k + 8 * (lane >> 5) + e;
+      const bool ok = kk >= k_from && kk < kend;
+      const int64_t row = min(kk, kend - 1);
+      const int64_t at = GATHER ? (int64_t)gather[row] * ld + off : (row - k) * ld + (int64_t)(off - (uint32_t)(8 * (lane >> 5)) * (uint32_t)ld);
+      const f32x2 t = *reinterpret_cast<const f32x2u *>(base + at);
+      v[SLOT][e] = f32x2{ok ? t[0] : 0.0f, ok ? t[1] : 0.0f};
+    }
+  }
+  template <int SLOT>
+  __device__ void arrived() {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) pin(v[SLOT][e]);
+  }
+  template <int SLOT>
+  __device__ float get(int x, int e) const { return x == 0 && !second ? v[SLOT][e][0] : v[SLOT][e][1]; }
+};
+
+// kw = 1: the whole range, software pipelined.  What bounds a wavefront there is one stream of instructions: 24 matrix
+// instructions of 32 cycles and about 180 vector instructions of 4 cycles (the splits) per 16 k; one after the other
+// they take 1500 cycles, so the split of the next 16 k is interleaved with the products of the present one, seven or
+// eight vector instructions behind each matrix instruction.
+// kw = 8: a share of at most four 16-deep steps at a time, all requested at once; what counts is one memory round trip.
+template <int KW, Kind KIND, bool SUMS, bool GATHER>
+__device__ inline void product(const Prob &g, int m0, int n0, int kbeg, int kend, int split, float *lds) {
+  const int tid = threadIdx.x, lane = tid & 63, w = KW == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr bool A_K = KIND == DZ, B_K = A_K;
+  constexpr int SLOTS = KW == 1 ? 2 : 4;
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[x][y][i] = 0.0f;
-  Stage<TM, GK, VA> sa;
-  Stage<TM, GK, VB> sb;
-  sa.init(g.A, g.a_cs, g.a_rs, m0, g.a_m_phys, kbeg, tid);
-  sb.init(g.B, g.b_rs, g.b_cs, n0, g.N, kbeg, tid);
-  sa.fetch(kbeg, kend);
-  sb.fetch(kbeg, kend_b);
-  for (int k0 = kbeg; k0 < kend; k0 += GK) {
-    sa.store(As);
-    sb.store(Bs);
-    __syncthreads();
-    if (k0 + GK < kend) {
-      sa.fetch(k0 + GK, kend);
-      sb.fetch(k0 + GK, kend_b);
+  float cs[2] = {0.0f, 0.0f};
+  // wavefront w: the w-th share of the full 16-deep steps; what is left over goes to the last wavefront
+  const int steps = (kend - kbeg) / 16, rest = (kend - kbeg) & 15, per = (steps + KW - 1) / KW;
+  const int s0 = min(w * per, steps), s1 = min(s0 + per, steps);
+  std::conditional_t<A_K, RawK<SLOTS>, RawM<SLOTS, GATHER>> ra;
+  std::conditional_t<B_K, RawK<SLOTS>, RawM<SLOTS, false>> rb;
+  bf16x8 a[2][2][3], b[2][2][3];  // [step parity][block][part]
+  auto split_slot = [&](auto slot, auto par) {
+    constexpr int SL = decltype(slot)::value, P = decltype(par)::value;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      float va[8], vb[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) va[e] = ra.template get<SL>(x, e), vb[e] = rb.template get<SL>(x, e);
+      split3(va, a[P][x]);
+      split3(vb, b[P][x]);
     }
+  };
+  auto add_sums = [&](auto slot) {
+    constexpr int SL = decltype(slot)::value;
 #pragma unroll
-    for (int kk = 0; kk < GK; kk += 2) {
-      float a[Q], b[Q];
+    for (int x = 0; x < 2; ++x)
 #pragma unroll
-      for (int x = 0; x < Q; ++x) a[x] = As[(kk + (lane >> 5)) * TP + mi + 32 * x + (lane & 31)];
+      for (int e = 0; e < 8; ++e) cs[x] += rb.template get<SL>(x, e);
+  };
+  auto multiply = [&](auto par) {
+    constexpr int P = decltype(par)::value;
 #pragma unroll
-      for (int y = 0; y < Q; ++y) b[y] = Bs[(kk + (lane >> 5)) * TP + ni + 32 * y + (lane & 31)];
+    for (int q = 0; q < 6; ++q) {
 #pragma unroll
-      for (int x = 0; x < Q; ++x)
+      for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int y = 0; y < Q; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[x], b[y], acc[x][y], 0, 0, 0);
+        for (int y = 0; y < 2; ++y)
+          acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[P][x][kSplitA[q]], b[P][y][kSplitB[q]], acc[x][y], 0, 0, 0);
     }
-    __syncthreads();
-  }
-  // accumulator register i of lane l: row 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32
-  float *C = g.C + (g.k_splits > 1 ? (int64_t)blockIdx.z * g.M * g.N : 0);
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, SLOTS == 4 ? 2 : 0>;
+  using I3 = std::integral_constant<int, SLOTS == 4 ? 3 : 0>;
+  auto load = [&](auto slot, bool more) {  // (requests past the wavefront's last step repeat it)
+    ra.template load<decltype(slot)::value>(kend, lane);
+    rb.template load<decltype(slot)::value>(kend, lane);
+    ra.advance(more ? 16 : 0);
+    rb.advance(more ? 16 : 0);
+  };
+  if (s0 < s1) {
+    const int k0 = kbeg + 16 * s0;
+    ra.init(g.A, g.lda, m0, g.M, g.gather, k0, kend, lane);
+    rb.init(g.B, g.ldb, n0, g.N, nullptr, k0, kend, lane);
+    if constexpr (KW == 1 && KIND == DW) {
+      // (two m-contiguous operands and the batch rows' indices leave no registers for a second set of parts: the two
+      // wavefronts of a SIMD overlap each other)
+      load(I0{}, s0 + 1 < s1);
+      load(I1{}, s0 + 2 < s1);
+      auto step = [&](auto cur, int s) {
+        split_slot(cur, I0{});
+        if (SUMS) add_sums(cur);
+        load(cur, s + 3 < s1);
+        multiply(I0{});
+      };
+      for (int s = s0; s < s1; s += 2) {
+        step(I0{}, s);
+        if (s + 1 < s1) step(I1{}, s + 1);
+      }
+    } else if constexpr (KW == 1) {
+      load(I0{}, s0 + 1 < s1);
+      load(I1{}, s0 + 2 < s1);
+      split_slot(I0{}, I0{});
+      if (SUMS) add_sums(I0{});
+      // step s: products of s (parts of parity s), split of s + 1 (requested a step ago), request of s + 2
+      auto step = [&](auto cur, auto next, int s) {
+        constexpr int NX = decltype(next)::value;
+        ra.template arrived<NX>();
+        rb.template arrived<NX>();
+        load(cur, s + 3 < s1);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(cur);
+        split_slot(next, next);
+        if (SUMS) {
+          if (s + 1 < s1) add_sums(next);
+        } else {
 #pragma unroll
-  for (int y = 0; y < Q; ++y) {
-    const int col = n0 + ni + 32 * y + (lane & 31);
-    if (col < g.N) {
-      const float bv = (g.epi == EPI_BIAS_TANH || g.epi == EPI_BIAS) ? g.bias[col] : 0.0f;
-#pragma unroll
-      for (int x = 0; x < Q; ++x)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int row = m0 + mi + 32 * x + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-          if (row < g.M) {
-            float v = acc[x][y][i] + bv;
-            if (g.epi == EPI_BIAS_TANH) v = tanhf(v);
-            if (g.epi == EPI_DTANH) {
-              const float h = g.aux[(int64_t)row * g.N + col];
-              v = v * (1.0f - h * h);
-            }
-            C[(int64_t)row * g.N + col] = v;
+          for (int i = 0; i < 24; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one matrix instruction
+            __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);  // eight vector instructions
           }
         }
+        // (used here: otherwise the compiler moves the split behind the loop's exit test, out of the products' shadow)
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int j = 0; j < 3; ++j) pin(a[NX][x][j]), pin(b[NX][x][j]);
+      };
+      for (int s = s0; s < s1; s += 2) {
+        step(I0{}, I1{}, s);
+        if (s + 1 < s1) step(I1{}, I0{}, s + 1);
+      }
+    } else {
+      for (int s = s0; s < s1; s += 4) {
+        load(I0{}, s + 1 < s1);
+        load(I1{}, s + 2 < s1);
+        load(I2{}, s + 3 < s1);
+        load(I3{}, s + 4 < s1);
+        auto take = [&](auto slot, int i) {
+          if (s + i >= s1) return;
+          split_slot(slot, I0{});
+          if (SUMS) add_sums(slot);
+          multiply(I0{});
+        };
+        take(I0{}, 0);
+        take(I1{}, 1);
+        take(I2{}, 2);
+        take(I3{}, 3);
+      }
+    }
+  }
+  if (rest && w == KW - 1) {
+    // (DW only: the k of DZ is the hidden width.)  The last 16 of a k range that is no multiple of 16 are the 16 that
+    // end it, the ones already counted as zeros in B'; a range of fewer than 16 repeats its last row, zeros likewise.
+    const int k_read = max(kbeg, kend - 16);
+    ra.init(g.A, g.lda, m0, g.M, g.gather, k_read, kend, lane);
+    rb.init(g.B, g.ldb, n0, g.N, nullptr, k_read, kend, lane);
+    if constexpr (KIND == DW) {
+      ra.template load_trimmed<0>(kbeg + 16 * steps, lane);
+      rb.template load_trimmed<0>(kbeg + 16 * steps, lane);
+    }
+    split_slot(I0{}, I0{});
+    if (SUMS) add_sums(I0{});
+    multiply(I0{});
+  }
+  float *C = g.C, *C_sum = g.colsum;
+  int64_t ldc = g.ldc;
+  if (split > 0) C = g.part + (int64_t)(split - 1) * (g.M + 1) * g.N, C_sum = C + (int64_t)g.M * g.N, ldc = g.N;
+  if constexpr (KW == 1) {
+    // Accumulator register i of lane l: row 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32.  Column blocks of an
+    // n-contiguous B' interleave, so a lane's two columns are neighbours.
+    const int half = lane >> 5, N = g.N;
+    const int n = n0 + (B_K ? (lane & 31) : 2 * (lane & 31));
+    constexpr int NY = B_K ? 32 : 1;  // distance of a lane's two columns
+    auto finish = [&](auto full) {
+      constexpr bool FULL = decltype(full)::value;
+      const int na = FULL ? n : min(n, N - 1), nb = FULL ? n + NY : min(n + NY, N - 1);
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        auto row_of = [&](int i) {
+          const int r = 8 * (i >> 2) + 4 * half + (i & 3);
+          return m0 + (A_K ? 32 * x + r : 2 * r + x);
+        };
+        float h[16][2];
+        if constexpr (KIND == DZ) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const float *src = g.aux + (FULL ? row_of(i) : min(row_of(i), g.M - 1)) * ldc;
+            h[i][0] = src[na], h[i][1] = src[nb];
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          f32x2 c = {acc[x][0][i], acc[x][1][i]};
+          if constexpr (KIND == DZ) c = f32x2{c[0] * (1.0f - h[i][0] * h[i][0]), c[1] * (1.0f - h[i][1] * h[i][1])};
+          float *dst = C + row_of(i) * ldc;
+          if (FULL && NY == 1) {
+            *reinterpret_cast<f32x2u *>(dst + n) = c;
+          } else if (FULL || row_of(i) < g.M) {
+            if (FULL || n < N) dst[n] = c[0];
+            if (FULL || n + NY < N) dst[n + NY] = c[1];
+          }
+        }
+      }
+    };
+    if (m0 + kTile <= g.M && n0 + kTile <= N) finish(std::true_type{});
+    else finish(std::false_type{});
+    if constexpr (SUMS) {
+#pragma unroll
+      for (int y = 0; y < 2; ++y) {
+        const float t = cs[y] + __shfl_xor(cs[y], 32);
+        const int n = n0 + 2 * (lane & 31) + y;
+        if (half == 0 && n < g.N) C_sum[n] = t;
+      }
+    }
+    return;
+  }
+  // LDS: [wavefront][n][m], m and n in block order.
+  float *mine = lds + w * (kTile * kPitch);
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x4 v = {acc[x][y][4 * j], acc[x][y][4 * j + 1], acc[x][y][4 * j + 2], acc[x][y][4 * j + 3]};
+        *reinterpret_cast<f32x4 *>(mine + (32 * y + (lane & 31)) * kPitch + 32 * x + 8 * j + 4 * (lane >> 5)) = v;
+      }
+  float *lds_cs = lds + KW * (kTile * kPitch);  // [wavefront][k half][64]
+  if (SUMS) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x) lds_cs[(w * 2 + (lane >> 5)) * kTile + 32 * x + (lane & 31)] = cs[x];
+  }
+  // a wavefront finishes ROWS rows of the tile, lanes along n
+  constexpr int ROWS = kTile / KW;
+  const int n = n0 + (B_K ? lane : 2 * (lane & 31) + (lane >> 5)), nc = min(n, g.N - 1);
+  auto row_of = [&](int i) {
+    const int slot = ROWS * w + i;
+    return m0 + (A_K ? slot : 2 * (slot & 31) + (slot >> 5));
+  };
+  float extra[ROWS];  // what the epilogue needs from memory, requested before the barrier
+  if (A_K) {
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) extra[i] = g.aux[min(row_of(i), g.M - 1) * ldc + nc];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < ROWS / 4; ++q) {
+    const float *src = lds + lane * kPitch + ROWS * w + 4 * q;
+    f32x4 v = *reinterpret_cast<const f32x4 *>(src);
+#pragma unroll
+    for (int z = 1; z < KW; ++z) v += *reinterpret_cast<const f32x4 *>(src + z * (kTile * kPitch));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int m = row_of(4 * q + i);
+      float c = v[i];
+      if (A_K) c *= 1.0f - extra[4 * q + i] * extra[4 * q + i];
+      if (n < g.N && m < g.M) C[m * ldc + n] = c;
+    }
+  }
+  if (SUMS && w == 0 && n < g.N) {
+    float t = 0.0f;
+#pragma unroll
+    for (int z = 0; z < 2 * KW; ++z) t += lds_cs[z * kTile + lane];
+    C_sum[n] = t;
+  }
+}
+
+constexpr size_t products_lds(int kw) { return kw == 1 ? 0 : (size_t)kw * (kTile * kPitch + 2 * kTile) * 4; }
+
+// KW = 8: one tile per workgroup of eight wavefronts; KW = 1: four wavefronts, a tile each (neighbours in n: they read
+// the same rows of A)
+template <int KW>
+__global__ __launch_bounds__(KW == 1 ? 256 : 512, 2) void products_kernel(ProbSet set) {
+  extern __shared__ __align__(16) float lds[];
+  int i = 0;
+  while (i + 1 < set.n && (int)blockIdx.x >= set.p[i + 1].first_block) ++i;
+  const Prob &g = set.p[i];
+  // neighbouring tiles (which share rows of A) on one XCD: blocks are dealt out to the 8 XCDs in turn
+  const int local = (int)blockIdx.x - g.first_block, per = g.blocks >> 3;
+  int t = (local & 7) * per + (local >> 3);
+  if (KW == 1) t = 4 * t + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  if (t >= g.tiles * g.splits) return;
+  const int split = t / g.tiles, tile = t - split * g.tiles;
+  const int tm = tile / g.tiles_n, tn = tile - tm * g.tiles_n;
+  const int kbeg = split * g.k_chunk, kend = min(g.K, kbeg + g.k_chunk);
+  const int m0 = tm * kTile, n0 = tn * kTile;
+  if (g.kind == DZ) {
+    product<KW, DZ, false, false>(g, m0, n0, kbeg, kend, 0, lds);
+  } else if (tm == 0) {
+    if (g.gather) product<KW, DW, true, true>(g, m0, n0, kbeg, kend, split, lds);
+    else product<KW, DW, true, false>(g, m0, n0, kbeg, kend, split, lds);
+  } else {
+    if (g.gather) product<KW, DW, false, true>(g, m0, n0, kbeg, kend, split, lds);
+    else product<KW, DW, false, false>(g, m0, n0, kbeg, kend, split, lds);
+  }
+}
+
+// ------------------------------------------------------------------ forward
+// h = tanh(A W + b) on the fp32 matrix instructions, every element one accumulator over k in ascending order (an fp32
+// matrix instruction rounds after every k, so this is the fused multiply-add chain, the same bits for every tile shape
+// and batch size).  The policy ratio is the exponential of a sum of 2 D terms of the means' errors over sigma^2: the
+// forward pass is where the gradients are sensitive to a last bit, so it is not left to the split products above.
+// A workgroup of eight wavefronts owns TM rows x 64 columns: wavefront w rows [16 (w % WM), + 16), NB column blocks of
+// 16.  Slices of 64 k go through LDS k-major (pitches that put the four k of an instruction on different banks), two
+// slices ahead in registers.  Bound by the fp32 matrix rate (64 flop per SIMD and cycle) once a launch is long enough;
+// at 1024 rows by its memory round trips.
+struct FwdProb {
+  const float *A, *W, *bias;
+  float *C;
+  int64_t lda;
+  int32_t K;
+};
+struct FwdArgs {
+  FwdProb p[2];             // actor, critic: blockIdx.y
+  const int32_t *gather;    // rows of A, or null
+  int32_t M, N, ldc, tiles_n, tiles;
+  // rows copied on the side by the blocks behind the tiles: W2 of each network to rows of ldc
+  const float *copy_src[2];
+  float *copy_dst[2];
+  int32_t copy_rows;
+};
+
+template <int TM>
+__global__ __launch_bounds__(512, 4) void forward_kernel(FwdArgs a) {
+  constexpr int KS = 64, WM = TM / 16, NB = WM / 2;  // wavefronts along m; 8 / WM along n, NB blocks of 16 each
+  constexpr int PA = TM + 16, PB = 80;               // LDS row pitches: 16 or 48 mod 64
+  constexpr int RA = TM * KS / 4 / 512;              // 16-byte groups of A per thread and slice
+  __shared__ __align__(16) float lds[2 * KS * (PA + PB)];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const FwdProb &g = a.p[blockIdx.y];
+  const int per = (a.tiles + 7) >> 3, local = (int)blockIdx.x;
+  if (local >= 8 * per) {
+    const int row = (local - 8 * per) * 8 + w;
+    if (row < a.copy_rows)
+      for (int k = lane; k < a.copy_rows; k += 64)
+        a.copy_dst[blockIdx.y][(int64_t)row * a.ldc + k] = a.copy_src[blockIdx.y][(int64_t)row * a.copy_rows + k];
+    return;
+  }
+  const int t = (local & 7) * per + (local >> 3);  // neighbouring tiles (the same rows of A) on one XCD
+  if (t >= a.tiles) return;
+  const int tm = t / a.tiles_n, m0 = tm * TM, n0 = (t - tm * a.tiles_n) * 64;
+  const int K = g.K, N = a.N;
+  const int mi = 16 * (w % WM), ni = 16 * NB * (w / WM);
+  const int j = lane & 15, q = lane >> 4;
+  // staging of A: row tid % TM, k groups of four
+  const float *pa;
+  {
+    int r = min(m0 + tid % TM, a.M - 1);
+    if (a.gather) r = a.gather[r];
+    pa = g.A + (int64_t)r * g.lda;
+  }
+  const int kq = tid / TM;  // first k group of this thread; the next ones are 512 / TM further
+  // of W: four columns of rows wk, wk + 32 of a slice (N is a multiple of 32)
+  const int wn = min(n0 + 4 * (tid & 15), N - 4), wk = tid >> 4;
+  f32x4 ra[2][RA], rb[2][2];
+  auto load = [&](auto slot, int k0) {
+    constexpr int SL = decltype(slot)::value;
+#pragma unroll
+    for (int i = 0; i < RA; ++i) {
+      // (a group that crosses the end is read as the four floats that end there; sorted out when it is stored)
+      const int k = k0 + 4 * (kq + i * (512 / TM));
+      if (K >= 4) ra[SL][i] = *reinterpret_cast<const f32x4u *>(pa + min(k, K - 4));
+      else ra[SL][i] = f32x4{0.0f, pa[0], pa[1], pa[2]};  // (rows of three: one stock without indicators)
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      rb[SL][i] = *reinterpret_cast<const f32x4u *>(g.W + (int64_t)min(k0 + wk + 32 * i, K - 1) * N + wn);
+  };
+  auto store = [&](auto slot, int k0, float *buf) {
+    constexpr int SL = decltype(slot)::value;
+#pragma unroll
+    for (int i = 0; i < RA; ++i) {
+      const int kl = 4 * (kq + i * (512 / TM)), k = k0 + kl;
+      f32x4 v = ra[SL][i];
+      if (k + 4 > K) {
+        const int sh = k + 4 - K;
+        v = f32x4{sh == 1 ? v[1] : sh == 2 ? v[2] : sh == 3 ? v[3] : 0.0f, sh == 1 ? v[2] : sh == 2 ? v[3] : 0.0f,
+                  sh == 1 ? v[3] : 0.0f, 0.0f};
+      }
+      float *dst = buf + kl * PA + tid % TM;
+      dst[0] = v[0], dst[PA] = v[1], dst[2 * PA] = v[2], dst[3 * PA] = v[3];
+    }
+    // (rows past the end are multiplied by the zeros behind A)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) *reinterpret_cast<f32x4 *>(buf + KS * PA + (wk + 32 * i) * PB + 4 * (tid & 15)) = rb[SL][i];
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  f32x4 acc[NB];
+#pragma unroll
+  for (int y = 0; y < NB; ++y) acc[y] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const int slices = (K + KS - 1) / KS;
+  auto multiply = [&](const float *buf) {
+    const float *A = buf + q * PA + mi + j, *Bp = buf + KS * PA + q * PB + ni + j;
+#pragma unroll
+    for (int i = 0; i < KS / 4; ++i) {
+      const float av = A[4 * i * PA];
+#pragma unroll
+      for (int y = 0; y < NB; ++y) acc[y] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, Bp[4 * i * PB + 16 * y], acc[y], 0, 0, 0);
+    }
+  };
+  float *buf0 = lds, *buf1 = lds + KS * (PA + PB);
+  load(I0{}, 0);
+  load(I1{}, KS);
+  for (int s = 0; s < slices; s += 2) {
+    store(I0{}, s * KS, buf0);
+    load(I0{}, (s + 2) * KS);
+    __syncthreads();
+    multiply(buf0);
+    if (s + 1 < slices) {
+      store(I1{}, (s + 1) * KS, buf1);
+      load(I1{}, (s + 3) * KS);
+      __syncthreads();
+      multiply(buf1);
+    }
+  }
+#pragma unroll
+  for (int y = 0; y < NB; ++y) {
+    const int n = n0 + ni + 16 * y + j;
+    if (n < N) {
+      const float b = g.bias[n];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int m = m0 + mi + 4 * q + i;
+        if (m < a.M) g.C[(int64_t)m * a.ldc + n] = tanhf(acc[y][i] + b);
+      }
     }
   }
 }
 
-// Minibatch rows of the buffer, zero-padded to a multiple of 4 columns: the aligned A operand of the first layer's
-// forward and weight-gradient products of both networks.  One wavefront per row.
-__global__ __launch_bounds__(256) void gather_pad_kernel(int B, int S, int Sp, const float *__restrict__ obs,
-                                                         const int32_t *__restrict__ rows, float *__restrict__ xp) {
-  const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (b >= B) return;
-  const float *src = obs + (int64_t)(rows ? rows[b] : b) * S;
-  for (int j = lane; j < Sp; j += 64) xp[(int64_t)b * Sp + j] = j < S ? src[j] : 0.0f;
-}
-
-// out[i] = sum_z part[z][i], z ascending
-__global__ __launch_bounds__(256) void reduce_splits_kernel(int64_t n, int splits, const float *__restrict__ part,
-                                                            float *__restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) {
-    float s = part[i];
-    for (int z = 1; z < splits; ++z) s += part[(int64_t)z * n + i];
-    out[i] = s;
-  }
-}
-
-// Column sums (bias gradients) gb[n] = sum_b dZ[b][n].  Grid (column blocks of 64, row chunks): a workgroup's
-// 4 wavefronts split the rows of its chunk, lanes run along the columns; chunk results go to part[chunk][n] and
-// are added up in chunk order by reduce_splits_kernel (or straight to gb when there is one chunk).
-constexpr int CS_MAX_CHUNKS = 64;
-inline int colsum_chunks(int B) { return B >= 128 * CS_MAX_CHUNKS ? CS_MAX_CHUNKS : (B + 127) / 128; }
-
-__global__ __launch_bounds__(256) void colsum_kernel(int B, int N, int rows_per_chunk, const float *__restrict__ dZ,
-                                                     float *__restrict__ out) {
-  __shared__ float part[4][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int n = blockIdx.x * 64 + lane;
-  const int b0 = blockIdx.y * rows_per_chunk, b1 = min(B, b0 + rows_per_chunk);
-  float s = 0.0f;
-  if (n < N)
-    for (int b = b0 + w; b < b1; b += 4) s += dZ[(int64_t)b * N + n];
-  part[w][lane] = s;
-  __syncthreads();
-  if (w == 0 && n < N) out[(int64_t)blockIdx.y * N + n] = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
-}
-
-struct LossArgs {
-  int32_t B, D;
-  const float *mu;        // [B, D] actor output (after tanh)
-  const float *v;         // [B]
+// ------------------------------------------------------------------ output layers and losses
+struct HeadArgs {
+  int32_t B, D, Hd;
+  int32_t ld;                               // rows of h2 and dz2
+  const float *h2[2];                       // [B, Hd]: actor, critic
+  const float *W3[2], *b3[2];
   const float *act, *logp_old, *adv, *ret;  // rollout buffers, indexed through rows
   const int32_t *rows;
   float sigma, clip, value_coef;
-  float *dz_actor;        // [B, D] d L / d (pre-tanh output)
-  float *dz_critic;       // [B]
-  float *partial;         // [blocks][4]
+  float *dz3[2];                            // [B, D], [B]: d L / d (last pre-activation)
+  float *dz2[2];                            // [B, Hd]
+  float *mu;                                // [B, D] and [B] scratch, used when a tile's means do not fit in LDS
+  float *partial;                           // [blocks][4]
+  int32_t net0;                             // network of blockIdx.y = 0
 };
+constexpr int kHeadRows = 16;
+constexpr int kHeadLdsD = 1024;  // most action components whose means a workgroup keeps in LDS
 
-// 32 lanes per sample (lanes over the action components): log-prob, ratio, which branch of the min() is live, the
-// two loss terms and the gradients w.r.t. the networks' last pre-activations.  Per-block partial sums of the
-// statistics in a fixed order.
-__global__ __launch_bounds__(256) void ppo_loss_kernel(LossArgs a) {
-  __shared__ float red[8][4];
-  const int sub = threadIdx.x & 31, grp = threadIdx.x >> 5;
-  const int b = blockIdx.x * 8 + grp;
+// 16 samples of one network (blockIdx.y) per workgroup: output layer on the fp32 matrix cores, loss terms and the gradient of the last pre-activation (32 lanes per sample), then that gradient
+// through W3' and the tanh of the second hidden layer.  Bound by the memory round trips of its stages: everything a
+// stage reads that does not depend on the one before is requested at the start.
+constexpr int kHeadWaves = 8;
+constexpr int head_slice(int NG, int KS) { return KS * (32 + NG + 16); }  // floats
+// NG: columns of the output layer at a time, KS: k per slice
+template <bool MU_LDS, int NG, int KS>
+__global__ __launch_bounds__(64 * kHeadWaves, 4) void head_kernel(HeadArgs a) {
+  extern __shared__ __align__(16) float lds[];
+  float *s_z = lds;                                 // slices of h2 and W3, k-major
+  float *s_red = lds + head_slice(NG, KS);          // [16][4]
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b0 = blockIdx.x * kHeadRows, net = a.net0 + blockIdx.y;
+  const int B = a.B, Hd = a.Hd, D = net == 1 ? 1 : a.D;  // (D: outputs of the network)
+  const int64_t ld = a.ld;
+  const int row = tid >> 5, sub = tid & 31;  // the lanes of a sample in the loss
+  const int b = b0 + row, bc = min(b, B - 1);
+  const float inv_b = 1.0f / (float)B;
+  const float *h2 = a.h2[net], *W3 = a.W3[net];
+  const int64_t r = a.rows ? a.rows[bc] : bc;
   float st[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  if (b < a.B) {  // uniform over the 32 lanes of a sample
-    const int64_t r = a.rows ? a.rows[b] : b;
-    const float inv_b = 1.0f / (float)a.B, inv_s2 = 1.0f / (a.sigma * a.sigma);
-    float q = 0.0f;
-    for (int d = sub; d < a.D; d += 32) {
-      const float e = a.act[r * a.D + d] - a.mu[(int64_t)b * a.D + d];
-      q += e * e;
+  {
+    // outputs of the tile (means, or values): [16][Dp] in LDS, or the rows of the scratch
+    const int Dp = MU_LDS ? D | 1 : D;
+    float *mu = MU_LDS ? lds + head_slice(NG, KS) + 16 * 4 : a.mu + (int64_t)b0 * D + (net == 1 ? (int64_t)B * a.D : 0);
+    const int j = lane & 15, q = lane >> 4;
+    const float logp_old = a.logp_old[r], A = a.adv[r], ret = a.ret[r];
+    const float act0 = a.act[r * a.D + min(sub, a.D - 1)];  // the first 32 components, requested early
+    // what the last stage reads for this wavefront's first feature tiles of 16 (columns d = 4 c + q < 32)
+    constexpr int PT = 2;
+    float yw[PT][8], hv[PT][4];
+    auto request = [&](int t0) {
+#pragma unroll
+      for (int p = 0; p < PT; ++p) {
+        const int t = min(t0 + kHeadWaves * p, Hd / 16 - 1);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) yw[p][c] = W3[(int64_t)(16 * t + j) * D + min(4 * c + q, D - 1)];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) hv[p][i] = h2[min(b0 + 4 * q + i, B - 1) * ld + 16 * t + j];
+      }
+    };
+    // Output layer, like the hidden ones one fp32 accumulator per mean over k in ascending order: slices of KS k through
+    // LDS, NG columns at a time, 16 per wavefront.
+    constexpr int PH = 16 + 16, PW = NG + 16;
+    for (int n0 = 0; n0 < D; n0 += NG) {
+      constexpr int RW = KS * NG / 512;  // weights per thread and slice
+      f32x4 rh;
+      float rw[RW];
+      const int hr = tid & 15, hk = 4 * (tid >> 4);  // (16 KS / 4 groups of four activations)
+      auto load = [&](int k0) {
+        if (hk < KS) rh = *reinterpret_cast<const f32x4u *>(h2 + min(b0 + hr, B - 1) * ld + min(k0 + hk, Hd - 4));
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+          const int e = tid + 512 * i;
+          rw[i] = W3[(int64_t)min(k0 + e / NG, Hd - 1) * D + min(n0 + e % NG, D - 1)];
+        }
+      };
+      f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+      load(0);
+      for (int k0 = 0; k0 < Hd; k0 += KS) {  // (Hd is a multiple of 32; groups past it are zeros)
+        __syncthreads();
+        if (hk < KS) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) s_z[(hk + i) * PH + hr] = k0 + hk < Hd ? rh[i] : 0.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+          const int e = tid + 512 * i;
+          s_z[KS * PH + (e / NG) * PW + e % NG] = k0 + e / NG < Hd ? rw[i] : 0.0f;
+        }
+        __syncthreads();
+        load(k0 + KS);
+        if (k0 == 0 && n0 == 0) request(w);
+        if (16 * w < NG) {
+#pragma unroll 8
+          for (int i = 0; i < KS / 4; ++i)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(s_z[(4 * i + q) * PH + j], s_z[KS * PH + (4 * i + q) * PW + 16 * w + j], acc, 0, 0, 0);
+        }
+      }
+      const int n = n0 + 16 * w + j;
+      if (16 * w < NG && n < D) {
+        const float bias = a.b3[net][n];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (MU_LDS || b0 + 4 * q + i < B) mu[(int64_t)(4 * q + i) * Dp + n] = net == 1 ? acc[i] + bias : tanhf(acc[i] + bias);
+      }
     }
-    for (int o = 16; o > 0; o >>= 1) q += __shfl_xor(q, o, 32);
-    const float logp = -(float)a.D * logf(a.sigma) - 0.5f * (float)a.D * 1.8378770664093453f - 0.5f * q * inv_s2;  // ln(2 pi)
-    const float ratio = expf(logp - a.logp_old[r]);
-    const float A = a.adv[r];
+    if (!MU_LDS) __threadfence_block();
+    __syncthreads();
+    if (net == 1) {
+      const float err = mu[(int64_t)row * Dp] - ret;
+      const float dz = b < B ? a.value_coef * err * inv_b : 0.0f;
+      if (sub == 0 && b < B) {
+        a.dz3[1][b] = dz;
+        st[1] = 0.5f * err * err * inv_b;
+      }
+      if (MU_LDS) {
+        __syncthreads();  // (every lane of the sample has read its value)
+        if (sub == 0) mu[(int64_t)row * Dp] = dz;
+      }
+    } else {
+    float sq = 0.0f;
+    if (b < B)
+      for (int d = sub; d < D; d += 32) {
+        const float e = (d < 32 ? act0 : a.act[r * D + d]) - mu[(int64_t)row * Dp + d];
+        sq += e * e;
+      }
+    for (int o = 16; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 32);
+    const float inv_s2 = 1.0f / (a.sigma * a.sigma);
+    const float logp = -(float)D * logf(a.sigma) - 0.5f * (float)D * 1.8378770664093453f - 0.5f * sq * inv_s2;  // ln(2 pi)
+    const float ratio = expf(logp - logp_old);
     const float rc = fminf(fmaxf(ratio, 1.0f - a.clip), 1.0f + a.clip);
     const float s1 = ratio * A, s2 = rc * A;
     const bool live = s1 <= s2;
-    for (int d = sub; d < a.D; d += 32) {
-      const float m = a.mu[(int64_t)b * a.D + d];
-      const float e = a.act[r * a.D + d] - m;
-      const float dmu = live ? -(ratio * A * e * inv_s2) * inv_b : 0.0f;
-      a.dz_actor[(int64_t)b * a.D + d] = dmu * (1.0f - m * m);
+    for (int d = sub; d < D; d += 32) {
+      float dz = 0.0f;
+      if (b < B) {
+        const float m = mu[(int64_t)row * Dp + d];
+        const float e = (d < 32 ? act0 : a.act[r * D + d]) - m;
+        dz = (live ? -(ratio * A * e * inv_s2) * inv_b : 0.0f) * (1.0f - m * m);
+        a.dz3[0][(int64_t)b * D + d] = dz;
+      }
+      if (MU_LDS) mu[(int64_t)row * Dp + d] = dz;
     }
-    const float err = a.v[b] - a.ret[r];
-    if (sub == 0) {
+    if (sub == 0 && b < B) {
       st[0] = -(live ? s1 : s2) * inv_b;
-      st[1] = 0.5f * err * err * inv_b;
       st[2] = live ? 0.0f : inv_b;
       st[3] = ratio * inv_b;
-      a.dz_critic[b] = a.value_coef * err * inv_b;
+    }
+    }
+    if (!MU_LDS) __threadfence_block();
+    __syncthreads();
+    // dz2 = (dz3 W3') (1 - h2^2): feature tiles of 16 dealt out to the wavefronts
+    const float *dz = MU_LDS ? mu : a.dz3[net] + (int64_t)b0 * D;
+    const float *dzrow = dz + (int64_t)(MU_LDS ? j : min(b0 + j, B - 1) - b0) * Dp;
+    for (int t0 = w; t0 < Hd / 16; t0 += PT * kHeadWaves) {
+      if (t0 != w) request(t0);
+#pragma unroll
+      for (int p = 0; p < PT; ++p) {
+        const int t = t0 + kHeadWaves * p;
+        if (t < Hd / 16) {
+          f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+          for (int c = 0; c < 8; ++c) {
+            const int d = 4 * c + q;
+            const float x = dzrow[min(d, D - 1)];
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(d < D ? x : 0.0f, d < D ? yw[p][c] : 0.0f, acc, 0, 0, 0);
+          }
+          for (int d0 = 32; d0 < D; d0 += 32) {
+            float x[8], y[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+              const int d = d0 + 4 * c + q, dc = min(d, D - 1);
+              x[c] = dzrow[dc], y[c] = W3[(int64_t)(16 * t + j) * D + dc];
+              if (d >= D) x[c] = 0.0f, y[c] = 0.0f;
+            }
+#pragma unroll
+            for (int c = 0; c < 8; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c], y[c], acc, 0, 0, 0);
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int bb = b0 + 4 * q + i;
+            if (bb < B) a.dz2[net][bb * ld + 16 * t + j] = acc[i] * (1.0f - hv[p][i] * hv[p][i]);
+          }
+        }
+      }
     }
   }
   if (sub == 0)
-    for (int i = 0; i < 4; ++i) red[grp][i] = st[i];
+    for (int i = 0; i < 4; ++i) s_red[row * 4 + i] = st[i];
   __syncthreads();
-  if (threadIdx.x < 4) {
+  if (tid < 4 && (tid == 1) == (net == 1)) {
     float t = 0.0f;
-    for (int g = 0; g < 8; ++g) t += red[g][threadIdx.x];
-    a.partial[(int64_t)blockIdx.x * 4 + threadIdx.x] = t;
+    for (int g = 0; g < kHeadRows; ++g) t += s_red[g * 4 + tid];
+    a.partial[(int64_t)blockIdx.x * 4 + tid] = t;
   }
 }
 
-// stats[i] = sum over blocks of partial[block][i]: 64 lanes stride the blocks, then a fixed-shape tree
-__global__ __launch_bounds__(256) void ppo_stats_kernel(int blocks, const float *__restrict__ partial,
-                                                        float *__restrict__ stats) {
-  __shared__ float red[4][64];
-  const int i = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  float s = 0.0f;
-  for (int k = lane; k < blocks; k += 64) s += partial[(int64_t)k * 4 + i];
-  red[i][lane] = s;
-  __syncthreads();
-  for (int o = 32; o > 0; o >>= 1) {
-    if (lane < o) red[i][lane] += red[i][lane + o];
-    __syncthreads();
-  }
-  if (lane == 0) stats[i] = red[i][0];
-}
-
-struct AdamSeg {
-  float *theta, *m, *v;
-  const float *g;
+// ------------------------------------------------------------------ sums of the split gradients, Adam
+struct FinishSeg {
+  float *g;                 // gradient: the first split's part, completed here
+  const float *part;        // later parts, seg_stride floats apart
+  float *theta, *m, *v;     // Adam (theta null: gradients only)
   int64_t n;
 };
-struct AdamBatch {
-  AdamSeg seg[12];
+constexpr int kSegCriticB3 = 11;  // (tensors in the order W1 b1 W2 b2 W3 b3, actor first)
+struct FinishArgs {
+  FinishSeg seg[12];
+  int64_t seg_stride[12];
+  int32_t later;            // number of later parts
+  float lr, b1, b2, eps, inv_c1, inv_c2;
+  const float *partial;     // [blocks][4]
+  int32_t blocks;
+  float *stats;             // or null
+  const float *dz_value;    // [batch]
+  int32_t batch;
 };
 
-// blockIdx.y = tensor
-__global__ __launch_bounds__(256) void adam_batch_kernel(AdamBatch t, float lr, float b1, float b2, float eps,
-                                                         float inv_c1, float inv_c2) {
-  const AdamSeg s = t.seg[blockIdx.y];
+__device__ inline void adam_element(float g, float *theta, float *m, float *v, float lr, float b1, float b2, float eps,
+                                    float inv_c1, float inv_c2) {
+  const float mi = b1 * *m + (1.0f - b1) * g;
+  const float vi = b2 * *v + (1.0f - b2) * g * g;
+  *m = mi;
+  *v = vi;
+  *theta -= lr * (mi * inv_c1) / (sqrtf(vi * inv_c2) + eps);
+}
+
+// blockIdx.y = tensor; 12: the statistics (64 lanes stride the blocks, then a fixed-shape tree)
+__global__ __launch_bounds__(256) void finish_kernel(FinishArgs a) {
+  if (blockIdx.y == 12) {
+    if (blockIdx.x != 0 || !a.stats) return;
+    __shared__ float red[4][64];
+    const int i = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    float s = 0.0f;
+    for (int k = lane; k < a.blocks; k += 64) s += a.partial[(int64_t)k * 4 + i];
+    red[i][lane] = s;
+    __syncthreads();
+    for (int o = 32; o > 0; o >>= 1) {
+      if (lane < o) red[i][lane] += red[i][lane + o];
+      __syncthreads();
+    }
+    if (lane == 0) a.stats[i] = red[i][0];
+    return;
+  }
+  if (blockIdx.y == kSegCriticB3) {
+    // The one gradient that is a single number: the sum of the value head's dz over the batch, where terms of either
+    // sign cancel and the order of the sum shows.  Up to 64 chunks of the batch, four interleaved sums each, added up
+    // chunk by chunk.
+    if (blockIdx.x != 0) return;
+    __shared__ float s_sum[64][4];
+    const int chunks = min(64, (a.batch + 127) / 128), per = (a.batch + chunks - 1) / chunks;
+    const int c = threadIdx.x >> 2, q = threadIdx.x & 3;
+    float g = 0.0f;
+    if (c < chunks) {
+      const int b1 = min(a.batch, (c + 1) * per);
+#pragma unroll 8
+      for (int b = c * per + q; b < b1; b += 4) g += a.dz_value[b];
+    }
+    s_sum[c][q] = g;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      g = 0.0f;
+      for (int z = 0; z < chunks; ++z) {
+        const float t = (s_sum[z][0] + s_sum[z][1]) + (s_sum[z][2] + s_sum[z][3]);
+        g = z == 0 ? t : g + t;
+      }
+      const FinishSeg s = a.seg[kSegCriticB3];
+      if (s.theta) adam_element(g, s.theta, s.m, s.v, a.lr, a.b1, a.b2, a.eps, a.inv_c1, a.inv_c2);
+      else *s.g = g;
+    }
+    return;
+  }
+  const FinishSeg s = a.seg[blockIdx.y];
+  const int64_t stride = a.seg_stride[blockIdx.y];
+  if (a.later == 0 && !s.theta) return;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < s.n; i += (int64_t)gridDim.x * 256) {
-    const float gi = s.g[i];
-    const float mi = b1 * s.m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * s.v[i] + (1.0f - b2) * gi * gi;
-    s.m[i] = mi;
-    s.v[i] = vi;
-    s.theta[i] -= lr * (mi * inv_c1) / (sqrtf(vi * inv_c2) + eps);
+    float g = s.g[i];
+    for (int z = 0; z < a.later; ++z) g += s.part[z * stride + i];
+    if (s.theta)
+      adam_element(g, s.theta + i, s.m + i, s.v + i, a.lr, a.b1, a.b2, a.eps, a.inv_c1, a.inv_c2);
+    else
+      s.g[i] = g;
   }
 }
 
@@ -344,78 +879,7 @@ __global__ __launch_bounds__(256) void adam_kernel(int64_t n, float *__restrict_
                                                    float *__restrict__ m, float *__restrict__ v, float lr, float b1,
                                                    float b2, float eps, float inv_c1, float inv_c2) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    theta[i] -= lr * (mi * inv_c1) / (sqrtf(vi * inv_c2) + eps);
-  }
-}
-
-template <int TM, int GK>
-void launch_gemm(hipStream_t st, const dim3 &grid, const GemmArgs &g, bool va, bool vb) {
-  if (va && vb)
-    hipLaunchKernelGGL((gemm_f32_kernel<TM, GK, true, true>), grid, dim3(256), 0, st, g);
-  else if (va)
-    hipLaunchKernelGGL((gemm_f32_kernel<TM, GK, true, false>), grid, dim3(256), 0, st, g);
-  else if (vb)
-    hipLaunchKernelGGL((gemm_f32_kernel<TM, GK, false, true>), grid, dim3(256), 0, st, g);
-  else
-    hipLaunchKernelGGL((gemm_f32_kernel<TM, GK, false, false>), grid, dim3(256), 0, st, g);
-}
-
-// may an operand be staged with 16-byte loads?  ks / ms: strides along k and along m (or n); mn_lim, K: extents
-bool vec_ok(const float *p, int64_t ks, int64_t ms, int mn_lim, int K, int k_valid, int k_chunk) {
-  if (reinterpret_cast<uintptr_t>(p) & 15u) return false;
-  if (ks == 1) return ms % 4 == 0 && K % 4 == 0 && k_valid % 4 == 0 && k_chunk % 4 == 0;
-  if (ms == 1) return ks % 4 == 0 && mn_lim % 4 == 0 && mn_lim >= 4;
-  return false;
-}
-
-// splitk: scratch for partial products when the k range is split (weight gradients: k is the batch, the output
-// is small), NULL to forbid splitting.  Tiles of 128 when they still fill the chip, else 64.
-hipError_t gemm(hipStream_t st, GemmArgs g, float *splitk = nullptr, size_t splitk_floats = 0) {
-  if (!g.a_m_phys) g.a_m_phys = g.M;
-  if (!g.b_k_valid) g.b_k_valid = g.K;
-  const int64_t tiles128 = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
-  const int TM = tiles128 >= 256 ? 128 : 64;
-  const int64_t tiles = (int64_t)((g.M + TM - 1) / TM) * ((g.N + TM - 1) / TM);
-  int splits = 1;
-  if (splitk && g.epi == EPI_NONE && tiles < 256 && g.K >= 512) {
-    splits = (int)((512 + tiles - 1) / tiles);
-    if (splits > 32) splits = 32;
-    while (splits > 1 && (g.K / splits < 128 || (size_t)splits * g.M * g.N > splitk_floats)) --splits;
-  }
-  float *out = g.C;
-  g.k_splits = splits;
-  g.k_chunk = splits > 1 ? ((g.K + splits - 1) / splits + 63) / 64 * 64 : g.K;
-  if (splits > 1) g.C = splitk;
-  const bool va = vec_ok(g.A, g.a_cs, g.a_rs, g.a_m_phys, g.K, g.K, g.k_chunk);
-  const bool vb = vec_ok(g.B, g.b_rs, g.b_cs, g.N, g.K, g.b_k_valid, g.k_chunk);
-  const dim3 grid((unsigned)((g.N + TM - 1) / TM), (unsigned)((g.M + TM - 1) / TM), (unsigned)splits);
-  if (TM == 128)
-    launch_gemm<128, 16>(st, grid, g, va, vb);
-  else
-    launch_gemm<64, 32>(st, grid, g, va, vb);
-  if (splits > 1) {
-    const int64_t n = (int64_t)g.M * g.N;
-    hipLaunchKernelGGL(reduce_splits_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, splits, splitk, out);
-  }
-  return hipGetLastError();
-}
-
-hipError_t colsum(hipStream_t st, int B, int N, const float *dZ, float *gb, float *scratch, size_t scratch_floats) {
-  const int chunks = colsum_chunks(B), per = (B + chunks - 1) / chunks;
-  if ((size_t)chunks * N > scratch_floats) return hipErrorInvalidValue;
-  float *dst = chunks > 1 ? scratch : gb;
-  hipLaunchKernelGGL(colsum_kernel, dim3((unsigned)((N + 63) / 64), (unsigned)chunks), dim3(256), 0, st, B, N, per, dZ,
-                     dst);
-  if (chunks > 1)
-    hipLaunchKernelGGL(reduce_splits_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, (int64_t)N, chunks,
-                       scratch, gb);
-  return hipGetLastError();
+  if (i < n) adam_element(g[i], theta + i, m + i, v + i, lr, b1, b2, eps, inv_c1, inv_c2);
 }
 
 #define LRN(x)                      \
@@ -424,126 +888,217 @@ hipError_t colsum(hipStream_t st, int B, int N, const float *dZ, float *gb, floa
     if (e_ != hipSuccess) return e_; \
   } while (0)
 
-struct Scratch {
-  float *xp;               // [B, Sp] gathered minibatch observations, zero-padded to Sp = 4 ceil(S / 4) columns
-  float *h1[2], *h2[2];    // hidden activations of the actor [0] and the critic [1]
-  float *out, *dz3, *dz2, *dz1, *v, *dzc, *partial, *splitk;
-  size_t splitk_floats;
+size_t align256(size_t x) { return (x + 255) / 256 * 256; }
+
+// ------------------------------------------------------------------ scratch
+constexpr size_t kStaticScratchBytes = (size_t)24 << 20;
+
+struct Plan {
+  bool together;   // both networks in every launch; else one after the other, sharing the dz buffers
+  bool padded;     // activation rows, and a copy of W2, end in 32 unused floats (see row_floats)
+  int splits;      // k splits of the weight gradients
+  size_t bytes;
 };
 
-// forward of network `net` (0 actor, 1 critic) with kept activations
-hipError_t net_forward(hipStream_t st, int B, int S, int Sp, int Hd, int O, bool out_tanh, int net,
-                       const pr_net_params &p, const Scratch &w, float *out) {
-  GemmArgs g{};
-  g.A = w.xp, g.a_rs = Sp, g.a_cs = 1, g.B = p.W1, g.b_rs = Hd, g.b_cs = 1, g.C = w.h1[net], g.M = B, g.N = Hd;
-  g.K = Sp, g.b_k_valid = S, g.bias = p.b1, g.epi = EPI_BIAS_TANH;
-  LRN(gemm(st, g));
-  g = GemmArgs{};
-  g.A = w.h1[net], g.a_rs = Hd, g.a_cs = 1, g.B = p.W2, g.b_rs = Hd, g.b_cs = 1, g.C = w.h2[net], g.M = B, g.N = Hd;
-  g.K = Hd, g.bias = p.b2, g.epi = EPI_BIAS_TANH;
-  LRN(gemm(st, g));
-  g = GemmArgs{};
-  g.A = w.h2[net], g.a_rs = Hd, g.a_cs = 1, g.B = p.W3, g.b_rs = O, g.b_cs = 1, g.C = out, g.M = B, g.N = O, g.K = Hd;
-  g.bias = p.b3, g.epi = out_tanh ? EPI_BIAS_TANH : EPI_BIAS;
-  return gemm(st, g);
+// A tile reads 64 rows of a few cache lines each.  Rows of 512 floats are 2 KiB apart: all of a tile's lines then fall
+// on a handful of L2 channels and L1 sets (measured: 25 us for a product that takes 13 us with rows of 544).
+int row_floats(int Hd, bool padded) { return padded ? Hd + 32 : Hd; }
+bool wants_padding(int Hd) { return Hd % 128 == 0; }
+
+int64_t net_params(int S, int Hd, int O) { return (int64_t)(S + 1) * Hd + (int64_t)(Hd + 1) * Hd + (int64_t)(Hd + 1) * O; }
+
+size_t plan_bytes(int B, int Hd, int D, int S, const Plan &p) {
+  const size_t f = 4, ld = row_floats(Hd, p.padded);
+  size_t t = (p.together ? 8 : 6) * align256((size_t)B * ld * f) + align256((size_t)B * D * f) + align256((size_t)B * f) +
+             align256((size_t)((B + kHeadRows - 1) / kHeadRows) * 4 * f);
+  if (p.padded) t += 2 * align256((size_t)Hd * ld * f);
+  if (D > kHeadLdsD) t += align256((size_t)B * (D + 1) * f);
+  const int64_t n = net_params(S, Hd, D) + net_params(S, Hd, 1);
+  return t + align256((size_t)(p.splits - 1) * n * f);
 }
 
-// backward from dz3 = d loss / d (last pre-activation) to the six gradient tensors
-hipError_t net_backward(hipStream_t st, int B, int S, int Sp, int Hd, int O, int net, const pr_net_params &p,
-                        const Scratch &w, const float *dz3, const pr_net_params &grad) {
-  const float *h1 = w.h1[net], *h2 = w.h2[net];
-  GemmArgs g{};
-  // gW3 = H2^T dZ3, gb3
-  g.A = h2, g.a_rs = 1, g.a_cs = Hd, g.B = dz3, g.b_rs = O, g.b_cs = 1, g.C = grad.W3, g.M = Hd, g.N = O, g.K = B;
-  LRN(gemm(st, g, w.splitk, w.splitk_floats));
-  LRN(colsum(st, B, O, dz3, grad.b3, w.splitk, w.splitk_floats));
-  // dZ2 = (dZ3 W3^T) (1 - H2^2)
-  g = GemmArgs{};
-  g.A = dz3, g.a_rs = O, g.a_cs = 1, g.B = p.W3, g.b_rs = 1, g.b_cs = O, g.C = w.dz2, g.M = B, g.N = Hd, g.K = O;
-  g.aux = h2, g.epi = EPI_DTANH;
-  LRN(gemm(st, g));
-  // gW2 = H1^T dZ2, gb2
-  g = GemmArgs{};
-  g.A = h1, g.a_rs = 1, g.a_cs = Hd, g.B = w.dz2, g.b_rs = Hd, g.b_cs = 1, g.C = grad.W2, g.M = Hd, g.N = Hd, g.K = B;
-  LRN(gemm(st, g, w.splitk, w.splitk_floats));
-  LRN(colsum(st, B, Hd, w.dz2, grad.b2, w.splitk, w.splitk_floats));
-  // dZ1 = (dZ2 W2^T) (1 - H1^2)
-  g = GemmArgs{};
-  g.A = w.dz2, g.a_rs = Hd, g.a_cs = 1, g.B = p.W2, g.b_rs = 1, g.b_cs = Hd, g.C = w.dz1, g.M = B, g.N = Hd, g.K = Hd;
-  g.aux = h1, g.epi = EPI_DTANH;
-  LRN(gemm(st, g));
-  // gW1 = X^T dZ1 (the padded rows of X^T are read, their products are never stored), gb1
-  g = GemmArgs{};
-  g.A = w.xp, g.a_rs = 1, g.a_cs = Sp, g.a_m_phys = Sp, g.B = w.dz1, g.b_rs = Hd, g.b_cs = 1, g.C = grad.W1, g.M = S;
-  g.N = Hd, g.K = B;
-  LRN(gemm(st, g, w.splitk, w.splitk_floats));
-  LRN(colsum(st, B, Hd, w.dz1, grad.b1, w.splitk, w.splitk_floats));
+// The weight gradients' k (the batch) is split until a workgroup walks about 512 samples, or until there are 256
+// workgroups.  Shapes that fit the fixed scratch of the no-allocation call one way or another stay inside it: fewer
+// splits first, then unpadded rows, then the two networks one after the other (six instead of eight activation-sized
+// buffers: what that call has always needed at most).
+Plan make_plan(int B, int Hd, int D, int S) {
+  const int64_t tiles = (int64_t)((Hd + 63) / 64) * (((S + 63) / 64) + (Hd + 63) / 64) * 2;
+  int64_t want = (B + 511) / 512;
+  if (tiles * want < 256) want = std::min<int64_t>((B + 127) / 128, (256 + tiles - 1) / tiles);
+  want = std::max<int64_t>(1, std::min<int64_t>(want, 32));
+  Plan best{true, wants_padding(Hd), (int)want, 0};
+  best.bytes = plan_bytes(B, Hd, D, S, best);
+  if (best.bytes <= kStaticScratchBytes) return best;
+  for (int i = 0; i < 3; ++i) {
+    Plan q{i < 2, i == 0 && best.padded, 1, 0};
+    if (plan_bytes(B, Hd, D, S, q) > kStaticScratchBytes) continue;
+    for (q.splits = (int)want; (q.bytes = plan_bytes(B, Hd, D, S, q)) > kStaticScratchBytes; --q.splits) {}
+    return q;
+  }
+  return best;
+}
+
+// C = products of `set`: fills in the tiling and launches
+hipError_t launch_products(hipStream_t st, ProbSet &set) {
+  int64_t waves = 0;
+  for (int i = 0; i < set.n; ++i) {
+    Prob &p = set.p[i];
+    p.tiles_n = (p.N + kTile - 1) / kTile;
+    const int64_t tiles = (int64_t)((p.M + kTile - 1) / kTile) * p.tiles_n;
+    if (tiles * p.splits > (1 << 30)) return hipErrorInvalidValue;
+    p.tiles = (int32_t)tiles;
+    p.k_chunk = p.splits > 1 ? ((p.K + p.splits - 1) / p.splits + 31) / 32 * 32 : p.K;
+    waves += tiles * p.splits;
+  }
+  // a wavefront per tile when that gives most SIMDs one
+  const bool own = waves >= kOwnTiles;
+  int32_t next = 0;
+  for (int i = 0; i < set.n; ++i) {
+    Prob &p = set.p[i];
+    const int64_t wg = own ? ((int64_t)p.tiles * p.splits + 3) / 4 : (int64_t)p.tiles * p.splits;
+    p.first_block = next;
+    p.blocks = (int32_t)((wg + 7) / 8 * 8);
+    next += p.blocks;
+  }
+  if (own) {
+    hipLaunchKernelGGL(products_kernel<1>, dim3((unsigned)next), dim3(256), 0, st, set);
+  } else {
+    LRN(allow_full_lds<products_kernel<8>>());
+    hipLaunchKernelGGL(products_kernel<8>, dim3((unsigned)next), dim3(512), products_lds(8), st, set);
+  }
   return hipGetLastError();
 }
 
-size_t align256(size_t x) { return (x + 255) / 256 * 256; }
-
 }  // namespace
 
-// partial products of a split weight gradient: up to 8 copies of the largest (Hd x Hd; S <= 2 Hd assumed else fewer splits)
-static size_t splitk_floats(int Hd) {
-  const size_t a = (size_t)8 * Hd * Hd, b = (size_t)CS_MAX_CHUNKS * Hd;  // split products / column-sum chunks
-  return a > b ? a : b;
-}
+size_t ppo_scratch_bytes(int B, int Hd, int D, int S) { return make_plan(B, Hd, D, S).bytes; }
 
-size_t ppo_scratch_bytes(int B, int Hd, int D, int S) {
-  const size_t f = 4, Sp = (size_t)(S + 3) / 4 * 4;
-  return align256((size_t)B * Sp * f) + 4 * align256((size_t)B * Hd * f) + 2 * align256((size_t)B * D * f) +
-         2 * align256((size_t)B * Hd * f) + 2 * align256((size_t)B * f) + align256((size_t)((B + 7) / 8) * 4 * f) +
-         align256(splitk_floats(Hd) * f);
-}
-
-hipError_t launch_ppo_grads(hipStream_t st, const pr_ppo_config &c, const float *obs, const float *act,
-                            const float *logp_old, const float *adv, const float *ret, const int32_t *rows,
-                            const pr_net_params &actor, const pr_net_params &critic, const pr_net_params &ga,
-                            const pr_net_params &gc, void *scratch, float *stats) {
-  const int B = c.batch, D = c.n_stocks, Hd = c.hidden, S = 1 + 2 * D + D * c.n_ind, Sp = (S + 3) / 4 * 4;
-  unsigned char *p = static_cast<unsigned char *>(scratch);
-  auto take = [&](size_t bytes) {
-    float *r = reinterpret_cast<float *>(p);
-    p += align256(bytes);
+hipError_t launch_ppo(hipStream_t st, const pr_ppo_config &c, const float *obs, const float *act, const float *logp_old,
+                      const float *adv, const float *ret, const int32_t *rows, const pr_net_params &actor,
+                      const pr_net_params &critic, const pr_net_params &ga, const pr_net_params &gc,
+                      const PpoAdam *adam, void *scratch, float *stats) {
+  const int B = c.batch, D = c.n_stocks, Hd = c.hidden, S = 1 + 2 * D + D * c.n_ind;
+  const Plan plan = make_plan(B, Hd, D, S);
+  unsigned char *sp = static_cast<unsigned char *>(scratch);
+  auto take = [&](size_t floats) {
+    float *r = reinterpret_cast<float *>(sp);
+    sp += align256(floats * 4);
     return r;
   };
-  Scratch w;
-  w.xp = take((size_t)B * Sp * 4);
-  for (int net = 0; net < 2; ++net) {
-    w.h1[net] = take((size_t)B * Hd * 4);
-    w.h2[net] = take((size_t)B * Hd * 4);
+  const int ld = row_floats(Hd, plan.padded);
+  const size_t act_floats = (size_t)B * ld;
+  float *h1[2], *h2[2], *dz2[2], *dz1[2], *dz3[2];
+  for (int i = 0; i < 2; ++i) h1[i] = take(act_floats), h2[i] = take(act_floats);
+  for (int i = 0; i < 2; ++i) {
+    dz2[i] = i == 0 || plan.together ? take(act_floats) : dz2[0];
+    dz1[i] = i == 0 || plan.together ? take(act_floats) : dz1[0];
   }
-  w.out = take((size_t)B * D * 4);
-  w.dz3 = take((size_t)B * D * 4);
-  w.dz2 = take((size_t)B * Hd * 4);
-  w.dz1 = take((size_t)B * Hd * 4);
-  w.v = take((size_t)B * 4);
-  w.dzc = take((size_t)B * 4);
-  const int blocks = (B + 7) / 8;
-  w.partial = take((size_t)blocks * 4 * 4);
-  w.splitk_floats = splitk_floats(Hd);
-  w.splitk = take(w.splitk_floats * 4);
-  // gather once, both forwards (each network keeps its own activations), the loss, both backward passes
-  hipLaunchKernelGGL(gather_pad_kernel, dim3((unsigned)((B + 3) / 4)), dim3(256), 0, st, B, S, Sp, obs, rows, w.xp);
-  LRN(net_forward(st, B, S, Sp, Hd, 1, false, 1, critic, w, w.v));
-  LRN(net_forward(st, B, S, Sp, Hd, D, true, 0, actor, w, w.out));
-  LossArgs l;
-  l.B = B, l.D = D, l.mu = w.out, l.v = w.v, l.act = act, l.logp_old = logp_old, l.adv = adv, l.ret = ret, l.rows = rows;
-  l.sigma = c.sigma, l.clip = c.clip, l.value_coef = c.value_coef, l.dz_actor = w.dz3, l.dz_critic = w.dzc;
-  l.partial = w.partial;
-  hipLaunchKernelGGL(ppo_loss_kernel, dim3(blocks), dim3(256), 0, st, l);
-  if (stats) hipLaunchKernelGGL(ppo_stats_kernel, dim3(1), dim3(256), 0, st, blocks, w.partial, stats);
-  LRN(net_backward(st, B, S, Sp, Hd, D, 0, actor, w, w.dz3, ga));
-  LRN(net_backward(st, B, S, Sp, Hd, 1, 1, critic, w, w.dzc, gc));
+  float *w2[2] = {nullptr, nullptr};
+  if (plan.padded) w2[0] = take((size_t)Hd * ld), w2[1] = take((size_t)Hd * ld);
+  dz3[0] = take((size_t)B * D), dz3[1] = take(B);
+  const int blocks = (B + kHeadRows - 1) / kHeadRows;
+  float *partial = take((size_t)blocks * 4);
+  float *mu = D > kHeadLdsD ? take((size_t)B * (D + 1)) : nullptr;
+  float *part = take(0);
+
+  const pr_net_params *net[2] = {&actor, &critic}, *grad[2] = {&ga, &gc};
+  const int out[2] = {D, 1};
+  // later parts of the weight gradients: per network and layer [splits - 1][M + 1][N]
+  float *parts[2][3];
+  const int gm[3] = {S, Hd, Hd};
+  for (int i = 0; i < 2; ++i)
+    for (int l = 0; l < 3; ++l) {
+      parts[i][l] = part;
+      part += (size_t)(plan.splits - 1) * (gm[l] + 1) * (l < 2 ? Hd : out[i]);
+    }
+  auto input_grad = [&](int i) {
+    Prob p{};
+    p.kind = DZ, p.M = B, p.N = Hd, p.K = Hd, p.A = dz2[i], p.lda = ld, p.splits = 1, p.ldc = ld;
+    p.B = plan.padded ? w2[i] : net[i]->W2, p.ldb = ld;
+    p.aux = h1[i], p.C = dz1[i];
+    return p;
+  };
+  auto weight_grad = [&](int i, int layer) {
+    Prob p{};
+    p.kind = DW, p.M = gm[layer], p.N = layer < 2 ? Hd : out[i], p.K = B, p.splits = plan.splits, p.part = parts[i][layer];
+    if (layer == 0)
+      p.A = obs, p.lda = S, p.gather = rows, p.B = dz1[i], p.C = grad[i]->W1, p.colsum = grad[i]->b1;
+    else if (layer == 1)
+      p.A = h1[i], p.lda = ld, p.B = dz2[i], p.C = grad[i]->W2, p.colsum = grad[i]->b2;
+    else
+      p.A = h2[i], p.lda = ld, p.B = dz3[i], p.C = grad[i]->W3, p.colsum = grad[i]->b3;
+    p.ldb = layer < 2 ? ld : p.N, p.ldc = p.N;
+    return p;
+  };
+  for (int layer = 0; layer < 2; ++layer) {
+    FwdArgs f{};
+    f.gather = layer == 0 ? rows : nullptr, f.M = B, f.N = Hd, f.ldc = ld;
+    for (int i = 0; i < 2; ++i) {
+      FwdProb &p = f.p[i];
+      if (layer == 0) p.A = obs, p.lda = S, p.K = S, p.W = net[i]->W1, p.bias = net[i]->b1, p.C = h1[i];
+      else p.A = h1[i], p.lda = ld, p.K = Hd, p.W = net[i]->W2, p.bias = net[i]->b2, p.C = h2[i];
+      f.copy_src[i] = net[i]->W2, f.copy_dst[i] = w2[i];
+    }
+    f.copy_rows = layer == 1 && plan.padded ? Hd : 0;
+    f.tiles_n = (Hd + 63) / 64;
+    // 32-row tiles while 64-row ones would leave compute units without two workgroups
+    const int TM = 2 * (int64_t)((B + 63) / 64) * f.tiles_n >= 512 ? 64 : 32;
+    f.tiles = (B + TM - 1) / TM * f.tiles_n;
+    const dim3 grid((unsigned)((f.tiles + 7) / 8 * 8 + (f.copy_rows + 7) / 8), 2);
+    if (TM == 64) hipLaunchKernelGGL(forward_kernel<64>, grid, dim3(512), 0, st, f);
+    else hipLaunchKernelGGL(forward_kernel<32>, grid, dim3(512), 0, st, f);
+    LRN(hipGetLastError());
+  }
+  ProbSet set{};
+  HeadArgs h{};
+  h.B = B, h.D = D, h.Hd = Hd, h.act = act, h.logp_old = logp_old, h.adv = adv, h.ret = ret, h.rows = rows;
+  h.ld = ld, h.sigma = c.sigma, h.clip = c.clip, h.value_coef = c.value_coef, h.mu = mu, h.partial = partial;
+  for (int i = 0; i < 2; ++i)
+    h.h2[i] = h2[i], h.W3[i] = net[i]->W3, h.b3[i] = net[i]->b3, h.dz3[i] = dz3[i], h.dz2[i] = dz2[i];
+  for (int pass = 0; pass < (plan.together ? 1 : 2); ++pass) {
+    h.net0 = pass;
+    const dim3 grid((unsigned)blocks, plan.together ? 2 : 1);
+    auto launch = [&](auto kern, int slice, hipError_t e) {
+      const size_t lds = (slice + 16 * 4 + (D <= kHeadLdsD ? 16 * (size_t)(D | 1) : 0)) * 4;
+      if (e == hipSuccess) hipLaunchKernelGGL(kern, grid, dim3(64 * kHeadWaves), lds, st, h);
+      return e != hipSuccess ? e : hipGetLastError();
+    };
+    if (D <= 32) LRN(launch(head_kernel<true, 32, 128>, head_slice(32, 128), allow_full_lds<head_kernel<true, 32, 128>>()));
+    else if (D <= kHeadLdsD) LRN(launch(head_kernel<true, 128, 32>, head_slice(128, 32), allow_full_lds<head_kernel<true, 128, 32>>()));
+    else LRN(launch(head_kernel<false, 128, 32>, head_slice(128, 32), hipSuccess));
+    set.n = 0;
+    for (int i = pass; i < (plan.together ? 2 : pass + 1); ++i) set.p[set.n++] = input_grad(i), set.p[set.n++] = weight_grad(i, 1);
+    LRN(launch_products(st, set));
+    set.n = 0;
+    for (int i = pass; i < (plan.together ? 2 : pass + 1); ++i) set.p[set.n++] = weight_grad(i, 0), set.p[set.n++] = weight_grad(i, 2);
+    LRN(launch_products(st, set));
+  }
+  FinishArgs f{};
+  f.later = plan.splits - 1, f.partial = partial, f.blocks = blocks, f.stats = stats, f.dz_value = dz3[1], f.batch = B;
+  int64_t nmax = 1;
+  for (int i = 0; i < 2; ++i)
+    for (int t = 0; t < 6; ++t) {
+      const int l = t / 2, N = l < 2 ? Hd : out[i];
+      FinishSeg &s = f.seg[6 * i + t];
+      s.g = (&grad[i]->W1)[t];
+      s.n = t % 2 == 0 ? (int64_t)gm[l] * N : N;
+      s.part = parts[i][l] + (t % 2 == 0 ? 0 : (int64_t)gm[l] * N);
+      f.seg_stride[6 * i + t] = (int64_t)(gm[l] + 1) * N;
+      if (adam) s.theta = (&net[i]->W1)[t], s.m = (&adam->m[i]->W1)[t], s.v = (&adam->v[i]->W1)[t];
+      nmax = std::max(nmax, s.n);
+    }
+  if (adam) {
+    const double c1 = 1.0 - pow((double)c.beta1, (double)c.adam_step), c2 = 1.0 - pow((double)c.beta2, (double)c.adam_step);
+    f.lr = c.lr, f.b1 = c.beta1, f.b2 = c.beta2, f.eps = c.adam_eps, f.inv_c1 = (float)(1.0 / c1), f.inv_c2 = (float)(1.0 / c2);
+  }
+  const int64_t bx = plan.splits == 1 && !adam ? 1 : std::min<int64_t>((nmax + 255) / 256, 1024);
+  hipLaunchKernelGGL(finish_kernel, dim3((unsigned)bx, 13), dim3(256), 0, st, f);
   return hipGetLastError();
 }
 
 // ---- the same minibatch for callers that cannot allocate or own a workspace: scratch in a fixed device array
 // (one copy per GPU the library runs on, held until the process ends).  In host code the array's name is only a
 // stand-in for the symbol: its device address is looked up once per device and that pointer is what kernels get.
-constexpr size_t kStaticScratchBytes = (size_t)24 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
@@ -572,23 +1127,7 @@ hipError_t launch_ppo_grads_static(hipStream_t st, const pr_ppo_config &c, const
     g_scratch_ptr[dev].store(ptr, std::memory_order_release);
   }
   // nothing in the scratch has to start at zero: every region is written by this call before it is read
-  return launch_ppo_grads(st, c, obs, act, logp_old, adv, ret, rows, actor, critic, ga, gc, ptr, stats);
-}
-
-hipError_t launch_adam12(hipStream_t st, const int64_t *n, float *const *theta, float *const *g, float *const *m,
-                         float *const *v, float lr, float b1, float b2, float eps, int32_t t) {
-  AdamBatch bt;
-  int64_t nmax = 1;
-  for (int i = 0; i < 12; ++i) {
-    bt.seg[i].theta = theta[i], bt.seg[i].g = g[i], bt.seg[i].m = m[i], bt.seg[i].v = v[i], bt.seg[i].n = n[i];
-    if (n[i] > nmax) nmax = n[i];
-  }
-  const double c1 = 1.0 - pow((double)b1, (double)t), c2 = 1.0 - pow((double)b2, (double)t);
-  int64_t bx = (nmax + 255) / 256;
-  if (bx > 1024) bx = 1024;
-  hipLaunchKernelGGL(adam_batch_kernel, dim3((unsigned)bx, 12), dim3(256), 0, st, bt, lr, b1, b2, eps, (float)(1.0 / c1),
-                     (float)(1.0 / c2));
-  return hipGetLastError();
+  return launch_ppo(st, c, obs, act, logp_old, adv, ret, rows, actor, critic, ga, gc, nullptr, ptr, stats);
 }
 
 hipError_t launch_adam(hipStream_t st, int64_t n, float *theta, const float *g, float *m, float *v, float lr, float b1,

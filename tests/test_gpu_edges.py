@@ -58,3 +58,39 @@ def test_trading_metrics_tiles(T, N, D):
         want = [(V[-1] - V[0]) / V[0], ann, np.sqrt(252.0) * sd, mdd,
                 np.sqrt(252.0) * (r.mean() - 0.01 / 252.0) / sd if sd > 0 else 0.0, ann / mdd if mdd > 0 else 0.0]
         np.testing.assert_allclose(got[:, n], want, rtol=1e-8, atol=1e-11)
+
+
+# the learner's products: rows of three inputs, one k slice and its remainders, one tile of 32 columns, k splits of the
+# weight gradients with a ragged last one, output layers of one, 33 and more columns than the LDS tile of means holds,
+# tiles of 32 and 64 rows, a wavefront per tile and a tile per workgroup
+@pytest.mark.parametrize("B,D,K,Hd", [(1, 1, 0, 32), (17, 1, 1, 64), (65, 33, 1, 96), (700, 5, 2, 64), (2500, 7, 3, 160),
+                                      (4100, 16, 2, 256), (5, 1030, 0, 32), (40, 130, 0, 128), (1024, 30, 8, 512)])
+def test_learner_products_at_their_edges(B, D, K, Hd):
+    w = inputs.WORKLOADS["dow30"].replace(n_stocks=D, n_ind=K, hidden=Hd)
+    rng = np.random.default_rng(B + D)
+    R = B + 37
+    S = w.state_dim
+    nets = {n: {k: v[0] for k, v in inputs.make_weights(w, critic=(n == "critic")).items()} for n in ("actor", "critic")}
+    if S * 0.01 > 3.0:
+        nets = {n: {k: v * np.float32(np.sqrt(300.0 / S)) if k == "W1" else v for k, v in p.items()} for n, p in nets.items()}
+    obs = rng.standard_normal((R, S)).astype(np.float32)
+    a = nets["actor"]
+    mu = oracle.mlp(obs, a["W1"], a["b1"], a["W2"], a["b2"], a["W3"], a["b3"], True, False)
+    act = (mu + w.sigma * rng.standard_normal((R, D))).astype(np.float32)
+    logp = -0.5 * ((act - mu) / w.sigma) ** 2
+    # ratios well away from the clip bounds: which branch of the min() is live is then the same in fp32 and fp64
+    logp_old = (logp.sum(1) - D * (np.log(w.sigma) + 0.5 * np.log(2 * np.pi)) + rng.choice([-0.4, -0.05, 0.1, 0.5], R)).astype(np.float32)
+    adv, ret = rng.standard_normal(R).astype(np.float32), rng.standard_normal(R).astype(np.float32)
+    rows = rng.permutation(R)[:B].astype(np.int32)
+    ga, gc, stats, _ = oracle.ppo_grads(obs[rows], act[rows], logp_old[rows], adv[rows], ret[rows], nets["actor"],
+                                        nets["critic"], w.sigma, 0.2, 0.5)
+    up = lambda net: {k: _t(v) for k, v in net.items()}
+    dga, dgc, dstats = pr.ppo_minibatch_grads(pr.make_ppo_config(w, batch=B), _t(obs), _t(act), _t(logp_old), _t(adv),
+                                              _t(ret), _t(rows), up(nets["actor"]), up(nets["critic"]))
+    torch.cuda.synchronize()
+    tol = parity.TOL_F32 * max(1.0, D / 100.0)     # the ratio sums 2 D errors of the means
+    for want, got in ((ga, dga), (gc, dgc)):
+        for k in oracle.NET_KEYS:
+            err = np.abs(parity.to_np(got[k]) - want[k]).max() / max(np.abs(want[k]).max(), 1e-30)
+            assert err <= tol, (k, err)
+    np.testing.assert_allclose(parity.to_np(dstats), stats, rtol=2e-4, atol=1e-6)
