@@ -22,6 +22,7 @@ struct pr_handle {
   float *b_packed[2][3];
   float *mu_scratch;      // [N, D]
   int32_t *start;         // [N] episode start rows (zeros unless a replay table is set)
+  ObsShadow shadow;       // bf16 observations of the layer-per-launch actor, or null
   float *split;           // activations between the launches of the layer-per-launch actor (small batches), or null
   int32_t S;
 };
@@ -177,6 +178,7 @@ StepIO step_io(const pr_handle *h, const pr_buffers *o, int t, const float *mu, 
   io.reward = o->reward + (size_t)t * N;
   io.done = o->done + (size_t)t * N;
   io.logp = o->logp ? o->logp + (size_t)t * N : nullptr;
+  io.shadow = h->shadow;
   io.shares = o->shares ? o->shares + (size_t)t * N * D : nullptr;
   return io;
 }
@@ -318,7 +320,7 @@ int rollout_step_T(pr_handle *h, int32_t T, const float *noise, const pr_buffers
     POD_HIP(launch_rollout_fused(h->stream, h->cfg, h->dims, h->st, h->market.price, h->market.ind, h->actor_fused,
                                  per_agent, T, noise, nullptr, *out));
   } else {
-    POD_HIP(launch_observe(h->stream, h->dims, h->st, h->market.price, h->market.ind, out->obs));
+    POD_HIP(launch_observe(h->stream, h->dims, h->st, h->market.price, h->market.ind, out->obs, h->shadow));
     for (int t = 0; t < T; ++t) {
       float *mu = out->mu ? out->mu + (size_t)t * N * D : h->mu_scratch;
       POD_HIP(launch_mlp(h->stream, h->actor, (int64_t)N, out->obs + (size_t)t * N * S, (int64_t)S, mu, (int32_t)N,
@@ -343,7 +345,7 @@ int rollout_step_forced(pr_handle *h, int32_t T, const float *mu, const float *n
                                  h->actor_fused, h->cfg.n_envs / h->cfg.n_agents, T, noise, mu, *out));
     return PR_OK;
   }
-  POD_HIP(launch_observe(h->stream, h->dims, h->st, h->market.price, h->market.ind, out->obs));
+  POD_HIP(launch_observe(h->stream, h->dims, h->st, h->market.price, h->market.ind, out->obs, h->shadow));
   for (int t = 0; t < T; ++t)
     POD_HIP(launch_env_step(h->stream, h->dims, h->st, h->market.price, h->market.ind,
                             step_io(h, out, t, mu + (size_t)t * N * D, noise)));

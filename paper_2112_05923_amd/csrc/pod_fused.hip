@@ -215,8 +215,8 @@ __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
     s_cash[lane] = cash;
   }
   for (int idx = tid; idx < E * D; idx += NT) {
-    const int dd = idx / E, e = idx - dd * E;
-    s_h[e * Dp + dd] = a.st.h[(size_t)dd * N + n0 + e];
+    const int e = idx / D, dd = idx - e * D;
+    s_h[e * Dp + dd] = a.st.h[(size_t)n0 * D + idx];
   }
   if (tid < E)
     for (int dd = D; dd < DMAX; ++dd) {
@@ -756,8 +756,8 @@ __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
     a.st.ep_cnt[n] = ep_cnt;
   }
   for (int idx = tid; idx < E * D; idx += NT) {
-    const int dd = idx / E, e = idx - dd * E;
-    a.st.h[(size_t)dd * N + n0 + e] = s_h[e * Dp + dd];
+    const int e = idx / D, dd = idx - e * D;
+    a.st.h[(size_t)n0 * D + idx] = s_h[e * Dp + dd];
   }
 }
 

@@ -32,12 +32,12 @@ inline hipError_t allow_full_lds() {
 }
 
 // ---------------------------------------------------------------- env state
-// Structure-of-arrays env state in the workspace; n is the fastest axis of
-// every array so that a tile of consecutive envs is one contiguous segment.
+// Structure-of-arrays env state in the workspace; a tile of consecutive envs
+// is one contiguous segment of every array.
 struct EnvState {
   float *cash;       // [N]
   int32_t *tau;      // [N]
-  int32_t *h;        // [D][N]
+  int32_t *h;        // [N][D]
   double *ep_ret;    // [N]
   double *ep_sum;    // [N]
   double *ep_sqsum;  // [N]
@@ -52,6 +52,13 @@ struct EnvDims {
   float s_cash, s_price, s_hold, s_ind;
 };
 
+// Observations in bf16 as the layer-per-launch actor reads them: [N][pitch], columns in the order of its rotated first
+// layer [indicators | cash | prices | holdings | zeros].
+struct ObsShadow {
+  uint16_t *p;
+  int32_t pitch, cols;  // elements; columns up to `cols` are read
+};
+
 struct StepIO {
   const float *mu;     // [N, D] policy mean of this step
   const float *noise;  // [N, D]
@@ -61,10 +68,11 @@ struct StepIO {
   uint8_t *done;       // [N]
   float *logp;         // [N] or null
   int32_t *shares;     // [N, D] or null
+  ObsShadow shadow;    // the next observation for the actor, or null
 };
 
 hipError_t launch_observe(hipStream_t st, const EnvDims &d, const EnvState &s, const float *price, const float *ind,
-                          float *obs);
+                          float *obs, const ObsShadow &shadow);
 hipError_t launch_env_step(hipStream_t st, const EnvDims &d, const EnvState &s, const float *price, const float *ind,
                            const StepIO &io);
 hipError_t launch_state_reset(hipStream_t st, const EnvDims &d, const EnvState &s);
@@ -72,7 +80,6 @@ hipError_t launch_check_starts(hipStream_t st, int32_t N, int32_t H, int32_t row
 hipError_t launch_state_copy(hipStream_t st, const EnvDims &d, const EnvState &s, const pr_state &user, bool to_user);
 hipError_t launch_leaderboard(hipStream_t st, int32_t N, int32_t P, const EnvState &s, double *scratch_mean,
                               double *score_mean, double *score_var, int32_t *rank);
-size_t env_step_lds_bytes(const EnvDims &d, int *envs_per_block);
 
 // ---------------------------------------------------------------------- GAE
 // obs_scale: host pointer to the four observation scales.

@@ -94,3 +94,21 @@ def test_learner_products_at_their_edges(B, D, K, Hd):
             err = np.abs(parity.to_np(got[k]) - want[k]).max() / max(np.abs(want[k]).max(), 1e-30)
             assert err <= tol, (k, err)
     np.testing.assert_allclose(parity.to_np(dstats), stats, rtol=2e-4, atol=1e-6)
+
+
+# 16 / 8 / 4 envs per workgroup of the env step, one, two and four stocks per thread, a last workgroup that is not full, no indicators, indicator rows that are no multiple of four floats and ones beyond the prefetched groups;
+# episodes that end inside the rollout, and hardly any cash
+@pytest.mark.parametrize("N,D,K,cash0", [(35, 32, 17, 1e6), (33, 33, 3, 1e6), (16, 64, 1, 4e4), (3, 65, 4, 1e6), (17, 128, 0, 2e4), (9, 129, 1, 1e6), (8, 256, 9, 3e4), (5, 257, 5, 1e6),
+                                         (7, 511, 2, 5e4), (4, 512, 10, 1e6)])
+def test_env_step_tiles(N, D, K, cash0):
+    w = inputs.WORKLOADS["large"].replace(n_envs=N, n_stocks=D, n_ind=K, steps=14, cash0=cash0)
+    d = inputs.make_all(w, horizon=6, n_market=1 if N == 8 else None, steps=14)
+    cfg = pr.make_config(w, horizon=6, n_market=1 if N == 8 else None, schedule=pr.PR_SCHED_STEPWISE)
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    ro = pr.Rollout(cfg, _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+    mu = np.random.default_rng(D).uniform(-1, 1, d["noise"].shape).astype(np.float32)
+    out = ro.alloc_buffers(14, value=False, logp=True, mu=False, shares=True)
+    ro.step_forced(14, _t(mu), _t(d["noise"]), out)
+    torch.cuda.synchronize()
+    rec = {k: parity.to_np(v) for k, v in out.items()}
+    parity.check_env_record(w, oracle.cfg_from_workload(w, horizon=6), rec, d["price"], d["ind"], d["noise"], mu)
