@@ -16,14 +16,14 @@ struct pr_handle {
   EnvState st;
   pr_market market;
   PackedNet actor, critic;
-  PackedNet actor_fused;  // the actor with layer 1 packed in the input order of the persistent rollout kernel
-  void *w1_fused;
+  PackedNet actor_rot;    // the actor with layer 1 packed for inputs in the order [indicators | cash | prices | holdings]
+  void *w1_rot;           // (null when no rollout of this handle reads that order)
   void *w_packed[2][3];   // device, per net and layer
   float *b_packed[2][3];
   float *mu_scratch;      // [N, D]
   int32_t *start;         // [N] episode start rows (zeros unless a replay table is set)
   ObsShadow shadow;       // bf16 observations of the layer-per-launch actor, or null
-  float *split;           // activations between the launches of the layer-per-launch actor (small batches), or null
+  void *split[3];         // hidden activations and input of the layer-per-launch networks (small batches)
   int32_t S;
 };
 
@@ -52,10 +52,15 @@ bool is_pow2_float(float x) {
 
 struct Layout {
   size_t w[2][3], b[2][3];
-  size_t w1_fused;
-  size_t cash, tau, h, ep_ret, ep_sum, ep_sqsum, ep_cnt, mu, start, split;
+  size_t w1_rot;
+  size_t cash, tau, h, ep_ret, ep_sum, ep_sqsum, ep_cnt, mu, start, split[3];
   size_t total;
 };
+
+// the stepwise policy of small bf16 batches reads a bf16 copy of the observations, written along with them
+bool uses_shadow(const pr_config &c) {
+  return c.schedule == PR_SCHED_STEPWISE && layers_supported(c.n_envs, c.hidden, c.mlp_dtype);
+}
 
 int state_dim(const pr_config &c) { return 1 + 2 * c.n_stocks + c.n_stocks * c.n_ind; }
 
@@ -102,7 +107,7 @@ Layout make_layout(const pr_config &c) {
       L.b[net][l] = take((size_t)padded_out(out_dim[l]) * 4 * P);
     }
   }
-  L.w1_fused = c.schedule == PR_SCHED_FUSED ? take(packed_weight_bytes(S, Hd, bf) * P) : 0;
+  L.w1_rot = c.schedule == PR_SCHED_FUSED || uses_shadow(c) ? take(packed_weight_bytes(S, Hd, bf) * P) : 0;
   L.cash = take(N * 4);
   L.tau = take(N * 4);
   L.h = take(N * D * 4);
@@ -112,7 +117,9 @@ Layout make_layout(const pr_config &c) {
   L.ep_cnt = take(N * 4);
   L.mu = take(N * D * 4);
   L.start = take(N * 4);
-  L.split = take((size_t)split_scratch_rows(c.n_envs, Hd) * Hd * 4 * 2);
+  const size_t rows = (size_t)split_scratch_rows(c.n_envs, Hd);
+  for (int i = 0; i < 2; ++i) L.split[i] = take(bf ? rows * layers_pitch(Hd) * 2 : rows * Hd * 4);
+  L.split[2] = take(bf ? rows * layers_pitch(S) * 2 : 0);
   L.total = off;
   return L;
 }
@@ -136,8 +143,10 @@ void fill_net(PackedNet &pn, const pr_handle *h, int net) {
   pn.bf16 = bf;
   pn.out_tanh = net == 0 ? 1 : 0;
   pn.split_rows = split_scratch_rows(c.n_envs, Hd);
-  pn.split_h[0] = pn.split_rows ? h->split : nullptr;
-  pn.split_h[1] = pn.split_rows ? h->split + (size_t)pn.split_rows * Hd : nullptr;
+  for (int i = 0; i < 2; ++i) pn.split_h[i] = pn.split_rows ? h->split[i] : nullptr;
+  pn.split_x.p = pn.split_rows && bf ? static_cast<uint16_t *>(h->split[2]) : nullptr;
+  pn.split_x.pitch = layers_pitch(S);
+  pn.split_x.cols = (S + 15) / 16 * 16;
 }
 
 bool weights_ok(const pr_weights *w) { return w && w->W1 && w->b1 && w->W2 && w->b2 && w->W3 && w->b3; }
@@ -155,10 +164,11 @@ int pack_nets(pr_handle *h, const pr_weights *actor, const pr_weights *critic) {
       POD_HIP(launch_pack_layer(h->stream, W[l], b[l], P, in_dim[l], out_dim[l], bf, 0, h->w_packed[net][l],
                                 h->b_packed[net][l]));
   }
-  // The persistent rollout kernel keeps its observation tile as [indicators | cash | prices | holdings]:
-  // the same layer-1 weights with their rows rotated by the D K indicator columns (biases are shared).
-  if (c.schedule == PR_SCHED_FUSED)
-    POD_HIP(launch_pack_layer(h->stream, actor->W1, actor->b1, P, S, Hd, bf, D * c.n_ind, h->w1_fused,
+  // The persistent rollout kernel keeps its observation tile as [indicators | cash | prices | holdings] (and so does the
+  // bf16 copy of the observations): the same layer-1 weights with their rows rotated by the D K indicator columns
+  // (biases are shared).
+  if (h->w1_rot)
+    POD_HIP(launch_pack_layer(h->stream, actor->W1, actor->b1, P, S, Hd, bf, D * c.n_ind, h->w1_rot,
                               h->b_packed[0][0]));
   return PR_OK;
 }
@@ -168,7 +178,7 @@ int check_buffers(const pr_buffers *o) {
   return PR_OK;
 }
 
-StepIO step_io(const pr_handle *h, const pr_buffers *o, int t, const float *mu, const float *noise) {
+StepIO step_io(const pr_handle *h, const pr_buffers *o, int t, const float *mu, const float *noise, const ObsShadow &shadow) {
   const size_t N = (size_t)h->cfg.n_envs, D = (size_t)h->cfg.n_stocks, S = (size_t)h->S;
   StepIO io;
   io.mu = mu;
@@ -178,7 +188,7 @@ StepIO step_io(const pr_handle *h, const pr_buffers *o, int t, const float *mu, 
   io.reward = o->reward + (size_t)t * N;
   io.done = o->done + (size_t)t * N;
   io.logp = o->logp ? o->logp + (size_t)t * N : nullptr;
-  io.shadow = h->shadow;
+  io.shadow = shadow;
   io.shares = o->shares ? o->shares + (size_t)t * N * D : nullptr;
   return io;
 }
@@ -242,7 +252,7 @@ int rollout_init(const pr_config *cfg, const pr_market *market, const pr_weights
   h->st.ep_cnt = reinterpret_cast<int32_t *>(ws + L.ep_cnt);
   h->mu_scratch = reinterpret_cast<float *>(ws + L.mu);
   h->start = reinterpret_cast<int32_t *>(ws + L.start);
-  h->split = reinterpret_cast<float *>(ws + L.split);
+  for (int i = 0; i < 3; ++i) h->split[i] = ws + L.split[i];
   h->st.start = h->start;
 
   EnvDims &d = h->dims;
@@ -265,10 +275,11 @@ int rollout_init(const pr_config *cfg, const pr_market *market, const pr_weights
   d.s_ind = cfg->obs_scale[3];
 
   fill_net(h->actor, h, 0);
-  h->w1_fused = cfg->schedule == PR_SCHED_FUSED ? static_cast<void *>(ws + L.w1_fused) : nullptr;
-  h->actor_fused = h->actor;
-  h->actor_fused.W[0] = h->w1_fused;
+  h->w1_rot = cfg->schedule == PR_SCHED_FUSED || uses_shadow(*cfg) ? static_cast<void *>(ws + L.w1_rot) : nullptr;
+  h->actor_rot = h->actor;
+  h->actor_rot.W[0] = h->w1_rot;
   fill_net(h->critic, h, 1);
+  if (uses_shadow(*cfg)) h->shadow = h->actor.split_x;
   int prc = pack_nets(h, actor, critic);
   if (prc == PR_OK) {
     hipError_t e = hipMemsetAsync(h->start, 0, (size_t)cfg->n_envs * 4, h->stream);
@@ -317,16 +328,19 @@ int rollout_step_T(pr_handle *h, int32_t T, const float *noise, const pr_buffers
   const size_t N = (size_t)h->cfg.n_envs, D = (size_t)h->cfg.n_stocks, S = (size_t)h->S;
   const int32_t per_agent = h->cfg.n_envs / h->cfg.n_agents;
   if (h->cfg.schedule == PR_SCHED_FUSED) {
-    POD_HIP(launch_rollout_fused(h->stream, h->cfg, h->dims, h->st, h->market.price, h->market.ind, h->actor_fused,
+    POD_HIP(launch_rollout_fused(h->stream, h->cfg, h->dims, h->st, h->market.price, h->market.ind, h->actor_rot,
                                  per_agent, T, noise, nullptr, *out));
   } else {
     POD_HIP(launch_observe(h->stream, h->dims, h->st, h->market.price, h->market.ind, out->obs, h->shadow));
     for (int t = 0; t < T; ++t) {
       float *mu = out->mu ? out->mu + (size_t)t * N * D : h->mu_scratch;
-      POD_HIP(launch_mlp(h->stream, h->actor, (int64_t)N, out->obs + (size_t)t * N * S, (int64_t)S, mu, (int32_t)N,
-                         per_agent));
+      if (h->shadow.p)
+        POD_HIP(launch_layers(h->stream, h->actor_rot, (int64_t)N, h->shadow, mu, (int32_t)N, per_agent));
+      else
+        POD_HIP(launch_mlp(h->stream, h->actor, (int64_t)N, out->obs + (size_t)t * N * S, (int64_t)S, mu, (int32_t)N,
+                           per_agent));
       POD_HIP(launch_env_step(h->stream, h->dims, h->st, h->market.price, h->market.ind,
-                              step_io(h, out, t, mu, noise)));
+                              step_io(h, out, t, mu, noise, h->shadow)));
     }
   }
   if (out->value)
@@ -342,13 +356,13 @@ int rollout_step_forced(pr_handle *h, int32_t T, const float *mu, const float *n
   const size_t N = (size_t)h->cfg.n_envs, D = (size_t)h->cfg.n_stocks;
   if (h->cfg.schedule == PR_SCHED_FUSED) {
     POD_HIP(launch_rollout_fused(h->stream, h->cfg, h->dims, h->st, h->market.price, h->market.ind,
-                                 h->actor_fused, h->cfg.n_envs / h->cfg.n_agents, T, noise, mu, *out));
+                                 h->actor_rot, h->cfg.n_envs / h->cfg.n_agents, T, noise, mu, *out));
     return PR_OK;
   }
-  POD_HIP(launch_observe(h->stream, h->dims, h->st, h->market.price, h->market.ind, out->obs, h->shadow));
+  POD_HIP(launch_observe(h->stream, h->dims, h->st, h->market.price, h->market.ind, out->obs, ObsShadow{}));
   for (int t = 0; t < T; ++t)
     POD_HIP(launch_env_step(h->stream, h->dims, h->st, h->market.price, h->market.ind,
-                            step_io(h, out, t, mu + (size_t)t * N * D, noise)));
+                            step_io(h, out, t, mu + (size_t)t * N * D, noise, ObsShadow{})));
   return PR_OK;
 }
 

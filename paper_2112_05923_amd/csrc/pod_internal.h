@@ -131,7 +131,9 @@ struct PackedNet {
   int32_t nkb[3], nct[3];         // k-blocks and column tiles per layer
   int32_t bf16;                   // operand type
   int32_t out_tanh;               // tanh on the last layer
-  float *split_h[2];              // scratch for the layer-per-launch path: two [split_rows, hidden] fp32 buffers, or null
+  void *split_h[2];               // scratch for the layer-per-launch path: two buffers of split_rows rows of hidden
+                                  // activations (fp32 [hidden] or bf16 [layers_pitch(hidden)]), or null
+  ObsShadow split_x;              // and, for bf16 networks, of its input
   int64_t split_rows;
 };
 // Rows up to which the layer-per-launch path is worth its scratch (fewer 64-row tiles than half the compute units
@@ -148,6 +150,12 @@ hipError_t launch_pack_layer(hipStream_t st, const float *W, const float *b, int
 hipError_t launch_mlp(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx, float *Y,
                       int32_t N, int32_t envs_per_agent);
 bool mlp_supported(int S, int Hd, int O, int bf16);
+// The bf16 layer-per-launch path: x holds the rows (columns up to x.cols zero-padded) in the order layer 1 was packed for.
+bool layers_supported(int64_t rows, int hidden, int bf16);
+int32_t layers_pitch(int cols);
+hipError_t launch_layers(hipStream_t st, const PackedNet &net, int64_t rows, const ObsShadow &x, float *Y, int32_t N,
+                         int32_t envs_per_agent);
+hipError_t launch_rows_to_bf16(hipStream_t st, int64_t rows, const float *X, int64_t ldx, int S, const ObsShadow &out);
 
 // ------------------------------------------------------- persistent rollout
 // One launch for T steps: each workgroup keeps 64 envs on its compute unit (actor forward, sampling, trading

@@ -1,0 +1,308 @@
+// One network layer per launch for batches of 64 to 8192 rows (the per-step policy of a few thousand envs), bf16
+// operands: a small-batch GEMM with the bias and tanh in its epilogue.
+//
+// A kernel that carries a row tile through all three layers would leave most compute units idle at these sizes.  Here a
+// workgroup owns 64 rows x 128 output features of one layer, so 2048 rows x 1024 features are 256 workgroups.
+#include "pod_internal.h"
+
+#include "pod_tile.h"
+
+namespace pod {
+
+namespace {
+
+using tile::f32x16;
+using tile::f32x4;
+using tile::u32x2;
+using tile::u32x4;
+
+constexpr int kThreads = 512;
+constexpr int kRows = 64, kFeatures = 128;
+
+struct LayerArgs {
+  const __bf16 *X;     // [rows][xpitch], columns up to 16 nkb readable
+  int32_t xpitch;
+  int32_t rows;
+  void *Y;             // bf16 [rows][ldy] (hidden) or fp32 [rows][ldy] (output)
+  int32_t ldy;
+  const void *W;       // packed weights of the layer, agent-major
+  const float *b;      // padded biases, agent-major
+  int64_t w_stride;    // bytes between agents
+  int32_t b_stride;    // floats between agents
+  int32_t out_dim, nkb, nct;
+  int32_t out_tanh;
+  int32_t N, envs_per_agent;
+  int32_t tiles_r, tiles_f;    // 64-row and 128-feature tiles
+  int32_t patch_r, patch_f;    // tiles per XCD in either direction
+  int32_t split_f;             // XCDs side by side in the feature direction
+};
+
+// The eight wavefronts are four k-groups of two; a group takes every fourth k-block, its wavefronts 64 rows x 64
+// features each (2 x 2 accumulators of 32 x 32): an LDS operand feeds two and a weight block two matrix instructions, and
+// every weight block is read by exactly one wavefront, straight into registers.  Per iteration of KI k-blocks the input
+// rows pass through a double-buffered LDS tile (one barrier per iteration); weights and rows are requested a whole
+// iteration before they are used, in two register sets, so the loads of the loop body are in flight behind its matrix
+// instructions.  At the end the groups' partial sums are added through LDS, each group finishing one accumulator.
+// What bounds it: the bytes a compute unit draws from the L2 (per k and workgroup 384 B for 4 cycles of matrix work;
+// 64 B per cycle and compute unit) and, with few iterations, their latency.
+// KI = 16: 128 registers of weights and rows in flight, one workgroup per compute unit; KI = 8: half of that and two
+// workgroups per compute unit, for launches with more workgroups than compute units.
+template <int KI, bool HIDDEN>
+__global__ __launch_bounds__(kThreads, KI == 16 ? 2 : 4) void layer_kernel(LayerArgs a) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  constexpr int LB = KI / 4;               // k-blocks per group and iteration
+  constexpr int NP = KI / 4;               // 16-byte pieces of the input rows per thread and iteration
+  constexpr int PITCH = KI * 32 + 16;      // bytes per row of a staged chunk
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), grp = wave >> 1, half = wave & 1;
+
+  // neighbouring tiles on one XCD (block b runs on XCD b % 8): a patch of patch_r x patch_f tiles shares its L2
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int sr = slot / a.patch_f, sf = slot - sr * a.patch_f;
+  const int tr = (xcd / a.split_f) * a.patch_r + sr, tf = (xcd % a.split_f) * a.patch_f + sf;
+  if (sr >= a.patch_r || tr >= a.tiles_r || tf >= a.tiles_f) return;
+  const int row0 = tr * kRows;
+  const int agent = (row0 % a.N) / a.envs_per_agent;
+  const u32x4 *W = reinterpret_cast<const u32x4 *>(static_cast<const unsigned char *>(a.W) + (size_t)agent * a.w_stride);
+  const float *bias = a.b + (size_t)agent * a.b_stride;
+  const int nkb = a.nkb, nct = a.nct;
+  const int nit = (nkb + KI - 1) / KI;
+
+  // input rows: piece p of the tile is 16 bytes of row p / (2 KI)
+  const __bf16 *xp[NP];
+  int xcol[NP], xdst[NP];
+  const int last_col = nkb * 16 - 8;
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    const int p = tid + kThreads * i, r = p / (2 * KI), c = p % (2 * KI);
+    xp[i] = a.X + (size_t)min(row0 + r, a.rows - 1) * a.xpitch;
+    xcol[i] = 8 * c;
+    xdst[i] = r * PITCH + 16 * c;
+  }
+  u32x4 x[NP];
+  auto load_x = [&](int it) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+      x[i] = *reinterpret_cast<const u32x4 *>(xp[i] + min(xcol[i] + it * KI * 16, last_col));
+  };
+  auto put_x = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) *reinterpret_cast<u32x4 *>(lds + buf * (kRows * PITCH) + xdst[i]) = x[i];
+  };
+  // weights: blocks KI it + 4 j + grp, feature tiles 4 tf + 2 half + {0, 1}
+  const u32x4 *wp[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) wp[c] = W + (size_t)min(tf * 4 + half * 2 + c, nct - 1) * 64 + lane;
+  u32x4 wa[LB][2], wb[LB][2];
+  auto load_w = [&](u32x4(&w)[LB][2], int it, int j) {
+    const size_t o = (size_t)min(it * KI + 4 * j + grp, nkb - 1) * nct * 64;
+    w[j][0] = wp[0][o];
+    w[j][1] = wp[1][o];
+  };
+
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[c][t][i] = 0.0f;
+  const unsigned char *xl = lds + (lane & 31) * PITCH + 16 * (lane >> 5) + 32 * grp;
+  auto mma = [&](const u32x4(&w)[LB][2], int buf, int j) {
+    u32x4 v[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+      v[t] = *reinterpret_cast<const u32x4 *>(xl + buf * (kRows * PITCH) + t * 32 * PITCH + j * 128);
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) tile::Op<true>::mma(w[j][c], v[t], acc[c][t]);
+  };
+
+  load_x(0);
+#pragma unroll
+  for (int j = 0; j < LB; ++j) load_w(wa, 0, j);
+  put_x(0);
+  if (nit > 1) {
+    load_x(1);
+#pragma unroll
+    for (int j = 0; j < LB; ++j) load_w(wb, 1, j);
+  }
+  __syncthreads();
+  // iteration it: rows of it + 1 into the other LDS buffer, rows and weights of it + 2 requested
+  auto step = [&](u32x4(&w)[LB][2], int it, int buf) {
+    put_x(buf ^ 1);
+    load_x(it + 2);
+#pragma unroll
+    for (int j = 0; j < LB; ++j) {
+      mma(w, buf, j);
+      load_w(w, it + 2, j);
+    }
+    __syncthreads();
+  };
+  // the last two or three iterations: the k-blocks of the last one may end anywhere
+  auto tail = [&](u32x4(&w)[LB][2], int it, int buf) {
+    if (it + 1 < nit) put_x(buf ^ 1);
+    if (it + 2 < nit) load_x(it + 2);
+#pragma unroll
+    for (int j = 0; j < LB; ++j) {
+      if (it * KI + 4 * j + grp < nkb) mma(w, buf, j);
+      if (it + 2 < nit) load_w(w, it + 2, j);
+    }
+    __syncthreads();
+  };
+  int it = 0;
+  for (; it + 4 <= nit; it += 2) {
+    step(wa, it, 0);
+    step(wb, it + 1, 1);
+  }
+  tail(wa, it, 0);
+  if (it + 1 < nit) tail(wb, it + 1, 1);
+  if (it + 2 < nit) tail(wa, it + 2, 0);
+
+  // -- partial sums: group t finishes accumulator t = (feature tile t / 2, row tile t % 2) of both halves
+  float *red = reinterpret_cast<float *>(lds);  // [2 accumulators][3 groups][2 halves][16][64]
+  f32x16 sum;
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    if (p) __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int t = 2 * p + q;
+      if (t != grp) {
+        float *d = red + ((q * 3 + (grp < t ? grp : grp - 1)) * 2 + half) * 1024 + lane;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) d[i * 64] = acc[t >> 1][t & 1][i];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int t = 2 * p + q;
+      if (t == grp) {
+        sum = acc[t >> 1][t & 1];
+#pragma unroll
+        for (int g = 0; g < 3; ++g) {
+          const float *s = red + ((q * 3 + g) * 2 + half) * 1024 + lane;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) sum[i] += s[i * 64];
+        }
+      }
+    }
+  }
+  // -- bias and tanh, then whole rows out through LDS (behind the 48 KiB of partial sums)
+  constexpr int OESZ = HIDDEN ? 2 : 4, OPITCH = kFeatures * OESZ + 16;
+  unsigned char *stage = lds + 48 * 1024;
+  {
+    const int f0 = half * 64 + (grp >> 1) * 32, row = (grp & 1) * 32 + (lane & 31);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int f = f0 + 8 * j + 4 * (lane >> 5);
+      const f32x4 bv = *reinterpret_cast<const f32x4 *>(bias + min(tf * kFeatures + f, nct * 32 - 4));
+      float y[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float z = sum[4 * j + i] + bv[i];
+        y[i] = HIDDEN ? tile::tanh_from_scaled(z * tile::kTwoLog2e) : a.out_tanh ? tile::tanh_accurate(z) : z;
+      }
+      tile::Op<HIDDEN>::store4(stage + row * OPITCH + f * OESZ, y[0], y[1], y[2], y[3]);
+    }
+  }
+  __syncthreads();
+  const int nr = min(kRows, a.rows - row0);
+  if (HIDDEN) {
+    // (the hidden width is a multiple of 32: a 16-byte piece is inside or outside as a whole)
+    __bf16 *Y = static_cast<__bf16 *>(a.Y);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int p = tid + kThreads * i, r = p >> 4, c = p & 15;
+      if (r < nr && tf * kFeatures + 8 * c < a.out_dim)
+        *reinterpret_cast<u32x4 *>(Y + (size_t)(row0 + r) * a.ldy + tf * kFeatures + 8 * c) =
+            *reinterpret_cast<const u32x4 *>(stage + r * OPITCH + 16 * c);
+    }
+  } else {
+    float *Y = static_cast<float *>(a.Y);
+    for (int p = tid; p < nr * kFeatures; p += kThreads) {
+      const int r = p >> 7, c = p & 127;
+      if (tf * kFeatures + c < a.out_dim)
+        Y[(size_t)(row0 + r) * a.ldy + tf * kFeatures + c] = *reinterpret_cast<const float *>(stage + r * OPITCH + 4 * c);
+    }
+  }
+}
+
+// rows of X to bf16, zeros up to the end of the last k-block; one wavefront per row
+__global__ __launch_bounds__(256) void rows_to_bf16_kernel(const float *__restrict__ X, int64_t ldx, int rows, int S,
+                                                           int cols, __bf16 *__restrict__ out, int pitch) {
+  const int lane = threadIdx.x & 63, r = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= rows) return;
+  const float *x = X + r * ldx;
+  __bf16 *o = out + (size_t)r * pitch;
+#pragma unroll 4
+  for (int c = lane; c < cols; c += 64) o[c] = (__bf16)(c < S ? x[c] : 0.0f);
+}
+
+template <int KI, bool HIDDEN>
+hipError_t launch_layer(hipStream_t st, const LayerArgs &a, unsigned blocks) {
+  constexpr auto kern = layer_kernel<KI, HIDDEN>;
+  const hipError_t e = allow_full_lds<kern>();
+  if (e != hipSuccess) return e;
+  const size_t chunks = 2 * (size_t)kRows * (KI * 32 + 16);
+  const size_t ends = 48 * 1024 + (size_t)kRows * (kFeatures * (HIDDEN ? 2 : 4) + 16);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), chunks > ends ? chunks : ends, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// Up to 8192 rows a whole-network launch would have less than half a tile per compute unit; from 128 hidden units on a
+// layer has whole feature tiles.
+bool layers_supported(int64_t rows, int hidden, int bf16) { return bf16 && hidden >= 128 && rows >= 64 && rows <= 8192; }
+
+// (the extra 64 columns keep the rows of a power-of-two width off one set of L2 channels)
+int32_t layers_pitch(int cols) { return (cols + 15) / 16 * 16 + 64; }
+
+hipError_t launch_layers(hipStream_t st, const PackedNet &net, int64_t rows, const ObsShadow &x, float *Y, int32_t N,
+                         int32_t envs_per_agent) {
+  const int Hd = net.out_dim[0];
+  const void *in = x.p;
+  int32_t pitch = x.pitch;
+  for (int l = 0; l < 3; ++l) {
+    LayerArgs a;
+    a.X = static_cast<const __bf16 *>(in), a.xpitch = pitch, a.rows = (int32_t)rows;
+    a.Y = l == 2 ? static_cast<void *>(Y) : net.split_h[l];
+    a.ldy = l == 2 ? net.out_dim[2] : layers_pitch(Hd);
+    a.W = net.W[l], a.b = net.b[l], a.w_stride = net.w_stride[l], a.b_stride = net.b_stride[l];
+    a.out_dim = net.out_dim[l], a.nkb = net.nkb[l], a.nct = net.nct[l];
+    a.out_tanh = net.out_tanh;
+    a.N = N, a.envs_per_agent = envs_per_agent;
+    a.tiles_r = (int32_t)((rows + kRows - 1) / kRows), a.tiles_f = (net.nct[l] + 3) / 4;
+    // an XCD's patch: the split of the eight XCDs that reads the fewest bytes (input rows and weight columns weigh the
+    // same per k), among those that leave the fewest tiles on the busiest XCD
+    int best = 0, best_tiles = 0, best_bytes = 0;
+    for (int sf = 1; sf <= 8; sf *= 2) {
+      const int pr = (a.tiles_r + 8 / sf - 1) / (8 / sf), pf = (a.tiles_f + sf - 1) / sf;
+      const int tiles = pr * pf, bytes = pr * kRows + pf * kFeatures;
+      if (best == 0 || tiles < best_tiles || (tiles == best_tiles && bytes < best_bytes))
+        best = sf, best_tiles = tiles, best_bytes = bytes;
+    }
+    a.split_f = best;
+    a.patch_r = (a.tiles_r + 8 / best - 1) / (8 / best), a.patch_f = (a.tiles_f + best - 1) / best;
+    const unsigned blocks = 8u * (unsigned)(a.patch_r * a.patch_f);
+    const bool two = blocks > 256;  // more workgroups than compute units
+    hipError_t e;
+    if (l < 2) e = two ? launch_layer<8, true>(st, a, blocks) : launch_layer<16, true>(st, a, blocks);
+    else e = two ? launch_layer<8, false>(st, a, blocks) : launch_layer<16, false>(st, a, blocks);
+    if (e != hipSuccess) return e;
+    in = a.Y;
+    pitch = a.ldy;
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_rows_to_bf16(hipStream_t st, int64_t rows, const float *X, int64_t ldx, int S, const ObsShadow &out) {
+  hipLaunchKernelGGL(rows_to_bf16_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, X, ldx, (int)rows, S, out.cols,
+                     reinterpret_cast<__bf16 *>(out.p), out.pitch);
+  return hipGetLastError();
+}
+
+}  // namespace pod

@@ -112,3 +112,28 @@ def test_env_step_tiles(N, D, K, cash0):
     torch.cuda.synchronize()
     rec = {k: parity.to_np(v) for k, v in out.items()}
     parity.check_env_record(w, oracle.cfg_from_workload(w, horizon=6), rec, d["price"], d["ind"], d["noise"], mu)
+
+
+# one launch per layer (64..8192 rows, bf16): partial row and feature tiles, 1 to 40 k-blocks (whole and partial
+# iterations, an odd and an even number of them), more workgroups than compute units, several agents
+@pytest.mark.parametrize("N,rows,agents,Hd,D,K", [(64, 64, 1, 128, 2, 0), (100, 65, 1, 160, 15, 1), (256, 256, 4, 128, 30, 8),
+                                                  (700, 700, 1, 512, 32, 0), (256, 200, 2, 544, 127, 3), (4200, 4200, 1, 512, 60, 2),
+                                                  (130, 130, 1, 1024, 160, 2), (8192, 8192, 1, 256, 16, 2)])
+def test_layer_launches(N, rows, agents, Hd, D, K):
+    w = inputs.WORKLOADS["large"].replace(n_envs=N, n_agents=agents, hidden=Hd, n_stocks=D, n_ind=K, steps=2)
+    d = inputs.make_all(w, horizon=2, n_market=1, steps=2)
+    cfg = pr.make_config(w, horizon=2, n_market=1, schedule=pr.PR_SCHED_STEPWISE)
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    ro = pr.Rollout(cfg, _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+    X = np.random.default_rng(rows).standard_normal((rows, w.state_dim)).astype(np.float32)
+    mu, val = (parity.to_np(ro.mlp_forward(net, _t(X))) for net in (pr.PR_NET_ACTOR, pr.PR_NET_CRITIC))
+    out = ro.alloc_buffers(2, value=False, logp=False, mu=True, shares=False)
+    ro.step_T(2, _t(d["noise"]), out)
+    torch.cuda.synchronize()
+    obs, mus = parity.to_np(out["obs"]), parity.to_np(out["mu"])
+    pick = np.unique(np.concatenate([np.arange(0, rows, max(1, rows // 150)), np.arange(rows - 40, rows)]))
+    for a in range(agents):
+        sel = pick[pick // (N // agents) == a]
+        parity.check_networks(w, d["actor"], d["critic"], X[sel], mu[sel], val[sel], agent=a)
+        for t in range(2):
+            parity.check_networks(w, d["actor"], d["critic"], obs[t][sel], mus[t][sel], agent=a)
