@@ -76,11 +76,13 @@ __global__ __launch_bounds__(kThreads) void observe_kernel(EnvDims d, EnvState s
 // everything else hangs off it:
 //  - the cursor is read by every thread of an env (no barrier in front of the prices), the market part of the next
 //    observation is requested together with the prices and written while the orders are packed;
-//  - the ledger (one lane per env) adds the sales from a dense row, and walks only the purchases: the threads pack them
-//    into a list in stock order (ballots inside a wavefront, counts per 32 or 64 stocks across);
+//  - the ledger adds the sales from a dense row, and walks only the purchases: the threads pack them into a list in
+//    stock order (ballots inside a wavefront, counts per 32 or 64 stocks across).  It runs in the env's own wavefront
+//    (half) and needs one dependent operation per purchase while the cash lasts, none for a purchase it does not
+//    buy a single share of, and the quotient only in between (13.5 -> 1.8 us of a step with 250 purchases);
 //  - the account values before and after are sums over the env's threads in binary64.
-// Measured per step: 2048 envs x 500 stocks x 4 indicators 106 -> 31 us, 5000 x 100 x 8 30 -> 16 us, 4096 x 30 x 8
-// 11.2 -> 6.8 us, 16 x 5 x 2 6.0 -> 4.8 us (before: order slots of up to 32 envs and a ledger over all of them in LDS,
+// Measured per step: 2048 envs x 500 stocks x 4 indicators 106 -> 18.5 us, 5000 x 100 x 8 30 -> 15 us, 4096 x 30 x 8
+// 11.2 -> 6.4 us, 16 x 5 x 2 6.0 -> 4.8 us (before: order slots of up to 32 envs and a ledger over all of them in LDS,
 // holdings stored stock-major and hence moved in short runs).  The bytes of the first of these take 10 us.
 constexpr int kEnvThreads = 512;
 typedef float env_f32x4 __attribute__((ext_vector_type(4)));
@@ -95,6 +97,19 @@ __device__ inline double sum_lanes(double v, int width) {
   return v;
 }
 
+// s + v[0][0] + v[0][1] + ... in this order (two register sets, read one ahead of the other by hand, were slower)
+__device__ inline float serial_sum(float s, const env_f32x4 *v, int n) {
+#pragma unroll 8
+  for (int c = 0; c < n; ++c) {
+    const env_f32x4 x = v[c];
+    s = s + x[0];
+    s = s + x[1];
+    s = s + x[2];
+    s = s + x[3];
+  }
+  return s;
+}
+
 template <int E, int ND>
 __global__ __launch_bounds__(kEnvThreads, 4) void env_step_kernel(EnvDims d, EnvState s, const float *__restrict__ price,
                                                                  const float *__restrict__ ind, StepIO io) {
@@ -104,17 +119,17 @@ __global__ __launch_bounds__(kEnvThreads, 4) void env_step_kernel(EnvDims d, Env
   constexpr int NCW = TPE / CW, NC = ND * NCW;          // counts per pass over the stocks, per env
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int D = d.D, DK = D * d.K, D4 = (D + 3) & ~3;
-  const int LP = D + 9;                                     // purchases per env, zero entries behind them; odd pitch in 16 bytes
-  Purchase *s_list = reinterpret_cast<Purchase *>(lds_raw);  // [E][LP | 1]
-  const int lp = LP | 1;
+  const int lp = D | 1;                                      // (odd pitch in 16 bytes)
+  Purchase *s_list = reinterpret_cast<Purchase *>(lds_raw);  // [E][lp] purchases in stock order
   float *s_sell = reinterpret_cast<float *>(s_list + E * lp);  // [E][D4] proceeds of the sales, 0 elsewhere
   const int sp_ = D4 + 4;
   float *s_sq = s_sell + E * sp_;                             // [E][sp_] squared noise
-  int32_t *s_buy = reinterpret_cast<int32_t *>(s_sq + E * sp_);  // [E][lp] shares bought, by list position
+  const int op = D4 + 20;
+  float *s_out = s_sq + E * sp_;                              // [E][op] outlay k u of the purchases, by list position
+  int32_t *s_buy = reinterpret_cast<int32_t *>(s_out + E * op);  // [E][lp] shares bought, by list position
   double *s_part = reinterpret_cast<double *>(s_buy + E * lp + (E * lp & 1));  // [2][E][2] account value before / after
   float *s_e2 = reinterpret_cast<float *>(s_part + 4 * E);  // [E] sum of the squares
   int32_t *s_cnt = reinterpret_cast<int32_t *>(s_e2 + E);        // [E][NC]
-  float *s_cash = reinterpret_cast<float *>(s_cnt + E * NC);       // [E] cash after the trades
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int e = tid / TPE, tl = tid & (TPE - 1), cw = tl / CW;  // cw: which wavefront of the env
@@ -124,6 +139,7 @@ __global__ __launch_bounds__(kEnvThreads, 4) void env_step_kernel(EnvDims d, Env
   // -- requests that depend on nothing
   const int32_t tau = s.tau[n], start = s.start[n];
   const float cash_in = s.cash[n];
+  float cash = cash_in, e2 = 0.0f;
   float mu[ND], eps[ND];
   int32_t h[ND];
   const size_t g0 = (size_t)n * D;
@@ -210,9 +226,12 @@ __global__ __launch_bounds__(kEnvThreads, 4) void env_step_kernel(EnvDims d, Env
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
       rank[i] += base[i];
-      if (kf[i] > 0.0f) s_list[e * lp + rank[i]] = Purchase{kf[i], unit[i], 1.0 / (double)unit[i]};
+      if (kf[i] > 0.0f) {
+        s_list[e * lp + rank[i]] = Purchase{kf[i], unit[i], 1.0 / (double)unit[i]};
+        s_out[e * op + rank[i]] = kf[i] * unit[i];
+      }
     }
-    if (tl < 8) s_list[e * lp + total + tl] = Purchase{0.0f, 0.0f, 0.0};
+    if (tl < 16) s_out[e * op + total + tl] = 0.0f;
   }
   // -- market part of the next observation
 #pragma unroll
@@ -241,65 +260,72 @@ __global__ __launch_bounds__(kEnvThreads, 4) void env_step_kernel(EnvDims d, Env
   }
   __syncthreads();
 
-  if (wave == 0) {
+  if (cw == NCW - 1 && io.logp) {
+    // the squares in stock order (the log-probability is the same number in every schedule)
+    const env_f32x4 *sq = reinterpret_cast<const env_f32x4 *>(s_sq + e * sp_);
+    e2 = serial_sum(0.0f, sq, D4 / 4);
+    if (NCW > 1 && (lane & (CW - 1)) == 0) s_e2[e] = e2;
+  }
+  if (cw == 0) {
     // -- the ledger (Table 1 actions: sell / buy / hold): all sales, then all purchases, in stock order, each limited
     // by the cash left:
     //   m = floor(cash / u); q = min(k, max(m, 0)); if (q u > cash) q -= 1; cash -= q u        (binary32)
-    // The binary32 quotient comes from one binary64 product with the reciprocal of u prepared by the other lanes:
-    // the product is within 2^-52 of cash / u, and a quotient of two binary32 numbers is at least 2^-49 (relative)
-    // away from every binary32 rounding boundary it does not hit exactly, so the product rounded to binary32 is
-    // the correctly rounded cash / u.  The quotient is never negative (cash is not), so truncation is the floor
-    // and needs no clamp at 0; the outlay of one share less, (q - 1) u rounded once, is the fused q u - u (the
-    // same real number, one rounding); both candidate balances are formed before the comparison is known.
-    // A chunk of entries is read into registers first, so that the dependent chain on the cash runs on registers only.
-    if (lane < E) {
-      float cash = s.cash[min(n0 + lane, d.N - 1)];
-      const env_f32x4 *sell = reinterpret_cast<const env_f32x4 *>(s_sell + lane * sp_);
-#pragma unroll 4
-      for (int c = 0; c < D4 / 4; ++c) {
-        const env_f32x4 v = sell[c];
-        cash = cash + v[0];
-        cash = cash + v[1];
-        cash = cash + v[2];
-        cash = cash + v[3];
-      }
-      int nb = 0;
+    const env_f32x4 *sell = reinterpret_cast<const env_f32x4 *>(s_sell + e * sp_);
+    cash = serial_sum(cash, sell, D4 / 4);
+    const int cl = lane & (CW - 1);
+    const Purchase *list = s_list + e * lp;
+    auto affordable = [&](float c, float u) {  // of the CW entries the env's lanes hold: those the cash buys a share of
+      const uint64_t all = __ballot(!(c < u));
+      return CW == 64 ? all : (all >> (lane & ~(CW - 1))) & ((1ull << (CW & 63)) - 1ull);
+    };
+    for (int c0 = 0; c0 < total; c0 += CW) {
+      const int p = c0 + cl;
+      const Purchase mine = list[min(p, total - 1)];
+      const float u = p < total ? mine.u : __builtin_inff();
+      int32_t got = 0;
+      for (int s0 = 0; s0 < CW && c0 + s0 < total; s0 += 16) {
+        if (((affordable(cash, u) >> s0) & 0xffffull) == 0) continue;
+        // sixteen purchases in full: as long as the balance stays clear of 0 (2^-20 of what it was, so every outlay
+        // k u before it was below the balance by more than its own rounding), each quotient was at least k
+        const env_f32x4 *out = reinterpret_cast<const env_f32x4 *>(s_out + e * op + c0 + s0);
+        const float clear = cash * 0x1p-20f;
+        float full = cash;
+        int in_full = 0;
 #pragma unroll
-      for (int c = 0; c < NC; ++c) nb += s_cnt[lane * NC + c];
-      const Purchase *list = s_list + lane * lp;
-      int32_t *bought = s_buy + lane * lp;
-      constexpr int CH = 8;
-      for (int p0 = 0; p0 < nb; p0 += CH) {  // (entries behind the last purchase buy nothing)
-        Purchase b[CH];
-#pragma unroll
-        for (int j = 0; j < CH; ++j) b[j] = list[p0 + j];
-#pragma unroll
-        for (int j = 0; j < CH; ++j) {
-          const float ratio = (float)((double)cash * b[j].rcp);
-          const float q0 = fminf(b[j].k, truncf(ratio));
-          const float out_q = q0 * b[j].u, out_q1 = fmaf(q0, b[j].u, -b[j].u);
+        for (int c = 0; c < 4; ++c) {
+          const env_f32x4 v = out[c];
+          full = full - v[0];
+          full = full - v[1];
+          full = full - v[2];
+          full = full - v[3];
+          if (full >= clear) cash = full, in_full = 4 * c + 4;  // (outlays are not negative: never true again once false)
+        }
+        if ((unsigned)(cl - s0) < (unsigned)in_full) got = (int32_t)mine.k;
+        if (in_full == 16) continue;
+        // one by one, those that buy nothing (cash < u: the quotient is below 1 and rounds below 1) skipped.
+        // The binary32 quotient comes from one binary64 product with the prepared reciprocal of u: the product is
+        // within 2^-52 of cash / u, and a quotient of two binary32 numbers is at least 2^-49 (relative) away from
+        // every binary32 rounding boundary it does not hit exactly, so the product rounded to binary32 is the
+        // correctly rounded cash / u.  It is never negative (cash is not), so truncation is the floor and needs no
+        // clamp at 0; the outlay of one share less, (q - 1) u rounded once, is the fused q u - u.
+        uint64_t ahead = (0xffffull << s0) & (~0ull << (s0 + in_full));
+        while (true) {
+          const uint64_t left = affordable(cash, u) & ahead;
+          if (left == 0) break;
+          const int j = __builtin_ctzll(left);
+          const Purchase b = list[c0 + j];
+          const float ratio = (float)((double)cash * b.rcp);
+          const float q0 = fminf(b.k, truncf(ratio));
+          const float out_q = q0 * b.u, out_q1 = fmaf(q0, b.u, -b.u);
           const float bal0 = cash - out_q, bal1 = cash - out_q1;
           const bool over = out_q > cash;
           cash = over ? bal1 : bal0;
-          bought[p0 + j] = (int32_t)(over ? q0 - 1.0f : q0);
+          if (cl == j) got = (int32_t)(over ? q0 - 1.0f : q0);
+          ahead &= ~1ull << j;
         }
       }
-      s_cash[lane] = cash;
+      if (p < total) s_buy[e * lp + p] = got;
     }
-  }
-  if (wave == 1 && lane < E && io.logp) {
-    // the squares in stock order (the log-probability is the same number in every schedule)
-    float e2 = 0.0f;
-    const env_f32x4 *sq = reinterpret_cast<const env_f32x4 *>(s_sq + lane * sp_);
-#pragma unroll 4
-    for (int c = 0; c < D4 / 4; ++c) {
-      const env_f32x4 v = sq[c];
-      e2 += v[0];
-      e2 += v[1];
-      e2 += v[2];
-      e2 += v[3];
-    }
-    s_e2[lane] = e2;
   }
   if (live) {
     // -- meanwhile: indicator groups beyond the first NI of a thread (K > 8), and the last DK % 4 indicators
@@ -336,11 +362,10 @@ __global__ __launch_bounds__(kEnvThreads, 4) void env_step_kernel(EnvDims d, Env
   __syncthreads();
   if (live && tl == 0) {
     // -- reward and episode bookkeeping (binary64), reset of the env if its episode ended
-    double v0 = (double)cash_in, v1 = (double)s_cash[e];
+    double v0 = (double)cash_in, v1 = (double)cash;
 #pragma unroll
     for (int c = 0; c < NCW; ++c) v0 += s_part[e * 2 + c], v1 += s_part[2 * E + e * 2 + c];
     const double r = (v1 - v0) * (double)d.rho;
-    float cash = s_cash[e];
     double ep = s.ep_ret[n] + r;
     if (ri.done) {
       s.ep_sum[n] += ep;
@@ -357,14 +382,14 @@ __global__ __launch_bounds__(kEnvThreads, 4) void env_step_kernel(EnvDims d, Env
     if (sp) sp[DK] = (__bf16)v;
     io.reward[n] = (float)r;
     io.done[n] = (uint8_t)ri.done;
-    if (io.logp) io.logp[n] = fmaf(-0.5f, s_e2[e], d.logp_const);
+    if (io.logp) io.logp[n] = fmaf(-0.5f, NCW > 1 ? s_e2[e] : e2, d.logp_const);
   }
 }
 
 size_t env_lds(int E, int D) {
-  const int D4 = (D + 3) & ~3, lp = (D + 9) | 1;
-  return (size_t)E * lp * sizeof(Purchase) + (size_t)2 * E * (D4 + 4) * 4 + ((size_t)E * lp + 1) * 4 + (size_t)4 * E * 8 +
-         (size_t)E * 4 + (size_t)E * 8 * 4 + (size_t)E * 4;
+  const int D4 = (D + 3) & ~3, lp = D | 1;
+  return (size_t)E * lp * sizeof(Purchase) + (size_t)E * (2 * (D4 + 4) + D4 + 20) * 4 + ((size_t)E * lp + 1) * 4 + (size_t)4 * E * 8 +
+         (size_t)E * 4 + (size_t)E * 8 * 4;
 }
 
 // ------------------------------------------------------------ state plumbing
@@ -498,11 +523,14 @@ static hipError_t launch_step(hipStream_t st, const EnvDims &d, const EnvState &
 
 hipError_t launch_env_step(hipStream_t st, const EnvDims &d, const EnvState &s, const float *price, const float *ind,
                            const StepIO &io) {
-  // half a wavefront per env up to four stocks per thread, then more threads per env
+  // Half a wavefront per env up to 128 stocks, a whole one up to 256, two beyond; twice as many when all workgroups are
+  // then still resident at once, two per compute unit (fewer stocks per thread and an undivided wavefront for the ledger:
+  // 512 envs x 60 stocks 8.9 -> 7.4 us, 1024 x 256 13.1 -> 11.3 us; 5000 x 100 would go from 17.5 to 19.7).
   if (d.D <= 32) return launch_step<16, 1>(st, d, s, price, ind, io);
-  if (d.D <= 64) return launch_step<16, 2>(st, d, s, price, ind, io);
-  if (d.D <= 128) return launch_step<16, 4>(st, d, s, price, ind, io);
-  if (d.D <= 256) return launch_step<8, 4>(st, d, s, price, ind, io);
+  const bool few8 = d.N <= 8 * 512, few4 = d.N <= 4 * 512;
+  if (d.D <= 64) return few8 ? launch_step<8, 1>(st, d, s, price, ind, io) : launch_step<16, 2>(st, d, s, price, ind, io);
+  if (d.D <= 128) return few8 ? launch_step<8, 2>(st, d, s, price, ind, io) : launch_step<16, 4>(st, d, s, price, ind, io);
+  if (d.D <= 256) return few4 ? launch_step<4, 2>(st, d, s, price, ind, io) : launch_step<8, 4>(st, d, s, price, ind, io);
   if (d.D <= 512) return launch_step<4, 4>(st, d, s, price, ind, io);
   return hipErrorInvalidValue;  // (the networks of this library have at most 512 outputs)
 }
