@@ -127,7 +127,6 @@ Layout make_layout(const pr_config &c) {
 void fill_net(PackedNet &pn, const pr_handle *h, int net) {
   const pr_config &c = h->cfg;
   const int S = h->S, Hd = c.hidden, D = c.n_stocks, bf = c.mlp_dtype;
-  const int KB = bf ? 16 : 8;
   const int in_dim[3] = {S, Hd, Hd};
   const int out_dim[3] = {Hd, Hd, net == 0 ? D : 1};
   for (int l = 0; l < 3; ++l) {
@@ -137,7 +136,7 @@ void fill_net(PackedNet &pn, const pr_handle *h, int net) {
     pn.b_stride[l] = padded_out(out_dim[l]);
     pn.in_dim[l] = in_dim[l];
     pn.out_dim[l] = out_dim[l];
-    pn.nkb[l] = (in_dim[l] + KB - 1) / KB;
+    pn.nkb[l] = (in_dim[l] + 15) / 16;
     pn.nct[l] = (out_dim[l] + 31) / 32;
   }
   pn.bf16 = bf;

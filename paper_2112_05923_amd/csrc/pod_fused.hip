@@ -58,8 +58,8 @@ constexpr int kDp = DMAX + 1;    // odd row pitch: the per-env serial walks of t
 constexpr int kLagPrio = 2;  // wavefront priority of the lagging group's matrix steps in the split schedule (1..3 measure alike)
 constexpr int MUP = 33;         // row pitch of a policy-mean plane (lanes of one store differ in the row: 32 would hit one bank)
 // Planes the output layer's k range is split into (one per group of wavefronts), by the compile-time k-block count
-// of the kernel instance.
-constexpr int mu_planes(int nkb2) { return (nkb2 > 0 && nkb2 % 4 == 0) ? 4 : 1; }
+// of the kernel instance.  fp32 networks: eight, one per wavefront, each holding its output weights in registers.
+constexpr int mu_planes(bool bf16, int nkb2) { return !bf16 ? 8 : (nkb2 > 0 && nkb2 % 4 == 0) ? 4 : 1; }
 
 struct Row {
   int32_t row_val;  // market row the portfolio is valued at (cursor + 1)
@@ -139,7 +139,7 @@ __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n0 = blockIdx.x * E;
+  const int n0 = (int)xcd_index(blockIdx.x, gridDim.x) * E;
   const size_t N = (size_t)d.N;
   const bool is_market = SPLIT ? wave < NW / 2 : wave != 0;
   const int mw = SPLIT ? wave : wave - 1;  // index among the market wavefronts
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
   float *s_pv = reinterpret_cast<float *>(s_q + E * Dp);    // valuation prices
   float *s_e2 = s_pv + E * Dp;                              // squared noise
   // output-layer accumulators of the actor, one [E][32] plane per k part of that layer (summed in the pre-compute)
-  constexpr int KS = mu_planes(NKB2);
+  constexpr int KS = mu_planes(BF16, NKB2);
   float *s_mu = reinterpret_cast<float *>(ldsX);
 
   // ---- ledger lanes (wavefront LW, see below): per-env scalars in registers for the whole rollout
@@ -170,9 +170,12 @@ __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
   double asset = 0.0, ep_ret = 0.0, ep_sum = 0.0, ep_sqsum = 0.0;
 
   Net net;
+  // fp32: this wavefront's k-blocks of the output layer
+  constexpr int NW3 = ACTOR && !BF16 ? NKB2 / KS : 1;
+  typename O::Block w3r[NW3];
   if (ACTOR) {
     net = net_of(a.actor, (n0 % d.N) / a.envs_per_agent);
-    stage_net<NT>(net, ldsBias, ldsW3, tid);
+    stage_net<NT>(net, ldsBias, BF16 ? ldsW3 : nullptr, tid);
     if constexpr (SPLIT) {
       // Output-layer blocks in the k order of an accumulator half: the lane of half g takes, from the standard
       // block's two lanes of its output feature, the four k of each that an accumulator lane of half g holds.
@@ -188,6 +191,10 @@ __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
       __syncthreads();
 #pragma unroll
       for (int j = 0; j < NKB2 * 64 / NT; ++j) ldsW3[tid + NT * j] = v[j];
+    }
+    if constexpr (!BF16) {
+#pragma unroll
+      for (int i = 0; i < NW3; ++i) fetch_w(w3r[i], net.W[2] + (wave * NW3 + i) * (64 * kPlanes<typename O::Block>) + lane);
     }
     // padded k columns of the input tile must read as zero
     for (int i = tid; i < E * a.L.xpitch / 4; i += NT) reinterpret_cast<uint32_t *>(ldsX)[i] = 0u;
@@ -248,7 +255,7 @@ __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
         s_p[e * Dp + lp] = v;
         const float pv = v * d.s_price;
         __builtin_nontemporal_store(pv, &orow[1 + lp]);
-        if (ACTOR) O::store1(ldsX + (size_t)e * a.L.xpitch + (DK + 1 + lp) * O::ESZ, pv);
+        if (ACTOR) O::store1(ldsX + (size_t)e * a.L.xpitch + O::off(DK + 1 + lp), pv);
         f32x4 sv = ind_v[i];
         sv[0] *= d.s_ind;
         sv[1] *= d.s_ind;
@@ -257,7 +264,7 @@ __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
         // observation rows are 4-byte aligned only; a 16-byte store needs no more than that
         __builtin_nontemporal_store(sv, reinterpret_cast<f32x4 *>(orow + 1 + 2 * D) + li);
         // (indicators lead the LDS tile, so a group of four is one aligned store)
-        if (ACTOR) O::store4(ldsX + (size_t)e * a.L.xpitch + 4 * li * O::ESZ, sv[0], sv[1], sv[2], sv[3]);
+        if (ACTOR) O::store4(ldsX + (size_t)e * a.L.xpitch + O::off(4 * li), sv[0], sv[1], sv[2], sv[3]);
       }
     }
   };
@@ -272,10 +279,10 @@ __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
       const float sv = s_cash[tid] * d.s_cash;
       __builtin_nontemporal_store(sv, &obs_row[(size_t)(n0 + tid) * S]);
       if (ACTOR) {
-        O::store1(ldsX + (size_t)tid * a.L.xpitch + DK * O::ESZ, sv);
+        O::store1(ldsX + (size_t)tid * a.L.xpitch + O::off(DK), sv);
         // the policy means were parked over the head of this tile: restore the zero k padding of every row
         const int kp = (a.L.xpitch - 16) / O::ESZ;
-        for (int c = S; c < kp; ++c) O::store1(ldsX + (size_t)tid * a.L.xpitch + c * O::ESZ, 0.0f);
+        for (int c = S; c < kp; ++c) O::store1(ldsX + (size_t)tid * a.L.xpitch + O::off(c), 0.0f);
       }
     }
     const int dd = tid & 31, e0 = (tid >> 6) * (E / NW) + ((tid >> 5) & 1);
@@ -293,7 +300,7 @@ __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
         }
         const float sv = (float)h * d.s_hold;
         __builtin_nontemporal_store(sv, &obs_row[(size_t)(n0 + e) * S + 1 + D + dd]);
-        if (ACTOR) O::store1(ldsX + (size_t)e * a.L.xpitch + (DK + 1 + D + dd) * O::ESZ, sv);
+        if (ACTOR) O::store1(ldsX + (size_t)e * a.L.xpitch + O::off(DK + 1 + D + dd), sv);
       }
     }
   };
@@ -364,7 +371,7 @@ __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
 
   // Weight ring of the actor.  Layer 1's first blocks are requested a phase early (here, and after each step's
   // ledger) so that they are in flight while the observation is completed.
-  u32x4 ring[PDR][CTH];
+  typename O::Block ring[PDR][CTH];
   const float *lb3 = ldsBias + (ACTOR ? (a.actor.nct[0] + a.actor.nct[1]) * 32 : 0);
   if (ACTOR) prime<CTH, PDR>(ring, net.W[0], net.nkb[0], net.nct[0], wave * CTH, lane);
   // split schedule: layer-1 accumulators of group A, carried from the ledger phase of one step into the next
@@ -495,8 +502,12 @@ __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
       // its noise, valuation prices and market rows -- the slot in which B runs step (e))
     } else {
       if (ACTOR) {
+        auto w3 = [&](int kb0, int i) -> typename O::Block {
+          if constexpr (BF16) return LdsW3<true>{ldsW3, lane}(kb0, i);
+          else return w3r[i];
+        };
         mlp_tile<BF16, NW, CTH, false, NKB1, NKB2, true, true, KS, NBT>(
-            net, ring, ldsX, a.L.xpitch, ldsH, a.L.hpitch, ldsBias, ldsW3, tid,
+            net, ring, ldsX, a.L.xpitch, ldsH, a.L.hpitch, ldsBias, w3, tid,
             [&]() {
               fetch_step_inputs(t);
               fetch_valuation(rows_t);
@@ -769,17 +780,20 @@ struct FusedShape {
 
 FusedShape fused_shape(const pr_config &c) {
   const int S = 1 + 2 * c.n_stocks + c.n_stocks * c.n_ind;
-  const int KB = c.mlp_dtype == PR_MLP_BF16 ? 16 : 8;
+  const bool bf = c.mlp_dtype == PR_MLP_BF16;
   FusedShape f;
-  f.envs = c.mlp_dtype == PR_MLP_BF16 ? 64 : 32;
+  f.envs = bf ? 64 : 32;
   f.cth = (c.hidden / 32) / NW;
   f.nkb1 = f.nkb2 = 0;
   // the named shapes: 301 inputs with 512 hidden units in bf16 / 256 hidden units in fp32
   // (the split schedule of this instance runs the first 11 k-blocks of layer 1 before the portfolio columns
   // exist: they must all be indicator columns)
-  if (KB == 16 && f.cth == 2 && (S + 15) / 16 == 19 && c.hidden / 16 == 32 && c.n_stocks * c.n_ind >= 11 * 16)
+  if (bf && f.cth == 2 && (S + 15) / 16 == 19 && c.hidden / 16 == 32 && c.n_stocks * c.n_ind >= 11 * 16)
     f.nkb1 = 19, f.nkb2 = 32;
-  if (KB == 8 && f.cth == 1 && (S + 7) / 8 == 38 && c.hidden / 8 == 32) f.nkb1 = 38, f.nkb2 = 32;
+  if (!bf) {
+    f.nkb2 = 16;  // (256 hidden units)
+    if ((S + 15) / 16 == 19) f.nkb1 = 19;
+  }
   return f;
 }
 
@@ -787,24 +801,23 @@ FusedShape fused_shape(const pr_config &c) {
 FusedLayout fused_layout(const pr_config &c, bool with_actor) {
   const int D = c.n_stocks, S = 1 + 2 * D + D * c.n_ind, Hd = c.hidden;
   const bool bf = c.mlp_dtype == PR_MLP_BF16;
-  const int KB = bf ? 16 : 8, esz = bf ? 2 : 4;
   const FusedShape fs = fused_shape(c);
   const int E = fs.envs;
-  const int nkb1 = (S + KB - 1) / KB, nct = Hd / 32;
+  const int nkb1 = (S + 15) / 16, nct = Hd / 32;
   FusedLayout L;
-  L.xpitch = tile_pitch(nkb1 * KB, esz);
-  L.hpitch = tile_pitch(Hd, esz);
+  L.xpitch = tile_pitch(bf, nkb1);
+  L.hpitch = tile_pitch(bf, Hd / 16);
   // the env scratch (slots 16 B, executed shares, valuation prices, squared noise) must fit in the hidden tile
   const size_t env_scratch = (size_t)7 * E * kDp * 4;
   if ((size_t)E * L.hpitch < env_scratch) L.hpitch = (int32_t)(((env_scratch + E - 1) / E + 15) / 16 * 16);
   size_t off = (size_t)E * L.hpitch;
   L.off_x = (int32_t)off;
   size_t xbytes = (size_t)E * L.xpitch;
-  const size_t mu_bytes = with_actor ? (size_t)mu_planes(fs.nkb2) * E * MUP * 4 : 0;
+  const size_t mu_bytes = with_actor ? (size_t)mu_planes(bf, fs.nkb2) * E * MUP * 4 : 0;
   if (xbytes < mu_bytes) xbytes = (mu_bytes + 15) / 16 * 16;
   off += xbytes;
   L.off_w3 = (int32_t)off;
-  if (with_actor) off += (size_t)(Hd / KB) * 1024;  // output layer: one feature tile, Hd / KB k-blocks of 1 KiB
+  if (with_actor && bf) off += (size_t)(Hd / 16) * 1024;  // output layer: one feature tile, Hd / 16 k-blocks of 1 KiB
   L.off_bias = (int32_t)off;
   if (with_actor) off += (size_t)(2 * nct + 1) * 32 * 4;
   L.off_h = (int32_t)off;
@@ -873,7 +886,6 @@ hipError_t launch_rollout_fused(hipStream_t st, const pr_config &c, const EnvDim
   a.logp = out.logp;
   a.mu_out = mu_forced ? nullptr : out.mu;
   a.shares = out.shares;
-  const int DK = d.D * d.K;
   const bool with_actor = mu_forced == nullptr;
   a.L = fused_layout(c, with_actor);
   if (reinterpret_cast<uintptr_t>(ind) & 15u) return hipErrorInvalidValue;  // 16-byte indicator loads
@@ -881,9 +893,8 @@ hipError_t launch_rollout_fused(hipStream_t st, const pr_config &c, const EnvDim
   if (lds > kLdsMax) return hipErrorInvalidValue;
   const FusedShape fs = fused_shape(c);
   const unsigned blocks = (unsigned)(d.N / fs.envs);
-  const int KB = actor.bf16 ? 16 : 8, esz = actor.bf16 ? 2 : 4;
-  if (with_actor && ((actor.bf16 != 0) != (c.mlp_dtype == PR_MLP_BF16) || tile_pitch(actor.nkb[0] * KB, esz) != a.L.xpitch ||
-                     tile_pitch(actor.nkb[1] * KB, esz) > a.L.hpitch || actor.nkb[2] != actor.nkb[1] || actor.nct[2] != 1))
+  if (with_actor && ((actor.bf16 != 0) != (c.mlp_dtype == PR_MLP_BF16) || tile_pitch(actor.bf16, actor.nkb[0]) != a.L.xpitch ||
+                     tile_pitch(actor.bf16, actor.nkb[1]) > a.L.hpitch || actor.nkb[2] != actor.nkb[1] || actor.nct[2] != 1))
     return hipErrorInvalidValue;  // the packed network is not the one the layout was made for
   if (c.mlp_dtype == PR_MLP_BF16) {
     if (!with_actor) return launch_fused_inst<true, 64, false, 1, 0, 0>(st, a, blocks, lds);
@@ -891,9 +902,9 @@ hipError_t launch_rollout_fused(hipStream_t st, const pr_config &c, const EnvDim
     if (fs.cth == 2) return launch_fused_inst<true, 64, true, 2, 0, 0>(st, a, blocks, lds);
     if (fs.cth == 1) return launch_fused_inst<true, 64, true, 1, 0, 0>(st, a, blocks, lds);
   } else {
-    if (!with_actor) return launch_fused_inst<false, 32, false, 1, 0, 0>(st, a, blocks, lds);
-    if (fs.cth == 1 && fs.nkb1 == 38 && fs.nkb2 == 32) return launch_fused_inst<false, 32, true, 1, 38, 32>(st, a, blocks, lds);
-    if (fs.cth == 1) return launch_fused_inst<false, 32, true, 1, 0, 0>(st, a, blocks, lds);
+    if (!with_actor) return launch_fused_inst<false, 32, false, 1, 0, 16>(st, a, blocks, lds);
+    if (fs.cth == 1 && fs.nkb1 == 19) return launch_fused_inst<false, 32, true, 1, 19, 16>(st, a, blocks, lds);
+    if (fs.cth == 1) return launch_fused_inst<false, 32, true, 1, 0, 16>(st, a, blocks, lds);
   }
   return hipErrorInvalidValue;
 }

@@ -120,7 +120,7 @@ hipError_t launch_calib_probe(hipStream_t st, const int32_t role_of_wave[8], int
 // Packed network of one agent set.  Weight blocks are stored in the register
 // layout of the matrix-core instruction: block (kb, ct) holds, for the 64 lanes
 // of a wavefront, the 16 bytes lane l feeds as operand for output features
-// [32 ct, 32 ct + 32) and inputs [KB kb, KB kb + KB); KB = 16 (bf16) or 8 (fp32).
+// [32 ct, 32 ct + 32) and inputs [16 kb, 16 kb + 16); for fp32, three such blocks with the parts of the split values.
 // Blocks are ordered k-major: [kb][ct][lane].
 struct PackedNet {
   const void *W[3];       // packed weights per layer, agent-major

@@ -205,7 +205,8 @@ __global__ __launch_bounds__(kThreads, KI == 16 ? 2 : 4) void layer_kernel(Layer
         const float z = sum[4 * j + i] + bv[i];
         y[i] = HIDDEN ? tile::tanh_from_scaled(z * tile::kTwoLog2e) : a.out_tanh ? tile::tanh_accurate(z) : z;
       }
-      tile::Op<HIDDEN>::store4(stage + row * OPITCH + f * OESZ, y[0], y[1], y[2], y[3]);
+      if (HIDDEN) tile::Op<true>::store4(stage + row * OPITCH + f * OESZ, y[0], y[1], y[2], y[3]);
+      else *reinterpret_cast<f32x4 *>(stage + row * OPITCH + f * OESZ) = f32x4{y[0], y[1], y[2], y[3]};
     }
   }
   __syncthreads();

@@ -13,10 +13,10 @@
 // block is one 1-KiB fully coalesced load.  Accumulators (fp32) stay in
 // registers for a whole layer; bias + tanh are applied once, on the way to LDS.
 //
-// Operand types: bf16 (v_mfma_f32_32x32x16_bf16, k-block 16) or fp32
-// (v_mfma_f32_32x32x2_f32 x 4, k-block 8).  In both, lane l of a wavefront
-// feeds row/column (l % 32) and the k-half (l / 32) of a k-block: 16 bytes per
-// lane and operand.
+// Operand types: bf16 (v_mfma_f32_32x32x16_bf16, k-block 16) or fp32, whose
+// values travel as three bf16 numbers (six of the same instructions per
+// k-block).  In both, lane l of a wavefront feeds row/column (l % 32) and the
+// k-half (l / 32) of a k-block: 16 bytes per lane, operand and part.
 #include "pod_internal.h"
 #include <type_traits>
 
@@ -48,8 +48,9 @@ struct MlpArgs {
 };
 
 // B-operand block (ct, kb) of a packed layer for this lane.
-__device__ inline u32x4 load_b(const u32x4 *Wp, int nct, int ct, int kb, int lane) {
-  return Wp[((size_t)kb * nct + ct) * 64 + lane];
+template <class B>
+__device__ inline void load_b(B &b, const u32x4 *Wp, int nct, int ct, int kb, int lane) {
+  tile::fetch_w(b, Wp + ((size_t)kb * nct + ct) * (64 * tile::kPlanes<B>) + lane);
 }
 
 // acc += A(tile in LDS, all k-blocks) * B.  Wavefront-uniform control flow.
@@ -61,30 +62,28 @@ __device__ inline void layer_from_lds(f32x16 (&acc)[RT][CT], const unsigned char
   int cts[CT];
 #pragma unroll
   for (int c = 0; c < CT; ++c) cts[c] = min(ct0 + c, nct - 1);
-  u32x4 ring[PD][CT];
+  typename O::Block ring[PD][CT];
 #pragma unroll
   for (int s = 0; s < PD; ++s)
     if (s < nkb) {
 #pragma unroll
-      for (int c = 0; c < CT; ++c) ring[s][c] = load_b(Wp, nct, cts[c], s, lane);
+      for (int c = 0; c < CT; ++c) load_b(ring[s][c], Wp, nct, cts[c], s, lane);
     }
   for (int kb0 = 0; kb0 < nkb; kb0 += PD) {
 #pragma unroll
     for (int s = 0; s < PD; ++s) {
       const int kb = kb0 + s;
       if (kb < nkb) {
-        u32x4 a[RT];
+        typename O::Block a[RT];
 #pragma unroll
         for (int r = 0; r < RT; ++r)
-          a[r] = *reinterpret_cast<const u32x4 *>(ldsA + (size_t)(r * 32 + arow) * pitch + kb * 32 + 16 * g);
+          tile::fetch_x(a[r], ldsA + (size_t)(r * 32 + arow) * pitch + kb * O::KBYTES + O::HALF * g);
 #pragma unroll
         for (int r = 0; r < RT; ++r)
 #pragma unroll
           for (int c = 0; c < CT; ++c) O::mma(a[r], ring[s][c], acc[r][c]);
-        if (kb + PD < nkb) {
 #pragma unroll
-          for (int c = 0; c < CT; ++c) ring[s][c] = load_b(Wp, nct, cts[c], kb + PD, lane);
-        }
+        for (int c = 0; c < CT; ++c) load_b(ring[s][c], Wp, nct, cts[c], min(kb + PD, nkb - 1), lane);
       }
     }
   }
@@ -109,13 +108,13 @@ __device__ inline void layer_from_global(f32x16 (&acc)[RT][CT], unsigned char *l
   int cts[CT];
 #pragma unroll
   for (int c = 0; c < CT; ++c) cts[c] = min(ct0 + c, nct - 1);
-  u32x4 ring[PD][CT];
+  typename O::Block ring[PD][CT];
   if (active) {
 #pragma unroll
     for (int s = 0; s < PD; ++s)
       if (s < nkb) {
 #pragma unroll
-        for (int c = 0; c < CT; ++c) ring[s][c] = load_b(Wp, nct, cts[c], s, lane);
+        for (int c = 0; c < CT; ++c) load_b(ring[s][c], Wp, nct, cts[c], s, lane);
       }
   }
 
@@ -147,7 +146,7 @@ __device__ inline void layer_from_global(f32x16 (&acc)[RT][CT], unsigned char *l
     for (int i = 0; i < NPRE; ++i) {
       const int idx = tid + kThreads * i;
       const int row = idx / (KC / 4), col = 4 * (idx % (KC / 4));
-      O::store4(ldsX + buf * xbuf + (size_t)row * xpitch + col * O::ESZ, pre[i][0], pre[i][1], pre[i][2], pre[i][3]);
+      O::store4(ldsX + buf * xbuf + (size_t)row * xpitch + O::off(col), pre[i][0], pre[i][1], pre[i][2], pre[i][3]);
     }
   };
 
@@ -163,18 +162,17 @@ __device__ inline void layer_from_global(f32x16 (&acc)[RT][CT], unsigned char *l
       for (int s = 0; s < PD; ++s) {
         const int kb = ch * PD + s;
         if (kb < nkb) {
-          u32x4 a[RT];
+          typename O::Block a[RT];
 #pragma unroll
           for (int r = 0; r < RT; ++r)
-            a[r] = *reinterpret_cast<const u32x4 *>(buf + (size_t)(r * 32 + arow) * xpitch + s * 32 + 16 * g);
+            tile::fetch_x(a[r], buf + (size_t)(r * 32 + arow) * xpitch + s * O::KBYTES + O::HALF * g);
 #pragma unroll
           for (int r = 0; r < RT; ++r)
 #pragma unroll
             for (int c = 0; c < CT; ++c) O::mma(a[r], ring[s][c], acc[r][c]);
-          if (kb + PD < nkb) {
+          // (no branch around the refill: the compiler's wait for the matrix results would not count the path past it)
 #pragma unroll
-            for (int c = 0; c < CT; ++c) ring[s][c] = load_b(Wp, nct, cts[c], kb + PD, lane);
-          }
+          for (int c = 0; c < CT; ++c) load_b(ring[s][c], Wp, nct, cts[c], min(kb + PD, nkb - 1), lane);
         }
       }
     }
@@ -212,7 +210,7 @@ __device__ inline void epilogue_to_lds(const f32x16 (&acc)[RT][CT], const float 
           const int row = r * 32 + 8 * (i >> 2) + 4 * g + (i & 3);
           const float z = acc[r][c][i] + bv;
           const float hval = BF16 ? tile::tanh_from_scaled(z * tile::kTwoLog2e) : tanh_accurate(z);
-          O::store1(ldsH + (size_t)row * hpitch + col * O::ESZ, hval);
+          O::store1(ldsH + (size_t)row * hpitch + O::off(col), hval);
         }
     }
   }
@@ -240,14 +238,17 @@ __device__ inline void epilogue_to_global(const f32x16 (&acc)[RT][CT], const flo
   }
 }
 
+// k-blocks of weights in flight per wavefront, and of an input chunk: what the registers hold
+constexpr int chunk_blocks(bool bf16, int ct) { return ct >= (bf16 ? 8 : 4) ? 2 : 4; }
+
 // TAG only separates the symbol of the per-step launches (0) from that of the
 // whole-buffer launches (1) so that a profiler reports them as two kernels.
 template <bool BF16, int RT, int CTH, int CTO, int TAG>
 __global__ __launch_bounds__(kThreads) void mlp3_kernel(MlpArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
   constexpr int BM = 32 * RT;
-  constexpr int PDH = CTH >= 8 ? 2 : 4;
-  constexpr int PDO = CTO >= 8 ? 2 : 4;
+  constexpr int PDH = chunk_blocks(BF16, CTH);
+  constexpr int PDO = chunk_blocks(BF16, CTO);
   unsigned char *ldsH = lds;
   unsigned char *ldsX = lds + (size_t)BM * a.hpitch;
 
@@ -298,10 +299,10 @@ __global__ __launch_bounds__(kThreads) void mlp3_kernel(MlpArgs a) {
 // kernel that carries a row tile through all three layers leaves the rest idle.  Here a launch computes ONE
 // layer, tiled over rows x output features: workgroup (x, y) owns rows [32 x, 32 x + 32) and the four feature
 // tiles [4 y, 4 y + 4), one per wavefront, so rows / 32 x features / 128 workgroups run (512 for 2048 rows and
-// 1024 hidden units); the input rows are staged 16 k-blocks at a time, because with so little arithmetic per
+// 1024 hidden units); the input rows are staged 8 k-blocks at a time, because with so little arithmetic per
 // workgroup the time goes to the memory round trips, one per staged chunk.  Activations travel between the launches as
 // fp32 rows in global memory (they stay in L2).
-constexpr int kSplitPD = 16;  // k-blocks per staged chunk of the layer-per-launch kernel
+constexpr int kSplitPD = 8;   // k-blocks per staged chunk of the layer-per-launch kernel
 struct LayerArgs {
   const float *X;      // [rows, ldx]
   int64_t ldx, rows;
@@ -356,6 +357,8 @@ __global__ __launch_bounds__(kThreads) void dense_layer_kernel(LayerArgs a) {
 // the matrix cores, and dropped into the LDS input tile, converted to the
 // operand type, once layer 1 has finished reading it.
 constexpr int XPRE_MAX = 10;  // 16-byte loads per thread and tile
+// (an fp32 value takes three times the LDS of a bf16 one)
+constexpr int tile_rows(bool bf16) { return bf16 ? 64 : 32; }
 
 struct TileArgs {
   const float *X;
@@ -374,12 +377,12 @@ template <bool BF16, int NW, int CTH, int NKB1, int NKB2, int TAG>
 __global__ __launch_bounds__(NW * 64) void mlp_tiles_kernel(TileArgs a) {
   using namespace tile;
   using O = tile::Op<BF16>;
-  constexpr int NT = NW * 64;
+  constexpr int NT = NW * 64, BM = tile_rows(BF16), PL = kPlanes<typename O::Block>;
   extern __shared__ __align__(16) unsigned char lds[];
   unsigned char *ldsH = lds;
   unsigned char *ldsX = lds + (size_t)BM * a.hpitch;
   u32x4 *ldsW3 = reinterpret_cast<u32x4 *>(ldsX + (size_t)BM * a.xpitch);
-  float *ldsBias = reinterpret_cast<float *>(ldsW3 + (size_t)a.net.nkb[2] * 64);
+  float *ldsBias = reinterpret_cast<float *>(ldsW3 + (size_t)a.net.nkb[2] * (64 * PL));
   const int tid = threadIdx.x;
   const int S = a.S, G = a.groups;
   const int64_t ntiles = a.rows / BM;
@@ -422,7 +425,7 @@ __global__ __launch_bounds__(NW * 64) void mlp_tiles_kernel(TileArgs a) {
         const float o2 = shift == 0 ? v[2] : shift == 1 ? v[3] : 0.0f;
         const float o3 = shift == 0 ? v[3] : 0.0f;
         // the group that straddles S also writes the zero padding of the k columns
-        if (idx < ngroups) O::store4(ldsX + (size_t)row * a.xpitch + c4 * O::ESZ, o0, o1, o2, o3);
+        if (idx < ngroups) O::store4(ldsX + (size_t)row * a.xpitch + O::off(c4), o0, o1, o2, o3);
       }
     }
   };
@@ -430,7 +433,7 @@ __global__ __launch_bounds__(NW * 64) void mlp_tiles_kernel(TileArgs a) {
   // The first tile's rows are requested before anything else, so that they travel while the tile is cleared and
   // the first network's biases and output weights are staged; every tile's first weight blocks are requested
   // before the barrier that completes its inputs.
-  int64_t t = blockIdx.x;
+  int64_t t = xcd_index(blockIdx.x, gridDim.x);
   int staged_agent = -1;
   if (t < ntiles) fetch(t);
   // k columns beyond the last group (when Kp > 4 * groups) are never written by stash: clear the tile once
@@ -438,12 +441,12 @@ __global__ __launch_bounds__(NW * 64) void mlp_tiles_kernel(TileArgs a) {
   __syncthreads();
   if (t < ntiles) {
     const int agent = (int)(((a.row_base + t * BM) % a.N) / a.envs_per_agent);
-    stage_net<NT>(net_of(a.net, agent), ldsBias, ldsW3, tid);
+    stage_net<NT, PL>(net_of(a.net, agent), ldsBias, ldsW3, tid);
     staged_agent = agent;
     stash();
   }
   const int lane_p = tid & 63, ct0_p = __builtin_amdgcn_readfirstlane(tid >> 6) * CTH;
-  u32x4 ring[ring_depth(CTH)][CTH];
+  typename O::Block ring[ring_depth(CTH)][CTH];
   for (; t < ntiles; t += gridDim.x) {
     const int64_t row0 = t * BM;
     const int64_t tn = t + gridDim.x;
@@ -453,14 +456,14 @@ __global__ __launch_bounds__(NW * 64) void mlp_tiles_kernel(TileArgs a) {
     if (ct0_p < net.nct[0]) prime<CTH, ring_depth(CTH)>(ring, net.W[0], net.nkb[0], net.nct[0], ct0_p, lane_p);
     if (agent != staged_agent) {
       __syncthreads();  // the previous tile's output layer may still read its weights and biases
-      stage_net<NT>(net, ldsBias, ldsW3, tid);
+      stage_net<NT, PL>(net, ldsBias, ldsW3, tid);
       staged_agent = agent;
     }
     __syncthreads();  // input tile, biases and W3 complete; previous tile's output layer is done with ldsH
     const int O_dim = net.out_dim;
     float *Y = a.Y + row0 * O_dim;
-    mlp_tile<BF16, NW, CTH, false, NKB1, NKB2, true, false>(
-        net, ring, ldsX, a.xpitch, ldsH, a.hpitch, ldsBias, ldsW3, tid,
+    mlp_tile<BF16, NW, CTH, false, NKB1, NKB2, true, false, 1, BM / 32>(
+        net, ring, ldsX, a.xpitch, ldsH, a.hpitch, ldsBias, LdsW3<BF16>{ldsW3, lane_p}, tid,
         [&]() {
           if (more) fetch(tn);
         },
@@ -557,7 +560,7 @@ __global__ __launch_bounds__(NW * 64) void mlp_wide_kernel(WideArgs a) {
     const int O_dim = net.out_dim;
     u32x4 ring[PD][CTH];
     mlp_tile<true, NW, CTH, WIDE_OUT, 0, 0, true, false>(
-        net, ring, nullptr, 0, ldsH, a.hpitch, ldsBias, ldsW3, tid, [] {}, [] {},
+        net, ring, nullptr, 0, ldsH, a.hpitch, ldsBias, LdsW3<true>{ldsW3, lane}, tid, [] {}, [] {},
         [&](int b, int f, float y) {
           if (b < nrows) Y[(size_t)b * O_dim + f] = y;
         },
@@ -1035,25 +1038,24 @@ __global__ void pack_layer_kernel(const float *__restrict__ W, const float *__re
     const int kb = (int)((j >> 6) / nct);
     const int col = ct * 32 + (lane & 31), g = lane >> 5;
     const float *Wa = W + (size_t)agent * in_dim * out_dim;
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int k = kb * 16 + 8 * g + e;
+      const int ks = k < k_rot ? in_dim - k_rot + k : k - k_rot;
+      v[e] = (k < in_dim && col < out_dim) ? Wa[(size_t)ks * out_dim + col] : 0.0f;
+    }
+    bf16x8 *dst = reinterpret_cast<bf16x8 *>(Wp);
     if (bf16) {
-      __bf16 v[8];
+      bf16x8 p;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int k = kb * 16 + 8 * g + e;
-        const int ks = k < k_rot ? in_dim - k_rot + k : k - k_rot;
-        v[e] = (__bf16)((k < in_dim && col < out_dim) ? Wa[(size_t)ks * out_dim + col] : 0.0f);
-      }
-      __bf16 *dst = reinterpret_cast<__bf16 *>(Wp) + i * 8;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) dst[e] = v[e];
+      for (int e = 0; e < 8; ++e) p[e] = (__bf16)v[e];
+      dst[i] = p;
     } else {
-      float *dst = reinterpret_cast<float *>(Wp) + i * 4;
+      bf16x8 p[3];
+      split3(v, p);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int k = kb * 8 + 4 * g + e;
-        const int ks = k < k_rot ? in_dim - k_rot + k : k - k_rot;
-        dst[e] = (k < in_dim && col < out_dim) ? Wa[(size_t)ks * out_dim + col] : 0.0f;
-      }
+      for (int q = 0; q < 3; ++q) dst[(i >> 6) * 192 + q * 64 + lane] = p[q];
     }
   }
   const size_t nb = (size_t)P * nct * 32;
@@ -1064,7 +1066,7 @@ __global__ void pack_layer_kernel(const float *__restrict__ W, const float *__re
   }
 }
 
-int kblock(int bf16) { return bf16 ? 16 : 8; }
+constexpr int kBlock = 16;  // inputs per k-block
 
 struct Shape {
   int cth, cto;  // column tiles per wavefront, hidden / output layers
@@ -1077,7 +1079,7 @@ bool pick_shape(int Hd, int O, int bf16, Shape *s) {
   int cth = need_h <= 1 ? 1 : need_h <= 2 ? 2 : need_h <= 4 ? 4 : need_h <= 8 ? 8 : 0;
   int cto = need_o <= 1 ? 1 : need_o <= 4 ? 4 : 0;
   if (!cth || !cto) return false;
-  if (!bf16 && cth > 4) return false;       // fp32 hidden tile of 1024 columns exceeds LDS
+  if (!bf16 && cth > 4) return false;       // an fp32 hidden tile of 1024 columns exceeds LDS
   if (cto == 4 && cth < 4) return false;    // wide outputs only with wide hidden layers
   s->cth = cth;
   s->cto = cto;
@@ -1098,15 +1100,13 @@ bool mlp_supported(int S, int Hd, int O, int bf16) {
 int padded_out(int out_dim) { return (out_dim + 31) / 32 * 32; }
 
 size_t packed_weight_bytes(int in_dim, int out_dim, int bf16) {
-  const int KB = kblock(bf16);
-  const size_t nkb = (in_dim + KB - 1) / KB, nct = (out_dim + 31) / 32;
-  return nkb * nct * 64 * 16;
+  const size_t nkb = (in_dim + kBlock - 1) / kBlock, nct = (out_dim + 31) / 32;
+  return nkb * nct * 64 * 16 * (bf16 ? 1 : 3);
 }
 
 hipError_t launch_pack_layer(hipStream_t st, const float *W, const float *b, int P, int in_dim, int out_dim, int bf16,
                              int k_rot, void *Wp, float *bp) {
-  const int KB = kblock(bf16);
-  const int nkb = (in_dim + KB - 1) / KB, nct = (out_dim + 31) / 32;
+  const int nkb = (in_dim + kBlock - 1) / kBlock, nct = (out_dim + 31) / 32;
   const size_t n = (size_t)P * nct * nkb * 64;
   const size_t nb = (size_t)P * nct * 32;
   const size_t total = n > nb ? n : nb;
@@ -1115,7 +1115,7 @@ hipError_t launch_pack_layer(hipStream_t st, const float *W, const float *b, int
   return hipGetLastError();
 }
 
-template <bool BF16, int CTH, int CTO, int TAG, int RT = 2>
+template <bool BF16, int CTH, int CTO, int TAG, int RT>
 static hipError_t launch_tagged(hipStream_t st, const MlpArgs &a, unsigned blocks, size_t lds) {
   constexpr auto kern = mlp3_kernel<BF16, RT, CTH, CTO, TAG>;
   const hipError_t e = allow_full_lds<kern>();
@@ -1124,10 +1124,10 @@ static hipError_t launch_tagged(hipStream_t st, const MlpArgs &a, unsigned block
   return hipGetLastError();
 }
 
-template <bool BF16, int CTH, int CTO>
+template <bool BF16, int CTH, int CTO, int RT>
 static hipError_t launch_one(hipStream_t st, const MlpArgs &a, unsigned blocks, size_t lds) {
-  return a.rows > a.N ? launch_tagged<BF16, CTH, CTO, 1>(st, a, blocks, lds)
-                      : launch_tagged<BF16, CTH, CTO, 0>(st, a, blocks, lds);
+  return a.rows > a.N ? launch_tagged<BF16, CTH, CTO, 1, RT>(st, a, blocks, lds)
+                      : launch_tagged<BF16, CTH, CTO, 0, RT>(st, a, blocks, lds);
 }
 
 
@@ -1170,8 +1170,8 @@ static bool try_launch_tiles(hipStream_t st, const PackedNet &net, int64_t rows,
   const int nct = net.nct[0];
   const int NW = nct >= 8 ? 8 : 4;
   const int cth = (nct + NW - 1) / NW;
-  if ((tile::BM * G + NW * 64 - 1) / (NW * 64) > XPRE_MAX) return false;
-  const int esz = net.bf16 ? 2 : 4, KB = kblock(net.bf16);
+  const int bm = tile_rows(net.bf16);
+  if ((bm * G + NW * 64 - 1) / (NW * 64) > XPRE_MAX) return false;
   TileArgs a;
   a.X = X;
   a.rows = rows;
@@ -1183,18 +1183,18 @@ static bool try_launch_tiles(hipStream_t st, const PackedNet &net, int64_t rows,
   a.S = S;
   a.groups = G;
   a.g_magic = (int32_t)(uint32_t)((0x100000000ull + (uint64_t)G - 1) / (uint64_t)G);
-  a.xpitch = tile::tile_pitch(net.nkb[0] * KB, esz);
-  a.hpitch = tile::tile_pitch(Hd, esz);
-  const size_t lds = (size_t)tile::BM * (a.xpitch + a.hpitch) + (size_t)net.nkb[2] * 1024 +
+  a.xpitch = tile::tile_pitch(net.bf16, net.nkb[0]);
+  a.hpitch = tile::tile_pitch(net.bf16, net.nkb[1]);
+  const size_t lds = (size_t)bm * (a.xpitch + a.hpitch) + (size_t)net.nkb[2] * (net.bf16 ? 1024 : 3072) +
                      (size_t)(net.nct[0] + net.nct[1] + net.nct[2]) * 32 * 4;
   if (lds > 160 * 1024) return false;
-  const int64_t ntiles = rows / tile::BM;
+  const int64_t ntiles = rows / bm;
   const unsigned blocks = (unsigned)(ntiles < compute_units() ? ntiles : compute_units());
   const bool bf = net.bf16 != 0;
-  // shapes of the named workloads get straight-line k loops (S = 301: 19 bf16 / 38 fp32 k-blocks)
+  // shapes of the named workloads get straight-line k loops (S = 301: 19 k-blocks)
   if (bf && NW == 8 && cth == 2 && net.nkb[0] == 19 && net.nkb[1] == 32) *err = launch_tiles<true, 8, 2, 19, 32>(st, a, blocks, lds);
-  else if (!bf && NW == 8 && cth == 1 && net.nkb[0] == 38 && net.nkb[1] == 32) *err = launch_tiles<false, 8, 1, 38, 32>(st, a, blocks, lds);
-  else if (NW == 8 && cth == 2) *err = bf ? launch_tiles<true, 8, 2>(st, a, blocks, lds) : launch_tiles<false, 8, 2>(st, a, blocks, lds);
+  else if (!bf && NW == 8 && cth == 1 && net.nkb[0] == 19 && net.nkb[1] == 16) *err = launch_tiles<false, 8, 1, 19, 16>(st, a, blocks, lds);
+  else if (NW == 8 && cth == 2 && bf) *err = launch_tiles<true, 8, 2>(st, a, blocks, lds);
   else if (NW == 8 && cth == 1) *err = bf ? launch_tiles<true, 8, 1>(st, a, blocks, lds) : launch_tiles<false, 8, 1>(st, a, blocks, lds);
   else if (NW == 4 && cth == 1) *err = bf ? launch_tiles<true, 4, 1>(st, a, blocks, lds) : launch_tiles<false, 4, 1>(st, a, blocks, lds);
   else if (NW == 4 && cth == 2) *err = bf ? launch_tiles<true, 4, 2>(st, a, blocks, lds) : launch_tiles<false, 4, 2>(st, a, blocks, lds);
@@ -1231,7 +1231,7 @@ static bool try_launch_value(hipStream_t st, const PackedNet &net, int64_t rows,
   a.S = S;
   a.groups = net.nkb[0] * 4;
   a.g_magic = (uint32_t)((0x100000000ull + (uint64_t)a.groups - 1) / (uint64_t)a.groups);
-  a.xpitch = tile::tile_pitch(net.nkb[0] * 16, 2);
+  a.xpitch = tile::tile_pitch<true>(net.nkb[0]);
   // LDS: hidden half A | input tile or hidden half B | b1, b2 | output weights | partial sums
   size_t off = (size_t)VBM * VHPITCH;
   a.off_xb = (int32_t)off;
@@ -1276,8 +1276,8 @@ static bool try_launch_wide(hipStream_t st, const PackedNet &net, int64_t rows, 
   WideArgs a;
   a.X = X, a.ldx = ldx, a.rows = rows, a.row_base = row_base, a.Y = Y, a.net = net, a.N = N;
   a.envs_per_agent = envs_per_agent, a.S = net.in_dim[0];
-  a.cpitch = tile::tile_pitch(cc, 2);
-  a.hpitch = tile::tile_pitch(Hd, 2);
+  a.cpitch = tile::tile_pitch<true>(cc / 16);
+  a.hpitch = tile::tile_pitch<true>(Hd / 16);
   size_t lds = (size_t)tile::BM * a.hpitch + 2 * (size_t)tile::BM * a.cpitch +
                (size_t)(net.nct[0] + net.nct[1] + net.nct[2]) * 32 * 4;
   // the output layer's weights are streamed when it has several feature tiles, or when they do not fit next to a
@@ -1322,7 +1322,7 @@ static bool try_launch_split(hipStream_t st, const PackedNet &net, int64_t rows,
     a.in_dim = net.in_dim[l], a.out_dim = net.out_dim[l], a.nkb = net.nkb[l], a.nct = net.nct[l];
     a.act = l < 2 || net.out_tanh;
     a.N = N, a.envs_per_agent = envs_per_agent;
-    a.xpitch = kSplitPD * kblock(0) * 4 + 16;
+    a.xpitch = tile::tile_pitch<false>(kSplitPD);
     const size_t lds = 2 * (size_t)32 * a.xpitch;
     const dim3 grid((unsigned)tiles, (unsigned)((net.nct[l] + kWaves - 1) / kWaves));
     *err = allow_full_lds<dense_layer_kernel<1, kSplitPD>>();
@@ -1375,8 +1375,6 @@ hipError_t launch_mlp(hipStream_t st, const PackedNet &net, int64_t rows, const 
     hipError_t terr = hipSuccess;
     if (try_launch_wide(st, net, rows, row_offset, X, ldx, Y, N, envs_per_agent, &terr)) return terr;
   }
-  const int esz = net.bf16 ? 2 : 4, KB = kblock(net.bf16);
-  const int pd = s.cth >= 8 ? 2 : 4;
   MlpArgs a;
   a.X = X;
   a.ldx = ldx;
@@ -1386,31 +1384,28 @@ hipError_t launch_mlp(hipStream_t st, const PackedNet &net, int64_t rows, const 
   a.N = N;
   a.envs_per_agent = envs_per_agent;
   a.row_offset = row_offset;
-  a.xpitch = pd * KB * esz + 16;
-  a.hpitch = net.out_dim[0] * esz + 16;
-  const size_t lds = (size_t)BM * a.hpitch + 2 * (size_t)BM * a.xpitch;
+  a.xpitch = tile::tile_pitch(net.bf16, chunk_blocks(net.bf16, s.cth));
+  a.hpitch = tile::tile_pitch(net.bf16, net.nkb[1]);
+  // fp32 networks: 32-row tiles when the hidden tile of 64 rows does not fit in LDS, and on fewer 64-row tiles than
+  // compute units (4096 envs per step: twice as many compute units at work)
+  const int rt = !net.bf16 && (s.cth == 4 || (rows > 32 && (rows + BM - 1) / BM < compute_units())) ? 1 : 2;
+  const size_t lds = (size_t)(32 * rt) * (a.hpitch + 2 * a.xpitch);
   if (lds > 160 * 1024) return hipErrorInvalidValue;
-  const unsigned blocks = (unsigned)((rows + BM - 1) / BM);
-  // fp32 networks on fewer 64-row tiles than compute units (4096 envs per step): 32-row tiles put twice as many
-  // compute units to work, and the fp32 matrix time per tile halves
-  if (!net.bf16 && s.cto == 1 && rows > 32 && (rows + BM - 1) / BM < compute_units()) {
-    const unsigned blocks32 = (unsigned)((rows + 31) / 32);
-    if (s.cth == 1) return launch_tagged<false, 1, 1, 0, 1>(st, a, blocks32, lds);
-    if (s.cth == 2) return launch_tagged<false, 2, 1, 0, 1>(st, a, blocks32, lds);
-    if (s.cth == 4) return launch_tagged<false, 4, 1, 0, 1>(st, a, blocks32, lds);
-  }
-#define POD_CASE(B, H, O_) \
-  if ((net.bf16 != 0) == B && s.cth == H && s.cto == O_) return launch_one<B, H, O_>(st, a, blocks, lds);
-  POD_CASE(true, 1, 1)
-  POD_CASE(true, 2, 1)
-  POD_CASE(true, 4, 1)
-  POD_CASE(true, 4, 4)
-  POD_CASE(true, 8, 1)
-  POD_CASE(true, 8, 4)
-  POD_CASE(false, 1, 1)
-  POD_CASE(false, 2, 1)
-  POD_CASE(false, 4, 1)
-  POD_CASE(false, 4, 4)
+  const unsigned blocks = (unsigned)((rows + 32 * rt - 1) / (32 * rt));
+#define POD_CASE(B, H, O_, RT_) \
+  if ((net.bf16 != 0) == B && s.cth == H && s.cto == O_ && rt == RT_) return launch_one<B, H, O_, RT_>(st, a, blocks, lds);
+  POD_CASE(true, 1, 1, 2)
+  POD_CASE(true, 2, 1, 2)
+  POD_CASE(true, 4, 1, 2)
+  POD_CASE(true, 4, 4, 2)
+  POD_CASE(true, 8, 1, 2)
+  POD_CASE(true, 8, 4, 2)
+  POD_CASE(false, 1, 1, 1)
+  POD_CASE(false, 1, 1, 2)
+  POD_CASE(false, 2, 1, 1)
+  POD_CASE(false, 2, 1, 2)
+  POD_CASE(false, 4, 1, 1)
+  POD_CASE(false, 4, 4, 1)
 #undef POD_CASE
   return hipErrorInvalidValue;
 }

@@ -8,8 +8,8 @@
 // 32x32 accumulator a lane then owns ONE batch row (l % 32) and, per group
 // j = 0..3, FOUR CONSECUTIVE output features 8 j + 4 (l / 32) + {0..3}.  Four
 // consecutive features are four consecutive k of the next layer, so the
-// epilogue packs them and writes them with a single 8-byte (bf16) or 16-byte
-// (fp32) LDS store into the row-major [batch][feature] tile the next layer
+// epilogue packs them and writes them with a single 8-byte LDS store (bf16;
+// fp32: one per part of the split values) into the row-major [batch][feature] tile the next layer
 // reads its B operand from.
 //
 // The NW wavefronts of a workgroup split the output features; each streams
@@ -21,12 +21,12 @@
 #pragma once
 
 #include "pod_internal.h"
+#include "pod_split3.h"
 #include <type_traits>
 
 namespace pod {
 namespace tile {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -35,13 +35,39 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int BM = 64;  // batch rows per tile (two 32-row MFMA tiles)
 
+// An operand block of one lane: eight consecutive k of one row or output feature.  bf16: 16 bytes.  fp32: the three bf16
+// numbers every value is the exact sum of (pod_split3.h), one 16-byte piece per part.
+struct Blk3 {
+  u32x4 p[3];
+};
+template <class B>
+inline constexpr int kPlanes = 1;
+template <>
+inline constexpr int kPlanes<Blk3> = 3;
+
+// weights: the parts of a block are 64 lanes apart; activations: next to each other in the row
+__device__ inline void fetch_w(u32x4 &b, const u32x4 *p) { b = p[0]; }
+__device__ inline void fetch_w(Blk3 &b, const u32x4 *p) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) b.p[i] = p[64 * i];
+}
+__device__ inline void fetch_x(u32x4 &b, const unsigned char *p) { b = *reinterpret_cast<const u32x4 *>(p); }
+__device__ inline void fetch_x(Blk3 &b, const unsigned char *p) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) b.p[i] = *reinterpret_cast<const u32x4 *>(p + 16 * i);
+}
+
+// Operand types.  KB: inputs per k-block; ESZ: LDS bytes per value; KBYTES, HALF: bytes of a k-block and of half of one
+// in an activation row; off(c): where column c starts.
 template <bool BF16>
 struct Op;
 
 template <>
 struct Op<true> {
   static constexpr int KB = 16;
-  static constexpr int ESZ = 2;
+  static constexpr int ESZ = 2, KBYTES = 32, HALF = 16;
+  typedef u32x4 Block;
+  static __host__ __device__ inline int off(int c) { return 2 * c; }
   // acc += W_block (features x k) * X_block (k x batch)
   static __device__ inline void mma(const u32x4 &w, const u32x4 &x, f32x16 &c) {
     c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c, 0, 0,
@@ -54,21 +80,35 @@ struct Op<true> {
   }
 };
 
+// fp32 networks: the matrix cores take bf16 sixteen times as fast as fp32, so the six products that carry an fp32
+// product to better than its own rounding cost 3/8 of the fp32 instructions (192 cycles against 512 per 32 x 32 x 16).
+// Measured with 256 hidden units: critic over 8.5 million rows of 64 agents 35.1 -> 19.4 ms, 128 persistent steps of
+// 65536 envs 27.2 -> 19.6 ms; critic over 2.1 million rows of one agent 8.2 -> 4.5 ms.
 template <>
 struct Op<false> {
-  static constexpr int KB = 8;
-  static constexpr int ESZ = 4;
-  static __device__ inline void mma(const u32x4 &w, const u32x4 &x, f32x16 &c) {
-    const f32x4 wf = __builtin_bit_cast(f32x4, w), xf = __builtin_bit_cast(f32x4, x);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[0], xf[0], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[1], xf[1], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[2], xf[2], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[3], xf[3], c, 0, 0, 0);
+  static constexpr int KB = 16;
+  static constexpr int ESZ = 6, KBYTES = 96, HALF = 48;
+  typedef Blk3 Block;
+  static __host__ __device__ inline int off(int c) { return (c >> 3) * 48 + (c & 7) * 2; }
+  static __device__ inline void mma(const Blk3 &w, const Blk3 &x, f32x16 &c) {
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w.p[kSplitA[i]]),
+                                                  __builtin_bit_cast(bf16x8, x.p[kSplitB[i]]), c, 0, 0, 0);
   }
-  static __device__ inline void store1(unsigned char *p, float v) { *reinterpret_cast<float *>(p) = v; }
+  static __device__ inline void store1(unsigned char *p, float v) {
+    uint32_t s[3];
+    split3_pair(v, 0.0f, s[0], s[1], s[2]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) *reinterpret_cast<uint16_t *>(p + 16 * i) = (uint16_t)s[i];
+  }
+  // (four columns from a multiple of four)
   static __device__ inline void store4(unsigned char *p, float a, float b, float c, float d) {
-    f32x4 v = {a, b, c, d};
-    *reinterpret_cast<f32x4 *>(p) = v;
+    uint32_t lo[3], hi[3];
+    split3_pair(a, b, lo[0], lo[1], lo[2]);
+    split3_pair(c, d, hi[0], hi[1], hi[2]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) *reinterpret_cast<u32x2 *>(p + 16 * i) = u32x2{lo[i], hi[i]};
   }
 };
 
@@ -124,13 +164,14 @@ __device__ inline u32x4 load_w(const u32x4 *W, int nct, int ct, int kb, int lane
 }
 
 // Fill the ring with k-blocks 0..PD-1 of a layer (feature tiles ct0..ct0+CT-1, clamped to the last tile).
-template <int CT, int PD>
-__device__ inline void prime(u32x4 (&ring)[PD][CT], const u32x4 *W, int nkb, int nct, int ct0, int lane) {
+template <int CT, int PD, class B>
+__device__ inline void prime(B (&ring)[PD][CT], const u32x4 *W, int nkb, int nct, int ct0, int lane) {
 #pragma unroll
   for (int s = 0; s < PD; ++s)
     if (s < nkb) {
 #pragma unroll
-      for (int c = 0; c < CT; ++c) ring[s][c] = load_w(W, nct, min(ct0 + c, nct - 1), s, lane);
+      for (int c = 0; c < CT; ++c)
+        fetch_w(ring[s][c], W + ((size_t)s * nct + min(ct0 + c, nct - 1)) * (64 * kPlanes<B>) + lane);
     }
 }
 
@@ -139,29 +180,30 @@ __device__ inline void prime(u32x4 (&ring)[PD][CT], const u32x4 *W, int nkb, int
 // The main loop has no branches (refills past the end re-read the last block), so the compiler's wait
 // counters stay exact and PD k-blocks of weights are really in flight behind the matrix instructions.
 template <bool BF16, int CT, int NBT, int PD>
-__device__ inline void mma_layer(f32x16 (&acc)[CT][NBT], u32x4 (&ring)[PD][CT], const unsigned char *ldsX, int pitch,
+__device__ inline void mma_layer(f32x16 (&acc)[CT][NBT], typename Op<BF16>::Block (&ring)[PD][CT], const unsigned char *ldsX, int pitch,
                                  int nkb, const u32x4 *W, int nct, int ct0, int bt0, int lane) {
   using O = Op<BF16>;
+  constexpr int NP = 64 * kPlanes<typename O::Block>;
   const int brow = lane & 31, g = lane >> 5;
-  const unsigned char *xbase = ldsX + (size_t)(bt0 * 32 + brow) * pitch + 16 * g;
+  const unsigned char *xbase = ldsX + (size_t)(bt0 * 32 + brow) * pitch + O::HALF * g;
   const u32x4 *wp[CT];
 #pragma unroll
-  for (int c = 0; c < CT; ++c) wp[c] = W + (size_t)min(ct0 + c, nct - 1) * 64 + lane;
+  for (int c = 0; c < CT; ++c) wp[c] = W + (size_t)min(ct0 + c, nct - 1) * NP + lane;
   int kb0 = 0;
   for (; kb0 + PD <= nkb; kb0 += PD) {
 #pragma unroll
     for (int s = 0; s < PD; ++s) {
       const int kb = kb0 + s;
-      u32x4 x[NBT];
+      typename O::Block x[NBT];
 #pragma unroll
-      for (int t = 0; t < NBT; ++t) x[t] = *reinterpret_cast<const u32x4 *>(xbase + (size_t)t * 32 * pitch + kb * 32);
+      for (int t = 0; t < NBT; ++t) fetch_x(x[t], xbase + (size_t)t * 32 * pitch + kb * O::KBYTES);
 #pragma unroll
       for (int c = 0; c < CT; ++c)
 #pragma unroll
         for (int t = 0; t < NBT; ++t) O::mma(ring[s][c], x[t], acc[c][t]);
       const int kn = min(kb + PD, nkb - 1);
 #pragma unroll
-      for (int c = 0; c < CT; ++c) ring[s][c] = wp[c][(size_t)kn * nct * 64];
+      for (int c = 0; c < CT; ++c) fetch_w(ring[s][c], wp[c] + (size_t)kn * nct * NP);
       // keep each refill right behind the matrix instructions that freed its slot: left alone, the
       // scheduler sinks all refills to the end of the loop body and the ring is one k-group deep
       __builtin_amdgcn_sched_barrier(0);
@@ -172,9 +214,9 @@ __device__ inline void mma_layer(f32x16 (&acc)[CT][NBT], u32x4 (&ring)[PD][CT], 
   for (int s = 0; s < PD - 1; ++s) {
     if (s < rem) {
       const int kb = kb0 + s;
-      u32x4 x[NBT];
+      typename O::Block x[NBT];
 #pragma unroll
-      for (int t = 0; t < NBT; ++t) x[t] = *reinterpret_cast<const u32x4 *>(xbase + (size_t)t * 32 * pitch + kb * 32);
+      for (int t = 0; t < NBT; ++t) fetch_x(x[t], xbase + (size_t)t * 32 * pitch + kb * O::KBYTES);
 #pragma unroll
       for (int c = 0; c < CT; ++c)
 #pragma unroll
@@ -191,6 +233,7 @@ __device__ inline void mma_layer_range(f32x16 (&acc)[CT][NBT], u32x4 (&ring)[PD]
                                        int pitch, int kb_lo, int kb_hi, int nkb, const u32x4 *W, int nct, int ct0,
                                        int bt0, int lane) {
   using O = Op<BF16>;
+  static_assert(BF16, "bf16 only");
   const int brow = lane & 31, g = lane >> 5;
   const unsigned char *xbase = ldsX + (size_t)(bt0 * 32 + brow) * pitch + 16 * g;
   const u32x4 *wp[CT];
@@ -236,29 +279,30 @@ __device__ inline void mma_layer_range(f32x16 (&acc)[CT][NBT], u32x4 (&ring)[PD]
 // weight load is placed exactly (across a loop back-edge the compiler falls back to waiting for all loads,
 // which exposes one L2 round trip per loop iteration).
 template <bool BF16, int CT, int NBT, int PD, int NKB>
-__device__ inline void mma_layer_static(f32x16 (&acc)[CT][NBT], u32x4 (&ring)[PD][CT], const unsigned char *ldsX,
+__device__ inline void mma_layer_static(f32x16 (&acc)[CT][NBT], typename Op<BF16>::Block (&ring)[PD][CT], const unsigned char *ldsX,
                                         int pitch, const u32x4 *W, int nct, int ct0, int bt0, int lane) {
   using O = Op<BF16>;
+  constexpr int NP = 64 * kPlanes<typename O::Block>;
   const int brow = lane & 31, g = lane >> 5;
-  const unsigned char *xbase = ldsX + (size_t)(bt0 * 32 + brow) * pitch + 16 * g;
+  const unsigned char *xbase = ldsX + (size_t)(bt0 * 32 + brow) * pitch + O::HALF * g;
   const u32x4 *wp[CT];
 #pragma unroll
-  for (int c = 0; c < CT; ++c) wp[c] = W + (size_t)min(ct0 + c, nct - 1) * 64 + lane;
+  for (int c = 0; c < CT; ++c) wp[c] = W + (size_t)min(ct0 + c, nct - 1) * NP + lane;
 #pragma unroll
   for (int kb = 0; kb < NKB; ++kb) {
     constexpr int dummy = 0;
     (void)dummy;
     const int s = kb % PD;
-    u32x4 x[NBT];
+    typename O::Block x[NBT];
 #pragma unroll
-    for (int t = 0; t < NBT; ++t) x[t] = *reinterpret_cast<const u32x4 *>(xbase + (size_t)t * 32 * pitch + kb * 32);
+    for (int t = 0; t < NBT; ++t) fetch_x(x[t], xbase + (size_t)t * 32 * pitch + kb * O::KBYTES);
 #pragma unroll
     for (int c = 0; c < CT; ++c)
 #pragma unroll
       for (int t = 0; t < NBT; ++t) O::mma(ring[s][c], x[t], acc[c][t]);
     if (kb + PD < NKB) {
 #pragma unroll
-      for (int c = 0; c < CT; ++c) ring[s][c] = wp[c][(size_t)(kb + PD) * nct * 64];
+      for (int c = 0; c < CT; ++c) fetch_w(ring[s][c], wp[c] + (size_t)(kb + PD) * nct * NP);
     }
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -275,6 +319,7 @@ __device__ inline void mma_range_static(f32x16 (&acc)[CT][NBT], u32x4 (&ring)[PD
                                         int pitch, const u32x4 *W, int nct, int kbw0, const u32x4 *Wn, int nctn,
                                         int kbn0, int ct0, int bt0, int lane) {
   using O = Op<BF16>;
+  static_assert(BF16, "bf16 only");
   static_assert(NKB >= PD, "a range must be at least as long as the ring");
   const int brow = lane & 31, g = lane >> 5;
   const unsigned char *xbase = ldsX + (size_t)(bt0 * 32 + brow) * pitch + 16 * g;
@@ -428,7 +473,7 @@ __device__ inline void epilogue_hidden(const f32x16 (&acc)[CT][NBT], const float
             else
               h[i] = tanh_accurate(acc[c][t][4 * j + i] + bv[i]);
           }
-          O::store4(ldsH + (size_t)((bt0 + t) * 32 + brow) * hpitch + f0 * O::ESZ, h[0], h[1], h[2], h[3]);
+          O::store4(ldsH + (size_t)((bt0 + t) * 32 + brow) * hpitch + O::off(f0), h[0], h[1], h[2], h[3]);
         }
       }
     }
@@ -468,8 +513,8 @@ __device__ inline void epilogue_out(const f32x16 (&acc)[CT][NBT], const float *b
 }
 
 // Copy one agent's three bias vectors (padded to multiples of 32) into LDS: [b1 | b2 | b3], and, when the
-// output layer is a single feature tile, its packed weights (nkb[2] blocks of 1 KiB) into ldsW3.
-template <int NT>
+// output layer is a single feature tile, its packed weights (nkb[2] blocks of PL KiB) into ldsW3.
+template <int NT, int PL = 1>
 __device__ inline void stage_net(const Net &net, float *ldsBias, u32x4 *ldsW3, int tid) {
   int off = 0;
 #pragma unroll
@@ -480,7 +525,7 @@ __device__ inline void stage_net(const Net &net, float *ldsBias, u32x4 *ldsW3, i
   }
   if (ldsW3 && net.nct[2] == 1) {
     // four loads in flight per thread before the first LDS store (a plain copy loop pays one round trip per pass)
-    const int n3 = net.nkb[2] * 64;
+    const int n3 = net.nkb[2] * (64 * PL);
     for (int base = tid; base < n3; base += 4 * NT) {
       u32x4 v[4];
 #pragma unroll
@@ -492,25 +537,37 @@ __device__ inline void stage_net(const Net &net, float *ldsBias, u32x4 *ldsW3, i
   }
 }
 
-// Output layer with one feature tile: weights from LDS (block kb = 64 lanes x 16 B), activations from ldsH.
+// Output layer with one feature tile: activations from ldsH, weights from w3(kb0, i): block kb0 + i (i a compile-time
+// number when NKB > 0).  By default they lie in LDS.
 // NKB > 0: straight-line code over a compile-time number of k-blocks with two accumulators (even / odd
 // k-blocks), which halves the dependent chain of matrix instructions and lets the LDS reads run ahead.
 // kb0: first k-block (NKB > 0 only), for callers that split the k range over several wavefronts.
-template <bool BF16, int NKB>
-__device__ inline void mma_out_lds(f32x16 &acc, const u32x4 *ldsW3, const unsigned char *ldsH, int hpitch, int nkb,
-                                   int bt, int lane, int kb0 = 0) {
+template <bool BF16>
+struct LdsW3 {
+  const u32x4 *base;
+  int lane;
+  __device__ inline typename Op<BF16>::Block operator()(int kb0, int i) const {
+    typename Op<BF16>::Block b;
+    fetch_w(b, base + (kb0 + i) * (64 * kPlanes<typename Op<BF16>::Block>) + lane);
+    return b;
+  }
+};
+
+template <bool BF16, int NKB, class W3>
+__device__ inline void mma_out(f32x16 &acc, const W3 &w3, const unsigned char *ldsH, int hpitch, int nkb, int bt, int lane,
+                               int kb0 = 0) {
   using O = Op<BF16>;
   const int brow = lane & 31, g = lane >> 5;
-  const unsigned char *xbase = ldsH + (size_t)(bt * 32 + brow) * hpitch + 16 * g + (NKB > 0 ? kb0 * 32 : 0);
-  if (NKB > 0) ldsW3 += kb0 * 64;
+  const unsigned char *xbase = ldsH + (size_t)(bt * 32 + brow) * hpitch + O::HALF * g + (NKB > 0 ? kb0 * O::KBYTES : 0);
   if (NKB > 0) {
     f32x16 acc2;
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc2[i] = 0.0f;
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb) {
-      const u32x4 wv = ldsW3[kb * 64 + lane];
-      const u32x4 xv = *reinterpret_cast<const u32x4 *>(xbase + kb * 32);
+      const typename O::Block wv = w3(kb0, kb);
+      typename O::Block xv;
+      fetch_x(xv, xbase + kb * O::KBYTES);
       if (kb & 1)
         O::mma(wv, xv, acc2);
       else
@@ -520,18 +577,19 @@ __device__ inline void mma_out_lds(f32x16 &acc, const u32x4 *ldsW3, const unsign
     for (int i = 0; i < 16; ++i) acc[i] += acc2[i];
   } else {
     for (int kb = 0; kb < nkb; ++kb) {
-      const u32x4 wv = ldsW3[kb * 64 + lane];
-      const u32x4 xv = *reinterpret_cast<const u32x4 *>(xbase + kb * 32);
+      const typename O::Block wv = w3(0, kb);
+      typename O::Block xv;
+      fetch_x(xv, xbase + kb * O::KBYTES);
       O::mma(wv, xv, acc);
     }
   }
 }
 
 // Layers 1-3 for the 64-row tile whose layer-1 input already sits in ldsX (row-major, xpitch bytes per row,
-// padded k columns zero).  ldsH receives the hidden tiles; ldsBias / ldsW3 as filled by stage_net.
+// padded k columns zero).  ldsH receives the hidden tiles; ldsBias as filled by stage_net.
 // NW wavefronts (4 or 8); CTH = feature tiles per wavefront in the hidden layers; NKB1 / NKB2 = k-blocks
 // of layers 1 / 2 when known at compile time (0: read them from `net`).
-// WIDE_OUT = false: the output layer has at most 32 features (one feature tile, weights in ldsW3).
+// WIDE_OUT = false: the output layer has at most 32 features (one feature tile, weights from w3, see mma_out).
 // Hooks: early() runs after layer 1's matrix work, before its epilogue -- the place to issue global loads that
 // are not needed soon.  late() runs once layer 2's epilogue is complete workgroup-wide; ldsX has been free
 // since layer 1 and may be refilled there.
@@ -550,10 +608,10 @@ struct WholeTileLayer1 {};
 // NBT: 32-row batch tiles of the tile (2: the usual 64 rows; 1: a 32-row tile, for shapes whose 64-row tiles do not
 // fit in LDS).
 template <bool BF16, int NW, int CTH, bool WIDE_OUT, int NKB1, int NKB2, bool PRIMED, bool RAW_OUT, int KSPLIT = 1,
-          int NBT = 2, class Early, class Late, class Sink, class Layer1 = WholeTileLayer1>
-__device__ inline void mlp_tile(const Net &net, u32x4 (&ring)[ring_depth(CTH)][CTH], const unsigned char *ldsX,
-                                int xpitch, unsigned char *ldsH, int hpitch, const float *ldsBias,
-                                const u32x4 *ldsW3, int tid, Early early, Late late, Sink sink,
+          int NBT = 2, class W3, class Early, class Late, class Sink, class Layer1 = WholeTileLayer1>
+__device__ inline void mlp_tile(const Net &net, typename Op<BF16>::Block (&ring)[ring_depth(CTH)][CTH],
+                                const unsigned char *ldsX, int xpitch, unsigned char *ldsH, int hpitch,
+                                const float *ldsBias, const W3 &w3, int tid, Early early, Late late, Sink sink,
                                 Layer1 layer1 = Layer1()) {
   constexpr int PD = ring_depth(CTH);
   // the wavefront index is uniform: tell the compiler, so that block addresses live in scalar registers
@@ -597,7 +655,7 @@ __device__ inline void mlp_tile(const Net &net, u32x4 (&ring)[ring_depth(CTH)][C
       const int bt = w % NBT, part = w / NBT;
       f32x16 acc[1][1];
       zero_acc<1, 1>(acc);
-      mma_out_lds<BF16, NKB2 / KSPLIT>(acc[0][0], ldsW3, ldsH, hpitch, net.nkb[2], bt, lane, part * (NKB2 / KSPLIT));
+      mma_out<BF16, NKB2 / KSPLIT>(acc[0][0], w3, ldsH, hpitch, net.nkb[2], bt, lane, part * (NKB2 / KSPLIT));
       epilogue_out<1, 1, true>(acc, lb3, net.out_dim, net.out_tanh, 1, 0, bt, lane,
                                [&](int b, int f, float z) { sink(b, f, z, part); });
     }
@@ -606,7 +664,7 @@ __device__ inline void mlp_tile(const Net &net, u32x4 (&ring)[ring_depth(CTH)][C
     if (w < NBT) {
       f32x16 acc[1][1];
       zero_acc<1, 1>(acc);
-      mma_out_lds<BF16, NKB2>(acc[0][0], ldsW3, ldsH, hpitch, net.nkb[2], w, lane);  // nkb[2] == nkb[1]
+      mma_out<BF16, NKB2>(acc[0][0], w3, ldsH, hpitch, net.nkb[2], w, lane);  // nkb[2] == nkb[1]
       epilogue_out<1, 1, RAW_OUT>(acc, lb3, net.out_dim, net.out_tanh, 1, 0, w, lane, sink);
     }
     late();
@@ -615,7 +673,7 @@ __device__ inline void mlp_tile(const Net &net, u32x4 (&ring)[ring_depth(CTH)][C
     constexpr int CTO = 4;
     const int co0 = w * CTO;
     if (co0 < net.nct[2]) {
-      u32x4 r4[2][CTO];
+      typename Op<BF16>::Block r4[2][CTO];
       f32x16 acc[CTO][NBT];
       zero_acc<CTO, NBT>(acc);
       prime<CTO, 2>(r4, net.W[2], net.nkb[2], net.nct[2], co0, lane);
@@ -625,8 +683,14 @@ __device__ inline void mlp_tile(const Net &net, u32x4 (&ring)[ring_depth(CTH)][C
   }
 }
 
-// Geometry of the LDS tiles.
-__host__ __device__ inline int tile_pitch(int k_elems_padded, int esz) { return k_elems_padded * esz + 16; }
+// Bytes per row of an LDS tile of nkb k-blocks: 16 more than the data, so that the rows of one access fall on different banks.
+template <bool BF16>
+__host__ __device__ constexpr int tile_pitch(int nkb) { return nkb * Op<BF16>::KBYTES + 16; }
+inline int tile_pitch(int bf16, int nkb) { return bf16 ? tile_pitch<true>(nkb) : tile_pitch<false>(nkb); }
+
+// Workgroup b runs on XCD b % 8: the index that gives every XCD a run of consecutive tiles, so that the workgroups that
+// share an L2 stream the same agent's weights.
+__device__ inline unsigned xcd_index(unsigned b, unsigned n) { return n % 8 ? b : (b & 7) * (n / 8) + (b >> 3); }
 
 }  // namespace tile
 }  // namespace pod

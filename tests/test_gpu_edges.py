@@ -137,3 +137,23 @@ def test_layer_launches(N, rows, agents, Hd, D, K):
         parity.check_networks(w, d["actor"], d["critic"], X[sel], mu[sel], val[sel], agent=a)
         for t in range(2):
             parity.check_networks(w, d["actor"], d["critic"], obs[t][sel], mus[t][sel], agent=a)
+
+
+# fp32 networks on the bf16 matrix cores: 32- and 64-row tiles of the chunk-staged kernel, the whole-tile kernel with a
+# ragged tail, one launch per layer; partial feature tiles, one k-block and many, wide outputs; several agents
+@pytest.mark.parametrize("N,rows,agents,Hd,D,K", [(16, 16, 1, 32, 3, 0), (48, 40, 1, 64, 5, 2), (64, 40, 1, 256, 30, 8),
+                                                  (16, 20, 1, 160, 30, 0), (64, 64 * 260 + 40, 1, 256, 30, 8), (128, 128, 2, 512, 130, 1),
+                                                  (128, 1000, 2, 512, 30, 4), (64, 4200, 1, 96, 33, 3), (192, 150, 3, 128, 17, 7)])
+def test_fp32_networks(N, rows, agents, Hd, D, K):
+    w = inputs.WORKLOADS["dow30"].replace(n_envs=N, n_agents=agents, hidden=Hd, n_stocks=D, n_ind=K, steps=2)
+    d = inputs.make_all(w, horizon=2, n_market=1, steps=2)
+    cfg = pr.make_config(w, horizon=2, n_market=1, schedule=pr.PR_SCHED_STEPWISE)
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    ro = pr.Rollout(cfg, _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+    X = np.random.default_rng(rows).standard_normal((rows, w.state_dim)).astype(np.float32)
+    X[::7] *= np.float32(1e-3)
+    mu, val = (parity.to_np(ro.mlp_forward(net, _t(X))) for net in (pr.PR_NET_ACTOR, pr.PR_NET_CRITIC))
+    pick = np.unique(np.concatenate([np.arange(0, rows, max(1, rows // 150)), np.arange(max(0, rows - 70), rows)]))
+    for a in range(agents):
+        sel = pick[(pick % N) // (N // agents) == a]
+        parity.check_networks(w, d["actor"], d["critic"], X[sel], mu[sel], val[sel], agent=a)
