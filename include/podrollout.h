@@ -61,12 +61,15 @@ typedef struct pr_config {
   int32_t hidden;       /* Hd, multiple of 32 */
   int32_t horizon;      /* H >= 1 */
   int32_t n_market;     /* M in {1, N}: env n reads market path n % M */
-  int32_t mlp_dtype;    /* PR_MLP_F32: fp32 operands on fp32 matrix cores;
+  int32_t mlp_dtype;    /* PR_MLP_F32: fp32 operands (on the bf16 matrix cores as
+                           exact sums of three bf16 numbers);
                            PR_MLP_BF16: observations, weights and hidden
                            activations rounded to bf16 (nearest-even),
                            fp32 accumulate, fp32 bias / tanh / outputs */
-  int32_t schedule;     /* PR_SCHED_STEPWISE: one actor launch and one env launch
-                           per step; PR_SCHED_FUSED: one persistent launch that
+  int32_t schedule;     /* PR_SCHED_STEPWISE: actor and env launches for every
+                           step (networks of 64 or 128 hidden units on at most
+                           320 inputs and 32 stocks: one launch for all steps);
+                           PR_SCHED_FUSED: one persistent launch that
                            keeps each env tile on one compute unit for all T
                            steps (bf16 networks with 256 or 512 hidden units,
                            fp32 networks with 256; D <= 32, D K <= 252 and a
@@ -185,8 +188,8 @@ int rollout_step_forced(pr_handle *h, int32_t T, const float *mu, const float *n
 
 /* One network on its own: rows of X ([rows, S], row stride ldx floats) through
  * the actor (Y [rows, D]) or the critic (Y [rows]) of the agent that owns env
- * (row % N).  This is the kernel rollout_step_T uses for the critic and, in the
- * stepwise schedule, for the actor. */
+ * (row % N).  These are the kernels rollout_step_T uses for the critic and, in the
+ * stepwise schedule of all but small networks, for the actor. */
 int rollout_mlp_forward(pr_handle *h, int32_t net, int64_t rows, const float *X, int64_t ldx, float *Y);
 
 /* Copy the per-env state out of / into the handle (device buffers). */

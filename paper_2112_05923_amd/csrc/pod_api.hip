@@ -59,8 +59,11 @@ struct Layout {
 
 // the stepwise policy of small bf16 batches reads a bf16 copy of the observations, written along with them
 bool uses_shadow(const pr_config &c) {
-  return c.schedule == PR_SCHED_STEPWISE && layers_supported(c.n_envs, c.hidden, c.mlp_dtype);
+  return c.schedule == PR_SCHED_STEPWISE && !small_supported(c) && layers_supported(c.n_envs, c.hidden, c.mlp_dtype);
 }
+
+// rollouts of this config read layer 1 in the order [indicators | cash | prices | holdings]
+bool uses_rotated(const pr_config &c) { return c.schedule == PR_SCHED_FUSED || small_supported(c) || uses_shadow(c); }
 
 int state_dim(const pr_config &c) { return 1 + 2 * c.n_stocks + c.n_stocks * c.n_ind; }
 
@@ -107,7 +110,7 @@ Layout make_layout(const pr_config &c) {
       L.b[net][l] = take((size_t)padded_out(out_dim[l]) * 4 * P);
     }
   }
-  L.w1_rot = c.schedule == PR_SCHED_FUSED || uses_shadow(c) ? take(packed_weight_bytes(S, Hd, bf) * P) : 0;
+  L.w1_rot = uses_rotated(c) ? take(packed_weight_bytes(S, Hd, bf) * P) : 0;
   L.cash = take(N * 4);
   L.tau = take(N * 4);
   L.h = take(N * D * 4);
@@ -163,8 +166,8 @@ int pack_nets(pr_handle *h, const pr_weights *actor, const pr_weights *critic) {
       POD_HIP(launch_pack_layer(h->stream, W[l], b[l], P, in_dim[l], out_dim[l], bf, 0, h->w_packed[net][l],
                                 h->b_packed[net][l]));
   }
-  // The persistent rollout kernel keeps its observation tile as [indicators | cash | prices | holdings] (and so does the
-  // bf16 copy of the observations): the same layer-1 weights with their rows rotated by the D K indicator columns
+  // The persistent rollout kernel keeps its observation tile as [indicators | cash | prices | holdings] (and so do
+  // the one for small networks and the bf16 copy of the observations): the same layer-1 weights with their rows rotated by the D K indicator columns
   // (biases are shared).
   if (h->w1_rot)
     POD_HIP(launch_pack_layer(h->stream, actor->W1, actor->b1, P, S, Hd, bf, D * c.n_ind, h->w1_rot,
@@ -274,7 +277,7 @@ int rollout_init(const pr_config *cfg, const pr_market *market, const pr_weights
   d.s_ind = cfg->obs_scale[3];
 
   fill_net(h->actor, h, 0);
-  h->w1_rot = cfg->schedule == PR_SCHED_FUSED || uses_shadow(*cfg) ? static_cast<void *>(ws + L.w1_rot) : nullptr;
+  h->w1_rot = uses_rotated(*cfg) ? static_cast<void *>(ws + L.w1_rot) : nullptr;
   h->actor_rot = h->actor;
   h->actor_rot.W[0] = h->w1_rot;
   fill_net(h->critic, h, 1);
@@ -329,6 +332,9 @@ int rollout_step_T(pr_handle *h, int32_t T, const float *noise, const pr_buffers
   if (h->cfg.schedule == PR_SCHED_FUSED) {
     POD_HIP(launch_rollout_fused(h->stream, h->cfg, h->dims, h->st, h->market.price, h->market.ind, h->actor_rot,
                                  per_agent, T, noise, nullptr, *out));
+  } else if (small_supported(h->cfg)) {
+    POD_HIP(launch_rollout_small(h->stream, h->dims, h->st, h->market.price, h->market.ind, h->actor_rot, per_agent, T, noise,
+                                 *out));
   } else {
     POD_HIP(launch_observe(h->stream, h->dims, h->st, h->market.price, h->market.ind, out->obs, h->shadow));
     for (int t = 0; t < T; ++t) {

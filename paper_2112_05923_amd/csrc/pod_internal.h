@@ -166,4 +166,10 @@ hipError_t launch_rollout_fused(hipStream_t st, const pr_config &c, const EnvDim
                                 const float *price, const float *ind, const PackedNet &actor, int32_t envs_per_agent,
                                 int32_t T, const float *noise, const float *mu_forced, const pr_buffers &out);
 
+// The stepwise schedule of small networks: all T steps in one launch, state and network on the compute units.
+bool small_supported(const pr_config &c);
+hipError_t launch_rollout_small(hipStream_t st, const EnvDims &d, const EnvState &s, const float *price, const float *ind,
+                                const PackedNet &actor, int32_t envs_per_agent, int32_t T, const float *noise,
+                                const pr_buffers &out);
+
 }  // namespace pod

@@ -1552,7 +1552,9 @@ hipError_t launch_mlp(hipStream_t st, const PackedNet &net, int64_t rows, const 
     // full tiles through the persistent whole-tile kernel when it covers the shape; the ragged tail below
     hipError_t terr = hipSuccess;
     const int64_t full = rows / BM * BM;
-    if (try_launch_tiles(st, net, full, row_offset, X, ldx, Y, N, envs_per_agent, &terr)) {
+    // (a ragged buffer of at most a tile per compute unit: one launch of the kernel below instead of two)
+    if ((full == rows || full / BM >= compute_units()) &&
+        try_launch_tiles(st, net, full, row_offset, X, ldx, Y, N, envs_per_agent, &terr)) {
       if (terr != hipSuccess || full == rows) return terr;
       X += full * ldx;
       Y += full * net.out_dim[2];

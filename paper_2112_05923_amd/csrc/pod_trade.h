@@ -1,0 +1,283 @@
+// The trades of one env step (Table 1 and Sec. 5.3 of the paper), shared by the
+// kernel that steps all envs once and the one that keeps small networks and
+// their envs on a compute unit for a whole rollout.
+//
+// Included only by translation units that are compiled with floating-point
+// contraction off: the share counts are decided by a fixed sequence of binary32
+// operations with one rounding each.
+#pragma once
+
+#include "pod_internal.h"
+
+namespace pod {
+namespace {
+
+constexpr int kEnvThreads = 512;
+typedef float env_f32x4 __attribute__((ext_vector_type(4)));
+typedef env_f32x4 env_f32x4u __attribute__((aligned(4)));
+
+struct RowInfo {
+  int32_t row_now;   // market row the trades execute at
+  int32_t row_val;   // market row the portfolio is valued at (cursor + 1)
+  int32_t row_obs;   // market row of the next observation (0 after a reset)
+  int32_t done;
+};
+
+__device__ inline RowInfo rows_of(const EnvDims &d, int32_t tau, int32_t start, int32_t n) {
+  const int32_t m = d.M == 1 ? 0 : n;
+  RowInfo r;
+  r.row_now = tau * d.M + m;
+  r.row_val = (tau + 1) * d.M + m;
+  r.done = (tau + 1 - start == d.H);
+  r.row_obs = r.done ? start * d.M + m : r.row_val;
+  return r;
+}
+
+struct __attribute__((aligned(16))) Purchase {
+  float k, u;   // wanted shares, unit cost
+  double rcp;   // 1 / u in binary64
+};
+
+__device__ inline double sum_lanes(double v, int width) {
+  for (int o = 1; o < width; o *= 2) v += __shfl_xor(v, o);
+  return v;
+}
+
+// s + v[0][0] + v[0][1] + ... in this order (two register sets, read one ahead of the other by hand, were slower)
+__device__ inline float serial_sum(float s, const env_f32x4 *v, int n) {
+#pragma unroll 8
+  for (int c = 0; c < n; ++c) {
+    const env_f32x4 x = v[c];
+    s = s + x[0];
+    s = s + x[1];
+    s = s + x[2];
+    s = s + x[3];
+  }
+  return s;
+}
+
+// 512 threads trade for E envs: TPE = 512 / E neighbouring threads own one env, and a thread the stocks tl, tl + TPE, ...
+// (at most ND) of its env, whose prices, holdings and orders stay in its registers.  What bounds the step is the chain
+// prices -> orders -> the serial walk over the purchases -> holdings; everything else hangs off it:
+//  - the ledger adds the sales from a dense row, and walks only the purchases: the threads pack them into a list in
+//    stock order (ballots inside a wavefront, counts through LDS across two).  It runs in the env's own wavefront
+//    (half) and needs one dependent operation per purchase while the cash lasts, none for a purchase it does not
+//    buy a single share of, and the quotient only in between (13.5 -> 1.8 us of a step with 250 purchases);
+//  - the account values before and after are sums over the env's threads in binary64;
+//  - up to a wavefront per env there is no barrier in here: an env's threads only meet each other.
+template <int E, int ND>
+struct Trade {
+  static constexpr int TPE = kEnvThreads / E;
+  static constexpr int CW = TPE < 64 ? TPE : 64;  // the part of a wavefront one env has
+  static constexpr int NCW = TPE / CW;            // wavefronts per env
+  int D, D4, lp, sp, op;
+  Purchase *list;  // [E][lp] purchases in stock order (odd pitch in 16 bytes)
+  float *sell;     // [E][sp] proceeds of the sales, 0 elsewhere
+  float *sq;       // [E][sp] squared noise
+  float *out;      // [E][op] outlay k u of the purchases, by list position
+  int32_t *buy;    // [E][lp] shares bought, by list position
+  double *part;    // [2][E][2] account value before / after, per wavefront of an env
+  float *e2s;      // [E] sum of the squares
+  int32_t *cnt;    // [E][ND NCW] purchases
+
+  __device__ Trade(unsigned char *lds, int D_) : D(D_), D4((D_ + 3) & ~3), lp(D_ | 1), sp(D4 + 4), op(D4 + 20) {
+    list = reinterpret_cast<Purchase *>(lds);
+    sell = reinterpret_cast<float *>(list + E * lp);
+    sq = sell + E * sp;
+    out = sq + E * sp;
+    buy = reinterpret_cast<int32_t *>(out + E * op);
+    part = reinterpret_cast<double *>(buy + E * lp);
+    e2s = reinterpret_cast<float *>(part + 4 * E);
+    cnt = reinterpret_cast<int32_t *>(e2s + E);
+  }
+
+  // all of an env's threads have written what the others read
+  __device__ static void meet() {
+    if (NCW > 1) {
+      __syncthreads();
+    } else {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+  }
+
+  // Sampled actions a_raw and their noise, prices pn the trades execute at and pv the account is valued at afterwards,
+  // holdings h (updated), executed shares q (signed), cash (updated); r and e2 (reward, and the summed squares if wanted)
+  // are complete in the env's first thread.  market(): between sizing and ledger; rest(): behind the ledger; booked(i): the
+  // thread's i-th stock is settled (live stocks only).
+  template <class Market, class Rest, class Booked>
+  __device__ inline void run(const EnvDims &d, bool live, const float (&a_raw)[ND], const float (&eps)[ND], const float (&pn)[ND],
+                             const float (&pv)[ND], int32_t (&h)[ND], int32_t (&q)[ND], float &cash, double &r, float &e2,
+                             bool want_e2, Market market, Rest rest, Booked booked) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int e = tid / TPE, tl = tid & (TPE - 1), cw = tl / CW, cl = lane & (CW - 1);
+    const float cash_in = cash;
+    auto mine_of = [&](uint64_t all) {  // the env's part of a ballot
+      return CW == 64 ? all : (all >> (lane & ~(CW - 1))) & ((1ull << (CW & 63)) - 1ull);
+    };
+    // -- size the orders
+    int32_t rank[ND], total = 0;
+    float unit[ND], kf[ND];
+    double a0 = 0.0;
+#pragma unroll
+    for (int i = 0; i < ND; ++i) {
+      const int dd = tl + TPE * i;
+      const bool ok = live && dd < D;
+      const float ac = fminf(1.0f, fmaxf(-1.0f, a_raw[i]));
+      const int32_t k = ok ? (int32_t)truncf(ac * d.hmax) : 0;
+      float sale = 0.0f;
+      q[i] = 0;
+      kf[i] = 0.0f;
+      unit[i] = 0.0f;
+      if (ok) a0 += (double)h[i] * (double)pn[i];
+      if (k < 0) {
+        const int32_t qs = min(-k, h[i]);
+        h[i] -= qs;
+        const float gross = pn[i] * (float)qs;
+        sale = gross * d.one_minus_c;
+        q[i] = -qs;
+      } else if (k > 0) {
+        kf[i] = (float)k;
+        unit[i] = pn[i] * d.one_plus_c;
+      }
+      if (dd < D4) {
+        sell[e * sp + dd] = sale;
+        sq[e * sp + dd] = ok ? eps[i] * eps[i] : 0.0f;
+      }
+      const uint64_t mine = mine_of(__ballot(k > 0));
+      rank[i] = __popcll(mine & ((1ull << cl) - 1ull));
+      if (NCW == 1) {
+        rank[i] += total;
+        total += __popcll(mine);
+      } else if (cl == 0) {
+        cnt[(e * ND + i) * NCW + cw] = __popcll(mine);
+      }
+    }
+    a0 = sum_lanes(a0, CW);
+    if (NCW > 1) {
+      if (cl == 0) part[e * 2 + cw] = a0;
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < ND; ++i)
+#pragma unroll
+        for (int w = 0; w < NCW; ++w) {
+          const int c = cnt[(e * ND + i) * NCW + w];
+          if (w == cw) rank[i] += total;
+          total += c;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < ND; ++i)
+      if (kf[i] > 0.0f) {
+        list[e * lp + rank[i]] = Purchase{kf[i], unit[i], 1.0 / (double)unit[i]};
+        out[e * op + rank[i]] = kf[i] * unit[i];
+      }
+    if (tl < 16) out[e * op + total + tl] = 0.0f;
+    market();
+    meet();
+
+    e2 = 0.0f;
+    if (cw == NCW - 1 && want_e2) {
+      // the squares in stock order (the log-probability is the same number in every schedule)
+      e2 = serial_sum(0.0f, reinterpret_cast<const env_f32x4 *>(sq + e * sp), D4 / 4);
+      if (NCW > 1 && cl == 0) e2s[e] = e2;
+    }
+    if (cw == 0) {
+      // -- the ledger (Table 1 actions: sell / buy / hold): all sales, then all purchases, in stock order, each limited
+      // by the cash left:
+      //   m = floor(cash / u); q = min(k, max(m, 0)); if (q u > cash) q -= 1; cash -= q u        (binary32)
+      cash = serial_sum(cash, reinterpret_cast<const env_f32x4 *>(sell + e * sp), D4 / 4);
+      const Purchase *lst = list + e * lp;
+      auto affordable = [&](float c, float u) { return mine_of(__ballot(!(c < u))); };
+      for (int c0 = 0; c0 < total; c0 += CW) {
+        const int p = c0 + cl;
+        const Purchase mine = lst[min(p, total - 1)];
+        const float u = p < total ? mine.u : __builtin_inff();
+        int32_t got = 0;
+        for (int s0 = 0; s0 < CW && c0 + s0 < total; s0 += 16) {
+          if (((affordable(cash, u) >> s0) & 0xffffull) == 0) continue;
+          // sixteen purchases in full: as long as the balance stays clear of 0 (2^-20 of what it was, so every outlay
+          // k u before it was below the balance by more than its own rounding), each quotient was at least k
+          const env_f32x4 *ov = reinterpret_cast<const env_f32x4 *>(out + e * op + c0 + s0);
+          const float clear = cash * 0x1p-20f;
+          float full = cash;
+          int in_full = 0;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const env_f32x4 v = ov[c];
+            full = full - v[0];
+            full = full - v[1];
+            full = full - v[2];
+            full = full - v[3];
+            if (full >= clear) cash = full, in_full = 4 * c + 4;  // (outlays are not negative: never true again once false)
+          }
+          if ((unsigned)(cl - s0) < (unsigned)in_full) got = (int32_t)mine.k;
+          if (in_full == 16) continue;
+          // one by one, those that buy nothing (cash < u: the quotient is below 1 and rounds below 1) skipped.
+          // The binary32 quotient comes from one binary64 product with the prepared reciprocal of u: the product is
+          // within 2^-52 of cash / u, and a quotient of two binary32 numbers is at least 2^-49 (relative) away from
+          // every binary32 rounding boundary it does not hit exactly, so the product rounded to binary32 is the
+          // correctly rounded cash / u.  It is never negative (cash is not), so truncation is the floor and needs no
+          // clamp at 0; the outlay of one share less, (q - 1) u rounded once, is the fused q u - u.
+          uint64_t ahead = (0xffffull << s0) & (~0ull << (s0 + in_full));
+          while (true) {
+            const uint64_t left = affordable(cash, u) & ahead;
+            if (left == 0) break;
+            const int j = __builtin_ctzll(left);
+            const Purchase b = lst[c0 + j];
+            const float ratio = (float)((double)cash * b.rcp);
+            const float q0 = fminf(b.k, truncf(ratio));
+            const float out_q = q0 * b.u, out_q1 = fmaf(q0, b.u, -b.u);
+            const float bal0 = cash - out_q, bal1 = cash - out_q1;
+            const bool over = out_q > cash;
+            cash = over ? bal1 : bal0;
+            if (cl == j) got = (int32_t)(over ? q0 - 1.0f : q0);
+            ahead &= ~1ull << j;
+          }
+        }
+        if (p < total) buy[e * lp + p] = got;
+      }
+    }
+    rest();
+    meet();
+
+    // -- executed trades, holdings, account value after them
+    double a1 = 0.0;
+#pragma unroll
+    for (int i = 0; i < ND; ++i) {
+      if (kf[i] > 0.0f) {
+        q[i] = buy[e * lp + rank[i]];
+        h[i] += q[i];
+      }
+      if (live && tl + TPE * i < D) {
+        a1 += (double)h[i] * (double)pv[i];
+        booked(i);
+      }
+    }
+    a1 = sum_lanes(a1, CW);
+    double v0 = (double)cash_in, v1 = (double)cash;
+    if (NCW > 1) {
+      if (cl == 0) part[2 * E + e * 2 + cw] = a1;
+      __syncthreads();
+      if (tl == 0) {
+#pragma unroll
+        for (int w = 0; w < NCW; ++w) v0 += part[e * 2 + w], v1 += part[2 * E + e * 2 + w];
+        e2 = e2s[e];
+      }
+    } else {
+      v0 += a0;
+      v1 += a1;
+    }
+    r = (v1 - v0) * (double)d.rho;
+  }
+};
+
+inline size_t trade_lds(int E, int D) {
+  const int D4 = (D + 3) & ~3, lp = D | 1;
+  return (size_t)E * lp * sizeof(Purchase) + (size_t)E * (2 * (D4 + 4) + D4 + 20) * 4 + (size_t)E * lp * 4 +
+         (size_t)4 * E * 8 + (size_t)E * 4 + (size_t)E * 8 * 4;
+}
+
+}  // namespace
+}  // namespace pod

@@ -157,3 +157,31 @@ def test_fp32_networks(N, rows, agents, Hd, D, K):
     for a in range(agents):
         sel = pick[(pick % N) // (N // agents) == a]
         parity.check_networks(w, d["actor"], d["critic"], X[sel], mu[sel], val[sel], agent=a)
+
+
+# small networks, all steps in one launch: every instance (64 / 128 hidden units, few and many layer-1 blocks per wavefront),
+# a last workgroup that is not full, several agents, no indicators and rows that are no multiple of four of them
+@pytest.mark.parametrize("base,N,agents,Hd,D,K", [("tiny", 16, 1, 64, 5, 2), ("tiny", 17, 1, 64, 1, 0), ("tiny", 40, 1, 64, 30, 2),
+                                                  ("tiny", 192, 3, 64, 30, 8), ("tiny", 33, 1, 128, 3, 1), ("tiny", 128, 2, 128, 31, 3),
+                                                  ("tiny", 50, 1, 128, 29, 9), ("large", 16, 1, 64, 32, 0), ("large", 31, 1, 64, 31, 8),
+                                                  ("large", 64, 1, 128, 7, 3), ("large", 128, 2, 128, 32, 7)])
+def test_small_network_rollout(base, N, agents, Hd, D, K):
+    T, H = 21, 9
+    w = inputs.WORKLOADS[base].replace(n_envs=N, n_agents=agents, hidden=Hd, n_stocks=D, n_ind=K, steps=T, cash0=5e4)
+    d = inputs.make_all(w, horizon=H, steps=T)
+    cfg = pr.make_config(w, horizon=H, schedule=pr.PR_SCHED_STEPWISE)
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    ro = pr.Rollout(cfg, _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+    parts = []
+    for t0, n in ((0, 1), (1, T - 1)):   # (state carried across calls)
+        out = ro.alloc_buffers(n, value=False, logp=True, mu=True, shares=True)
+        ro.step_T(n, _t(d["noise"][t0:t0 + n]), out)
+        torch.cuda.synchronize()
+        parts.append({k: parity.to_np(v) for k, v in out.items() if v is not None})
+    rec = {k: np.concatenate([parts[0][k][:1], parts[1][k]]) for k in parts[0]}
+    assert np.array_equal(parts[0]["obs"][1], parts[1]["obs"][0])
+    parity.check_env_record(w, oracle.cfg_from_workload(w, horizon=H), rec, d["price"], d["ind"], d["noise"], rec["mu"])
+    for a in range(agents):
+        envs = np.arange(a * (N // agents), (a + 1) * (N // agents))[-25:]
+        for t in (0, T - 1):
+            parity.check_networks(w, d["actor"], d["critic"], rec["obs"][t][envs], rec["mu"][t][envs], agent=a)
