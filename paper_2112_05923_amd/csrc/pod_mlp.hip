@@ -210,7 +210,7 @@ __device__ inline void epilogue_to_lds(const f32x16 (&acc)[RT][CT], const float 
           const int row = r * 32 + 8 * (i >> 2) + 4 * g + (i & 3);
           const float z = acc[r][c][i] + bv;
           const float hval = BF16 ? tile::tanh_from_scaled(z * tile::kTwoLog2e) : tanh_accurate(z);
-          O::store1(ldsH + (size_t)row * hpitch + O::off(col), hval);
+          O::template store1<true>(ldsH + (size_t)row * hpitch + O::off(col), hval);
         }
     }
   }

@@ -184,11 +184,11 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
 #pragma unroll
     for (int i = 0; i < F; ++i) z[i] = BF16 ? tanh_from_scaled(z[i] * kTwoLog2e) : tanh_accurate(z[i]);
     unsigned char *o = ldsH + e * HP + O::off(f0);
-    if constexpr (F == 4) O::store4(o, z[0], z[1], z[2], z[3]);
+    if constexpr (F == 4) O::template store4<true>(o, z[0], z[1], z[2], z[3]);
     else if constexpr (BF16) *reinterpret_cast<uint32_t *>(o) = bf16_pair(z[0], z[1]);
     else {
       uint32_t s[3];
-      split3_pair(z[0], z[1], s[0], s[1], s[2]);
+      split3_pair<true>(z[0], z[1], s[0], s[1], s[2]);
 #pragma unroll
       for (int i = 0; i < 3; ++i) *reinterpret_cast<uint32_t *>(o + 16 * i) = s[i];
     }

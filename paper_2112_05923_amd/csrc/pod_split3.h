@@ -9,6 +9,12 @@
 // rounding of an fp32 multiply-add (2^-24), and the products that are formed are
 // exact in the fp32 accumulator's input.  (Parts below the smallest normal number
 // may be lost: operands smaller than about 1e-33.)
+//
+// An infinity leaves the last part infinite and the others at 2^127, and a NaN the
+// last part: the last part meets the first of the other operand only, so an infinite
+// input times a finite weight is that infinity, as in fp32.  (Taken apart like the
+// others it would be inf - inf = NaN in every sum it meets.  Only where an operand of
+// 2^127 or more meets one above 500, beyond fp32 twice over, may the result be NaN.)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -44,26 +50,30 @@ __device__ inline float tanh_f32(float x) {
   return ax < 0.6f ? small : big;
 }
 
-// two numbers -> three packed pairs
+// two numbers -> three packed pairs.  SMALL: both below 2^127 (tanh outputs; a NaN stays one)
+template <bool SMALL = false>
 __device__ inline void split3_pair(float a, float b, uint32_t &p0, uint32_t &p1, uint32_t &p2) {
+  constexpr float M = 1.7014118346046923e38f;
+  auto first = [](float x) { return SMALL ? x : __builtin_amdgcn_fmed3f(x, -M, M); };
   // (the packed pairs are settled before they are taken apart: left alone, the compiler converts a second time instead)
-  p0 = bf16_pair(a, b);
+  p0 = bf16_pair(first(a), first(b));
   asm("" : "+v"(p0));
   a -= bf16_low(p0), b -= bf16_high(p0);
-  p1 = bf16_pair(a, b);
+  p1 = bf16_pair(first(a), first(b));
   asm("" : "+v"(p1));
   a -= bf16_low(p1), b -= bf16_high(p1);
   p2 = bf16_pair(a, b);
 }
 
 // eight consecutive k of an operand row -> its three matrix operands
+template <bool SMALL = false>
 __device__ inline void split3(const float (&v)[8], bf16x8 (&out)[3]) {
   typedef uint32_t u32x4_ __attribute__((ext_vector_type(4)));
   u32x4_ o[3];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     uint32_t p0, p1, p2;
-    split3_pair(v[2 * i], v[2 * i + 1], p0, p1, p2);
+    split3_pair<SMALL>(v[2 * i], v[2 * i + 1], p0, p1, p2);
     o[0][i] = p0, o[1][i] = p1, o[2][i] = p2;
   }
 #pragma unroll

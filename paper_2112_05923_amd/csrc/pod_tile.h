@@ -73,7 +73,9 @@ struct Op<true> {
     c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c, 0, 0,
                                                 0);
   }
+  template <bool SMALL = false>
   static __device__ inline void store1(unsigned char *p, float v) { *reinterpret_cast<__bf16 *>(p) = (__bf16)v; }
+  template <bool SMALL = false>
   static __device__ inline void store4(unsigned char *p, float a, float b, float c, float d) {
     bf16x4 v = {(__bf16)a, (__bf16)b, (__bf16)c, (__bf16)d};
     *reinterpret_cast<u32x2 *>(p) = __builtin_bit_cast(u32x2, v);
@@ -96,17 +98,19 @@ struct Op<false> {
       c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w.p[kSplitA[i]]),
                                                   __builtin_bit_cast(bf16x8, x.p[kSplitB[i]]), c, 0, 0, 0);
   }
+  template <bool SMALL = false>
   static __device__ inline void store1(unsigned char *p, float v) {
     uint32_t s[3];
-    split3_pair(v, 0.0f, s[0], s[1], s[2]);
+    split3_pair<SMALL>(v, 0.0f, s[0], s[1], s[2]);
 #pragma unroll
     for (int i = 0; i < 3; ++i) *reinterpret_cast<uint16_t *>(p + 16 * i) = (uint16_t)s[i];
   }
-  // (four columns from a multiple of four)
+  // (four columns from a multiple of four; SMALL: of tanh outputs)
+  template <bool SMALL = false>
   static __device__ inline void store4(unsigned char *p, float a, float b, float c, float d) {
     uint32_t lo[3], hi[3];
-    split3_pair(a, b, lo[0], lo[1], lo[2]);
-    split3_pair(c, d, hi[0], hi[1], hi[2]);
+    split3_pair<SMALL>(a, b, lo[0], lo[1], lo[2]);
+    split3_pair<SMALL>(c, d, hi[0], hi[1], hi[2]);
 #pragma unroll
     for (int i = 0; i < 3; ++i) *reinterpret_cast<u32x2 *>(p + 16 * i) = u32x2{lo[i], hi[i]};
   }
@@ -473,7 +477,7 @@ __device__ inline void epilogue_hidden(const f32x16 (&acc)[CT][NBT], const float
             else
               h[i] = tanh_accurate(acc[c][t][4 * j + i] + bv[i]);
           }
-          O::store4(ldsH + (size_t)((bt0 + t) * 32 + brow) * hpitch + O::off(f0), h[0], h[1], h[2], h[3]);
+          O::template store4<true>(ldsH + (size_t)((bt0 + t) * 32 + brow) * hpitch + O::off(f0), h[0], h[1], h[2], h[3]);
         }
       }
     }

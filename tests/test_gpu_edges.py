@@ -185,3 +185,37 @@ def test_small_network_rollout(base, N, agents, Hd, D, K):
         envs = np.arange(a * (N // agents), (a + 1) * (N // agents))[-25:]
         for t in (0, T - 1):
             parity.check_networks(w, d["actor"], d["critic"], rec["obs"][t][envs], rec["mu"][t][envs], agent=a)
+
+
+# fp32 networks with infinities, numbers next to the largest and NaN among inputs and weights: every kernel of the
+# forward pass and both rollouts that keep their input tile give what fp32 sums give (a saturated unit, or NaN)
+@pytest.mark.parametrize("N,rows,Hd,D,K,fused", [(16, 16, 32, 3, 1, False), (64, 64 * 260 + 40, 256, 30, 8, False),
+                                                 (128, 1000, 512, 30, 4, False), (64, 64, 256, 30, 8, True),
+                                                 (16, 40, 64, 5, 2, False), (32, 40, 128, 30, 8, False)])
+def test_fp32_networks_with_nonfinite_numbers(N, rows, Hd, D, K, fused):
+    w = inputs.WORKLOADS["dow30"].replace(n_envs=N, hidden=Hd, n_stocks=D, n_ind=K, steps=1)
+    d = inputs.make_all(w, horizon=1, steps=1)
+    inf = np.float32(np.inf)
+    d["ind"][:, 3, 1], d["ind"][:, 5, D * K - 1], d["ind"][:, 7, 0] = inf, -inf, np.nan
+    d["actor"]["W1"][0, 2, 5] = inf    # price of the second stock, positive
+    d["critic"]["W1"][0, 2, Hd - 1] = -inf
+    schedule = pr.PR_SCHED_FUSED if fused else pr.PR_SCHED_STEPWISE
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    ro = pr.Rollout(pr.make_config(w, horizon=1, schedule=schedule), _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+    X = np.abs(np.random.default_rng(rows).standard_normal((rows, w.state_dim))).astype(np.float32)
+    X[1, 4], X[2, 0], X[rows - 1, w.state_dim - 1] = inf, -inf, inf
+    X[4, 5], X[5, 6], X[6, 1] = np.finfo(np.float32).max, -1.8e38, np.nan
+    out = ro.alloc_buffers(1, value=True, logp=False, mu=True, shares=False)
+    got = [(X, *(parity.to_np(ro.mlp_forward(net, _t(X))) for net in (pr.PR_NET_ACTOR, pr.PR_NET_CRITIC)))]
+    ro.step_T(1, _t(d["noise"]), out)
+    torch.cuda.synchronize()
+    got.append((parity.to_np(out["obs"])[0], parity.to_np(out["mu"])[0], parity.to_np(out["value"])[0]))
+    for x, mu, value in got:
+        for net, y, tanh in ((d["actor"], mu, True), (d["critic"], value.reshape(len(x), 1), False)):
+            n = {k: v[0].astype(np.float64) for k, v in net.items()}
+            with np.errstate(invalid="ignore"):
+                h = np.tanh(np.tanh(x.astype(np.float64) @ n["W1"] + n["b1"]) @ n["W2"] + n["b2"])
+                want = h @ n["W3"] + n["b3"]
+                want = np.tanh(want) if tanh else want
+            assert np.isnan(want).any(axis=1).mean() < 0.4 and np.array_equal(np.isnan(y), np.isnan(want))
+            np.testing.assert_allclose(y, want, rtol=1e-4, atol=1e-4 * np.sqrt(np.nanmean(want * want)))
