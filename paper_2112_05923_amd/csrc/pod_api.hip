@@ -57,15 +57,16 @@ struct Layout {
   size_t total;
 };
 
+int state_dim(const pr_config &c) { return 1 + 2 * c.n_stocks + c.n_stocks * c.n_ind; }
+
 // the stepwise policy of small bf16 batches reads a bf16 copy of the observations, written along with them
 bool uses_shadow(const pr_config &c) {
-  return c.schedule == PR_SCHED_STEPWISE && !small_supported(c) && layers_supported(c.n_envs, c.hidden, c.mlp_dtype);
+  return c.schedule == PR_SCHED_STEPWISE && !small_supported(c) && layers_supported(c.n_envs, c.hidden, c.mlp_dtype) &&
+         !few_rows(c.n_envs, state_dim(c), c.hidden, c.mlp_dtype, true);
 }
 
 // rollouts of this config read layer 1 in the order [indicators | cash | prices | holdings]
 bool uses_rotated(const pr_config &c) { return c.schedule == PR_SCHED_FUSED || small_supported(c) || uses_shadow(c); }
-
-int state_dim(const pr_config &c) { return 1 + 2 * c.n_stocks + c.n_stocks * c.n_ind; }
 
 int validate_config(const pr_config *c) {
   if (!c) return PR_EINVAL;

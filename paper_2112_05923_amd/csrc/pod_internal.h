@@ -136,8 +136,8 @@ struct PackedNet {
   ObsShadow split_x;              // and, for bf16 networks, of its input
   int64_t split_rows;
 };
-// Rows up to which the layer-per-launch path is worth its scratch (fewer 64-row tiles than half the compute units
-// of the largest part), 0 if never for this batch size.
+// Rows the scratch of the layer-per-launch paths holds: all envs where a step's rows can take one of them (fewer 64-row
+// tiles than half the compute units), and always enough for a policy asked about a few; 0 for networks too narrow for them.
 int64_t split_scratch_rows(int64_t n_envs, int hidden);
 
 size_t packed_weight_bytes(int in_dim, int out_dim, int bf16);
@@ -155,6 +155,11 @@ bool layers_supported(int64_t rows, int hidden, int bf16);
 int32_t layers_pitch(int cols);
 hipError_t launch_layers(hipStream_t st, const PackedNet &net, int64_t rows, const ObsShadow &x, float *Y, int32_t N,
                          int32_t envs_per_agent);
+// Few rows of either operand type: a launch per layer that splits the inputs over a workgroup's wavefronts.  `converted`:
+// the alternative has its rows in bf16 already.
+bool few_rows(int64_t rows, int S, int hidden, int bf16, bool converted);
+hipError_t launch_few_rows(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx, float *Y,
+                           int32_t N, int32_t envs_per_agent);
 hipError_t launch_rows_to_bf16(hipStream_t st, int64_t rows, const float *X, int64_t ldx, int S, const ObsShadow &out);
 
 // ------------------------------------------------------- persistent rollout

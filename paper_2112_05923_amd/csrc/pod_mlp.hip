@@ -1239,7 +1239,9 @@ bool pick_shape(int Hd, int O, int bf16, Shape *s) {
 }  // namespace
 
 int64_t split_scratch_rows(int64_t n_envs, int hidden) {
-  return (hidden >= 128 && n_envs >= 64 && (n_envs + 63) / 64 * 2 <= 256) ? n_envs : 0;
+  constexpr int64_t kFew = 1024;
+  if (hidden < 64) return 0;
+  return n_envs > kFew && (n_envs + 63) / 64 * 2 <= 256 ? n_envs : kFew;
 }
 
 bool mlp_supported(int S, int Hd, int O, int bf16) {
@@ -1475,20 +1477,24 @@ static bool try_launch_wide(hipStream_t st, const PackedNet &net, int64_t rows, 
   return true;
 }
 
-// Few rows: one launch per layer (dense_layer_kernel, or launch_layers for bf16).  Needs the scratch of the packed
-// network.
+// Up to 8192 rows: one launch per layer (launch_few_rows; where that is not the faster one, dense_layer_kernel, or
+// launch_layers for bf16).  Needs the scratch of the packed network.
 static bool try_launch_split(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx, float *Y,
                              int32_t N, int32_t envs_per_agent, hipError_t *err) {
   const int Hd = net.out_dim[0];
-  if (!net.split_h[0] || !net.split_h[1] || rows > net.split_rows || rows < 64 || Hd < 128) return false;
+  if (!net.split_h[0] || !net.split_h[1] || rows > net.split_rows || (reinterpret_cast<uintptr_t>(X) & 3u)) return false;
+  if (envs_per_agent < N && envs_per_agent % 64 != 0) return false;  // a row tile never spans two agents
+  if (few_rows(rows, net.in_dim[0], Hd, net.bf16, false)) {
+    *err = launch_few_rows(st, net, rows, X, ldx, Y, N, envs_per_agent);
+    return true;
+  }
+  if (rows < 64 || Hd < 128) return false;
   if (net.bf16) {
-    if (envs_per_agent < N && envs_per_agent % 64 != 0) return false;  // a row tile never spans two agents
     *err = launch_rows_to_bf16(st, rows, X, ldx, net.in_dim[0], net.split_x);
     if (*err == hipSuccess) *err = launch_layers(st, net, rows, net.split_x, Y, N, envs_per_agent);
     return true;
   }
   if ((rows + 63) / 64 * 2 > compute_units()) return false;  // enough tiles for the whole-network kernels
-  if (envs_per_agent < N && envs_per_agent % 32 != 0) return false;
   const int64_t tiles = (rows + 31) / 32;
   const float *in = X;
   int64_t ld_in = ldx;

@@ -219,3 +219,27 @@ def test_fp32_networks_with_nonfinite_numbers(N, rows, Hd, D, K, fused):
                 want = np.tanh(want) if tanh else want
             assert np.isnan(want).any(axis=1).mean() < 0.4 and np.array_equal(np.isnan(y), np.isnan(want))
             np.testing.assert_allclose(y, want, rtol=1e-4, atol=1e-4 * np.sqrt(np.nanmean(want * want)))
+
+
+# few rows: a launch per layer with the inputs split over the wavefronts; one row, partial 32- and 64-row tiles, a k-block
+# per wavefront and many, last blocks that end inside a row, more rows than envs, several agents, either width of tile
+@pytest.mark.parametrize("base,N,rows,agents,Hd,D,K", [("dow30", 16, 1, 1, 64, 1, 0), ("large", 16, 1, 1, 128, 1, 1), ("dow30", 16, 33, 1, 512, 5, 2),
+                                                       ("large", 48, 48, 1, 512, 30, 8), ("large", 16, 1000, 1, 256, 33, 3), ("dow30", 192, 180, 3, 96, 17, 7),
+                                                       ("large", 256, 600, 2, 544, 127, 3), ("dow30", 16400, 1024, 1, 512, 30, 8), ("dow30", 4096, 4095, 2, 256, 30, 8),
+                                                       ("large", 1088, 1030, 1, 1024, 70, 3), ("large", 16, 7, 1, 1024, 500, 4)])
+def test_few_rows(base, N, rows, agents, Hd, D, K):
+    w = inputs.WORKLOADS[base].replace(n_envs=N, n_agents=agents, hidden=Hd, n_stocks=D, n_ind=K, steps=1)
+    d = inputs.make_all(w, horizon=1, n_market=1, steps=1)
+    cfg = pr.make_config(w, horizon=1, n_market=1, schedule=pr.PR_SCHED_STEPWISE)
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    ro = pr.Rollout(cfg, _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+    # rows with something else behind them, at a stride that is no multiple of four
+    wide = np.full((rows, w.state_dim + 3), np.nan, np.float32)
+    X = wide[:, :w.state_dim] = np.random.default_rng(rows).standard_normal((rows, w.state_dim)).astype(np.float32)
+    x = _t(wide)[:, :w.state_dim]
+    mu, val = (parity.to_np(ro.mlp_forward(net, x)) for net in (pr.PR_NET_ACTOR, pr.PR_NET_CRITIC))
+    pick = np.unique(np.concatenate([np.arange(0, rows, max(1, rows // 150)), np.arange(max(0, rows - 70), rows)]))
+    for a in range(agents):
+        sel = pick[(pick % N) // (N // agents) == a]
+        if len(sel):
+            parity.check_networks(w, d["actor"], d["critic"], X[sel], mu[sel], val[sel], agent=a)
