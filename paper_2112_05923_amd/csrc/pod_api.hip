@@ -158,21 +158,21 @@ int pack_nets(pr_handle *h, const pr_weights *actor, const pr_weights *critic) {
   const pr_config &c = h->cfg;
   const int S = h->S, Hd = c.hidden, D = c.n_stocks, P = c.n_agents, bf = c.mlp_dtype;
   const pr_weights *ws[2] = {actor, critic};
+  PackJob jobs[kMaxPackJobs];
+  int n = 0;
   for (int net = 0; net < 2; ++net) {
     const float *W[3] = {ws[net]->W1, ws[net]->W2, ws[net]->W3};
     const float *b[3] = {ws[net]->b1, ws[net]->b2, ws[net]->b3};
     const int in_dim[3] = {S, Hd, Hd};
     const int out_dim[3] = {Hd, Hd, net == 0 ? D : 1};
     for (int l = 0; l < 3; ++l)
-      POD_HIP(launch_pack_layer(h->stream, W[l], b[l], P, in_dim[l], out_dim[l], bf, 0, h->w_packed[net][l],
-                                h->b_packed[net][l]));
+      jobs[n++] = {W[l], b[l], h->w_packed[net][l], h->b_packed[net][l], in_dim[l], out_dim[l], 0};
   }
   // The persistent rollout kernel keeps its observation tile as [indicators | cash | prices | holdings] (and so do
-  // the one for small networks and the bf16 copy of the observations): the same layer-1 weights with their rows rotated by the D K indicator columns
-  // (biases are shared).
-  if (h->w1_rot)
-    POD_HIP(launch_pack_layer(h->stream, actor->W1, actor->b1, P, S, Hd, bf, D * c.n_ind, h->w1_rot,
-                              h->b_packed[0][0]));
+  // the one for small networks and the bf16 copy of the observations): the same layer-1 weights with their rows rotated
+  // by the D K indicator columns (biases are shared).
+  if (h->w1_rot) jobs[n++] = {actor->W1, actor->b1, h->w1_rot, h->b_packed[0][0], S, Hd, D * c.n_ind};
+  POD_HIP(launch_pack_layers(h->stream, jobs, n, P, bf));
   return PR_OK;
 }
 

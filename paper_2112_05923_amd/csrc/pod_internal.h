@@ -142,10 +142,16 @@ int64_t split_scratch_rows(int64_t n_envs, int hidden);
 
 size_t packed_weight_bytes(int in_dim, int out_dim, int bf16);
 int padded_out(int out_dim);
-// k_rot > 0: packed k row k' holds input row (k' < k_rot ? in_dim - k_rot + k' : k' - k_rot), i.e. the last k_rot
-// inputs come first.
-hipError_t launch_pack_layer(hipStream_t st, const float *W, const float *b, int P, int in_dim, int out_dim, int bf16,
-                             int k_rot, void *Wp, float *bp);
+// One layer to pack.  k_rot > 0: packed k row k' holds input row (k' < k_rot ? in_dim - k_rot + k' : k' - k_rot), i.e. the
+// last k_rot inputs come first.
+struct PackJob {
+  const float *W, *b;  // [P, in_dim, out_dim], [P, out_dim]
+  void *Wp;
+  float *bp;
+  int32_t in_dim, out_dim, k_rot;
+};
+constexpr int kMaxPackJobs = 7;  // three layers of two networks, and the actor's first layer in the rollout's order
+hipError_t launch_pack_layers(hipStream_t st, const PackJob *jobs, int n, int P, int bf16);
 // rows of X [rows, ldx] -> Y [rows, out_dim[2]]; row r uses agent ((r % N) / envs_per_agent).
 hipError_t launch_mlp(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx, float *Y,
                       int32_t N, int32_t envs_per_agent);
