@@ -275,9 +275,9 @@ int ppo_minibatch_grads(void *hip_stream, const pr_ppo_config *cfg, const float 
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and the same
  * results bit for bit, but the scratch lives in a fixed device array inside the library:
  * PR_STATIC_SCRATCH_BYTES (24 MiB) per GPU the library is used on, held until the process ends -- enough for the
- * paper's minibatch of 1024 with 512 hidden units and 30 stocks x 8 indicators (22.5 MB); ppo_workspace_bytes minus
- * the gradient tensors is what a shape needs.  A shape that needs more is refused with PR_ETOOBIG before any device
- * work.  The call allocates nothing (no hipMalloc / hipFree, no allocating library routine) and only enqueues on
+ * paper's minibatch of 1024 with 512 hidden units and 30 stocks x 8 indicators (22.5 MB).  Counted are the gathered
+ * rows, six buffers of batch x hidden, the outputs twice and eight partial W2 gradients; a shape for which these are more
+ * is refused with PR_ETOOBIG before any device work.  The call allocates nothing (no hipMalloc / hipFree, no allocating library routine) and only enqueues on
  * hip_stream.  All calls on one GPU share that GPU's array, which keeps the previous call's contents (nothing in
  * it has to start at zero): calls whose device work overlaps on one GPU -- two streams, two host threads -- race;
  * serialise them.  The first call on a device looks up the array's address there (not a stream operation, so make

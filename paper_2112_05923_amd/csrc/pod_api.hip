@@ -488,8 +488,7 @@ int ppo_minibatch_grads_noalloc(void *hip_stream, const pr_ppo_config *cfg, cons
   if (!net_ok(actor) || !net_ok(critic) || !net_ok(grad_actor) || !net_ok(grad_critic)) return PR_EINVAL;
   static_assert(PR_STATIC_SCRATCH_BYTES == (size_t)24 << 20, "header and library disagree on the scratch size");
   if (ppo_static_scratch_bytes() != PR_STATIC_SCRATCH_BYTES ||
-      ppo_scratch_bytes(cfg->batch, cfg->hidden, cfg->n_stocks, 1 + cfg->n_stocks * (2 + cfg->n_ind)) >
-          PR_STATIC_SCRATCH_BYTES)
+      !ppo_static_covers(cfg->batch, cfg->hidden, cfg->n_stocks, 1 + cfg->n_stocks * (2 + cfg->n_ind)))
     return PR_ETOOBIG;
   POD_HIP(launch_ppo_grads_static(static_cast<hipStream_t>(hip_stream), *cfg, obs, act_raw, logp_old, adv, ret, rows,
                                   *actor, *critic, *grad_actor, *grad_critic, stats));

@@ -98,8 +98,9 @@ hipError_t launch_ppo(hipStream_t st, const pr_ppo_config &c, const float *obs, 
                       const pr_net_params &critic, const pr_net_params &ga, const pr_net_params &gc,
                       const PpoAdam *adam, void *scratch, float *stats);
 // The same with the scratch in a fixed device array of ppo_static_scratch_bytes() (no workspace, no allocation);
-// hipErrorInvalidValue when the shape needs more.
+// hipErrorInvalidValue for the shapes it is not for.
 size_t ppo_static_scratch_bytes();
+bool ppo_static_covers(int B, int Hd, int D, int S);
 hipError_t launch_ppo_grads_static(hipStream_t st, const pr_ppo_config &c, const float *obs, const float *act,
                                    const float *logp_old, const float *adv, const float *ret, const int32_t *rows,
                                    const pr_net_params &actor, const pr_net_params &critic, const pr_net_params &ga,

@@ -21,8 +21,8 @@
 // dropped is smaller than the rounding of one fp32 product (pod_split3.h).  Six bf16 instructions take 6/16 of the time
 // of the fp32 instruction's same work.
 //
-// Measured (301-512-512 networks): a step at batch 1024 94 us (315 us as 38 launches); gradients at 15000 samples with
-// 256 hidden units 330 us (750 us).
+// Measured (301-512-512 networks): a step at batch 1024 93 us (315 us as 38 launches); gradients at 15000 samples with
+// 256 hidden units 356 us (753 us).
 #include <math.h>
 
 #include <algorithm>
@@ -1108,12 +1108,22 @@ std::atomic<void *> g_scratch_ptr[kMaxDevices];
 
 size_t ppo_static_scratch_bytes() { return kStaticScratchBytes; }
 
+// The shapes of the no-allocation call: those whose minibatch with gathered rows, six activation-sized buffers and eight
+// partial W2 gradients takes no more than the array.  make_plan needs less for some that are larger; where a caller is
+// told to bring a workspace does not move with the plan.
+bool ppo_static_covers(int B, int Hd, int D, int S) {
+  const size_t f = 4, Sp = (size_t)(S + 3) / 4 * 4;
+  const size_t bytes = align256((size_t)B * Sp * f) + 6 * align256((size_t)B * Hd * f) + 2 * align256((size_t)B * D * f) +
+                       2 * align256((size_t)B * f) + align256((size_t)((B + 7) / 8) * 4 * f) + align256((size_t)8 * Hd * Hd * f);
+  return bytes <= kStaticScratchBytes && ppo_scratch_bytes(B, Hd, D, S) <= kStaticScratchBytes;
+}
+
 hipError_t launch_ppo_grads_static(hipStream_t st, const pr_ppo_config &c, const float *obs, const float *act,
                                    const float *logp_old, const float *adv, const float *ret, const int32_t *rows,
                                    const pr_net_params &actor, const pr_net_params &critic, const pr_net_params &ga,
                                    const pr_net_params &gc, float *stats) {
   const int S = 1 + 2 * c.n_stocks + c.n_stocks * c.n_ind;
-  if (ppo_scratch_bytes(c.batch, c.hidden, c.n_stocks, S) > kStaticScratchBytes) return hipErrorInvalidValue;
+  if (!ppo_static_covers(c.batch, c.hidden, c.n_stocks, S)) return hipErrorInvalidValue;
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;

@@ -67,3 +67,17 @@ def test_noalloc_refuses_shapes_beyond_its_scratch_and_bad_arguments():
     torch.cuda.synchronize()
     assert float(ga["W1"].min()) == 7.0 and float(ga["W1"].max()) == 7.0       # nothing was enqueued
     assert pr.lib().ppo_minibatch_grads_noalloc(None, C.byref(cfg), *([None] * 6), *([None] * 4), None) == pr.PR_EINVAL
+
+
+# refused before any device work, so no device is needed: shapes just past the stated count of the scratch
+@pytest.mark.parametrize("B,D,K,Hd", [(1, 1, 0, 1024), (1500, 1, 0, 512), (2000, 5, 0, 512), (1300, 30, 8, 512), (4096, 30, 8, 256)])
+def test_noalloc_serves_no_shape_beyond_its_stated_scratch(B, D, K, Hd):
+    S = 1 + 2 * D + D * K
+    up = lambda floats: (4 * floats + 255) // 256 * 256
+    count = up(B * (S + 3 & ~3)) + 6 * up(B * Hd) + 2 * up(B * D) + 2 * up(B) + up((B + 7) // 8 * 4) + up(8 * Hd * Hd)
+    assert count > pr.PR_STATIC_SCRATCH_BYTES
+    w = inputs.WORKLOADS["large"].replace(n_stocks=D, n_ind=K, hidden=Hd)
+    cfg = pr.make_ppo_config(w, batch=B)
+    p = pr.PrNetParams(*([256] * 6))
+    rc = pr.lib().ppo_minibatch_grads_noalloc(None, C.byref(cfg), *([256] * 6), *([C.byref(p)] * 4), None)
+    assert rc == pr.PR_ETOOBIG
