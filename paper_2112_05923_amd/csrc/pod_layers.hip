@@ -1,5 +1,5 @@
-// One network layer per launch for batches of 64 to 8192 rows (the per-step policy of a few thousand envs), bf16
-// operands: a small-batch GEMM with the bias and tanh in its epilogue.
+// One network layer per launch for batches up to 8192 rows that are more than launch_few_rows takes (the per-step policy
+// of a few thousand envs), bf16 operands: a small-batch GEMM with the bias and tanh in its epilogue.
 //
 // A kernel that carries a row tile through all three layers would leave most compute units idle at these sizes.  Here a
 // workgroup owns 64 rows x 128 output features of one layer, so 2048 rows x 1024 features are 256 workgroups.

@@ -294,14 +294,12 @@ __global__ __launch_bounds__(kThreads) void mlp3_kernel(MlpArgs a) {
 }
 
 
-// ------------------------------------------------ one layer per launch, for few rows (fp32; bf16: pod_layers.hip)
-// A step of a small batch (a few thousand envs) has fewer 64-row tiles than the chip has compute units, and a
-// kernel that carries a row tile through all three layers leaves the rest idle.  Here a launch computes ONE
-// layer, tiled over rows x output features: workgroup (x, y) owns rows [32 x, 32 x + 32) and the four feature
-// tiles [4 y, 4 y + 4), one per wavefront, so rows / 32 x features / 128 workgroups run (512 for 2048 rows and
-// 1024 hidden units); the input rows are staged 8 k-blocks at a time, because with so little arithmetic per
-// workgroup the time goes to the memory round trips, one per staged chunk.  Activations travel between the launches as
-// fp32 rows in global memory (they stay in L2).
+// ------------------------------------------------ one layer per launch, fp32 (bf16: pod_layers.hip)
+// What launch_few_rows leaves of batches up to 8192 rows: more than 4096, or thousands of inputs.  A kernel that carries a
+// row tile through all three layers would leave compute units idle there.  Workgroup (x, y) of a launch owns rows
+// [32 x, 32 x + 32) and the four feature tiles [4 y, 4 y + 4) of ONE layer, one per wavefront; the input rows are staged 8
+// k-blocks at a time, because with so little arithmetic per workgroup the time goes to the memory round trips, one per
+// staged chunk.  Activations travel between the launches as fp32 rows in global memory (they stay in L2).
 constexpr int kSplitPD = 8;   // k-blocks per staged chunk of the layer-per-launch kernel
 struct LayerArgs {
   const float *X;      // [rows, ldx]
