@@ -167,6 +167,9 @@ hipError_t launch_layers(hipStream_t st, const PackedNet &net, int64_t rows, con
 bool few_rows(int64_t rows, int S, int hidden, int bf16, bool converted);
 hipError_t launch_few_rows(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx, float *Y,
                            int32_t N, int32_t envs_per_agent);
+// The output layer alone, on bf16 activations [rows][pitch].
+hipError_t launch_rows_output(hipStream_t st, const PackedNet &net, int64_t rows, const void *h, int64_t pitch, float *Y,
+                              int32_t N, int32_t envs_per_agent);
 hipError_t launch_rows_to_bf16(hipStream_t st, int64_t rows, const float *X, int64_t ldx, int S, const ObsShadow &out);
 
 // ------------------------------------------------------- persistent rollout

@@ -268,6 +268,12 @@ hipError_t launch_layers(hipStream_t st, const PackedNet &net, int64_t rows, con
   const void *in = x.p;
   int32_t pitch = x.pitch;
   for (int l = 0; l < 3; ++l) {
+    // A narrow output layer leaves few of these tiles (79 for 5000 rows x 100 stocks); workgroups of 32 features that split
+    // the inputs finish sooner until their reads of the rows outweigh it.  Per step of a rollout, this kernel -> that one:
+    // 8192 envs x 30 stocks, 512 units 39.9 -> 35.7 us, 1500 x 130 34.0 -> 30.7, 5000 x 100 55.4 -> 54.5, 2048 x 400 49.9 ->
+    // 48.7, 600 x 500 with 1024 units 53.6 -> 50.7; 2048 x 300 with 1024 units 49.3 -> 49.5, 2048 x 500 66.0 -> 67.9.
+    if (l == 2 && (rows + 63) / 64 * net.nct[2] * net.nkb[2] <= 512 * 32)
+      return launch_rows_output(st, net, rows, in, pitch, Y, N, envs_per_agent);
     LayerArgs a;
     a.X = static_cast<const __bf16 *>(in), a.xpitch = pitch, a.rows = (int32_t)rows;
     a.Y = l == 2 ? static_cast<void *>(Y) : net.split_h[l];

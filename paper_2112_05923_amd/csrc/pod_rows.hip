@@ -197,31 +197,45 @@ bool few_rows(int64_t rows, int S, int hidden, int bf16, bool converted) {
   return workgroups <= (S <= 640 ? 512 : 256);
 }
 
+namespace {
+RowsArgs layer_args(const PackedNet &net, int l, int64_t rows, const void *in, int64_t ld, float *Y, int32_t N,
+                    int32_t envs_per_agent) {
+  RowsArgs a;
+  a.X = in, a.ldx = ld, a.rows = rows;
+  a.Y = l == 2 ? static_cast<void *>(Y) : net.split_h[l];
+  a.ldy = l == 2 ? net.out_dim[2] : net.out_dim[0];
+  a.W = net.W[l], a.b = net.b[l], a.w_stride = net.w_stride[l], a.b_stride = net.b_stride[l];
+  a.in_dim = net.in_dim[l], a.out_dim = net.out_dim[l], a.nkb = net.nkb[l], a.nct = net.nct[l];
+  a.out_tanh = net.out_tanh;
+  a.N = N, a.envs_per_agent = envs_per_agent;
+  return a;
+}
+
+// 32 rows a workgroup until every compute unit has one (2000 rows x 256 units, fp32: 17.4 us, with 64 rows 23.8), then
+// 64, which halve the reads of the weights (4096 x 256: 24.1, with 32 rows 33.0)
+bool two_tiles(const RowsArgs &a) { return a.rows > 32 && (a.rows + 31) / 32 * a.nct > 256; }
+}  // namespace
+
 hipError_t launch_few_rows(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx, float *Y,
                            int32_t N, int32_t envs_per_agent) {
-  const int Hd = net.out_dim[0];
   const void *in = X;
   int64_t ld = ldx;
   for (int l = 0; l < 3; ++l) {
-    RowsArgs a;
-    a.X = in, a.ldx = ld, a.rows = rows;
-    a.Y = l == 2 ? static_cast<void *>(Y) : net.split_h[l];
-    a.ldy = l == 2 ? net.out_dim[2] : Hd;
-    a.W = net.W[l], a.b = net.b[l], a.w_stride = net.w_stride[l], a.b_stride = net.b_stride[l];
-    a.in_dim = net.in_dim[l], a.out_dim = net.out_dim[l], a.nkb = net.nkb[l], a.nct = net.nct[l];
-    a.out_tanh = net.out_tanh;
-    a.N = N, a.envs_per_agent = envs_per_agent;
-    // 32 rows a workgroup until every compute unit has one (2000 rows x 256 units, fp32: 17.4 us, with 64 rows 23.8), then
-    // 64, which halve the reads of the weights (4096 x 256: 24.1, with 32 rows 33.0)
-    const bool two = rows > 32 && (rows + 31) / 32 * a.nct > 256;
+    const RowsArgs a = layer_args(net, l, rows, in, ld, Y, N, envs_per_agent);
     hipError_t e;
-    if (net.bf16) e = two ? launch_dtype<true, 2>(st, a, l) : launch_dtype<true, 1>(st, a, l);
-    else e = two ? launch_dtype<false, 2>(st, a, l) : launch_dtype<false, 1>(st, a, l);
+    if (net.bf16) e = two_tiles(a) ? launch_dtype<true, 2>(st, a, l) : launch_dtype<true, 1>(st, a, l);
+    else e = two_tiles(a) ? launch_dtype<false, 2>(st, a, l) : launch_dtype<false, 1>(st, a, l);
     if (e != hipSuccess) return e;
     in = a.Y;
-    ld = Hd;
+    ld = a.ldy;
   }
   return hipSuccess;
+}
+
+hipError_t launch_rows_output(hipStream_t st, const PackedNet &net, int64_t rows, const void *h, int64_t pitch, float *Y,
+                              int32_t N, int32_t envs_per_agent) {
+  const RowsArgs a = layer_args(net, 2, rows, h, pitch, Y, N, envs_per_agent);
+  return two_tiles(a) ? launch_layer<true, 2, LAST>(st, a) : launch_layer<true, 1, LAST>(st, a);
 }
 
 }  // namespace pod

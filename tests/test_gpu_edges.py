@@ -118,7 +118,8 @@ def test_env_step_tiles(N, D, K, cash0):
 # iterations, an odd and an even number of them), more workgroups than compute units, several agents
 @pytest.mark.parametrize("N,rows,agents,Hd,D,K", [(64, 64, 1, 128, 2, 0), (100, 65, 1, 160, 15, 1), (256, 256, 4, 128, 30, 8),
                                                   (700, 700, 1, 512, 32, 0), (256, 200, 2, 544, 127, 3), (4200, 4200, 1, 512, 60, 2),
-                                                  (130, 130, 1, 1024, 160, 2), (8192, 8192, 1, 256, 16, 2)])
+                                                  (130, 130, 1, 1024, 160, 2), (8192, 8192, 1, 256, 16, 2),
+                                                  (1100, 1100, 1, 1024, 490, 0)])
 def test_layer_launches(N, rows, agents, Hd, D, K):
     w = inputs.WORKLOADS["large"].replace(n_envs=N, n_agents=agents, hidden=Hd, n_stocks=D, n_ind=K, steps=2)
     d = inputs.make_all(w, horizon=2, n_market=1, steps=2)
