@@ -3,9 +3,9 @@
 //
 // A kernel that carries a row tile through the network streams every weight through one compute unit: 48 rows of 301 inputs
 // and 512 hidden units took 28 us for 0.87 MB of bf16 weights.  Here a workgroup owns 32 output features of one layer and 32
-// or 64 rows, its eight wavefronts split the inputs, and each requests all of its weight blocks and rows before its first
-// matrix instruction: a launch is one memory round trip, a few matrix instructions and one exchange of partial sums
-// through LDS.  Nothing is staged: a lane's operand is eight consecutive columns of one row, read from where they are.
+// or 64 rows and its eight wavefronts split the inputs: a launch is a memory round trip or two, a few matrix instructions
+// and one exchange of partial sums through LDS.  Nothing is staged: a lane's operand is eight consecutive columns of one
+// row, read from where they are.
 // What bounds it is that round trip and the start of a launch; with many rows it is the rows, read again by every feature
 // tile's workgroup.
 #include "pod_internal.h"
@@ -83,12 +83,15 @@ __device__ inline void operand_of(tile::Blk3 &x, const float (&v)[8], const u32x
   for (int i = 0; i < 3; ++i) x.p[i] = __builtin_bit_cast(u32x4, o[i]);
 }
 
-// RT: 32-row tiles per workgroup; KB: k-blocks a wavefront requests at a time
+// RT: 32-row tiles per workgroup; KB: k-blocks a wavefront requests at a time.  What hides a round trip is the other
+// workgroups of the compute unit rather than requests in flight, so the registers stay few: twice these blocks took 12.6
+// us where this takes 11.5 (48 rows x 512 units, bf16), 14.9 where 12.6 (48 x 256, fp32), 17.4 where 15.3 (4096 x 256,
+// bf16), four times these 24.3 -> 36.8 (4096 x 256, fp32).
 template <bool BF16, int RT, Layer L>
 __global__ __launch_bounds__(kThreads, 2) void rows_layer_kernel(RowsArgs a) {
   using O = tile::Op<BF16>;
   using Block = typename O::Block;
-  constexpr int KB = RT == 1 ? 4 : 2;
+  constexpr int KB = RT == 1 ? 2 : 1;
   extern __shared__ __align__(16) float planes[];  // [kWaves][32 RT][kPitch]
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t row0 = (int64_t)blockIdx.x * (32 * RT);
@@ -182,13 +185,13 @@ hipError_t launch_dtype(hipStream_t st, const RowsArgs &a, int l) {
 // Where the lines lie, in workgroups of 64 rows x 32 features; us per forward pass, the kernels that
 // take over -> this one.  A workgroup per feature tile reads the rows once each, which with many of them costs more than the
 // others' staging.
-//   bf16, 301 inputs: 48 rows x 512 units 28.4 -> 12.6, 1000 x 512 24.9 -> 14.2, 4096 x 256 (512 workgroups) 23.3 -> 17.1;
+//   bf16, 301 inputs: 48 rows x 512 units 28.4 -> 11.5, 1000 x 512 24.9 -> 13.6, 4096 x 256 (512 workgroups) 23.3 -> 15.3;
 //   4096 x 512 (1024) 26.8 -> 30.5, 8000 x 256 25.9 -> 32.2.  1001 inputs: 1024 x 512 (256) 32.4 -> 18.1.  3001: 500 x 1024 (256)
 //   55.2 -> 38.1.
 //   bf16 in a rollout, whose other kernels have their rows converted already (us per step): 1024 envs x 100 stocks (256) 35.3 ->
 //   29.6, 1000 x 300 x 3 indicators (256) 40.9 -> 38.1, 2000 x 60 (512) 32.1 -> 35.4; 500 stocks x 4: 256 x 1024 units (128) 52.1 ->
 //   40.6, 512 x 1024 (256) 53.6 -> 54.8.
-//   fp32: 8 x 512 46.9 -> 13.5, 1000 x 512 36.1 -> 20.4, 4096 x 256 28.2 -> 24.2, 4096 x 512 54.1 -> 44.8, with 1001 inputs 79.2 ->
+//   fp32: 8 x 512 46.9 -> 13.4, 1000 x 512 36.1 -> 20.3, 4096 x 256 28.2 -> 22.2, 4096 x 512 54.1 -> 44.2, with 1001 inputs 79.2 ->
 //   70.3, with 3001 149 -> 164 and 2048 x 512 132 -> 86; 8000 x 512 88.4 -> 91.9, 8000 x 256 41.2 -> 42.3.
 bool few_rows(int64_t rows, int S, int hidden, int bf16, bool converted) {
   const int64_t workgroups = (rows + 63) / 64 * (hidden / 32);
