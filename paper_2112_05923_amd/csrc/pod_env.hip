@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kThreads) void observe_kernel(EnvDims d, EnvState s
 template <int E, int ND>
 __global__ __launch_bounds__(kEnvThreads, 4) void env_step_kernel(EnvDims d, EnvState s, const float *__restrict__ price,
                                                                  const float *__restrict__ ind, StepIO io) {
-  using Tr = Trade<E, ND>;
+  using Tr = Trade<E, ND, false>;
   constexpr int TPE = Tr::TPE;         // threads per env
   constexpr int NI = ND == 1 ? 4 : 8;  // 16-byte indicator groups per thread that are requested with the prices
   extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -315,7 +315,7 @@ static hipError_t launch_step(hipStream_t st, const EnvDims &d, const EnvState &
   constexpr auto kern = env_step_kernel<E, ND>;
   const hipError_t e = allow_full_lds<kern>();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)((d.N + E - 1) / E)), dim3(kEnvThreads), trade_lds(E, d.D), st, d, s, price, ind, io);
+  hipLaunchKernelGGL(kern, dim3((unsigned)((d.N + E - 1) / E)), dim3(kEnvThreads), trade_lds(E, false, d.D), st, d, s, price, ind, io);
   return hipGetLastError();
 }
 

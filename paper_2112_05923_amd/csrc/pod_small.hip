@@ -12,9 +12,9 @@
 // trades' chain (pod_trade.h).  The loads of a step -- noise, the next market row
 // -- depend on the cursor only and travel behind the network.
 // Per step, before (a network launch or three and an env launch) -> now:
-//   fp32,  64 hidden units: 16 envs x 5 stocks 19.6 -> 3.9 us, 512 x 30 x 8 indicators 30 -> 5.0, 16384 x 30 x 8 52 -> 20
+//   fp32,  64 hidden units: 16 envs x 5 stocks 19.6 -> 3.6 us, 512 x 30 x 8 indicators 30 -> 5.1, 16384 x 30 x 8 52 -> 20
 //   fp32, 128: 64 x 10 x 2 27 -> 5.5, 512 x 30 x 8 37 -> 10.3 (120 of its registers spill), 4096 x 30 x 8 39 -> 14
-//   bf16, 128: 512 x 30 x 8 30 -> 4.0, 16384 x 30 x 8 34 -> 16
+//   bf16, 128: 512 x 30 x 8 30 -> 4.2, 16384 x 30 x 8 34 -> 16
 #include "pod_internal.h"
 #include "pod_tile.h"
 #include "pod_trade.h"
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
   using O = Op<BF16>;
   using Block = typename O::Block;
   using Gm = Geometry<NCT>;
-  using Tr = Trade<SE, 1>;
+  using Tr = Trade<SE, 1, true>;
   constexpr int TPE = Tr::TPE, NI = 4, KG = Gm::KG, F = Gm::F, B2 = Gm::NKB / KG;
   constexpr int XP = tile_pitch<BF16>(B1 * KG), HP = tile_pitch<BF16>(Gm::NKB);
   extern __shared__ __align__(16) unsigned char lds[];
@@ -324,7 +324,7 @@ hipError_t launch_inst(hipStream_t st, const SmallArgs &a) {
   if (e != hipSuccess) return e;
   const size_t planes = Gm::KG * Gm::PP > Gm::NKB * 36 ? Gm::KG * Gm::PP : Gm::NKB * 36;
   const size_t lds = (size_t)SE * (tile::tile_pitch<BF16>(B1 * Gm::KG) + tile::tile_pitch<BF16>(Gm::NKB)) + planes * SE * 4 +
-                     trade_lds(SE, a.d.D);
+                     trade_lds(SE, true, a.d.D);
   hipLaunchKernelGGL(kern, dim3((unsigned)((a.d.N + SE - 1) / SE)), dim3(kEnvThreads), lds, st, a);
   return hipGetLastError();
 }

@@ -15,6 +15,7 @@ namespace {
 constexpr int kEnvThreads = 512;
 typedef float env_f32x4 __attribute__((ext_vector_type(4)));
 typedef env_f32x4 env_f32x4u __attribute__((aligned(4)));
+typedef double env_f64x2 __attribute__((ext_vector_type(2)));
 
 struct RowInfo {
   int32_t row_now;   // market row the trades execute at
@@ -43,6 +44,22 @@ __device__ inline double sum_lanes(double v, int width) {
   return v;
 }
 
+// Account values are the cash plus the holdings h p in stock order, in binary64.  Threads that add them up in another
+// order get the same number when nothing is rounded on the way: cash and products are multiples of some 2^x, and while no
+// sum exceeds 2^53 of them every partial sum is a binary64 number.  Multiples of what: a product of the last place of its
+// price p, at least 2^-24 p; the cash of its lowest bit that is set (cash_unit is that or, for a power of two, less).
+// `lowest`: the smallest price, negative if a holding is; the bound leaves a factor of two for the rounding of the values
+// themselves, and fails for values that are negative, infinite or no numbers.
+__device__ inline float cash_unit(float c) {
+  const uint32_t b = __builtin_bit_cast(uint32_t, c);
+  return c - __builtin_bit_cast(float, b & (b - 1));
+}
+__device__ inline bool order_free(double v0, double v1, float lowest, float cash0, float cash1) {
+  const float bound = fminf(fminf(lowest * 0x1p28f, 0x1p127f), fminf(cash_unit(cash0), cash_unit(cash1)) * 0x1p52f);
+  const float f0 = (float)v0, f1 = (float)v1;
+  return f0 >= 0.0f && f1 >= 0.0f && f0 <= bound && f1 <= bound;
+}
+
 // s + v[0][0] + v[0][1] + ... in this order (two register sets, read one ahead of the other by hand, were slower)
 __device__ inline float serial_sum(float s, const env_f32x4 *v, int n) {
 #pragma unroll 8
@@ -63,22 +80,31 @@ __device__ inline float serial_sum(float s, const env_f32x4 *v, int n) {
 //    stock order (ballots inside a wavefront, counts through LDS across two).  It runs in the env's own wavefront
 //    (half) and needs one dependent operation per purchase while the cash lasts, none for a purchase it does not
 //    buy a single share of, and the quotient only in between (13.5 -> 1.8 us of a step with 250 purchases);
-//  - the account values before and after are sums over the env's threads in binary64;
+//  - the account values before and after are sums over the env's threads, taken again in stock order by one of them where
+//    the order shows in the last bit (prices far apart in size).  With WALK they are always taken in stock order: where
+//    one workgroup has the compute unit to itself the sums over lanes take longer (rollout_small_kernel, 5 stocks 3.97 ->
+//    3.60 us a step, 30 stocks 5.16 -> 4.98); where others want the same issue slots it is the other way round
+//    (env_step_kernel, 16384 envs x 30 stocks 15.5 us against 16.3, 4096 x 64 8.0 against 9.1);
 //  - up to a wavefront per env there is no barrier in here: an env's threads only meet each other.
-template <int E, int ND>
+template <int E, int ND, bool WALK>
 struct Trade {
   static constexpr int TPE = kEnvThreads / E;
   static constexpr int CW = TPE < 64 ? TPE : 64;  // the part of a wavefront one env has
   static constexpr int NCW = TPE / CW;            // wavefronts per env
+  static_assert(!WALK || NCW == 1, "");
   int D, D4, lp, sp, op;
   Purchase *list;  // [E][lp] purchases in stock order (odd pitch in 16 bytes)
   float *sell;     // [E][sp] proceeds of the sales, 0 elsewhere
   float *sq;       // [E][sp] squared noise
   float *out;      // [E][op] outlay k u of the purchases, by list position
   int32_t *buy;    // [E][lp] shares bought, by list position
-  double *part;    // [2][E][2] account value before / after, per wavefront of an env
+  double *part;    // [2][E][2] holdings' value before / after, per wavefront of an env
+  float *low;      // [E][2] and their smallest price
+  float *both;     // [E][2] cash before / after
   float *e2s;      // [E] sum of the squares
   int32_t *cnt;    // [E][ND NCW] purchases
+  float *now;      // several wavefronts per env (whose registers are few): [E][D4] prices of the trades
+  double *terms;   // WALK: [E][D4] holdings' values in stock order
 
   __device__ Trade(unsigned char *lds, int D_) : D(D_), D4((D_ + 3) & ~3), lp(D_ | 1), sp(D4 + 4), op(D4 + 20) {
     list = reinterpret_cast<Purchase *>(lds);
@@ -87,8 +113,12 @@ struct Trade {
     out = sq + E * sp;
     buy = reinterpret_cast<int32_t *>(out + E * op);
     part = reinterpret_cast<double *>(buy + E * lp);
-    e2s = reinterpret_cast<float *>(part + 4 * E);
+    low = reinterpret_cast<float *>(part + 4 * E);
+    both = low + 2 * E;
+    e2s = both + 2 * E;
     cnt = reinterpret_cast<int32_t *>(e2s + E);
+    now = reinterpret_cast<float *>(cnt + 8 * E);
+    terms = reinterpret_cast<double *>(now);
   }
 
   // all of an env's threads have written what the others read
@@ -130,7 +160,8 @@ struct Trade {
       q[i] = 0;
       kf[i] = 0.0f;
       unit[i] = 0.0f;
-      if (ok) a0 += (double)h[i] * (double)pn[i];
+      const double term = ok ? (double)h[i] * (double)pn[i] : 0.0;
+      a0 += term;
       if (k < 0) {
         const int32_t qs = min(-k, h[i]);
         h[i] -= qs;
@@ -143,6 +174,8 @@ struct Trade {
       }
       if (dd < D4) {
         sell[e * sp + dd] = sale;
+        if (NCW > 1) now[e * D4 + dd] = pn[i];
+        if (WALK) terms[e * D4 + dd] = term;
         sq[e * sp + dd] = ok ? eps[i] * eps[i] : 0.0f;
       }
       const uint64_t mine = mine_of(__ballot(k > 0));
@@ -154,7 +187,7 @@ struct Trade {
         cnt[(e * ND + i) * NCW + cw] = __popcll(mine);
       }
     }
-    a0 = sum_lanes(a0, CW);
+    if (!WALK) a0 = sum_lanes(a0, CW);
     if (NCW > 1) {
       if (cl == 0) part[e * 2 + cw] = a0;
       __syncthreads();
@@ -177,17 +210,30 @@ struct Trade {
     market();
     meet();
 
+    // the squares are summed in stock order (the log-probability is the same number in every schedule), and so are the sales
     e2 = 0.0f;
-    if (cw == NCW - 1 && want_e2) {
-      // the squares in stock order (the log-probability is the same number in every schedule)
-      e2 = serial_sum(0.0f, reinterpret_cast<const env_f32x4 *>(sq + e * sp), D4 / 4);
+    double v0 = (double)cash_in;
+    const env_f32x4 *sales = reinterpret_cast<const env_f32x4 *>(sell + e * sp), *squares = reinterpret_cast<const env_f32x4 *>(sq + e * sp);
+    if (WALK) {
+      const env_f64x2 *t = reinterpret_cast<const env_f64x2 *>(terms + e * D4);
+#pragma unroll 2
+      for (int c = 0; c < D4 / 4; ++c) {
+        const env_f32x4 x = sales[c], y = squares[c];
+        const env_f64x2 lo = t[2 * c], hi = t[2 * c + 1];
+        cash = cash + x[0], e2 = e2 + y[0], v0 = v0 + lo[0];
+        cash = cash + x[1], e2 = e2 + y[1], v0 = v0 + lo[1];
+        cash = cash + x[2], e2 = e2 + y[2], v0 = v0 + hi[0];
+        cash = cash + x[3], e2 = e2 + y[3], v0 = v0 + hi[1];
+      }
+    } else if (cw == NCW - 1 && want_e2) {
+      e2 = serial_sum(0.0f, squares, D4 / 4);
       if (NCW > 1 && cl == 0) e2s[e] = e2;
     }
     if (cw == 0) {
       // -- the ledger (Table 1 actions: sell / buy / hold): all sales, then all purchases, in stock order, each limited
       // by the cash left:
       //   m = floor(cash / u); q = min(k, max(m, 0)); if (q u > cash) q -= 1; cash -= q u        (binary32)
-      cash = serial_sum(cash, reinterpret_cast<const env_f32x4 *>(sell + e * sp), D4 / 4);
+      if (!WALK) cash = serial_sum(cash, sales, D4 / 4);
       const Purchase *lst = list + e * lp;
       auto affordable = [&](float c, float u) { return mine_of(__ballot(!(c < u))); };
       for (int c0 = 0; c0 < total; c0 += CW) {
@@ -243,40 +289,87 @@ struct Trade {
     meet();
 
     // -- executed trades, holdings, account value after them
-    double a1 = 0.0;
+    double a1 = 0.0, v1 = (double)cash;
+    float lowest = __builtin_inff();
+    int32_t sign = 0;
+    int32_t h1[ND];
+    // (not WALK) the values' terms in stock order where the purchases were, which all of an env's threads are past
+    double *term0 = reinterpret_cast<double *>(list + e * lp), *term1 = term0 + lp;
+    auto price_now = [&](int i) { return NCW > 1 ? now[e * D4 + min(tl + TPE * i, D - 1)] : pn[i]; };
+    auto put_terms = [&](int i) {
+      const int dd = tl + TPE * i;
+      if (dd < D) term0[dd] = (double)(h1[i] - q[i]) * (double)price_now(i), term1[dd] = (double)h1[i] * (double)pv[i];
+    };
+    auto add_terms = [&]() {
+      v0 = (double)cash_in, v1 = (double)cash;
+#pragma unroll 8
+      for (int dd = 0; dd < D; ++dd) v0 += term0[dd], v1 += term1[dd];
+    };
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
+      const int dd = tl + TPE * i;
       if (kf[i] > 0.0f) {
         q[i] = buy[e * lp + rank[i]];
         h[i] += q[i];
       }
-      if (live && tl + TPE * i < D) {
-        a1 += (double)h[i] * (double)pv[i];
+      h1[i] = h[i];
+      const double term = (double)h[i] * (double)pv[i];
+      if (WALK && dd < D) terms[e * D4 + dd] = term;
+      if (live && dd < D) {
+        a1 += term;
+        if (!WALK) lowest = fminf(lowest, fminf(price_now(i), pv[i])), sign |= h[i] | (h[i] - q[i]);
         booked(i);
       }
     }
-    a1 = sum_lanes(a1, CW);
-    double v0 = (double)cash_in, v1 = (double)cash;
-    if (NCW > 1) {
-      if (cl == 0) part[2 * E + e * 2 + cw] = a1;
-      __syncthreads();
-      if (tl == 0) {
-#pragma unroll
-        for (int w = 0; w < NCW; ++w) v0 += part[e * 2 + w], v1 += part[2 * E + e * 2 + w];
-        e2 = e2s[e];
+    if (WALK) {
+      meet();
+      const env_f64x2 *t = reinterpret_cast<const env_f64x2 *>(terms + e * D4);
+#pragma unroll 4
+      for (int c = 0; c < D4 / 2; ++c) {
+        const env_f64x2 x = t[c];
+        v1 = v1 + x[0];
+        v1 = v1 + x[1];
       }
     } else {
-      v0 += a0;
-      v1 += a1;
+      a1 = sum_lanes(a1, CW);
+      if (sign < 0) lowest = -1.0f;
+      bool again;  // for the whole workgroup, or wavefront
+      if (NCW > 1) {
+        for (int o = 1; o < CW; o *= 2) lowest = fminf(lowest, __shfl_xor(lowest, o));
+        if (cl == 0) part[2 * E + e * 2 + cw] = a1, low[e * 2 + cw] = lowest;
+        if (tl == 0) both[e * 2] = cash_in, both[e * 2 + 1] = cash;
+        __syncthreads();
+        // every wavefront looks at all envs: they agree without another barrier
+        const int el = lane & (E - 1);
+        double w0 = (double)both[el * 2], w1 = (double)both[el * 2 + 1];
+        lowest = __builtin_inff();
+#pragma unroll
+        for (int w = 0; w < NCW; ++w)
+          w0 += part[el * 2 + w], w1 += part[2 * E + el * 2 + w], lowest = fminf(lowest, low[el * 2 + w]);
+        again = __ballot(!order_free(w0, w1, lowest, both[el * 2], both[el * 2 + 1])) != 0;
+        v0 = __shfl(w0, e), v1 = __shfl(w1, e);
+        e2 = e2s[e];
+      } else {
+        v0 += a0;
+        v1 += a1;
+        again = __ballot(live && !order_free(v0, v1, lowest, cash_in, cash)) != 0;
+      }
+      if (again) {
+#pragma unroll
+        for (int i = 0; i < ND; ++i) put_terms(i);
+        meet();
+        if (tl == 0) add_terms();
+      }
     }
     r = (v1 - v0) * (double)d.rho;
   }
 };
 
-inline size_t trade_lds(int E, int D) {
+inline size_t trade_lds(int E, bool walk, int D) {
   const int D4 = (D + 3) & ~3, lp = D | 1;
   return (size_t)E * lp * sizeof(Purchase) + (size_t)E * (2 * (D4 + 4) + D4 + 20) * 4 + (size_t)E * lp * 4 +
-         (size_t)4 * E * 8 + (size_t)E * 4 + (size_t)E * 8 * 4;
+         (size_t)4 * E * 8 + (size_t)4 * E * 4 + (size_t)E * 4 + (size_t)E * 8 * 4 +
+         (walk ? (size_t)E * D4 * 8 : E * 64 < kEnvThreads ? (size_t)E * D4 * 4 : 0);
 }
 
 }  // namespace

@@ -244,3 +244,43 @@ def test_few_rows(base, N, rows, agents, Hd, D, K):
         sel = pick[(pick % N) // (N // agents) == a]
         if len(sel):
             parity.check_networks(w, d["actor"], d["critic"], X[sel], mu[sel], val[sel], agent=a)
+
+
+# every schedule and every tile of the env step: account values, in binary64, are the cash plus the holdings in stock order.
+# Prices next to each other in size, where any order gives the same number; over seven decades in one env, where the order
+# shows in the last bits; and both among the envs of one workgroup
+@pytest.mark.parametrize("spread", ["none", "all", "some"])
+@pytest.mark.parametrize("base,N,D,K,Hd,fused", [("large", 64, 30, 8, 512, True), ("dow30", 64, 30, 8, 256, True),
+                                                 ("tiny", 37, 30, 8, 64, False), ("large", 33, 32, 0, 128, False),
+                                                 ("large", 35, 31, 2, 256, False), ("large", 33, 60, 1, 256, False),
+                                                 ("large", 4100, 50, 0, 256, False), ("large", 9, 100, 2, 256, False),
+                                                 ("large", 4100, 100, 0, 256, False), ("large", 9, 200, 1, 512, False),
+                                                 ("large", 2050, 200, 0, 512, False), ("large", 7, 500, 1, 512, False)])
+def test_account_values_are_summed_in_stock_order(base, N, D, K, Hd, fused, spread):
+    T, H = 12, 7
+    # (the checker takes cash / price as a 32-bit integer: 1e5 over 1e-4 is one)
+    w = inputs.WORKLOADS[base].replace(n_envs=N, hidden=Hd, n_stocks=D, n_ind=K, steps=T, cash0=1e5)
+    d = inputs.make_all(w, horizon=H, steps=T)
+    rng = np.random.default_rng(N + D)
+    if spread != "none":
+        factor = 10.0 ** rng.uniform(-5.0, 1.0, (N, D))
+        d["price"] *= np.where((np.arange(N) % 3 == 1)[:, None] | (spread == "all"), factor, 1.0).astype(np.float32)
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    cfg = pr.make_config(w, horizon=H, schedule=pr.PR_SCHED_FUSED if fused else pr.PR_SCHED_STEPWISE)
+    ro = pr.Rollout(cfg, _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+    runs = ["forced"] + (["policy"] if Hd <= 128 or fused else [])
+    for run in runs:
+        ro.reset()
+        out = ro.alloc_buffers(T, value=False, logp=True, mu=run == "policy", shares=True)
+        if run == "forced":
+            mu = rng.uniform(-0.4, 1, d["noise"].shape).astype(np.float32)
+            ro.step_forced(T, _t(mu), _t(d["noise"]), out)
+        else:
+            ro.step_T(T, _t(d["noise"]), out)
+        torch.cuda.synchronize()
+        rec = {k: parity.to_np(v) for k, v in out.items()}
+        _, st = parity.check_env_record(w, oracle.cfg_from_workload(w, horizon=H), rec, d["price"], d["ind"], d["noise"],
+                                        mu if run == "forced" else rec["mu"])
+        got = {k: parity.to_np(v) for k, v in ro.get_state().items()}
+        for k, want in (("ep_return", st.ep_ret), ("ep_sum", st.ep_sum), ("ep_sqsum", st.ep_sqsum)):
+            assert np.array_equal(got[k], want), (run, k, float((got[k] != want).mean()))
