@@ -284,3 +284,36 @@ def test_account_values_are_summed_in_stock_order(base, N, D, K, Hd, fused, spre
         got = {k: parity.to_np(v) for k, v in ro.get_state().items()}
         for k, want in (("ep_return", st.ep_ret), ("ep_sum", st.ep_sum), ("ep_sqsum", st.ep_sqsum)):
             assert np.array_equal(got[k], want), (run, k, float((got[k] != want).mean()))
+
+
+# an infinite weight of the last input saturates its unit whatever the number of inputs and of hidden units is a multiple
+# of; 0 x infinity is NaN only where the sums themselves have it (gradients through that weight)
+@pytest.mark.parametrize("B,D,K,Hd,layer", [(70, 30, 8, 64, "W1"), (1500, 30, 8, 512, "W1"), (70, 1, 0, 32, "W1"),
+                                            (70, 5, 2, 96, "W2"), (2500, 5, 2, 96, "W2"), (70, 31, 2, 128, "W1")])
+def test_learner_with_an_infinite_weight_of_the_last_input(B, D, K, Hd, layer):
+    w = inputs.WORKLOADS["dow30"].replace(n_stocks=D, n_ind=K, hidden=Hd)
+    rng = np.random.default_rng(B + D)
+    S = w.state_dim
+    nets = {n: {k: v[0].copy() for k, v in inputs.make_weights(w, critic=(n == "critic")).items()} for n in ("actor", "critic")}
+    for n in nets.values():
+        n[layer][-1, 3] = np.inf
+    obs = np.abs(rng.standard_normal((B, S))).astype(np.float32)
+    a = nets["actor"]
+    mu = oracle.mlp(obs, a["W1"], a["b1"], a["W2"], a["b2"], a["W3"], a["b3"], True, False)
+    assert np.isfinite(mu).all()
+    act = (mu + w.sigma * rng.standard_normal((B, D))).astype(np.float32)
+    logp = (-0.5 * ((act - mu) / w.sigma) ** 2).sum(1) - D * (np.log(w.sigma) + 0.5 * np.log(2 * np.pi))
+    logp_old = (logp + rng.choice([-0.4, -0.05, 0.1, 0.5], B)).astype(np.float32)
+    adv, ret = rng.standard_normal(B).astype(np.float32), rng.standard_normal(B).astype(np.float32)
+    ga, gc, stats, _ = oracle.ppo_grads(obs, act, logp_old, adv, ret, nets["actor"], nets["critic"], w.sigma, 0.2, 0.5)
+    up = lambda net: {k: _t(v) for k, v in net.items()}
+    dga, dgc, dstats = pr.ppo_minibatch_grads(pr.make_ppo_config(w, batch=B), _t(obs), _t(act), _t(logp_old), _t(adv),
+                                              _t(ret), None, up(nets["actor"]), up(nets["critic"]))
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(parity.to_np(dstats), stats, rtol=2e-4, atol=1e-6)
+    for want, got in ((ga, dga), (gc, dgc)):
+        for k in oracle.NET_KEYS:
+            g = parity.to_np(got[k])
+            assert np.array_equal(np.isnan(g), np.isnan(want[k])), (k, np.isnan(g).mean(), np.isnan(want[k]).mean())
+            ok = ~np.isnan(want[k])
+            assert np.abs(g - want[k])[ok].max(initial=0.0) <= parity.TOL_F32 * max(np.abs(want[k])[ok].max(initial=0.0), 1e-30), k
