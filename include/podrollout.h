@@ -189,7 +189,11 @@ int rollout_step_forced(pr_handle *h, int32_t T, const float *mu, const float *n
 /* One network on its own: rows of X ([rows, S], row stride ldx floats) through
  * the actor (Y [rows, D]) or the critic (Y [rows]) of the agent that owns env
  * (row % N).  These are the kernels rollout_step_T uses for the critic and, in the
- * stepwise schedule of all but small networks, for the actor. */
+ * stepwise schedule of all but small networks, for the actor.  Several host threads may
+ * ask one handle.  What a call on up to 8192 rows keeps between its launches lies in the
+ * workspace, beside what a rollout keeps there, and the handle's stream orders it; a call
+ * that is captured into a graph writes nothing but Y, so the graph can be replayed on any
+ * stream, beside other work of the handle (on few rows it takes longer). */
 int rollout_mlp_forward(pr_handle *h, int32_t net, int64_t rows, const float *X, int64_t ldx, float *Y);
 
 /* Copy the per-env state out of / into the handle (device buffers). */

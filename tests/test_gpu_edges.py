@@ -317,3 +317,77 @@ def test_learner_with_an_infinite_weight_of_the_last_input(B, D, K, Hd, layer):
             assert np.array_equal(np.isnan(g), np.isnan(want[k])), (k, np.isnan(g).mean(), np.isnan(want[k]).mean())
             ok = ~np.isnan(want[k])
             assert np.abs(g - want[k])[ok].max(initial=0.0) <= parity.TOL_F32 * max(np.abs(want[k])[ok].max(initial=0.0), 1e-30), k
+
+
+# queries of one handle from several sides at once: a captured query writes nothing but its output, so graphs replay beside
+# each other, eager queries and a captured rollout; launches of one call stay together when two threads ask
+@pytest.mark.parametrize("base,N,rows,Hd,D,K", [("large", 128, 48, 512, 30, 8), ("large", 16, 1000, 64, 5, 2), ("dow30", 128, 33, 256, 30, 8),
+                                                ("dow30", 1000, 1000, 512, 30, 4), ("large", 256, 200, 1024, 300, 2), ("dow30", 64, 1, 96, 3, 0)])
+def test_queries_side_by_side(base, N, rows, Hd, D, K):
+    import threading
+    T = 6
+    w = inputs.WORKLOADS[base].replace(n_envs=N, hidden=Hd, n_stocks=D, n_ind=K, steps=T)
+    side, others = torch.cuda.Stream(), [torch.cuda.Stream() for _ in range(3)]
+    with torch.cuda.stream(side):
+        d = inputs.make_all(w, horizon=T, n_market=1, steps=T)
+        dev = lambda m: {k: _t(v) for k, v in m.items()}
+        ro = pr.Rollout(pr.make_config(w, horizon=T, n_market=1), _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+        g = torch.Generator(device=DEV)
+        g.manual_seed(rows)
+        X = [torch.randn((rows, w.state_dim), generator=g, device=DEV) for _ in range(4)]
+        new = lambda: torch.full((rows, D), float("nan"), device=DEV)
+        noise, out = _t(d["noise"]), ro.alloc_buffers(T, value=True, logp=True)
+
+        def roll():
+            ro.reset()
+            ro.step_T(T, noise, out)
+
+        roll()
+        side.synchronize()
+        rolled = {k: v.clone() for k, v in out.items()}
+        eager = [ro.mlp_forward(pr.PR_NET_ACTOR, x) for x in X]
+        Y, graphs = [new() for _ in X], [torch.cuda.CUDAGraph() for _ in range(3)]
+        side.synchronize()
+        for i in range(2):
+            with torch.cuda.graph(graphs[i], stream=side):
+                ro.mlp_forward(pr.PR_NET_ACTOR, X[i], Y[i])
+        with torch.cuda.graph(graphs[2], stream=side):
+            roll()
+        side.synchronize()
+        # alone: only Y changes, and the numbers are the network's
+        for i in range(2):
+            before = ro.workspace.clone()
+            graphs[i].replay()
+            side.synchronize()
+            assert torch.equal(ro.workspace, before)
+            parity.check_networks(w, d["actor"], d["critic"], parity.to_np(X[i])[-70:], parity.to_np(Y[i])[-70:])
+        captured = [y.clone() for y in Y[:2]]
+        for rep in range(8):
+            for t in (*Y, *out.values()):
+                t.fill_(1)
+            torch.cuda.synchronize()
+            for s, gr in zip(others, graphs):
+                with torch.cuda.stream(s):
+                    gr.replay()
+            for _ in range(4):
+                for i in (2, 3):
+                    ro.mlp_forward(pr.PR_NET_ACTOR, X[i], Y[i])
+            torch.cuda.synchronize()
+            for i in range(4):
+                assert torch.equal(Y[i], captured[i] if i < 2 else eager[i]), (rep, i)
+            for k in out:
+                assert torch.equal(out[k], rolled[k]), (rep, k)
+        # two threads, one stream
+        outs = [[new() for _ in range(50)] for _ in range(2)]
+
+        def ask(i):
+            for y in outs[i]:
+                ro.mlp_forward(pr.PR_NET_ACTOR, X[i], y)
+
+        threads = [threading.Thread(target=ask, args=(i,)) for i in range(2)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        side.synchronize()
+        assert all(torch.equal(y, eager[i]) for i in range(2) for y in outs[i])
