@@ -88,7 +88,7 @@ hipError_t launch_trading_metrics(hipStream_t st, int32_t T, int32_t N, int32_t 
                                   double *metrics, int32_t *length);
 hipError_t launch_population_refill(hipStream_t st, int32_t P, int64_t count, const int32_t *rank, int32_t keep,
                                     float sigma, const float *noise, float *params);
-size_t ppo_scratch_bytes(int B, int Hd, int D, int S);
+size_t ppo_scratch_bytes(int B, int Hd, int D, int S, bool adam);
 // Gradients into ga / gc (whose tensors also hold intermediate sums), and with `adam` the update of both networks.
 struct PpoAdam {
   const pr_net_params *m[2], *v[2];  // actor, critic

@@ -921,18 +921,32 @@ size_t plan_bytes(int B, int Hd, int D, int S, const Plan &p) {
   return t + align256((size_t)(p.splits - 1) * n * f);
 }
 
+// What the no-allocation call states that it needs: the minibatch with gathered rows, six activation-sized buffers and
+// eight partial W2 gradients.
+bool static_stated(int B, int Hd, int D, int S) {
+  const size_t f = 4, Sp = (size_t)(S + 3) / 4 * 4;
+  return align256((size_t)B * Sp * f) + 6 * align256((size_t)B * Hd * f) + 2 * align256((size_t)B * D * f) +
+             2 * align256((size_t)B * f) + align256((size_t)((B + 7) / 8) * 4 * f) + align256((size_t)8 * Hd * Hd * f) <=
+         kStaticScratchBytes;
+}
+
 // The weight gradients' k (the batch) is split until a workgroup walks about 512 samples, or until there are 256
-// workgroups.  Shapes that fit the fixed scratch of the no-allocation call one way or another stay inside it: fewer
-// splits first, then unpadded rows, then the two networks one after the other (six instead of eight activation-sized
-// buffers: what that call has always needed at most).
-Plan make_plan(int B, int Hd, int D, int S) {
-  const int64_t tiles = (int64_t)((Hd + 63) / 64) * (((S + 63) / 64) + (Hd + 63) / 64) * 2;
-  int64_t want = (B + 511) / 512;
+// workgroups, but in the second case not beyond 32 of a launch per XCD, which would take a second round (64 units, 301
+// inputs: 22 splits 59.6 us a step at batch 4096 and 100.9 at 9800, 20 splits 55.4 and 92.9).
+// Gradients for which there is the no-allocation call give that call's bits, so they have a plan that fits its scratch:
+// fewer splits first, then unpadded rows, then the two networks one after the other (six instead of eight activation-sized
+// buffers).  That costs up to four times the time (128 units, 7800 samples: 540 us for 116), so no other call is held to it.
+Plan make_plan(int B, int Hd, int D, int S, bool adam) {
+  const int nh = (Hd + 63) / 64, ns = (S + 63) / 64, no = (D + 63) / 64;
+  const int64_t tiles = (int64_t)nh * (ns + nh) * 2, base = (B + 511) / 512;
+  int64_t want = base;
   if (tiles * want < 256) want = std::min<int64_t>((B + 127) / 128, (256 + tiles - 1) / tiles);
+  auto per_xcd = [&](int64_t w) { return 2 * ((nh * ns * w + 7) / 8) + (nh * no * w + 7) / 8 + (nh * w + 7) / 8; };
+  while (want > base && per_xcd(want) > 32) --want;
   want = std::max<int64_t>(1, std::min<int64_t>(want, 32));
   Plan best{true, wants_padding(Hd), (int)want, 0};
   best.bytes = plan_bytes(B, Hd, D, S, best);
-  if (best.bytes <= kStaticScratchBytes) return best;
+  if (adam || !static_stated(B, Hd, D, S) || best.bytes <= kStaticScratchBytes) return best;
   for (int i = 0; i < 3; ++i) {
     Plan q{i < 2, i == 0 && best.padded, 1, 0};
     if (plan_bytes(B, Hd, D, S, q) > kStaticScratchBytes) continue;
@@ -975,14 +989,14 @@ hipError_t launch_products(hipStream_t st, ProbSet &set) {
 
 }  // namespace
 
-size_t ppo_scratch_bytes(int B, int Hd, int D, int S) { return make_plan(B, Hd, D, S).bytes; }
+size_t ppo_scratch_bytes(int B, int Hd, int D, int S, bool adam) { return make_plan(B, Hd, D, S, adam).bytes; }
 
 hipError_t launch_ppo(hipStream_t st, const pr_ppo_config &c, const float *obs, const float *act, const float *logp_old,
                       const float *adv, const float *ret, const int32_t *rows, const pr_net_params &actor,
                       const pr_net_params &critic, const pr_net_params &ga, const pr_net_params &gc,
                       const PpoAdam *adam, void *scratch, float *stats) {
   const int B = c.batch, D = c.n_stocks, Hd = c.hidden, S = 1 + 2 * D + D * c.n_ind;
-  const Plan plan = make_plan(B, Hd, D, S);
+  const Plan plan = make_plan(B, Hd, D, S, adam != nullptr);
   unsigned char *sp = static_cast<unsigned char *>(scratch);
   auto take = [&](size_t floats) {
     float *r = reinterpret_cast<float *>(sp);
@@ -1112,14 +1126,10 @@ std::atomic<void *> g_scratch_ptr[kMaxDevices];
 
 size_t ppo_static_scratch_bytes() { return kStaticScratchBytes; }
 
-// The shapes of the no-allocation call: those whose minibatch with gathered rows, six activation-sized buffers and eight
-// partial W2 gradients takes no more than the array.  make_plan needs less for some that are larger; where a caller is
-// told to bring a workspace does not move with the plan.
+// make_plan needs less than stated for some shapes that are larger; where a caller is told to bring a workspace does not
+// move with the plan.
 bool ppo_static_covers(int B, int Hd, int D, int S) {
-  const size_t f = 4, Sp = (size_t)(S + 3) / 4 * 4;
-  const size_t bytes = align256((size_t)B * Sp * f) + 6 * align256((size_t)B * Hd * f) + 2 * align256((size_t)B * D * f) +
-                       2 * align256((size_t)B * f) + align256((size_t)((B + 7) / 8) * 4 * f) + align256((size_t)8 * Hd * Hd * f);
-  return bytes <= kStaticScratchBytes && ppo_scratch_bytes(B, Hd, D, S) <= kStaticScratchBytes;
+  return static_stated(B, Hd, D, S) && ppo_scratch_bytes(B, Hd, D, S, false) <= kStaticScratchBytes;
 }
 
 hipError_t launch_ppo_grads_static(hipStream_t st, const pr_ppo_config &c, const float *obs, const float *act,

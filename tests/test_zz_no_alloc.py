@@ -81,3 +81,40 @@ def test_noalloc_serves_no_shape_beyond_its_stated_scratch(B, D, K, Hd):
     p = pr.PrNetParams(*([256] * 6))
     rc = pr.lib().ppo_minibatch_grads_noalloc(None, C.byref(cfg), *([256] * 6), *([C.byref(p)] * 4), None)
     assert rc == pr.PR_ETOOBIG
+
+
+# batches the stated scratch covers only with fewer k splits, with rows close together, or with one network after the other:
+# the call with a workspace gives the same bits; the optimiser step, which keeps to no such limit, the same to rounding
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,D,K,Hd", [(2400, 30, 8, 256), (2800, 30, 8, 256), (3100, 15, 8, 256), (4400, 30, 8, 128), (10500, 15, 8, 64)])
+def test_noalloc_near_the_end_of_its_scratch(B, D, K, Hd):
+    w = inputs.WORKLOADS["dow30"].replace(n_stocks=D, n_ind=K, hidden=Hd)
+    cfg = pr.make_ppo_config(w, batch=B, adam_step=3)
+    nets, batch = _case(w, B, B + 50, seed=B)
+    want_a, want_c, want_stats = pr.ppo_minibatch_grads(cfg, *batch, nets["actor"], nets["critic"])
+    ga, gc = _empty_grads(cfg, float("nan"))
+    stats = torch.full((4,), float("nan"), device=DEV)
+    pr.ppo_minibatch_grads_noalloc(cfg, *batch, nets["actor"], nets["critic"], ga, gc, stats)
+    zeros = lambda net: {k: torch.zeros_like(v) for k, v in net.items()}
+    like = lambda net: {k: v.clone() for k, v in net.items()}
+    a, c, m = like(nets["actor"]), like(nets["critic"]), [zeros(nets[n]) for n in ("actor", "actor", "critic", "critic")]
+    pr.ppo_learner_step(cfg, *batch, a, c, *m, pr.ppo_workspace(cfg, DEV))
+    torch.cuda.synchronize()
+    assert torch.equal(stats, want_stats)
+    for got, want, m1 in ((ga, want_a, m[0]), (gc, want_c, m[2])):
+        for k in pr.NET_KEYS:
+            assert torch.equal(got[k], want[k]), k
+            # the first moment after one step is (1 - beta1) times the gradient
+            g = m1[k].double() / (1.0 - cfg.beta1)
+            assert float((g - want[k]).norm()) <= 1e-5 * float(want[k].double().norm()), k
+
+
+# no shape beyond that scratch is held to it: two networks' activations side by side
+@pytest.mark.parametrize("B,D,K,Hd", [(1540, 30, 8, 512), (2000, 30, 8, 512), (4000, 30, 8, 256), (7800, 30, 8, 128), (15000, 30, 8, 64)])
+def test_workspace_of_larger_batches_holds_both_networks(B, D, K, Hd):
+    n, last = C.c_size_t(0), 0
+    for b in (B - 64, B, B + 64):
+        cfg = pr.make_ppo_config(inputs.WORKLOADS["large"].replace(n_stocks=D, n_ind=K, hidden=Hd), batch=b)
+        assert pr.lib().ppo_workspace_bytes(C.byref(cfg), C.byref(n)) == pr.PR_OK
+        assert n.value >= max(last, 8 * 4 * b * Hd)
+        last = n.value
