@@ -544,12 +544,13 @@ __global__ __launch_bounds__(512, 4) void forward_kernel(FwdArgs a) {
       float *dst = buf + kl * PA + tid % TM;
       dst[0] = v[0], dst[PA] = v[1], dst[2 * PA] = v[2], dst[3 * PA] = v[3];
     }
-    // (rows past the end are zeros like those behind A: zero times an infinite weight would be NaN)
+    float *wdst = buf + KS * PA + wk * PB + 4 * (tid & 15);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      f32x4 v = rb[SL][i];
-      if (k0 + KS > K && k0 + wk + 32 * i >= K) v = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-      *reinterpret_cast<f32x4 *>(buf + KS * PA + (wk + 32 * i) * PB + 4 * (tid & 15)) = v;
+    for (int i = 0; i < 2; ++i) *reinterpret_cast<f32x4 *>(wdst + 32 * i * PB) = rb[SL][i];
+    if (k0 + KS > K) {  // (rows past the end are zeros like those behind A: zero times an infinite weight would be NaN)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (k0 + wk + 32 * i >= K) *reinterpret_cast<f32x4 *>(wdst + 32 * i * PB) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     }
   };
   using I0 = std::integral_constant<int, 0>;
