@@ -68,7 +68,9 @@ typedef struct pr_config {
                            fp32 accumulate, fp32 bias / tanh / outputs */
   int32_t schedule;     /* PR_SCHED_STEPWISE: actor and env launches for every
                            step (networks of 64 or 128 hidden units on at most
-                           320 inputs and 32 stocks: one launch for all steps);
+                           320 inputs and 32 stocks: one launch for all steps,
+                           but for more than 8192 envs with fp32 networks of 128
+                           units on more than 160 inputs);
                            PR_SCHED_FUSED: one persistent launch that
                            keeps each env tile on one compute unit for all T
                            steps (bf16 networks with 256 or 512 hidden units,

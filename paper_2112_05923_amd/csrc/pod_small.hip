@@ -12,9 +12,10 @@
 // trades' chain (pod_trade.h).  The loads of a step -- noise, the next market row
 // -- depend on the cursor only and travel behind the network.
 // Per step, before (a network launch or three and an env launch) -> now:
-//   fp32,  64 hidden units: 16 envs x 5 stocks 19.6 -> 3.6 us, 512 x 30 x 8 indicators 30 -> 5.1, 16384 x 30 x 8 52 -> 20
-//   fp32, 128: 64 x 10 x 2 27 -> 5.5, 512 x 30 x 8 37 -> 10.3 (120 of its registers spill), 4096 x 30 x 8 39 -> 14
-//   bf16, 128: 512 x 30 x 8 30 -> 4.2, 16384 x 30 x 8 34 -> 16
+//   fp32,  64 hidden units: 16 envs x 5 stocks 19.6 -> 3.6 us, 512 x 30 x 8 indicators 30 -> 5.1, 16384 x 30 x 8 55 -> 21
+//   fp32, 128: 64 x 10 x 2 27 -> 5.5, 512 x 30 x 8 37 -> 10.9 (121 of its registers spill; 26 with up to 160 inputs),
+//   4096 x 30 x 8 40 -> 15
+//   bf16, 128: 512 x 30 x 8 30 -> 4.2, 16384 x 30 x 8 38 -> 18
 #include "pod_internal.h"
 #include "pod_tile.h"
 #include "pod_trade.h"
@@ -346,8 +347,18 @@ hipError_t launch_dtype(hipStream_t st, const SmallArgs &a) {
 }  // namespace
 
 // 64 or 128 hidden units, up to 320 inputs and 32 stocks: what eight wavefronts hold in registers.
+// A round of workgroups, one per compute unit, is 4096 envs.  The launches per step that take over cost about 17 us and
+// then grow more slowly, so the line lies where they win over a rollout of 24 steps; us per step, this kernel and those:
+//   fp32, 128 units, 301 inputs (121 registers spill): 4096 envs 15.1 and 21.7, 8192 30.5 and 34.9, 12288 45.7 and 42.7,
+//   65536 241 and 152; 171 inputs: 8192 29.0 and 29.3, 12288 43.5 and 34.1
+//   fp32, 128 units, 151 inputs: 4096 6.6 and 19.1, 65536 104 and 116; 61 inputs: 65536 97 and 103
+//   fp32, 64 units, 301 inputs: 4096 5.4 and 18.0, 65536 83 and 136; bf16, 128 units, 301 inputs: 65536 71 and 86
+// The state and the policy are loaded once a call, so a call of a single step has less of it (us): fp32, 128 units, 301 inputs
+// 4096 envs 35 and 30, 8192 63 and 43; 151 inputs 4096 18 and 25, 16384 52 and 45, 65536 193 and 139; bf16 301 inputs
+// 4096 13 and 26, 65536 151 and 138.  The number of steps is not asked: a rollout gives the same bits however it is cut.
 bool small_supported(const pr_config &c) {
   const int S = 1 + 2 * c.n_stocks + c.n_stocks * c.n_ind;
+  if (c.mlp_dtype == PR_MLP_F32 && c.hidden == 128 && S > 160 && c.n_envs > 8192) return false;
   return c.schedule == PR_SCHED_STEPWISE && (c.hidden == 64 || c.hidden == 128) && c.n_stocks <= 32 && S <= 16 * kMaxBlocks;
 }
 

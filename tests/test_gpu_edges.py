@@ -391,3 +391,30 @@ def test_queries_side_by_side(base, N, rows, Hd, D, K):
             t.join()
         side.synchronize()
         assert all(torch.equal(y, eager[i]) for i in range(2) for y in outs[i])
+
+
+# either side of the number of envs up to which a small network's rollout is one launch: the same rollout however it is cut
+@pytest.mark.parametrize("N", [8192, 8193])
+def test_small_networks_of_many_envs(N):
+    T, H = 4, 3
+    w = inputs.WORKLOADS["tiny"].replace(n_envs=N, hidden=128, n_stocks=30, n_ind=8, steps=T, cash0=5e4)
+    d = inputs.make_all(w, horizon=H, n_market=1, steps=T)
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    ro = pr.Rollout(pr.make_config(w, horizon=H, n_market=1), _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+    recs = []
+    for cuts in ((T,), (1, T - 1)):
+        ro.reset()
+        t0, parts = 0, []
+        for n in cuts:
+            out = ro.alloc_buffers(n, value=False, logp=True, mu=True, shares=True)
+            ro.step_T(n, _t(d["noise"][t0:t0 + n]), out)
+            torch.cuda.synchronize()
+            parts.append({k: parity.to_np(v) for k, v in out.items()})
+            t0 += n
+        recs.append({k: np.concatenate([p[k][:len(p["reward"])] for p in parts] + ([parts[-1][k][-1:]] if k == "obs" else []))
+                     for k in parts[0]})
+    rec = recs[0]
+    assert all(np.array_equal(rec[k], recs[1][k]) for k in rec)
+    parity.check_env_record(w, oracle.cfg_from_workload(w, horizon=H), rec, d["price"], d["ind"], d["noise"], rec["mu"])
+    envs = np.r_[0:40, N - 40:N]
+    parity.check_networks(w, d["actor"], d["critic"], rec["obs"][T - 1][envs], rec["mu"][T - 1][envs])
