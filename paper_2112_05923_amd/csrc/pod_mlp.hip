@@ -633,7 +633,6 @@ struct ValueArgs {
 template <int NKB1, int SS>
 __global__ __launch_bounds__(512) void value_kernel(ValueArgs a) {
   using namespace tile;
-  using O = tile::Op<true>;
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   constexpr int NW = 8, NBT = 4, NT = NW * 64, CTH = 16 / NW, PD = 4, NKBH = VHALF / 16;
   extern __shared__ __align__(16) unsigned char lds[];

@@ -36,20 +36,6 @@ __device__ inline uint32_t bf16_pair(float a, float b) {
 __device__ inline float bf16_low(uint32_t p) { return __builtin_bit_cast(float, p << 16); }
 __device__ inline float bf16_high(uint32_t p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
 
-// tanh to about 1e-7 relative: below 0.6 an odd polynomial (least-squares fit of tanh(x)/x in x^2, driven to equal
-// ripple, 5e-9 before rounding), above it 1 - 2 / (e^{2|x|} + 1), where the subtraction costs less than half a unit.
-__device__ inline float tanh_f32(float x) {
-  const float ax = fabsf(x), z = x * x;
-  float q = fmaf(z, -0.005696077365428209f, 0.020631417632102966f);
-  q = fmaf(z, q, -0.05373746529221535f);
-  q = fmaf(z, q, 0.13331416249275208f);
-  q = fmaf(z, q, -0.3333328068256378f);
-  const float small = fmaf(z * x, q, x);
-  const float e = __builtin_amdgcn_exp2f(ax * 2.8853900817779268f);
-  const float big = copysignf(fmaf(-2.0f, __builtin_amdgcn_rcpf(e + 1.0f), 1.0f), x);
-  return ax < 0.6f ? small : big;
-}
-
 // two numbers -> three packed pairs.  SMALL: both below 2^127 (tanh outputs; a NaN stays one)
 template <bool SMALL = false>
 __device__ inline void split3_pair(float a, float b, uint32_t &p0, uint32_t &p1, uint32_t &p2) {

@@ -160,13 +160,8 @@ __device__ inline Net net_of(const PackedNet &p, int agent) {
   return n;
 }
 
-// Weight block (feature tile ct, k-block kb) for this lane.  Blocks are stored k-major ([kb][ct][lane]):
-// the blocks a workgroup needs for one k-block are one contiguous run, so the requests of a k-step spread
-// over all L2 channels instead of piling onto the few channels a power-of-two stride would select.
-__device__ inline u32x4 load_w(const u32x4 *W, int nct, int ct, int kb, int lane) {
-  return W[((size_t)kb * nct + ct) * 64 + lane];
-}
-
+// (Weight blocks are stored k-major, [kb][ct][lane]: those a workgroup needs for one k-block are one contiguous run, so the
+// requests of a k-step spread over all L2 channels instead of piling onto the few that a power-of-two stride selects.)
 // Fill the ring with k-blocks 0..PD-1 of a layer (feature tiles ct0..ct0+CT-1, clamped to the last tile).
 template <int CT, int PD, class B>
 __device__ inline void prime(B (&ring)[PD][CT], const u32x4 *W, int nkb, int nct, int ct0, int lane) {

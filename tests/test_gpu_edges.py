@@ -418,3 +418,32 @@ def test_small_networks_of_many_envs(N):
     parity.check_env_record(w, oracle.cfg_from_workload(w, horizon=H), rec, d["price"], d["ind"], d["noise"], rec["mu"])
     envs = np.r_[0:40, N - 40:N]
     parity.check_networks(w, d["actor"], d["critic"], rec["obs"][T - 1][envs], rec["mu"][T - 1][envs])
+
+
+# Summed over the batch, the gradient of the first bias shows what its terms have in common: a product that is rounded one
+# way only puts errors into it that grow with the batch, not with its root.  Terms of magnitude m (the sum of |dz2 W2|, times
+# tanh') whose errors are independent and at most 2^-24 m leave 2^-24 of the root of the sum of m^2, and so at most do the
+# additions and the critic's own outputs
+@pytest.mark.parametrize("B,D,K,Hd", [(16384, 5, 2, 64), (3001, 10, 4, 96), (20000, 8, 2, 256), (4096, 30, 8, 512)])
+def test_first_bias_gradient_of_large_batches(B, D, K, Hd):
+    w = inputs.WORKLOADS["dow30"].replace(n_stocks=D, n_ind=K, hidden=Hd)
+    rng = np.random.default_rng(B)
+    S = w.state_dim
+    nets = {n: {k: v[0] for k, v in inputs.make_weights(w, critic=(n == "critic")).items()} for n in ("actor", "critic")}
+    obs = rng.standard_normal((B, S)).astype(np.float32)
+    act, ret = rng.standard_normal((B, D)).astype(np.float32), rng.standard_normal(B).astype(np.float32)
+    zero = np.zeros(B, np.float32)
+    up = lambda net: {k: _t(v) for k, v in net.items()}
+    _, gc, _ = pr.ppo_minibatch_grads(pr.make_ppo_config(w, batch=B), _t(obs), _t(act), _t(zero), _t(zero), _t(ret), None,
+                                      up(nets["actor"]), up(nets["critic"]))
+    torch.cuda.synchronize()
+    c = {k: v.astype(np.float64) for k, v in nets["critic"].items()}
+    h1 = np.tanh(obs.astype(np.float64) @ c["W1"] + c["b1"])
+    h2 = np.tanh(h1 @ c["W2"] + c["b2"])
+    dz3 = 0.5 * (h2 @ c["W3"] + c["b3"] - ret[:, None]) / B
+    dz2 = dz3 @ c["W3"].T * (1.0 - h2 * h2)
+    want = (dz2 @ c["W2"].T * (1.0 - h1 * h1)).sum(0)
+    m = np.abs(dz2) @ np.abs(c["W2"]).T * (1.0 - h1 * h1)
+    bound = 3.0 * 2.0 ** -24 * np.linalg.norm(np.sqrt((m * m).sum(0)))
+    err = np.linalg.norm(parity.to_np(gc["b1"]) - want)
+    assert err <= bound, err / bound
