@@ -447,3 +447,43 @@ def test_first_bias_gradient_of_large_batches(B, D, K, Hd):
     bound = 3.0 * 2.0 ** -24 * np.linalg.norm(np.sqrt((m * m).sum(0)))
     err = np.linalg.norm(parity.to_np(gc["b1"]) - want)
     assert err <= bound, err / bound
+
+
+def _chain(x, w, b, act):
+    """One layer in binary32, one fused multiply-add after the other in ascending order; the activation to one rounding."""
+    acc = np.zeros((len(x), w.shape[1]), np.float32)
+    for k in range(w.shape[0]):
+        acc = (acc.astype(np.float64) + x[:, k:k + 1].astype(np.float64) * w[k].astype(np.float64)).astype(np.float32)
+    z = acc + b
+    return np.tanh(z.astype(np.float64)).astype(np.float32) if act else z
+
+
+# fp32 networks as sums of bf16 products are no less precise than the multiply-add chain of fp32 instructions: 2-norm of the
+# error against 64 bits, in every kernel of the forward pass (few rows, a launch per layer, whole network per tile, chunk by
+# chunk, value head) and inside both rollouts.  tanh is the kernels' own (3e-7 at most, 1e-7 in the mean)
+@pytest.mark.parametrize("N,rows,Hd,D,K,fused", [(48, 48, 512, 30, 8, False), (4096, 4096, 256, 30, 8, False), (5000, 5000, 512, 30, 8, False),
+                                                 (64, 64 * 260, 256, 30, 8, False), (128, 9000, 128, 17, 3, False), (48, 40, 32, 12, 2, False),
+                                                 (64, 64, 256, 30, 8, True), (96, 96, 256, 12, 4, True), (40, 40, 64, 5, 2, False), (33, 33, 128, 30, 8, False)])
+def test_fp32_networks_are_as_precise_as_fp32_sums(N, rows, Hd, D, K, fused):
+    w = inputs.WORKLOADS["dow30"].replace(n_envs=N, hidden=Hd, n_stocks=D, n_ind=K, steps=2)
+    d = inputs.make_all(w, horizon=2, n_market=1, steps=2)
+    cfg = pr.make_config(w, horizon=2, n_market=1, schedule=pr.PR_SCHED_FUSED if fused else pr.PR_SCHED_STEPWISE)
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    ro = pr.Rollout(cfg, _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+    X = np.random.default_rng(rows).standard_normal((rows, w.state_dim)).astype(np.float32)
+    pick = np.unique(np.linspace(0, rows - 1, 160).astype(int))
+    got = [(X[pick], net, parity.to_np(ro.mlp_forward(net, _t(X)))[pick]) for net in (pr.PR_NET_ACTOR, pr.PR_NET_CRITIC)]
+    out = ro.alloc_buffers(2, value=True, logp=False, mu=True, shares=False)
+    ro.step_T(2, _t(d["noise"]), out)
+    torch.cuda.synchronize()
+    obs, envs = parity.to_np(out["obs"])[1], np.unique(np.linspace(0, N - 1, 160).astype(int))
+    got += [(obs[envs], pr.PR_NET_ACTOR, parity.to_np(out["mu"])[1][envs]), (obs[envs], pr.PR_NET_CRITIC, parity.to_np(out["value"])[1][envs, None])]
+    for x, which, y in got:
+        net = {k: v[0] for k, v in d["actor" if which == pr.PR_NET_ACTOR else "critic"].items()}
+        n = {k: v.astype(np.float64) for k, v in net.items()}
+        last = which == pr.PR_NET_ACTOR
+        z = np.tanh(np.tanh(x.astype(np.float64) @ n["W1"] + n["b1"]) @ n["W2"] + n["b2"]) @ n["W3"] + n["b3"]
+        want = np.tanh(z) if last else z
+        f = _chain(_chain(_chain(x, net["W1"], net["b1"], True), net["W2"], net["b2"], True), net["W3"], net["b3"], last)
+        err, chain = (float(np.linalg.norm(v.astype(np.float64) - want) / np.linalg.norm(want)) for v in (y, f))
+        assert err <= chain + 1e-7, (which, err, chain)
