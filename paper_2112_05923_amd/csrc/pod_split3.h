@@ -9,6 +9,8 @@
 // rounding of an fp32 multiply-add (2^-24), and the products that are formed are
 // exact in the fp32 accumulator's input.  (Parts below the smallest normal number
 // may be lost: operands smaller than about 1e-33.)
+// The accumulator does not round to nearest: what does not fit is dropped towards minus infinity, 2^-28 of the terms'
+// magnitude in the mean.  One result does not notice; a sum over many results does (pod_learner.hip).
 //
 // An infinity leaves the last part infinite and the others at 2^127, and a NaN the
 // last part: the last part meets the first of the other operand only, so an infinite
