@@ -57,9 +57,10 @@ __global__ __launch_bounds__(kThreads) void observe_kernel(EnvDims d, EnvState s
 // One launch per step: 512 threads step E envs (the trades: pod_trade.h).  The cursor is read by every thread of an env (no
 // barrier in front of the prices), the market part of the next observation is requested together with the prices and
 // written while the orders are packed.
-// Measured per step: 2048 envs x 500 stocks x 4 indicators 106 -> 18 us, 5000 x 100 x 8 30 -> 14 us, 4096 x 30 x 8
-// 11.2 -> 6.3 us, 16 x 5 x 2 6.0 -> 4.5 us (before: order slots of up to 32 envs and a ledger over all of them in LDS,
-// holdings stored stock-major and hence moved in short runs).  The bytes of the first of these take 10 us.
+// Measured per step (kernel trace): 2048 envs x 500 stocks x 4 indicators 106 -> 22 us, 5000 x 100 x 8 30.2 -> 18.6,
+// 16384 x 100 x 8 60 -> 37, 4096 x 30 x 8 12.3 -> 7.1, 16384 x 30 x 8 17.0 -> 15.5, 16 x 5 x 2 6.0 -> 3.8 (before: order
+// slots of up to 32 envs and a ledger over all of them in LDS, holdings stored stock-major and hence moved in short
+// runs).  The bytes of the first of these take 10 us.
 template <int E, int ND>
 __global__ __launch_bounds__(kEnvThreads, 4) void env_step_kernel(EnvDims d, EnvState s, const float *__restrict__ price,
                                                                  const float *__restrict__ ind, StepIO io) {
