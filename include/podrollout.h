@@ -300,7 +300,8 @@ int adam_update(void *hip_stream, int64_t n, float *theta, const float *grad, fl
                 float beta2, float eps, int32_t t);
 
 /* ppo_minibatch_grads followed by adam_update on all twelve tensors (gradients live in the workspace).
- * m_*, v_*: Adam moments, same shapes as the parameters, zero before the first step. */
+ * m_*, v_*: Adam moments, same shapes as the parameters, zero before the first step.  (For batches that only just fit the
+ * scratch of the no-allocation call, whose plan the gradients keep to, the step adds the same products up in other parts.) */
 int ppo_learner_step(void *hip_stream, const pr_ppo_config *cfg, const float *obs, const float *act_raw,
                      const float *logp_old, const float *adv, const float *ret, const int32_t *rows,
                      const pr_net_params *actor, const pr_net_params *critic, const pr_net_params *m_actor,
