@@ -156,6 +156,11 @@ hipError_t launch_pack_layers(hipStream_t st, const PackJob *jobs, int n, int P,
 // rows of X [rows, ldx] -> Y [rows, out_dim[2]]; row r uses agent ((r % N) / envs_per_agent).
 hipError_t launch_mlp(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx, float *Y,
                       int32_t N, int32_t envs_per_agent);
+// The fp32 value head with 256 hidden units over many dense rows, on `cus` compute units: with several agents whole steps
+// of N rows, whose envs per agent are a multiple of 32.
+bool value_rows_covers(int64_t rows, int32_t N, int32_t envs_per_agent);
+hipError_t launch_value_rows(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, float *Y, int32_t N,
+                             int32_t envs_per_agent, int cus);
 bool mlp_supported(int S, int Hd, int O, int bf16);
 // The bf16 layer-per-launch path: x holds the rows (columns up to x.cols zero-padded) in the order layer 1 was packed for.
 bool layers_supported(int64_t rows, int hidden, int bf16);

@@ -1023,15 +1023,14 @@ __global__ __launch_bounds__(512) void value_kernel(ValueArgs a) {
 }
 
 // ------------------------------------------------ fp32 value head
-// The fp32 critic with 256 hidden units over a long buffer.  64 rows in three bf16 parts are 118 KB of LDS, so the hidden
-// tile overlays the input tile (the next input waits in registers meanwhile) and the output layer, one feature, is a
-// dot product in layer 2's epilogue: 16 partial sums per row (8 wavefronts x 2 lane halves) meet in LDS.
-// One feature tile per wavefront: per k-block three weight and six activation pieces feed twelve matrix instructions, 32 B
-// of weights per cycle and compute unit (the 32-row tiles of the kernel above need twice that, the L2's limit).
-// (8.5 million rows of 301 inputs, 64 agents: 19.4 ms in 32-row tiles.)
+// The fp32 critic with 256 hidden units, one 64-row tile per workgroup.  64 rows in three bf16 parts are 118 KB of LDS, so
+// the hidden tile overlays the input tile and the output layer, one feature, is a dot product in layer 2's epilogue: 16
+// partial sums per row (8 wavefronts x 2 lane halves) meet in LDS.  One feature tile per wavefront: per k-block three weight
+// and six activation pieces feed twelve matrix instructions, 32 B of weights per cycle and compute unit (the 32-row tiles of
+// the kernel above need twice that, the L2's limit).
 struct ValueF32Args {
   const float *X;
-  int64_t rows;      // multiple of 64
+  int64_t rows;
   float *Y;          // [rows]
   PackedNet net;
   int32_t N, envs_per_agent;
@@ -1053,122 +1052,79 @@ __global__ __launch_bounds__(512) void value_f32_kernel(ValueF32Args a) {
   float *ldsPart = ldsBias + 3 * 256 + 32;                   // [16][64]
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int S = a.S, G = a.groups, ngroups = BM * G;
-  const int64_t ntiles = a.rows / BM;
+  const int64_t row0 = (int64_t)xcd_index(blockIdx.x, gridDim.x) * BM;
+  const int last = (int)min((int64_t)BM, a.rows - row0) - 1;
+  const Net net = net_of(a.net, (int)(row0 % a.N / a.envs_per_agent));
 
+  // (rows behind the last one read that one again)
+  const float *src = a.X + row0 * S;
   f32x4 pre[NX];
-  auto fetch = [&](int64_t t) {
-    int tid_f = threadIdx.x;
-    asm volatile("" : "+v"(tid_f));
-    const float *src = a.X + t * BM * S;
 #pragma unroll
-    for (int i = 0; i < NX; ++i) {
-      const int idx = min(tid_f + NT * i, ngroups - 1);
-      const int row = (int)__umulhi((unsigned)idx, a.g_magic);
-      const int c4 = 4 * (idx - row * G);
-      const int shift = max(0, c4 + 4 - S);
-      pre[i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(src + (size_t)row * S + c4 - shift));  // 4-byte aligned
-    }
-  };
-  auto stash = [&]() {
-    int tid_f = threadIdx.x;
-    asm volatile("" : "+v"(tid_f));
-#pragma unroll
-    for (int i = 0; i < NX; ++i) {
-      const int idx = tid_f + NT * i, idc = min(idx, ngroups - 1);
-      const int row = (int)__umulhi((unsigned)idc, a.g_magic);
-      const int c4 = 4 * (idc - row * G);
-      const int shift = max(0, c4 + 4 - S);
-      const f32x4 v = pre[i];
-      const float o0 = shift == 0 ? v[0] : shift == 1 ? v[1] : shift == 2 ? v[2] : v[3];
-      const float o1 = shift == 0 ? v[1] : shift == 1 ? v[2] : shift == 2 ? v[3] : 0.0f;
-      const float o2 = shift == 0 ? v[2] : shift == 1 ? v[3] : 0.0f;
-      const float o3 = shift == 0 ? v[3] : 0.0f;
-      if (idx < ngroups) O::store4(ldsX + (size_t)row * a.xpitch + O::off(c4), o0, o1, o2, o3);
-    }
-    // k columns behind the last group
-    for (int i = tid_f; i < BM * (4 * a.net.nkb[0] - G); i += NT) {
-      const int row = i & (BM - 1), c4 = 4 * (G + (i >> 6));
-      O::store4(ldsX + (size_t)row * a.xpitch + O::off(c4), 0.0f, 0.0f, 0.0f, 0.0f);
-    }
-  };
-  auto stage = [&](const Net &net) {
-    for (int i = tid; i < 256; i += NT) {
-      ldsBias[i] = net.b[0][i];
-      ldsBias[256 + i] = net.b[1][i];
-      // output weight of hidden feature i: the parts of lane 32 g, element e of block kb
-      const __bf16 *wp = reinterpret_cast<const __bf16 *>(net.W[2] + (size_t)(i >> 4) * 192 + 32 * ((i >> 3) & 1)) + (i & 7);
-      ldsBias[512 + i] = (float)wp[0] + ((float)wp[512] + (float)wp[1024]);
-    }
-    if (tid == 0) ldsBias[768] = net.b[2][0];
-  };
-  auto agent_of = [&](int64_t t) { return (int)((t * BM % a.N) / a.envs_per_agent); };
-
-  int64_t t = xcd_index(blockIdx.x, gridDim.x), t_prev = -1;
-  if (t >= ntiles) return;
-  fetch(t);
-  int staged = agent_of(t);
-  Net net = net_of(a.net, staged);
-  stage(net);
-  stash();
+  for (int i = 0; i < NX; ++i) {
+    const int idx = min(tid + NT * i, ngroups - 1);
+    const int row = (int)__umulhi((unsigned)idx, a.g_magic);
+    const int c4 = 4 * (idx - row * G);
+    const int shift = max(0, c4 + 4 - S);
+    pre[i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(src + (size_t)min(row, last) * S + c4 - shift));  // 4-byte aligned
+  }
   typename O::Block ring[PD][1];
   prime<1, PD>(ring, net.W[0], net.nkb[0], 8, w, lane);
-  float b3 = 0.0f;
-  for (; t < ntiles; t += gridDim.x) {
-    const int64_t tn = t + gridDim.x;
-    const bool more = tn < ntiles;
-    __syncthreads();  // input tile complete, partial sums of the previous tile too
-    if (t_prev >= 0 && tid < BM) {
-      float y = b3;
-#pragma unroll
-      for (int p = 0; p < 16; ++p) y += ldsPart[p * BM + tid];
-      __builtin_nontemporal_store(y, &a.Y[t_prev * BM + tid]);
-    }
-    b3 = ldsBias[768];
-    f32x16 acc[1][2];
-    zero_acc<1, 2>(acc);
-    if (NKB1 > 0) mma_layer_static<false, 1, 2, PD, NKB1>(acc, ring, ldsX, a.xpitch, net.W[0], 8, w, 0, lane);
-    else mma_layer<false, 1, 2, PD>(acc, ring, ldsX, a.xpitch, net.nkb[0], net.W[0], 8, w, 0, lane);
-    prime<1, PD>(ring, net.W[1], NKB2, 8, w, lane);
-    if (more) fetch(tn);
-    __syncthreads();  // every wavefront has read the input tile
-    epilogue_hidden<false, 1, 2>(acc, ldsBias, ldsX, HP, 8, w, 0, lane);
-    __syncthreads();
-    zero_acc<1, 2>(acc);
-    mma_layer_static<false, 1, 2, PD, NKB2>(acc, ring, ldsX, HP, net.W[1], 8, w, 0, lane);
-    // layer 2's epilogue: y += tanh(z + b2) w3 over the lane's 16 features
-    const int g = lane >> 5;
-    float part[2] = {0.0f, 0.0f};
-    auto output = [&]() {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int f0 = w * 32 + 8 * j + 4 * g;
-        const f32x4 bv = *reinterpret_cast<const f32x4 *>(ldsBias + 256 + f0), wv = *reinterpret_cast<const f32x4 *>(ldsBias + 512 + f0);
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) part[b] = fmaf(tanh_accurate(acc[0][b][4 * j + i] + bv[i]), wv[i], part[b]);
-      }
-    };
-    output();
-    const int agent_n = more ? agent_of(tn) : staged;
-    if (agent_n != staged) net = net_of(a.net, agent_n);
-    prime<1, PD>(ring, net.W[0], net.nkb[0], 8, w, lane);
-    __syncthreads();  // every wavefront has read the hidden tile, its biases and the output weights
-    if (agent_n != staged) {
-      stage(net);
-      staged = agent_n;
-    }
-    if (more) stash();
-#pragma unroll
-    for (int b = 0; b < 2; ++b) ldsPart[(2 * w + g) * BM + b * 32 + (lane & 31)] = part[b];
-    t_prev = t;
+  for (int i = tid; i < 256; i += NT) {
+    ldsBias[i] = net.b[0][i];
+    ldsBias[256 + i] = net.b[1][i];
+    // output weight of hidden feature i: the parts of lane 32 g, element e of block kb
+    const __bf16 *wp = reinterpret_cast<const __bf16 *>(net.W[2] + (size_t)(i >> 4) * 192 + 32 * ((i >> 3) & 1)) + (i & 7);
+    ldsBias[512 + i] = (float)wp[0] + ((float)wp[512] + (float)wp[1024]);
   }
+  if (tid == 0) ldsBias[768] = net.b[2][0];
+#pragma unroll
+  for (int i = 0; i < NX; ++i) {
+    const int idx = tid + NT * i, idc = min(idx, ngroups - 1);
+    const int row = (int)__umulhi((unsigned)idc, a.g_magic);
+    const int c4 = 4 * (idc - row * G);
+    const int shift = max(0, c4 + 4 - S);
+    const f32x4 v = pre[i];
+    const float o0 = shift == 0 ? v[0] : shift == 1 ? v[1] : shift == 2 ? v[2] : v[3];
+    const float o1 = shift == 0 ? v[1] : shift == 1 ? v[2] : shift == 2 ? v[3] : 0.0f;
+    const float o2 = shift == 0 ? v[2] : shift == 1 ? v[3] : 0.0f;
+    const float o3 = shift == 0 ? v[3] : 0.0f;
+    if (idx < ngroups) O::store4(ldsX + (size_t)row * a.xpitch + O::off(c4), o0, o1, o2, o3);
+  }
+  // k columns behind the last group
+  for (int i = tid; i < BM * (4 * a.net.nkb[0] - G); i += NT)
+    O::store4(ldsX + (size_t)(i & (BM - 1)) * a.xpitch + O::off(4 * (G + (i >> 6))), 0.0f, 0.0f, 0.0f, 0.0f);
   __syncthreads();
-  if (tid < BM) {
-    float y = b3;
+
+  f32x16 acc[1][2];
+  zero_acc<1, 2>(acc);
+  if (NKB1 > 0) mma_layer_static<false, 1, 2, PD, NKB1>(acc, ring, ldsX, a.xpitch, net.W[0], 8, w, 0, lane);
+  else mma_layer<false, 1, 2, PD>(acc, ring, ldsX, a.xpitch, net.nkb[0], net.W[0], 8, w, 0, lane);
+  prime<1, PD>(ring, net.W[1], NKB2, 8, w, lane);
+  __syncthreads();  // every wavefront has read the input tile
+  epilogue_hidden<false, 1, 2>(acc, ldsBias, ldsX, HP, 8, w, 0, lane);
+  __syncthreads();
+  zero_acc<1, 2>(acc);
+  mma_layer_static<false, 1, 2, PD, NKB2>(acc, ring, ldsX, HP, net.W[1], 8, w, 0, lane);
+  // layer 2's epilogue: y += tanh(z + b2) w3 over the lane's 16 features
+  const int g = lane >> 5;
+  float part[2] = {0.0f, 0.0f};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int f0 = w * 32 + 8 * j + 4 * g;
+    const f32x4 bv = *reinterpret_cast<const f32x4 *>(ldsBias + 256 + f0), wv = *reinterpret_cast<const f32x4 *>(ldsBias + 512 + f0);
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) part[b] = fmaf(tanh_accurate(acc[0][b][4 * j + i] + bv[i]), wv[i], part[b]);
+  }
+#pragma unroll
+  for (int b = 0; b < 2; ++b) ldsPart[(2 * w + g) * BM + b * 32 + (lane & 31)] = part[b];
+  __syncthreads();
+  if (tid <= last) {
+    float y = ldsBias[768];
 #pragma unroll
     for (int p = 0; p < 16; ++p) y += ldsPart[p * BM + tid];
-    __builtin_nontemporal_store(y, &a.Y[t_prev * BM + tid]);
+    a.Y[row0 + tid] = y;
   }
 }
 
@@ -1411,15 +1367,25 @@ static bool try_launch_value(hipStream_t st, const PackedNet &net, int64_t rows,
   return true;
 }
 
-// The fp32 value head covers 256 hidden units and dense rows of 5 to 320 columns, with a tile for every compute unit.
-// `rows` must be a multiple of 64 and X must start at a multiple of N rows of the caller's buffer.
+// The fp32 value head with 256 hidden units over dense rows: workgroups of 128 rows, a wavefront per 32 (pod_value.hip),
+// from the second 64-row tile per compute unit on, where the workgroups that share a tile take two passes (301 inputs: 20480
+// rows 49 us against 58, 65536 95 against 109, 98304 137 against 160; 16384 rows, one pass, 48 against 31).
 static bool try_launch_value_f32(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx,
                                  float *Y, int32_t N, int32_t envs_per_agent, hipError_t *err) {
   const int S = net.in_dim[0], Hd = net.out_dim[0];
-  if (net.bf16 || net.out_dim[2] != 1 || Hd != 256 || net.out_dim[1] != Hd || net.out_tanh || ldx != S || S < 5) return false;
+  if (net.bf16 || net.out_dim[2] != 1 || Hd != 256 || net.out_dim[1] != Hd || net.out_tanh || ldx != S) return false;
   if ((reinterpret_cast<uintptr_t>(X) & 3u) || (envs_per_agent < N && envs_per_agent % tile::BM != 0)) return false;
-  const int64_t ntiles = rows / tile::BM;
-  if (tile::BM * ((S + 3) / 4) > 512 * XPRE_MAX || ntiles < compute_units()) return false;
+  const int64_t ntiles = (rows + tile::BM - 1) / tile::BM;
+  // (of several agents the whole steps; what is left begins at the first env again)
+  const int64_t whole = envs_per_agent < N ? rows / N * N : rows;
+  if (whole > (int64_t)tile::BM * compute_units() && value_rows_covers(whole, N, envs_per_agent)) {
+    *err = launch_value_rows(st, net, whole, X, Y, N, envs_per_agent, compute_units());
+    if (*err == hipSuccess && whole < rows)
+      *err = launch_mlp(st, net, rows - whole, X + whole * S, ldx, Y + whole, N, envs_per_agent);
+    return true;
+  }
+  // (half a tile per compute unit: 32-row tiles of the whole-network kernel take as long, 24 us for 8192 rows)
+  if (S < 5 || tile::BM * ((S + 3) / 4) > 512 * XPRE_MAX || 2 * ntiles <= compute_units()) return false;
   ValueF32Args a;
   a.X = X, a.rows = rows, a.Y = Y, a.net = net, a.N = N, a.envs_per_agent = envs_per_agent, a.S = S;
   a.groups = (S + 3) / 4;
@@ -1427,16 +1393,15 @@ static bool try_launch_value_f32(hipStream_t st, const PackedNet &net, int64_t r
   a.xpitch = tile::tile_pitch<false>(net.nkb[0]);
   const int hp = tile::tile_pitch<false>(net.nkb[1]);
   const size_t lds = (size_t)tile::BM * (a.xpitch > hp ? a.xpitch : hp) + (3 * 256 + 32 + 16 * tile::BM) * 4;
-  if (lds > (size_t)kMaxLdsBytes) return false;
+  if (lds > (size_t)kMaxLdsBytes || ntiles > 0x7fffffff) return false;
   auto launch = [&](auto nkb1) {
     constexpr auto kern = value_f32_kernel<decltype(nkb1)::value>;
     *err = allow_full_lds<kern>();
     if (*err != hipSuccess) return;
-    hipLaunchKernelGGL(kern, dim3((unsigned)compute_units()), dim3(512), lds, st, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(512), lds, st, a);
     *err = hipGetLastError();
   };
-  // the observation width of the named workloads in straight-line code: 4.26 million rows of 301 inputs 7.44 -> 7.21 ms,
-  // 266240 rows 446 -> 432 us
+  // the observation width of the named workloads in straight-line code
   if (net.nkb[0] == 19) launch(std::integral_constant<int, 19>{});
   else launch(std::integral_constant<int, 0>{});
   return true;
@@ -1552,16 +1517,9 @@ hipError_t launch_mlp(hipStream_t st, const PackedNet &net, int64_t rows, const 
       rows -= full;
     }
   }
-  if (rows >= BM && row_offset == 0) {
+  if (row_offset == 0) {
     hipError_t terr = hipSuccess;
-    const int64_t full = rows / BM * BM;
-    if (try_launch_value_f32(st, net, full, X, ldx, Y, N, envs_per_agent, &terr)) {
-      if (terr != hipSuccess || full == rows) return terr;
-      X += full * ldx;
-      Y += full;
-      row_offset = full;
-      rows -= full;
-    }
+    if (try_launch_value_f32(st, net, rows, X, ldx, Y, N, envs_per_agent, &terr)) return terr;
   }
   if (rows >= BM) {
     // full tiles through the persistent whole-tile kernel when it covers the shape; the ragged tail below

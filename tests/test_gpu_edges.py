@@ -487,3 +487,34 @@ def test_fp32_networks_are_as_precise_as_fp32_sums(N, rows, Hd, D, K, fused):
         f = _chain(_chain(_chain(x, net["W1"], net["b1"], True), net["W2"], net["b2"], True), net["W3"], net["b3"], last)
         err, chain = (float(np.linalg.norm(v.astype(np.float64) - want) / np.linalg.norm(want)) for v in (y, f))
         assert err <= chain + 1e-7, (which, err, chain)
+
+
+# the fp32 value head: tiles of 64 rows up to one per compute unit (9000 rows; 16384 = all of them), workgroups of 128 rows
+# beyond; ragged last tiles, runs of 32 rows behind the end, one k-block and an odd and an even number of them, inputs that
+# end inside a lane's eight, agents of fewer envs than a tile, rows left over behind the agents' last whole step; an infinite
+# and a missing input stay in their row
+@pytest.mark.parametrize("N,rows,agents,D,K", [(64, 9000, 1, 30, 8), (64, 16384, 1, 12, 4), (64, 16385, 1, 30, 8), (64, 70000, 1, 7, 3),
+                                               (64, 16500, 1, 1, 2), (64, 17000, 1, 2, 1), (192, 17000, 3, 30, 8), (640, 33000, 10, 5, 5),
+                                               (512, 66048, 2, 30, 7)])
+def test_fp32_value_head_tiles(N, rows, agents, D, K):
+    w = inputs.WORKLOADS["dow30"].replace(n_envs=N, n_agents=agents, n_stocks=D, n_ind=K, steps=2)
+    d = inputs.make_all(w, horizon=2, n_market=1, steps=2)
+    cfg = pr.make_config(w, horizon=2, n_market=1, schedule=pr.PR_SCHED_STEPWISE)
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    ro = pr.Rollout(cfg, _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+    X = np.random.default_rng(rows).standard_normal((rows, w.state_dim)).astype(np.float32)
+    bad = [5, rows - 3]
+    X[5, w.state_dim - 1], X[rows - 3, 0] = np.inf, np.nan
+    val = parity.to_np(ro.mlp_forward(pr.PR_NET_CRITIC, _t(X)))
+    assert np.isnan(val[rows - 3, 0]) and np.isfinite(np.delete(val[:, 0], bad)).all()
+    last = {k: v[(5 % N) // (N // agents)].astype(np.float64) for k, v in d["critic"].items()}
+    # the infinite input takes every unit to its end
+    want5 = np.tanh(np.sign(last["W1"][-1]) @ last["W2"] + last["b2"]) @ last["W3"] + last["b3"]
+    assert abs(val[5, 0] - want5[0]) <= 1e-5 * max(1.0, abs(want5[0]))
+    pick = np.unique(np.concatenate([np.arange(0, rows, max(1, rows // 150)), np.arange(120, 136), np.arange(16380, 16390),
+                                     np.arange(rows - 70, rows)]))
+    pick = np.setdiff1d(pick[pick < rows], bad)
+    for a in range(agents):
+        sel = pick[(pick % N) // (N // agents) == a]
+        assert len(sel)
+        parity.check_networks(w, d["actor"], d["critic"], X[sel], None, val[sel], agent=a)
