@@ -17,7 +17,8 @@ struct pr_handle {
   EnvState st;
   pr_market market;
   PackedNet actor, critic;
-  PackedNet actor_rot;    // the actor with layer 1 packed for inputs in the order [indicators | cash | prices | holdings]
+  PackedNet actor_rot;    // the actor with layer 1 packed for inputs in the order [indicators | cash | prices | holdings],
+                          // or [indicators | prices | holdings | cash] (market_first)
   void *w1_rot;           // (null when no rollout of this handle reads that order)
   void *w_packed[2][3];   // device, per net and layer
   float *b_packed[2][3];
@@ -71,6 +72,14 @@ bool uses_shadow(const pr_config &c) {
 // rollouts of this config read layer 1 in the order [indicators | cash | prices | holdings]
 bool uses_rotated(const pr_config &c) { return c.schedule == PR_SCHED_FUSED || small_supported(c) || uses_shadow(c); }
 
+// k-blocks of that copy of layer 1.  The persistent fp32 rollout of few envs reads blocks of 32 inputs, with the cash last,
+// so that all market columns come first.
+bool market_first(const pr_config &c) { return c.schedule == PR_SCHED_FUSED && fused_few_envs(c); }
+int rotated_blocks(const pr_config &c) {
+  const int nkb = (state_dim(c) + 15) / 16;
+  return market_first(c) ? (nkb + 1) & ~1 : nkb;
+}
+
 int validate_config(const pr_config *c) {
   if (!c) return PR_EINVAL;
   if (c->n_envs < 1 || c->n_agents < 1 || c->n_envs % c->n_agents != 0) return PR_EINVAL;
@@ -114,7 +123,7 @@ Layout make_layout(const pr_config &c) {
       L.b[net][l] = take((size_t)padded_out(out_dim[l]) * 4 * P);
     }
   }
-  L.w1_rot = uses_rotated(c) ? take(packed_weight_bytes(S, Hd, bf) * P) : 0;
+  L.w1_rot = uses_rotated(c) ? take(packed_weight_bytes(16 * rotated_blocks(c), Hd, bf) * P) : 0;
   L.cash = take(N * 4);
   L.tau = take(N * 4);
   L.h = take(N * D * 4);
@@ -187,12 +196,13 @@ int pack_nets(pr_handle *h, const pr_weights *actor, const pr_weights *critic) {
     const int in_dim[3] = {S, Hd, Hd};
     const int out_dim[3] = {Hd, Hd, net == 0 ? D : 1};
     for (int l = 0; l < 3; ++l)
-      jobs[n++] = {W[l], b[l], h->w_packed[net][l], h->b_packed[net][l], in_dim[l], out_dim[l], 0};
+      jobs[n++] = {W[l], b[l], h->w_packed[net][l], h->b_packed[net][l], in_dim[l], out_dim[l], (in_dim[l] + 15) / 16, 0, 0};
   }
   // The persistent rollout kernel keeps its observation tile as [indicators | cash | prices | holdings] (and so do
   // the one for small networks and the bf16 copy of the observations): the same layer-1 weights with their rows rotated
   // by the D K indicator columns (biases are shared).
-  if (h->w1_rot) jobs[n++] = {actor->W1, actor->b1, h->w1_rot, h->b_packed[0][0], S, Hd, D * c.n_ind};
+  if (h->w1_rot)
+    jobs[n++] = {actor->W1, actor->b1, h->w1_rot, h->b_packed[0][0], S, Hd, rotated_blocks(c), D * c.n_ind, market_first(c) ? 1 : 0};
   POD_HIP(launch_pack_layers(h->stream, jobs, n, P, bf));
   return PR_OK;
 }
@@ -306,6 +316,8 @@ int rollout_init(const pr_config *cfg, const pr_market *market, const pr_weights
   h->w1_rot = uses_rotated(*cfg) ? static_cast<void *>(ws + L.w1_rot) : nullptr;
   h->actor_rot = h->actor;
   h->actor_rot.W[0] = h->w1_rot;
+  h->actor_rot.nkb[0] = rotated_blocks(*cfg);
+  h->actor_rot.w_stride[0] = (int64_t)packed_weight_bytes(16 * rotated_blocks(*cfg), cfg->hidden, cfg->mlp_dtype);
   fill_net(h->critic, h, 1);
   if (uses_shadow(*cfg)) h->shadow = h->actor.split_x;
   int prc = pack_nets(h, actor, critic);

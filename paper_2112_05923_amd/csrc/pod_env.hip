@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kEnvThreads, 4) void env_step_kernel(EnvDims d, Env
   float cash = cash_in, e2;
   double r;
   trade.run(
-      d, live, a_raw, eps, pn, pv, h, q, cash, r, e2, io.logp != nullptr,
+      d, live, a_raw, eps, pn, Tr::unit_of(d, pn), pv, h, q, cash, r, e2, io.logp != nullptr,
       [&]() {
         // market part of the next observation
 #pragma unroll

@@ -854,7 +854,9 @@ bool fused_supported(const pr_config &c) {
   return fused_lds_bytes(c, true) <= kLdsMax;
 }
 
-size_t fused_lds_bytes(const pr_config &c, bool with_actor) { return (size_t)fused_layout(c, with_actor).total; }
+size_t fused_lds_bytes(const pr_config &c, bool with_actor) {
+  return with_actor && fused_few_envs(c) ? fused_f32_lds_bytes(c) : (size_t)fused_layout(c, with_actor).total;
+}
 
 template <bool BF16, int E, bool ACTOR, int CTH, int NKB1, int NKB2>
 static hipError_t launch_fused_inst(hipStream_t st, const FusedArgs &a, unsigned blocks, size_t lds) {
@@ -869,6 +871,9 @@ hipError_t launch_rollout_fused(hipStream_t st, const pr_config &c, const EnvDim
                                 const float *price, const float *ind, const PackedNet &actor, int32_t envs_per_agent,
                                 int32_t T, const float *noise, const float *mu_forced, const pr_buffers &out) {
   if (!fused_supported(c)) return hipErrorInvalidValue;
+  if (reinterpret_cast<uintptr_t>(ind) & 15u) return hipErrorInvalidValue;  // 16-byte indicator loads
+  if (!mu_forced && fused_few_envs(c))
+    return launch_rollout_fused_f32(st, c, d, s, price, ind, actor, envs_per_agent, T, noise, out);
   FusedArgs a;
   a.d = d;
   a.st = s;
@@ -888,7 +893,6 @@ hipError_t launch_rollout_fused(hipStream_t st, const pr_config &c, const EnvDim
   a.shares = out.shares;
   const bool with_actor = mu_forced == nullptr;
   a.L = fused_layout(c, with_actor);
-  if (reinterpret_cast<uintptr_t>(ind) & 15u) return hipErrorInvalidValue;  // 16-byte indicator loads
   const size_t lds = (size_t)a.L.total;
   if (lds > kLdsMax) return hipErrorInvalidValue;
   const FusedShape fs = fused_shape(c);

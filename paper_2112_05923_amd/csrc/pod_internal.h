@@ -143,13 +143,13 @@ int64_t split_scratch_rows(int64_t n_envs, int hidden);
 
 size_t packed_weight_bytes(int in_dim, int out_dim, int bf16);
 int padded_out(int out_dim);
-// One layer to pack.  k_rot > 0: packed k row k' holds input row (k' < k_rot ? in_dim - k_rot + k' : k' - k_rot), i.e. the
-// last k_rot inputs come first.
+// One layer to pack, in nkb k-blocks (zeros behind the last input).  The last k_rot inputs come first, and of the others
+// the first k_last come last.
 struct PackJob {
   const float *W, *b;  // [P, in_dim, out_dim], [P, out_dim]
   void *Wp;
   float *bp;
-  int32_t in_dim, out_dim, k_rot;
+  int32_t in_dim, out_dim, nkb, k_rot, k_last;
 };
 constexpr int kMaxPackJobs = 7;  // three layers of two networks, and the actor's first layer in the rollout's order
 hipError_t launch_pack_layers(hipStream_t st, const PackJob *jobs, int n, int P, int bf16);
@@ -185,6 +185,13 @@ size_t fused_lds_bytes(const pr_config &c, bool with_actor);
 hipError_t launch_rollout_fused(hipStream_t st, const pr_config &c, const EnvDims &d, const EnvState &s,
                                 const float *price, const float *ind, const PackedNet &actor, int32_t envs_per_agent,
                                 int32_t T, const float *noise, const float *mu_forced, const pr_buffers &out);
+
+// The same with the actor for the few envs of an fp32 network (16 per workgroup).
+bool fused_few_envs(const pr_config &c);
+size_t fused_f32_lds_bytes(const pr_config &c);
+hipError_t launch_rollout_fused_f32(hipStream_t st, const pr_config &c, const EnvDims &d, const EnvState &s,
+                                    const float *price, const float *ind, const PackedNet &actor, int32_t envs_per_agent,
+                                    int32_t T, const float *noise, const pr_buffers &out);
 
 // The stepwise schedule of small networks: all T steps in one launch, state and network on the compute units.
 bool small_supported(const pr_config &c);

@@ -1142,7 +1142,7 @@ __global__ __launch_bounds__(256) void pack_layers_kernel(PackArgs a) {
   int q = 0;
   while (q + 1 < kMaxPackJobs && blockIdx.x >= a.end[q]) ++q;
   const PackJob &jb = a.job[q];
-  const int nkb = (jb.in_dim + 15) / 16, nct = (jb.out_dim + 31) / 32;
+  const int nkb = jb.nkb, nct = (jb.out_dim + 31) / 32;
   const int lane = threadIdx.x & 63;
   const uint32_t unit = (blockIdx.x - (q ? a.end[q - 1] : 0u)) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t row = unit / (uint32_t)nct, ct = unit - row * nct;
@@ -1155,7 +1155,8 @@ __global__ __launch_bounds__(256) void pack_layers_kernel(PackArgs a) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int k = kb * 16 + 8 * g + e;
-    const int ks = k < jb.k_rot ? jb.in_dim - jb.k_rot + k : k - jb.k_rot;
+    const int rest = jb.in_dim - jb.k_rot, kr = k - jb.k_rot + jb.k_last;
+    const int ks = k < jb.k_rot ? rest + k : kr < rest ? kr : kr - rest;
     v[e] = (k < jb.in_dim && col < jb.out_dim) ? Wa[(size_t)ks * jb.out_dim + col] : 0.0f;
   }
   bf16x8 *dst = static_cast<bf16x8 *>(jb.Wp) + (size_t)unit * (a.bf16 ? 64 : 192) + lane;
@@ -1221,7 +1222,7 @@ hipError_t launch_pack_layers(hipStream_t st, const PackJob *jobs, int n, int P,
   for (int i = 0; i < kMaxPackJobs; ++i) {
     if (i < n) {
       a.job[i] = jobs[i];
-      blocks += ((uint64_t)P * ((jobs[i].in_dim + 15) / 16) * ((jobs[i].out_dim + 31) / 32) + 3) / 4;
+      blocks += ((uint64_t)P * jobs[i].nkb * ((jobs[i].out_dim + 31) / 32) + 3) / 4;
     }
     a.end[i] = (uint32_t)blocks;
   }

@@ -159,6 +159,8 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
     }
     if (own) put_price(pn[0]), put_holding(h[0]);
   }
+  trade.put_term(0, tl < D ? (double)h[0] * (double)pn[0] : 0.0);
+  double value = trade.value(cash);  // the account's, before the next trades
   __syncthreads();
 
   // partial sums of feature tile `tile`, lanes of the 16 rows only
@@ -219,6 +221,7 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
       const int g = tl + TPE * j;
       if (g < NG) iv[j] = *reinterpret_cast<const env_f32x4u *>(irow + 4 * g);
     }
+    const typename Tr::Unit units = Tr::unit_of(d, pn);
     // -- policy
     f32x16 acc;
     zero(acc);
@@ -267,7 +270,7 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
     float e2;
     double r;
     trade.run(
-        d, live, a_raw, eps, pn, pv, h, q, cash, r, e2, a.logp != nullptr,
+        d, live, a_raw, eps, pn, units, pv, h, q, cash, r, e2, a.logp != nullptr,
         [&]() {
           if (own) put_price(po);
           if (live) {
@@ -287,6 +290,9 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
           if (a.shares) a.shares[g0 + tl] = q[0];
         });
     // -- episode bookkeeping (binary64; the env's first thread holds the sums), reset if the episode ended
+    const double after = trade.value(cash);
+    r = (after - value) * (double)d.rho;
+    value = ri.done ? (double)d.cash0 : after;
     ep_ret += r;
     if (ri.done) {
       ep_sum += ep_ret;

@@ -73,7 +73,7 @@ __device__ inline float serial_sum(float s, const env_f32x4 *v, int n) {
   return s;
 }
 
-// 512 threads trade for E envs: TPE = 512 / E neighbouring threads own one env, and a thread the stocks tl, tl + TPE, ...
+// NT threads (the workgroup's 512, or its last 256) trade for E envs: TPE = NT / E neighbouring threads own one env, and a thread the stocks tl, tl + TPE, ...
 // (at most ND) of its env, whose prices, holdings and orders stay in its registers.  What bounds the step is the chain
 // prices -> orders -> the serial walk over the purchases -> holdings; everything else hangs off it:
 //  - the ledger adds the sales from a dense row, and walks only the purchases: the threads pack them into a list in
@@ -81,17 +81,19 @@ __device__ inline float serial_sum(float s, const env_f32x4 *v, int n) {
 //    (half) and needs one dependent operation per purchase while the cash lasts, none for a purchase it does not
 //    buy a single share of, and the quotient only in between (13.5 -> 1.8 us of a step with 250 purchases);
 //  - the account values before and after are sums over the env's threads, taken again in stock order by one of them where
-//    the order shows in the last bit (prices far apart in size).  With WALK they are always taken in stock order: where
-//    one workgroup has the compute unit to itself the sums over lanes take longer (rollout_small_kernel, 5 stocks 3.97 ->
-//    3.60 us a step, 30 stocks 5.16 -> 4.98); where others want the same issue slots it is the other way round
-//    (env_step_kernel, 16384 envs x 30 stocks 15.5 us against 16.3, 4096 x 64 8.0 against 9.1);
+//    the order shows in the last bit (prices far apart in size).  With WALK they are always taken in stock order, by value()
+//    and not here: a kernel that goes on with the same envs knows the value before and needs the one after for the reward
+//    only.  Where one workgroup has the compute unit to itself the sums over lanes take longer (rollout_small_kernel, 5
+//    stocks 3.97 -> 3.60 us a step, 30 stocks 5.16 -> 4.98); where others want the same issue slots it is the other way
+//    round (env_step_kernel, 16384 envs x 30 stocks 15.5 us against 16.3, 4096 x 64 8.0 against 9.1);
 //  - up to a wavefront per env there is no barrier in here: an env's threads only meet each other.
-template <int E, int ND, bool WALK>
+template <int E, int ND, bool WALK, int NT = kEnvThreads>
 struct Trade {
-  static constexpr int TPE = kEnvThreads / E;
+  static constexpr int TPE = NT / E;
   static constexpr int CW = TPE < 64 ? TPE : 64;  // the part of a wavefront one env has
   static constexpr int NCW = TPE / CW;            // wavefronts per env
-  static_assert(!WALK || NCW == 1, "");
+  static constexpr int CHUNK = CW < 16 ? CW : 16; // purchases tried in full together
+  static_assert((!WALK || NCW == 1) && CW % CHUNK == 0 && CHUNK % 4 == 0 && (NT & (NT - 1)) == 0, "");
   int D, D4, lp, sp, op;
   Purchase *list;  // [E][lp] purchases in stock order (odd pitch in 16 bytes)
   float *sell;     // [E][sp] proceeds of the sales, 0 elsewhere
@@ -104,7 +106,7 @@ struct Trade {
   float *e2s;      // [E] sum of the squares
   int32_t *cnt;    // [E][ND NCW] purchases
   float *now;      // several wavefronts per env (whose registers are few): [E][D4] prices of the trades
-  double *terms;   // WALK: [E][D4] holdings' values in stock order
+  double *terms;   // WALK: [E][D4] holdings' values after the trades, in stock order
 
   __device__ Trade(unsigned char *lds, int D_) : D(D_), D4((D_ + 3) & ~3), lp(D_ | 1), sp(D4 + 4), op(D4 + 20) {
     list = reinterpret_cast<Purchase *>(lds);
@@ -132,15 +134,31 @@ struct Trade {
     }
   }
 
+  // What a purchase of the thread's stocks needs of their prices alone (a binary64 division: where the prices are known
+  // before the actions, this is too).
+  struct Unit {
+    float cost[ND];
+    double rcp[ND];  // 1 / cost
+  };
+  __device__ static Unit unit_of(const EnvDims &d, const float (&pn)[ND]) {
+    Unit u;
+#pragma unroll
+    for (int i = 0; i < ND; ++i) {
+      u.cost[i] = pn[i] * d.one_plus_c;
+      u.rcp[i] = 1.0 / (double)u.cost[i];
+    }
+    return u;
+  }
+
   // Sampled actions a_raw and their noise, prices pn the trades execute at and pv the account is valued at afterwards,
-  // holdings h (updated), executed shares q (signed), cash (updated); r and e2 (reward, and the summed squares if wanted)
-  // are complete in the env's first thread.  market(): between sizing and ledger; rest(): behind the ledger; booked(i): the
-  // thread's i-th stock is settled (live stocks only).
+  // holdings h (updated), executed shares q (signed), cash (updated); e2 (the summed squares if wanted) is complete in the
+  // env's first thread, and without WALK r (the reward).  market(): between sizing and ledger; rest(): behind the ledger;
+  // booked(i): the thread's i-th stock is settled (live stocks only).
   template <class Market, class Rest, class Booked>
   __device__ inline void run(const EnvDims &d, bool live, const float (&a_raw)[ND], const float (&eps)[ND], const float (&pn)[ND],
-                             const float (&pv)[ND], int32_t (&h)[ND], int32_t (&q)[ND], float &cash, double &r, float &e2,
-                             bool want_e2, Market market, Rest rest, Booked booked) {
-    const int tid = threadIdx.x, lane = tid & 63;
+                             const Unit &units, const float (&pv)[ND], int32_t (&h)[ND], int32_t (&q)[ND], float &cash, double &r,
+                             float &e2, bool want_e2, Market market, Rest rest, Booked booked) {
+    const int tid = threadIdx.x & (NT - 1), lane = tid & 63;
     const int e = tid / TPE, tl = tid & (TPE - 1), cw = tl / CW, cl = lane & (CW - 1);
     const float cash_in = cash;
     auto mine_of = [&](uint64_t all) {  // the env's part of a ballot
@@ -148,7 +166,7 @@ struct Trade {
     };
     // -- size the orders
     int32_t rank[ND], total = 0;
-    float unit[ND], kf[ND];
+    float kf[ND];
     double a0 = 0.0;
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
@@ -159,9 +177,7 @@ struct Trade {
       float sale = 0.0f;
       q[i] = 0;
       kf[i] = 0.0f;
-      unit[i] = 0.0f;
-      const double term = ok ? (double)h[i] * (double)pn[i] : 0.0;
-      a0 += term;
+      if (!WALK) a0 += ok ? (double)h[i] * (double)pn[i] : 0.0;
       if (k < 0) {
         const int32_t qs = min(-k, h[i]);
         h[i] -= qs;
@@ -170,12 +186,10 @@ struct Trade {
         q[i] = -qs;
       } else if (k > 0) {
         kf[i] = (float)k;
-        unit[i] = pn[i] * d.one_plus_c;
       }
       if (dd < D4) {
         sell[e * sp + dd] = sale;
         if (NCW > 1) now[e * D4 + dd] = pn[i];
-        if (WALK) terms[e * D4 + dd] = term;
         sq[e * sp + dd] = ok ? eps[i] * eps[i] : 0.0f;
       }
       const uint64_t mine = mine_of(__ballot(k > 0));
@@ -203,8 +217,8 @@ struct Trade {
 #pragma unroll
     for (int i = 0; i < ND; ++i)
       if (kf[i] > 0.0f) {
-        list[e * lp + rank[i]] = Purchase{kf[i], unit[i], 1.0 / (double)unit[i]};
-        out[e * op + rank[i]] = kf[i] * unit[i];
+        list[e * lp + rank[i]] = Purchase{kf[i], units.cost[i], units.rcp[i]};
+        out[e * op + rank[i]] = kf[i] * units.cost[i];
       }
     if (tl < 16) out[e * op + total + tl] = 0.0f;
     market();
@@ -212,18 +226,15 @@ struct Trade {
 
     // the squares are summed in stock order (the log-probability is the same number in every schedule), and so are the sales
     e2 = 0.0f;
-    double v0 = (double)cash_in;
     const env_f32x4 *sales = reinterpret_cast<const env_f32x4 *>(sell + e * sp), *squares = reinterpret_cast<const env_f32x4 *>(sq + e * sp);
     if (WALK) {
-      const env_f64x2 *t = reinterpret_cast<const env_f64x2 *>(terms + e * D4);
-#pragma unroll 2
+#pragma unroll 4
       for (int c = 0; c < D4 / 4; ++c) {
         const env_f32x4 x = sales[c], y = squares[c];
-        const env_f64x2 lo = t[2 * c], hi = t[2 * c + 1];
-        cash = cash + x[0], e2 = e2 + y[0], v0 = v0 + lo[0];
-        cash = cash + x[1], e2 = e2 + y[1], v0 = v0 + lo[1];
-        cash = cash + x[2], e2 = e2 + y[2], v0 = v0 + hi[0];
-        cash = cash + x[3], e2 = e2 + y[3], v0 = v0 + hi[1];
+        cash = cash + x[0], e2 = e2 + y[0];
+        cash = cash + x[1], e2 = e2 + y[1];
+        cash = cash + x[2], e2 = e2 + y[2];
+        cash = cash + x[3], e2 = e2 + y[3];
       }
     } else if (cw == NCW - 1 && want_e2) {
       e2 = serial_sum(0.0f, squares, D4 / 4);
@@ -241,16 +252,17 @@ struct Trade {
         const Purchase mine = lst[min(p, total - 1)];
         const float u = p < total ? mine.u : __builtin_inff();
         int32_t got = 0;
-        for (int s0 = 0; s0 < CW && c0 + s0 < total; s0 += 16) {
-          if (((affordable(cash, u) >> s0) & 0xffffull) == 0) continue;
-          // sixteen purchases in full: as long as the balance stays clear of 0 (2^-20 of what it was, so every outlay
+        constexpr uint64_t all = (1ull << CHUNK) - 1ull;
+        for (int s0 = 0; s0 < CW && c0 + s0 < total; s0 += CHUNK) {
+          if (((affordable(cash, u) >> s0) & all) == 0) continue;
+          // sixteen (or eight) purchases in full: as long as the balance stays clear of 0 (2^-20 of what it was, so every outlay
           // k u before it was below the balance by more than its own rounding), each quotient was at least k
           const env_f32x4 *ov = reinterpret_cast<const env_f32x4 *>(out + e * op + c0 + s0);
           const float clear = cash * 0x1p-20f;
           float full = cash;
           int in_full = 0;
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
+          for (int c = 0; c < CHUNK / 4; ++c) {
             const env_f32x4 v = ov[c];
             full = full - v[0];
             full = full - v[1];
@@ -259,14 +271,14 @@ struct Trade {
             if (full >= clear) cash = full, in_full = 4 * c + 4;  // (outlays are not negative: never true again once false)
           }
           if ((unsigned)(cl - s0) < (unsigned)in_full) got = (int32_t)mine.k;
-          if (in_full == 16) continue;
+          if (in_full == CHUNK) continue;
           // one by one, those that buy nothing (cash < u: the quotient is below 1 and rounds below 1) skipped.
           // The binary32 quotient comes from one binary64 product with the prepared reciprocal of u: the product is
           // within 2^-52 of cash / u, and a quotient of two binary32 numbers is at least 2^-49 (relative) away from
           // every binary32 rounding boundary it does not hit exactly, so the product rounded to binary32 is the
           // correctly rounded cash / u.  It is never negative (cash is not), so truncation is the floor and needs no
           // clamp at 0; the outlay of one share less, (q - 1) u rounded once, is the fused q u - u.
-          uint64_t ahead = (0xffffull << s0) & (~0ull << (s0 + in_full));
+          uint64_t ahead = (all << s0) & (~0ull << (s0 + in_full));
           while (true) {
             const uint64_t left = affordable(cash, u) & ahead;
             if (left == 0) break;
@@ -289,7 +301,7 @@ struct Trade {
     meet();
 
     // -- executed trades, holdings, account value after them
-    double a1 = 0.0, v1 = (double)cash;
+    double a1 = 0.0, v0 = (double)cash_in, v1 = (double)cash;
     float lowest = __builtin_inff();
     int32_t sign = 0;
     int32_t h1[ND];
@@ -314,23 +326,14 @@ struct Trade {
       }
       h1[i] = h[i];
       const double term = (double)h[i] * (double)pv[i];
-      if (WALK && dd < D) terms[e * D4 + dd] = term;
+      if (WALK) put_term(i, dd < D ? term : 0.0);
       if (live && dd < D) {
         a1 += term;
         if (!WALK) lowest = fminf(lowest, fminf(price_now(i), pv[i])), sign |= h[i] | (h[i] - q[i]);
         booked(i);
       }
     }
-    if (WALK) {
-      meet();
-      const env_f64x2 *t = reinterpret_cast<const env_f64x2 *>(terms + e * D4);
-#pragma unroll 4
-      for (int c = 0; c < D4 / 2; ++c) {
-        const env_f64x2 x = t[c];
-        v1 = v1 + x[0];
-        v1 = v1 + x[1];
-      }
-    } else {
+    if (!WALK) {
       a1 = sum_lanes(a1, CW);
       if (sign < 0) lowest = -1.0f;
       bool again;  // for the whole workgroup, or wavefront
@@ -360,8 +363,26 @@ struct Trade {
         meet();
         if (tl == 0) add_terms();
       }
+      r = (v1 - v0) * (double)d.rho;
     }
-    r = (v1 - v0) * (double)d.rho;
+  }
+
+  // WALK: the account value after run(), in stock order (all of an env's threads take it)
+  __device__ inline double value(float cash) const {
+    const env_f64x2 *t = reinterpret_cast<const env_f64x2 *>(terms + ((threadIdx.x & (NT - 1)) / TPE) * D4);
+    double v = (double)cash;
+    meet();
+#pragma unroll 4
+    for (int c = 0; c < D4 / 2; ++c) {
+      const env_f64x2 x = t[c];
+      v = v + x[0];
+      v = v + x[1];
+    }
+    return v;
+  }
+  __device__ inline void put_term(int i, double term) {  // of the thread's i-th stock, of the D4
+    const int t = threadIdx.x & (NT - 1), dd = (t & (TPE - 1)) + TPE * i;
+    if (dd < D4) terms[(t / TPE) * D4 + dd] = term;
   }
 };
 

@@ -518,3 +518,35 @@ def test_fp32_value_head_tiles(N, rows, agents, D, K):
         sel = pick[(pick % N) // (N // agents) == a]
         assert len(sel)
         parity.check_networks(w, d["actor"], d["critic"], X[sel], None, val[sel], agent=a)
+
+
+# the persistent rollout of fp32 networks: 16 envs per workgroup up to 4096 envs, 32 beyond; no block of market columns only
+# and almost all of them such, inputs that end inside a block of 32, all stock slots in use, several agents, one market for
+# all, episodes that end inside a call and on its last step, calls that go on where the last one stopped
+@pytest.mark.parametrize("N,agents,H,n_market,D,K", [(32, 1, 5, None, 1, 4), (64, 2, 7, 1, 32, 7), (96, 1, 3, None, 2, 2), (160, 5, 6, None, 12, 1),
+                                                     (4096, 1, 4, None, 28, 9), (4128, 1, 5, None, 30, 8), (8192, 2, 8, 1, 7, 4)])
+def test_fused_fp32_env_counts(N, agents, H, n_market, D, K):
+    if agents > 1:
+        N = N // agents // 64 * 64 * agents or 64 * agents
+    w = inputs.WORKLOADS["dow30"].replace(n_envs=N, n_agents=agents, n_stocks=D, n_ind=K, steps=8, cash0=3.0e4)
+    d = inputs.make_all(w, horizon=H, n_market=n_market, steps=8)
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    make = lambda schedule: pr.Rollout(pr.make_config(w, horizon=H, n_market=n_market, schedule=schedule), _t(d["price"]), _t(d["ind"]),
+                                       dev(d["actor"]), dev(d["critic"]))
+    fused, steps = make(pr.PR_SCHED_FUSED), make(pr.PR_SCHED_STEPWISE)
+    noise = _t(d["noise"])
+    for t0, T in ((0, 1), (1, 4), (5, 3)):
+        a, b = (ro.alloc_buffers(T, value=False, logp=True, mu=True, shares=True) for ro in (fused, steps))
+        fused.step_T(T, noise[t0:t0 + T].contiguous(), a)
+        steps.step_forced(T, a["mu"], noise[t0:t0 + T].contiguous(), b)
+        mu = steps.mlp_forward(pr.PR_NET_ACTOR, a["obs"][:T].reshape(T * N, w.state_dim)).reshape(T, N, D)
+        torch.cuda.synchronize()
+        for k in ("obs", "act_raw", "reward", "done", "logp", "shares"):
+            assert torch.equal(a[k], b[k]), (k, t0)
+        # (against the step's largest mean: with one stock a mean can be as near to zero as it likes, the rounding of its
+        # 256 terms h W3, about 256 x 2^-24 x 0.1, cannot)
+        err = (mu - a["mu"]).abs().amax(dim=(1, 2)) / mu.abs().amax(dim=(1, 2))
+        assert float(err.max()) <= 2.0 * parity.TOL_NORM_F32
+    sa, sb = fused.get_state(), steps.get_state()
+    for k in sa:
+        assert torch.equal(sa[k], sb[k]), k
