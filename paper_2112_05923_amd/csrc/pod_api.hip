@@ -74,7 +74,7 @@ bool uses_rotated(const pr_config &c) { return c.schedule == PR_SCHED_FUSED || s
 
 // k-blocks of that copy of layer 1.  The persistent fp32 rollout of few envs reads blocks of 32 inputs, with the cash last,
 // so that all market columns come first.
-bool market_first(const pr_config &c) { return c.schedule == PR_SCHED_FUSED && fused_few_envs(c); }
+bool market_first(const pr_config &c) { return c.schedule == PR_SCHED_FUSED && c.mlp_dtype == PR_MLP_F32; }
 int rotated_blocks(const pr_config &c) {
   const int nkb = (state_dim(c) + 15) / 16;
   return market_first(c) ? (nkb + 1) & ~1 : nkb;

@@ -1,7 +1,6 @@
-// Persistent rollout kernel: one workgroup keeps a tile of envs (64 with bf16
-// networks, 32 with fp32 networks) on its compute unit for all T steps of a
-// rollout (the worker of Sec. 4.2: actor x batched environment; stock-trading
-// task of Table 1 / Sec. 5.3).
+// Persistent rollout kernel of bf16 networks: one workgroup keeps a tile of 64
+// envs on its compute unit for all T steps of a rollout (the worker of Sec. 4.2:
+// actor x batched environment; stock-trading task of Table 1 / Sec. 5.3).
 //
 // Envs are independent, so no grid-wide synchronisation is needed: each
 // workgroup loops   obs_t (LDS) -> actor (matrix cores) -> sample -> trade ->
@@ -43,8 +42,7 @@ using namespace tile;
 
 constexpr int NW = 8;
 constexpr int NT = NW * 64;
-// envs per workgroup: 64 (bf16 networks) or 32 (fp32 networks, whose 64-row tiles do not fit in LDS); a template
-// parameter E of the kernel
+// (fp32 networks: pod_fused_f32.hip.  Their rollout with the means given runs here, 32 envs per workgroup.)
 constexpr int DMAX = 32;         // stock slots per env row in LDS; slots D..31 hold neutral values (k = 0, h = 0)
 constexpr int kDp = DMAX + 1;    // odd row pitch: the per-env serial walks of the ledger hit distinct banks
 // Lane maps of the parallel env work (no index divisions anywhere in the step loop):
@@ -58,8 +56,8 @@ constexpr int kDp = DMAX + 1;    // odd row pitch: the per-env serial walks of t
 constexpr int kLagPrio = 2;  // wavefront priority of the lagging group's matrix steps in the split schedule (1..3 measure alike)
 constexpr int MUP = 33;         // row pitch of a policy-mean plane (lanes of one store differ in the row: 32 would hit one bank)
 // Planes the output layer's k range is split into (one per group of wavefronts), by the compile-time k-block count
-// of the kernel instance.  fp32 networks: eight, one per wavefront, each holding its output weights in registers.
-constexpr int mu_planes(bool bf16, int nkb2) { return !bf16 ? 8 : (nkb2 > 0 && nkb2 % 4 == 0) ? 4 : 1; }
+// of the kernel instance.
+constexpr int mu_planes(int nkb2) { return nkb2 > 0 && nkb2 % 4 == 0 ? 4 : 1; }
 
 struct Row {
   int32_t row_val;  // market row the portfolio is valued at (cursor + 1)
@@ -115,13 +113,13 @@ __device__ inline Row row_of(const EnvDims &d, int32_t tau, int32_t start, int32
   return r;
 }
 
-template <bool BF16, int E, int CTH, int NKB1, int NKB2, bool ACTOR>
+template <int E, int CTH, int NKB1, int NKB2, bool ACTOR>
 __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
-  static_assert(E == 64 || E == 32, "one or two 32-row batch tiles");
+  static_assert(E == 64 || (E == 32 && !ACTOR), "the actor's tiles have 64 rows");
   constexpr int NBT = E / 32;
-  using O = tile::Op<BF16>;
+  using O = tile::Op<true>;
   // the named bf16 shape runs its actor as two wavefront groups half a layer out of step (see the step loop)
-  constexpr bool SPLIT = ACTOR && BF16 && E == 64 && CTH == 2 && NKB2 == 32 && NKB1 >= 16;
+  constexpr bool SPLIT = ACTOR && E == 64 && CTH == 2 && NKB2 == 32 && NKB1 >= 16;
   constexpr int PDR = SPLIT ? 8 : ring_depth(CTH);  // weight blocks in flight per feature tile
   // Roles of the wavefronts outside the actor.  The ledger wavefront LW walks the cash chains; MW others carry
   // the market rows of the next observation.  In the split schedule these are the four wavefronts of group A,
@@ -161,7 +159,7 @@ __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
   float *s_pv = reinterpret_cast<float *>(s_q + E * Dp);    // valuation prices
   float *s_e2 = s_pv + E * Dp;                              // squared noise
   // output-layer accumulators of the actor, one [E][32] plane per k part of that layer (summed in the pre-compute)
-  constexpr int KS = mu_planes(BF16, NKB2);
+  constexpr int KS = mu_planes(NKB2);
   float *s_mu = reinterpret_cast<float *>(ldsX);
 
   // ---- ledger lanes (wavefront LW, see below): per-env scalars in registers for the whole rollout
@@ -170,12 +168,9 @@ __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
   double asset = 0.0, ep_ret = 0.0, ep_sum = 0.0, ep_sqsum = 0.0;
 
   Net net;
-  // fp32: this wavefront's k-blocks of the output layer
-  constexpr int NW3 = ACTOR && !BF16 ? NKB2 / KS : 1;
-  typename O::Block w3r[NW3];
   if (ACTOR) {
     net = net_of(a.actor, (n0 % d.N) / a.envs_per_agent);
-    stage_net<NT>(net, ldsBias, BF16 ? ldsW3 : nullptr, tid);
+    stage_net<NT>(net, ldsBias, ldsW3, tid);
     if constexpr (SPLIT) {
       // Output-layer blocks in the k order of an accumulator half: the lane of half g takes, from the standard
       // block's two lanes of its output feature, the four k of each that an accumulator lane of half g holds.
@@ -191,10 +186,6 @@ __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
       __syncthreads();
 #pragma unroll
       for (int j = 0; j < NKB2 * 64 / NT; ++j) ldsW3[tid + NT * j] = v[j];
-    }
-    if constexpr (!BF16) {
-#pragma unroll
-      for (int i = 0; i < NW3; ++i) fetch_w(w3r[i], net.W[2] + (wave * NW3 + i) * (64 * kPlanes<typename O::Block>) + lane);
     }
     // padded k columns of the input tile must read as zero
     for (int i = tid; i < E * a.L.xpitch / 4; i += NT) reinterpret_cast<uint32_t *>(ldsX)[i] = 0u;
@@ -502,11 +493,8 @@ __global__ __launch_bounds__(NT) void rollout_fused_kernel(FusedArgs a) {
       // its noise, valuation prices and market rows -- the slot in which B runs step (e))
     } else {
       if (ACTOR) {
-        auto w3 = [&](int kb0, int i) -> typename O::Block {
-          if constexpr (BF16) return LdsW3<true>{ldsW3, lane}(kb0, i);
-          else return w3r[i];
-        };
-        mlp_tile<BF16, NW, CTH, false, NKB1, NKB2, true, true, KS, NBT>(
+        const LdsW3<true> w3{ldsW3, lane};
+        mlp_tile<true, NW, CTH, false, NKB1, NKB2, true, true, KS, NBT>(
             net, ring, ldsX, a.L.xpitch, ldsH, a.L.hpitch, ldsBias, w3, tid,
             [&]() {
               fetch_step_inputs(t);
@@ -785,15 +773,11 @@ FusedShape fused_shape(const pr_config &c) {
   f.envs = bf ? 64 : 32;
   f.cth = (c.hidden / 32) / NW;
   f.nkb1 = f.nkb2 = 0;
-  // the named shapes: 301 inputs with 512 hidden units in bf16 / 256 hidden units in fp32
+  // the named shape: 301 inputs with 512 hidden units
   // (the split schedule of this instance runs the first 11 k-blocks of layer 1 before the portfolio columns
   // exist: they must all be indicator columns)
   if (bf && f.cth == 2 && (S + 15) / 16 == 19 && c.hidden / 16 == 32 && c.n_stocks * c.n_ind >= 11 * 16)
     f.nkb1 = 19, f.nkb2 = 32;
-  if (!bf) {
-    f.nkb2 = 16;  // (256 hidden units)
-    if ((S + 15) / 16 == 19) f.nkb1 = 19;
-  }
   return f;
 }
 
@@ -813,7 +797,7 @@ FusedLayout fused_layout(const pr_config &c, bool with_actor) {
   size_t off = (size_t)E * L.hpitch;
   L.off_x = (int32_t)off;
   size_t xbytes = (size_t)E * L.xpitch;
-  const size_t mu_bytes = with_actor ? (size_t)mu_planes(bf, fs.nkb2) * E * MUP * 4 : 0;
+  const size_t mu_bytes = with_actor ? (size_t)mu_planes(fs.nkb2) * E * MUP * 4 : 0;
   if (xbytes < mu_bytes) xbytes = (mu_bytes + 15) / 16 * 16;
   off += xbytes;
   L.off_w3 = (int32_t)off;
@@ -840,7 +824,7 @@ constexpr size_t kLdsMax = kMaxLdsBytes;
 
 // Shapes the persistent kernel covers: networks whose whole input tile, hidden tile and output-layer weights fit
 // in LDS next to the env arrays -- bf16 with 256 or 512 hidden units on 64-env tiles, fp32 with 256 hidden units
-// on 32-env tiles; N (and the envs of an agent) a multiple of the tile; D <= 32; D K <= 252 and a multiple of 4
+// on tiles of 16 or 32; N (and the envs of an agent) a multiple of the tile; D <= 32; D K <= 252 and a multiple of 4
 // (the indicator rows are moved in 16-byte groups; the market tensors must be 16-byte aligned); one output
 // feature tile.
 bool fused_supported(const pr_config &c) {
@@ -855,12 +839,12 @@ bool fused_supported(const pr_config &c) {
 }
 
 size_t fused_lds_bytes(const pr_config &c, bool with_actor) {
-  return with_actor && fused_few_envs(c) ? fused_f32_lds_bytes(c) : (size_t)fused_layout(c, with_actor).total;
+  return with_actor && c.mlp_dtype == PR_MLP_F32 ? fused_f32_lds_bytes(c) : (size_t)fused_layout(c, with_actor).total;
 }
 
-template <bool BF16, int E, bool ACTOR, int CTH, int NKB1, int NKB2>
+template <int E, bool ACTOR, int CTH, int NKB1, int NKB2>
 static hipError_t launch_fused_inst(hipStream_t st, const FusedArgs &a, unsigned blocks, size_t lds) {
-  constexpr auto kern = rollout_fused_kernel<BF16, E, CTH, NKB1, NKB2, ACTOR>;
+  constexpr auto kern = rollout_fused_kernel<E, CTH, NKB1, NKB2, ACTOR>;
   const hipError_t e = allow_full_lds<kern>();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(NT), lds, st, a);
@@ -872,8 +856,8 @@ hipError_t launch_rollout_fused(hipStream_t st, const pr_config &c, const EnvDim
                                 int32_t T, const float *noise, const float *mu_forced, const pr_buffers &out) {
   if (!fused_supported(c)) return hipErrorInvalidValue;
   if (reinterpret_cast<uintptr_t>(ind) & 15u) return hipErrorInvalidValue;  // 16-byte indicator loads
-  if (!mu_forced && fused_few_envs(c))
-    return launch_rollout_fused_f32(st, c, d, s, price, ind, actor, envs_per_agent, T, noise, out);
+  if (!mu_forced && c.mlp_dtype == PR_MLP_F32)
+    return launch_rollout_fused_f32(st, d, s, price, ind, actor, envs_per_agent, T, noise, out);
   FusedArgs a;
   a.d = d;
   a.st = s;
@@ -897,20 +881,14 @@ hipError_t launch_rollout_fused(hipStream_t st, const pr_config &c, const EnvDim
   if (lds > kLdsMax) return hipErrorInvalidValue;
   const FusedShape fs = fused_shape(c);
   const unsigned blocks = (unsigned)(d.N / fs.envs);
-  if (with_actor && ((actor.bf16 != 0) != (c.mlp_dtype == PR_MLP_BF16) || tile_pitch(actor.bf16, actor.nkb[0]) != a.L.xpitch ||
-                     tile_pitch(actor.bf16, actor.nkb[1]) > a.L.hpitch || actor.nkb[2] != actor.nkb[1] || actor.nct[2] != 1))
+  if (with_actor && (!actor.bf16 || tile_pitch(1, actor.nkb[0]) != a.L.xpitch || tile_pitch(1, actor.nkb[1]) > a.L.hpitch ||
+                     actor.nkb[2] != actor.nkb[1] || actor.nct[2] != 1))
     return hipErrorInvalidValue;  // the packed network is not the one the layout was made for
-  if (c.mlp_dtype == PR_MLP_BF16) {
-    if (!with_actor) return launch_fused_inst<true, 64, false, 1, 0, 0>(st, a, blocks, lds);
-    if (fs.cth == 2 && fs.nkb1 == 19 && fs.nkb2 == 32) return launch_fused_inst<true, 64, true, 2, 19, 32>(st, a, blocks, lds);
-    if (fs.cth == 2) return launch_fused_inst<true, 64, true, 2, 0, 0>(st, a, blocks, lds);
-    if (fs.cth == 1) return launch_fused_inst<true, 64, true, 1, 0, 0>(st, a, blocks, lds);
-  } else {
-    if (!with_actor) return launch_fused_inst<false, 32, false, 1, 0, 16>(st, a, blocks, lds);
-    // (straight-line layer 1 for the observation width of the named workloads: 17.5 -> 16.1 us a step and tile)
-    if (fs.cth == 1 && fs.nkb1 == 19) return launch_fused_inst<false, 32, true, 1, 19, 16>(st, a, blocks, lds);
-    if (fs.cth == 1) return launch_fused_inst<false, 32, true, 1, 0, 16>(st, a, blocks, lds);
-  }
+  if (!with_actor)
+    return fs.envs == 64 ? launch_fused_inst<64, false, 1, 0, 0>(st, a, blocks, lds) : launch_fused_inst<32, false, 1, 0, 0>(st, a, blocks, lds);
+  if (fs.cth == 2 && fs.nkb1 == 19 && fs.nkb2 == 32) return launch_fused_inst<64, true, 2, 19, 32>(st, a, blocks, lds);
+  if (fs.cth == 2) return launch_fused_inst<64, true, 2, 0, 0>(st, a, blocks, lds);
+  if (fs.cth == 1) return launch_fused_inst<64, true, 1, 0, 0>(st, a, blocks, lds);
   return hipErrorInvalidValue;
 }
 

@@ -1,12 +1,11 @@
-// Persistent rollout kernel for the few envs of an fp32 network of 256 hidden units:
-// one workgroup keeps 16 envs on its compute unit for all T steps (the worker of
-// Sec. 4.2; see pod_fused.hip, which has the others).
+// Persistent rollout kernel for fp32 networks of 256 hidden units: one workgroup keeps
+// 16 or 32 envs on its compute unit for all T steps (the worker of Sec. 4.2; see
+// pod_fused.hip, which has the bf16 networks).
 //
-// A step is a chain -- observation, three layers, sample, trade, observation -- and
-// while every workgroup has a compute unit to itself everything on it is latency.
-// Four wavefronts run the network, a SIMD each, four others the envs, and what depends
-// on no decision leaves the chain:
-//   network                                   envs (sixteen threads each)
+// A step is a chain -- observation, three layers, sample, trade, observation.  Four
+// wavefronts run the network, a SIMD each, four others the envs, and what depends on no
+// decision leaves the chain:
+//   network                                   envs (sixteen or eight threads each)
 //   layer 1, the portfolio's columns, tanh    reward of step t - 1; request noise and the next market rows
 //   --- hidden layer complete, input free
 //   layer 2, tanh, output layer               write the market rows of observation t + 1 (records and input tile)
@@ -16,15 +15,19 @@
 // The two kinds of wavefront run separate loops with the same barriers: neither's
 // registers are live in the other's code.
 //
-// Bound by the weight stream -- 850 KB a step, which a compute unit takes in at 64 B a
-// clock, 5.8 us at 2.3 GHz; 84 KB of layer 2 stay in LDS and the output layer's 48 KB in
-// registers (without either 12.3 us a step for 11.4) -- and by the chains beside it: two
-// epilogues of 1.1 us, trades 3 us.  301 inputs, per step: 1024 envs 16.2 -> 9.1 us,
-// 4096 16.9 -> 11.4 (32 envs on every second compute unit, all eight wavefronts taking
-// turns at network and envs); 12 stocks x 4 indicators, 4096 envs, 14.2 -> 8.4.
+// Bound with 16 envs by the weight stream -- 850 KB a step, which a compute unit takes in
+// at 64 B a clock, 5.8 us at 2.3 GHz; 84 KB of layer 2 stay in LDS and the output layer's
+// 48 KB in registers (without either 12.3 us a step for 11.4) -- and by the chains beside
+// it: two epilogues of 1 us, trades 3 us.  With 32 envs the matrix instructions take as
+// long as the stream, and the chip clocks down to 1.7-1.9 GHz: 6 us of matrix work in 17.
+// 301 inputs, per step, against 32 envs whose eight wavefronts all take turns at network
+// and envs: 1024 envs 16.2 -> 8.2 us, 4096 16.9 -> 10.9, 8192 20.4 -> 17.2, 16384 37.9 ->
+// 34.0, 65536 of 64 agents 151 -> 135; 12 stocks x 4 indicators, 4096 envs, 14.2 -> 8.4.
 //
 // Compiled with floating-point contraction off (integer decisions depend on
 // one rounding per operation).
+#include <type_traits>
+
 #include "pod_internal.h"
 #include "pod_tile.h"
 #include "pod_trade.h"
@@ -36,20 +39,67 @@ namespace {
 using namespace tile;
 using O = Op<false>;
 
-constexpr int E = 16;               // envs per workgroup
 constexpr int NM = 4, NE = 4;       // wavefronts of the network / of the envs
 constexpr int NT = 64 * (NM + NE);
-constexpr int KBYTES = 2 * O::KBYTES;  // of 32 inputs in an activation row
-constexpr int NK2 = 8, HP = tile_pitch<false>(2 * NK2);
+constexpr int HP = tile_pitch<false>(16);
 constexpr int MUP = 36;             // row pitch of a plane of partial means
-constexpr int PLANE = E * MUP;
-constexpr int NL = 7;               // units of layer 2 per wavefront that stay in LDS
-constexpr int PK = 2, PU = 4 * PK;   // blocks of 32 inputs, and units of weights, in flight per wavefront
+constexpr int LB = 8 * 192;         // 16-byte pieces of a k-block of a hidden layer
 
-using Tr = Trade<E, 2, true, 64 * NE>;
-constexpr int TPE = Tr::TPE, ND = 2, ROWS = E / NE;
+// What differs between 16 and 32 envs: the matrix instruction, and with it how weights, inputs and sums lie in the lanes.
+//  32: v_mfma_f32_32x32x16, lane l feeds feature l % 32 and row l % 32, inputs 8 (l / 32) .. + 7 of 16
+//  16: v_mfma_f32_16x16x32, lane l feeds feature l % 16 and row l % 16, inputs 8 (l / 16) .. + 7 of 32
+// A unit is such an operand of the packed weights, whose blocks are made for the first: for 16 envs, half the features of
+// two blocks.  A lane holds sums of its row for groups of four features.
+template <int E>
+struct Geometry {
+  static constexpr bool SM = E == 16;
+  typedef std::conditional_t<SM, f32x4, f32x16> Acc;
+  static constexpr int NACC = SM ? 4 : 2;             // accumulators of a wavefront's 64 features: units per block of inputs
+  static constexpr int KIN = SM ? 32 : 16;            // inputs per block
+  static constexpr int KBYTES = KIN * O::ESZ;         // ... in an activation row
+  static constexpr int BLOCK = SM ? 2 * LB : LB;      // 16-byte pieces between the blocks of a hidden layer
+  static constexpr int NK2 = 256 / KIN;
+  static constexpr int PK = SM ? 2 : 4, PU = PK * NACC;  // blocks, and units of weights, in flight per wavefront
+  static constexpr int NL = SM ? 7 : 1;               // units of layer 2 per wavefront that stay in LDS
+  static constexpr int NG = SM ? 4 : 8;               // groups of four features per lane
+  static constexpr int N3 = SM ? 2 : 4, NC3 = SM ? 2 : 1;  // output layer: blocks of a wavefront's inputs, tiles of outputs
+  static constexpr int ND = E / 8, ROWS = E / NE;     // stocks per thread and market rows per wavefront of the envs
+  static constexpr int PLANE = E * MUP;
+  using Tr = Trade<E, ND, true, 64 * NE>;
 
-__host__ __device__ inline int input_pitch(int nkb) { return tile_pitch<false>((nkb + 1) & ~1); }
+  static __device__ inline int row(int lane) { return lane & (E - 1); }
+  static __device__ inline int part(int lane) { return lane / E; }
+  static __device__ inline const u32x4 *base(const u32x4 *W, int w, int lane) {  // of unit 0 of features 64 w ..
+    return SM ? W + ((size_t)(lane >> 5) * 8 + 2 * w) * 192 + ((lane >> 4) & 1) * 32 + (lane & 15) : W + (size_t)(2 * w) * 192 + lane;
+  }
+  static __device__ inline const u32x4 *unit(const u32x4 *W, int u) {
+    return W + (size_t)(u / NACC) * BLOCK + (SM ? ((u >> 1) & 1) * 192 + (u & 1) * 16 : (u & 1) * 192);
+  }
+  static __device__ inline void fetch_unit(Blk3 &b, const u32x4 *W, int u) { fetch_w(b, unit(W, u)); }
+  static __device__ inline void mma(const Blk3 &w, const Blk3 &x, Acc &c) {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+      const bf16x8 a = __builtin_bit_cast(bf16x8, w.p[kSplitA[i]]), b = __builtin_bit_cast(bf16x8, x.p[kSplitB[i]]);
+      if constexpr (SM) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+      else c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+    }
+  }
+  static __device__ inline void clear(Acc &c) {
+#pragma unroll
+    for (int i = 0; i < (SM ? 4 : 16); ++i) c[i] = 0.0f;
+  }
+  // group m of a wavefront's features: its first feature (of lane part q), and its sums
+  static __device__ inline int feature(int m, int q) { return (SM ? 16 : 8) * m + 4 * q; }
+  static __device__ inline float get(const Acc (&c)[NACC], int m, int i) { return SM ? c[m][i] : c[m >> 2][4 * (m & 3) + i]; }
+  static __device__ inline void put(Acc (&c)[NACC], int m, int i, float v) {
+    if (SM) c[m][i] = v;
+    else c[m >> 2][4 * (m & 3) + i] = v;
+  }
+};
+
+// whole blocks of 32 inputs for the short instruction
+template <int E>
+__host__ __device__ inline int input_pitch(int S) { return tile_pitch<false>(E == 16 ? (S + 31) / 32 * 2 : (S + 15) / 16); }
 
 struct F32Args {
   EnvDims d;
@@ -68,28 +118,15 @@ struct F32Args {
   int32_t *shares;     // opt [T, N, D]
 };
 
-// v_mfma_f32_16x16x32: lane l feeds feature l % 16 and row l % 16, inputs 8 (l / 16) .. + 7 of 32, and holds features
-// 4 (l / 16) .. + 3 of row l % 16.  A unit is such an operand of the packed weights, whose blocks are made for 32 features
-// and 16 inputs: half the features of two blocks.
-__device__ inline void mma16(const Blk3 &w, const Blk3 &x, f32x4 &c) {
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w.p[kSplitA[i]]),
-                                                __builtin_bit_cast(bf16x8, x.p[kSplitB[i]]), c, 0, 0, 0);
-}
-
-// Where a lane's part of unit 0 lies, in a layer of nct feature tiles, for features from 32 ct on.
-__device__ inline const u32x4 *unit_base(const u32x4 *W, int nct, int ct, int lane) {
-  return W + ((size_t)(lane >> 5) * nct + ct) * 192 + ((lane >> 4) & 1) * 32 + (lane & 15);
-}
-
-// The 64 features of a wavefront are four units per 32 inputs.
-// tanh of sixteen values, one operation at a time over all of them (see tanh_in_place).
-__device__ inline void tanh_accurate_16(f32x4 (&z)[4]) {
+// tanh of sixteen values, one operation at a time over all of them (see tanh_in_place), with between(0 .. 11) behind each.
+template <class Between>
+__device__ inline void tanh_accurate_16(float (&z)[16], Between between) {
   float e[16], x2[16], ps[16];
+  int stage = 0;
   auto all = [&](auto op) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) op(i, z[i >> 2][i & 3]);
+    for (int i = 0; i < 16; ++i) op(i, z[i]);
+    between(stage++);
     __builtin_amdgcn_sched_barrier(0);
   };
   all([&](int i, float x) { e[i] = fabsf(x) * kTwoLog2e; });
@@ -103,16 +140,12 @@ __device__ inline void tanh_accurate_16(f32x4 (&z)[4]) {
   all([&](int i, float x) { x2[i] = x2[i] * x; });
   all([&](int i, float x) { ps[i] = fmaf(x2[i], ps[i], x); });
   all([&](int i, float x) { e[i] = copysignf(1.0f - 2.0f * e[i], x); });
-  all([&](int i, float x) { z[i >> 2][i & 3] = fabsf(x) < 0.25f ? ps[i] : e[i]; });
+  all([&](int i, float x) { z[i] = fabsf(x) < 0.25f ? ps[i] : e[i]; });
 }
 
-__device__ inline void fetch_unit(Blk3 &b, const u32x4 *W, int u) {
-  fetch_w(b, W + (size_t)(u >> 2) * (2 * 8 * 192) + ((u >> 1) & 1) * 192 + (u & 1) * 16);
-}
-
-// acc += inputs 32 [0, n) of a range; the ring holds the first units.  N > 0: n at compile time, in straight-line code.
-template <int N>
-__device__ inline void products(f32x4 (&acc)[4], Blk3 (&ring)[PU], const unsigned char *x, const u32x4 *W, int n) {
+// acc += blocks [0, n) of a range of inputs; the ring holds the first units.  N > 0: n at compile time, in straight-line code.
+template <class G, int N>
+__device__ inline void products(typename G::Acc (&acc)[G::NACC], Blk3 (&ring)[G::PU], const unsigned char *x, const u32x4 *W, int n) {
   if constexpr (N > 0) {
     Blk3 xn;
     fetch_x(xn, x);
@@ -120,64 +153,69 @@ __device__ inline void products(f32x4 (&acc)[4], Blk3 (&ring)[PU], const unsigne
     for (int K = 0; K < N; ++K) {
       const Blk3 xv = xn;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int u = 4 * K + j;
+      for (int j = 0; j < G::NACC; ++j) {
+        const int u = G::NACC * K + j;
         if (j == 0 && K + 1 < N) {
-          fetch_x(xn, x + (K + 1) * KBYTES);
+          fetch_x(xn, x + (K + 1) * G::KBYTES);
           __builtin_amdgcn_sched_barrier(0);
         }
-        mma16(ring[u % PU], xv, acc[j]);
-        if (u + PU < 4 * N) fetch_unit(ring[u % PU], W, u + PU);
+        G::mma(ring[u % G::PU], xv, acc[j]);
+        if (u + G::PU < G::NACC * N) G::fetch_unit(ring[u % G::PU], W, u + G::PU);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
   } else {
     auto block = [&](int K, int k) {  // (k: K modulo PK, at compile time)
       Blk3 xv;
-      fetch_x(xv, x + K * KBYTES);
+      fetch_x(xv, x + K * G::KBYTES);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        mma16(ring[4 * k + j], xv, acc[j]);
-        fetch_unit(ring[4 * k + j], W, 4 * min(K + PK, n - 1) + j);
+      for (int j = 0; j < G::NACC; ++j) {
+        G::mma(ring[G::NACC * k + j], xv, acc[j]);
+        G::fetch_unit(ring[G::NACC * k + j], W, G::NACC * min(K + G::PK, n - 1) + j);
         __builtin_amdgcn_sched_barrier(0);
       }
     };
     int K = 0;
-    for (; K + PK <= n; K += PK) {
+    for (; K + G::PK <= n; K += G::PK) {
 #pragma unroll
-      for (int k = 0; k < PK; ++k) block(K + k, k);
+      for (int k = 0; k < G::PK; ++k) block(K + k, k);
     }
 #pragma unroll
-    for (int k = 0; k < PK - 1; ++k)
+    for (int k = 0; k < G::PK - 1; ++k)
       if (K + k < n) block(K + k, k);
   }
 }
 
 // Layer 2: the first NL units from LDS (`own`, this lane's), the others through the ring, which holds the first of them.
-__device__ inline void products2(f32x4 (&acc)[4], Blk3 (&ring)[PU], const unsigned char *x, const u32x4 *own, const u32x4 *W) {
+template <class G>
+__device__ inline void products2(typename G::Acc (&acc)[G::NACC], Blk3 (&ring)[G::PU], const unsigned char *x, const u32x4 *own, const u32x4 *W) {
+  constexpr int NL = G::NL;
   Blk3 xn, wn;
   fetch_x(xn, x);
   fetch_w(wn, own);
 #pragma unroll
-  for (int K = 0; K < NK2; ++K) {
+  for (int K = 0; K < G::NK2; ++K) {
     const Blk3 xv = xn;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int u = 4 * K + j, r = u - NL;
-      const Blk3 wv = r < 0 ? wn : ring[r < 0 ? 0 : r % PU];
-      if (j == 0 && K + 1 < NK2) fetch_x(xn, x + (K + 1) * KBYTES);
+    for (int j = 0; j < G::NACC; ++j) {
+      const int u = G::NACC * K + j, r = u - NL;
+      const Blk3 wv = r < 0 ? wn : ring[r < 0 ? 0 : r % G::PU];
+      if (j == 0 && K + 1 < G::NK2) fetch_x(xn, x + (K + 1) * G::KBYTES);
       if (u + 1 < NL) fetch_w(wn, own + (u + 1) * 192);
       __builtin_amdgcn_sched_barrier(0);
-      mma16(wv, xv, acc[j]);
-      if (r >= 0 && u + PU < 4 * NK2) fetch_unit(ring[r % PU], W, u + PU);
+      G::mma(wv, xv, acc[j]);
+      if (r >= 0 && u + G::PU < G::NACC * G::NK2) G::fetch_unit(ring[r % G::PU], W, u + G::PU);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
 }
 
-// NK1, NH: 32-input blocks of layer 1, and how many of them hold market columns only (0: at run time)
-template <int NK1, int NH>
+// NK1, NH: blocks of layer 1, and how many of them hold market columns only (0: at run time)
+template <int E, int NK1, int NH>
 __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
+  using G = Geometry<E>;
+  using Tr = typename G::Tr;
+  constexpr int PLANE = G::PLANE, TPE = Tr::TPE, ND = G::ND, ROWS = G::ROWS, PU = G::PU, NL = G::NL;
   extern __shared__ __align__(16) unsigned char lds[];
   const EnvDims &d = a.d;
   const int D = d.D, DK = D * d.K, S = d.S;
@@ -197,36 +235,55 @@ __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
 
   if (w < NM) {
     // ---------------------------------------------------------------- the network, features 64 w ..
-    const int nk1 = NK1 > 0 ? NK1 : net.nkb[0] / 2, nh = NH > 0 ? NH : (DK + D) / 32;
-    const int row = lane & 15, kq = lane >> 4;
-    const unsigned char *xrow = ldsX + row * a.xpitch + O::HALF * kq, *hrow = ldsH + row * HP + O::HALF * kq;
+    const int nk1 = NK1 > 0 ? NK1 : (S + G::KIN - 1) / G::KIN, nh = NH > 0 ? NH : (DK + D) / G::KIN;
+    const int row = G::row(lane), part = G::part(lane);
+    const unsigned char *xrow = ldsX + row * a.xpitch + O::HALF * part, *hrow = ldsH + row * HP + O::HALF * part;
     Blk3 ring[PU];
-    f32x4 acc[4];
+    typename G::Acc acc[G::NACC];
     auto prime_range = [&](const u32x4 *W, int n) {
 #pragma unroll
       for (int u = 0; u < PU; ++u)
-        if (u / 4 < n) fetch_unit(ring[u], W, u);
+        if (u / G::NACC < n) G::fetch_unit(ring[u], W, u);
     };
     auto clear = [&]() {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int j = 0; j < G::NACC; ++j) G::clear(acc[j]);
     };
-    auto activate = [&](const float *bias) {
+    // tanh of the sums, and between its operations, part by part, the ring is filled: all at once the
+    // requests take longer to issue than they take to be answered (2 us for 24 KB a wavefront, the vector units idle)
+    auto activate = [&](const float *bias, auto unit_of_next) {
+      constexpr int PER = 3 * PU * 4 / (12 * G::NG);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j] += *reinterpret_cast<const f32x4 *>(bias + 64 * w + 16 * j + 4 * kq);
-      tanh_accurate_16(acc);
+      for (int m0 = 0; m0 < G::NG; m0 += 4) {
+        float z[16];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          const f32x4 b = *reinterpret_cast<const f32x4 *>(bias + 64 * w + G::feature(m0 + m, part));
+#pragma unroll
+          for (int i = 0; i < 4; ++i) z[4 * m + i] = G::get(acc, m0 + m, i) + b[i];
+        }
+        tanh_accurate_16(z, [&](int stage) {
+#pragma unroll
+          for (int k = 0; k < PER; ++k) {
+            const int p = (stage + 3 * m0) * PER + k;
+            ring[p / 3].p[p % 3] = unit_of_next(p / 3)[64 * (p % 3)];
+          }
+        });
+#pragma unroll
+        for (int m = 0; m < 16; ++m) G::put(acc, m0 + (m >> 2), m & 3, z[m]);
+      }
     };
     int lane_s = lane;
     const u32x4 *W1, *W2;
     auto addresses = [&]() {  // (opaque per step, or the addresses of all weight blocks are kept across the steps)
       asm volatile("" : "+v"(lane_s));
-      W1 = unit_base(net.W[0], 8, 2 * w, lane_s);
-      W2 = unit_base(net.W[1], 8, 2 * w, lane_s);
+      W1 = G::base(net.W[0], w, lane_s);
+      W2 = G::base(net.W[1], w, lane_s);
     };
     auto head = [&]() {
       clear();
-      products<NH>(acc, ring, xrow, W1, nh);
-      prime_range(W1 + (size_t)nh * (2 * 8 * 192), nk1 - nh);
+      products<G, NH>(acc, ring, xrow, W1, nh);
+      prime_range(W1 + (size_t)nh * G::BLOCK, nk1 - nh);
     };
     addresses();
     // kept: the first units of layer 2 (LDS) and the output layer's weights (registers).  A lane of that layer's operand
@@ -235,20 +292,21 @@ __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
 #pragma unroll
     for (int u = 0; u < NL; ++u) {
       Blk3 b;
-      fetch_unit(b, W2, u);
+      G::fetch_unit(b, W2, u);
 #pragma unroll
       for (int i = 0; i < 3; ++i) own[u * 192 + 64 * i] = b.p[i];
     }
-    const unsigned char *W3 = reinterpret_cast<const unsigned char *>(net.W[2] + (size_t)w * (4 * 192) + (kq >> 1) * 32 + row) + 8 * (kq & 1);
-    Blk3 w3[2][2];
+    const unsigned char *W3 = reinterpret_cast<const unsigned char *>(net.W[2] + (size_t)w * (4 * 192) + (E == 16 ? (part >> 1) * 32 : 0) + row) + 8 * (part & 1);
+    constexpr int W3K = E == 16 ? 2 * 192 : 192, W3H = E == 16 ? 192 : 32;  // pieces from block to block, and to the second half
+    Blk3 w3[G::N3][G::NC3];
 #pragma unroll
-    for (int K = 0; K < 2; ++K)
+    for (int K = 0; K < G::N3; ++K)
 #pragma unroll
-      for (int c = 0; c < 2; ++c)
+      for (int c = 0; c < G::NC3; ++c)
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-          const u32x2 lo = *reinterpret_cast<const u32x2 *>(W3 + (K * 384 + c * 16 + i * 64) * 16);
-          const u32x2 hi = *reinterpret_cast<const u32x2 *>(W3 + (K * 384 + 192 + c * 16 + i * 64) * 16);
+          const u32x2 lo = *reinterpret_cast<const u32x2 *>(W3 + (K * W3K + c * 16 + i * 64) * 16);
+          const u32x2 hi = *reinterpret_cast<const u32x2 *>(W3 + (K * W3K + W3H + c * 16 + i * 64) * 16);
           w3[K][c].p[i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
         }
     prime_range(W1, nh);
@@ -256,40 +314,58 @@ __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
     head();
     for (int t = 0; t < a.T; ++t) {
       __syncthreads();  // observation t complete
-      products<NK1 - NH>(acc, ring, xrow + nh * KBYTES, W1 + (size_t)nh * (2 * 8 * 192), nk1 - nh);
+      {
+        // (sums of their own, like the output layer's below)
+        typename G::Acc head_sums[G::NACC];
+#pragma unroll
+        for (int j = 0; j < G::NACC; ++j) head_sums[j] = acc[j];
+        clear();
+        products<G, NK1 - NH>(acc, ring, xrow + nh * G::KBYTES, W1 + (size_t)nh * G::BLOCK, nk1 - nh);
+#pragma unroll
+        for (int j = 0; j < G::NACC; ++j) acc[j] += head_sums[j];
+      }
       addresses();
+      activate(ldsBias, [&](int u) { return G::unit(W2, NL + u); });
 #pragma unroll
-      for (int u = 0; u < PU; ++u) fetch_unit(ring[u], W2, NL + u);
-      activate(ldsBias);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        O::store4<true>(ldsH + row * HP + O::off(64 * w + 16 * j + 4 * kq), acc[j][0], acc[j][1], acc[j][2], acc[j][3]);
+      for (int m = 0; m < G::NG; ++m)
+        O::store4<true>(ldsH + row * HP + O::off(64 * w + G::feature(m, part)), G::get(acc, m, 0), G::get(acc, m, 1), G::get(acc, m, 2),
+                        G::get(acc, m, 3));
       __syncthreads();  // first hidden layer complete, input tile free
       clear();
-      products2(acc, ring, hrow, own, W2);
-      // Output layer, from registers: the eight values a lane holds of 32 features are an operand of the transposed product
-      // in another order of its inputs.  Each wavefront adds up its own features for all outputs.
-      prime_range(W1, nh);
-      activate(ldsBias + 256);
-      f32x4 o[2][2];  // (one sum over both halves leaves a larger error: 3.16e-7 in the 2-norm of the means for 3.06e-7)
+      products2<G>(acc, ring, hrow, own, W2);
+      // Output layer, from registers: the eight values a lane holds of two groups of features are an operand of the
+      // transposed product in another order of its inputs.  Each wavefront adds up its own features for all outputs.
+      const int last_head = max(nh - 1, 0);
+      activate(ldsBias + 256, [&](int u) { return G::unit(W1, NH > 0 ? u : G::NACC * min(u / G::NACC, last_head) + u % G::NACC); });
+      // (each block's sums start at zero and are added to the others afterwards: one chain over all leaves a larger error, 16
+      // envs, 2-norm of the means 3.16e-7 for 3.06e-7)
+      typename G::Acc o[G::NC3];
 #pragma unroll
-      for (int K = 0; K < 2; ++K) {
+      for (int K = 0; K < G::N3; ++K) {
         float v[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = acc[2 * K + (i >> 2)][i & 3];
+        for (int i = 0; i < 8; ++i) v[i] = G::get(acc, 2 * K + (i >> 2), i & 3);
         bf16x8 xs[3];
         split3<true>(v, xs);
         Blk3 xv;
 #pragma unroll
         for (int i = 0; i < 3; ++i) xv.p[i] = __builtin_bit_cast(u32x4, xs[i]);
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          o[K][c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-          mma16(w3[K][c], xv, o[K][c]);
+        for (int c = 0; c < G::NC3; ++c) {
+          typename G::Acc p;
+          G::clear(p);
+          G::mma(w3[K][c], xv, p);
+          o[c] = K == 0 ? p : o[c] + p;
         }
       }
+      float *plane = planes + w * PLANE + row * MUP;
 #pragma unroll
-      for (int c = 0; c < 2; ++c) *reinterpret_cast<f32x4 *>(planes + w * PLANE + row * MUP + 16 * c + 4 * kq) = o[0][c] + o[1][c];
+      for (int m = 0; m < (E == 16 ? 2 : 4); ++m) {
+        f32x4 v;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = o[E == 16 ? m : 0][(E == 16 ? 0 : 4 * m) + i];
+        *reinterpret_cast<f32x4 *>(plane + G::feature(m, part)) = v;
+      }
       __syncthreads();  // means and the market columns of observation t + 1 complete
       if (t + 1 < a.T) head();
     }
@@ -297,7 +373,6 @@ __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
   }
 
   // ------------------------------------------------------------------ the envs
-  __builtin_amdgcn_s_setprio(3);
   Tr trade(ldsH, D);
   trade.terms = ldsTerms;
   const int et = tid - 64 * NM, e = et / TPE, tl = et & (TPE - 1), ew = w - NM;
@@ -412,6 +487,7 @@ __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
     __syncthreads();  // input tile free
     emit_market(obs_next);
     __syncthreads();  // means complete, the hidden tile is free
+    __builtin_amdgcn_s_setprio(3);  // (from here to the next observation the network can wait, elsewhere the envs)
     float a_raw[ND], mu[ND];
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
@@ -443,6 +519,7 @@ __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
 #pragma unroll
     for (int i = 0; i < ND; ++i) pn[i] = po[i];
     put_cash(obs_next);
+    __builtin_amdgcn_s_setprio(0);
   }
   settle(a.T - 1);
 #pragma unroll
@@ -458,39 +535,53 @@ __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
   }
 }
 
-}  // namespace
-
-// Up to a workgroup for each of the 256 compute units; with two rounds of them, 32 envs per workgroup take as long (8192 envs
-// 20.4 us a step against 20.7, 16384 37.9 against 39.5, 5120 17.5 against 20.7).
-bool fused_few_envs(const pr_config &c) { return c.mlp_dtype == PR_MLP_F32 && c.n_envs <= 256 * E; }
-
-// LDS of the kernel; the input tile has whole blocks of 32 inputs.
-size_t fused_f32_lds_bytes(const pr_config &c) {
-  const int S = 1 + 2 * c.n_stocks + c.n_stocks * c.n_ind;
-  return (size_t)E * (input_pitch((S + 15) / 16) + HP) + ((size_t)NM * PLANE + (2 * 256 + 32)) * 4 + (size_t)E * 32 * 8 + (size_t)NM * NL * 3072;
+template <int E>
+size_t lds_bytes(int S) {
+  using G = Geometry<E>;
+  return (size_t)E * (input_pitch<E>(S) + HP) + ((size_t)NM * G::PLANE + (2 * 256 + 32)) * 4 + (size_t)E * 32 * 8 + (size_t)NM * G::NL * 3072;
 }
 
-hipError_t launch_rollout_fused_f32(hipStream_t st, const pr_config &c, const EnvDims &d, const EnvState &s,
-                                    const float *price, const float *ind, const PackedNet &actor, int32_t envs_per_agent,
-                                    int32_t T, const float *noise, const pr_buffers &out) {
+template <int E, int NK1, int NH>
+hipError_t launch_inst(hipStream_t st, const F32Args &a, size_t lds) {
+  constexpr auto kern = rollout_f32_kernel<E, NK1, NH>;
+  const hipError_t e = allow_full_lds<kern>();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(a.d.N / E)), dim3(NT), lds, st, a);
+  return hipGetLastError();
+}
+
+template <int E, int NK1, int NH>
+hipError_t launch_geometry(hipStream_t st, F32Args a) {
+  const EnvDims &d = a.d;
+  a.xpitch = input_pitch<E>(d.S);
+  const size_t lds = lds_bytes<E>(d.S);
+  if (d.N % E || a.envs_per_agent % E || trade_lds(E, true, d.D) > (size_t)E * HP || lds > (size_t)kMaxLdsBytes) return hipErrorInvalidValue;
+  constexpr int KIN = Geometry<E>::KIN;
+  // straight-line layer 1 for the blocks of the named workloads
+  if ((d.S + KIN - 1) / KIN == NK1 && (d.D * d.K + d.D) / KIN == NH) return launch_inst<E, NK1, NH>(st, a, lds);
+  return launch_inst<E, 0, 0>(st, a, lds);
+}
+
+// 16 envs up to a workgroup for each of the 256 compute units; beyond, the weights streamed once for 32 envs are worth
+// more (301 inputs, per step: 4096 envs 10.9 us against 14.1, 1024 8.2 against 13.0; 8192 in two rounds 21 against 17.2).
+bool sixteen(int N) { return N <= 256 * 16; }
+
+}  // namespace
+
+size_t fused_f32_lds_bytes(const pr_config &c) {
+  const int S = 1 + 2 * c.n_stocks + c.n_stocks * c.n_ind;
+  return sixteen(c.n_envs) ? lds_bytes<16>(S) : lds_bytes<32>(S);
+}
+
+hipError_t launch_rollout_fused_f32(hipStream_t st, const EnvDims &d, const EnvState &s, const float *price, const float *ind,
+                                    const PackedNet &actor, int32_t envs_per_agent, int32_t T, const float *noise,
+                                    const pr_buffers &out) {
   F32Args a;
   a.d = d, a.st = s, a.price = price, a.ind = ind, a.actor = actor, a.envs_per_agent = envs_per_agent, a.T = T;
-  a.xpitch = input_pitch(actor.nkb[0]);
   a.noise = noise, a.obs = out.obs, a.act_raw = out.act_raw, a.reward = out.reward, a.done = out.done, a.logp = out.logp;
   a.mu_out = out.mu, a.shares = out.shares;
-  if (actor.bf16 || actor.nkb[0] % 2 || actor.nkb[1] != 2 * NK2 || actor.nct[0] != 8 || actor.nct[2] != 1 || d.N % E || envs_per_agent % E)
-    return hipErrorInvalidValue;
-  const size_t lds = fused_f32_lds_bytes(c);
-  if (trade_lds(E, true, d.D) > (size_t)E * HP || lds > (size_t)kMaxLdsBytes) return hipErrorInvalidValue;
-  auto launch = [&](auto nk1, auto nh) {
-    constexpr auto kern = rollout_f32_kernel<decltype(nk1)::value, decltype(nh)::value>;
-    const hipError_t e = allow_full_lds<kern>();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(d.N / E)), dim3(NT), lds, st, a);
-    return hipGetLastError();
-  };
-  if (actor.nkb[0] == 20 && (d.D * d.K + d.D) / 32 == 8) return launch(std::integral_constant<int, 10>{}, std::integral_constant<int, 8>{});
-  return launch(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+  if (actor.bf16 || actor.nkb[0] % 2 || actor.nkb[1] != 16 || actor.nct[0] != 8 || actor.nct[2] != 1) return hipErrorInvalidValue;
+  return sixteen(d.N) ? launch_geometry<16, 10, 8>(st, a) : launch_geometry<32, 19, 16>(st, a);
 }
 
 }  // namespace pod

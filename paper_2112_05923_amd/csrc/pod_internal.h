@@ -186,12 +186,11 @@ hipError_t launch_rollout_fused(hipStream_t st, const pr_config &c, const EnvDim
                                 const float *price, const float *ind, const PackedNet &actor, int32_t envs_per_agent,
                                 int32_t T, const float *noise, const float *mu_forced, const pr_buffers &out);
 
-// The same with the actor for the few envs of an fp32 network (16 per workgroup).
-bool fused_few_envs(const pr_config &c);
+// The same with the actor for fp32 networks.
 size_t fused_f32_lds_bytes(const pr_config &c);
-hipError_t launch_rollout_fused_f32(hipStream_t st, const pr_config &c, const EnvDims &d, const EnvState &s,
-                                    const float *price, const float *ind, const PackedNet &actor, int32_t envs_per_agent,
-                                    int32_t T, const float *noise, const pr_buffers &out);
+hipError_t launch_rollout_fused_f32(hipStream_t st, const EnvDims &d, const EnvState &s, const float *price, const float *ind,
+                                    const PackedNet &actor, int32_t envs_per_agent, int32_t T, const float *noise,
+                                    const pr_buffers &out);
 
 // The stepwise schedule of small networks: all T steps in one launch, state and network on the compute units.
 bool small_supported(const pr_config &c);
