@@ -183,12 +183,15 @@ struct RawM {  // m- (n-) contiguous operand: [slot][8] pairs
 // instructions of 32 cycles and about 180 vector instructions of 4 cycles (the splits) per 16 k; one after the other
 // they take 1500 cycles, so the split of the next 16 k is interleaved with the products of the present one, seven or
 // eight vector instructions behind each matrix instruction.
-// kw = 8: a share of at most four 16-deep steps at a time, all requested at once; what counts is one memory round trip.
-template <int KW, Kind KIND, bool SUMS, bool GATHER>
+// kw = 8: a share of at most SLOTS 16-deep steps at a time, all requested at once; what counts is one memory round trip.
+// SLOTS = 4 asks for four in any case (a branch around a request makes the compiler wait for all of them before the
+// first product: 28.8 us for 26.7 at 1024 samples x 512 units).  A request is 32 scattered lines, though, and where no
+// share is deeper than two steps the ones nobody uses cost more than that: SLOTS = 2 asks only for what is there (300
+// samples x 256 units, launches 4 and 5 together 16.5 us for 20.2; 4096 x 128, 23.3 for 28.4).
+template <int KW, int SLOTS, Kind KIND, bool SUMS, bool GATHER>
 __device__ inline void product(const Prob &g, int m0, int n0, int kbeg, int kend, int split, float *lds) {
   const int tid = threadIdx.x, lane = tid & 63, w = KW == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr bool A_K = KIND == DZ, B_K = A_K;
-  constexpr int SLOTS = KW == 1 ? 2 : 4;
   f32x16 acc[2][2];
 #pragma unroll
   for (int x = 0; x < 2; ++x)
@@ -304,11 +307,13 @@ __device__ inline void product(const Prob &g, int m0, int n0, int kbeg, int kend
         if (s + 1 < s1) step(I1{}, I0{}, s + 1);
       }
     } else {
-      for (int s = s0; s < s1; s += 4) {
+      for (int s = s0; s < s1; s += SLOTS) {
         load(I0{}, s + 1 < s1);
-        load(I1{}, s + 2 < s1);
-        load(I2{}, s + 3 < s1);
-        load(I3{}, s + 4 < s1);
+        if (SLOTS == 4 || s + 1 < s1) load(I1{}, s + 2 < s1);
+        if constexpr (SLOTS == 4) {
+          load(I2{}, s + 3 < s1);
+          load(I3{}, s + 4 < s1);
+        }
         auto take = [&](auto slot, int i) {
           if (s + i >= s1) return;
           split_slot(slot, I0{});
@@ -317,8 +322,10 @@ __device__ inline void product(const Prob &g, int m0, int n0, int kbeg, int kend
         };
         take(I0{}, 0);
         take(I1{}, 1);
-        take(I2{}, 2);
-        take(I3{}, 3);
+        if constexpr (SLOTS == 4) {
+          take(I2{}, 2);
+          take(I3{}, 3);
+        }
       }
     }
   }
@@ -446,7 +453,7 @@ constexpr size_t products_lds(int kw) { return kw == 1 ? 0 : (size_t)kw * (kTile
 
 // KW = 8: one tile per workgroup of eight wavefronts; KW = 1: four wavefronts, a tile each (neighbours in n: they read
 // the same rows of A)
-template <int KW>
+template <int KW, int SLOTS>
 __global__ __launch_bounds__(KW == 1 ? 256 : 512, 2) void products_kernel(ProbSet set) {
   extern __shared__ __align__(16) float lds[];
   int i = 0;
@@ -462,13 +469,13 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 512, 2) void products_kernel(ProbSe
   const int kbeg = split * g.k_chunk, kend = min(g.K, kbeg + g.k_chunk);
   const int m0 = tm * kTile, n0 = tn * kTile;
   if (g.kind == DZ) {
-    product<KW, DZ, false, false>(g, m0, n0, kbeg, kend, 0, lds);
+    product<KW, SLOTS, DZ, false, false>(g, m0, n0, kbeg, kend, 0, lds);
   } else if (tm == 0) {
-    if (g.gather) product<KW, DW, true, true>(g, m0, n0, kbeg, kend, split, lds);
-    else product<KW, DW, true, false>(g, m0, n0, kbeg, kend, split, lds);
+    if (g.gather) product<KW, SLOTS, DW, true, true>(g, m0, n0, kbeg, kend, split, lds);
+    else product<KW, SLOTS, DW, true, false>(g, m0, n0, kbeg, kend, split, lds);
   } else {
-    if (g.gather) product<KW, DW, false, true>(g, m0, n0, kbeg, kend, split, lds);
-    else product<KW, DW, false, false>(g, m0, n0, kbeg, kend, split, lds);
+    if (g.gather) product<KW, SLOTS, DW, false, true>(g, m0, n0, kbeg, kend, split, lds);
+    else product<KW, SLOTS, DW, false, false>(g, m0, n0, kbeg, kend, split, lds);
   }
 }
 
@@ -974,6 +981,7 @@ Plan make_plan(int B, int Hd, int D, int S, bool adam) {
 // C = products of `set`: fills in the tiling and launches
 hipError_t launch_products(hipStream_t st, ProbSet &set) {
   int64_t waves = 0;
+  int32_t deepest = 0;
   for (int i = 0; i < set.n; ++i) {
     Prob &p = set.p[i];
     p.tiles_n = (p.N + kTile - 1) / kTile;
@@ -982,6 +990,7 @@ hipError_t launch_products(hipStream_t st, ProbSet &set) {
     p.tiles = (int32_t)tiles;
     p.k_chunk = p.splits > 1 ? ((p.K + p.splits - 1) / p.splits + 31) / 32 * 32 : p.K;
     waves += tiles * p.splits;
+    deepest = std::max(deepest, p.k_chunk);
   }
   // a wavefront per tile when that gives most SIMDs one
   const bool own = waves >= kOwnTiles;
@@ -994,10 +1003,16 @@ hipError_t launch_products(hipStream_t st, ProbSet &set) {
     next += p.blocks;
   }
   if (own) {
-    hipLaunchKernelGGL(products_kernel<1>, dim3((unsigned)next), dim3(256), 0, st, set);
+    hipLaunchKernelGGL((products_kernel<1, 2>), dim3((unsigned)next), dim3(256), 0, st, set);
   } else {
-    LRN(allow_full_lds<products_kernel<8>>());
-    hipLaunchKernelGGL(products_kernel<8>, dim3((unsigned)next), dim3(512), products_lds(8), st, set);
+    const auto shared = [&](auto slots) {
+      constexpr auto *kern = products_kernel<8, decltype(slots)::value>;
+      const hipError_t e = allow_full_lds<kern>();
+      if (e == hipSuccess) hipLaunchKernelGGL(kern, dim3((unsigned)next), dim3(512), products_lds(8), st, set);
+      return e;
+    };
+    // (more than two steps of 16 for one of the eight wavefronts: see product)
+    LRN(deepest > 2 * 8 * 16 ? shared(std::integral_constant<int, 4>{}) : shared(std::integral_constant<int, 2>{}));
   }
   return hipGetLastError();
 }
