@@ -22,8 +22,8 @@
 // of the fp32 instruction's same work.  2-norm errors against 64 bits, relative to the fp32 instructions' (batches from
 // 256 to 32768, 64 to 512 units): gW1 0.72, gW2 0.71, gW3 0.89, gb1 0.91, the others as before.
 //
-// Measured (301-512-512 networks): a step at batch 1024 93 us (315 us as 38 launches); gradients at 15000 samples with
-// 256 hidden units 356 us (753 us).
+// Measured (301-512-512 networks): a step at batch 1024 92 us (315 us as 38 launches); gradients at 15000 samples with
+// 256 hidden units 316 us (753 us).
 #include <math.h>
 
 #include <algorithm>
@@ -482,138 +482,179 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 512, 2) void products_kernel(ProbSe
 // ------------------------------------------------------------------ forward
 // h = tanh(A W + b) on the fp32 matrix instructions, every element one accumulator over k in ascending order (an fp32
 // matrix instruction rounds after every k, so this is the fused multiply-add chain, the same bits for every tile shape
-// and batch size).  The split products above would take 6/16 of the matrix time; here they have not been tried.
-// A workgroup of eight wavefronts owns TM rows x 64 columns: wavefront w rows [16 (w % WM), + 16), NB column blocks of
-// 16.  Slices of 64 k go through LDS k-major (pitches that put the four k of an instruction on different banks), two
-// slices ahead in registers.  Bound by the fp32 matrix rate (64 flop per SIMD and cycle) once a launch is long enough;
-// at 1024 rows by its memory round trips.
+// and batch size).
+// A wavefront owns 16 TX rows x 16 TY columns and reads its operands straight from global memory into registers, DEPTH - 1
+// stages of 16 k ahead: no LDS and no barrier, so a SIMD's matrix unit has work whenever one of its wavefronts does.
+// Bound by the fp32 matrix rate where a launch is long (32 cycles an instruction: 27 us for the first layer of 15000
+// samples, 271 inputs and 256 units; it takes 62, the tanh 5 of it, where slices through LDS with a barrier each took 80);
+// otherwise by requests, of which a compute unit takes one in about 24 cycles, and by the round trips at either end.
+// Three shapes (both layers together, us; slices through LDS in brackets):
+//                                             2 x 4    1 x 4    1 x 1
+//   15000 samples x 256 units (7504 tiles)      115      140      213    (147)
+//   3000 x 512 (3008)                            80       77      120     (83)
+//   1024 x 512 (1024)                                   30.3     45.2    (32.1)
+//   1024 x 256 (512)                                    22.9     22.1
+//   300 x 256 (152 tiles of 16 x 64)                    17.9     12.0    (12.3)
+// 2 x 4 asks for 6 pieces of memory an instruction group of 32, 1 x 4 for 5 a group of 16, 1 x 1 for 5 a group of 4; with
+// few tiles it is the length of one wavefront's chain that counts.
 struct FwdProb {
   const float *A, *W, *bias;
   float *C;
   int64_t lda;
-  int32_t K;
 };
 struct FwdArgs {
-  FwdProb p[2];             // actor, critic: blockIdx.y
+  FwdProb p[2];             // actor, critic
   const int32_t *gather;    // rows of A, or null
-  int32_t M, N, ldc, tiles_n, tiles;
+  int32_t M, N, K, ldc, tiles_n, tiles;  // tiles: of both networks; a row of tiles is the actor's and then the critic's
   // rows copied on the side by the blocks behind the tiles: W2 of each network to rows of ldc
   const float *copy_src[2];
   float *copy_dst[2];
-  int32_t copy_rows;
+  int32_t first_copy, copy_rows;
 };
+constexpr int kFwdWaves = 4;
 
-template <int TM>
-__global__ __launch_bounds__(512, 4) void forward_kernel(FwdArgs a) {
-  constexpr int KS = 64, WM = TM / 16, NB = WM / 2;  // wavefronts along m; 8 / WM along n, NB blocks of 16 each
-  constexpr int PA = TM + 16, PB = 80;               // LDS row pitches: 16 or 48 mod 64
-  constexpr int RA = TM * KS / 4 / 512;              // 16-byte groups of A per thread and slice
-  __shared__ __align__(16) float lds[2 * KS * (PA + PB)];
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const FwdProb &g = a.p[blockIdx.y];
-  const int per = (a.tiles + 7) >> 3, local = (int)blockIdx.x;
-  if (local >= 8 * per) {
-    const int row = (local - 8 * per) * 8 + w;
-    if (row < a.copy_rows)
+// TY = 4: column block y is columns 4 j + y, so that a lane's weights of a row are one request; TY = 1: one block of 16.
+template <int TX, int TY, int DEPTH>
+__global__ __launch_bounds__(64 * kFwdWaves, 2) void forward_kernel(FwdArgs a) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  if ((int)blockIdx.x >= a.first_copy) {
+    const int row = ((int)blockIdx.x - a.first_copy) * kFwdWaves + w, net = row >= a.copy_rows, r = row - net * a.copy_rows;
+    if (row < 2 * a.copy_rows)
       for (int k = lane; k < a.copy_rows; k += 64)
-        a.copy_dst[blockIdx.y][(int64_t)row * a.ldc + k] = a.copy_src[blockIdx.y][(int64_t)row * a.copy_rows + k];
+        a.copy_dst[net][(int64_t)r * a.ldc + k] = a.copy_src[net][(int64_t)r * a.copy_rows + k];
     return;
   }
-  const int t = (local & 7) * per + (local >> 3);  // neighbouring tiles (the same rows of A) on one XCD
+  // neighbouring tiles (the same rows of A) in one workgroup and on one XCD
+  const int per = a.first_copy >> 3, t = (((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3)) * kFwdWaves + w;
   if (t >= a.tiles) return;
-  const int tm = t / a.tiles_n, m0 = tm * TM, n0 = (t - tm * a.tiles_n) * 64;
-  const int K = g.K, N = a.N;
-  const int mi = 16 * (w % WM), ni = 16 * NB * (w / WM);
-  const int j = lane & 15, q = lane >> 4;
-  // staging of A: row tid % TM, k groups of four
-  const float *pa;
-  {
-    int r = min(m0 + tid % TM, a.M - 1);
+  const int tm = t / (2 * a.tiles_n), tr = t - tm * 2 * a.tiles_n, net = tr >= a.tiles_n;
+  const int m0 = 16 * TX * tm, n0 = 16 * TY * (tr - net * a.tiles_n);
+  const FwdProb &g = a.p[net];
+  const int N = a.N, K = a.K, q = lane >> 4, j = lane & 15;
+  // A: lane (row j, q) reads k 4 q .. 4 q + 3 of a stage; swaps between the lane quarters give the operands of the
+  // stage's four instructions.  W: row 4 i + q for instruction i.  (N is a multiple of 32.)
+  typedef std::conditional_t<TY == 4, f32x4, float> Cols;
+  typedef std::conditional_t<TY == 4, f32x4u, float> ColsU;
+  const auto column = [](const Cols &c, int y) {
+    if constexpr (TY == 4) return c[y];
+    else return c;
+  };
+  const float *pa[TX];
+#pragma unroll
+  for (int x = 0; x < TX; ++x) {
+    int r = min(m0 + 16 * x + j, a.M - 1);
     if (a.gather) r = a.gather[r];
-    pa = g.A + (int64_t)r * g.lda;
+    pa[x] = g.A + (int64_t)r * g.lda;
   }
-  const int kq = tid / TM;  // first k group of this thread; the next ones are 512 / TM further
-  // of W: four columns of rows wk, wk + 32 of a slice (N is a multiple of 32)
-  const int wn = min(n0 + 4 * (tid & 15), N - 4), wk = tid >> 4;
-  f32x4 ra[2][RA], rb[2][2];
-  auto load = [&](auto slot, int k0) {
-    constexpr int SL = decltype(slot)::value;
+  const int n = n0 + TY * j, nc = min(n, N - TY);
+  const float *W = g.W;
+  const uint32_t wo = (uint32_t)(q * N + nc);
+  const Cols bias = *reinterpret_cast<const ColsU *>(g.bias + nc);
+  f32x4 acc[TX][TY];
 #pragma unroll
-    for (int i = 0; i < RA; ++i) {
-      // (a group that crosses the end is read as the four floats that end there; sorted out when it is stored)
-      const int k = k0 + 4 * (kq + i * (512 / TM));
-      if (K >= 4) ra[SL][i] = *reinterpret_cast<const f32x4u *>(pa + min(k, K - 4));
-      else ra[SL][i] = f32x4{0.0f, pa[0], pa[1], pa[2]};  // (rows of three: one stock without indicators)
-    }
+  for (int x = 0; x < TX; ++x)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-      rb[SL][i] = *reinterpret_cast<const f32x4u *>(g.W + (int64_t)min(k0 + wk + 32 * i, K - 1) * N + wn);
-  };
-  auto store = [&](auto slot, int k0, float *buf) {
-    constexpr int SL = decltype(slot)::value;
+    for (int y = 0; y < TY; ++y) acc[x][y] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  f32x4 va[DEPTH][TX], la[TX];
+  Cols vb[DEPTH][4], lb[4];
+  const int full = K >> 4;
+  if (K & 15) {  // what is left behind the full stages: requested first, used last
 #pragma unroll
-    for (int i = 0; i < RA; ++i) {
-      const int kl = 4 * (kq + i * (512 / TM)), k = k0 + kl;
-      f32x4 v = ra[SL][i];
-      if (k + 4 > K) {
-        const int sh = k + 4 - K;
-        v = f32x4{sh == 1 ? v[1] : sh == 2 ? v[2] : sh == 3 ? v[3] : 0.0f, sh == 1 ? v[2] : sh == 2 ? v[3] : 0.0f,
-                  sh == 1 ? v[3] : 0.0f, 0.0f};
-      }
-      float *dst = buf + kl * PA + tid % TM;
-      dst[0] = v[0], dst[PA] = v[1], dst[2 * PA] = v[2], dst[3 * PA] = v[3];
-    }
-    float *wdst = buf + KS * PA + wk * PB + 4 * (tid & 15);
+    for (int x = 0; x < TX; ++x)
 #pragma unroll
-    for (int i = 0; i < 2; ++i) *reinterpret_cast<f32x4 *>(wdst + 32 * i * PB) = rb[SL][i];
-    if (k0 + KS > K) {  // (rows past the end are zeros like those behind A: zero times an infinite weight would be NaN)
+      for (int i = 0; i < 4; ++i) la[x][i] = pa[x][min(16 * full + 4 * q + i, K - 1)];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        if (k0 + wk + 32 * i >= K) *reinterpret_cast<f32x4 *>(wdst + 32 * i * PB) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    }
-  };
-  using I0 = std::integral_constant<int, 0>;
-  using I1 = std::integral_constant<int, 1>;
-  f32x4 acc[NB];
-#pragma unroll
-  for (int y = 0; y < NB; ++y) acc[y] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  const int slices = (K + KS - 1) / KS;
-  auto multiply = [&](const float *buf) {
-    const float *A = buf + q * PA + mi + j, *Bp = buf + KS * PA + q * PB + ni + j;
-#pragma unroll
-    for (int i = 0; i < KS / 4; ++i) {
-      const float av = A[4 * i * PA];
-#pragma unroll
-      for (int y = 0; y < NB; ++y) acc[y] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, Bp[4 * i * PB + 16 * y], acc[y], 0, 0, 0);
-    }
-  };
-  float *buf0 = lds, *buf1 = lds + KS * (PA + PB);
-  load(I0{}, 0);
-  load(I1{}, KS);
-  for (int s = 0; s < slices; s += 2) {
-    store(I0{}, s * KS, buf0);
-    load(I0{}, (s + 2) * KS);
-    __syncthreads();
-    multiply(buf0);
-    if (s + 1 < slices) {
-      store(I1{}, (s + 1) * KS, buf1);
-      load(I1{}, (s + 3) * KS);
-      __syncthreads();
-      multiply(buf1);
-    }
+    for (int i = 0; i < 4; ++i)
+      lb[i] = *reinterpret_cast<const ColsU *>(W + (int64_t)min(16 * full + 4 * i + q, K - 1) * N + nc);
+    __builtin_amdgcn_sched_barrier(0);
   }
+  auto request = [&](int slot, int stage) {  // (past the last one: the last once more)
+    const int k = 16 * min(stage, full - 1);
 #pragma unroll
-  for (int y = 0; y < NB; ++y) {
-    const int n = n0 + ni + 16 * y + j;
-    if (n < N) {
-      const float b = g.bias[n];
+    for (int x = 0; x < TX; ++x) va[slot][x] = *reinterpret_cast<const f32x4u *>(pa[x] + (k + 4 * q));
+    const float *row = W + (int64_t)k * N;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) vb[slot][i] = *reinterpret_cast<const ColsU *>(row + (int64_t)(4 * i) * N + wo);
+  };
+  auto multiply = [&](const f32x4 (&av)[TX], const Cols (&bv)[4]) {
+    float op[TX][4];
+#pragma unroll
+    for (int x = 0; x < TX; ++x) {
+      uint32_t u[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int m = m0 + mi + 4 * q + i;
-        if (m < a.M) g.C[(int64_t)m * a.ldc + n] = tanhf(acc[y][i] + b);
+        const float f = av[x][i];
+        u[i] = __builtin_bit_cast(uint32_t, f);
+      }
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const auto s = __builtin_amdgcn_permlane32_swap(u[p], u[2 + p], false, false);
+        u[p] = s[0], u[2 + p] = s[1];
+      }
+#pragma unroll
+      for (int p = 0; p < 4; p += 2) {
+        const auto s = __builtin_amdgcn_permlane16_swap(u[p], u[p + 1], false, false);
+        const uint32_t s0 = s[0], s1 = s[1];
+        op[x][p] = __builtin_bit_cast(float, s0), op[x][p + 1] = __builtin_bit_cast(float, s1);
       }
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int x = 0; x < TX; ++x)
+#pragma unroll
+        for (int y = 0; y < TY; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(op[x][i], column(bv[i], y), acc[x][y], 0, 0, 0);
+  };
+  if (full > 0) {
+#pragma unroll
+    for (int i = 0; i < DEPTH - 1; ++i) request(i, i);
+    // (rounds of DEPTH stages, and what is left of one behind the loop: with the way out inside it the compiler waits for
+    // everything requested at its head)
+    int s = 0;
+    for (; s + DEPTH <= full; s += DEPTH) {
+#pragma unroll
+      for (int i = 0; i < DEPTH; ++i) {
+        request((i + DEPTH - 1) % DEPTH, s + i + DEPTH - 1);
+        if (TX == 1) __builtin_amdgcn_sched_barrier(0);
+        multiply(va[i], vb[i]);
+        if (TX > 1) {
+#pragma unroll
+          for (int z = 0; z < TX + 4; ++z) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 4 * TX * TY / (TX + 4), 0);  // matrix instructions
+            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                       // a request
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < DEPTH - 1; ++i)
+      if (s + i < full) multiply(va[i], vb[i]);
   }
+  if (K & 15) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {  // zeros behind the end
+#pragma unroll
+      for (int x = 0; x < TX; ++x)
+        if (16 * full + 4 * q + i >= K) la[x][i] = 0.0f;
+      if (16 * full + 4 * i + q >= K) lb[i] = Cols{};
+    }
+    multiply(la, lb);
+  }
+#pragma unroll
+  for (int x = 0; x < TX; ++x)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int m = m0 + 16 * x + 4 * q + i;
+      Cols c;
+      if constexpr (TY == 4) {
+#pragma unroll
+        for (int y = 0; y < 4; ++y) c[y] = tanhf(acc[x][y][i] + bias[y]);
+      } else {
+        c = tanhf(acc[x][0][i] + bias);
+      }
+      if (m < a.M && n < N) *reinterpret_cast<Cols *>(g.C + (int64_t)m * a.ldc + n) = c;
+    }
 }
 
 // ------------------------------------------------------------------ output layers and losses
@@ -1080,22 +1121,29 @@ hipError_t launch_ppo(hipStream_t st, const pr_ppo_config &c, const float *obs, 
   };
   for (int layer = 0; layer < 2; ++layer) {
     FwdArgs f{};
-    f.gather = layer == 0 ? rows : nullptr, f.M = B, f.N = Hd, f.ldc = ld;
+    f.gather = layer == 0 ? rows : nullptr, f.M = B, f.N = Hd, f.K = layer == 0 ? S : Hd, f.ldc = ld;
     for (int i = 0; i < 2; ++i) {
       FwdProb &p = f.p[i];
-      if (layer == 0) p.A = obs, p.lda = S, p.K = S, p.W = net[i]->W1, p.bias = net[i]->b1, p.C = h1[i];
-      else p.A = h1[i], p.lda = ld, p.K = Hd, p.W = net[i]->W2, p.bias = net[i]->b2, p.C = h2[i];
+      if (layer == 0) p.A = obs, p.lda = S, p.W = net[i]->W1, p.bias = net[i]->b1, p.C = h1[i];
+      else p.A = h1[i], p.lda = ld, p.W = net[i]->W2, p.bias = net[i]->b2, p.C = h2[i];
       f.copy_src[i] = net[i]->W2, f.copy_dst[i] = w2[i];
     }
     f.copy_rows = layer == 1 && plan.padded ? Hd : 0;
-    f.tiles_n = (Hd + 63) / 64;
-    // 32-row tiles while 64-row ones would leave compute units without two workgroups
-    const int TM = 2 * (int64_t)((B + 63) / 64) * f.tiles_n >= 512 ? 64 : 32;
-    f.tiles = (B + TM - 1) / TM * f.tiles_n;
-    const dim3 grid((unsigned)((f.tiles + 7) / 8 * 8 + (f.copy_rows + 7) / 8), 2);
-    if (TM == 64) hipLaunchKernelGGL(forward_kernel<64>, grid, dim3(512), 0, st, f);
-    else hipLaunchKernelGGL(forward_kernel<32>, grid, dim3(512), 0, st, f);
-    LRN(hipGetLastError());
+    const auto launch = [&](auto kern, int tx, int ty) {
+      f.tiles_n = (Hd + 16 * ty - 1) / (16 * ty);
+      const int64_t tiles = (int64_t)((B + 16 * tx - 1) / (16 * tx)) * 2 * f.tiles_n;
+      if (tiles > (1 << 30)) return hipErrorInvalidValue;
+      f.tiles = (int32_t)tiles;
+      f.first_copy = (int32_t)(((tiles + kFwdWaves - 1) / kFwdWaves + 7) / 8 * 8);
+      const int blocks = f.first_copy + (2 * f.copy_rows + kFwdWaves - 1) / kFwdWaves;
+      hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * kFwdWaves), 0, st, f);
+      return hipGetLastError();
+    };
+    // four tiles of 16 x 64 for every SIMD, and one for most of them: see forward_kernel
+    const int64_t tiles = (int64_t)((B + 15) / 16) * ((Hd + 63) / 64) * 2;
+    if (tiles >= 4096) LRN(launch(forward_kernel<2, 4, 4>, 2, 4));
+    else if (tiles >= 640) LRN(launch(forward_kernel<1, 4, 6>, 1, 4));
+    else LRN(launch(forward_kernel<1, 1, 8>, 1, 1));
   }
   ProbSet set{};
   HeadArgs h{};

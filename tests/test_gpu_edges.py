@@ -96,6 +96,14 @@ def test_learner_products_at_their_edges(B, D, K, Hd):
     np.testing.assert_allclose(parity.to_np(dstats), stats, rtol=2e-4, atol=1e-6)
 
 
+# the forward layers' three tiles (32 x 64, 16 x 64, 16 x 16): fewer k than a stage, no remainder, one of 5; fewer stages
+# than are requested ahead; rows that end inside a tile, half a tile of columns
+@pytest.mark.parametrize("B,D,K,Hd", [(11010, 3, 1, 160), (8195, 9, 2, 256), (5200, 5, 0, 96), (1000, 3, 1, 352),
+                                      (2049, 9, 2, 192), (33, 1, 0, 32), (19, 9, 2, 64)])
+def test_learner_forward_tiles(B, D, K, Hd):
+    test_learner_products_at_their_edges(B, D, K, Hd)
+
+
 # 16 / 8 / 4 envs per workgroup of the env step, one, two and four stocks per thread, a last workgroup that is not full, no indicators, indicator rows that are no multiple of four floats and ones beyond the prefetched groups;
 # episodes that end inside the rollout, and hardly any cash
 @pytest.mark.parametrize("N,D,K,cash0", [(35, 32, 17, 1e6), (33, 33, 3, 1e6), (16, 64, 1, 4e4), (3, 65, 4, 1e6), (17, 128, 0, 2e4), (9, 129, 1, 1e6), (8, 256, 9, 3e4), (5, 257, 5, 1e6),
