@@ -22,8 +22,8 @@
 // of the fp32 instruction's same work.  2-norm errors against 64 bits, relative to the fp32 instructions' (batches from
 // 256 to 32768, 64 to 512 units): gW1 0.72, gW2 0.71, gW3 0.89, gb1 0.91, the others as before.
 //
-// Measured (301-512-512 networks): a step at batch 1024 92 us (315 us as 38 launches); gradients at 15000 samples with
-// 256 hidden units 316 us (753 us).
+// Measured (301-512-512 networks): a step at batch 1024 84 us (315 us as 38 launches); gradients at 15000 samples with
+// 256 hidden units 285 us (753 us).
 #include <math.h>
 
 #include <algorithm>
@@ -497,75 +497,52 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 512, 2) void products_kernel(ProbSe
 //   300 x 256 (152 tiles of 16 x 64)                    17.9     12.0    (12.3)
 // 2 x 4 asks for 6 pieces of memory an instruction group of 32, 1 x 4 for 5 a group of 16, 1 x 1 for 5 a group of 4; with
 // few tiles it is the length of one wavefront's chain that counts.
-struct FwdProb {
-  const float *A, *W, *bias;
-  float *C;
-  int64_t lda;
-};
-struct FwdArgs {
-  FwdProb p[2];             // actor, critic
-  const int32_t *gather;    // rows of A, or null
-  int32_t M, N, K, ldc, tiles_n, tiles;  // tiles: of both networks; a row of tiles is the actor's and then the critic's
-  // rows copied on the side by the blocks behind the tiles: W2 of each network to rows of ldc
-  const float *copy_src[2];
-  float *copy_dst[2];
-  int32_t first_copy, copy_rows;
-};
-constexpr int kFwdWaves = 4;
+// An operand that is contiguous along k, lane (row j, q = lane / 16) with k 4 q .. 4 q + 3 of 16: swaps between the lane
+// quarters give the operands of the four instructions.
+__device__ inline void in_instruction_order(const f32x4 &v, float (&op)[4]) {
+  uint32_t u[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float f = v[i];
+    u[i] = __builtin_bit_cast(uint32_t, f);
+  }
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const auto s = __builtin_amdgcn_permlane32_swap(u[p], u[2 + p], false, false);
+    u[p] = s[0], u[2 + p] = s[1];
+  }
+#pragma unroll
+  for (int p = 0; p < 4; p += 2) {
+    const auto s = __builtin_amdgcn_permlane16_swap(u[p], u[p + 1], false, false);
+    const uint32_t s0 = s[0], s1 = s[1];
+    op[p] = __builtin_bit_cast(float, s0), op[p + 1] = __builtin_bit_cast(float, s1);
+  }
+}
 
+// acc += rows of A times columns of W [K, N], k ascending.  pa: this lane's rows; nc: its (first) column.
 // TY = 4: column block y is columns 4 j + y, so that a lane's weights of a row are one request; TY = 1: one block of 16.
-template <int TX, int TY, int DEPTH>
-__global__ __launch_bounds__(64 * kFwdWaves, 2) void forward_kernel(FwdArgs a) {
-  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  if ((int)blockIdx.x >= a.first_copy) {
-    const int row = ((int)blockIdx.x - a.first_copy) * kFwdWaves + w, net = row >= a.copy_rows, r = row - net * a.copy_rows;
-    if (row < 2 * a.copy_rows)
-      for (int k = lane; k < a.copy_rows; k += 64)
-        a.copy_dst[net][(int64_t)r * a.ldc + k] = a.copy_src[net][(int64_t)r * a.copy_rows + k];
-    return;
-  }
-  // neighbouring tiles (the same rows of A) in one workgroup and on one XCD
-  const int per = a.first_copy >> 3, t = (((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3)) * kFwdWaves + w;
-  if (t >= a.tiles) return;
-  const int tm = t / (2 * a.tiles_n), tr = t - tm * 2 * a.tiles_n, net = tr >= a.tiles_n;
-  const int m0 = 16 * TX * tm, n0 = 16 * TY * (tr - net * a.tiles_n);
-  const FwdProb &g = a.p[net];
-  const int N = a.N, K = a.K, q = lane >> 4, j = lane & 15;
-  // A: lane (row j, q) reads k 4 q .. 4 q + 3 of a stage; swaps between the lane quarters give the operands of the
-  // stage's four instructions.  W: row 4 i + q for instruction i.  (N is a multiple of 32.)
-  typedef std::conditional_t<TY == 4, f32x4, float> Cols;
-  typedef std::conditional_t<TY == 4, f32x4u, float> ColsU;
-  const auto column = [](const Cols &c, int y) {
-    if constexpr (TY == 4) return c[y];
-    else return c;
-  };
-  const float *pa[TX];
-#pragma unroll
-  for (int x = 0; x < TX; ++x) {
-    int r = min(m0 + 16 * x + j, a.M - 1);
-    if (a.gather) r = a.gather[r];
-    pa[x] = g.A + (int64_t)r * g.lda;
-  }
-  const int n = n0 + TY * j, nc = min(n, N - TY);
-  const float *W = g.W;
+template <int TY>
+using Cols = std::conditional_t<TY == 4, f32x4, float>;
+template <int TY>
+using ColsU = std::conditional_t<TY == 4, f32x4u, float>;
+
+// REST: K may be no multiple of 16.
+template <int TX, int TY, int DEPTH, bool REST>
+__device__ inline void stream_product(const float *const (&pa)[TX], const float *W, int N, int nc, int K, int lane,
+                                      f32x4 (&acc)[TX][TY]) {
+  const int q = lane >> 4;
   const uint32_t wo = (uint32_t)(q * N + nc);
-  const Cols bias = *reinterpret_cast<const ColsU *>(g.bias + nc);
-  f32x4 acc[TX][TY];
-#pragma unroll
-  for (int x = 0; x < TX; ++x)
-#pragma unroll
-    for (int y = 0; y < TY; ++y) acc[x][y] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   f32x4 va[DEPTH][TX], la[TX];
-  Cols vb[DEPTH][4], lb[4];
+  Cols<TY> vb[DEPTH][4], lb[4];
   const int full = K >> 4;
-  if (K & 15) {  // what is left behind the full stages: requested first, used last
+  if (REST && (K & 15)) {  // what is left behind the full stages: requested first, used last
 #pragma unroll
     for (int x = 0; x < TX; ++x)
 #pragma unroll
       for (int i = 0; i < 4; ++i) la[x][i] = pa[x][min(16 * full + 4 * q + i, K - 1)];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      lb[i] = *reinterpret_cast<const ColsU *>(W + (int64_t)min(16 * full + 4 * i + q, K - 1) * N + nc);
+      lb[i] = *reinterpret_cast<const ColsU<TY> *>(W + (int64_t)min(16 * full + 4 * i + q, K - 1) * N + nc);
     __builtin_amdgcn_sched_barrier(0);
   }
   auto request = [&](int slot, int stage) {  // (past the last one: the last once more)
@@ -574,36 +551,23 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void forward_kernel(FwdArgs a) {
     for (int x = 0; x < TX; ++x) va[slot][x] = *reinterpret_cast<const f32x4u *>(pa[x] + (k + 4 * q));
     const float *row = W + (int64_t)k * N;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) vb[slot][i] = *reinterpret_cast<const ColsU *>(row + (int64_t)(4 * i) * N + wo);
+    for (int i = 0; i < 4; ++i) vb[slot][i] = *reinterpret_cast<const ColsU<TY> *>(row + (int64_t)(4 * i) * N + wo);
   };
-  auto multiply = [&](const f32x4 (&av)[TX], const Cols (&bv)[4]) {
+  auto multiply = [&](const f32x4 (&av)[TX], const Cols<TY> (&bv)[4]) {
     float op[TX][4];
 #pragma unroll
-    for (int x = 0; x < TX; ++x) {
-      uint32_t u[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float f = av[x][i];
-        u[i] = __builtin_bit_cast(uint32_t, f);
-      }
-#pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        const auto s = __builtin_amdgcn_permlane32_swap(u[p], u[2 + p], false, false);
-        u[p] = s[0], u[2 + p] = s[1];
-      }
-#pragma unroll
-      for (int p = 0; p < 4; p += 2) {
-        const auto s = __builtin_amdgcn_permlane16_swap(u[p], u[p + 1], false, false);
-        const uint32_t s0 = s[0], s1 = s[1];
-        op[x][p] = __builtin_bit_cast(float, s0), op[x][p + 1] = __builtin_bit_cast(float, s1);
-      }
-    }
+    for (int x = 0; x < TX; ++x) in_instruction_order(av[x], op[x]);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int x = 0; x < TX; ++x)
 #pragma unroll
-        for (int y = 0; y < TY; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(op[x][i], column(bv[i], y), acc[x][y], 0, 0, 0);
+        for (int y = 0; y < TY; ++y) {
+          float b;
+          if constexpr (TY == 4) b = bv[i][y];
+          else b = bv[i];
+          acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(op[x][i], b, acc[x][y], 0, 0, 0);
+        }
   };
   if (full > 0) {
 #pragma unroll
@@ -631,29 +595,79 @@ __global__ __launch_bounds__(64 * kFwdWaves, 2) void forward_kernel(FwdArgs a) {
     for (int i = 0; i < DEPTH - 1; ++i)
       if (s + i < full) multiply(va[i], vb[i]);
   }
-  if (K & 15) {
+  if (REST && (K & 15)) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {  // zeros behind the end
 #pragma unroll
       for (int x = 0; x < TX; ++x)
         if (16 * full + 4 * q + i >= K) la[x][i] = 0.0f;
-      if (16 * full + 4 * i + q >= K) lb[i] = Cols{};
+      if (16 * full + 4 * i + q >= K) lb[i] = Cols<TY>{};
     }
     multiply(la, lb);
   }
+}
+
+struct FwdProb {
+  const float *A, *W, *bias;
+  float *C;
+  int64_t lda;
+};
+struct FwdArgs {
+  FwdProb p[2];             // actor, critic
+  const int32_t *gather;    // rows of A, or null
+  int32_t M, N, K, ldc, tiles_n, tiles;  // tiles: of both networks; a row of tiles is the actor's and then the critic's
+  // rows copied on the side by the blocks behind the tiles: W2 of each network to rows of ldc
+  const float *copy_src[2];
+  float *copy_dst[2];
+  int32_t first_copy, copy_rows;
+};
+constexpr int kFwdWaves = 4;
+
+template <int TX, int TY, int DEPTH>
+__global__ __launch_bounds__(64 * kFwdWaves, 2) void forward_kernel(FwdArgs a) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  if ((int)blockIdx.x >= a.first_copy) {
+    const int row = ((int)blockIdx.x - a.first_copy) * kFwdWaves + w, net = row >= a.copy_rows, r = row - net * a.copy_rows;
+    if (row < 2 * a.copy_rows)
+      for (int k = lane; k < a.copy_rows; k += 64)
+        a.copy_dst[net][(int64_t)r * a.ldc + k] = a.copy_src[net][(int64_t)r * a.copy_rows + k];
+    return;
+  }
+  // neighbouring tiles (the same rows of A) in one workgroup and on one XCD
+  const int per = a.first_copy >> 3, t = (((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3)) * kFwdWaves + w;
+  if (t >= a.tiles) return;
+  const int tm = t / (2 * a.tiles_n), tr = t - tm * 2 * a.tiles_n, net = tr >= a.tiles_n;
+  const int m0 = 16 * TX * tm, n0 = 16 * TY * (tr - net * a.tiles_n);
+  const FwdProb &g = a.p[net];
+  const int N = a.N, K = a.K, q = lane >> 4, j = lane & 15;
+  const float *pa[TX];
+#pragma unroll
+  for (int x = 0; x < TX; ++x) {
+    int r = min(m0 + 16 * x + j, a.M - 1);
+    if (a.gather) r = a.gather[r];
+    pa[x] = g.A + (int64_t)r * g.lda;
+  }
+  const int n = n0 + TY * j, nc = min(n, N - TY);  // (N is a multiple of 32)
+  const Cols<TY> bias = *reinterpret_cast<const ColsU<TY> *>(g.bias + nc);
+  f32x4 acc[TX][TY];
+#pragma unroll
+  for (int x = 0; x < TX; ++x)
+#pragma unroll
+    for (int y = 0; y < TY; ++y) acc[x][y] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  stream_product<TX, TY, DEPTH, true>(pa, g.W, N, nc, K, lane, acc);
 #pragma unroll
   for (int x = 0; x < TX; ++x)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int m = m0 + 16 * x + 4 * q + i;
-      Cols c;
+      Cols<TY> c;
       if constexpr (TY == 4) {
 #pragma unroll
         for (int y = 0; y < 4; ++y) c[y] = tanhf(acc[x][y][i] + bias[y]);
       } else {
         c = tanhf(acc[x][0][i] + bias);
       }
-      if (m < a.M && n < N) *reinterpret_cast<Cols *>(g.C + (int64_t)m * a.ldc + n) = c;
+      if (m < a.M && n < N) *reinterpret_cast<Cols<TY> *>(g.C + (int64_t)m * a.ldc + n) = c;
     }
 }
 
@@ -677,17 +691,16 @@ constexpr int kHeadLdsD = 1024;  // most action components whose means a workgro
 
 // 16 samples of one network (blockIdx.y) per workgroup: output layer on the fp32 matrix cores, loss terms and the
 // gradient of the last pre-activation (32 lanes per sample), then that gradient through W3' and the tanh of the second
-// hidden layer.  Bound by the memory round trips of its stages: everything a stage reads that does not depend on the one
-// before is requested at the start.  Four wavefronts per SIMD spill 21 to 33 registers for it; two spill none, which
-// gives a step at batch 1024 89.3 us for 92.6 and at 15000 (256 units) 339 for 336.
-constexpr int kHeadWaves = 8;
-constexpr int head_slice(int NG, int KS) { return KS * (32 + NG + 16); }  // floats
-// NG: columns of the output layer at a time, KS: k per slice
-template <bool MU_LDS, int NG, int KS>
+// hidden layer.  Bound by the round trips of its stages: what the last one reads is requested at the start, and the
+// output layer, one accumulator per mean over k in ascending order, is a stream of its operands without a barrier
+// (1024 samples x 512 units 11.6 us, 15000 x 256 32.8; with slices of k through LDS, a barrier each, and one feature of
+// four samples to a lane of the last stage, four times the requests, 19.1 and 59.4).  Three workgroups on a compute unit
+// instead of two, 80 registers and three stages ahead: 12.2 and 30.6 us.
+constexpr int kHeadWaves = 8, kHeadDepth = 4;
+template <bool MU_LDS>
 __global__ __launch_bounds__(64 * kHeadWaves, 4) void head_kernel(HeadArgs a) {
   extern __shared__ __align__(16) float lds[];
-  float *s_z = lds;                                 // slices of h2 and W3, k-major
-  float *s_red = lds + head_slice(NG, KS);          // [16][4]
+  float *s_red = lds;                               // [16][4]
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int b0 = blockIdx.x * kHeadRows, net = a.net0 + blockIdx.y;
   const int B = a.B, Hd = a.Hd, D = net == 1 ? 1 : a.D;  // (D: outputs of the network)
@@ -701,67 +714,56 @@ __global__ __launch_bounds__(64 * kHeadWaves, 4) void head_kernel(HeadArgs a) {
   {
     // outputs of the tile (means, or values): [16][Dp] in LDS, or the rows of the scratch
     const int Dp = MU_LDS ? D | 1 : D;
-    float *mu = MU_LDS ? lds + head_slice(NG, KS) + 16 * 4 : a.mu + (int64_t)b0 * D + (net == 1 ? (int64_t)B * a.D : 0);
+    float *mu = MU_LDS ? lds + 16 * 4 : a.mu + (int64_t)b0 * D + (net == 1 ? (int64_t)B * a.D : 0);
     const int j = lane & 15, q = lane >> 4;
-    const float logp_old = a.logp_old[r], A = a.adv[r], ret = a.ret[r];
-    const float act0 = a.act[r * a.D + min(sub, a.D - 1)];  // the first 32 components, requested early
-    // what the last stage reads for this wavefront's first feature tiles of 16 (columns d = 4 c + q < 32)
-    constexpr int PT = 2;
-    float yw[PT][8], hv[PT][4];
+    const float *h2_row = h2 + min(b0 + j, B - 1) * ld;
+    // The last stage forms (dz3 W3')' tiles of 16 features x 16 samples, so that a lane has four features in a row of
+    // one sample.  W3: components 4 q .. 4 q + 3 of 16 of feature row j (D < 4: from the first lane quarter).
+    auto request_w3 = [&](int t, int d0) {
+      const float *w3 = W3 + (int64_t)(16 * t + j) * D;
+      f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (D >= 4) {
+        v = *reinterpret_cast<const f32x4u *>(w3 + min(d0 + 4 * q, D - 4));
+      } else {
+        v[0] = w3[0];
+        if (D > 1) v[1] = w3[1];
+        if (D > 2) v[2] = w3[2];
+      }
+      return v;
+    };
+    // the same with zeros behind the end, components that the end moved back into place
+    auto in_place = [&](f32x4 v, int d0) {
+      const int d = d0 + 4 * q, back = D >= 4 ? d - min(d, D - 4) : d;
+      if (back & 1) v = f32x4{v[1], v[2], v[3], 0.0f};
+      if (back & 2) v = f32x4{v[2], v[3], 0.0f, 0.0f};
+      if (back >= 4) v = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      return v;
+    };
+    constexpr int PT = 2;  // tiles requested early: their first 32 components, and the activations
+    f32x4 yw[PT][2], hv[PT];
     auto request = [&](int t0) {
 #pragma unroll
       for (int p = 0; p < PT; ++p) {
         const int t = min(t0 + kHeadWaves * p, Hd / 16 - 1);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) yw[p][c] = W3[(int64_t)(16 * t + j) * D + min(4 * c + q, D - 1)];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) hv[p][i] = h2[min(b0 + 4 * q + i, B - 1) * ld + 16 * t + j];
+        yw[p][0] = request_w3(t, 0);
+        if (D > 16) yw[p][1] = request_w3(t, 16);
+        hv[p] = *reinterpret_cast<const f32x4 *>(h2_row + 16 * t + 4 * q);
       }
     };
-    // Output layer, like the hidden ones one fp32 accumulator per mean over k in ascending order: slices of KS k through
-    // LDS, NG columns at a time, 16 per wavefront.
-    constexpr int PH = 16 + 16, PW = NG + 16;
-    for (int n0 = 0; n0 < D; n0 += NG) {
-      constexpr int RW = KS * NG / 512;  // weights per thread and slice
-      f32x4 rh;
-      float rw[RW];
-      const int hr = tid & 15, hk = 4 * (tid >> 4);  // (16 KS / 4 groups of four activations)
-      auto load = [&](int k0) {
-        if (hk < KS) rh = *reinterpret_cast<const f32x4u *>(h2 + min(b0 + hr, B - 1) * ld + min(k0 + hk, Hd - 4));
-#pragma unroll
-        for (int i = 0; i < RW; ++i) {
-          const int e = tid + 512 * i;
-          rw[i] = W3[(int64_t)min(k0 + e / NG, Hd - 1) * D + min(n0 + e % NG, D - 1)];
-        }
-      };
-      f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-      load(0);
-      for (int k0 = 0; k0 < Hd; k0 += KS) {  // (Hd is a multiple of 32; groups past it are zeros)
-        __syncthreads();
-        if (hk < KS) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) s_z[(hk + i) * PH + hr] = k0 + hk < Hd ? rh[i] : 0.0f;
-        }
-#pragma unroll
-        for (int i = 0; i < RW; ++i) {
-          const int e = tid + 512 * i;
-          s_z[KS * PH + (e / NG) * PW + e % NG] = k0 + e / NG < Hd ? rw[i] : 0.0f;
-        }
-        __syncthreads();
-        load(k0 + KS);
-        if (k0 == 0 && n0 == 0) request(w);
-        if (16 * w < NG) {
-#pragma unroll 8
-          for (int i = 0; i < KS / 4; ++i)
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(s_z[(4 * i + q) * PH + j], s_z[KS * PH + (4 * i + q) * PW + 16 * w + j], acc, 0, 0, 0);
-        }
-      }
-      const int n = n0 + 16 * w + j;
-      if (16 * w < NG && n < D) {
-        const float bias = a.b3[net][n];
+    request(w);
+    const float logp_old = a.logp_old[r], A = a.adv[r], ret = a.ret[r];
+    const float act0 = a.act[r * a.D + min(sub, a.D - 1)];  // the first 32 components, requested early
+    for (int n0 = 16 * w; n0 < D; n0 += 16 * kHeadWaves) {
+      const int n = n0 + j;
+      const float bias = a.b3[net][min(n, D - 1)];
+      const float *const pa[1] = {h2_row};
+      f32x4 acc[1][1] = {{f32x4{0.0f, 0.0f, 0.0f, 0.0f}}};
+      stream_product<1, 1, kHeadDepth, false>(pa, W3, D, min(n, D - 1), Hd, lane, acc);
+      if (n < D) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (MU_LDS || b0 + 4 * q + i < B) mu[(int64_t)(4 * q + i) * Dp + n] = net == 1 ? acc[i] + bias : tanhf(acc[i] + bias);
+          if (MU_LDS || b0 + 4 * q + i < B)
+            mu[(int64_t)(4 * q + i) * Dp + n] = net == 1 ? acc[0][0][i] + bias : tanhf(acc[0][0][i] + bias);
       }
     }
     if (!MU_LDS) __threadfence_block();
@@ -819,27 +821,28 @@ __global__ __launch_bounds__(64 * kHeadWaves, 4) void head_kernel(HeadArgs a) {
         const int t = t0 + kHeadWaves * p;
         if (t < Hd / 16) {
           f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+          auto add = [&](const f32x4 &v, int d0) {  // components d0 .. d0 + 15
+            float op[4];
+            in_instruction_order(in_place(v, d0), op);
 #pragma unroll
-          for (int c = 0; c < 8; ++c) {
-            const int d = 4 * c + q;
-            const float x = dzrow[min(d, D - 1)];
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(d < D ? x : 0.0f, d < D ? yw[p][c] : 0.0f, acc, 0, 0, 0);
-          }
-          for (int d0 = 32; d0 < D; d0 += 32) {
-            float x[8], y[8];
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-              const int d = d0 + 4 * c + q, dc = min(d, D - 1);
-              x[c] = dzrow[dc], y[c] = W3[(int64_t)(16 * t + j) * D + dc];
-              if (d >= D) x[c] = 0.0f, y[c] = 0.0f;
+            for (int i = 0; i < 4; ++i) {
+              const int d = d0 + 4 * i + q;
+              const float x = dzrow[min(d, D - 1)];
+              acc = __builtin_amdgcn_mfma_f32_16x16x4f32(op[i], d < D ? x : 0.0f, acc, 0, 0, 0);
             }
-#pragma unroll
-            for (int c = 0; c < 8; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c], y[c], acc, 0, 0, 0);
+          };
+          add(yw[p][0], 0);
+          if (D > 16) add(yw[p][1], 16);
+          for (int d0 = 32; d0 < D; d0 += 32) {
+            const f32x4 v0 = request_w3(t, d0), v1 = request_w3(t, min(d0 + 16, D));
+            add(v0, d0);
+            if (d0 + 16 < D) add(v1, d0 + 16);
           }
+          if (b0 + j < B) {
+            f32x4 c;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int bb = b0 + 4 * q + i;
-            if (bb < B) a.dz2[net][bb * ld + 16 * t + j] = acc[i] * (1.0f - hv[p][i] * hv[p][i]);
+            for (int i = 0; i < 4; ++i) c[i] = acc[i] * (1.0f - hv[p][i] * hv[p][i]);
+            *reinterpret_cast<f32x4 *>(a.dz2[net] + (int64_t)(b0 + j) * ld + 16 * t + 4 * q) = c;
           }
         }
       }
@@ -1154,14 +1157,14 @@ hipError_t launch_ppo(hipStream_t st, const pr_ppo_config &c, const float *obs, 
   for (int pass = 0; pass < (plan.together ? 1 : 2); ++pass) {
     h.net0 = pass;
     const dim3 grid((unsigned)blocks, plan.together ? 2 : 1);
-    auto launch = [&](auto kern, int slice, hipError_t e) {
-      const size_t lds = (slice + 16 * 4 + (D <= kHeadLdsD ? 16 * (size_t)(D | 1) : 0)) * 4;
-      if (e == hipSuccess) hipLaunchKernelGGL(kern, grid, dim3(64 * kHeadWaves), lds, st, h);
-      return e != hipSuccess ? e : hipGetLastError();
-    };
-    if (D <= 32) LRN(launch(head_kernel<true, 32, 128>, head_slice(32, 128), allow_full_lds<head_kernel<true, 32, 128>>()));
-    else if (D <= kHeadLdsD) LRN(launch(head_kernel<true, 128, 32>, head_slice(128, 32), allow_full_lds<head_kernel<true, 128, 32>>()));
-    else LRN(launch(head_kernel<false, 128, 32>, head_slice(128, 32), hipSuccess));
+    const size_t lds = (16 * 4 + (D <= kHeadLdsD ? 16 * (size_t)(D | 1) : 0)) * 4;
+    if (D <= kHeadLdsD) {
+      LRN(allow_full_lds<head_kernel<true>>());
+      hipLaunchKernelGGL(head_kernel<true>, grid, dim3(64 * kHeadWaves), lds, st, h);
+    } else {
+      hipLaunchKernelGGL(head_kernel<false>, grid, dim3(64 * kHeadWaves), lds, st, h);
+    }
+    LRN(hipGetLastError());
     set.n = 0;
     for (int i = pass; i < (plan.together ? 2 : pass + 1); ++i) set.p[set.n++] = input_grad(i), set.p[set.n++] = weight_grad(i, 1);
     LRN(launch_products(st, set));

@@ -96,6 +96,14 @@ def test_learner_products_at_their_edges(B, D, K, Hd):
     np.testing.assert_allclose(parity.to_np(dstats), stats, rtol=2e-4, atol=1e-6)
 
 
+# the output layer and what goes back through it: 2, 3, 4, 16, 17, 18, 31, 47 and 1025 components (fewer than a request,
+# one that the end moves back by each amount, several groups of 16), one tile of samples and a last one of 1
+@pytest.mark.parametrize("B,D,K,Hd", [(16, 2, 1, 32), (33, 3, 1, 96), (40, 4, 1, 160), (17, 16, 0, 64), (49, 17, 2, 288),
+                                      (31, 18, 1, 64), (65, 31, 0, 512), (100, 47, 1, 64), (6, 1025, 0, 64)])
+def test_learner_output_layers(B, D, K, Hd):
+    test_learner_products_at_their_edges(B, D, K, Hd)
+
+
 # the forward layers' three tiles (32 x 64, 16 x 64, 16 x 16): fewer k than a stage, no remainder, one of 5; fewer stages
 # than are requested ahead; rows that end inside a tile, half a tile of columns
 @pytest.mark.parametrize("B,D,K,Hd", [(11010, 3, 1, 160), (8195, 9, 2, 256), (5200, 5, 0, 96), (1000, 3, 1, 352),
