@@ -72,7 +72,9 @@ struct ProbSet {
 // workgroup share one tile's k range (every operand element is still read by exactly one of them) and their
 // accumulators are added up, in order, in LDS at the end; with more, each wavefront takes a tile of its own.
 // Operand of a 32 x 32 x 16 product: lane l holds 8 consecutive k of row (column) l % 32, k group l / 32.
-//   k contiguous in memory: two 16-byte loads; row of block x is 32 x + l % 32;
+//   k contiguous in memory: four requests of 16 rows x 64 bytes, whose lane quarters then exchange halves; row of block x
+//   is 32 x + l % 32.  (A lane that reads its own eight k asks for two pieces of 32 rows each: 104 to 137 cycles of the
+//   compute unit a request from L2, where 16 rows x 64 bytes take 33.)
 //   m (n) contiguous: eight 8-byte loads, one per k, that serve both 32-row blocks: row of block x is 2 (l % 32) + x.
 constexpr int kTile = 64, kPitch = kTile + 4;
 
@@ -82,53 +84,52 @@ template <class T>
 __device__ inline void pin(T &x) { asm volatile("" : "+v"(x)); }  // x is needed, and settled, here
 
 template <int SLOTS>
-struct RawK {  // k-contiguous operand: [slot][block][8]
-  const float *p[2];
-  f32x4 v[SLOTS][2][2];
-  __device__ void init(const float *base, int64_t ld, int r0, int rows, const int32_t *gather, int k, int, int lane) {
+struct RawK {  // k-contiguous operand: [slot][group of 16 rows][4]
+  const float *base;  // uniform
+  uint32_t off[4];    // of row l % 16 of each group, k quarter l / 16
+  f32x4 v[SLOTS][4];
+  __device__ void init(const float *b, int64_t ld, int r0, int rows, const int32_t *, int k, int, int lane) {
+    base = b + r0 * ld + k;
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
-      int r = min(r0 + 32 * x + (lane & 31), rows - 1);
-      if (gather) r = gather[r];
-      p[x] = base + (int64_t)r * ld + k + 8 * (lane >> 5);
-    }
+    for (int z = 0; z < 4; ++z) off[z] = (uint32_t)(min(r0 + 16 * z + (lane & 15), rows - 1) - r0) * (uint32_t)ld + 4 * (lane >> 4);
   }
   template <int SLOT>
-  __device__ void load(int kend, int lane) {
+  __device__ void load(int, int, int) {
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-      for (int q = 0; q < 2; ++q) v[SLOT][x][q] = *reinterpret_cast<const f32x4u *>(p[x] + 4 * q);
+    for (int z = 0; z < 4; ++z) v[SLOT][z] = *reinterpret_cast<const f32x4u *>(base + off[z]);
   }
-  __device__ void advance(int step) {
-#pragma unroll
-    for (int x = 0; x < 2; ++x) p[x] += step;
-  }
+  __device__ void advance(int step) { base += step; }
+  __device__ void next_group(int) {}
   template <int SLOT>
   __device__ void arrived() {  // (a use of the slot: the wait for it stands here)
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-      for (int q = 0; q < 2; ++q) pin(v[SLOT][x][q]);
+    for (int z = 0; z < 4; ++z) pin(v[SLOT][z]);
   }
+  // the eight k of block x's row l % 32: the lane quarters exchange halves of two groups of rows
   template <int SLOT>
-  __device__ float get(int x, int e) const { return v[SLOT][x][e >> 2][e & 3]; }
+  __device__ void take(int x, float (&out)[8]) const {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float lo = v[SLOT][2 * x][e], hi = v[SLOT][2 * x + 1][e];
+      const auto s = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi), false, false);
+      const uint32_t s0 = s[0], s1 = s[1];
+      out[e] = __builtin_bit_cast(float, s0), out[4 + e] = __builtin_bit_cast(float, s1);
+    }
+  }
 };
 
-template <int SLOTS, bool GATHER>
+template <int SLOTS, bool GATHER, int GROUP>
 struct RawM {  // m- (n-) contiguous operand: [slot][8] pairs
+  static constexpr int group = 16 * GROUP;  // k of a group of steps
   const float *base;  // uniform
   const int32_t *gather;
   uint32_t off;       // of this lane's column pair and k half
   int64_t ld;
   int k, kend;
-  int32_t id[8];  // rows of the present 16 k (GATHER; requested one position ahead)
+  int32_t ids[2];  // GATHER: rows of the present group of steps (at most 64 k) and of the next one, a lane each
   bool second;    // the pair was moved down by one at the end of the row: its first element is the second loaded
   f32x2 v[SLOTS][8];
-  __device__ void rows_of(int lane) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) id[e] = gather[min(k + 8 * (lane >> 5) + e, kend - 1)];
-  }
+  __device__ int32_t rows_from(int k0, int lane) const { return gather[min(k0 + lane, kend - 1)]; }
   __device__ void init(const float *b, int64_t ld_, int c0, int cols, const int32_t *g, int k_, int kend_, int lane) {
     const int c = c0 + 2 * (lane & 31), last = cols > 1 ? cols - 2 : 0;
     second = c == cols - 1 && cols > 1;
@@ -136,26 +137,27 @@ struct RawM {  // m- (n-) contiguous operand: [slot][8] pairs
     off = (uint32_t)min(c, last);
     if constexpr (GATHER) {
       base = b;
-      rows_of(lane);
+      ids[0] = rows_from(k, lane), ids[1] = rows_from(k + group, lane);
     } else {
       base = b + k * ld;
       off += (uint32_t)(8 * (lane >> 5)) * (uint32_t)ld;
     }
   }
   template <int SLOT>
-  __device__ void load(int, int lane) {
+  __device__ void load(int which, int step, int lane) {  // (which, step: GATHER, position of the step's rows in `ids`)
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       if constexpr (GATHER)
-        v[SLOT][e] = *reinterpret_cast<const f32x2u *>(base + (id[e] * ld + off));
+        v[SLOT][e] = *reinterpret_cast<const f32x2u *>(base + (__shfl(ids[which], 16 * step + 8 * (lane >> 5) + e) * ld + off));
       else
         v[SLOT][e] = *reinterpret_cast<const f32x2u *>(base + e * ld + off);
     }
   }
   __device__ void advance(int step) {
-    k += step;
-    if constexpr (GATHER) rows_of(threadIdx.x & 63);
-    else base += step * ld;
+    if constexpr (!GATHER) k += step, base += step * ld;
+  }
+  __device__ void next_group(int lane) {
+    if constexpr (GATHER) k += group, ids[0] = ids[1], ids[1] = rows_from(k + group, lane);
   }
   // the 16 k at the present position with rows outside [k_from, kend) as zeros (the others clamped into the range)
   template <int SLOT>
@@ -177,21 +179,25 @@ struct RawM {  // m- (n-) contiguous operand: [slot][8] pairs
   }
   template <int SLOT>
   __device__ float get(int x, int e) const { return x == 0 && !second ? v[SLOT][e][0] : v[SLOT][e][1]; }
+  template <int SLOT>
+  __device__ void take(int x, float (&out)[8]) const {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) out[e] = get<SLOT>(x, e);
+  }
 };
 
-// kw = 1: the whole range, software pipelined.  What bounds a wavefront there is one stream of instructions: 24 matrix
-// instructions of 32 cycles and about 180 vector instructions of 4 cycles (the splits) per 16 k; one after the other
-// they take 1500 cycles, so the split of the next 16 k is interleaved with the products of the present one, seven or
-// eight vector instructions behind each matrix instruction.
+// kw = 1: the whole range, two or three steps requested ahead; the two wavefronts of a SIMD overlap each other's matrix
+// instructions (24 of 32 cycles for 16 k) and splits (about 290 vector instructions).
 // kw = 8: a share of at most SLOTS 16-deep steps at a time, all requested at once; what counts is one memory round trip.
 // SLOTS = 4 asks for four in any case (a branch around a request makes the compiler wait for all of them before the
 // first product: 28.8 us for 26.7 at 1024 samples x 512 units).  A request is 32 scattered lines, though, and where no
 // share is deeper than two steps the ones nobody uses cost more than that: SLOTS = 2 asks only for what is there (300
 // samples x 256 units, launches 4 and 5 together 16.5 us for 20.2; 4096 x 128, 23.3 for 28.4).
-template <int KW, int SLOTS, Kind KIND, bool SUMS, bool GATHER>
+template <int KW, int SLOTS_, Kind KIND, bool SUMS, bool GATHER>
 __device__ inline void product(const Prob &g, int m0, int n0, int kbeg, int kend, int split, float *lds) {
   const int tid = threadIdx.x, lane = tid & 63, w = KW == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr bool A_K = KIND == DZ, B_K = A_K;
+  constexpr int SLOTS = KW == 1 ? (GATHER ? 2 : 3) : SLOTS_;
   f32x16 acc[2][2];
 #pragma unroll
   for (int x = 0; x < 2; ++x)
@@ -203,54 +209,57 @@ __device__ inline void product(const Prob &g, int m0, int n0, int kbeg, int kend
   // wavefront w: the w-th share of the full 16-deep steps; what is left over goes to the last wavefront
   const int steps = (kend - kbeg) / 16, rest = (kend - kbeg) & 15, per = (steps + KW - 1) / KW;
   const int s0 = min(w * per, steps), s1 = min(s0 + per, steps);
-  std::conditional_t<A_K, RawK<SLOTS>, RawM<SLOTS, GATHER>> ra;
-  std::conditional_t<B_K, RawK<SLOTS>, RawM<SLOTS, false>> rb;
-  bf16x8 a[2][2][3], b[2][2][3];  // [step parity][block][part]
+  constexpr int GROUP = KW == 1 ? 4 : SLOTS;  // steps whose rows' indices are read at once (GATHER)
+  std::conditional_t<A_K, RawK<SLOTS>, RawM<SLOTS, GATHER, GROUP>> ra;
+  std::conditional_t<B_K, RawK<SLOTS>, RawM<SLOTS, false, GROUP>> rb;
+  bf16x8 a[2][3], b[2][3];  // [block][part]
   // The matrix instructions drop what does not fit into an accumulator towards minus infinity, about 2^-28 of the terms'
   // magnitude: nothing in a product, but gb1 adds dz1 up over the batch, and there it adds up too (2-norm error of gb1 at
   // 16384 samples x 64 units 1.3e-6; 3.6e-7 with fp32 instructions, which round to nearest, and as it is now).  So DZ forms
   // the odd rows, every second sample, negated.
   const uint32_t flip = (uint32_t)lane << 31;
-  auto split_slot = [&](auto slot, auto par) {
-    constexpr int SL = decltype(slot)::value, P = decltype(par)::value;
+  auto split_slot = [&](auto slot) {
+    constexpr int SL = decltype(slot)::value;
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
       float va[8], vb[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) va[e] = ra.template get<SL>(x, e), vb[e] = rb.template get<SL>(x, e);
+      ra.template take<SL>(x, va);
+      rb.template take<SL>(x, vb);
       if constexpr (KIND == DZ) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) va[e] = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, va[e]) ^ flip);
       }
-      split3(va, a[P][x]);
-      split3(vb, b[P][x]);
+      split3(va, a[x]);
+      split3(vb, b[x]);
     }
   };
   auto add_sums = [&](auto slot) {
     constexpr int SL = decltype(slot)::value;
+    if constexpr (SUMS) {
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+      for (int x = 0; x < 2; ++x)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) cs[x] += rb.template get<SL>(x, e);
+        for (int e = 0; e < 8; ++e) cs[x] += rb.template get<SL>(x, e);
+    }
   };
-  auto multiply = [&](auto par) {
-    constexpr int P = decltype(par)::value;
+  auto multiply = [&] {
 #pragma unroll
     for (int q = 0; q < 6; ++q) {
 #pragma unroll
       for (int x = 0; x < 2; ++x)
 #pragma unroll
         for (int y = 0; y < 2; ++y)
-          acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[P][x][kSplitA[q]], b[P][y][kSplitB[q]], acc[x][y], 0, 0, 0);
+          acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[x][kSplitA[q]], b[y][kSplitB[q]], acc[x][y], 0, 0, 0);
     }
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
-  using I2 = std::integral_constant<int, SLOTS == 4 ? 2 : 0>;
+  using I2 = std::integral_constant<int, SLOTS >= 3 ? 2 : 0>;
   using I3 = std::integral_constant<int, SLOTS == 4 ? 3 : 0>;
-  auto load = [&](auto slot, bool more) {  // (requests past the wavefront's last step repeat it)
-    ra.template load<decltype(slot)::value>(kend, lane);
-    rb.template load<decltype(slot)::value>(kend, lane);
+  // (requests past the wavefront's last step repeat it)
+  auto load = [&](auto slot, bool more, int which, int step) {
+    ra.template load<decltype(slot)::value>(which, step, lane);
+    rb.template load<decltype(slot)::value>(which, step, lane);
     ra.advance(more ? 16 : 0);
     rb.advance(more ? 16 : 0);
   };
@@ -258,67 +267,54 @@ __device__ inline void product(const Prob &g, int m0, int n0, int kbeg, int kend
     const int k0 = kbeg + 16 * s0;
     ra.init(g.A, g.lda, m0, g.M, g.gather, k0, kend, lane);
     rb.init(g.B, g.ldb, n0, g.N, nullptr, k0, kend, lane);
-    if constexpr (KW == 1 && KIND == DW) {
-      // (two m-contiguous operands and the batch rows' indices leave no registers for a second set of parts: the two
-      // wavefronts of a SIMD overlap each other)
-      load(I0{}, s0 + 1 < s1);
-      load(I1{}, s0 + 2 < s1);
-      auto step = [&](auto cur, int s) {
-        split_slot(cur, I0{});
+    if constexpr (KW == 1) {
+      // Rounds, and what is left of one behind the loop: with the way out inside it the compiler waits for everything
+      // requested at its head.
+      auto step = [&](auto cur, int s, bool request, int which, int at) {
+        split_slot(cur);
         if (SUMS) add_sums(cur);
-        load(cur, s + 3 < s1);
-        multiply(I0{});
-      };
-      for (int s = s0; s < s1; s += 2) {
-        step(I0{}, s);
-        if (s + 1 < s1) step(I1{}, s + 1);
-      }
-    } else if constexpr (KW == 1) {
-      load(I0{}, s0 + 1 < s1);
-      load(I1{}, s0 + 2 < s1);
-      split_slot(I0{}, I0{});
-      if (SUMS) add_sums(I0{});
-      // step s: products of s (parts of parity s), split of s + 1 (requested a step ago), request of s + 2
-      auto step = [&](auto cur, auto next, int s) {
-        constexpr int NX = decltype(next)::value;
-        ra.template arrived<NX>();
-        rb.template arrived<NX>();
-        load(cur, s + 3 < s1);
+        if (request) load(cur, s + SLOTS + 1 < s1, which, at);
+        multiply();
         __builtin_amdgcn_sched_barrier(0);
-        multiply(cur);
-        split_slot(next, next);
-        if (SUMS) {
-          if (s + 1 < s1) add_sums(next);
-        } else {
-#pragma unroll
-          for (int i = 0; i < 24; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one matrix instruction
-            __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);  // eight vector instructions
-          }
-        }
-        // (used here: otherwise the compiler moves the split behind the loop's exit test, out of the products' shadow)
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-          for (int j = 0; j < 3; ++j) pin(a[NX][x][j]), pin(b[NX][x][j]);
       };
-      for (int s = s0; s < s1; s += 2) {
-        step(I0{}, I1{}, s);
-        if (s + 1 < s1) step(I1{}, I0{}, s + 1);
+      int s = s0;
+      load(I0{}, s0 + 1 < s1, 0, 0);
+      load(I1{}, s0 + 2 < s1, 0, 1);
+      if constexpr (GATHER) {
+        for (; s + 4 <= s1; s += 4) {
+          step(I0{}, s, true, 0, 2);
+          step(I1{}, s + 1, true, 0, 3);
+          step(I0{}, s + 2, true, 1, 0);
+          step(I1{}, s + 3, true, 1, 1);
+          ra.next_group(lane);
+        }
+        if (s < s1) step(I0{}, s, true, 0, 2);
+        if (s + 1 < s1) step(I1{}, s, false, 0, 0);
+        if (s + 2 < s1) step(I0{}, s, false, 0, 0);
+      } else {
+        load(I2{}, s0 + 3 < s1, 0, 0);
+        for (; s + 3 <= s1; s += 3) {
+          step(I0{}, s, true, 0, 0);
+          step(I1{}, s + 1, true, 0, 0);
+          step(I2{}, s + 2, true, 0, 0);
+        }
+        if (s < s1) step(I0{}, s, false, 0, 0);
+        if (s + 1 < s1) step(I1{}, s, false, 0, 0);
       }
     } else {
       for (int s = s0; s < s1; s += SLOTS) {
-        load(I0{}, s + 1 < s1);
-        if (SLOTS == 4 || s + 1 < s1) load(I1{}, s + 2 < s1);
+        load(I0{}, s + 1 < s1, 0, 0);
+        if (SLOTS == 4 || s + 1 < s1) load(I1{}, s + 2 < s1, 0, 1);
         if constexpr (SLOTS == 4) {
-          load(I2{}, s + 3 < s1);
-          load(I3{}, s + 4 < s1);
+          load(I2{}, s + 3 < s1, 0, 2);
+          load(I3{}, s + 4 < s1, 0, 3);
         }
+        ra.next_group(lane);
         auto take = [&](auto slot, int i) {
           if (s + i >= s1) return;
-          split_slot(slot, I0{});
+          split_slot(slot);
           if (SUMS) add_sums(slot);
-          multiply(I0{});
+          multiply();
         };
         take(I0{}, 0);
         take(I1{}, 1);
@@ -339,9 +335,9 @@ __device__ inline void product(const Prob &g, int m0, int n0, int kbeg, int kend
       ra.template load_trimmed<0>(kbeg + 16 * steps, lane);
       rb.template load_trimmed<0>(kbeg + 16 * steps, lane);
     }
-    split_slot(I0{}, I0{});
+    split_slot(I0{});
     if (SUMS) add_sums(I0{});
-    multiply(I0{});
+    multiply();
   }
   float *C = g.C, *C_sum = g.colsum;
   int64_t ldc = g.ldc;
@@ -965,14 +961,15 @@ constexpr size_t kStaticScratchBytes = (size_t)24 << 20;
 
 struct Plan {
   bool together;   // both networks in every launch; else one after the other, sharing the dz buffers
-  bool padded;     // activation rows, and a copy of W2, end in 32 unused floats (see row_floats)
+  bool padded;     // activation rows, and a copy of W2, end in 16 unused floats (see row_floats)
   int splits;      // k splits of the weight gradients
   size_t bytes;
 };
 
 // A tile reads 64 rows of a few cache lines each.  Rows of 512 floats are 2 KiB apart: all of a tile's lines then fall
-// on a handful of L2 channels and L1 sets (measured: 25 us for a product that takes 13 us with rows of 544).
-int row_floats(int Hd, bool padded) { return padded ? Hd + 32 : Hd; }
+// on a handful of L2 channels (measured: 25 us for a product that takes 13 us with rows of 544), and rows a multiple of
+// 128 bytes apart on one bank of the L1 (16 rows x 64 bytes: 62 cycles a request, 33 with rows of 528).
+int row_floats(int Hd, bool padded) { return padded ? Hd + 16 : Hd; }
 bool wants_padding(int Hd) { return Hd % 128 == 0; }
 
 int64_t net_params(int S, int Hd, int O) { return (int64_t)(S + 1) * Hd + (int64_t)(Hd + 1) * Hd + (int64_t)(Hd + 1) * O; }
@@ -1047,7 +1044,7 @@ hipError_t launch_products(hipStream_t st, ProbSet &set) {
     next += p.blocks;
   }
   if (own) {
-    hipLaunchKernelGGL((products_kernel<1, 2>), dim3((unsigned)next), dim3(256), 0, st, set);
+    hipLaunchKernelGGL((products_kernel<1, 0>), dim3((unsigned)next), dim3(256), 0, st, set);
   } else {
     const auto shared = [&](auto slots) {
       constexpr auto *kern = products_kernel<8, decltype(slots)::value>;
