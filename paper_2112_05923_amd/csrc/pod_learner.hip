@@ -23,7 +23,7 @@
 // 256 to 32768, 64 to 512 units): gW1 0.72, gW2 0.71, gW3 0.89, gb1 0.91, the others as before.
 //
 // Measured (301-512-512 networks): a step at batch 1024 84 us (315 us as 38 launches); gradients at 15000 samples with
-// 256 hidden units 285 us (753 us).
+// 256 hidden units 277 us (753 us).
 #include <math.h>
 
 #include <algorithm>
@@ -70,7 +70,8 @@ struct ProbSet {
 // A wavefront computes a 64 x 64 tile of C, its operands read straight from global memory into the registers of the
 // matrix operands: no LDS and no barrier in the loop.  With fewer tiles than SIMDs the eight wavefronts of a
 // workgroup share one tile's k range (every operand element is still read by exactly one of them) and their
-// accumulators are added up, in order, in LDS at the end; with more, each wavefront takes a tile of its own.
+// accumulators are added up, in order, in LDS at the end; with more, each wavefront takes a tile of its own, or four of
+// them share operands (wide_product).
 // Operand of a 32 x 32 x 16 product: lane l holds 8 consecutive k of row (column) l % 32, k group l / 32.
 //   k contiguous in memory: four requests of 16 rows x 64 bytes, whose lane quarters then exchange halves; row of block x
 //   is 32 x + l % 32.  (A lane that reads its own eight k asks for two pieces of 32 rows each: 104 to 137 cycles of the
@@ -82,6 +83,13 @@ constexpr int kTile = 64, kPitch = kTile + 4;
 // present position into a slot, `advance` moves on.
 template <class T>
 __device__ inline void pin(T &x) { asm volatile("" : "+v"(x)); }  // x is needed, and settled, here
+
+// lo's odd lane quarters exchanged with hi's even ones
+__device__ inline void swap_quarters(float lo, float hi, float &even, float &odd) {
+  const auto s = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi), false, false);
+  const uint32_t s0 = s[0], s1 = s[1];
+  even = __builtin_bit_cast(float, s0), odd = __builtin_bit_cast(float, s1);
+}
 
 template <int SLOTS>
 struct RawK {  // k-contiguous operand: [slot][group of 16 rows][4]
@@ -109,12 +117,7 @@ struct RawK {  // k-contiguous operand: [slot][group of 16 rows][4]
   template <int SLOT>
   __device__ void take(int x, float (&out)[8]) const {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float lo = v[SLOT][2 * x][e], hi = v[SLOT][2 * x + 1][e];
-      const auto s = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi), false, false);
-      const uint32_t s0 = s[0], s1 = s[1];
-      out[e] = __builtin_bit_cast(float, s0), out[4 + e] = __builtin_bit_cast(float, s1);
-    }
+    for (int e = 0; e < 4; ++e) swap_quarters(v[SLOT][2 * x][e], v[SLOT][2 * x + 1][e], out[e], out[4 + e]);
   }
 };
 
@@ -186,8 +189,8 @@ struct RawM {  // m- (n-) contiguous operand: [slot][8] pairs
   }
 };
 
-// kw = 1: the whole range, two or three steps requested ahead; the two wavefronts of a SIMD overlap each other's matrix
-// instructions (24 of 32 cycles for 16 k) and splits (about 290 vector instructions).
+// kw = 1 (weight gradients): the whole range, two or three steps requested ahead; the two wavefronts of a SIMD overlap each
+// other's matrix instructions (24 of 32 cycles for 16 k) and splits (about 290 vector instructions).
 // kw = 8: a share of at most SLOTS 16-deep steps at a time, all requested at once; what counts is one memory round trip.
 // SLOTS = 4 asks for four in any case (a branch around a request makes the compiler wait for all of them before the
 // first product: 28.8 us for 26.7 at 1024 samples x 512 units).  A request is 32 scattered lines, though, and where no
@@ -343,47 +346,23 @@ __device__ inline void product(const Prob &g, int m0, int n0, int kbeg, int kend
   int64_t ldc = g.ldc;
   if (split > 0) C = g.part + (int64_t)(split - 1) * (g.M + 1) * g.N, C_sum = C + (int64_t)g.M * g.N, ldc = g.N;
   if constexpr (KW == 1) {
-    // Accumulator register i of lane l: row 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32.  Column blocks of an
-    // n-contiguous B' interleave, so a lane's two columns are neighbours.
-    const int half = lane >> 5, N = g.N;
-    const int n = n0 + (B_K ? (lane & 31) : 2 * (lane & 31));
-    constexpr int NY = B_K ? 32 : 1;  // distance of a lane's two columns
-    auto finish = [&](auto full) {
-      constexpr bool FULL = decltype(full)::value;
-      const int na = FULL ? n : min(n, N - 1), nb = FULL ? n + NY : min(n + NY, N - 1);
+    // (weight gradients: both operands m-contiguous)  Accumulator register i of lane l: row 8 (i / 4) + 4 (l / 32) + i % 4,
+    // column l % 32; the blocks interleave, so a lane's two columns are neighbours.
+    const int half = lane >> 5, N = g.N, n = n0 + 2 * (lane & 31);
+    const bool full = m0 + kTile <= g.M && n0 + kTile <= N;
 #pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        auto row_of = [&](int i) {
-          const int r = 8 * (i >> 2) + 4 * half + (i & 3);
-          return m0 + (A_K ? 32 * x + r : 2 * r + x);
-        };
-        float h[16][2];
-        if constexpr (KIND == DZ) {
+    for (int x = 0; x < 2; ++x)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const float *src = g.aux + (FULL ? row_of(i) : min(row_of(i), g.M - 1)) * ldc;
-            h[i][0] = src[na], h[i][1] = src[nb];
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          f32x2 c = {acc[x][0][i], acc[x][1][i]};
-          if constexpr (KIND == DZ) {
-            if (i & 1) c = -c;
-            c = f32x2{c[0] * (1.0f - h[i][0] * h[i][0]), c[1] * (1.0f - h[i][1] * h[i][1])};
-          }
-          float *dst = C + row_of(i) * ldc;
-          if (FULL && NY == 1) {
-            *reinterpret_cast<f32x2u *>(dst + n) = c;
-          } else if (FULL || row_of(i) < g.M) {
-            if (FULL || n < N) dst[n] = c[0];
-            if (FULL || n + NY < N) dst[n + NY] = c[1];
-          }
+      for (int i = 0; i < 16; ++i) {
+        const int m = m0 + 2 * (8 * (i >> 2) + 4 * half + (i & 3)) + x;
+        float *dst = C + m * ldc + n;
+        if (full) {
+          *reinterpret_cast<f32x2u *>(dst) = f32x2{acc[x][0][i], acc[x][1][i]};
+        } else if (m < g.M) {
+          if (n < N) dst[0] = acc[x][0][i];
+          if (n + 1 < N) dst[1] = acc[x][1][i];
         }
       }
-    };
-    if (m0 + kTile <= g.M && n0 + kTile <= N) finish(std::true_type{});
-    else finish(std::false_type{});
     if constexpr (SUMS) {
 #pragma unroll
       for (int y = 0; y < 2; ++y) {
@@ -447,8 +426,8 @@ __device__ inline void product(const Prob &g, int m0, int n0, int kbeg, int kend
 
 constexpr size_t products_lds(int kw) { return kw == 1 ? 0 : (size_t)kw * (kTile * kPitch + 2 * kTile) * 4; }
 
-// KW = 8: one tile per workgroup of eight wavefronts; KW = 1: four wavefronts, a tile each (neighbours in n: they read
-// the same rows of A)
+// KW = 8: one tile per workgroup of eight wavefronts; KW = 1 (weight gradients): four wavefronts, a tile each (neighbours
+// in n: they read the same rows of A)
 template <int KW, int SLOTS>
 __global__ __launch_bounds__(KW == 1 ? 256 : 512, 2) void products_kernel(ProbSet set) {
   extern __shared__ __align__(16) float lds[];
@@ -464,14 +443,300 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 512, 2) void products_kernel(ProbSe
   const int tm = tile / g.tiles_n, tn = tile - tm * g.tiles_n;
   const int kbeg = split * g.k_chunk, kend = min(g.K, kbeg + g.k_chunk);
   const int m0 = tm * kTile, n0 = tn * kTile;
-  if (g.kind == DZ) {
-    product<KW, SLOTS, DZ, false, false>(g, m0, n0, kbeg, kend, 0, lds);
+  if (KW == 8 && g.kind == DZ) {
+    product<8, KW == 8 ? SLOTS : 2, DZ, false, false>(g, m0, n0, kbeg, kend, 0, lds);
   } else if (tm == 0) {
     if (g.gather) product<KW, SLOTS, DW, true, true>(g, m0, n0, kbeg, kend, split, lds);
     else product<KW, SLOTS, DW, true, false>(g, m0, n0, kbeg, kend, split, lds);
   } else {
     if (g.gather) product<KW, SLOTS, DW, false, true>(g, m0, n0, kbeg, kend, split, lds);
     else product<KW, SLOTS, DW, false, false>(g, m0, n0, kbeg, kend, split, lds);
+  }
+}
+
+// ---- many tiles, input gradients among them: a workgroup of four wavefronts, 2 x 2 tiles of 64 x 64
+// The parts of an operand are formed once for the two wavefronts that need them: wavefront w reads rows 32 w .. + 31 of
+// both operands of the 128 x 128 tile, takes them apart and lays them into LDS as the matrix instructions want them: half
+// the requests and half the vector instructions of a wavefront for itself.  One barrier for 16 k; the parts of the next
+// 16 are formed behind the products of the present ones (six vector instructions to a matrix instruction of 32 cycles).
+// Bound by the matrix rate, which the power limit keeps at 1.7 GHz under such a load: 27 us at 15000 samples x 256 units
+// for the launch that takes 65 (79 with a wavefront for itself), 230 at 32768 x 512 for 410 (484); 3000 x 512 54 (62),
+// 33000 x 64, where half of the tile is empty, 49 (65).  The launch of weight gradients alone stays with a wavefront for
+// itself: 271 or 181 rows and 30 columns leave more of 128 x 128 empty (8192 x 512 57 us for 44, 32768 x 512 196 for 185,
+// 15000 x 256 60 for 64).  Operands fetched a step ahead with three buffers: 69 and 425 us in place of 65 and 410.
+constexpr int kWideMix = 6;                     // vector instructions to a matrix instruction
+constexpr int kWide = 128, kWideSlots = 4;      // (slots: steps of 16 k requested ahead)
+constexpr int kPartBytes = kWide * 32;      // LDS: [part][k half][row][8 k] of an operand (rows side by side: no bank conflicts)
+constexpr size_t kWideLds = 2 * 2 * 3 * kPartBytes;  // two buffers of both operands
+
+// Rows (columns) 32 w .. of an operand that is contiguous along k; lane l holds k half l / 32 of row l % 32.
+struct WideK {
+  const float *base;  // uniform: k 0
+  uint32_t off[2];
+  f32x4 v[kWideSlots][2];
+  __device__ void init(const float *b, int64_t ld, int r0, int rows, int, int w, int lane) {
+    base = b + r0 * ld;
+#pragma unroll
+    for (int z = 0; z < 2; ++z)
+      off[z] = (uint32_t)(min(r0 + 32 * w + 16 * z + (lane & 15), rows - 1) - r0) * (uint32_t)ld + 4 * (lane >> 4);
+  }
+  __device__ static int row(int place) { return place; }  // of the 32 that lane `place` (+ 32) holds
+  template <int SLOT>
+  __device__ void load(int k) {
+#pragma unroll
+    for (int z = 0; z < 2; ++z) v[SLOT][z] = *reinterpret_cast<const f32x4u *>(base + k + off[z]);
+  }
+  template <int SLOT>
+  __device__ void take(float (&out)[8]) const {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) swap_quarters(v[SLOT][0][e], v[SLOT][1][e], out[e], out[4 + e]);
+  }
+};
+
+// The same of one that is contiguous along m (n): a lane reads pairs of neighbours of four k, and the lane quarters
+// exchange: lane l holds k half l / 32 of row 2 (l % 16) + l / 16 % 2.
+struct WideM {
+  const float *base;
+  uint32_t off;
+  int64_t ld;
+  int kend;
+  bool second;  // the pair was moved down by one at the end of the row
+  f32x2 v[kWideSlots][4];
+  __device__ void init(const float *b, int64_t ld_, int c0, int cols, int kend_, int w, int lane) {
+    const int c = c0 + 32 * w + 2 * (lane & 15), last = cols > 1 ? cols - 2 : 0;
+    second = c == cols - 1 && cols > 1;
+    base = b, ld = ld_, kend = kend_;
+    off = (uint32_t)min(c, last) + (uint32_t)(4 * (lane >> 4)) * (uint32_t)ld;
+  }
+  __device__ static int row(int place) { return 2 * (place & 15) + (place >> 4); }
+  template <int SLOT>
+  __device__ void load(int k) {
+    const float *at = base + k * ld;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[SLOT][i] = *reinterpret_cast<const f32x2u *>(at + i * ld + off);
+  }
+  // the 16 k at position k with rows outside [k_from, kend) as zeros (the others clamped into the range)
+  __device__ void load_trimmed(int k, int k_from, int lane) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int kk = k + 4 * (lane >> 4) + i;
+      const bool ok = kk >= k_from && kk < kend;
+      const f32x2 t = *reinterpret_cast<const f32x2u *>(base + (int64_t)(min(kk, kend - 1) - 4 * (lane >> 4)) * ld + off);
+      v[0][i] = f32x2{ok ? t[0] : 0.0f, ok ? t[1] : 0.0f};
+    }
+  }
+  template <int SLOT>
+  __device__ void take(float (&out)[8]) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) swap_quarters(second ? v[SLOT][i][1] : v[SLOT][i][0], v[SLOT][i][1], out[i], out[4 + i]);
+  }
+};
+
+template <Kind KIND, bool SUMS>
+__device__ inline void wide_product(const Prob &g, int m0, int n0, int kbeg, int kend, int split, unsigned char *lds) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  constexpr bool DZ_ = KIND == DZ;
+  std::conditional_t<DZ_, WideK, WideM> ra, rb;
+  const int steps = max(kend - kbeg, 0) / 16, rest = max(kend - kbeg, 0) & 15;
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[x][y][i] = 0.0f;
+  float cs = 0.0f;
+  const int wm = w >> 1, wn = w & 1, half = lane >> 5;
+  const bool active = m0 + 64 * wm < g.M && n0 + 64 * wn < g.N;
+  const uint32_t flip = (uint32_t)lane << 31;  // odd rows of DZ negated: see product
+  const int place = lane & 31, half_at = half * (16 * kWide);
+  unsigned char *const put_a = lds + half_at + (32 * w + place) * 16, *const put_b = put_a + 3 * kPartBytes;
+  const unsigned char *const get_a = lds + half_at + (64 * wm + place) * 16;
+  const unsigned char *const get_b = lds + 3 * kPartBytes + half_at + (64 * wn + place) * 16;
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
+  auto request = [&](auto slot, int step) {  // (past the last step: the last once more)
+    const int k = kbeg + 16 * min(step, steps - 1);
+    ra.template load<decltype(slot)::value>(k);
+    rb.template load<decltype(slot)::value>(k);
+  };
+  bf16x8 pa[3], pb[3];  // parts on their way to LDS
+  auto split_slot = [&](auto slot) {
+    constexpr int SL = decltype(slot)::value;
+    float va[8], vb[8];
+    ra.template take<SL>(va);
+    rb.template take<SL>(vb);
+    if constexpr (DZ_) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) va[e] = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, va[e]) ^ flip);
+    }
+    if constexpr (SUMS) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) cs += vb[e];
+    }
+    split3(va, pa);
+    split3(vb, pb);
+  };
+  auto lay = [&](int buffer) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      *reinterpret_cast<bf16x8 *>(put_a + buffer * (6 * kPartBytes) + j * kPartBytes) = pa[j];
+      *reinterpret_cast<bf16x8 *>(put_b + buffer * (6 * kPartBytes) + j * kPartBytes) = pb[j];
+    }
+  };
+  bf16x8 a[2][3], b[2][3];
+  auto fetch = [&](int buffer) {
+#pragma unroll
+    for (int j = 2; j >= 0; --j)
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        a[x][j] = *reinterpret_cast<const bf16x8 *>(get_a + buffer * (6 * kPartBytes) + j * kPartBytes + x * 512);
+        b[x][2 - j] = *reinterpret_cast<const bf16x8 *>(get_b + buffer * (6 * kPartBytes) + (2 - j) * kPartBytes + x * 512);
+      }
+  };
+  auto multiply = [&] {
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+          acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[x][kSplitA[q]], b[y][kSplitB[q]], acc[x][y], 0, 0, 0);
+  };
+  // what this wavefront laid down is there, and everybody has read the other buffer
+  auto meet = [&] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+  // ACTIVE: this wavefront's tile is not all behind the edge
+  auto run = [&](auto act) {
+    constexpr bool ACTIVE = decltype(act)::value;
+    if (steps > 0) {
+      ra.init(g.A, g.lda, m0, g.M, kend, w, lane);
+      rb.init(g.B, g.ldb, n0, g.N, kend, w, lane);
+      request(I0{}, 0);
+      request(I1{}, 1);
+      request(I2{}, 2);
+      request(I3{}, 3);
+      split_slot(I0{});
+      lay(0);
+      request(I0{}, 4);
+      meet();
+      // step s: products of s out of buffer s % 2, parts of s + 1 into the other, request of s + 5
+      auto step = [&](auto next, int s) {
+        if (ACTIVE) fetch(s & 1);
+        split_slot(next);
+        if (ACTIVE) multiply();
+        request(next, s + 5);
+        lay((s + 1) & 1);
+        if (ACTIVE) {
+          __builtin_amdgcn_sched_group_barrier(0x100, 12, 0);
+#pragma unroll
+          for (int i = 0; i < 24; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);        // a matrix instruction
+            __builtin_amdgcn_sched_group_barrier(0x002, kWideMix, 0);  // vector instructions
+          }
+        }
+        meet();
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      int s = 0;
+      for (; s + 5 <= steps; s += 4) {
+        step(I1{}, s);
+        step(I2{}, s + 1);
+        step(I3{}, s + 2);
+        step(I0{}, s + 3);
+      }
+      auto last = [&](auto next, int i) {  // (s is a multiple of four)
+        if (s + i >= steps) return;
+        if (s + i + 1 < steps) split_slot(next), lay((i + 1) & 1);
+        if (ACTIVE) fetch(i & 1), multiply();
+        meet();
+      };
+      last(I1{}, 0);
+      last(I2{}, 1);
+      last(I3{}, 2);
+      last(I0{}, 3);
+    }
+    if constexpr (!DZ_) {
+      // (k of DZ is the hidden width.)  The last 16 of a k range that is no multiple of 16 are the 16 that end it, the ones
+      // already counted as zeros on both sides; a range of fewer than 16 repeats its last, zeros likewise.
+      if (rest) {
+        const int k_read = max(kbeg, kend - 16);
+        ra.init(g.A, g.lda, m0, g.M, kend, w, lane);
+        rb.init(g.B, g.ldb, n0, g.N, kend, w, lane);
+        ra.load_trimmed(k_read, kbeg + 16 * steps, lane);
+        rb.load_trimmed(k_read, kbeg + 16 * steps, lane);
+        split_slot(I0{});
+        lay(0);
+        meet();
+        if (ACTIVE) fetch(0), multiply();
+      }
+    }
+  };
+  if (active) run(std::true_type{});
+  else run(std::false_type{});
+  float *C = g.C, *C_sum = g.colsum;
+  int64_t ldc = g.ldc;
+  if (split > 0) C = g.part + (int64_t)(split - 1) * (g.M + 1) * g.N, C_sum = C + (int64_t)g.M * g.N, ldc = g.N;
+  if constexpr (SUMS) {
+    const float t = cs + __shfl_xor(cs, 32);
+    const int n = n0 + 32 * w + rb.row(place);
+    if (half == 0 && n < g.N) C_sum[n] = t;
+  }
+  if (!active) return;
+  // Accumulator register i of lane l: row in place 8 (i / 4) + 4 (l / 32) + i % 4, column in place l % 32.
+  const int N = g.N, n = n0 + 64 * wn + rb.row(place);
+  auto finish = [&](auto full) {
+    constexpr bool FULL = decltype(full)::value;
+    const int na = FULL ? n : min(n, N - 1), nb = FULL ? n + 32 : min(n + 32, N - 1);
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      auto row_of = [&](int i) { return m0 + 64 * wm + 32 * x + ra.row(8 * (i >> 2) + 4 * half + (i & 3)); };
+      float h[16][2];
+      if constexpr (DZ_) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float *src = g.aux + (FULL ? row_of(i) : min(row_of(i), g.M - 1)) * ldc;
+          h[i][0] = src[na], h[i][1] = src[nb];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        f32x2 c = {acc[x][0][i], acc[x][1][i]};
+        if constexpr (DZ_) {
+          if (i & 1) c = -c;
+          c = f32x2{c[0] * (1.0f - h[i][0] * h[i][0]), c[1] * (1.0f - h[i][1] * h[i][1])};
+        }
+        float *dst = C + row_of(i) * ldc;
+        if (FULL || row_of(i) < g.M) {
+          if (FULL || n < N) dst[n] = c[0];
+          if (FULL || n + 32 < N) dst[n + 32] = c[1];
+        }
+      }
+    }
+  };
+  if (m0 + 64 * wm + 64 <= g.M && n0 + 64 * wn + 64 <= N) finish(std::true_type{});
+  else finish(std::false_type{});
+}
+
+__global__ __launch_bounds__(256, 2) void wide_products_kernel(ProbSet set) {
+  __shared__ __align__(16) unsigned char lds[kWideLds];
+  int i = 0;
+  while (i + 1 < set.n && (int)blockIdx.x >= set.p[i + 1].first_block) ++i;
+  const Prob &g = set.p[i];
+  // neighbouring tiles (which share rows of A) on one XCD: blocks are dealt out to the 8 XCDs in turn
+  const int local = (int)blockIdx.x - g.first_block, per = g.blocks >> 3, t = (local & 7) * per + (local >> 3);
+  if (t >= g.tiles * g.splits) return;
+  const int split = t / g.tiles, tile = t - split * g.tiles;
+  const int tm = tile / g.tiles_n, tn = tile - tm * g.tiles_n;
+  const int kbeg = split * g.k_chunk, kend = min(g.K, kbeg + g.k_chunk);
+  const int m0 = tm * kWide, n0 = tn * kWide;
+  if (g.kind == DZ) {
+    wide_product<DZ, false>(g, m0, n0, kbeg, kend, 0, lds);
+  } else if (tm == 0) {
+    wide_product<DW, true>(g, m0, n0, kbeg, kend, split, lds);
+  } else {
+    wide_product<DW, false>(g, m0, n0, kbeg, kend, split, lds);
   }
 }
 
@@ -1034,16 +1299,22 @@ hipError_t launch_products(hipStream_t st, ProbSet &set) {
     deepest = std::max(deepest, p.k_chunk);
   }
   // a wavefront per tile when that gives most SIMDs one
-  const bool own = waves >= kOwnTiles;
+  const bool own = waves >= kOwnTiles, wide = own && set.p[set.n - 1].kind == DZ;
   int32_t next = 0;
   for (int i = 0; i < set.n; ++i) {
     Prob &p = set.p[i];
-    const int64_t wg = own ? ((int64_t)p.tiles * p.splits + 3) / 4 : (int64_t)p.tiles * p.splits;
+    if (wide) {
+      p.tiles_n = (p.N + kWide - 1) / kWide;
+      p.tiles = (p.M + kWide - 1) / kWide * p.tiles_n;
+    }
+    const int64_t wg = own && !wide ? ((int64_t)p.tiles * p.splits + 3) / 4 : (int64_t)p.tiles * p.splits;
     p.first_block = next;
     p.blocks = (int32_t)((wg + 7) / 8 * 8);
     next += p.blocks;
   }
-  if (own) {
+  if (wide) {
+    hipLaunchKernelGGL(wide_products_kernel, dim3((unsigned)next), dim3(256), 0, st, set);
+  } else if (own) {
     hipLaunchKernelGGL((products_kernel<1, 0>), dim3((unsigned)next), dim3(256), 0, st, set);
   } else {
     const auto shared = [&](auto slots) {
@@ -1163,7 +1434,9 @@ hipError_t launch_ppo(hipStream_t st, const pr_ppo_config &c, const float *obs, 
     }
     LRN(hipGetLastError());
     set.n = 0;
-    for (int i = pass; i < (plan.together ? 2 : pass + 1); ++i) set.p[set.n++] = input_grad(i), set.p[set.n++] = weight_grad(i, 1);
+    // (the longer products first: behind the others they would be what a launch ends with)
+    for (int i = pass; i < (plan.together ? 2 : pass + 1); ++i) set.p[set.n++] = weight_grad(i, 1);
+    for (int i = pass; i < (plan.together ? 2 : pass + 1); ++i) set.p[set.n++] = input_grad(i);
     LRN(launch_products(st, set));
     set.n = 0;
     for (int i = pass; i < (plan.together ? 2 : pass + 1); ++i) set.p[set.n++] = weight_grad(i, 0), set.p[set.n++] = weight_grad(i, 2);

@@ -104,6 +104,14 @@ def test_learner_output_layers(B, D, K, Hd):
     test_learner_products_at_their_edges(B, D, K, Hd)
 
 
+# backward with a workgroup per 128 x 128 tile: a quarter, a half and three quarters of the columns, rows that end inside
+# each of a tile's halves; k ranges of one step, of fewer than are requested ahead, with and without a remainder
+@pytest.mark.parametrize("B,D,K,Hd", [(32001, 1, 1, 64), (65540, 1, 0, 32), (10930, 2, 0, 96), (8200, 1, 1, 160),
+                                      (8270, 1, 0, 224)])
+def test_learner_backward_tiles(B, D, K, Hd):
+    test_learner_products_at_their_edges(B, D, K, Hd)
+
+
 # the forward layers' three tiles (32 x 64, 16 x 64, 16 x 16): fewer k than a stage, no remainder, one of 5; fewer stages
 # than are requested ahead; rows that end inside a tile, half a tile of columns
 @pytest.mark.parametrize("B,D,K,Hd", [(11010, 3, 1, 160), (8195, 9, 2, 256), (5200, 5, 0, 96), (1000, 3, 1, 352),
