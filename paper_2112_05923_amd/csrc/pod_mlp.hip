@@ -480,7 +480,11 @@ __global__ __launch_bounds__(NW * 64) void mlp_tiles_kernel(TileArgs a) {
 // 4-byte aligned) behind the matrix work of the chunk before it, converted and dropped into the other buffer;
 // one barrier per chunk; the weight ring runs on across the chunks.  Rows past `rows` (ragged last tile) are
 // read as zeros and not stored.
-// Registers are what it lacks: with 512 units 221 spill (234 with a wide output layer), with 1024 units 16 (27).
+// No request stands behind a branch and the waits of its loops are for what they use: critic of 640000 rows of 1001 inputs
+// and 512 units 2056 -> 1715 us (with a branch around the rows' requests 221 registers spilled, and every chunk waited for
+// the weights just requested), 524288 rows of 3001 and 1024 units 5617 -> 4870, actor of 70001 x 1001 355 -> 259.  With 1024
+// units a workgroup draws 8.2 MB of weights through its L1 for 64 rows (64 bytes a cycle: 1.8 ms of the 4.9, as long as
+// the matrix instructions take at full rate).
 struct WideArgs {
   const float *X;
   int64_t ldx, rows;
@@ -518,34 +522,37 @@ __global__ __launch_bounds__(NW * 64) void mlp_wide_kernel(WideArgs a) {
     const int nrows = (int)min((int64_t)BM, a.rows - row0);
     const int agent = (int)(((a.row_base + row0) % a.N) / a.envs_per_agent);
     const Net net = net_of(a.net, agent);
-    const int nkb = net.nkb[0], nch = (nkb + CKB - 1) / CKB;
+    const int nkb = net.nkb[0], nfull = nkb / CKB, nch = (nkb + CKB - 1) / CKB;
 
+    // Every request is made, from inside the row: rows past the end re-read the last one, a group that reaches past the
+    // end of a row is read as the four floats that end there (S >= 4).  With a branch around a request the compiler, which
+    // then cannot count, waits at every chunk for all that is under way, the weights just requested included.
     f32x4 pre[NG];
     auto fetch = [&](int ch) {
 #pragma unroll
       for (int i = 0; i < NG; ++i) {
         const int idx = tid + NT * i;
-        const int row = idx / (CC / 4), col = ch * CC + 4 * (idx % (CC / 4));
-        f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (row < nrows) {
-          const float *src = a.X + (row0 + row) * a.ldx + col;
-          if (col + 3 < S) {
-            v = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(src));
-          } else {
-            if (col < S) v[0] = src[0];
-            if (col + 1 < S) v[1] = src[1];
-            if (col + 2 < S) v[2] = src[2];
-          }
-        }
-        pre[i] = v;
+        const int row = min(idx / (CC / 4), nrows - 1), col = ch * CC + 4 * (idx % (CC / 4));
+        pre[i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(a.X + (row0 + row) * a.ldx + min(col, S - 4)));
       }
     };
-    auto stash = [&](int buf) {
+    auto stash = [&](int ch) {
+      if ((ch + 1) * CC > S) {
+#pragma unroll
+        for (int i = 0; i < NG; ++i) {
+          const int col = ch * CC + 4 * ((tid + NT * i) % (CC / 4)), back = col - min(col, S - 4);
+          f32x4 v = pre[i];
+          if (back & 1) v = f32x4{v[1], v[2], v[3], 0.0f};
+          if (back & 2) v = f32x4{v[2], v[3], 0.0f, 0.0f};
+          if (back >= 4) v = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+          pre[i] = v;
+        }
+      }
 #pragma unroll
       for (int i = 0; i < NG; ++i) {
         const int idx = tid + NT * i;
         const int row = idx / (CC / 4), c4 = 4 * (idx % (CC / 4));
-        O::store4(ldsC + buf * cbuf + (size_t)row * a.cpitch + c4 * O::ESZ, pre[i][0], pre[i][1], pre[i][2], pre[i][3]);
+        O::store4(ldsC + (ch & 1) * cbuf + (size_t)row * a.cpitch + c4 * O::ESZ, pre[i][0], pre[i][1], pre[i][2], pre[i][3]);
       }
     };
 
@@ -563,15 +570,26 @@ __global__ __launch_bounds__(NW * 64) void mlp_wide_kernel(WideArgs a) {
         [&](int b, int f, float y) {
           if (b < nrows) Y[(size_t)b * O_dim + f] = y;
         },
-        [&](f32x16 (&acc)[CTH][2], u32x4 (&rg)[PD][CTH], bool act) {
-          if (act) prime<CTH, PD>(rg, net.W[0], nkb, net.nct[0], ct0, lane);
-          for (int ch = 0; ch < nch; ++ch) {
-            stash(ch & 1);
+        [&](f32x16 (&acc)[CTH][2], u32x4 (&rg)[PD][CTH], bool) {  // (NW CTH feature tiles: every wavefront has its own)
+          prime<CTH, PD>(rg, net.W[0], nkb, net.nct[0], ct0, lane);
+          const u32x4 *wp[CTH];
+#pragma unroll
+          for (int c = 0; c < CTH; ++c) wp[c] = net.W[0] + (size_t)(ct0 + c) * 64 + lane;
+#pragma unroll
+          for (int i = 0; i < NG; ++i) asm volatile("" : "+v"(pre[i]));  // (arrived: the loop's waits are for its own requests)
+          for (int ch = 0; ch < nfull; ++ch) {
+            stash(ch);
             __syncthreads();  // chunk ch complete; everybody is done with the buffer chunk ch + 1 goes into
-            if (ch + 1 < nch) fetch(ch + 1);
-            if (act)
-              mma_layer_range<true, CTH, 2, PD>(acc, rg, ldsC + (ch & 1) * cbuf, a.cpitch, ch * CKB,
-                                                min(nkb, (ch + 1) * CKB), nkb, net.W[0], net.nct[0], ct0, 0, lane);
+            fetch(min(ch + 1, nch - 1));
+            asm volatile("" ::: "memory");  // (requested here: behind the weights they would be waited for with them)
+            __builtin_amdgcn_sched_barrier(0);
+            mma_chunk<CTH, 2, PD, CKB>(acc, rg, ldsC + (ch & 1) * cbuf, a.cpitch, ch * CKB, nkb, wp, net.nct[0], lane);
+          }
+          if (nfull < nch) {
+            stash(nfull);
+            __syncthreads();
+            mma_layer_range<true, CTH, 2, PD>(acc, rg, ldsC + (nfull & 1) * cbuf, a.cpitch, nfull * CKB, nkb, nkb, net.W[0],
+                                              net.nct[0], ct0, 0, lane);
           }
         });
     __syncthreads();  // the hidden tile and the chunk buffers are free again
@@ -1423,7 +1441,7 @@ static bool try_launch_wide(hipStream_t st, const PackedNet &net, int64_t rows, 
                             int64_t ldx, float *Y, int32_t N, int32_t envs_per_agent, hipError_t *err) {
   const int Hd = net.out_dim[0];
   if (!net.bf16 || (Hd != 512 && Hd != 1024) || net.out_dim[1] != Hd || (reinterpret_cast<uintptr_t>(X) & 3u)) return false;
-  if (net.nct[2] > 32) return false;
+  if (net.nct[2] > 32 || net.in_dim[0] < 4) return false;
   if (envs_per_agent < N && envs_per_agent % tile::BM != 0) return false;  // a tile must not straddle two agents
   // measured: with 512 hidden units and at most a tile or two per compute unit the chunk-staged kernel below is
   // as fast or faster (its four-wavefront workgroups start sooner); long buffers and 1024 hidden units win here

@@ -178,7 +178,9 @@ __device__ inline void prime(B (&ring)[PD][CT], const u32x4 *W, int nkb, int nct
 // row-major [batch][k] in LDS with `pitch` bytes per row.  The ring must be primed for this layer.
 // The main loop has no branches (refills past the end re-read the last block), so the compiler's wait
 // counters stay exact and PD k-blocks of weights are really in flight behind the matrix instructions.
-template <bool BF16, int CT, int NBT, int PD>
+// ARRIVED: the ring is waited for before the loop.  Where how many requests stand behind its blocks depends on the way here,
+// the compiler otherwise has the loop wait for all that is under way in every round.
+template <bool BF16, int CT, int NBT, int PD, bool ARRIVED = false>
 __device__ inline void mma_layer(f32x16 (&acc)[CT][NBT], typename Op<BF16>::Block (&ring)[PD][CT], const unsigned char *ldsX, int pitch,
                                  int nkb, const u32x4 *W, int nct, int ct0, int bt0, int lane) {
   using O = Op<BF16>;
@@ -188,6 +190,12 @@ __device__ inline void mma_layer(f32x16 (&acc)[CT][NBT], typename Op<BF16>::Bloc
   const u32x4 *wp[CT];
 #pragma unroll
   for (int c = 0; c < CT; ++c) wp[c] = W + (size_t)min(ct0 + c, nct - 1) * NP + lane;
+  if constexpr (ARRIVED) {
+#pragma unroll
+    for (int s = 0; s < PD; ++s)
+#pragma unroll
+      for (int c = 0; c < CT; ++c) asm volatile("" : "+v"(ring[s][c]));
+  }
   int kb0 = 0;
   for (; kb0 + PD <= nkb; kb0 += PD) {
 #pragma unroll
@@ -271,6 +279,27 @@ __device__ inline void mma_layer_range(f32x16 (&acc)[CT][NBT], u32x4 (&ring)[PD]
 #pragma unroll
         for (int t = 0; t < NBT; ++t) O::mma(ring[s][c], x[t], acc[c][t]);
     }
+  }
+}
+
+// A whole chunk of CKB k-blocks: straight-line code, the loop over the chunks is the caller's.
+template <int CT, int NBT, int PD, int CKB>
+__device__ inline void mma_chunk(f32x16 (&acc)[CT][NBT], u32x4 (&ring)[PD][CT], const unsigned char *ldsX, int pitch, int kb_lo,
+                                 int nkb, const u32x4 *const (&wp)[CT], int nct, int lane) {
+  const unsigned char *xbase = ldsX + (size_t)(lane & 31) * pitch + 16 * (lane >> 5);
+#pragma unroll
+  for (int k = 0; k < CKB; ++k) {
+    u32x4 x[NBT];
+#pragma unroll
+    for (int t = 0; t < NBT; ++t) x[t] = *reinterpret_cast<const u32x4 *>(xbase + (size_t)t * 32 * pitch + k * 32);
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+      for (int t = 0; t < NBT; ++t) Op<true>::mma(ring[k % PD][c], x[t], acc[c][t]);
+    const size_t kn = min(kb_lo + k + PD, nkb - 1);
+#pragma unroll
+    for (int c = 0; c < CT; ++c) ring[k % PD][c] = wp[c][kn * nct * 64];
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 
@@ -613,6 +642,10 @@ __device__ inline void mlp_tile(const Net &net, typename Op<BF16>::Block (&ring)
                                 const float *ldsBias, const W3 &w3, int tid, Early early, Late late, Sink sink,
                                 Layer1 layer1 = Layer1()) {
   constexpr int PD = ring_depth(CTH);
+  constexpr bool CHUNKED = !std::is_same<Layer1, WholeTileLayer1>::value;
+  // (8 x 2 feature tiles: critic of 70000 rows of 166 inputs 187 -> 147 us, actor of 20001 x 181 103 -> 82; 8 x 4: 5140 ->
+  // 4870 for 524288 x 3001.  With one tile to a wavefront, up to 256 units, 52 -> 55.)
+  constexpr bool WAIT = BF16 && NW == 8 && CTH >= 2;
   // the wavefront index is uniform: tell the compiler, so that block addresses live in scalar registers
   const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ct0 = w * CTH;
@@ -621,7 +654,7 @@ __device__ inline void mlp_tile(const Net &net, typename Op<BF16>::Block (&ring)
   {
     f32x16 acc[CTH][NBT];
     zero_acc<CTH, NBT>(acc);
-    if constexpr (!std::is_same<Layer1, WholeTileLayer1>::value) {
+    if constexpr (CHUNKED) {
       layer1(acc, ring, act);
       if (act) prime<CTH, PD>(ring, net.W[1], net.nkb[1], net.nct[1], ct0, lane);
     } else if (act) {
@@ -629,7 +662,7 @@ __device__ inline void mlp_tile(const Net &net, typename Op<BF16>::Block (&ring)
       if (NKB1 > 0)
         mma_layer_static<BF16, CTH, NBT, PD, NKB1>(acc, ring, ldsX, xpitch, net.W[0], net.nct[0], ct0, 0, lane);
       else
-        mma_layer<BF16, CTH, NBT, PD>(acc, ring, ldsX, xpitch, net.nkb[0], net.W[0], net.nct[0], ct0, 0, lane);
+        mma_layer<BF16, CTH, NBT, PD, WAIT>(acc, ring, ldsX, xpitch, net.nkb[0], net.W[0], net.nct[0], ct0, 0, lane);
       prime<CTH, PD>(ring, net.W[1], net.nkb[1], net.nct[1], ct0, lane);
     }
     early();
@@ -640,7 +673,7 @@ __device__ inline void mlp_tile(const Net &net, typename Op<BF16>::Block (&ring)
       if (NKB2 > 0)
         mma_layer_static<BF16, CTH, NBT, PD, NKB2>(acc, ring, ldsH, hpitch, net.W[1], net.nct[1], ct0, 0, lane);
       else
-        mma_layer<BF16, CTH, NBT, PD>(acc, ring, ldsH, hpitch, net.nkb[1], net.W[1], net.nct[1], ct0, 0, lane);
+        mma_layer<BF16, CTH, NBT, PD, WAIT>(acc, ring, ldsH, hpitch, net.nkb[1], net.W[1], net.nct[1], ct0, 0, lane);
     }
     __syncthreads();  // every wavefront has consumed the layer-1 tile; it is overwritten in place
     if (act) epilogue_hidden<BF16, CTH, NBT>(acc, lb2, ldsH, hpitch, net.nct[1], ct0, 0, lane);
@@ -676,7 +709,7 @@ __device__ inline void mlp_tile(const Net &net, typename Op<BF16>::Block (&ring)
       f32x16 acc[CTO][NBT];
       zero_acc<CTO, NBT>(acc);
       prime<CTO, 2>(r4, net.W[2], net.nkb[2], net.nct[2], co0, lane);
-      mma_layer<BF16, CTO, NBT, 2>(acc, r4, ldsH, hpitch, net.nkb[2], net.W[2], net.nct[2], co0, 0, lane);
+      mma_layer<BF16, CTO, NBT, 2, WAIT>(acc, r4, ldsH, hpitch, net.nkb[2], net.W[2], net.nct[2], co0, 0, lane);
       epilogue_out<CTO, NBT, RAW_OUT>(acc, lb3, net.out_dim, net.out_tanh, net.nct[2], co0, 0, lane, sink);
     }
   }

@@ -184,6 +184,22 @@ def test_fp32_networks(N, rows, agents, Hd, D, K):
         parity.check_networks(w, d["actor"], d["critic"], X[sel], mu[sel], val[sel], agent=a)
 
 
+# bf16 networks whose input rows arrive in chunks: one partial chunk, whole ones with the row's end inside the last group of
+# four (S % 4 = 1, 2, 3, 0) and at a chunk's end, a ragged last tile; rows of three (which another kernel takes)
+@pytest.mark.parametrize("rows,Hd,D,K", [(70, 1024, 1, 1), (131, 1024, 3, 2), (200, 1024, 21, 1), (300, 1024, 9, 5), (64, 1024, 21, 13),
+                                         (65600, 512, 18, 5), (65599, 512, 100, 8), (90, 1024, 70, 1), (77, 1024, 1, 0)])
+def test_bf16_chunked_inputs(rows, Hd, D, K):
+    w = inputs.WORKLOADS["wide"].replace(n_envs=64, hidden=Hd, n_stocks=D, n_ind=K, steps=2)
+    d = inputs.make_all(w, horizon=2, n_market=1, steps=2)
+    cfg = pr.make_config(w, horizon=2, n_market=1, schedule=pr.PR_SCHED_STEPWISE)
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    ro = pr.Rollout(cfg, _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+    X = np.random.default_rng(rows).standard_normal((rows, w.state_dim)).astype(np.float32)
+    mu, val = (parity.to_np(ro.mlp_forward(net, _t(X))) for net in (pr.PR_NET_ACTOR, pr.PR_NET_CRITIC))
+    pick = np.unique(np.concatenate([np.arange(0, rows, max(1, rows // 100)), np.arange(max(0, rows - 70), rows)]))
+    parity.check_networks(w, d["actor"], d["critic"], X[pick], mu[pick], val[pick])
+
+
 # small networks, all steps in one launch: every instance (64 / 128 hidden units, few and many layer-1 blocks per wavefront),
 # a last workgroup that is not full, several agents, no indicators and rows that are no multiple of four of them
 @pytest.mark.parametrize("base,N,agents,Hd,D,K", [("tiny", 16, 1, 64, 5, 2), ("tiny", 17, 1, 64, 1, 0), ("tiny", 40, 1, 64, 30, 2),
