@@ -223,6 +223,7 @@ StepIO step_io(const pr_handle *h, const pr_buffers *o, int t, const float *mu, 
   io.done = o->done + (size_t)t * N;
   io.logp = o->logp ? o->logp + (size_t)t * N : nullptr;
   io.shadow = shadow;
+  io.ind_done = false;
   io.shares = o->shares ? o->shares + (size_t)t * N * D : nullptr;
   return io;
 }
@@ -377,13 +378,17 @@ int rollout_step_T(pr_handle *h, int32_t T, const float *noise, const pr_buffers
     POD_HIP(launch_observe(h->stream, h->dims, h->st, h->market.price, h->market.ind, out->obs, h->shadow));
     for (int t = 0; t < T; ++t) {
       float *mu = out->mu ? out->mu + (size_t)t * N * D : h->mu_scratch;
-      if (h->shadow.p)
-        POD_HIP(launch_layers(h->stream, h->actor_rot, (int64_t)N, h->shadow, mu, (int32_t)N, per_agent));
-      else
+      StepIO io = step_io(h, out, t, mu, noise, h->shadow);
+      if (h->shadow.p) {
+        IndicatorMove move{h->dims, h->st, h->market.ind, io.obs_next, h->shadow, false};
+        POD_HIP(launch_layers(h->stream, h->actor_rot, (int64_t)N, h->shadow, mu, (int32_t)N, per_agent,
+                              h->cfg.n_ind > 0 ? &move : nullptr));
+        io.ind_done = move.moved;
+      } else {
         POD_HIP(launch_mlp(h->stream, h->actor, (int64_t)N, out->obs + (size_t)t * N * S, (int64_t)S, mu, (int32_t)N,
                            per_agent));
-      POD_HIP(launch_env_step(h->stream, h->dims, h->st, h->market.price, h->market.ind,
-                              step_io(h, out, t, mu, noise, h->shadow)));
+      }
+      POD_HIP(launch_env_step(h->stream, h->dims, h->st, h->market.price, h->market.ind, io));
     }
   }
   if (out->value)

@@ -54,14 +54,14 @@ __global__ __launch_bounds__(kThreads) void observe_kernel(EnvDims d, EnvState s
 }
 
 // ----------------------------------------------------------------- env step
-// One launch per step: 512 threads step E envs (the trades: pod_trade.h).  The cursor is read by every thread of an env (no
+// One launch per step: 512 threads step E envs (the trades: pod_trade.h).  IND: the next observation's indicators too.  The cursor is read by every thread of an env (no
 // barrier in front of the prices), the market part of the next observation is requested together with the prices and
 // written while the orders are packed.
 // Measured per step (kernel trace): 2048 envs x 500 stocks x 4 indicators 106 -> 22 us, 5000 x 100 x 8 30.2 -> 18.6,
 // 16384 x 100 x 8 60 -> 37, 4096 x 30 x 8 12.3 -> 7.1, 16384 x 30 x 8 17.0 -> 15.5, 16 x 5 x 2 6.0 -> 3.8 (before: order
 // slots of up to 32 envs and a ledger over all of them in LDS, holdings stored stock-major and hence moved in short
 // runs).  The bytes of the first of these take 10 us.
-template <int E, int ND>
+template <int E, int ND, bool IND>
 __global__ __launch_bounds__(kEnvThreads, 4) void env_step_kernel(EnvDims d, EnvState s, const float *__restrict__ price,
                                                                  const float *__restrict__ ind, StepIO io) {
   using Tr = Trade<E, ND, false>;
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(kEnvThreads, 4) void env_step_kernel(EnvDims d, Env
 #pragma unroll
   for (int j = 0; j < NI; ++j) {
     const int g = tl + TPE * j;
-    if (g < NG) iv[j] = *reinterpret_cast<const env_f32x4u *>(irow + 4 * g);
+    if (IND && g < NG) iv[j] = *reinterpret_cast<const env_f32x4u *>(irow + 4 * g);
   }
 
   float *o = io.obs_next + (size_t)n * d.S;
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(kEnvThreads, 4) void env_step_kernel(EnvDims d, Env
             if (sp) sp[DK + 1 + dd] = (__bf16)v;
           }
         }
-        if (live) {
+        if (IND && live) {
 #pragma unroll
           for (int j = 0; j < NI; ++j) {
             const int g = tl + TPE * j;
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(kEnvThreads, 4) void env_step_kernel(EnvDims d, Env
       },
       [&]() {
         // indicator groups beyond the first NI of a thread (K > 8), and the last DK % 4 indicators
-        if (live) {
+        if (IND && live) {
           for (int g = tl + TPE * NI; g < NG; g += TPE) put(g, *reinterpret_cast<const env_f32x4u *>(irow + 4 * g));
           if (tl < (DK & 3)) {
             const float v = irow[4 * NG + tl] * d.s_ind;
@@ -310,14 +310,20 @@ hipError_t launch_observe(hipStream_t st, const EnvDims &d, const EnvState &s, c
   return hipGetLastError();
 }
 
-template <int E, int ND>
-static hipError_t launch_step(hipStream_t st, const EnvDims &d, const EnvState &s, const float *price, const float *ind,
-                              const StepIO &io) {
-  constexpr auto kern = env_step_kernel<E, ND>;
+template <int E, int ND, bool IND>
+static hipError_t launch_step_inst(hipStream_t st, const EnvDims &d, const EnvState &s, const float *price, const float *ind,
+                                   const StepIO &io) {
+  constexpr auto kern = env_step_kernel<E, ND, IND>;
   const hipError_t e = allow_full_lds<kern>();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)((d.N + E - 1) / E)), dim3(kEnvThreads), trade_lds(E, false, d.D), st, d, s, price, ind, io);
   return hipGetLastError();
+}
+
+template <int E, int ND>
+static hipError_t launch_step(hipStream_t st, const EnvDims &d, const EnvState &s, const float *price, const float *ind,
+                              const StepIO &io) {
+  return io.ind_done ? launch_step_inst<E, ND, false>(st, d, s, price, ind, io) : launch_step_inst<E, ND, true>(st, d, s, price, ind, io);
 }
 
 hipError_t launch_env_step(hipStream_t st, const EnvDims &d, const EnvState &s, const float *price, const float *ind,

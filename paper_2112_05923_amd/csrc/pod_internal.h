@@ -69,6 +69,19 @@ struct StepIO {
   float *logp;         // [N] or null
   int32_t *shares;     // [N, D] or null
   ObsShadow shadow;    // the next observation for the actor, or null
+  bool ind_done;       // the next observation's indicators are there already (IndicatorMove)
+};
+
+// Indicators of the observation after a step, which need nothing the step computes: launch_layers moves them beside the
+// policy's second or third layer (the first one reads the shadow they go to) where that leaves compute units idle, and
+// says so.
+struct IndicatorMove {
+  EnvDims d;
+  EnvState s;
+  const float *ind;
+  float *obs_next;
+  ObsShadow shadow;
+  bool moved;
 };
 
 hipError_t launch_observe(hipStream_t st, const EnvDims &d, const EnvState &s, const float *price, const float *ind,
@@ -166,7 +179,7 @@ bool mlp_supported(int S, int Hd, int O, int bf16);
 bool layers_supported(int64_t rows, int hidden, int bf16);
 int32_t layers_pitch(int cols);
 hipError_t launch_layers(hipStream_t st, const PackedNet &net, int64_t rows, const ObsShadow &x, float *Y, int32_t N,
-                         int32_t envs_per_agent);
+                         int32_t envs_per_agent, IndicatorMove *move = nullptr);
 // Few rows of either operand type: a launch per layer that splits the inputs over a workgroup's wavefronts.  `converted`:
 // the alternative has its rows in bf16 already.
 bool few_rows(int64_t rows, int S, int hidden, int bf16, bool converted);

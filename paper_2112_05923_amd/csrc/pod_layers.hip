@@ -6,6 +6,7 @@
 #include "pod_internal.h"
 
 #include "pod_tile.h"
+#include "pod_trade.h"
 
 namespace pod {
 
@@ -35,7 +36,40 @@ struct LayerArgs {
   int32_t tiles_r, tiles_f;    // 64-row and 128-feature tiles
   int32_t patch_r, patch_f;    // tiles per XCD in either direction
   int32_t split_f;             // XCDs side by side in the feature direction
+  int32_t first_move;          // blocks from here on move indicators
 };
+
+// A wavefront moves an env's row, four groups of four indicators to a lane at a time.  Bound by HBM, which the layer's own
+// workgroups leave idle; in the env step the move waited with the trades.  128 steps of 5000 envs x 100 stocks x 8 8.4 ->
+// 8.0 ms, 256 of 2048 x 500 x 4 21.5 -> 21.0.
+__device__ inline void move_indicators(const IndicatorMove &m, int n, int lane) {
+  const int DK = m.d.D * m.d.K, NG = DK / 4;
+  if (n >= m.d.N) return;
+  const float *src = m.ind + (size_t)rows_of(m.d, m.s.tau[n], m.s.start[n], n).row_obs * DK;
+  float *o = m.obs_next + (size_t)n * m.d.S + 1 + 2 * m.d.D;
+  __bf16 *sp = reinterpret_cast<__bf16 *>(m.shadow.p) + (size_t)n * m.shadow.pitch;
+  typedef f32x4 f32x4u __attribute__((aligned(4)));
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  for (int g0 = lane; g0 < NG; g0 += 4 * 64) {
+    f32x4 v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const f32x4u *>(src + 4 * min(g0 + 64 * i, NG - 1));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int g = g0 + 64 * i;
+      if (g < NG) {
+        const f32x4 y = v[i] * m.d.s_ind;
+        __builtin_nontemporal_store(y, reinterpret_cast<f32x4u *>(o + 4 * g));
+        *reinterpret_cast<bf16x4 *>(sp + 4 * g) = bf16x4{(__bf16)y[0], (__bf16)y[1], (__bf16)y[2], (__bf16)y[3]};
+      }
+    }
+  }
+  if (lane < (DK & 3)) {
+    const float y = src[4 * NG + lane] * m.d.s_ind;
+    o[4 * NG + lane] = y;
+    sp[4 * NG + lane] = (__bf16)y;
+  }
+}
 
 // The eight wavefronts are four k-groups of two; a group takes every fourth k-block, its wavefronts 64 rows x 64
 // features each (2 x 2 accumulators of 32 x 32): an LDS operand feeds two and a weight block two matrix instructions, and
@@ -48,7 +82,7 @@ struct LayerArgs {
 // KI = 16: 128 registers of weights and rows in flight, one workgroup per compute unit; KI = 8: half of that and two
 // workgroups per compute unit, for launches with more workgroups than compute units.
 template <int KI, bool HIDDEN>
-__global__ __launch_bounds__(kThreads, KI == 16 ? 2 : 4) void layer_kernel(LayerArgs a) {
+__global__ __launch_bounds__(kThreads, KI == 16 ? 2 : 4) void layer_kernel(LayerArgs a, IndicatorMove move) {
   extern __shared__ __align__(16) unsigned char lds[];
   constexpr int LB = KI / 4;               // k-blocks per group and iteration
   constexpr int NP = KI / 4;               // 16-byte pieces of the input rows per thread and iteration
@@ -56,6 +90,10 @@ __global__ __launch_bounds__(kThreads, KI == 16 ? 2 : 4) void layer_kernel(Layer
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), grp = wave >> 1, half = wave & 1;
 
+  if ((int)blockIdx.x >= a.first_move) {
+    move_indicators(move, ((int)blockIdx.x - a.first_move) * (kThreads / 64) + wave, lane);
+    return;
+  }
   // neighbouring tiles on one XCD (block b runs on XCD b % 8): a patch of patch_r x patch_f tiles shares its L2
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int sr = slot / a.patch_f, sf = slot - sr * a.patch_f;
@@ -243,13 +281,13 @@ __global__ __launch_bounds__(256) void rows_to_bf16_kernel(const float *__restri
 }
 
 template <int KI, bool HIDDEN>
-hipError_t launch_layer(hipStream_t st, const LayerArgs &a, unsigned blocks) {
+hipError_t launch_layer(hipStream_t st, const LayerArgs &a, unsigned blocks, const IndicatorMove &move) {
   constexpr auto kern = layer_kernel<KI, HIDDEN>;
   const hipError_t e = allow_full_lds<kern>();
   if (e != hipSuccess) return e;
   const size_t chunks = 2 * (size_t)kRows * (KI * 32 + 16);
   const size_t ends = 48 * 1024 + (size_t)kRows * (kFeatures * (HIDDEN ? 2 : 4) + 16);
-  hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), chunks > ends ? chunks : ends, st, a);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), chunks > ends ? chunks : ends, st, a, move);
   return hipGetLastError();
 }
 
@@ -263,7 +301,7 @@ bool layers_supported(int64_t rows, int hidden, int bf16) { return bf16 && hidde
 int32_t layers_pitch(int cols) { return (cols + 15) / 16 * 16 + 64; }
 
 hipError_t launch_layers(hipStream_t st, const PackedNet &net, int64_t rows, const ObsShadow &x, float *Y, int32_t N,
-                         int32_t envs_per_agent) {
+                         int32_t envs_per_agent, IndicatorMove *move) {
   const int Hd = net.out_dim[0];
   const void *in = x.p;
   int32_t pitch = x.pitch;
@@ -296,9 +334,21 @@ hipError_t launch_layers(hipStream_t st, const PackedNet &net, int64_t rows, con
     a.patch_r = (a.tiles_r + 8 / best - 1) / (8 / best), a.patch_f = (a.tiles_f + best - 1) / best;
     const unsigned blocks = 8u * (unsigned)(a.patch_r * a.patch_f);
     const bool two = blocks > 256;  // more workgroups than compute units
+    a.first_move = (int32_t)blocks;
+    IndicatorMove m{};
+    unsigned all = blocks;
+    // Indicators beside it, where half of the compute units have room for a workgroup of them (one or two are resident) and
+    // the launch is long enough.  Behind full compute units they take longer than in the env step, where they wait with the
+    // trades (a step of 8192 envs x 30 stocks 36.0 -> 40.7 us, of 2048 x 500 beside the second layer 64 -> 70), and longer
+    // than a launch of 32 k-blocks with a workgroup on half of the compute units (2048 x 400, 512 units 51.8 -> 53.5).
+    // Where they are moved: 2048 x 500 64 -> 62, 5000 x 100 53 -> 49.5, 4500 x 128 47.0 -> 45.6, 4200 x 40 36.9 -> 35.8.
+    if (l > 0 && move && !move->moved && (two ? blocks <= 384 : blocks <= 128 && a.nkb >= 64)) {
+      move->moved = true;
+      m = *move, all += (unsigned)((m.d.N + kThreads / 64 - 1) / (kThreads / 64));
+    }
     hipError_t e;
-    if (l < 2) e = two ? launch_layer<8, true>(st, a, blocks) : launch_layer<16, true>(st, a, blocks);
-    else e = two ? launch_layer<8, false>(st, a, blocks) : launch_layer<16, false>(st, a, blocks);
+    if (l < 2) e = two ? launch_layer<8, true>(st, a, all, m) : launch_layer<16, true>(st, a, all, m);
+    else e = two ? launch_layer<8, false>(st, a, all, m) : launch_layer<16, false>(st, a, all, m);
     if (e != hipSuccess) return e;
     in = a.Y;
     pitch = a.ldy;

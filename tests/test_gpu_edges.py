@@ -184,6 +184,33 @@ def test_fp32_networks(N, rows, agents, Hd, D, K):
         parity.check_networks(w, d["actor"], d["critic"], X[sel], mu[sel], val[sel], agent=a)
 
 
+# the next observation's indicators beside the policy's second layer (two workgroups a compute unit), its third, and in the
+# env step: one group of four and a remainder, a partial round of groups, rows that end inside a workgroup, episodes that end
+@pytest.mark.parametrize("N,Hd,D,K", [(4163, 512, 33, 3), (4100, 512, 7, 1), (5000, 512, 100, 8), (2049, 1024, 260, 1), (2000, 1024, 290, 4),
+                                      (1100, 512, 140, 2)])
+def test_stepwise_indicators(N, Hd, D, K):
+    T = 5
+    w = inputs.WORKLOADS["wide"].replace(n_envs=N, hidden=Hd, n_stocks=D, n_ind=K, steps=T)
+    d = inputs.make_all(w, horizon=2, n_market=1, steps=T)
+    cfg = pr.make_config(w, horizon=2, n_market=1, schedule=pr.PR_SCHED_STEPWISE)
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    recs = []
+    for forced in (False, True):   # (forced: no policy, all in the env step)
+        ro = pr.Rollout(cfg, _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+        out = ro.alloc_buffers(T, value=False, logp=True, mu=True, shares=True)
+        if forced:
+            ro.step_forced(T, recs[0]["mu"], _t(d["noise"]), out)
+        else:
+            ro.step_T(T, _t(d["noise"]), out)
+        torch.cuda.synchronize()
+        recs.append(out)
+    for k in ("obs", "act_raw", "reward", "done", "logp", "shares"):
+        assert torch.equal(recs[0][k], recs[1][k]), k
+    pick = np.arange(0, N, max(1, N // 60))
+    for t in (1, T - 1):   # the policy saw the bf16 copy of these rows
+        parity.check_networks(w, d["actor"], d["critic"], parity.to_np(recs[0]["obs"][t])[pick], parity.to_np(recs[0]["mu"][t])[pick])
+
+
 # bf16 networks whose input rows arrive in chunks: one partial chunk, whole ones with the row's end inside the last group of
 # four (S % 4 = 1, 2, 3, 0) and at a chunk's end, a ragged last tile; rows of three (which another kernel takes)
 @pytest.mark.parametrize("rows,Hd,D,K", [(70, 1024, 1, 1), (131, 1024, 3, 2), (200, 1024, 21, 1), (300, 1024, 9, 5), (64, 1024, 21, 13),
