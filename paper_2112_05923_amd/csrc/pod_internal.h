@@ -52,6 +52,24 @@ struct EnvDims {
   float s_cash, s_price, s_hold, s_ind;
 };
 
+// Market rows of a step by the cursor rule (whole numbers only).
+struct RowInfo {
+  int32_t row_now;   // market row the trades execute at
+  int32_t row_val;   // market row the portfolio is valued at (cursor + 1)
+  int32_t row_obs;   // market row of the next observation (of the env's start row after a reset)
+  int32_t done;
+};
+
+__device__ inline RowInfo rows_of(const EnvDims &d, int32_t tau, int32_t start, int32_t n) {
+  const int32_t m = d.M == 1 ? 0 : n;
+  RowInfo r;
+  r.row_now = tau * d.M + m;
+  r.row_val = (tau + 1) * d.M + m;
+  r.done = (tau + 1 - start == d.H);
+  r.row_obs = r.done ? start * d.M + m : r.row_val;
+  return r;
+}
+
 // Observations in bf16 as the layer-per-launch actor reads them: [N][pitch], columns in the order of its rotated first
 // layer [indicators | cash | prices | holdings | zeros].
 struct ObsShadow {

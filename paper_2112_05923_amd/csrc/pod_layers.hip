@@ -6,7 +6,6 @@
 #include "pod_internal.h"
 
 #include "pod_tile.h"
-#include "pod_trade.h"
 
 namespace pod {
 

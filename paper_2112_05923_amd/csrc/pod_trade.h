@@ -17,23 +17,6 @@ typedef float env_f32x4 __attribute__((ext_vector_type(4)));
 typedef env_f32x4 env_f32x4u __attribute__((aligned(4)));
 typedef double env_f64x2 __attribute__((ext_vector_type(2)));
 
-struct RowInfo {
-  int32_t row_now;   // market row the trades execute at
-  int32_t row_val;   // market row the portfolio is valued at (cursor + 1)
-  int32_t row_obs;   // market row of the next observation (0 after a reset)
-  int32_t done;
-};
-
-__device__ inline RowInfo rows_of(const EnvDims &d, int32_t tau, int32_t start, int32_t n) {
-  const int32_t m = d.M == 1 ? 0 : n;
-  RowInfo r;
-  r.row_now = tau * d.M + m;
-  r.row_val = (tau + 1) * d.M + m;
-  r.done = (tau + 1 - start == d.H);
-  r.row_obs = r.done ? start * d.M + m : r.row_val;
-  return r;
-}
-
 struct __attribute__((aligned(16))) Purchase {
   float k, u;   // wanted shares, unit cost
   double rcp;   // 1 / u in binary64

@@ -153,3 +153,22 @@ def test_bench_refuses_more_than_one_gpu_and_reads_the_recorded_traffic():
         assert got == pytest.approx(float(re.search(r"hbm_bytes_per_launch: (\d+)", text).group(1)))
     else:
         assert got is None
+
+
+def test_sources_that_share_the_trades_are_compiled_with_contraction_off():
+    """Share counts are decided by binary32 operations with one rounding each: every translation unit that sees their
+    header, directly or through another one, and the persistent bf16 rollout that has its own, must not contract."""
+    from paper_2112_05923_amd import build
+
+    def closure(name, seen):
+        text = open(os.path.join(build.CSRC, name)).read()
+        for inc in re.findall(r'^\s*#\s*include\s+"([^"]+)"', text, flags=re.M):
+            if inc not in seen and os.path.exists(os.path.join(build.CSRC, inc)):
+                seen.add(inc)
+                closure(inc, seen)
+        return seen
+
+    trading = {f for f in build.sources() if "pod_trade.h" in closure(f, set())} | {"pod_fused.hip"}
+    assert {"pod_env.hip", "pod_small.hip", "pod_fused_f32.hip"} <= trading
+    for f in sorted(trading):
+        assert "-ffp-contract=off" in build.PER_FILE.get(f, []), f
