@@ -259,7 +259,7 @@ def test_small_network_rollout(base, N, agents, Hd, D, K):
 # forward pass and both rollouts that keep their input tile give what fp32 sums give (a saturated unit, or NaN)
 @pytest.mark.parametrize("N,rows,Hd,D,K,fused", [(16, 16, 32, 3, 1, False), (64, 64 * 260 + 40, 256, 30, 8, False),
                                                  (128, 1000, 512, 30, 4, False), (64, 64, 256, 30, 8, True),
-                                                 (16, 40, 64, 5, 2, False), (32, 40, 128, 30, 8, False)])
+                                                 (4128, 40, 256, 30, 8, True), (16, 40, 64, 5, 2, False), (32, 40, 128, 30, 8, False)])
 def test_fp32_networks_with_nonfinite_numbers(N, rows, Hd, D, K, fused):
     w = inputs.WORKLOADS["dow30"].replace(n_envs=N, hidden=Hd, n_stocks=D, n_ind=K, steps=1)
     d = inputs.make_all(w, horizon=1, steps=1)
@@ -530,7 +530,8 @@ def _chain(x, w, b, act):
 # chunk, value head) and inside both rollouts.  tanh is the kernels' own (3e-7 at most, 1e-7 in the mean)
 @pytest.mark.parametrize("N,rows,Hd,D,K,fused", [(48, 48, 512, 30, 8, False), (4096, 4096, 256, 30, 8, False), (5000, 5000, 512, 30, 8, False),
                                                  (64, 64 * 260, 256, 30, 8, False), (128, 9000, 128, 17, 3, False), (48, 40, 32, 12, 2, False),
-                                                 (64, 64, 256, 30, 8, True), (96, 96, 256, 12, 4, True), (40, 40, 64, 5, 2, False), (33, 33, 128, 30, 8, False)])
+                                                 (64, 64, 256, 30, 8, True), (96, 96, 256, 12, 4, True), (4128, 48, 256, 30, 8, True), (4160, 48, 256, 12, 4, True),
+                                                 (40, 40, 64, 5, 2, False), (33, 33, 128, 30, 8, False)])
 def test_fp32_networks_are_as_precise_as_fp32_sums(N, rows, Hd, D, K, fused):
     w = inputs.WORKLOADS["dow30"].replace(n_envs=N, hidden=Hd, n_stocks=D, n_ind=K, steps=2)
     d = inputs.make_all(w, horizon=2, n_market=1, steps=2)
@@ -587,11 +588,13 @@ def test_fp32_value_head_tiles(N, rows, agents, D, K):
         parity.check_networks(w, d["actor"], d["critic"], X[sel], None, val[sel], agent=a)
 
 
-# the persistent rollout of fp32 networks: 16 envs per workgroup up to 4096 envs, 32 beyond; no block of market columns only
-# and almost all of them such, inputs that end inside a block of 32, all stock slots in use, several agents, one market for
-# all, episodes that end inside a call and on its last step, calls that go on where the last one stopped
+# the persistent rollout of fp32 networks: 16 envs per workgroup up to 4096 envs, 32 beyond; either with no block of market
+# columns only and with almost all of them such, inputs that end inside a block, all stock slots in use, the widest input tile,
+# several agents, one market for all, episodes that end inside a call and on its last step, calls that go on where the last
+# one stopped
 @pytest.mark.parametrize("N,agents,H,n_market,D,K", [(32, 1, 5, None, 1, 4), (64, 2, 7, 1, 32, 7), (96, 1, 3, None, 2, 2), (160, 5, 6, None, 12, 1),
-                                                     (4096, 1, 4, None, 28, 9), (4128, 1, 5, None, 30, 8), (8192, 2, 8, 1, 7, 4)])
+                                                     (4096, 1, 4, None, 28, 9), (4128, 1, 5, None, 30, 8), (8192, 2, 8, 1, 7, 4),
+                                                     (4128, 1, 4, None, 32, 7), (4160, 1, 3, 1, 31, 8), (4128, 1, 5, None, 1, 4), (8320, 5, 6, None, 2, 2)])
 def test_fused_fp32_env_counts(N, agents, H, n_market, D, K):
     if agents > 1:
         N = N // agents // 64 * 64 * agents or 64 * agents
