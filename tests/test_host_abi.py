@@ -77,11 +77,13 @@ def test_persistent_kernel_lds_fits_the_compute_unit_for_every_shape_it_accepts(
     schedule must accept the named workloads it is documented for."""
     limit = 160 * 1024
     seen = 0
-    for dtype, hiddens in ((1, (256, 512)), (0, (256,))):
+    # (fp32: 16 envs a workgroup up to 4096 of them, 32 beyond)
+    for dtype, hiddens, n_envs in ((1, (256, 512), 128), (0, (256,), 128), (0, (256,), 8192)):
         for hidden in hiddens:
             for D in (1, 2, 5, 17, 24, 30, 32):
                 for K in (1, 2, 4, 7, 8, 10, 16):
-                    w = inputs.WORKLOADS["large"].replace(n_envs=128, n_stocks=D, n_ind=K, hidden=hidden, mlp_dtype=dtype)
+                    w = inputs.WORKLOADS["large"].replace(n_envs=n_envs, n_stocks=D, n_ind=K, hidden=hidden,
+                                                          mlp_dtype=dtype)
                     cfg = pr.make_config(w, horizon=8, schedule=pr.PR_SCHED_FUSED)
                     try:
                         a, b = pr.kernel_lds_bytes(cfg, True), pr.kernel_lds_bytes(cfg, False)
@@ -89,8 +91,8 @@ def test_persistent_kernel_lds_fits_the_compute_unit_for_every_shape_it_accepts(
                         assert e.code == pr.PR_EUNSUPPORTED
                         continue
                     seen += 1
-                    assert 0 < b <= a <= limit, (dtype, hidden, D, K, a, b)
-    assert seen >= 40
+                    assert 0 < b <= a <= limit, (dtype, hidden, n_envs, D, K, a, b)
+    assert seen >= 60
     for name in ("large", "dow30", "tournament"):
         cfg = pr.make_config(inputs.WORKLOADS[name], schedule=pr.PR_SCHED_FUSED)
         assert pr.kernel_lds_bytes(cfg) <= limit
