@@ -15,11 +15,12 @@
 // The two kinds of wavefront run separate loops with the same barriers: neither's
 // registers are live in the other's code.
 //
-// Bound with 16 envs by the weight stream -- 850 KB a step, which a compute unit takes in
-// at 64 B a clock, 5.8 us at 2.3 GHz; 84 KB of layer 2 stay in LDS and the output layer's
-// 48 KB in registers (without either 12.3 us a step for 11.4) -- and by the chains beside
-// it: two epilogues of 1 us, trades 3 us.  With 32 envs the matrix instructions take as
-// long as the stream, and the chip clocks down to 1.7-1.9 GHz: 6 us of matrix work in 17.
+// Bound with 16 envs by the weight stream -- 800 KB a step, which a compute unit takes in
+// at 64 B a clock, 6.6 us at the 1.9 GHz this runs at; 84 KB of layer 2 stay in LDS and the
+// output layer's 48 KB in registers (without either 12.3 us a step for 11.4) -- and by the
+// chains beside it: two epilogues of 1 us, trades 3 us; the matrix pipe is busy 38 % of a
+// step.  With 32 envs the matrix instructions take as long as the stream: 8 us of 17.6, the
+// chip at 1.75-1.8 GHz (counters of both: profiles/pmc_fp32_kernels.txt).
 // 301 inputs, per step, against 32 envs whose eight wavefronts all take turns at network
 // and envs: 1024 envs 16.2 -> 8.2 us, 4096 16.9 -> 10.9, 8192 20.4 -> 17.2, 16384 37.9 ->
 // 34.0, 65536 of 64 agents 151 -> 135; 12 stocks x 4 indicators, 4096 envs, 14.2 -> 8.4.
@@ -557,7 +558,10 @@ hipError_t launch_geometry(hipStream_t st, F32Args a) {
   const size_t lds = lds_bytes<E>(d.S);
   if (d.N % E || a.envs_per_agent % E || trade_lds(E, true, d.D) > (size_t)E * HP || lds > (size_t)kMaxLdsBytes) return hipErrorInvalidValue;
   constexpr int KIN = Geometry<E>::KIN;
-  // straight-line layer 1 for the blocks of the named workloads
+  // Layer 1 in straight-line code, each block's inputs read a block ahead, for the blocks of 30 stocks x 8 indicators (289 to
+  // 320 or 304 inputs, 256 to 287 or 271 of them market columns).  us a step with numbers of blocks at run time and this:
+  // 16 envs, where layer 1 is a third of the chain, 1024 envs 9.7 -> 8.0, 4096 12.2 -> 9.9; 32 envs 65536 of 64 agents 0.4
+  // and 1.2 % on two chips, 8192 and 16384 level.
   if ((d.S + KIN - 1) / KIN == NK1 && (d.D * d.K + d.D) / KIN == NH) return launch_inst<E, NK1, NH>(st, a, lds);
   return launch_inst<E, 0, 0>(st, a, lds);
 }

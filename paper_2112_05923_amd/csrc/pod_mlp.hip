@@ -479,12 +479,13 @@ __global__ __launch_bounds__(NW * 64) void mlp_tiles_kernel(TileArgs a) {
 // CC input columns through two LDS buffers.  A chunk is fetched into registers (16-byte loads; rows need only be
 // 4-byte aligned) behind the matrix work of the chunk before it, converted and dropped into the other buffer;
 // one barrier per chunk; the weight ring runs on across the chunks.  Rows past `rows` (ragged last tile) are
-// read as zeros and not stored.
+// the last one again and not stored.
 // No request stands behind a branch and the waits of its loops are for what they use: critic of 640000 rows of 1001 inputs
 // and 512 units 2056 -> 1715 us (with a branch around the rows' requests 221 registers spilled, and every chunk waited for
 // the weights just requested), 524288 rows of 3001 and 1024 units 5617 -> 4870, actor of 70001 x 1001 355 -> 259.  With 1024
 // units a workgroup draws 8.2 MB of weights through its L1 for 64 rows (64 bytes a cycle: 1.8 ms of the 4.9, as long as
-// the matrix instructions take at full rate).
+// the matrix instructions take at full rate).  Registers that spill: 13 with 512 units (12 with several feature tiles of
+// outputs), 17 with 1024 (31).
 struct WideArgs {
   const float *X;
   int64_t ldx, rows;
@@ -1420,7 +1421,7 @@ static bool try_launch_value_f32(hipStream_t st, const PackedNet &net, int64_t r
     hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(512), lds, st, a);
     *err = hipGetLastError();
   };
-  // the observation width of the named workloads in straight-line code
+  // layer 1 in straight-line code for 289 to 304 inputs (30 stocks x 8 indicators): 9000 rows 25.4 -> 24.2 us, 16384 31.8 -> 30.5
   if (net.nkb[0] == 19) launch(std::integral_constant<int, 19>{});
   else launch(std::integral_constant<int, 0>{});
   return true;
