@@ -13,7 +13,7 @@
 // -- depend on the cursor only and travel behind the network.
 // Per step, before (a network launch or three and an env launch) -> now:
 //   fp32,  64 hidden units: 16 envs x 5 stocks 19.6 -> 3.6 us, 512 x 30 x 8 indicators 30 -> 5.1, 16384 x 30 x 8 55 -> 21
-//   fp32, 128: 64 x 10 x 2 27 -> 5.5, 512 x 30 x 8 37 -> 10.9 (121 of its registers spill; 26 with up to 160 inputs),
+//   fp32, 128: 64 x 10 x 2 27 -> 5.5, 512 x 30 x 8 37 -> 10.9 (129 of its registers spill; 28 with up to 160 inputs),
 //   4096 x 30 x 8 40 -> 15
 //   bf16, 128: 512 x 30 x 8 30 -> 4.2, 16384 x 30 x 8 38 -> 18
 #include "pod_internal.h"
@@ -355,7 +355,7 @@ hipError_t launch_dtype(hipStream_t st, const SmallArgs &a) {
 // 64 or 128 hidden units, up to 320 inputs and 32 stocks: what eight wavefronts hold in registers.
 // A round of workgroups, one per compute unit, is 4096 envs.  The launches per step that take over cost about 17 us and
 // then grow more slowly, so the line lies where they win over a rollout of 24 steps; us per step, this kernel and those:
-//   fp32, 128 units, 301 inputs (121 registers spill): 4096 envs 15.1 and 21.7, 8192 30.5 and 34.9, 12288 45.7 and 42.7,
+//   fp32, 128 units, 301 inputs (129 registers spill): 4096 envs 15.1 and 21.7, 8192 30.5 and 34.9, 12288 45.7 and 42.7,
 //   65536 241 and 152; 171 inputs: 8192 29.0 and 29.3, 12288 43.5 and 34.1
 //   fp32, 128 units, 151 inputs: 4096 6.6 and 19.1, 65536 104 and 116; 61 inputs: 65536 97 and 103
 //   fp32, 64 units, 301 inputs: 4096 5.4 and 18.0, 65536 83 and 136; bf16, 128 units, 301 inputs: 65536 71 and 86

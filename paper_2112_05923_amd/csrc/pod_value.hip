@@ -9,12 +9,15 @@ namespace {
 
 using namespace stream;
 
-// Bound by the matrix cores and the power they draw: with random numbers in all operands the chip runs this kernel at 1.55
-// GHz, the matrix pipe busy 63 % of the time (with zeros it takes 8.9 us where it takes 12.0; without the tanh work and all
-// but the first LDS reads of a chunk, 10.3).  A workgroup takes 128 rows of one agent at a time (pod_stream.h); the rows'
-// own inputs come straight from memory into the registers of the lanes that multiply them, two k-blocks ahead.
+// Bound by the matrix cores and the power they draw: with random numbers in all operands the chip runs this kernel at
+// 1.65-1.75 GHz, the matrix pipe busy 66-69 % of the cycles (profiles/pmc_fp32_kernels.txt); with zeros it takes 8.4 us
+// where it takes 11.5, without the tanh work and all but the first LDS reads of a chunk 10.1.  A workgroup takes 128 rows of
+// one agent at a time (pod_stream.h); the rows' own inputs come straight from memory into the registers of the lanes that
+// multiply them, two k-blocks ahead.
 // 301 inputs, per 32 rows and compute unit, against 64-row tiles shared by eight wavefronts that keep taking the next one:
 // 8.5 million rows of 64 agents 14.1 -> 11.9 us, 2.1 million of one agent 13.9 -> 11.7.
+// 21 registers spill (88 bytes a lane), at a tile's ends and between its layers: none in the loop of layer 1, the one place
+// that counts requests, where one behind the copies would lengthen the wait and not shorten it.
 struct ValueRowsArgs {
   const float *X;  // rows x S, dense
   float *Y;
