@@ -459,9 +459,10 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 512, 2) void products_kernel(ProbSe
 // both operands of the 128 x 128 tile, takes them apart and lays them into LDS as the matrix instructions want them: half
 // the requests and half the vector instructions of a wavefront for itself.  One barrier for 16 k; the parts of the next
 // 16 are formed behind the products of the present ones (six vector instructions to a matrix instruction of 32 cycles).
-// Bound by the matrix rate, which the power limit keeps at 1.7 GHz under such a load: 27 us at 15000 samples x 256 units
-// for the launch that takes 65 (79 with a wavefront for itself), 230 at 32768 x 512 for 410 (484); 3000 x 512 54 (62),
-// 33000 x 64, where half of the tile is empty, 49 (65).  The launch of weight gradients alone stays with a wavefront for
+// Where it is long, matrix and vector work are about level and half overlapped: at 32768 samples x 512 units the matrix
+// pipe is busy 53 % of the cycles, at 1.7-1.9 GHz, the vector pipe 51 %; at 15000 x 256, a tile or two to a workgroup, 41 % each
+// (profiles/pmc_fp32_kernels.txt).  The launch at 15000 x 256 takes 65 us (79 with a wavefront for itself), at 32768 x 512
+// 410 (484); 3000 x 512 54 (62), 33000 x 64, where half of the tile is empty, 49 (65).  The launch of weight gradients alone stays with a wavefront for
 // itself: 271 or 181 rows and 30 columns leave more of 128 x 128 empty (8192 x 512 57 us for 44, 32768 x 512 196 for 185,
 // 15000 x 256 60 for 64).  Operands fetched a step ahead with three buffers: 69 and 425 us in place of 65 and 410.
 constexpr int kWideMix = 6;                     // vector instructions to a matrix instruction
@@ -746,9 +747,9 @@ __global__ __launch_bounds__(256, 2) void wide_products_kernel(ProbSet set) {
 // and batch size).
 // A wavefront owns 16 TX rows x 16 TY columns and reads its operands straight from global memory into registers, DEPTH - 1
 // stages of 16 k ahead: no LDS and no barrier, so a SIMD's matrix unit has work whenever one of its wavefronts does.
-// Bound by the fp32 matrix rate where a launch is long (32 cycles an instruction: 27 us for the first layer of 15000
-// samples, 271 inputs and 256 units; it takes 62, the tanh 5 of it, where slices through LDS with a barrier each took 80);
-// otherwise by requests, of which a compute unit takes one in about 24 cycles, and by the round trips at either end.
+// Bound by the fp32 matrix rate where a launch is long (32 cycles an instruction: the matrix pipe is busy 74 and 67 % of the
+// cycles at 32768 samples x 512 units, 57 % at 15000 x 256, at 1.9-2.05 GHz; there the first layer takes 60 us, the tanh 5 of
+// it, where slices through LDS with a barrier each took 80); otherwise by requests, of which a compute unit takes one in about 24 cycles, and by the round trips at either end.
 // Three shapes (both layers together, us; slices through LDS in brackets):
 //                                             2 x 4    1 x 4    1 x 1
 //   15000 samples x 256 units (7504 tiles)      115      140      213    (147)
@@ -1233,7 +1234,8 @@ struct Plan {
 
 // A tile reads 64 rows of a few cache lines each.  Rows of 512 floats are 2 KiB apart: all of a tile's lines then fall
 // on a handful of L2 channels (measured: 25 us for a product that takes 13 us with rows of 544), and rows a multiple of
-// 128 bytes apart on one bank of the L1 (16 rows x 64 bytes: 62 cycles a request, 33 with rows of 528).
+// 128 bytes apart on one bank of the L1 (16 rows x 64 bytes: 62 cycles a request, 33 with rows of 528).  A step at batch
+// 1024 x 512 units with rows of 544 and of 528: 88.0 and 86.0 us; gradients of 3000 to 32768 samples within half a percent.
 int row_floats(int Hd, bool padded) { return padded ? Hd + 16 : Hd; }
 bool wants_padding(int Hd) { return Hd % 128 == 0; }
 
@@ -1434,7 +1436,8 @@ hipError_t launch_ppo(hipStream_t st, const pr_ppo_config &c, const float *obs, 
     }
     LRN(hipGetLastError());
     set.n = 0;
-    // (the longer products first: behind the others they would be what a launch ends with)
+    // (the longer products first: behind the others they would be what a launch ends with.  Gradients at 15000 samples x 256
+    // units 282 -> 275 us, 33000 x 64 207 -> 201.5; 32768 x 512, many rounds of workgroups, 1254 -> 1268; others level)
     for (int i = pass; i < (plan.together ? 2 : pass + 1); ++i) set.p[set.n++] = weight_grad(i, 1);
     for (int i = pass; i < (plan.together ? 2 : pass + 1); ++i) set.p[set.n++] = input_grad(i);
     LRN(launch_products(st, set));

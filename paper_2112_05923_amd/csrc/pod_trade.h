@@ -70,6 +70,9 @@ __device__ inline float serial_sum(float s, const env_f32x4 *v, int n) {
 //    stocks 3.97 -> 3.60 us a step, 30 stocks 5.16 -> 4.98); where others want the same issue slots it is the other way
 //    round (env_step_kernel, 16384 envs x 30 stocks 15.5 us against 16.3, 4096 x 64 8.0 against 9.1);
 //  - up to a wavefront per env there is no barrier in here: an env's threads only meet each other.
+// The reciprocals of the unit costs (unit_of) are the caller's, before its actions are known, and with WALK so is the account
+// value: rollout_small_kernel, which had both in here, 16 envs x 5 stocks 3.55 -> 3.47 us a step, 512 x 30 with 64 units 5.30
+// -> 5.11, bf16 with 128 4.61 -> 4.38, fp32 with 128 level.
 template <int E, int ND, bool WALK, int NT = kEnvThreads>
 struct Trade {
   static constexpr int TPE = NT / E;
