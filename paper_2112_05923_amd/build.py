@@ -24,7 +24,8 @@ COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 PER_FILE = {"pod_env.hip": ["-ffp-contract=off"], "pod_fused.hip": ["-ffp-contract=off"], "pod_fused_f32.hip": ["-ffp-contract=off"],
-            "pod_population.hip": ["-ffp-contract=off"], "pod_small.hip": ["-ffp-contract=off"]}
+            "pod_population.hip": ["-ffp-contract=off"], "pod_small.hip": ["-ffp-contract=off"],
+            "pod_table.hip": ["-ffp-contract=off"]}
 
 
 def sources():

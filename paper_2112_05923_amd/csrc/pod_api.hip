@@ -28,6 +28,10 @@ struct pr_handle {
   void *split[3];         // hidden activations and input of the layer-per-launch networks (small batches) of a rollout
   void *query[3];         // the same for rollout_mlp_forward, whose launches for one call are enqueued under `enqueue`
   pthread_mutex_t enqueue;
+  int32_t table_rows;     // rows of the market
+  void *table_w[2][2];    // shared tables: layer 1 of either network, market and portfolio part (null: another schedule)
+  float *table_p;         // and its sums over market rows
+  int32_t *tau0;          // [N] cursors at the start of a rollout
   int32_t S;
 };
 
@@ -58,6 +62,7 @@ struct Layout {
   size_t w[2][3], b[2][3];
   size_t w1_rot;
   size_t cash, tau, h, ep_ret, ep_sum, ep_sqsum, ep_cnt, mu, start, split[3], query[3];
+  size_t table_w[2][2], table_p, tau0;
   size_t total;
 };
 
@@ -65,7 +70,7 @@ int state_dim(const pr_config &c) { return 1 + 2 * c.n_stocks + c.n_stocks * c.n
 
 // the stepwise policy of small bf16 batches reads a bf16 copy of the observations, written along with them
 bool uses_shadow(const pr_config &c) {
-  return c.schedule == PR_SCHED_STEPWISE && !small_supported(c) && layers_supported(c.n_envs, c.hidden, c.mlp_dtype) &&
+  return c.schedule == PR_SCHED_STEPWISE && !small_supported(c) && !table_supported(c) && layers_supported(c.n_envs, c.hidden, c.mlp_dtype) &&
          !few_rows(c.n_envs, state_dim(c), c.hidden, c.mlp_dtype, true);
 }
 
@@ -78,6 +83,11 @@ bool market_first(const pr_config &c) { return c.schedule == PR_SCHED_FUSED && c
 int rotated_blocks(const pr_config &c) {
   const int nkb = (state_dim(c) + 15) / 16;
   return market_first(c) ? (nkb + 1) & ~1 : nkb;
+}
+
+// k-blocks of the market (0) and the portfolio (1) part of layer 1 in rollouts over a shared table
+int table_blocks(const pr_config &c, int part) {
+  return part == 0 ? table_market_blocks(c.n_stocks, c.n_ind) : table_portfolio_blocks(c.n_stocks);
 }
 
 int validate_config(const pr_config *c) {
@@ -138,6 +148,12 @@ Layout make_layout(const pr_config &c) {
     for (int i = 0; i < 2; ++i) scratch[i] = take(bf ? rows * layers_pitch(Hd) * 2 : rows * Hd * 4);
     scratch[2] = take(bf ? rows * layers_pitch(S) * 2 : 0);
   }
+  if (table_supported(c)) {
+    for (int net = 0; net < 2; ++net)
+      for (int part = 0; part < 2; ++part) L.table_w[net][part] = take(packed_weight_bytes(16 * table_blocks(c, part), Hd, bf));
+    L.table_p = take(table_scratch_bytes(c.n_envs));
+    L.tau0 = take(N * 4);
+  }
   L.total = off;
   return L;
 }
@@ -196,13 +212,24 @@ int pack_nets(pr_handle *h, const pr_weights *actor, const pr_weights *critic) {
     const int in_dim[3] = {S, Hd, Hd};
     const int out_dim[3] = {Hd, Hd, net == 0 ? D : 1};
     for (int l = 0; l < 3; ++l)
-      jobs[n++] = {W[l], b[l], h->w_packed[net][l], h->b_packed[net][l], in_dim[l], out_dim[l], (in_dim[l] + 15) / 16, 0, 0};
+      jobs[n++] = {W[l], b[l], h->w_packed[net][l], h->b_packed[net][l], in_dim[l], out_dim[l], (in_dim[l] + 15) / 16, {{0, 0, in_dim[l]}}};
   }
   // The persistent rollout kernel keeps its observation tile as [indicators | cash | prices | holdings] (and so do
   // the one for small networks and the bf16 copy of the observations): the same layer-1 weights with their rows rotated
   // by the D K indicator columns (biases are shared).
-  if (h->w1_rot)
-    jobs[n++] = {actor->W1, actor->b1, h->w1_rot, h->b_packed[0][0], S, Hd, rotated_blocks(c), D * c.n_ind, market_first(c) ? 1 : 0};
+  const int DK = D * c.n_ind;
+  if (h->w1_rot) {
+    const int cash = market_first(c) ? 1 : 0;  // the cash behind the others, or in front of them
+    jobs[n++] = {actor->W1, actor->b1, h->w1_rot, h->b_packed[0][0], S, Hd, rotated_blocks(c),
+                 {{0, 1 + 2 * D, DK}, {DK, cash, 1 + 2 * D - cash}, {S - cash, 0, cash}}};
+  }
+  // Over a shared table layer 1 is taken in two parts: [indicators | prices], and [holdings | zeros | cash].
+  for (int net = 0; net < 2 && h->table_w[0][0]; ++net) {
+    jobs[n++] = {ws[net]->W1, ws[net]->b1, h->table_w[net][0], h->b_packed[net][0], S, Hd, table_blocks(c, 0),
+                 {{0, 1 + 2 * D, DK}, {(DK + 3) & ~3, 1, D}}};
+    jobs[n++] = {ws[net]->W1, ws[net]->b1, h->table_w[net][1], h->b_packed[net][0], S, Hd, table_blocks(c, 1),
+                 {{0, 1 + D, D}, {16 * table_blocks(c, 1) - 1, 0, 1}}};
+  }
   POD_HIP(launch_pack_layers(h->stream, jobs, n, P, bf));
   return PR_OK;
 }
@@ -210,6 +237,13 @@ int pack_nets(pr_handle *h, const pr_weights *actor, const pr_weights *critic) {
 int check_buffers(const pr_buffers *o) {
   if (!o || !o->obs || !o->act_raw || !o->reward || !o->done) return PR_EINVAL;
   return PR_OK;
+}
+
+TableNet table_net(const pr_handle *h, int net) {
+  TableNet t;
+  t.Wm = h->table_w[net][0], t.Wp = h->table_w[net][1];
+  for (int l = 0; l < 3; ++l) t.W[l] = h->w_packed[net][l], t.b[l] = h->b_packed[net][l];
+  return t;
 }
 
 StepIO step_io(const pr_handle *h, const pr_buffers *o, int t, const float *mu, const float *noise, const ObsShadow &shadow) {
@@ -293,6 +327,13 @@ int rollout_init(const pr_config *cfg, const pr_market *market, const pr_weights
   h->start = reinterpret_cast<int32_t *>(ws + L.start);
   for (int i = 0; i < 3; ++i) h->split[i] = ws + L.split[i], h->query[i] = ws + L.query[i];
   h->st.start = h->start;
+  h->table_rows = cfg->horizon + 1;
+  if (table_supported(*cfg)) {
+    for (int net = 0; net < 2; ++net)
+      for (int part = 0; part < 2; ++part) h->table_w[net][part] = ws + L.table_w[net][part];
+    h->table_p = reinterpret_cast<float *>(ws + L.table_p);
+    h->tau0 = reinterpret_cast<int32_t *>(ws + L.tau0);
+  }
 
   EnvDims &d = h->dims;
   d.N = cfg->n_envs;
@@ -358,6 +399,7 @@ int rollout_set_replay(pr_handle *h, const pr_market *table, int32_t table_rows,
   if (bad) return PR_EINVAL;
   POD_HIP(hipMemcpyAsync(h->start, start, (size_t)h->cfg.n_envs * 4, hipMemcpyDeviceToDevice, h->stream));
   h->market = *table;
+  h->table_rows = table_rows;
   POD_HIP(launch_state_reset(h->stream, h->dims, h->st));
   return PR_OK;
 }
@@ -368,7 +410,16 @@ int rollout_step_T(pr_handle *h, int32_t T, const float *noise, const pr_buffers
   if (rc != PR_OK) return rc;
   const size_t N = (size_t)h->cfg.n_envs, D = (size_t)h->cfg.n_stocks, S = (size_t)h->S;
   const int32_t per_agent = h->cfg.n_envs / h->cfg.n_agents;
-  if (h->cfg.schedule == PR_SCHED_FUSED) {
+  if (h->table_p) {
+    const TableMarket m{h->market.price, h->market.ind, h->table_rows};
+    POD_HIP(launch_rollout_table(h->stream, h->dims, h->st, m, table_net(h, 0), h->table_p, h->tau0, T, noise, *out, compute_units()));
+    const int64_t rows = (int64_t)(T + 1) * (int64_t)N;
+    if (out->value && value_table_covers(rows, (int32_t)N, h->table_rows)) {
+      POD_HIP(launch_value_table(h->stream, h->dims, h->st, m, table_net(h, 1), h->table_p, h->tau0, rows, out->obs, out->value,
+                                 compute_units()));
+      return PR_OK;
+    }
+  } else if (h->cfg.schedule == PR_SCHED_FUSED) {
     POD_HIP(launch_rollout_fused(h->stream, h->cfg, h->dims, h->st, h->market.price, h->market.ind, h->actor_rot,
                                  per_agent, T, noise, nullptr, *out));
   } else if (small_supported(h->cfg)) {

@@ -174,15 +174,20 @@ int64_t split_scratch_rows(int64_t n_envs, int hidden);
 
 size_t packed_weight_bytes(int in_dim, int out_dim, int bf16);
 int padded_out(int out_dim);
-// One layer to pack, in nkb k-blocks (zeros behind the last input).  The last k_rot inputs come first, and of the others
-// the first k_last come last.
+// Inputs `at` .. `at` + count - 1 of a packed layer are rows `row` .. of its weights.
+struct PackRun {
+  int32_t at, row, count;
+};
+// One layer to pack, in nkb k-blocks: its rows in up to three runs, zeros elsewhere.
 struct PackJob {
   const float *W, *b;  // [P, in_dim, out_dim], [P, out_dim]
   void *Wp;
   float *bp;
-  int32_t in_dim, out_dim, nkb, k_rot, k_last;
+  int32_t in_dim, out_dim, nkb;
+  PackRun run[3];
 };
-constexpr int kMaxPackJobs = 7;  // three layers of two networks, and the actor's first layer in the rollout's order
+// three layers of two networks, and the actor's first layer in the rollout's order or both first layers in their parts
+constexpr int kMaxPackJobs = 10;
 hipError_t launch_pack_layers(hipStream_t st, const PackJob *jobs, int n, int P, int bf16);
 // rows of X [rows, ldx] -> Y [rows, out_dim[2]]; row r uses agent ((r % N) / envs_per_agent).
 hipError_t launch_mlp(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx, float *Y,
@@ -193,6 +198,7 @@ bool value_rows_covers(int64_t rows, int32_t N, int32_t envs_per_agent);
 hipError_t launch_value_rows(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, float *Y, int32_t N,
                              int32_t envs_per_agent, int cus);
 bool mlp_supported(int S, int Hd, int O, int bf16);
+int compute_units();  // of the device the library was first used on
 // The bf16 layer-per-launch path: x holds the rows (columns up to x.cols zero-padded) in the order layer 1 was packed for.
 bool layers_supported(int64_t rows, int hidden, int bf16);
 int32_t layers_pitch(int cols);
@@ -228,5 +234,29 @@ bool small_supported(const pr_config &c);
 hipError_t launch_rollout_small(hipStream_t st, const EnvDims &d, const EnvState &s, const float *price, const float *ind,
                                 const PackedNet &actor, int32_t envs_per_agent, int32_t T, const float *noise,
                                 const pr_buffers &out);
+
+// Stepwise rollouts of bf16 networks over one shared market table (pod_table.hip): the market part of layer 1 is formed per
+// table row into P (or per env and step, where those are fewer or the table is longer than P), everything else in one launch.
+bool table_supported(const pr_config &c);
+int table_market_blocks(int D, int K);
+int table_portfolio_blocks(int D);
+int64_t table_rows_kept(int64_t n_envs);
+size_t table_scratch_bytes(int64_t n_envs);
+struct TableMarket {
+  const float *price, *ind;
+  int32_t rows;
+};
+struct TableNet {
+  const void *Wm, *Wp;    // layer 1: inputs [indicators | prices], and [holdings | zeros | cash]
+  const void *W[3];       // the layers behind it
+  const float *b[3];
+};
+// tau0: [N], receives the cursors the call starts at.
+hipError_t launch_rollout_table(hipStream_t st, const EnvDims &d, const EnvState &s, const TableMarket &m, const TableNet &actor,
+                                float *P, int32_t *tau0, int32_t T, const float *noise, const pr_buffers &out, int cus);
+// The value head over the observations of such a rollout, where they are at least twice the table's rows.
+bool value_table_covers(int64_t rows, int32_t n_envs, int32_t table_rows);
+hipError_t launch_value_table(hipStream_t st, const EnvDims &d, const EnvState &s, const TableMarket &m, const TableNet &critic,
+                              float *P, const int32_t *tau0, int64_t rows, const float *obs, float *Y, int cus);
 
 }  // namespace pod

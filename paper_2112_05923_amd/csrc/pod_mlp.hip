@@ -1170,13 +1170,28 @@ __global__ __launch_bounds__(256) void pack_layers_kernel(PackArgs a) {
   if (agent >= (uint32_t)a.P) return;
   const int col = (int)ct * 32 + (lane & 31), g = lane >> 5;
   const float *Wa = jb.W + (size_t)agent * jb.in_dim * jb.out_dim;
+  // (a k-block inside one run, as nearly all are, needs no search per input)
   float v[8];
+  int first = -1;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int k = kb * 16 + 8 * g + e;
-    const int rest = jb.in_dim - jb.k_rot, kr = k - jb.k_rot + jb.k_last;
-    const int ks = k < jb.k_rot ? rest + k : kr < rest ? kr : kr - rest;
-    v[e] = (k < jb.in_dim && col < jb.out_dim) ? Wa[(size_t)ks * jb.out_dim + col] : 0.0f;
+  for (int i = 0; i < 3; ++i)
+    if (kb * 16 >= jb.run[i].at && kb * 16 + 16 <= jb.run[i].at + jb.run[i].count) first = kb * 16 - jb.run[i].at + jb.run[i].row;
+  if (first >= 0) {
+    const float *w = Wa + (size_t)(first + 8 * g) * jb.out_dim + min(col, jb.out_dim - 1);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = w[(size_t)e * jb.out_dim];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = col < jb.out_dim ? v[e] : 0.0f;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int k = kb * 16 + 8 * g + e;
+      int ks = -1;
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+        if ((unsigned)(k - jb.run[i].at) < (unsigned)jb.run[i].count) ks = k - jb.run[i].at + jb.run[i].row;
+      v[e] = (ks >= 0 && col < jb.out_dim) ? Wa[(size_t)ks * jb.out_dim + col] : 0.0f;
+    }
   }
   bf16x8 *dst = static_cast<bf16x8 *>(jb.Wp) + (size_t)unit * (a.bf16 ? 64 : 192) + lane;
   if (a.bf16) {

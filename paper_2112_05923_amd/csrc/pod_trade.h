@@ -80,6 +80,7 @@ struct Trade {
   static constexpr int NCW = TPE / CW;            // wavefronts per env
   static constexpr int CHUNK = CW < 16 ? CW : 16; // purchases tried in full together
   static_assert((!WALK || NCW == 1) && CW % CHUNK == 0 && CHUNK % 4 == 0 && (NT & (NT - 1)) == 0, "");
+  int me;  // the thread; a kernel that loops over steps sets an opaque copy in each, or what follows from it is kept across them
   int D, D4, lp, sp, op;
   Purchase *list;  // [E][lp] purchases in stock order (odd pitch in 16 bytes)
   float *sell;     // [E][sp] proceeds of the sales, 0 elsewhere
@@ -94,7 +95,7 @@ struct Trade {
   float *now;      // several wavefronts per env (whose registers are few): [E][D4] prices of the trades
   double *terms;   // WALK: [E][D4] holdings' values after the trades, in stock order
 
-  __device__ Trade(unsigned char *lds, int D_) : D(D_), D4((D_ + 3) & ~3), lp(D_ | 1), sp(D4 + 4), op(D4 + 20) {
+  __device__ Trade(unsigned char *lds, int D_) : me(threadIdx.x & (NT - 1)), D(D_), D4((D_ + 3) & ~3), lp(D_ | 1), sp(D4 + 4), op(D4 + 20) {
     list = reinterpret_cast<Purchase *>(lds);
     sell = reinterpret_cast<float *>(list + E * lp);
     sq = sell + E * sp;
@@ -144,7 +145,7 @@ struct Trade {
   __device__ inline void run(const EnvDims &d, bool live, const float (&a_raw)[ND], const float (&eps)[ND], const float (&pn)[ND],
                              const Unit &units, const float (&pv)[ND], int32_t (&h)[ND], int32_t (&q)[ND], float &cash, double &r,
                              float &e2, bool want_e2, Market market, Rest rest, Booked booked) {
-    const int tid = threadIdx.x & (NT - 1), lane = tid & 63;
+    const int tid = me, lane = tid & 63;
     const int e = tid / TPE, tl = tid & (TPE - 1), cw = tl / CW, cl = lane & (CW - 1);
     const float cash_in = cash;
     auto mine_of = [&](uint64_t all) {  // the env's part of a ballot
@@ -355,7 +356,7 @@ struct Trade {
 
   // WALK: the account value after run(), in stock order (all of an env's threads take it)
   __device__ inline double value(float cash) const {
-    const env_f64x2 *t = reinterpret_cast<const env_f64x2 *>(terms + ((threadIdx.x & (NT - 1)) / TPE) * D4);
+    const env_f64x2 *t = reinterpret_cast<const env_f64x2 *>(terms + (me / TPE) * D4);
     double v = (double)cash;
     meet();
 #pragma unroll 4
@@ -367,8 +368,8 @@ struct Trade {
     return v;
   }
   __device__ inline void put_term(int i, double term) {  // of the thread's i-th stock, of the D4
-    const int t = threadIdx.x & (NT - 1), dd = (t & (TPE - 1)) + TPE * i;
-    if (dd < D4) terms[(t / TPE) * D4 + dd] = term;
+    const int dd = (me & (TPE - 1)) + TPE * i;
+    if (dd < D4) terms[(me / TPE) * D4 + dd] = term;
   }
 };
 

@@ -1,0 +1,86 @@
+"""Rollouts of bf16 networks over one shared market table (n_market = 1, 33 to 128 stocks, 512 hidden units): the kernels
+of pod_table.hip, which form the market part of layer 1 once per table row or once per env and step."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import parity
+from paper_2112_05923_amd import inputs
+from paper_2112_05923_amd import podrollout as pr
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+# (envs, stocks, indicators, table rows, horizon, steps of a call): both sizes of a workgroup (up to 16 envs, up to 32) with
+# full and ragged last ones, every instance of the portfolio blocks at its edges (33, 63 | 64, 95 | 96, 127 | 128 stocks) and
+# of the output layer (2, 3, 4 feature tiles), rows that end anywhere in a group of four, episodes that end inside a call.
+CASES = [
+    (200, 100, 8, 90, 40, 90),      # by table row
+    (37, 33, 1, 64, 20, 24),
+    (37, 63, 3, 2000, 11, 30),      # by env and step
+    (4200, 64, 2, 60, 7, 9),        # two rounds' worth of 16: 17 envs a workgroup
+    (8192, 95, 1, 50, 5, 6),
+    (5000, 96, 3, 300, 9, 10),
+    (9001, 127, 1, 40, 4, 5),       # more than 32 for every compute unit
+    (300, 128, 2, 80, 30, 33),
+    (16, 101, 5, 33, 32, 40),
+    (1, 40, 8, 64, 8, 20),
+    (1500, 35, 1, 64000, 64, 90),   # a table longer than the rows kept: in pieces of 42 steps
+]
+
+
+def _setup(N, D, K, rows, H, T):
+    w = inputs.WORKLOADS["large"].replace(n_envs=N, n_stocks=D, n_ind=K, steps=T, hidden=512, cost=2.0e-3)
+    d = inputs.make_all(w, horizon=min(rows, 500) - 1, n_market=1, steps=T)
+    if rows > 500:  # (a price path that long runs into the smallest numbers: the same 500 rows again and again)
+        for k in ("price", "ind"):
+            d[k] = np.ascontiguousarray(np.resize(d[k], (rows,) + d[k].shape[1:]))
+    rng = np.random.default_rng(N + D)
+    start = rng.integers(0, rows - H, N).astype(np.int32)
+    start[0], start[N - 1] = 0, rows - 1 - H
+    dev = lambda net: {k: torch.from_numpy(v).to(DEV) for k, v in net.items()}
+    price, ind = torch.from_numpy(d["price"]).to(DEV), torch.from_numpy(d["ind"]).to(DEV)
+    cfg = pr.make_config(w, horizon=H, n_market=1, schedule=pr.PR_SCHED_STEPWISE)
+    ro = pr.Rollout(cfg, price[:H + 1], ind[:H + 1], dev(d["actor"]), dev(d["critic"]))
+    ro.set_replay(price, ind, torch.from_numpy(start).to(DEV))
+    return w, d, start, ro, torch.from_numpy(d["noise"]).to(DEV)
+
+
+@pytest.mark.parametrize("N,D,K,rows,H,T", CASES)
+def test_rollout_over_a_shared_table(N, D, K, rows, H, T):
+    """Environment stage of sampled envs bit for bit on the recorded means, networks within the stated tolerance on sampled
+    rows, and the same bits when the rollout is cut into calls (whose market sums are formed by env and step)."""
+    w, d, start, ro, noise = _setup(N, D, K, rows, H, T)
+    out = ro.alloc_buffers(T, value=True, logp=True, mu=True, shares=True)
+    ro.step_T(T, noise, out)
+    end = ro.get_state()
+    S = w.state_dim
+    rec = {k: parity.to_np(v) for k, v in out.items()}
+    pick = np.unique(np.concatenate([np.arange(min(N, 40)), np.arange(max(0, N - 40), N), np.arange(0, N, max(1, N // 50))]))
+    sub = {k: np.ascontiguousarray(v[:, pick]) for k, v in rec.items()}
+    ocfg = oracle.cfg_from_workload(w.replace(n_envs=len(pick)), horizon=H)
+    ost = oracle.State(ocfg, len(pick), start=start[pick])
+    chk, ost = parity.check_env_record(w.replace(n_envs=len(pick)), ocfg, sub, d["price"], d["ind"],
+                                       np.ascontiguousarray(d["noise"][:, pick]), sub["mu"], state0=ost)
+    assert np.array_equal(parity.to_np(end["cursor"])[pick], ost.tau) and np.array_equal(parity.to_np(end["cash"])[pick], ost.cash)
+    assert np.array_equal(parity.to_np(end["holdings"])[pick], ost.h)
+    ts = sorted({0, min(H, T) - 1, min(H, T - 1), T - 1})
+    few = pick[:: max(1, len(pick) // 24)]
+    parity.check_networks(w, d["actor"], d["critic"], rec["obs"][ts][:, few].reshape(-1, S), rec["mu"][ts][:, few].reshape(-1, D),
+                          rec["value"][ts][:, few].reshape(-1))
+    # every value against the critic asked about the recorded observations
+    again = ro.mlp_forward(pr.PR_NET_CRITIC, out["obs"].view(-1, S))
+    parity.check_two_tier("value", parity.to_np(out["value"]).reshape(1, -1), parity.to_np(again).reshape(1, -1), True)
+    ro.reset()
+    cut = ro.alloc_buffers(T, value=False, logp=True, mu=True, shares=True)
+    t = 0
+    for n in [1, 2, T - 3 - T // 3, T // 3]:
+        part = {k: v[t:t + n + (k == "obs")] for k, v in cut.items()}
+        ro.step_T(n, noise[t:t + n].contiguous(), part)
+        t += n
+    assert t == T
+    for k, v in cut.items():
+        assert torch.equal(v, out[k]), k
+    for k, v in ro.get_state().items():
+        assert torch.equal(v, end[k]), k
