@@ -247,7 +247,7 @@ template <int E, int KBP>
 __global__ __launch_bounds__(NT, 2) void rollout_table_kernel(TableArgs a) {
   using G = TableGeo<E, KBP>;
   constexpr int TPE = G::TPE, ND = G::ND, XP = G::XP;
-  using Tr = Trade<E, ND, false>;
+  using Tr = Trade<E, ND, false, kEnvThreads, true>;
   extern __shared__ __align__(16) unsigned char lds[];
   const EnvDims &d = a.d;
   const int D = d.D, DK = D * d.K, S = d.S, NG = DK / 4;

@@ -73,14 +73,17 @@ __device__ inline float serial_sum(float s, const env_f32x4 *v, int n) {
 // The reciprocals of the unit costs (unit_of) are the caller's, before its actions are known, and with WALK so is the account
 // value: rollout_small_kernel, which had both in here, 16 envs x 5 stocks 3.55 -> 3.47 us a step, 512 x 30 with 64 units 5.30
 // -> 5.11, bf16 with 128 4.61 -> 4.38, fp32 with 128 level.
-template <int E, int ND, bool WALK, int NT = kEnvThreads>
+// SET: the kernel sets the thread's index `me`, an opaque copy of it in each step, or what follows from it is kept across them.
+// (Held where nobody sets it, it costs rollout_small_kernel 2 %.)
+template <int E, int ND, bool WALK, int NT = kEnvThreads, bool SET = false>
 struct Trade {
   static constexpr int TPE = NT / E;
   static constexpr int CW = TPE < 64 ? TPE : 64;  // the part of a wavefront one env has
   static constexpr int NCW = TPE / CW;            // wavefronts per env
   static constexpr int CHUNK = CW < 16 ? CW : 16; // purchases tried in full together
   static_assert((!WALK || NCW == 1) && CW % CHUNK == 0 && CHUNK % 4 == 0 && (NT & (NT - 1)) == 0, "");
-  int me;  // the thread; a kernel that loops over steps sets an opaque copy in each, or what follows from it is kept across them
+  int me;
+  __device__ inline int thread() const { return SET ? me : threadIdx.x & (NT - 1); }
   int D, D4, lp, sp, op;
   Purchase *list;  // [E][lp] purchases in stock order (odd pitch in 16 bytes)
   float *sell;     // [E][sp] proceeds of the sales, 0 elsewhere
@@ -145,7 +148,7 @@ struct Trade {
   __device__ inline void run(const EnvDims &d, bool live, const float (&a_raw)[ND], const float (&eps)[ND], const float (&pn)[ND],
                              const Unit &units, const float (&pv)[ND], int32_t (&h)[ND], int32_t (&q)[ND], float &cash, double &r,
                              float &e2, bool want_e2, Market market, Rest rest, Booked booked) {
-    const int tid = me, lane = tid & 63;
+    const int tid = thread(), lane = tid & 63;
     const int e = tid / TPE, tl = tid & (TPE - 1), cw = tl / CW, cl = lane & (CW - 1);
     const float cash_in = cash;
     auto mine_of = [&](uint64_t all) {  // the env's part of a ballot
@@ -356,7 +359,7 @@ struct Trade {
 
   // WALK: the account value after run(), in stock order (all of an env's threads take it)
   __device__ inline double value(float cash) const {
-    const env_f64x2 *t = reinterpret_cast<const env_f64x2 *>(terms + (me / TPE) * D4);
+    const env_f64x2 *t = reinterpret_cast<const env_f64x2 *>(terms + (thread() / TPE) * D4);
     double v = (double)cash;
     meet();
 #pragma unroll 4
@@ -368,8 +371,8 @@ struct Trade {
     return v;
   }
   __device__ inline void put_term(int i, double term) {  // of the thread's i-th stock, of the D4
-    const int dd = (me & (TPE - 1)) + TPE * i;
-    if (dd < D4) terms[(me / TPE) * D4 + dd] = term;
+    const int t = thread(), dd = (t & (TPE - 1)) + TPE * i;
+    if (dd < D4) terms[(t / TPE) * D4 + dd] = term;
   }
 };
 
