@@ -44,3 +44,24 @@ def test_value_head_of_numbers_of_all_sizes(D, K):
     err = np.abs(y - want) / np.sqrt(np.mean(want * want))
     for first in range(12):
         assert err[first::97].max() <= 4e-6, (first, err[first::97].max())
+
+
+# The persistent rollout forms the market part of layer 1 over a scale of the row's own: envs whose indicators are 1e12, 1e6 and
+# 1e3 times smaller than prices, as large, 1e9 times larger, or all zero; both sizes of a workgroup, blocks of market columns
+# that are full and not, one and two blocks of portfolio columns.  Bounds as above: what the scale loses is 2^-39 of the row's
+# largest number.
+@pytest.mark.parametrize("N,D,K", [(64, 30, 8), (4128, 30, 8), (96, 12, 4), (32, 32, 7), (4160, 32, 7), (32, 1, 4)])
+def test_rollout_of_markets_of_all_sizes(N, D, K):
+    w = inputs.WORKLOADS["dow30"].replace(n_envs=N, n_agents=1, n_stocks=D, n_ind=K, steps=2)
+    d = inputs.make_all(w, horizon=2, steps=2)
+    sizes = np.array([1e-12, 1e-6, 1e-3, 1.0, 1e9, 0.0], np.float32)
+    d["ind"] = d["ind"] * sizes[np.arange(N) % 6][None, :, None]
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    ro = pr.Rollout(pr.make_config(w, horizon=2, schedule=pr.PR_SCHED_FUSED), _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+    out = ro.alloc_buffers(2, value=False, logp=False, mu=True, shares=False)
+    ro.step_T(2, _t(d["noise"]), out)
+    torch.cuda.synchronize()
+    X, mu = parity.to_np(out["obs"])[:2].reshape(2 * N, -1).astype(np.float64), parity.to_np(out["mu"]).reshape(2 * N, D)
+    n = {k: v[0].astype(np.float64) for k, v in d["actor"].items()}
+    want = np.tanh(np.tanh(np.tanh(X @ n["W1"] + n["b1"]) @ n["W2"] + n["b2"]) @ n["W3"] + n["b3"])
+    assert np.abs(mu - want).max() / np.sqrt(np.mean(want * want)) <= 4e-6
