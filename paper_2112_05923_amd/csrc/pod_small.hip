@@ -48,64 +48,102 @@ struct SmallArgs {
   int32_t *shares;     // opt [T, N, D]
 };
 
-template <int NCT>
+// A product of 16 features x 32 inputs x the 16 envs: lane l holds inputs 8 (l / 16) + 0..7 of feature (env) l % 16 and gets
+// the sums of features 4 (l / 16) + 0..3 of env l % 16.  fp32: the three largest of the six products in a chain of their own.
+struct Sums {
+  f32x4 hi = {0.0f, 0.0f, 0.0f, 0.0f}, lo = {0.0f, 0.0f, 0.0f, 0.0f};
+};
+__device__ inline f32x4 mfma16(const u32x4 &w, const u32x4 &x, const f32x4 &c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c, 0, 0, 0);
+}
+__device__ inline void mma16(const u32x4 &w, const u32x4 &x, Sums &s) { s.hi = mfma16(w, x, s.hi); }
+__device__ inline void mma16(const tile::Blk3 &w, const tile::Blk3 &x, Sums &s) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    s.lo = mfma16(w.p[kSplitA[i]], x.p[kSplitB[i]], s.lo);
+    s.hi = mfma16(w.p[kSplitA[3 + i]], x.p[kSplitB[3 + i]], s.hi);
+  }
+}
+
+template <int HD>
 struct Geometry {
-  static constexpr int HD = 32 * NCT;          // hidden units
-  static constexpr int KG = kWaves / NCT;      // wavefronts that share a feature tile's k-blocks
-  static constexpr int F = HD * SE / kEnvThreads;  // features per thread between the layers
-  static constexpr int PP = HD + 4;            // row pitch of a plane of partial sums
-  static constexpr int NKB = HD / 16;          // k-blocks of layers 2 and 3
+  static constexpr int TILES = HD / 16;       // feature tiles of a hidden layer
+  static constexpr int WT = kWaves / TILES;   // wavefronts that share one
+  static constexpr int F = 4 / WT;            // features of a lane that its wavefront takes through tanh
+  static constexpr int KS = HD / 32;          // k-steps of layers 2 and 3
+};
+constexpr int kMeanPitch = 36, kSharePitch = 66;  // floats: partial means of an env; a wavefront's sums of a feature
+
+// What a step's trades need of a stock's price, in LDS.
+struct __attribute__((aligned(16))) Quote {
+  float price, cost;  // and the unit cost of a purchase
+  double rcp;         // 1 / cost
 };
 
-// NCT: hidden feature tiles (2 or 4); B1: layer-1 k-blocks per wavefront
-template <bool BF16, int NCT, int B1>
+inline size_t small_lds(int KS, bool split, bool apart, int xpitch, int hpitch, int D) {
+  return (size_t)SE * (xpitch + 2 * hpitch) + (size_t)KS * SE * kMeanPitch * 4 + (split ? (size_t)kWaves * 2 * kSharePitch * 4 : 0) +
+         (apart ? 2 * (size_t)SE * (D | 1) * sizeof(Quote) + 2 * SE * 4 : 0) + trade_lds(SE, true, D) +
+         (apart ? (size_t)SE * ((D + 3) & ~3) * 8 : 0);
+}
+
+// HD: hidden units; KS1: k-steps (of 32 inputs) of layer 1; SPLIT: the two wavefronts of a feature tile take half of them each;
+// APART: four wavefronts trade, with 16 threads to an env, and the others move the market and keep the books beside them; or all
+// eight do all of it, 32 threads to an env
+template <bool BF16, int HD, int KS1, bool SPLIT, bool APART>
 __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs a) {
   using namespace tile;
   using O = Op<BF16>;
   using Block = typename O::Block;
-  using Gm = Geometry<NCT>;
-  using Tr = Trade<SE, 1, true>;
-  constexpr int TPE = Tr::TPE, NI = 4, KG = Gm::KG, F = Gm::F, B2 = Gm::NKB / KG;
-  constexpr int XP = tile_pitch<BF16>(B1 * KG), HP = tile_pitch<BF16>(Gm::NKB);
+  using Gm = Geometry<HD>;
+  using Tr = Trade<SE, 1, true, APART ? kEnvThreads / 2 : kEnvThreads>;
+  constexpr int TPE = Tr::TPE, NI = 4, F = Gm::F, KS = Gm::KS, NCT = HD / 32, NP = 64 * kPlanes<Block>;
+  static_assert(!SPLIT || (Gm::WT == 2 && KS1 % 2 == 0), "");
+  constexpr int B1 = SPLIT ? KS1 / 2 : KS1;
+  constexpr int XP = tile_pitch<BF16>(2 * KS1), HP = tile_pitch<BF16>(2 * KS);
   extern __shared__ __align__(16) unsigned char lds[];
   const EnvDims &d = a.d;
-  const int D = d.D, DK = D * d.K, S = d.S, NG = DK / 4;
-  unsigned char *ldsX = lds, *ldsH = ldsX + SE * XP;
-  float *part = reinterpret_cast<float *>(ldsH + SE * HP);  // [KG][SE][PP], and [NKB][SE][36] for the output layer
-  unsigned char *ldsT = reinterpret_cast<unsigned char *>(part + (KG * Gm::PP > Gm::NKB * 36 ? KG * Gm::PP : Gm::NKB * 36) * SE);
-  Tr trade(ldsT, D);
+  const int D = d.D, DK = D * d.K, S = d.S, NG = DK / 4, D4 = (D + 3) & ~3, QP = D | 1;
+  unsigned char *ldsX = lds, *ldsH1 = ldsX + SE * XP, *ldsH2 = ldsH1 + SE * HP;
+  float *means = reinterpret_cast<float *>(ldsH2 + SE * HP);  // [KS][SE][kMeanPitch]
+  float *share = means + KS * SE * kMeanPitch;                // SPLIT: [kWaves][2][kSharePitch]
+  // APART, by the step's parity: [2][SE][QP], [2][SE] cash after the trades, and a second set of the trades' terms
+  Quote *quotes = reinterpret_cast<Quote *>(share + (SPLIT ? kWaves * 2 * kSharePitch : 0));
+  float *balance = reinterpret_cast<float *>(quotes + (APART ? 2 * SE * QP : 0));
+  Tr trade(reinterpret_cast<unsigned char *>(balance + (APART ? 2 * SE : 0)), D);
+  double *const terms0 = trade.terms;
+  auto terms_of = [&](int t) { trade.terms = APART ? terms0 + (t & 1) * SE * D4 : terms0; };
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int e = tid / TPE, tl = tid & (TPE - 1), dd = min(tl, D - 1);
+  const bool trader = !APART || w < kWaves / 2, keeper = !APART || !trader;
+  const int e = trade.thread() / TPE, tl = tid & (TPE - 1), dd = min(tl, D - 1);  // of either kind: its env, lane of the env, stock
   const int n0 = blockIdx.x * SE, n = min(n0 + e, d.N - 1);
   const bool live = n0 + e < d.N, own = live && tl < D;
   const size_t N = (size_t)d.N;
 
-  // -- the network: this wavefront's weight blocks, this thread's biases
+  // -- the network: this wavefront's weight blocks, this lane's biases
   const Net net = net_of(a.net, (n0 % d.N) / a.envs_per_agent);
-  const int ct = w % NCT, kg = w / NCT;
-  Block w1[B1], w2[B2], w3;
-#pragma unroll
-  for (int i = 0; i < B1; ++i) {
-    const int kb = kg + KG * i;
-    w1[i] = Block{};
-    if (kb < net.nkb[0]) fetch_w(w1[i], net.W[0] + ((size_t)kb * NCT + ct) * (64 * kPlanes<Block>) + lane);
-  }
-  // (fp32 with 128 hidden units: layer 2's blocks would not fit next to the others and are read again in every step)
-  constexpr bool KEEP2 = BF16 || NCT == 2;
-  auto fetch2 = [&](int lane_f) {
-#pragma unroll
-    for (int i = 0; i < B2; ++i) fetch_w(w2[i], net.W[1] + ((size_t)(kg + KG * i) * NCT + ct) * (64 * kPlanes<Block>) + lane_f);
+  const int ft = w % Gm::TILES, wt = w / Gm::TILES;  // feature tile of layers 1 and 2, and which of its wavefronts this is
+  const int ot = w & 1, ok = w >> 1;                 // output tile and k-step of layer 3
+  const int q4 = lane >> 4, row = lane & 15;
+  // (packed blocks are 32 features x 16 inputs)
+  auto fetch = [&](Block &b, const u32x4 *W, int nct, int nkb, int tile, int ks) {
+    const int kb = 2 * ks + (q4 >> 1);
+    fetch_w(b, W + ((size_t)min(kb, nkb - 1) * nct + (tile >> 1)) * NP + (tile & 1) * 16 + row + 32 * (q4 & 1));
+    if (kb >= nkb) b = Block{};
   };
-  if (KEEP2) fetch2(lane);
-  fetch_w(w3, net.W[2] + (size_t)min(w, Gm::NKB - 1) * (64 * kPlanes<Block>) + lane);
-  const int f0 = tl * F;  // this thread's features of row e, between the layers
+  Block w1[B1], w2[KS], w3;
+#pragma unroll
+  for (int i = 0; i < B1; ++i) fetch(w1[i], net.W[0], NCT, net.nkb[0], ft, SPLIT ? wt * B1 + i : i);
+#pragma unroll
+  for (int i = 0; i < KS; ++i) fetch(w2[i], net.W[1], NCT, 2 * KS, ft, i);
+  fetch(w3, net.W[2], 1, 2 * KS, ot, min(ok, KS - 1));
+  const int f0 = 16 * ft + 4 * q4 + F * wt;  // the first of this lane's features of env `row`
   float bias1[F], bias2[F];
 #pragma unroll
   for (int i = 0; i < F; ++i) bias1[i] = net.b[0][f0 + i], bias2[i] = net.b[1][f0 + i];
   const float bias3 = net.b[2][tl];
 
-  // -- state
+  // -- state: of the traders cash and holdings, of the others the books
   int32_t tau = a.st.tau[n];
   const int32_t start = a.st.start[n];
   float cash = a.st.cash[n];
@@ -124,6 +162,10 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
     const float v = p * d.s_price;
     orow[1 + tl] = v;
     O::store1(xrow + O::off(DK + 1 + tl), v);
+  };
+  auto quote = [&](float p, int par) {
+    const float u = p * d.one_plus_c;
+    quotes[(par * SE + e) * QP + tl] = Quote{p, u, 1.0 / (double)u};
   };
   auto put_holding = [&](int32_t x) {
     const float v = (float)x * d.s_hold;
@@ -147,46 +189,36 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
 
   for (int i = tid; i < SE * XP / 4; i += kEnvThreads) reinterpret_cast<uint32_t *>(ldsX)[i] = 0u;
   __syncthreads();
-  float pn[1];
-  {
-    const size_t row = (size_t)tau * d.M + (d.M == 1 ? 0 : n);
-    const float *irow = a.ind + row * DK;
-    pn[0] = a.price[row * D + dd];
+  double value = 0.0;  // the account's, before the trades that are settled next
+  float pn[1] = {a.price[((size_t)tau * d.M + (d.M == 1 ? 0 : n)) * D + dd]};
+  if (trader) {
+    if (own) put_holding(h[0]);
+    if (live && tl == 0) put_cash(cash);
+  }
+  if (keeper) {
+    const float *irow = a.ind + ((size_t)tau * d.M + (d.M == 1 ? 0 : n)) * DK;
     if (live) {
       for (int g = tl; g < min(NG, TPE * NI); g += TPE) put_ind(g, *reinterpret_cast<const env_f32x4u *>(irow + 4 * g));
       put_ind_rest(irow);
-      if (tl == 0) put_cash(cash);
     }
-    if (own) put_price(pn[0]), put_holding(h[0]);
+    if (own) put_price(pn[0]);
+    if (APART && tl < D) quote(pn[0], 0);
+    terms_of(1);
+    trade.put_term(0, tl < D ? (double)h[0] * (double)pn[0] : 0.0);
+    value = trade.value(cash);
   }
-  trade.put_term(0, tl < D ? (double)h[0] * (double)pn[0] : 0.0);
-  double value = trade.value(cash);  // the account's, before the next trades
   __syncthreads();
 
-  // partial sums of feature tile `tile`, lanes of the 16 rows only
-  const unsigned char *xop = ldsX + (lane & 15) * XP + O::HALF * (lane >> 5);
-  const unsigned char *hop = ldsH + (lane & 15) * HP + O::HALF * (lane >> 5);
-  auto put_part = [&](const f32x16 &acc, float *plane, int pitch, int col0) {
-    if ((lane & 31) < SE) {
-      float *p = plane + (lane & 15) * pitch + col0 + 4 * (lane >> 5);
+  const unsigned char *xop = ldsX + row * XP + O::off(8 * q4) + (SPLIT ? wt * B1 * 2 * O::KBYTES : 0);
+  const unsigned char *h1op = ldsH1 + row * HP + O::off(8 * q4), *h2op = ldsH2 + row * HP + O::off(8 * q4);
+  // tanh of this lane's sums into a hidden tile
+  auto activate = [&](float (&z)[F], const float (&bias)[F], unsigned char *H) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) *reinterpret_cast<f32x4 *>(p + 8 * j) = f32x4{acc[4 * j], acc[4 * j + 1], acc[4 * j + 2], acc[4 * j + 3]};
+    for (int i = 0; i < F; ++i) {
+      z[i] += bias[i];
+      z[i] = BF16 ? tanh_from_scaled(z[i] * kTwoLog2e) : tanh_accurate(z[i]);
     }
-  };
-  // hidden activations of this thread's features from the partial sums
-  auto activate = [&](const float (&bias)[F]) {
-    float z[F];
-#pragma unroll
-    for (int i = 0; i < F; ++i) z[i] = bias[i];
-#pragma unroll
-    for (int k = 0; k < KG; ++k) {
-      const float *p = part + (k * SE + e) * Gm::PP + f0;
-#pragma unroll
-      for (int i = 0; i < F; ++i) z[i] += p[i];
-    }
-#pragma unroll
-    for (int i = 0; i < F; ++i) z[i] = BF16 ? tanh_from_scaled(z[i] * kTwoLog2e) : tanh_accurate(z[i]);
-    unsigned char *o = ldsH + e * HP + O::off(f0);
+    unsigned char *o = H + row * HP + O::off(f0);
     if constexpr (F == 4) O::template store4<true>(o, z[0], z[1], z[2], z[3]);
     else if constexpr (BF16) *reinterpret_cast<uint32_t *>(o) = bf16_pair(z[0], z[1]);
     else {
@@ -196,158 +228,202 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
       for (int i = 0; i < 3; ++i) *reinterpret_cast<uint32_t *>(o + 16 * i) = s[i];
     }
   };
-  auto zero = [](f32x16 &acc) {
+  // a layer's products in two chains (one behind the other they wait for each other), and their sum
+  auto product = [&](auto &wb, const unsigned char *x) {
+    constexpr int NB = sizeof(wb) / sizeof(Block);
+    Sums s[2];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+    for (int i = 0; i < NB; ++i) {
+      Block b;
+      fetch_x(b, x + 2 * i * O::KBYTES);
+      mma16(wb[i], b, s[i & 1]);
+    }
+    f32x4 v = NB > 1 ? s[0].hi + s[1].hi : s[0].hi;
+    if (!BF16) v += NB > 1 ? s[0].lo + s[1].lo : s[0].lo;
+    return v;
   };
-
-  for (int t = 0; t < a.T; ++t) {
-    const size_t g0 = ((size_t)t * N + n) * D;
-    // -- requests of the step
-    if (!KEEP2) {
-      int lane_f = lane;
-      asm volatile("" : "+v"(lane_f));
-      fetch2(lane_f);
-    }
-    const RowInfo ri = rows_of(d, tau, start, n);
-    float eps[1], pv[1];
-    eps[0] = __builtin_nontemporal_load(a.noise + g0 + dd);
-    pv[0] = a.price[(size_t)ri.row_val * D + dd];
-    const float po = a.price[(size_t)ri.row_obs * D + dd];
-    const float *irow = a.ind + (size_t)ri.row_obs * DK;
-    env_f32x4 iv[NI];
+  auto mine = [&](float (&z)[F], const f32x4 &v) {
 #pragma unroll
-    for (int j = 0; j < NI; ++j) {
-      const int g = tl + TPE * j;
-      if (g < NG) iv[j] = *reinterpret_cast<const env_f32x4u *>(irow + 4 * g);
-    }
-    const typename Tr::Unit units = Tr::unit_of(d, pn);
-    // -- policy
-    f32x16 acc;
-    zero(acc);
-#pragma unroll
-    for (int i = 0; i < B1; ++i) {
-      Block x;
-      fetch_x(x, xop + (kg + KG * i) * O::KBYTES);
-      O::mma(w1[i], x, acc);
-    }
-    put_part(acc, part + kg * SE * Gm::PP, Gm::PP, ct * 32);
-    __syncthreads();
-    activate(bias1);
-    __syncthreads();
-    zero(acc);
-#pragma unroll
-    for (int i = 0; i < B2; ++i) {
-      Block x;
-      fetch_x(x, hop + (kg + KG * i) * O::KBYTES);
-      O::mma(w2[i], x, acc);
-    }
-    put_part(acc, part + kg * SE * Gm::PP, Gm::PP, ct * 32);
-    __syncthreads();
-    activate(bias2);
-    __syncthreads();
-    if (w < Gm::NKB) {
-      zero(acc);
-      Block x;
-      fetch_x(x, hop + w * O::KBYTES);
-      O::mma(w3, x, acc);
-      put_part(acc, part + w * SE * 36, 36, 0);
-    }
-    __syncthreads();
-    float z = 0.0f;
-#pragma unroll
-    for (int k = 0; k < Gm::NKB; ++k) z += part[(k * SE + e) * 36 + tl];
-    const float mu = finish_out(z, bias3, 1);
-    // -- sample and trade
-    float a_raw[1];
-    a_raw[0] = mu + d.sigma * eps[0];  // two roundings (contraction is off)
-    if (own) {
-      a.act_raw[g0 + tl] = a_raw[0];
-      if (a.mu) a.mu[g0 + tl] = mu;
-    }
-    orow += N * S;
-    int32_t q[1];
-    float e2;
-    double r;
-    trade.run(
-        d, live, a_raw, eps, pn, units, pv, h, q, cash, r, e2, a.logp != nullptr,
-        [&]() {
-          if (own) put_price(po);
-          if (live) {
-#pragma unroll
-            for (int j = 0; j < NI; ++j) {
-              const int g = tl + TPE * j;
-              if (g < NG) put_ind(g, iv[j]);
-            }
-          }
-        },
-        [&]() {
-          if (live) put_ind_rest(irow);
-        },
-        [&](int) {
-          if (ri.done) h[0] = 0;
-          put_holding(h[0]);
-          if (a.shares) a.shares[g0 + tl] = q[0];
-        });
-    // -- episode bookkeeping (binary64; the env's first thread holds the sums), reset if the episode ended
-    const double after = trade.value(cash);
-    r = (after - value) * (double)d.rho;
-    value = ri.done ? (double)d.cash0 : after;
+    for (int i = 0; i < F; ++i) z[i] = F == 4 || wt == 0 ? v[i] : v[(2 + i) & 3];
+  };
+  // The books of step t (binary64; the first thread of an env holds the sums).  Nothing in the next step waits for them, so
+  // wavefronts apart from the traders keep them while that step trades.
+  auto settle = [&](int t, float c, bool ended) {
+    terms_of(t);
+    const double after = trade.value(c);
+    const double r = (after - value) * (double)d.rho;
+    value = ended ? (double)d.cash0 : after;
     ep_ret += r;
-    if (ri.done) {
+    if (ended) {
       ep_sum += ep_ret;
       ep_sqsum += ep_ret * ep_ret;
       ep_cnt += 1;
       ep_ret = 0.0;
-      cash = d.cash0;
+    }
+    if (live && tl == 0) {
+      a.reward[(size_t)t * N + n] = (float)r;
+      a.done[(size_t)t * N + n] = (uint8_t)ended;
+    }
+  };
+
+  bool ended = false;
+  for (int t = 0; t < a.T; ++t) {
+    const size_t g0 = ((size_t)t * N + n) * D;
+    // -- requests of the step
+    const RowInfo ri = rows_of(d, tau, start, n);
+    float eps[1], pv[1], po;
+    env_f32x4 iv[NI];
+    const float *irow = a.ind + (size_t)ri.row_obs * DK;
+    typename Tr::Unit units;
+    if (trader) {
+      eps[0] = __builtin_nontemporal_load(a.noise + g0 + dd);
+      pv[0] = a.price[(size_t)ri.row_val * D + dd];
+    }
+    if (keeper) {
+      po = a.price[(size_t)ri.row_obs * D + dd];
+#pragma unroll
+      for (int j = 0; j < NI; ++j) {
+        const int g = tl + TPE * j;
+        if (g < NG) iv[j] = *reinterpret_cast<const env_f32x4u *>(irow + 4 * g);
+      }
+    }
+    if (!APART) units = Tr::unit_of(d, pn);
+    // -- policy
+    float f[F];
+    {
+      const f32x4 v = product(w1, xop);
+      mine(f, v);
+      if constexpr (SPLIT) {
+        // the other wavefront's half of the k-steps for this one's features, and the other way round
+        float other[F];
+#pragma unroll
+        for (int i = 0; i < F; ++i) other[i] = wt == 0 ? v[(2 + i) & 3] : v[i];
+#pragma unroll
+        for (int i = 0; i < F; ++i) share[(w * 2 + i) * kSharePitch + lane] = other[i];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < F; ++i) f[i] += share[((w ^ 4) * 2 + i) * kSharePitch + lane];
+      }
+    }
+    activate(f, bias1, ldsH1);
+    __syncthreads();
+    mine(f, product(w2, h1op));
+    activate(f, bias2, ldsH2);
+    __syncthreads();
+    if (ok < KS && 16 * ot < D) {
+      Block w3s[1] = {w3};
+      *reinterpret_cast<f32x4 *>(means + (ok * SE + row) * kMeanPitch + 16 * ot + 4 * q4) = product(w3s, h2op + 2 * ok * O::KBYTES);
+    }
+    __syncthreads();
+    orow += N * S;
+    // (layer 1 has read the present observation)
+    auto move_market = [&]() {
+      if (own) put_price(po);
+      if (live) {
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+          const int g = tl + TPE * j;
+          if (g < NG) put_ind(g, iv[j]);
+        }
+      }
+    };
+    if (trader) {
+      // -- sample and trade
+      if (APART) {
+        __builtin_amdgcn_s_setprio(2);
+        const Quote u = quotes[((t & 1) * SE + e) * QP + dd];
+        pn[0] = u.price, units.cost[0] = u.cost, units.rcp[0] = u.rcp;
+      }
+      float z = 0.0f, a_raw[1];
+#pragma unroll
+      for (int k = 0; k < KS; ++k) z += means[(k * SE + e) * kMeanPitch + dd];
+      const float mu = finish_out(z, bias3, 1);
+      a_raw[0] = mu + d.sigma * eps[0];  // two roundings (contraction is off)
+      if (own) {
+        a.act_raw[g0 + tl] = a_raw[0];
+        if (a.mu) a.mu[g0 + tl] = mu;
+      }
+      terms_of(t);
+      int32_t q[1];
+      float e2;
+      double r;
+      trade.run(
+          d, live, a_raw, eps, pn, units, pv, h, q, cash, r, e2, a.logp != nullptr,
+          [&]() {
+            if (!APART) move_market();
+          },
+          [&]() {
+            if (!APART && live) put_ind_rest(irow);
+          },
+          [&](int) {
+            if (ri.done) h[0] = 0;
+            put_holding(h[0]);
+            if (a.shares) a.shares[g0 + tl] = q[0];
+          });
+      if (APART && tl == 0) balance[(t & 1) * SE + e] = cash;
+      if (!APART) settle(t, cash, ri.done);
+      if (ri.done) cash = d.cash0;
+      if (live && tl == 0) {
+        put_cash(cash);
+        if (a.logp) a.logp[(size_t)t * N + n] = fmaf(-0.5f, e2, d.logp_const);
+      }
+      if (APART) __builtin_amdgcn_s_setprio(0);
+      else pn[0] = po;
+    } else {
+      move_market();
+      if (tl < D) quote(po, (t + 1) & 1);
+      if (live) put_ind_rest(irow);
+      if (t > 0) settle(t - 1, balance[((t - 1) & 1) * SE + e], ended);
+      ended = ri.done;
     }
     tau = ri.done ? start : tau + 1;
-    pn[0] = po;
-    if (live && tl == 0) {
-      put_cash(cash);
-      a.reward[(size_t)t * N + n] = (float)r;
-      a.done[(size_t)t * N + n] = (uint8_t)ri.done;
-      if (a.logp) a.logp[(size_t)t * N + n] = fmaf(-0.5f, e2, d.logp_const);
-    }
     __syncthreads();  // the next observation is complete
   }
 
-  if (own) a.st.h[(size_t)n * D + tl] = h[0];
-  if (live && tl == 0) {
-    a.st.tau[n] = tau;
-    a.st.cash[n] = cash;
-    a.st.ep_ret[n] = ep_ret;
-    a.st.ep_sum[n] = ep_sum;
-    a.st.ep_sqsum[n] = ep_sqsum;
-    a.st.ep_cnt[n] = ep_cnt;
+  if (trader) {
+    if (own) a.st.h[(size_t)n * D + tl] = h[0];
+    if (live && tl == 0) a.st.tau[n] = tau, a.st.cash[n] = cash;
+  }
+  if (keeper) {
+    if (APART && a.T > 0) settle(a.T - 1, balance[((a.T - 1) & 1) * SE + e], ended);
+    if (live && tl == 0) {
+      a.st.ep_ret[n] = ep_ret;
+      a.st.ep_sum[n] = ep_sum;
+      a.st.ep_sqsum[n] = ep_sqsum;
+      a.st.ep_cnt[n] = ep_cnt;
+    }
   }
 }
 
-template <bool BF16, int NCT, int B1>
-hipError_t launch_inst(hipStream_t st, const SmallArgs &a) {
-  using Gm = Geometry<NCT>;
-  constexpr auto kern = rollout_small_kernel<BF16, NCT, B1>;
+template <bool BF16, int HD, int KS1, bool SPLIT, bool APART>
+hipError_t launch_stocks(hipStream_t st, const SmallArgs &a) {
+  constexpr int KS = Geometry<HD>::KS;
+  constexpr auto kern = rollout_small_kernel<BF16, HD, KS1, SPLIT, APART>;
   const hipError_t e = allow_full_lds<kern>();
   if (e != hipSuccess) return e;
-  const size_t planes = Gm::KG * Gm::PP > Gm::NKB * 36 ? Gm::KG * Gm::PP : Gm::NKB * 36;
-  const size_t lds = (size_t)SE * (tile::tile_pitch<BF16>(B1 * Gm::KG) + tile::tile_pitch<BF16>(Gm::NKB)) + planes * SE * 4 +
-                     trade_lds(SE, true, a.d.D);
+  const size_t lds = small_lds(KS, SPLIT, APART, tile::tile_pitch<BF16>(2 * KS1), tile::tile_pitch<BF16>(2 * KS), a.d.D);
   hipLaunchKernelGGL(kern, dim3((unsigned)((a.d.N + SE - 1) / SE)), dim3(kEnvThreads), lds, st, a);
   return hipGetLastError();
+}
+
+template <bool BF16, int HD, int KS1, bool SPLIT = false>
+hipError_t launch_inst(hipStream_t st, const SmallArgs &a) {
+  return a.d.D <= 16 ? launch_stocks<BF16, HD, KS1, SPLIT, true>(st, a) : launch_stocks<BF16, HD, KS1, SPLIT, false>(st, a);
 }
 
 template <bool BF16>
 hipError_t launch_dtype(hipStream_t st, const SmallArgs &a) {
   const int nkb = a.net.nkb[0];
-  // the smallest instance whose wavefronts hold layer 1: blocks beyond the last are multiplied by zeros
+  // the smallest instance whose wavefronts hold layer 1: inputs beyond the last are multiplied by zeros
   if (a.net.nct[0] == 2) {
-    if (nkb <= 4) return launch_inst<BF16, 2, 1>(st, a);
-    if (nkb <= 8) return launch_inst<BF16, 2, 2>(st, a);
-    return launch_inst<BF16, 2, 5>(st, a);
+    if (nkb <= 2) return launch_inst<BF16, 64, 1>(st, a);
+    if (nkb <= 4) return launch_inst<BF16, 64, 2>(st, a);
+    if (nkb <= 8) return launch_inst<BF16, 64, 4, !BF16>(st, a);
+    return launch_inst<BF16, 64, 10, !BF16>(st, a);
   }
-  if (nkb <= 4) return launch_inst<BF16, 4, 2>(st, a);
-  if (nkb <= 10) return launch_inst<BF16, 4, 5>(st, a);
-  return launch_inst<BF16, 4, 10>(st, a);
+  if (nkb <= 4) return launch_inst<BF16, 128, 2>(st, a);
+  if (nkb <= 10) return launch_inst<BF16, 128, 5>(st, a);
+  return launch_inst<BF16, 128, 10>(st, a);
 }
 
 }  // namespace
