@@ -7,15 +7,20 @@
 // from the first step to the last, the observation lives in LDS as the operand
 // layer 1 reads, and only the rollout's records go to memory.
 //
-// What bounds a step is latency: three layers of one to ten matrix steps per
-// wavefront, each followed by two barriers (partial sums, activations), then the
-// trades' chain (pod_trade.h).  The loads of a step -- noise, the next market row
-// -- depend on the cursor only and travel behind the network.
-// Per step, before (a network launch or three and an env launch) -> now:
-//   fp32,  64 hidden units: 16 envs x 5 stocks 19.6 -> 3.6 us, 512 x 30 x 8 indicators 30 -> 5.1, 16384 x 30 x 8 55 -> 21
-//   fp32, 128: 64 x 10 x 2 27 -> 5.5, 512 x 30 x 8 37 -> 10.9 (129 of its registers spill; 28 with up to 160 inputs),
-//   4096 x 30 x 8 40 -> 15
-//   bf16, 128: 512 x 30 x 8 30 -> 4.2, 16384 x 30 x 8 38 -> 18
+// What bounds a step is latency: three layers, each one product and one barrier, then
+// the trades' chain (pod_trade.h).  A wavefront owns 16 features of a layer with all of
+// their inputs (16 x 16 x 32 instructions: the 16 envs fill their columns); partial sums
+// over k-blocks, which went through LDS with a barrier of their own, took as long again
+// (16 envs x 5 stocks, 64 steps with values 239 -> 207 us).  With up to 16 stocks half of the
+// wavefronts are enough to trade, and the others move the market, prepare the next quotes and
+// keep the books of the step before meanwhile (207 -> 152; with 30 stocks and four wavefronts
+// the trades themselves take longer than that saves: 512 envs x 30 x 8 333 -> 341).  The loads
+// of a step -- noise, the next market row -- depend on the cursor only and travel behind the
+// network.
+// Per step, first (a network launch or three and an env launch) -> in one launch -> now:
+//   fp32,  64 hidden units: 16 envs x 5 stocks 19.6 -> 3.5 -> 2.1 us, 512 x 30 x 8 indicators 30 -> 5.1 -> 4.5
+//   fp32, 128: 64 x 10 x 2 27 -> 5.3 -> 2.9, 512 x 30 x 8 37 -> 10.9 -> 7.0 (57 registers spill; 129 before)
+//   bf16, 128: 512 x 30 x 8 30 -> 4.0 -> 3.2
 #include "pod_internal.h"
 #include "pod_tile.h"
 #include "pod_trade.h"
@@ -95,7 +100,10 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
   using O = Op<BF16>;
   using Block = typename O::Block;
   using Gm = Geometry<HD>;
-  using Tr = Trade<SE, 1, true, APART ? kEnvThreads / 2 : kEnvThreads>;
+  // where the weights leave few registers, what follows from the thread's index is formed anew in every step
+  // (512 envs x 30 stocks x 8, 128 units, 64 steps 604 -> 504 us; 64 units, which spill ten registers without it, 337 -> 348)
+  constexpr bool TIGHT = !BF16 && HD == 128 && KS1 > 2;
+  using Tr = Trade<SE, 1, true, APART ? kEnvThreads / 2 : kEnvThreads, TIGHT>;
   constexpr int TPE = Tr::TPE, NI = 4, F = Gm::F, KS = Gm::KS, NCT = HD / 32, NP = 64 * kPlanes<Block>;
   static_assert(!SPLIT || (Gm::WT == 2 && KS1 % 2 == 0), "");
   constexpr int B1 = SPLIT ? KS1 / 2 : KS1;
@@ -115,7 +123,8 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool trader = !APART || w < kWaves / 2, keeper = !APART || !trader;
-  const int e = trade.thread() / TPE, tl = tid & (TPE - 1), dd = min(tl, D - 1);  // of either kind: its env, lane of the env, stock
+  int e = trade.thread() / TPE, tl = tid & (TPE - 1);  // of either kind: its env, its lane of the env
+  const int dd = min(tl, D - 1);
   const int n0 = blockIdx.x * SE, n = min(n0 + e, d.N - 1);
   const bool live = n0 + e < d.N, own = live && tl < D;
   const size_t N = (size_t)d.N;
@@ -151,17 +160,17 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
   double ep_ret = a.st.ep_ret[n], ep_sum = a.st.ep_sum[n], ep_sqsum = a.st.ep_sqsum[n];
   int32_t ep_cnt = a.st.ep_cnt[n];
 
-  unsigned char *xrow = ldsX + e * XP;
+  auto xrow = [&](int byte) { return ldsX + e * XP + byte; };
   float *orow = a.obs + (size_t)n * S;  // of the observation being written
   auto put_ind = [&](int g, env_f32x4 v) {
     v[0] *= d.s_ind, v[1] *= d.s_ind, v[2] *= d.s_ind, v[3] *= d.s_ind;
     *reinterpret_cast<env_f32x4u *>(orow + 1 + 2 * D + 4 * g) = v;
-    O::store4(xrow + O::off(4 * g), v[0], v[1], v[2], v[3]);
+    O::store4(xrow(O::off(4 * g)), v[0], v[1], v[2], v[3]);
   };
   auto put_price = [&](float p) {
     const float v = p * d.s_price;
     orow[1 + tl] = v;
-    O::store1(xrow + O::off(DK + 1 + tl), v);
+    O::store1(xrow(O::off(DK + 1 + tl)), v);
   };
   auto quote = [&](float p, int par) {
     const float u = p * d.one_plus_c;
@@ -170,12 +179,12 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
   auto put_holding = [&](int32_t x) {
     const float v = (float)x * d.s_hold;
     orow[1 + D + tl] = v;
-    O::store1(xrow + O::off(DK + 1 + D + tl), v);
+    O::store1(xrow(O::off(DK + 1 + D + tl)), v);
   };
   auto put_cash = [&](float c) {
     const float v = c * d.s_cash;
     orow[0] = v;
-    O::store1(xrow + O::off(DK), v);
+    O::store1(xrow(O::off(DK)), v);
   };
   // indicators beyond the groups a thread holds in registers, and the last DK % 4
   auto put_ind_rest = [&](const float *irow) {
@@ -183,7 +192,7 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
     if (tl < (DK & 3)) {
       const float v = irow[4 * NG + tl] * d.s_ind;
       orow[1 + 2 * D + 4 * NG + tl] = v;
-      O::store1(xrow + O::off(4 * NG + tl), v);
+      O::store1(xrow(O::off(4 * NG + tl)), v);
     }
   };
 
@@ -268,6 +277,7 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
 
   bool ended = false;
   for (int t = 0; t < a.T; ++t) {
+    if (TIGHT) asm volatile("" : "+v"(tl), "+v"(e), "+v"(trade.me));
     const size_t g0 = ((size_t)t * N + n) * D;
     // -- requests of the step
     const RowInfo ri = rows_of(d, tau, start, n);

@@ -255,6 +255,32 @@ def test_small_network_rollout(base, N, agents, Hd, D, K):
             parity.check_networks(w, d["actor"], d["critic"], rec["obs"][t][envs], rec["mu"][t][envs], agent=a)
 
 
+# Either side of 16 stocks, up to which the books of a step are kept beside the trades of the next: state and episode sums after
+# calls of one step, of episodes that end in the last step of a call, and of several episodes
+@pytest.mark.parametrize("base,Hd,D,K", [("tiny", 64, 16, 1), ("tiny", 64, 17, 1), ("tiny", 64, 12, 8), ("tiny", 128, 16, 9),
+                                         ("large", 128, 16, 0), ("large", 64, 13, 20), ("large", 128, 17, 4)])
+def test_small_network_books(base, Hd, D, K):
+    T, H, N = 14, 4, 37
+    w = inputs.WORKLOADS[base].replace(n_envs=N, hidden=Hd, n_stocks=D, n_ind=K, steps=T, cash0=5e4)
+    d = inputs.make_all(w, horizon=H, steps=T)
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    ro = pr.Rollout(pr.make_config(w, horizon=H), _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+    parts, t0 = [], 0
+    for n in (1, 3, 1, 9):
+        out = ro.alloc_buffers(n, value=False, logp=True, mu=True, shares=True)
+        ro.step_T(n, _t(d["noise"][t0:t0 + n]), out)
+        torch.cuda.synchronize()
+        parts.append({k: parity.to_np(v)[:n] for k, v in out.items()})
+        last, t0 = parity.to_np(out["obs"])[n:], t0 + n
+    rec = {k: np.concatenate([p[k] for p in parts] + ([last] if k == "obs" else [])) for k in parts[0]}
+    _, st = parity.check_env_record(w, oracle.cfg_from_workload(w, horizon=H), rec, d["price"], d["ind"], d["noise"], rec["mu"])
+    got = {k: parity.to_np(v) for k, v in ro.get_state().items()}
+    assert np.array_equal(got["ep_count"], st.ep_cnt) and np.array_equal(got["cursor"], st.tau) and np.array_equal(got["holdings"], st.h)
+    assert np.array_equal(got["cash"], st.cash)
+    for k, want in (("ep_return", st.ep_ret), ("ep_sum", st.ep_sum), ("ep_sqsum", st.ep_sqsum)):
+        np.testing.assert_allclose(got[k], want, rtol=1e-9, atol=1e-9)
+
+
 # fp32 networks with infinities, numbers next to the largest and NaN among inputs and weights: every kernel of the
 # forward pass and both rollouts that keep their input tile give what fp32 sums give (a saturated unit, or NaN)
 @pytest.mark.parametrize("N,rows,Hd,D,K,fused", [(16, 16, 32, 3, 1, False), (64, 64 * 260 + 40, 256, 30, 8, False),
