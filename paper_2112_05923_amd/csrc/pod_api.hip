@@ -1,6 +1,8 @@
 // C ABI of libpodrollout: argument validation, workspace layout and the
 // sequencing of kernel launches.  No arithmetic of the method lives here.
 #include <math.h>
+
+#include <algorithm>
 #include <new>
 #include <pthread.h>
 #include <stdlib.h>
@@ -21,6 +23,9 @@ struct pr_handle {
   PackedNet actor_rot;    // the actor with layer 1 packed for inputs in the order [indicators | cash | prices | holdings],
                           // or [indicators | prices | zeros | holdings | cash | zeros] (market_first)
   void *w1_rot;           // (null when no rollout of this handle reads that order)
+  PackedNet critic_rot;   // the critic likewise, where its hidden layers run beside the actor's (null W[0]: they do not)
+  void *beside_h[2];      // its activations: of one step, and of `beside_steps` steps
+  int32_t beside_steps;
   void *w_packed[2][3];   // device, per net and layer
   float *b_packed[2][3];
   void *half_w[2][3];     // layers in fp16 parts, and their factors, where a kernel takes them
@@ -63,7 +68,7 @@ bool is_pow2_float(float x) {
 
 struct Layout {
   size_t w[2][3], b[2][3];
-  size_t w1_rot;
+  size_t w1_rot, w1_beside, beside_h[2];
   size_t cash, tau, h, ep_ret, ep_sum, ep_sqsum, ep_cnt, mu, start, split[3], query[3];
   size_t table_w[2][2], table_p, tau0;
   size_t half_w[2][3], half_u[2][3];
@@ -80,6 +85,19 @@ bool uses_shadow(const pr_config &c) {
 
 // rollouts of this config read layer 1 in the order [indicators | cash | prices | holdings]
 bool uses_rotated(const pr_config &c) { return c.schedule == PR_SCHED_FUSED || small_supported(c) || uses_shadow(c); }
+
+// The value head's hidden layers run beside the actor's, step by step, on the bf16 rows the actor reads, instead of over the whole
+// record afterwards, where that fills compute units the actor's leave idle (or one round of taller tiles) and the inputs are too
+// many for the kernels that keep a tile's inputs in LDS.  Rollouts, us per step: 2048 envs x 300 stocks, 512 units 50.7 -> 46.1,
+// 1024 x 300 with 1024 units 49.7 -> 44.8, 600 x 500 56.7 -> 51.7, 1500 x 130, 512 units 35.9 -> 33.9; one round of tall
+// tiles, 2048 x 500 with 1024 units 84.4 -> 79.8 (the value head alone is bound by its weights there); with more tiles than that
+// it is slower: 1400 x 200 with 1024 units (352 tiles) 50.9 -> 52.9, 4000 x 100, 512 units (504) 48.8 -> 51.6.
+bool value_beside(const pr_config &c) { return uses_shadow(c) && state_dim(c) > 320 && layers_room_beside(c.n_envs, c.n_envs / c.n_agents, c.hidden); }
+// steps whose last activations are kept for one launch of the output layer: 32 MiB, or one step's
+int32_t value_beside_steps(const pr_config &c) {
+  const int64_t step = (int64_t)c.n_envs * layers_pitch(c.hidden) * 2;
+  return (int32_t)std::max<int64_t>(1, ((int64_t)32 << 20) / step);
+}
 
 // k-blocks of that copy of layer 1.  The persistent fp32 rollout has the market columns in blocks of their own.
 bool market_first(const pr_config &c) { return c.schedule == PR_SCHED_FUSED && c.mlp_dtype == PR_MLP_F32; }
@@ -144,6 +162,12 @@ Layout make_layout(const pr_config &c) {
     }
   }
   L.w1_rot = uses_rotated(c) ? take(packed_weight_bytes(16 * rotated_blocks(c), Hd, bf) * P) : 0;
+  L.w1_beside = L.beside_h[0] = L.beside_h[1] = 0;
+  if (value_beside(c)) {
+    L.w1_beside = take(packed_weight_bytes(16 * rotated_blocks(c), Hd, bf) * P);
+    L.beside_h[0] = take(N * layers_pitch(Hd) * 2);
+    L.beside_h[1] = take(value_beside_steps(c) * N * layers_pitch(Hd) * 2);
+  }
   L.cash = take(N * 4);
   L.tau = take(N * 4);
   L.h = take(N * D * 4);
@@ -239,6 +263,10 @@ int pack_nets(pr_handle *h, const pr_weights *actor, const pr_weights *critic) {
   if (h->w1_rot) {
     const int portfolio = 16 * f32_market_blocks(D, c.n_ind);
     PackJob &j = jobs[n++] = {actor->W1, actor->b1, h->w1_rot, h->b_packed[0][0], S, Hd, rotated_blocks(c), {{0, 1 + 2 * D, DK}, {DK, 0, 1 + 2 * D}}};
+    if (h->critic_rot.W[0]) {
+      PackJob &k = jobs[n++] = j;
+      k.W = critic->W1, k.b = critic->b1, k.Wp = const_cast<void *>(h->critic_rot.W[0]), k.bp = h->b_packed[1][0];
+    }
     if (market_first(c)) j.run[1] = {DK, 1, D}, j.run[2] = {portfolio, 1 + D, D}, j.run[3] = {portfolio + D, 0, 1};
   }
   // Over a shared table layer 1 is taken in two parts: [indicators | prices], and [holdings | zeros | cash].
@@ -392,6 +420,13 @@ int rollout_init(const pr_config *cfg, const pr_market *market, const pr_weights
   h->actor_rot.w_stride[0] = (int64_t)packed_weight_bytes(16 * rotated_blocks(*cfg), cfg->hidden, cfg->mlp_dtype);
   fill_net(h->critic, h, 1);
   if (uses_shadow(*cfg)) h->shadow = h->actor.split_x;
+  if (value_beside(*cfg)) {
+    h->critic_rot = h->critic;
+    h->critic_rot.W[0] = ws + L.w1_beside;
+    h->critic_rot.nkb[0] = h->actor_rot.nkb[0], h->critic_rot.w_stride[0] = h->actor_rot.w_stride[0];
+    for (int i = 0; i < 2; ++i) h->beside_h[i] = ws + L.beside_h[i];
+    h->beside_steps = value_beside_steps(*cfg);
+  }
   int prc = pack_nets(h, actor, critic);
   if (prc == PR_OK) {
     hipError_t e = hipMemsetAsync(h->start, 0, (size_t)cfg->n_envs * 4, h->stream);
@@ -457,19 +492,41 @@ int rollout_step_T(pr_handle *h, int32_t T, const float *noise, const pr_buffers
                                  *out));
   } else {
     POD_HIP(launch_observe(h->stream, h->dims, h->st, h->market.price, h->market.ind, out->obs, h->shadow));
+    const bool beside = out->value && h->critic_rot.W[0];
+    PackedNet critic = h->critic_rot;
+    const size_t step_bytes = N * layers_pitch(h->cfg.hidden) * 2;
+    // where the value head's activations of step t go, and its outputs once the slots are full or the record ends
+    auto value_slot = [&](int t) {
+      critic.split_h[0] = h->beside_h[0];
+      critic.split_h[1] = static_cast<unsigned char *>(h->beside_h[1]) + (size_t)(t % h->beside_steps) * step_bytes;
+    };
+    auto value_out = [&](int t) {
+      const int filled = t % h->beside_steps + 1;
+      if (filled < h->beside_steps && t < T) return hipSuccess;
+      return launch_value_dot(h->stream, critic, (int64_t)filled * (int64_t)N, h->beside_h[1], out->value + (size_t)(t + 1 - filled) * N,
+                              (int32_t)N, per_agent);
+    };
     for (int t = 0; t < T; ++t) {
       float *mu = out->mu ? out->mu + (size_t)t * N * D : h->mu_scratch;
       StepIO io = step_io(h, out, t, mu, noise, h->shadow);
       if (h->shadow.p) {
+        if (beside) value_slot(t);
         IndicatorMove move{h->dims, h->st, h->market.ind, io.obs_next, h->shadow, false};
         POD_HIP(launch_layers(h->stream, h->actor_rot, (int64_t)N, h->shadow, mu, (int32_t)N, per_agent,
-                              h->cfg.n_ind > 0 ? &move : nullptr));
+                              h->cfg.n_ind > 0 ? &move : nullptr, beside ? &critic : nullptr));
+        if (beside) POD_HIP(value_out(t));
         io.ind_done = move.moved;
       } else {
         POD_HIP(launch_mlp(h->stream, h->actor, (int64_t)N, out->obs + (size_t)t * N * S, (int64_t)S, mu, (int32_t)N,
                            per_agent));
       }
       POD_HIP(launch_env_step(h->stream, h->dims, h->st, h->market.price, h->market.ind, io));
+    }
+    if (beside) {
+      value_slot(T);
+      POD_HIP(launch_hidden(h->stream, critic, (int64_t)N, h->shadow, (int32_t)N, per_agent));
+      POD_HIP(value_out(T));
+      return PR_OK;
     }
   }
   if (out->value)

@@ -216,9 +216,15 @@ bool mlp_supported(int S, int Hd, int O, int bf16);
 int compute_units();  // of the device the library was first used on
 // The bf16 layer-per-launch path: x holds the rows (columns up to x.cols zero-padded) in the order layer 1 was packed for.
 bool layers_supported(int64_t rows, int hidden, int bf16);
+// the hidden layers of two networks side by side over N rows are a workgroup or less per compute unit
+bool layers_room_beside(int32_t N, int32_t envs_per_agent, int hidden);
 int32_t layers_pitch(int cols);
 hipError_t launch_layers(hipStream_t st, const PackedNet &net, int64_t rows, const ObsShadow &x, float *Y, int32_t N,
-                         int32_t envs_per_agent, IndicatorMove *move = nullptr);
+                         int32_t envs_per_agent, IndicatorMove *move = nullptr, const PackedNet *beside = nullptr);
+// `beside`: the hidden layers of a second network of the same shape on the same rows, in the same launches, into its split_h;
+// launch_hidden: those of one network alone.  launch_value_dot: a value head's output layer on rows of such activations.
+hipError_t launch_hidden(hipStream_t st, const PackedNet &net, int64_t rows, const ObsShadow &x, int32_t N, int32_t envs_per_agent);
+hipError_t launch_value_dot(hipStream_t st, const PackedNet &net, int64_t rows, const void *h, float *Y, int32_t N, int32_t envs_per_agent);
 // Few rows of either operand type: a launch per layer that splits the inputs over a workgroup's wavefronts.  `converted`:
 // the alternative has its rows in bf16 already.
 bool few_rows(int64_t rows, int S, int hidden, int bf16, bool converted);

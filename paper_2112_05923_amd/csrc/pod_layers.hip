@@ -17,22 +17,24 @@ using tile::u32x2;
 using tile::u32x4;
 
 constexpr int kThreads = 512;
-constexpr int kRows = 64, kFeatures = 128;
+constexpr int kFeatures = 128;
 
 struct LayerArgs {
-  const __bf16 *X;     // [rows][xpitch], columns up to 16 nkb readable
+  // the layer of one network, or of two of the same shape side by side
+  const __bf16 *X[2];  // [rows][xpitch], columns up to 16 nkb readable
+  void *Y[2];          // bf16 [rows][ldy] (hidden) or fp32 [rows][ldy] (output)
+  const void *W[2];    // packed weights of the layer, agent-major
+  const float *b[2];   // padded biases, agent-major
   int32_t xpitch;
   int32_t rows;
-  void *Y;             // bf16 [rows][ldy] (hidden) or fp32 [rows][ldy] (output)
   int32_t ldy;
-  const void *W;       // packed weights of the layer, agent-major
-  const float *b;      // padded biases, agent-major
   int64_t w_stride;    // bytes between agents
   int32_t b_stride;    // floats between agents
   int32_t out_dim, nkb, nct;
   int32_t out_tanh;
   int32_t N, envs_per_agent;
-  int32_t tiles_r, tiles_f;    // 64-row and 128-feature tiles
+  int32_t tiles_r, tiles_f;    // row tiles and 128-feature tiles (of all networks)
+  int32_t own_f;               // and of one network
   int32_t patch_r, patch_f;    // tiles per XCD in either direction
   int32_t split_f;             // XCDs side by side in the feature direction
   int32_t first_move;          // blocks from here on move indicators
@@ -72,19 +74,25 @@ __device__ inline void move_indicators(const IndicatorMove &m, int n, int lane) 
 
 // The eight wavefronts are four k-groups of two; a group takes every fourth k-block, its wavefronts 64 rows x 64
 // features each (2 x 2 accumulators of 32 x 32): an LDS operand feeds two and a weight block two matrix instructions, and
-// every weight block is read by exactly one wavefront, straight into registers.  Per iteration of KI k-blocks the input
+// every weight block is read by exactly one wavefront, straight into registers (RB = 4: 128 rows, 2 x 4 accumulators).  Per iteration of KI k-blocks the input
 // rows pass through a double-buffered LDS tile (one barrier per iteration); weights and rows are requested a whole
 // iteration before they are used, in two register sets, so the loads of the loop body are in flight behind its matrix
-// instructions.  At the end the groups' partial sums are added through LDS, each group finishing one accumulator.
-// What bounds it: the bytes a compute unit draws from the L2 (per k and workgroup 384 B for 4 cycles of matrix work;
-// 64 B per cycle and compute unit) and, with few iterations, their latency.
+// instructions.  At the end the groups' partial sums are added through LDS, four accumulators at a time in pieces of 16 bytes,
+// each group finishing one (numbers of 4 bytes, two at a time: 0.3 us more).
+// What bounds it, 2048 rows of 3001 inputs x 1024 features, 20.8 us: per 16 k-blocks 96 KB at the 48 bytes a cycle that a
+// compute unit gets (0.97 us; 64 at best) and the matrix instructions (0.5) half beside them; about 6 us before the first
+// product and after the last.  Not where the bytes come from: with all requests to the same 100 KB 21.2 us, with
+// rows requested an iteration earlier still 21.5.  Rows and weights straight from memory, without LDS and barriers, are bound by their
+// bytes alone (15 us of a loop), but eight partial sums cost 4 us and it came out level; so did 128 rows a tile with 512
+// registers a wavefront, for two networks together.
 // KI = 16: 128 registers of weights and rows in flight, one workgroup per compute unit; KI = 8: half of that and two
 // workgroups per compute unit, for launches with more workgroups than compute units.
-template <int KI, bool HIDDEN>
-__global__ __launch_bounds__(kThreads, KI == 16 ? 2 : 4) void layer_kernel(LayerArgs a, IndicatorMove move) {
+template <int KI, int RB, bool HIDDEN>
+__global__ __launch_bounds__(kThreads, KI == 8 && RB == 2 ? 4 : 2) void layer_kernel(LayerArgs a, IndicatorMove move) {
   extern __shared__ __align__(16) unsigned char lds[];
+  constexpr int kRows = 32 * RB;
   constexpr int LB = KI / 4;               // k-blocks per group and iteration
-  constexpr int NP = KI / 4;               // 16-byte pieces of the input rows per thread and iteration
+  constexpr int NP = KI * RB / 8;          // 16-byte pieces of the input rows per thread and iteration
   constexpr int PITCH = KI * 32 + 16;      // bytes per row of a staged chunk
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), grp = wave >> 1, half = wave & 1;
@@ -96,15 +104,20 @@ __global__ __launch_bounds__(kThreads, KI == 16 ? 2 : 4) void layer_kernel(Layer
   // neighbouring tiles on one XCD (block b runs on XCD b % 8): a patch of patch_r x patch_f tiles shares its L2
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int sr = slot / a.patch_f, sf = slot - sr * a.patch_f;
-  const int tr = (xcd / a.split_f) * a.patch_r + sr, tf = (xcd % a.split_f) * a.patch_f + sf;
-  if (sr >= a.patch_r || tr >= a.tiles_r || tf >= a.tiles_f) return;
+  const int tr = (xcd / a.split_f) * a.patch_r + sr, tile_f = (xcd % a.split_f) * a.patch_f + sf;
+  if (sr >= a.patch_r || tr >= a.tiles_r || tile_f >= a.tiles_f) return;
+  // (both networks' pointers arrive with the other arguments: picked by an index they would be a round trip of their own)
+  const bool second = tile_f >= a.own_f;
+  const int tf = second ? tile_f - a.own_f : tile_f;
+  auto own = [&](auto &two) { return second ? two[1] : two[0]; };
   const int row0 = tr * kRows;
   const int agent = (row0 % a.N) / a.envs_per_agent;
-  const u32x4 *W = reinterpret_cast<const u32x4 *>(static_cast<const unsigned char *>(a.W) + (size_t)agent * a.w_stride);
-  const float *bias = a.b + (size_t)agent * a.b_stride;
+  const u32x4 *W = reinterpret_cast<const u32x4 *>(static_cast<const unsigned char *>(own(a.W)) + (size_t)agent * a.w_stride);
+  const float *bias = own(a.b) + (size_t)agent * a.b_stride;
   const int nkb = a.nkb, nct = a.nct;
   const int nit = (nkb + KI - 1) / KI;
 
+  const __bf16 *X = own(a.X);
   // input rows: piece p of the tile is 16 bytes of row p / (2 KI)
   const __bf16 *xp[NP];
   int xcol[NP], xdst[NP];
@@ -112,7 +125,7 @@ __global__ __launch_bounds__(kThreads, KI == 16 ? 2 : 4) void layer_kernel(Layer
 #pragma unroll
   for (int i = 0; i < NP; ++i) {
     const int p = tid + kThreads * i, r = p / (2 * KI), c = p % (2 * KI);
-    xp[i] = a.X + (size_t)min(row0 + r, a.rows - 1) * a.xpitch;
+    xp[i] = X + (size_t)min(row0 + r, a.rows - 1) * a.xpitch;
     xcol[i] = 8 * c;
     xdst[i] = r * PITCH + 16 * c;
   }
@@ -137,23 +150,23 @@ __global__ __launch_bounds__(kThreads, KI == 16 ? 2 : 4) void layer_kernel(Layer
     w[j][1] = wp[1][o];
   };
 
-  f32x16 acc[2][2];
+  f32x16 acc[2][RB];
 #pragma unroll
   for (int c = 0; c < 2; ++c)
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < RB; ++t)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[c][t][i] = 0.0f;
   const unsigned char *xl = lds + (lane & 31) * PITCH + 16 * (lane >> 5) + 32 * grp;
   auto mma = [&](const u32x4(&w)[LB][2], int buf, int j) {
-    u32x4 v[2];
+    u32x4 v[RB];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < RB; ++t)
       v[t] = *reinterpret_cast<const u32x4 *>(xl + buf * (kRows * PITCH) + t * 32 * PITCH + j * 128);
 #pragma unroll
     for (int c = 0; c < 2; ++c)
 #pragma unroll
-      for (int t = 0; t < 2; ++t) tile::Op<true>::mma(w[j][c], v[t], acc[c][t]);
+      for (int t = 0; t < RB; ++t) tile::Op<true>::mma(w[j][c], v[t], acc[c][t]);
   };
 
   load_x(0);
@@ -197,41 +210,50 @@ __global__ __launch_bounds__(kThreads, KI == 16 ? 2 : 4) void layer_kernel(Layer
   if (it + 1 < nit) tail(wb, it + 1, 1);
   if (it + 2 < nit) tail(wa, it + 2, 0);
 
-  // -- partial sums: group t finishes accumulator t = (feature tile t / 2, row tile t % 2) of both halves
-  float *red = reinterpret_cast<float *>(lds);  // [2 accumulators][3 groups][2 halves][16][64]
-  f32x16 sum;
+  // -- partial sums: group g finishes accumulators g, g + 4, .. of both halves (accumulator t = feature tile t / RB, row tile
+  // t % RB), PER of them a round
+  constexpr int PER = KI == 8 && RB == 2 ? 2 : 4, MINE = RB / 2;
+  f32x4 *red = reinterpret_cast<f32x4 *>(lds);  // [PER accumulators][3 groups][2 halves][4][64]
+  f32x16 sum[MINE];
 #pragma unroll
-  for (int p = 0; p < 2; ++p) {
+  for (int p = 0; p < 2 * RB / PER; ++p) {
     if (p) __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int t = 2 * p + q;
-      if (t != grp) {
-        float *d = red + ((q * 3 + (grp < t ? grp : grp - 1)) * 2 + half) * 1024 + lane;
+    for (int q = 0; q < PER; ++q) {
+      const int t = PER * p + q, owner = t & 3;
+      if (owner != grp) {
+        f32x4 *d = red + ((q * 3 + (grp < owner ? grp : grp - 1)) * 2 + half) * 256 + lane;
+        const f32x16 &v = acc[t / RB][t % RB];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) d[i * 64] = acc[t >> 1][t & 1][i];
+        for (int i = 0; i < 4; ++i) d[i * 64] = f32x4{v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]};
       }
     }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int t = 2 * p + q;
-      if (t == grp) {
-        sum = acc[t >> 1][t & 1];
+    for (int q = 0; q < PER; ++q) {
+      const int t = PER * p + q;
+      if ((t & 3) == grp) {
+        f32x16 &o = sum[t >> 2];
+        o = acc[t / RB][t % RB];
 #pragma unroll
         for (int g = 0; g < 3; ++g) {
-          const float *s = red + ((q * 3 + g) * 2 + half) * 1024 + lane;
+          const f32x4 *r = red + ((q * 3 + g) * 2 + half) * 256 + lane;
 #pragma unroll
-          for (int i = 0; i < 16; ++i) sum[i] += s[i * 64];
+          for (int i = 0; i < 4; ++i) {
+            const f32x4 v = r[i * 64];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) o[4 * i + k] += v[k];
+          }
         }
       }
     }
   }
-  // -- bias and tanh, then whole rows out through LDS (behind the 48 KiB of partial sums)
+  // -- bias and tanh, then whole rows out through LDS (behind the partial sums)
   constexpr int OESZ = HIDDEN ? 2 : 4, OPITCH = kFeatures * OESZ + 16;
-  unsigned char *stage = lds + 48 * 1024;
-  {
-    const int f0 = half * 64 + (grp >> 1) * 32, row = (grp & 1) * 32 + (lane & 31);
+  unsigned char *stage = lds + PER * 24 * 1024;
+#pragma unroll
+  for (int m = 0; m < MINE; ++m) {
+    const int t = grp + 4 * m, f0 = half * 64 + (t / RB) * 32, row = (t % RB) * 32 + (lane & 31);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int f = f0 + 8 * j + 4 * (lane >> 5);
@@ -239,7 +261,7 @@ __global__ __launch_bounds__(kThreads, KI == 16 ? 2 : 4) void layer_kernel(Layer
       float y[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float z = sum[4 * j + i] + bv[i];
+        const float z = sum[m][4 * j + i] + bv[i];
         y[i] = HIDDEN ? tile::tanh_from_scaled(z * tile::kTwoLog2e) : a.out_tanh ? tile::tanh_accurate(z) : z;
       }
       if (HIDDEN) tile::Op<true>::store4(stage + row * OPITCH + f * OESZ, y[0], y[1], y[2], y[3]);
@@ -250,16 +272,16 @@ __global__ __launch_bounds__(kThreads, KI == 16 ? 2 : 4) void layer_kernel(Layer
   const int nr = min(kRows, a.rows - row0);
   if (HIDDEN) {
     // (the hidden width is a multiple of 32: a 16-byte piece is inside or outside as a whole)
-    __bf16 *Y = static_cast<__bf16 *>(a.Y);
+    __bf16 *Y = static_cast<__bf16 *>(own(a.Y));
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < RB; ++i) {
       const int p = tid + kThreads * i, r = p >> 4, c = p & 15;
       if (r < nr && tf * kFeatures + 8 * c < a.out_dim)
         *reinterpret_cast<u32x4 *>(Y + (size_t)(row0 + r) * a.ldy + tf * kFeatures + 8 * c) =
             *reinterpret_cast<const u32x4 *>(stage + r * OPITCH + 16 * c);
     }
   } else {
-    float *Y = static_cast<float *>(a.Y);
+    float *Y = static_cast<float *>(own(a.Y));
     for (int p = tid; p < nr * kFeatures; p += kThreads) {
       const int r = p >> 7, c = p & 127;
       if (tf * kFeatures + c < a.out_dim)
@@ -279,13 +301,38 @@ __global__ __launch_bounds__(256) void rows_to_bf16_kernel(const float *__restri
   for (int c = lane; c < cols; c += 64) o[c] = (__bf16)(c < S ? x[c] : 0.0f);
 }
 
-template <int KI, bool HIDDEN>
+// The output layer of a value head on bf16 activations, its one feature: a wavefront per row, eight neighbouring inputs to a lane.
+// Bound by the rows' bytes, which are still in the last-level cache.
+constexpr int kDotRows = kThreads / 64;
+__global__ __launch_bounds__(kThreads) void value_dot_kernel(const __bf16 *__restrict__ h, int pitch, int pieces, int64_t rows,
+                                                            const void *W, int64_t w_stride, const float *b, int32_t b_stride, int32_t N,
+                                                            int32_t envs_per_agent, float *__restrict__ Y) {
+  typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+  const int lane = threadIdx.x & 63;
+  const int64_t r = (int64_t)blockIdx.x * kDotRows + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  if (r >= rows) return;
+  const int agent = (int)(r % N) / envs_per_agent;
+  const u32x4 *w = reinterpret_cast<const u32x4 *>(static_cast<const unsigned char *>(W) + (size_t)agent * w_stride);
+  const u32x4 *x = reinterpret_cast<const u32x4 *>(h + r * pitch);
+  float s = 0.0f;
+  for (int p = lane; p < pieces; p += 64) {
+    // (packed blocks: feature 0 of inputs 16 kb + 8 g .. sits in lane 32 g)
+    const bf16x8 xv = __builtin_bit_cast(bf16x8, x[p]), wv = __builtin_bit_cast(bf16x8, w[(p >> 1) * 64 + 32 * (p & 1)]);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s = fmaf((float)xv[i], (float)wv[i], s);
+  }
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if (lane == 0) Y[r] = s + b[(size_t)agent * b_stride];
+}
+
+template <int KI, int RB, bool HIDDEN>
 hipError_t launch_layer(hipStream_t st, const LayerArgs &a, unsigned blocks, const IndicatorMove &move) {
-  constexpr auto kern = layer_kernel<KI, HIDDEN>;
+  constexpr auto kern = layer_kernel<KI, RB, HIDDEN>;
+  constexpr int kRows = 32 * RB;
   const hipError_t e = allow_full_lds<kern>();
   if (e != hipSuccess) return e;
   const size_t chunks = 2 * (size_t)kRows * (KI * 32 + 16);
-  const size_t ends = 48 * 1024 + (size_t)kRows * (kFeatures * (HIDDEN ? 2 : 4) + 16);
+  const size_t ends = (KI == 8 && RB == 2 ? 48 : 96) * 1024 + (size_t)kRows * (kFeatures * (HIDDEN ? 2 : 4) + 16);
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), chunks > ends ? chunks : ends, st, a, move);
   return hipGetLastError();
 }
@@ -299,60 +346,108 @@ bool layers_supported(int64_t rows, int hidden, int bf16) { return bf16 && hidde
 // (the extra 64 columns keep the rows of a power-of-two width off one set of L2 channels)
 int32_t layers_pitch(int cols) { return (cols + 15) / 16 * 16 + 64; }
 
-hipError_t launch_layers(hipStream_t st, const PackedNet &net, int64_t rows, const ObsShadow &x, float *Y, int32_t N,
-                         int32_t envs_per_agent, IndicatorMove *move) {
+namespace {
+
+// 128 rows a tile where there are more workgroups of 64 than compute units and those of 128 are full rounds, or nearly: two
+// thirds of the bytes for the same work, but one workgroup on a compute unit instead of two.  Rollouts with values, per step:
+// 8000 envs x 60 stocks x 8, 512 units (252 tiles) 63.6 -> 61.8 us, 6000 x 60 (188) 56.1 -> 57.0, 4500 x 128 (144) 59.1 -> 60.8.
+bool tall_tiles(int64_t rows, int64_t tiles_f, int32_t N, int32_t envs_per_agent) {
+  const int64_t tall = (rows + 127) / 128 * tiles_f;
+  const bool one_agent = N == envs_per_agent || envs_per_agent % 128 == 0;  // (in a tile)
+  return one_agent && (rows + 63) / 64 * tiles_f > 256 && (tall - 1) % 256 >= 223;
+}
+
+// Layer l of `count` networks of one shape.  `move`: indicators beside it, where there is room.
+hipError_t launch_one_layer(hipStream_t st, const PackedNet *const *nets, int count, int l, int64_t rows, const ObsShadow &x, float *Y,
+                            int32_t N, int32_t envs_per_agent, IndicatorMove *move) {
+  const PackedNet &net = *nets[0];
   const int Hd = net.out_dim[0];
-  const void *in = x.p;
-  int32_t pitch = x.pitch;
+  LayerArgs a;
+  for (int i = 0; i < 2; ++i) {
+    const PackedNet &p = *nets[i < count ? i : 0];
+    a.X[i] = static_cast<const __bf16 *>(l == 0 ? x.p : p.split_h[l - 1]);
+    a.Y[i] = l == 2 ? static_cast<void *>(Y) : p.split_h[l];
+    a.W[i] = p.W[l], a.b[i] = p.b[l];
+  }
+  a.xpitch = l == 0 ? x.pitch : layers_pitch(Hd), a.rows = (int32_t)rows;
+  a.ldy = l == 2 ? net.out_dim[2] : layers_pitch(Hd);
+  a.w_stride = net.w_stride[l], a.b_stride = net.b_stride[l];
+  a.out_dim = net.out_dim[l], a.nkb = net.nkb[l], a.nct = net.nct[l];
+  a.out_tanh = net.out_tanh;
+  a.N = N, a.envs_per_agent = envs_per_agent;
+  a.own_f = (net.nct[l] + 3) / 4;
+  a.tiles_f = count * a.own_f;
+  const bool tall = l < 2 && tall_tiles(rows, a.tiles_f, N, envs_per_agent);
+  const int tile_rows = tall ? 128 : 64;
+  a.tiles_r = (int32_t)((rows + tile_rows - 1) / tile_rows);
+  // an XCD's patch: the split of the eight XCDs that reads the fewest bytes (input rows and weight columns weigh the
+  // same per k), among those that leave the fewest tiles on the busiest XCD
+  int best = 0, best_tiles = 0, best_bytes = 0;
+  for (int sf = 1; sf <= 8; sf *= 2) {
+    const int pr = (a.tiles_r + 8 / sf - 1) / (8 / sf), pf = (a.tiles_f + sf - 1) / sf;
+    const int tiles = pr * pf, bytes = pr * tile_rows + pf * kFeatures;
+    if (best == 0 || tiles < best_tiles || (tiles == best_tiles && bytes < best_bytes))
+      best = sf, best_tiles = tiles, best_bytes = bytes;
+  }
+  a.split_f = best;
+  a.patch_r = (a.tiles_r + 8 / best - 1) / (8 / best), a.patch_f = (a.tiles_f + best - 1) / best;
+  const unsigned blocks = 8u * (unsigned)(a.patch_r * a.patch_f);
+  const bool two = blocks > 256;  // more workgroups than compute units
+  a.first_move = (int32_t)blocks;
+  IndicatorMove m{};
+  unsigned all = blocks;
+  // Indicators beside it, where half of the compute units have room for a workgroup of them (one or two are resident) and
+  // the launch is long enough.  Behind full compute units they take longer than in the env step, where they wait with the
+  // trades (a step of 8192 envs x 30 stocks 36.0 -> 40.7 us, of 2048 x 500 beside the second layer 64 -> 70), and longer
+  // than a launch of 32 k-blocks with a workgroup on half of the compute units (2048 x 400, 512 units 51.8 -> 53.5).
+  // Where they are moved: 2048 x 500 64 -> 62, 5000 x 100 53 -> 49.5, 4500 x 128 47.0 -> 45.6, 4200 x 40 36.9 -> 35.8.
+  if (l > 0 && move && !move->moved && (two ? blocks <= 384 : blocks <= 128 && a.nkb >= 64)) {
+    move->moved = true;
+    m = *move, all += (unsigned)((m.d.N + kThreads / 64 - 1) / (kThreads / 64));
+  }
+  if (tall) return launch_layer<8, 4, true>(st, a, all, m);
+  if (l < 2) return two ? launch_layer<8, 2, true>(st, a, all, m) : launch_layer<16, 2, true>(st, a, all, m);
+  return two ? launch_layer<8, 2, false>(st, a, all, m) : launch_layer<16, 2, false>(st, a, all, m);
+}
+
+}  // namespace
+
+bool layers_room_beside(int32_t N, int32_t envs_per_agent, int hidden) {
+  const int64_t tiles_f = 2 * ((hidden + 127) / 128);
+  if (((int64_t)N + 63) / 64 * tiles_f <= 256) return true;
+  return hidden >= 1024 && ((int64_t)N + 127) / 128 * tiles_f <= 256 && tall_tiles(N, tiles_f, N, envs_per_agent);
+}
+
+hipError_t launch_hidden(hipStream_t st, const PackedNet &net, int64_t rows, const ObsShadow &x, int32_t N, int32_t envs_per_agent) {
+  const PackedNet *nets[1] = {&net};
+  for (int l = 0; l < 2; ++l) {
+    const hipError_t e = launch_one_layer(st, nets, 1, l, rows, x, nullptr, N, envs_per_agent, nullptr);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_layers(hipStream_t st, const PackedNet &net, int64_t rows, const ObsShadow &x, float *Y, int32_t N,
+                         int32_t envs_per_agent, IndicatorMove *move, const PackedNet *beside) {
+  const PackedNet *nets[2] = {&net, beside};
   for (int l = 0; l < 3; ++l) {
     // A narrow output layer leaves few of these tiles (79 for 5000 rows x 100 stocks); workgroups of 32 features that split
     // the inputs finish sooner until their reads of the rows outweigh it.  Per step of a rollout, this kernel -> that one:
     // 8192 envs x 30 stocks, 512 units 39.9 -> 35.7 us, 1500 x 130 34.0 -> 30.7, 5000 x 100 55.4 -> 54.5, 2048 x 400 49.9 ->
     // 48.7, 600 x 500 with 1024 units 53.6 -> 50.7; 2048 x 300 with 1024 units 49.3 -> 49.5, 2048 x 500 66.0 -> 67.9.
     if (l == 2 && (rows + 63) / 64 * net.nct[2] * net.nkb[2] <= 512 * 32)
-      return launch_rows_output(st, net, rows, in, pitch, Y, N, envs_per_agent);
-    LayerArgs a;
-    a.X = static_cast<const __bf16 *>(in), a.xpitch = pitch, a.rows = (int32_t)rows;
-    a.Y = l == 2 ? static_cast<void *>(Y) : net.split_h[l];
-    a.ldy = l == 2 ? net.out_dim[2] : layers_pitch(Hd);
-    a.W = net.W[l], a.b = net.b[l], a.w_stride = net.w_stride[l], a.b_stride = net.b_stride[l];
-    a.out_dim = net.out_dim[l], a.nkb = net.nkb[l], a.nct = net.nct[l];
-    a.out_tanh = net.out_tanh;
-    a.N = N, a.envs_per_agent = envs_per_agent;
-    a.tiles_r = (int32_t)((rows + kRows - 1) / kRows), a.tiles_f = (net.nct[l] + 3) / 4;
-    // an XCD's patch: the split of the eight XCDs that reads the fewest bytes (input rows and weight columns weigh the
-    // same per k), among those that leave the fewest tiles on the busiest XCD
-    int best = 0, best_tiles = 0, best_bytes = 0;
-    for (int sf = 1; sf <= 8; sf *= 2) {
-      const int pr = (a.tiles_r + 8 / sf - 1) / (8 / sf), pf = (a.tiles_f + sf - 1) / sf;
-      const int tiles = pr * pf, bytes = pr * kRows + pf * kFeatures;
-      if (best == 0 || tiles < best_tiles || (tiles == best_tiles && bytes < best_bytes))
-        best = sf, best_tiles = tiles, best_bytes = bytes;
-    }
-    a.split_f = best;
-    a.patch_r = (a.tiles_r + 8 / best - 1) / (8 / best), a.patch_f = (a.tiles_f + best - 1) / best;
-    const unsigned blocks = 8u * (unsigned)(a.patch_r * a.patch_f);
-    const bool two = blocks > 256;  // more workgroups than compute units
-    a.first_move = (int32_t)blocks;
-    IndicatorMove m{};
-    unsigned all = blocks;
-    // Indicators beside it, where half of the compute units have room for a workgroup of them (one or two are resident) and
-    // the launch is long enough.  Behind full compute units they take longer than in the env step, where they wait with the
-    // trades (a step of 8192 envs x 30 stocks 36.0 -> 40.7 us, of 2048 x 500 beside the second layer 64 -> 70), and longer
-    // than a launch of 32 k-blocks with a workgroup on half of the compute units (2048 x 400, 512 units 51.8 -> 53.5).
-    // Where they are moved: 2048 x 500 64 -> 62, 5000 x 100 53 -> 49.5, 4500 x 128 47.0 -> 45.6, 4200 x 40 36.9 -> 35.8.
-    if (l > 0 && move && !move->moved && (two ? blocks <= 384 : blocks <= 128 && a.nkb >= 64)) {
-      move->moved = true;
-      m = *move, all += (unsigned)((m.d.N + kThreads / 64 - 1) / (kThreads / 64));
-    }
-    hipError_t e;
-    if (l < 2) e = two ? launch_layer<8, true>(st, a, all, m) : launch_layer<16, true>(st, a, all, m);
-    else e = two ? launch_layer<8, false>(st, a, all, m) : launch_layer<16, false>(st, a, all, m);
+      return launch_rows_output(st, net, rows, net.split_h[1], layers_pitch(net.out_dim[0]), Y, N, envs_per_agent);
+    const hipError_t e = launch_one_layer(st, nets, beside && l < 2 ? 2 : 1, l, rows, x, Y, N, envs_per_agent, move);
     if (e != hipSuccess) return e;
-    in = a.Y;
-    pitch = a.ldy;
   }
   return hipSuccess;
+}
+
+hipError_t launch_value_dot(hipStream_t st, const PackedNet &net, int64_t rows, const void *h, float *Y, int32_t N, int32_t envs_per_agent) {
+  hipLaunchKernelGGL(value_dot_kernel, dim3((unsigned)((rows + kDotRows - 1) / kDotRows)), dim3(kThreads), 0, st,
+                     static_cast<const __bf16 *>(h), layers_pitch(net.out_dim[0]), net.out_dim[0] / 8, rows, net.W[2], net.w_stride[2],
+                     net.b[2], net.b_stride[2], N, envs_per_agent, Y);
+  return hipGetLastError();
 }
 
 hipError_t launch_rows_to_bf16(hipStream_t st, int64_t rows, const float *X, int64_t ldx, int S, const ObsShadow &out) {

@@ -281,6 +281,40 @@ def test_small_network_books(base, Hd, D, K):
         np.testing.assert_allclose(got[k], want, rtol=1e-9, atol=1e-9)
 
 
+# The value head's hidden layers beside the policy's, step by step (two networks are a workgroup per compute unit or fewer), and
+# policies over tiles of 128 rows: ragged rows, several agents, more steps than are kept for one launch of the output layer
+@pytest.mark.parametrize("N,agents,Hd,D,K,T", [(1030, 1, 512, 40, 8, 30), (1152, 2, 512, 37, 9, 3), (560, 1, 1024, 130, 2, 2),
+                                               (2048, 1, 512, 33, 8, 2), (1100, 1, 544, 90, 3, 2), (4150, 1, 512, 40, 8, 2),
+                                               (4480, 5, 512, 40, 8, 2), (4480, 7, 512, 35, 10, 2)])
+def test_value_head_beside_the_policy(N, agents, Hd, D, K, T):
+    H = 2
+    w = inputs.WORKLOADS["large"].replace(n_envs=N, n_agents=agents, hidden=Hd, n_stocks=D, n_ind=K, steps=T, cash0=5e4)
+    d = inputs.make_all(w, horizon=H, n_market=1, steps=T)
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    ro = pr.Rollout(pr.make_config(w, horizon=H, n_market=N, schedule=pr.PR_SCHED_STEPWISE), _t(np.repeat(d["price"], N, 1)),
+                    _t(np.repeat(d["ind"], N, 1)), dev(d["actor"]), dev(d["critic"]))
+    recs = []
+    for n in (T, T, 1):  # (a second rollout over the first one's activations; one step)
+        ro.reset()
+        out = ro.alloc_buffers(n, value=True, logp=True, mu=True, shares=True)
+        ro.step_T(n, _t(d["noise"][:n]), out)
+        torch.cuda.synchronize()
+        recs.append({k: parity.to_np(v) for k, v in out.items()})
+    rec = recs[0]
+    assert all(np.array_equal(rec[k], recs[1][k]) for k in rec)
+    assert np.array_equal(rec["value"][:1], recs[2]["value"][:1])
+    per = N // agents
+    for a in range(agents):
+        envs = np.r_[a * per:a * per + 6, (a + 1) * per - 6:(a + 1) * per]
+        for t in (0, T - 1):
+            parity.check_networks(w, d["actor"], d["critic"], rec["obs"][t][envs], rec["mu"][t][envs], rec["value"][t][envs], agent=a)
+    # all values against the same network asked on its own (bf16 operands: one activation rounded the other way moves a value
+    # by 2^-9 of one of Hd terms)
+    for t in (0, T // 2, T):
+        want = parity.to_np(ro.mlp_forward(pr.PR_NET_CRITIC, _t(rec["obs"][t]))).reshape(-1)
+        assert np.linalg.norm(rec["value"][t] - want) <= 4e-3 * np.linalg.norm(want)
+
+
 # fp32 networks with infinities, numbers next to the largest and NaN among inputs and weights: every kernel of the
 # forward pass and both rollouts that keep their input tile give what fp32 sums give (a saturated unit, or NaN)
 @pytest.mark.parametrize("N,rows,Hd,D,K,fused", [(16, 16, 32, 3, 1, False), (64, 64 * 260 + 40, 256, 30, 8, False),
