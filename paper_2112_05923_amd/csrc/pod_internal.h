@@ -258,6 +258,10 @@ hipError_t launch_rollout_small(hipStream_t st, const EnvDims &d, const EnvState
                                 const PackedNet &actor, int32_t envs_per_agent, int32_t T, const float *noise,
                                 const pr_buffers &out);
 
+// And the value head over the observations of such a rollout, whole steps of N rows, on `cus` compute units.
+hipError_t launch_value_small(hipStream_t st, const PackedNet &critic, int64_t rows, const float *X, int32_t S, float *Y, int32_t N,
+                              int32_t envs_per_agent, int cus);
+
 // Stepwise rollouts of bf16 networks over one shared market table (pod_table.hip): the market part of layer 1 is formed per
 // table row into P (or per env and step, where those are fewer or the table is longer than P), everything else in one launch.
 bool table_supported(const pr_config &c);

@@ -21,6 +21,8 @@
 //   fp32,  64 hidden units: 16 envs x 5 stocks 19.6 -> 3.5 -> 2.1 us, 512 x 30 x 8 indicators 30 -> 5.1 -> 4.5
 //   fp32, 128: 64 x 10 x 2 27 -> 5.3 -> 2.9, 512 x 30 x 8 37 -> 10.9 -> 7.0 (57 registers spill; 129 before)
 //   bf16, 128: 512 x 30 x 8 30 -> 4.0 -> 3.2
+#include <algorithm>
+
 #include "pod_internal.h"
 #include "pod_tile.h"
 #include "pod_trade.h"
@@ -436,6 +438,164 @@ hipError_t launch_dtype(hipStream_t st, const SmallArgs &a) {
   return launch_inst<BF16, 128, 10>(st, a);
 }
 
+// ---------------------------------------------------------------- value head
+struct ValueSmallArgs {
+  const float *X;   // [rows][S]
+  int64_t rows;
+  PackedNet net;
+  int32_t S, N, envs_per_agent, per_agent;  // per_agent: workgroups of an agent
+  float *Y;
+};
+
+// The critic of such a rollout over its record: eight wavefronts own 16 features each of 16 rows (128 hidden units) or 32, with the
+// weights in registers from the first tile to the last.  A tile's rows are requested behind the products of the one before;
+// the output layer's one feature is summed from the activations where they are formed.
+// Bound by the products, 16 x 16 x 32 instructions, where there are many rows and by two barriers and the rows' round trip
+// where there are few.  The kernels for any network it takes the place of kept a tile's weights in a ring and a last
+// tile that is not full had a launch of its own (9 us).  Rollouts with values, fp32: 512 envs x 30 stocks x 8, 64 units, 64 steps
+// 341 -> 315 us, 16384, 32 steps 1230 -> 945; 4096 with 128 units 471 -> 418, 300 x 12 x 4 261 -> 242; bf16, 333 x 17 x 5 198 -> 177.
+template <bool BF16, int HD, int KS1>
+__global__ __launch_bounds__(kEnvThreads, 2) void value_small_kernel(ValueSmallArgs a) {
+  using namespace tile;
+  using O = Op<BF16>;
+  using Block = typename O::Block;
+  constexpr int TILES = HD / 16, RT = kWaves / TILES, RR = 16 * RT, TPR = kEnvThreads / RR, KS = HD / 32, NCT = HD / 32;
+  constexpr int NP = 64 * kPlanes<Block>, GROUPS = (8 * KS1 + TPR - 1) / TPR;
+  constexpr int XP = tile_pitch<BF16>(2 * KS1), HP = tile_pitch<BF16>(2 * KS);
+  __shared__ __align__(16) unsigned char ldsX[RR * XP];
+  __shared__ __align__(16) unsigned char ldsH[RR * HP];
+  __shared__ float part[TILES * RR];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ft = w % TILES, rt = w / TILES, q4 = lane >> 4, row = lane & 15, S = a.S;
+
+  // tiles of an agent: its rows in each step; of a single one the rows as they are
+  const bool several = a.envs_per_agent < a.N;
+  const int agent = blockIdx.x / a.per_agent, first = blockIdx.x - agent * a.per_agent;
+  const int64_t in_step = several ? a.envs_per_agent / RR : 1;
+  const int64_t tiles = several ? a.rows / a.N * in_step : (a.rows + RR - 1) / RR;
+  auto row0_of = [&](int64_t k) {
+    if (!several) return k * RR;
+    const int64_t t = k / in_step;
+    return t * a.N + (int64_t)agent * a.envs_per_agent + (k - t * in_step) * RR;
+  };
+
+  const Net net = net_of(a.net, agent);
+  auto fetch = [&](Block &b, const u32x4 *W, int nkb, int ks) {
+    const int kb = 2 * ks + (q4 >> 1);
+    fetch_w(b, W + ((size_t)min(kb, nkb - 1) * NCT + (ft >> 1)) * NP + (ft & 1) * 16 + row + 32 * (q4 & 1));
+    if (kb >= nkb) b = Block{};
+  };
+  Block w1[KS1], w2[KS];
+#pragma unroll
+  for (int i = 0; i < KS1; ++i) fetch(w1[i], net.W[0], net.nkb[0], i);
+#pragma unroll
+  for (int i = 0; i < KS; ++i) fetch(w2[i], net.W[1], 2 * KS, i);
+  const int f0 = 16 * ft + 4 * q4;
+  const f32x4 bias1 = *reinterpret_cast<const f32x4 *>(net.b[0] + f0), bias2 = *reinterpret_cast<const f32x4 *>(net.b[1] + f0);
+  f32x4 w3;  // (feature 0 of the packed output layer: input 16 kb + 8 g + e sits in lane 32 g)
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int f = f0 + i;
+    const __bf16 *p = reinterpret_cast<const __bf16 *>(net.W[2] + (size_t)(f >> 4) * NP + 32 * ((f >> 3) & 1)) + (f & 7);
+    w3[i] = (float)p[0];
+    if (!BF16) w3[i] = w3[i] + ((float)p[512] + (float)p[1024]);
+  }
+  const float b3 = net.b[2][0];
+
+  for (int i = tid; i < RR * XP / 4; i += kEnvThreads) reinterpret_cast<uint32_t *>(ldsX)[i] = 0u;
+  const int e = tid / TPR, tl = tid & (TPR - 1);
+  f32x4 pre[GROUPS];
+  auto request = [&](int64_t k) {
+    const float *x = a.X + min(row0_of(min(k, tiles - 1)) + e, a.rows - 1) * S;
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g) {
+      const int c = 4 * (tl + TPR * g);
+      if (c + 4 <= S) pre[g] = *reinterpret_cast<const env_f32x4u *>(x + c);
+      else if (c < S) pre[g] = f32x4{x[c], c + 1 < S ? x[c + 1] : 0.0f, c + 2 < S ? x[c + 2] : 0.0f, 0.0f};
+    }
+  };
+  auto stash = [&]() {
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g) {
+      const int c = 4 * (tl + TPR * g);
+      if (c < S) O::store4(ldsX + e * XP + O::off(c), pre[g][0], pre[g][1], pre[g][2], pre[g][3]);
+    }
+  };
+  const unsigned char *xop = ldsX + (16 * rt + row) * XP + O::off(8 * q4), *hop = ldsH + (16 * rt + row) * HP + O::off(8 * q4);
+  auto product = [&](auto &wb, const unsigned char *x, const f32x4 &bias) {
+    constexpr int NB = sizeof(wb) / sizeof(Block);
+    Sums s[2];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      Block b;
+      fetch_x(b, x + 2 * i * O::KBYTES);
+      mma16(wb[i], b, s[i & 1]);
+    }
+    f32x4 v = s[0].hi + s[1].hi;
+    if (!BF16) v += s[0].lo + s[1].lo;
+    v += bias;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = BF16 ? tanh_from_scaled(v[i] * kTwoLog2e) : tanh_accurate(v[i]);
+    return v;
+  };
+  auto finish = [&](int64_t k) {
+    if (tid < RR) {
+      float y = b3;
+#pragma unroll
+      for (int i = 0; i < TILES; ++i) y += part[i * RR + tid];
+      const int64_t r = row0_of(k) + tid;
+      if (r < a.rows) a.Y[r] = y;
+    }
+  };
+
+  if (first >= tiles) return;
+  request(first);
+  __syncthreads();  // (the zeros)
+  stash();
+  for (int64_t k = first; k < tiles; k += a.per_agent) {
+    __syncthreads();  // the tile's rows, and the sums of the one before
+    if (k > first) finish(k - a.per_agent);
+    request(k + a.per_agent);
+    const f32x4 h1 = product(w1, xop, bias1);
+    O::template store4<true>(ldsH + (16 * rt + row) * HP + O::off(f0), h1[0], h1[1], h1[2], h1[3]);
+    __syncthreads();
+    const f32x4 h2 = product(w2, hop, bias2);
+    float s = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s = fmaf(BF16 ? (float)(__bf16)h2[i] : h2[i], w3[i], s);
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    if (q4 == 0) part[ft * RR + 16 * rt + row] = s;
+    stash();
+  }
+  __syncthreads();
+  finish(first + (tiles - 1 - first) / a.per_agent * a.per_agent);
+}
+
+template <bool BF16, int HD, int KS1>
+hipError_t launch_value_inst(hipStream_t st, ValueSmallArgs a, int cus) {
+  constexpr int RR = 16 * (kWaves / (HD / 16));
+  const int agents = a.N / a.envs_per_agent;
+  const int64_t tiles = agents > 1 ? a.rows / a.N * (a.envs_per_agent / RR) : (a.rows + RR - 1) / RR;
+  a.per_agent = (int32_t)std::min<int64_t>(tiles, std::max(1, cus / agents));
+  hipLaunchKernelGGL((value_small_kernel<BF16, HD, KS1>), dim3((unsigned)(a.per_agent * agents)), dim3(kEnvThreads), 0, st, a);
+  return hipGetLastError();
+}
+
+template <bool BF16>
+hipError_t launch_value_dtype(hipStream_t st, const ValueSmallArgs &a, int cus) {
+  const int nkb = a.net.nkb[0];
+  if (a.net.nct[0] == 2) {
+    if (nkb <= 2) return launch_value_inst<BF16, 64, 1>(st, a, cus);
+    if (nkb <= 4) return launch_value_inst<BF16, 64, 2>(st, a, cus);
+    if (nkb <= 8) return launch_value_inst<BF16, 64, 4>(st, a, cus);
+    return launch_value_inst<BF16, 64, 10>(st, a, cus);
+  }
+  if (nkb <= 4) return launch_value_inst<BF16, 128, 2>(st, a, cus);
+  if (nkb <= 10) return launch_value_inst<BF16, 128, 5>(st, a, cus);
+  return launch_value_inst<BF16, 128, 10>(st, a, cus);
+}
+
 }  // namespace
 
 // 64 or 128 hidden units, up to 320 inputs and 32 stocks: what eight wavefronts hold in registers.
@@ -462,6 +622,13 @@ hipError_t launch_rollout_small(hipStream_t st, const EnvDims &d, const EnvState
   a.obs = out.obs, a.act_raw = out.act_raw, a.reward = out.reward, a.done = out.done, a.logp = out.logp, a.mu = out.mu;
   a.shares = out.shares;
   return actor.bf16 ? launch_dtype<true>(st, a) : launch_dtype<false>(st, a);
+}
+
+hipError_t launch_value_small(hipStream_t st, const PackedNet &critic, int64_t rows, const float *X, int32_t S, float *Y, int32_t N,
+                              int32_t envs_per_agent, int cus) {
+  ValueSmallArgs a;
+  a.X = X, a.rows = rows, a.net = critic, a.S = S, a.N = N, a.envs_per_agent = envs_per_agent, a.per_agent = 1, a.Y = Y;
+  return critic.bf16 ? launch_value_dtype<true>(st, a, cus) : launch_value_dtype<false>(st, a, cus);
 }
 
 }  // namespace pod

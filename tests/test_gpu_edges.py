@@ -315,6 +315,34 @@ def test_value_head_beside_the_policy(N, agents, Hd, D, K, T):
         assert np.linalg.norm(rec["value"][t] - want) <= 4e-3 * np.linalg.norm(want)
 
 
+# Value heads of small networks over a record: tiles that a workgroup has several of, a last tile that is not full, few inputs and
+# rows that are no multiple of four of them, several agents.  All rows against the same network asked on its own, some of each
+# agent's against the oracle.
+@pytest.mark.parametrize("base,N,agents,Hd,D,K,T", [("tiny", 16, 1, 64, 1, 0, 3), ("tiny", 1037, 1, 64, 5, 2, 15), ("tiny", 77, 1, 64, 20, 3, 5),
+                                                    ("tiny", 192, 3, 64, 30, 8, 200), ("tiny", 33, 1, 128, 2, 0, 4), ("tiny", 128, 2, 128, 12, 9, 90),
+                                                    ("tiny", 500, 1, 128, 31, 8, 12), ("large", 50, 1, 64, 13, 1, 2), ("large", 256, 4, 64, 32, 6, 70),
+                                                    ("large", 41, 1, 128, 8, 4, 9), ("large", 8250, 1, 128, 29, 8, 1)])
+def test_small_value_head(base, N, agents, Hd, D, K, T):
+    w = inputs.WORKLOADS[base].replace(n_envs=N, n_agents=agents, hidden=Hd, n_stocks=D, n_ind=K, steps=T, cash0=5e4)
+    d = inputs.make_all(w, horizon=2, n_market=1, steps=T)
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    ro = pr.Rollout(pr.make_config(w, horizon=2, n_market=1), _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+    out = ro.alloc_buffers(T, value=True, logp=False, mu=True, shares=False)
+    ro.step_T(T, _t(d["noise"]), out)
+    obs, value = out["obs"], parity.to_np(out["value"])
+    # (each kernel is within 1e-6 of 64 bits in fp32; with bf16 operands an activation rounded the other way moves a value by
+    # 2^-9 of one of Hd terms)
+    tol = 4e-3 if base == "large" else 2e-6
+    for t in range(T + 1):
+        want = parity.to_np(ro.mlp_forward(pr.PR_NET_CRITIC, obs[t])).reshape(-1)
+        assert np.linalg.norm(value[t] - want) <= tol * np.linalg.norm(want), t
+    per = N // agents
+    for a in range(agents):
+        envs = np.r_[a * per:a * per + 5, (a + 1) * per - 5:(a + 1) * per]
+        for t in (0, T):
+            parity.check_networks(w, d["actor"], d["critic"], parity.to_np(obs[t])[envs], value_rows=value[t][envs], agent=a)
+
+
 # fp32 networks with infinities, numbers next to the largest and NaN among inputs and weights: every kernel of the
 # forward pass and both rollouts that keep their input tile give what fp32 sums give (a saturated unit, or NaN)
 @pytest.mark.parametrize("N,rows,Hd,D,K,fused", [(16, 16, 32, 3, 1, False), (64, 64 * 260 + 40, 256, 30, 8, False),
