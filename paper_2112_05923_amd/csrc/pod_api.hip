@@ -80,7 +80,8 @@ int state_dim(const pr_config &c) { return 1 + 2 * c.n_stocks + c.n_stocks * c.n
 // the stepwise policy of small bf16 batches reads a bf16 copy of the observations, written along with them
 bool uses_shadow(const pr_config &c) {
   return c.schedule == PR_SCHED_STEPWISE && !small_supported(c) && !table_supported(c) && layers_supported(c.n_envs, c.hidden, c.mlp_dtype) &&
-         !few_rows(c.n_envs, state_dim(c), c.hidden, c.mlp_dtype, true);
+         !few_rows(c.n_envs, state_dim(c), c.hidden, c.mlp_dtype, true) &&
+         !query_supported(c.n_envs, state_dim(c), c.hidden, c.n_stocks, c.mlp_dtype, c.n_envs, c.n_envs / c.n_agents);
 }
 
 // rollouts of this config read layer 1 in the order [indicators | cash | prices | holdings]

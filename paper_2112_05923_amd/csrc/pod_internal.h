@@ -230,6 +230,10 @@ hipError_t launch_value_dot(hipStream_t st, const PackedNet &net, int64_t rows, 
 bool few_rows(int64_t rows, int S, int hidden, int bf16, bool converted);
 hipError_t launch_few_rows(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx, float *Y,
                            int32_t N, int32_t envs_per_agent);
+// Few rows of networks whose weights pass through one compute unit quickly: all layers in one launch that keeps nothing.
+bool query_supported(int64_t rows, int S, int hidden, int outputs, int bf16, int32_t N, int32_t envs_per_agent);
+hipError_t launch_query(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx, float *Y, int32_t N,
+                        int32_t envs_per_agent);
 // The output layer alone, on bf16 activations [rows][pitch].
 hipError_t launch_rows_output(hipStream_t st, const PackedNet &net, int64_t rows, const void *h, int64_t pitch, float *Y,
                               int32_t N, int32_t envs_per_agent);

@@ -343,6 +343,30 @@ def test_small_value_head(base, N, agents, Hd, D, K, T):
             parity.check_networks(w, d["actor"], d["critic"], parity.to_np(obs[t])[envs], value_rows=value[t][envs], agent=a)
 
 
+# networks in one launch, 16 rows a workgroup: a single row, full and partial workgroups, one k-block, odd numbers of them, inputs
+# that are no multiple of four, one output and all 32, agents, and either side of the last row count that takes it
+@pytest.mark.parametrize("base,N,rows,agents,Hd,D,K", [("tiny", 16, 1, 1, 64, 1, 0), ("tiny", 16, 17, 1, 64, 32, 0), ("tiny", 192, 180, 3, 64, 5, 2),
+                                                       ("tiny", 16, 31, 1, 128, 7, 0), ("tiny", 128, 100, 2, 256, 32, 16), ("tiny", 16, 300, 1, 256, 17, 9),
+                                                       ("large", 16, 15, 1, 64, 1, 1), ("large", 16, 33, 1, 128, 16, 4), ("large", 256, 250, 4, 256, 29, 17),
+                                                       ("large", 16, 16, 1, 512, 30, 19), ("large", 128, 65, 2, 512, 3, 0), ("large", 8200, 8192, 1, 512, 12, 2),
+                                                       ("large", 8200, 8193, 1, 512, 12, 2), ("tiny", 8200, 8192, 1, 64, 12, 2)])
+def test_networks_in_one_launch(base, N, rows, agents, Hd, D, K):
+    w = inputs.WORKLOADS[base].replace(n_envs=N, n_agents=agents, hidden=Hd, n_stocks=D, n_ind=K, steps=1)
+    d = inputs.make_all(w, horizon=1, n_market=1, steps=1)
+    dev = lambda m: {k: _t(v) for k, v in m.items()}
+    ro = pr.Rollout(pr.make_config(w, horizon=1, n_market=1), _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+    X = np.random.default_rng(rows).standard_normal((rows, w.state_dim + 3)).astype(np.float32)
+    X[:, w.state_dim:] = np.nan  # (rows end there: what lies behind may be anything)
+    Xd = _t(X)
+    mu, val = (parity.to_np(ro.mlp_forward(net, Xd[:, :w.state_dim])) for net in (pr.PR_NET_ACTOR, pr.PR_NET_CRITIC))
+    per = N // agents
+    for a in range(agents):
+        pick = np.array([r for r in range(rows) if (r % N) // per == a])
+        pick = np.unique(np.concatenate([pick[:: max(1, len(pick) // 40)], pick[-20:]])) if len(pick) else pick
+        if len(pick):
+            parity.check_networks(w, d["actor"], d["critic"], X[pick][:, :w.state_dim], mu[pick], val[pick], agent=a)
+
+
 # fp32 networks with infinities, numbers next to the largest and NaN among inputs and weights: every kernel of the
 # forward pass and both rollouts that keep their input tile give what fp32 sums give (a saturated unit, or NaN)
 @pytest.mark.parametrize("N,rows,Hd,D,K,fused", [(16, 16, 32, 3, 1, False), (64, 64 * 260 + 40, 256, 30, 8, False),
