@@ -599,18 +599,15 @@ hipError_t launch_value_dtype(hipStream_t st, const ValueSmallArgs &a, int cus) 
 }  // namespace
 
 // 64 or 128 hidden units, up to 320 inputs and 32 stocks: what eight wavefronts hold in registers.
-// A round of workgroups, one per compute unit, is 4096 envs.  The launches per step that take over cost about 17 us and
-// then grow more slowly, so the line lies where they win over a rollout of 24 steps; us per step, this kernel and those:
-//   fp32, 128 units, 301 inputs (129 registers spill): 4096 envs 15.1 and 21.7, 8192 30.5 and 34.9, 12288 45.7 and 42.7,
-//   65536 241 and 152; 171 inputs: 8192 29.0 and 29.3, 12288 43.5 and 34.1
-//   fp32, 128 units, 151 inputs: 4096 6.6 and 19.1, 65536 104 and 116; 61 inputs: 65536 97 and 103
-//   fp32, 64 units, 301 inputs: 4096 5.4 and 18.0, 65536 83 and 136; bf16, 128 units, 301 inputs: 65536 71 and 86
-// The state and the policy are loaded once a call, so a call of a single step has less of it (us): fp32, 128 units, 301 inputs
-// 4096 envs 35 and 30, 8192 63 and 43; 151 inputs 4096 18 and 25, 16384 52 and 45, 65536 193 and 139; bf16 301 inputs
-// 4096 13 and 26, 65536 151 and 138.  The number of steps is not asked: a rollout gives the same bits however it is cut.
+// A round of workgroups, one per compute unit, is 4096 envs, and the launches per step that would take over (query_kernel or
+// mlp_tiles_kernel, and an env step) never win.  Rollouts with values of 24 steps, 16 of 16384 envs and 6 of 65536; us, this and those:
+//   envs                         512           4096          8192          16384          65536
+//   fp32, 128 units, 301     203 and 359   324 and 525   639 and 903   871 and 1166  1498 and 1629
+//   fp32, 128 units, 151     109 and 328   181 and 438   327 and 694   446 and 854    792 and 1204
+//   fp32,  64 units, 301     132 and 344   191 and 470   372 and 793   505 and 1025   876 and 1420
+//   bf16, 128 units, 301      97 and 292   150 and 345   310 and 500   429 and 726    738 and 808
 bool small_supported(const pr_config &c) {
   const int S = 1 + 2 * c.n_stocks + c.n_stocks * c.n_ind;
-  if (c.mlp_dtype == PR_MLP_F32 && c.hidden == 128 && S > 160 && c.n_envs > 8192) return false;
   return c.schedule == PR_SCHED_STEPWISE && (c.hidden == 64 || c.hidden == 128) && c.n_stocks <= 32 && S <= 16 * kMaxBlocks;
 }
 

@@ -572,7 +572,7 @@ def test_queries_side_by_side(base, N, rows, Hd, D, K):
         assert all(torch.equal(y, eager[i]) for i in range(2) for y in outs[i])
 
 
-# either side of the number of envs up to which a small network's rollout is one launch: the same rollout however it is cut
+# a small network over many envs, a last workgroup full or of one: the same rollout however it is cut
 @pytest.mark.parametrize("N", [8192, 8193])
 def test_small_networks_of_many_envs(N):
     T, H = 4, 3
