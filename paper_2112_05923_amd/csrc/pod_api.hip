@@ -8,7 +8,6 @@
 #include <stdlib.h>
 #include <string.h>
 
-#include "pod_half2.h"
 #include "pod_internal.h"
 
 using namespace pod;
@@ -21,15 +20,15 @@ struct pr_handle {
   pr_market market;
   PackedNet actor, critic;
   PackedNet actor_rot;    // the actor with layer 1 packed for inputs in the order [indicators | cash | prices | holdings],
-                          // or [indicators | prices | zeros | holdings | cash | zeros] (market_first)
+                          // or [indicators | prices | holdings | cash] (market_first)
   void *w1_rot;           // (null when no rollout of this handle reads that order)
   PackedNet critic_rot;   // the critic likewise, where its hidden layers run beside the actor's (null W[0]: they do not)
   void *beside_h[2];      // its activations: of one step, and of `beside_steps` steps
   int32_t beside_steps;
   void *w_packed[2][3];   // device, per net and layer
   float *b_packed[2][3];
-  void *half_w[2][3];     // layers in fp16 parts, and their factors, where a kernel takes them
-  float *half_u[2][3];
+  void *half_w[2];        // the critic's hidden layers in fp16 parts, and their factors (null: no value head takes them)
+  float *half_u[2];
   float *mu_scratch;      // [N, D]
   int32_t *start;         // [N] episode start rows (zeros unless a replay table is set)
   ObsShadow shadow;       // bf16 observations of the layer-per-launch actor, or null
@@ -71,7 +70,7 @@ struct Layout {
   size_t w1_rot, w1_beside, beside_h[2];
   size_t cash, tau, h, ep_ret, ep_sum, ep_sqsum, ep_cnt, mu, start, split[3], query[3];
   size_t table_w[2][2], table_p, tau0;
-  size_t half_w[2][3], half_u[2][3];
+  size_t half_w[2], half_u[2];
   size_t total;
 };
 
@@ -100,10 +99,12 @@ int32_t value_beside_steps(const pr_config &c) {
   return (int32_t)std::max<int64_t>(1, ((int64_t)32 << 20) / step);
 }
 
-// k-blocks of that copy of layer 1.  The persistent fp32 rollout has the market columns in blocks of their own.
+// k-blocks of that copy of layer 1.  The persistent fp32 rollout of few envs reads blocks of 32 inputs, with the cash last,
+// so that all market columns come first.
 bool market_first(const pr_config &c) { return c.schedule == PR_SCHED_FUSED && c.mlp_dtype == PR_MLP_F32; }
 int rotated_blocks(const pr_config &c) {
-  return market_first(c) ? f32_market_blocks(c.n_stocks, c.n_ind) + f32_portfolio_blocks(c.n_stocks) : (state_dim(c) + 15) / 16;
+  const int nkb = (state_dim(c) + 15) / 16;
+  return market_first(c) ? (nkb + 1) & ~1 : nkb;
 }
 
 // k-blocks of the market (0) and the portfolio (1) part of layer 1 in rollouts over a shared table
@@ -111,13 +112,8 @@ int table_blocks(const pr_config &c, int part) {
   return part == 0 ? table_market_blocks(c.n_stocks, c.n_ind) : table_portfolio_blocks(c.n_stocks);
 }
 
-// k-blocks of a layer some kernel takes in fp16 parts, or 0: the persistent rollout the actor (the market part of layer 1), the
-// value head over many rows the critic's hidden layers
-int half_blocks(const pr_config &c, int net, int l) {
-  if (c.mlp_dtype != PR_MLP_F32 || c.hidden != 256) return 0;
-  if (net == 1) return l == 2 ? 0 : l == 1 ? 16 : (state_dim(c) + 15) / 16;
-  return !market_first(c) ? 0 : l == 0 ? f32_market_blocks(c.n_stocks, c.n_ind) : 16;
-}
+// the value head over many rows takes the critic in fp16 parts
+bool value_in_halves(const pr_config &c) { return c.mlp_dtype == PR_MLP_F32 && c.hidden == 256; }
 
 int validate_config(const pr_config *c) {
   if (!c) return PR_EINVAL;
@@ -189,13 +185,12 @@ Layout make_layout(const pr_config &c) {
     L.table_p = take(table_scratch_bytes(c.n_envs));
     L.tau0 = take(N * 4);
   }
-  for (int net = 0; net < 2; ++net)
-    for (int l = 0; l < 3; ++l) {
-      const int nct = l < 2 ? Hd / 32 : (D + 31) / 32;
-      if (!half_blocks(c, net, l)) continue;
-      L.half_w[net][l] = take((size_t)halves_bytes(half_blocks(c, net, l), nct) * P);
-      L.half_u[net][l] = take((size_t)nct * 32 * 4 * P);
+  if (value_in_halves(c)) {
+    for (int l = 0; l < 2; ++l) {
+      L.half_w[l] = take((size_t)halves_bytes((in_dim[l] + 15) / 16, Hd / 32) * P);
+      L.half_u[l] = take((size_t)Hd * 4 * P);
     }
+  }
   L.total = off;
   return L;
 }
@@ -235,7 +230,7 @@ void fill_net(PackedNet &pn, const pr_handle *h, int net) {
   pn.bf16 = bf;
   pn.out_tanh = net == 0 ? 1 : 0;
   pn.split_rows = split_scratch_rows(c.n_envs, Hd);
-  for (int l = 0; l < 3; ++l) pn.half_w[l] = h->half_w[net][l], pn.half_u[l] = h->half_u[net][l];
+  for (int l = 0; l < 2; ++l) pn.half_w[l] = net == 1 ? h->half_w[l] : nullptr, pn.half_u[l] = net == 1 ? h->half_u[l] : nullptr;
   set_scratch(pn, h->split);
   pn.split_x.pitch = layers_pitch(S);
   pn.split_x.cols = (S + 15) / 16 * 16;
@@ -262,13 +257,13 @@ int pack_nets(pr_handle *h, const pr_weights *actor, const pr_weights *critic) {
   // by the D K indicator columns (biases are shared).
   const int DK = D * c.n_ind;
   if (h->w1_rot) {
-    const int portfolio = 16 * f32_market_blocks(D, c.n_ind);
-    PackJob &j = jobs[n++] = {actor->W1, actor->b1, h->w1_rot, h->b_packed[0][0], S, Hd, rotated_blocks(c), {{0, 1 + 2 * D, DK}, {DK, 0, 1 + 2 * D}}};
+    const int cash = market_first(c) ? 1 : 0;  // the cash behind the others, or in front of them
+    PackJob &j = jobs[n++] = {actor->W1, actor->b1, h->w1_rot, h->b_packed[0][0], S, Hd, rotated_blocks(c),
+                              {{0, 1 + 2 * D, DK}, {DK, cash, 1 + 2 * D - cash}, {S - cash, 0, cash}}};
     if (h->critic_rot.W[0]) {
       PackJob &k = jobs[n++] = j;
       k.W = critic->W1, k.b = critic->b1, k.Wp = const_cast<void *>(h->critic_rot.W[0]), k.bp = h->b_packed[1][0];
     }
-    if (market_first(c)) j.run[1] = {DK, 1, D}, j.run[2] = {portfolio, 1 + D, D}, j.run[3] = {portfolio + D, 0, 1};
   }
   // Over a shared table layer 1 is taken in two parts: [indicators | prices], and [holdings | zeros | cash].
   for (int net = 0; net < 2 && h->table_w[0][0]; ++net) {
@@ -278,14 +273,6 @@ int pack_nets(pr_handle *h, const pr_weights *actor, const pr_weights *critic) {
                  {{0, 1 + D, D}, {16 * table_blocks(c, 1) - 1, 0, 1}}};
   }
   POD_HIP(launch_pack_layers(h->stream, jobs, n, P, bf));
-  if (market_first(c)) {
-    const PackedNet &a = h->actor_rot;
-    HalvesJob halves[3];
-    for (int l = 0; l < 3; ++l)
-      halves[l] = {a.W[l], a.w_stride[l], a.half_w[l], halves_bytes(half_blocks(c, 0, l), a.nct[l]), a.half_u[l], half_blocks(c, 0, l), a.nct[l],
-                   l == 0 ? 0 : kHiddenExp};
-    POD_HIP(launch_halves(h->stream, halves, 3, P));
-  }
   return PR_OK;
 }
 
@@ -390,9 +377,8 @@ int rollout_init(const pr_config *cfg, const pr_market *market, const pr_weights
     h->tau0 = reinterpret_cast<int32_t *>(ws + L.tau0);
   }
 
-  for (int net = 0; net < 2; ++net)
-    for (int l = 0; l < 3; ++l)
-      if (half_blocks(*cfg, net, l)) h->half_w[net][l] = ws + L.half_w[net][l], h->half_u[net][l] = reinterpret_cast<float *>(ws + L.half_u[net][l]);
+  if (value_in_halves(*cfg))
+    for (int l = 0; l < 2; ++l) h->half_w[l] = ws + L.half_w[l], h->half_u[l] = reinterpret_cast<float *>(ws + L.half_u[l]);
 
   EnvDims &d = h->dims;
   d.N = cfg->n_envs;

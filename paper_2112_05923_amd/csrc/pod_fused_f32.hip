@@ -15,25 +15,20 @@
 // The two kinds of wavefront run separate loops with the same barriers: neither's
 // registers are live in the other's code.
 //
-// Hidden layers and the market part of layer 1 are products of two fp16 parts per operand (pod_half2.h): half the matrix
-// work and two thirds of the weights' bytes of three bf16 parts.  A row's market columns have a scale of their own, found while
-// they are written beside layer 2.  The portfolio's columns come at the end of the trades and are a block or two: there three
-// bf16 parts, which need no scale, cost less than a search for one.
-//
-// Bound with 16 envs by the chain of a step -- tail of layer 1, activation, layer 2, activation, output layer, trades of 3 us --
-// beside a weight stream of 510 KB (96 KB of layer 2 stay in LDS, the output layer's 32 KB in registers), 4.2 us at 64 B a
-// clock; with 32 envs by vector work (1700 instructions a wavefront and step, 49 % of the cycles) and the same chain, the
-// matrix pipe busy 27 % at 1.85 GHz.
-// 301 inputs, per step, against three bf16 parts in all products: 1024 envs 8.1 -> 6.6 us, 4096 9.9 -> 7.9, 8192 17.0 ->
-// 14.2, 16384 33.6 -> 27.6, 65536 of 64 agents 139 -> 110; 12 stocks x 4 indicators, 4096 envs 8.6 -> 6.0, 8192 11.7 -> 10.1.
-// 2-norm of the means' error against 64 bits: 4096 envs 3.02e-7 -> 2.72e-7, 8192 3.12 -> 2.80, 1024 envs of 8 stocks x 4
-// indicators 2.19 -> 2.10 (2.26 with layer 2 in one chain over all inputs, not in two halves added up).
+// Bound with 16 envs by the weight stream -- 800 KB a step, which a compute unit takes in
+// at 64 B a clock, 6.6 us at the 1.9 GHz this runs at; 84 KB of layer 2 stay in LDS and the
+// output layer's 48 KB in registers (without either 12.3 us a step for 11.4) -- and by the
+// chains beside it: two epilogues of 1 us, trades 3 us; the matrix pipe is busy 38 % of a
+// step.  With 32 envs the matrix instructions take as long as the stream: 8 us of 17.6, the
+// chip at 1.75-1.8 GHz (counters of both: profiles/pmc_fp32_kernels.txt).
+// 301 inputs, per step, against 32 envs whose eight wavefronts all take turns at network
+// and envs: 1024 envs 16.2 -> 8.2 us, 4096 16.9 -> 10.9, 8192 20.4 -> 17.2, 16384 37.9 ->
+// 34.0, 65536 of 64 agents 151 -> 135; 12 stocks x 4 indicators, 4096 envs, 14.2 -> 8.4.
 //
 // Compiled with floating-point contraction off (integer decisions depend on
 // one rounding per operation).
 #include <type_traits>
 
-#include "pod_half2.h"
 #include "pod_internal.h"
 #include "pod_tile.h"
 #include "pod_trade.h"
@@ -47,16 +42,9 @@ using O = Op<false>;
 
 constexpr int NM = 4, NE = 4;       // wavefronts of the network / of the envs
 constexpr int NT = 64 * (NM + NE);
+constexpr int HP = tile_pitch<false>(16);
 constexpr int MUP = 36;             // row pitch of a plane of partial means
-
-// An operand of the hidden layers, eight consecutive inputs of a row or a feature: their two fp16 parts.
-struct Blk2 {
-  u32x4 p[2];
-};
-// ... in an activation row: 16 bytes of first parts, 16 of second ones; where column c starts
-__host__ __device__ inline int half_off(int c) { return (c >> 3) * 32 + (c & 7) * 2; }
-__host__ __device__ constexpr int half_pitch(int nkb) { return nkb * 64 + 16; }
-constexpr int HP = half_pitch(16);
+constexpr int LB = 8 * 192;         // 16-byte pieces of a k-block of a hidden layer
 
 // What differs between 16 and 32 envs: the matrix instruction, and with it how weights, inputs and sums lie in the lanes.
 //  32: v_mfma_f32_32x32x16, lane l feeds feature l % 32 and row l % 32, inputs 8 (l / 32) .. + 7 of 16
@@ -69,13 +57,11 @@ struct Geometry {
   typedef std::conditional_t<SM, f32x4, f32x16> Acc;
   static constexpr int NACC = SM ? 4 : 2;             // accumulators of a wavefront's 64 features: units per block of inputs
   static constexpr int KIN = SM ? 32 : 16;            // inputs per block
-  static constexpr int KBYTES = KIN * 4;              // ... in an activation row of fp16 parts
-  static constexpr int BLOCK = (SM ? 2 : 1) * 8 * 128;  // 16-byte pieces between the blocks of a hidden layer
-  static constexpr int PBLOCK = (SM ? 2 : 1) * 8 * 192, PBYTES = KIN * O::ESZ;  // ... and of its part in three bf16 numbers
+  static constexpr int KBYTES = KIN * O::ESZ;         // ... in an activation row
+  static constexpr int BLOCK = SM ? 2 * LB : LB;      // 16-byte pieces between the blocks of a hidden layer
   static constexpr int NK2 = 256 / KIN;
-  static constexpr int PK = SM ? 3 : 6, PU = PK * NACC;  // blocks, and units of weights, in flight per wavefront
-  static constexpr int NP = SM ? 2 : 3;               // blocks of portfolio columns at most
-  static constexpr int NL = SM ? 12 : 5;              // units of layer 2 per wavefront that stay in LDS
+  static constexpr int PK = SM ? 2 : 4, PU = PK * NACC;  // blocks, and units of weights, in flight per wavefront
+  static constexpr int NL = SM ? 7 : 1;               // units of layer 2 per wavefront that stay in LDS
   static constexpr int NG = SM ? 4 : 8;               // groups of four features per lane
   static constexpr int N3 = SM ? 2 : 4, NC3 = SM ? 2 : 1;  // output layer: blocks of a wavefront's inputs, tiles of outputs
   static constexpr int ND = E / 8, ROWS = E / NE;     // stocks per thread and market rows per wavefront of the envs
@@ -84,29 +70,17 @@ struct Geometry {
 
   static __device__ inline int row(int lane) { return lane & (E - 1); }
   static __device__ inline int part(int lane) { return lane / E; }
-  // of unit 0 of features 64 w .., in blocks of PIECES 16-byte pieces
-  template <int PIECES>
-  static __device__ inline const u32x4 *base(const u32x4 *W, int w, int lane) {
-    return SM ? W + ((size_t)(lane >> 5) * 8 + 2 * w) * PIECES + ((lane >> 4) & 1) * 32 + (lane & 15) : W + (size_t)(2 * w) * PIECES + lane;
+  static __device__ inline const u32x4 *base(const u32x4 *W, int w, int lane) {  // of unit 0 of features 64 w ..
+    return SM ? W + ((size_t)(lane >> 5) * 8 + 2 * w) * 192 + ((lane >> 4) & 1) * 32 + (lane & 15) : W + (size_t)(2 * w) * 192 + lane;
   }
   static __device__ inline const u32x4 *unit(const u32x4 *W, int u) {
-    return W + (size_t)(u / NACC) * BLOCK + (SM ? ((u >> 1) & 1) * 128 + (u & 1) * 16 : (u & 1) * 128);
+    return W + (size_t)(u / NACC) * BLOCK + (SM ? ((u >> 1) & 1) * 192 + (u & 1) * 16 : (u & 1) * 192);
   }
-  static __device__ inline const u32x4 *unit3(const u32x4 *W, int u) {
-    return W + (size_t)(u / NACC) * PBLOCK + (SM ? ((u >> 1) & 1) * 192 + (u & 1) * 16 : (u & 1) * 192);
-  }
-  static __device__ inline void mma(const Blk2 &w, const Blk2 &x, Acc &c) {
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {  // the smallest first
-      const f16x8 a = __builtin_bit_cast(f16x8, w.p[i == 0]), b = __builtin_bit_cast(f16x8, x.p[i == 1]);
-      if constexpr (SM) c = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
-      else c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
-    }
-  }
-  static __device__ inline void mma3(const u32x4 *w, const Blk3 &x, Acc &c) {
+  static __device__ inline void fetch_unit(Blk3 &b, const u32x4 *W, int u) { fetch_w(b, unit(W, u)); }
+  static __device__ inline void mma(const Blk3 &w, const Blk3 &x, Acc &c) {
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
-      const bf16x8 a = __builtin_bit_cast(bf16x8, w[kSplitA[i]]), b = __builtin_bit_cast(bf16x8, x.p[kSplitB[i]]);
+      const bf16x8 a = __builtin_bit_cast(bf16x8, w.p[kSplitA[i]]), b = __builtin_bit_cast(bf16x8, x.p[kSplitB[i]]);
       if constexpr (SM) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
       else c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
     }
@@ -124,39 +98,17 @@ struct Geometry {
   }
 };
 
-__device__ inline void fetch_half(Blk2 &b, const u32x4 *p) { b.p[0] = p[0], b.p[1] = p[64]; }
-__device__ inline void fetch_half(Blk2 &b, const unsigned char *p) {
-  b.p[0] = *reinterpret_cast<const u32x4 *>(p), b.p[1] = *reinterpret_cast<const u32x4 *>(p + 16);
-}
-__device__ inline void put_half4(unsigned char *p, const float (&v)[4]) {  // (scaled tanh outputs)
-  uint32_t h0, h1, l0, l1;
-  split2_pair<true>(v[0], v[1], h0, l0);
-  split2_pair<true>(v[2], v[3], h1, l1);
-  *reinterpret_cast<u32x2 *>(p) = u32x2{h0, h1};
-  *reinterpret_cast<u32x2 *>(p + 16) = u32x2{l0, l1};
-}
-
-// the largest of the wavefront's numbers, none of which is negative
-__device__ inline float wave_max(float x) {
-  int v = __builtin_bit_cast(int, x);
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true));  // one, two, four, eight lanes of a row of 16 over
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true));
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true));
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true));
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, true));  // the last lane of a row to the next row, of two to the next two
-  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, true));
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(v, 63));
-}
+// whole blocks of 32 inputs for the short instruction
+template <int E>
+__host__ __device__ inline int input_pitch(int S) { return tile_pitch<false>(E == 16 ? (S + 31) / 32 * 2 : (S + 15) / 16); }
 
 struct F32Args {
   EnvDims d;
   EnvState st;
   const float *price, *ind;
-  PackedNet actor;  // layer 1 in the input order [indicators | prices | zeros | holdings | cash | zeros], either part in whole
-                    // blocks of 32 inputs; in fp16 parts its market part and the other layers
+  PackedNet actor;  // layer 1 in the input order [indicators | prices | holdings | cash], whole blocks of 32 inputs
   int32_t envs_per_agent, T;
-  int32_t market, portfolio;  // k-blocks of either part
-  int32_t hidden_bytes;       // of the hidden tile's place, which the trades take as well
+  int32_t xpitch;
   const float *noise;  // [T, N, D]
   float *obs;          // [T+1, N, S]
   float *act_raw;      // [T, N, D]
@@ -167,8 +119,7 @@ struct F32Args {
   int32_t *shares;     // opt [T, N, D]
 };
 
-// tanh of sixteen values, times kHiddenScale, one operation at a time over all of them (see tanh_in_place), with between(0 .. 11)
-// behind each.
+// tanh of sixteen values, one operation at a time over all of them (see tanh_in_place), with between(0 .. 11) behind each.
 template <class Between>
 __device__ inline void tanh_accurate_16(float (&z)[16], Between between) {
   float e[16], x2[16], ps[16];
@@ -189,39 +140,39 @@ __device__ inline void tanh_accurate_16(float (&z)[16], Between between) {
   all([&](int i, float) { ps[i] = fmaf(x2[i], ps[i], -1.0f / 3.0f); });
   all([&](int i, float x) { x2[i] = x2[i] * x; });
   all([&](int i, float x) { ps[i] = fmaf(x2[i], ps[i], x); });
-  all([&](int i, float x) { e[i] = copysignf(fmaf(e[i], -2.0f * kHiddenScale, kHiddenScale), x), ps[i] = ps[i] * kHiddenScale; });
+  all([&](int i, float x) { e[i] = copysignf(1.0f - 2.0f * e[i], x); });
   all([&](int i, float x) { z[i] = fabsf(x) < 0.25f ? ps[i] : e[i]; });
 }
 
 // acc += blocks [0, n) of a range of inputs; the ring holds the first units.  N > 0: n at compile time, in straight-line code.
 template <class G, int N>
-__device__ inline void products(typename G::Acc (&acc)[G::NACC], Blk2 (&ring)[G::PU], const unsigned char *x, const u32x4 *W, int n) {
+__device__ inline void products(typename G::Acc (&acc)[G::NACC], Blk3 (&ring)[G::PU], const unsigned char *x, const u32x4 *W, int n) {
   if constexpr (N > 0) {
-    Blk2 xn;
-    fetch_half(xn, x);
+    Blk3 xn;
+    fetch_x(xn, x);
 #pragma unroll
     for (int K = 0; K < N; ++K) {
-      const Blk2 xv = xn;
+      const Blk3 xv = xn;
 #pragma unroll
       for (int j = 0; j < G::NACC; ++j) {
         const int u = G::NACC * K + j;
         if (j == 0 && K + 1 < N) {
-          fetch_half(xn, x + (K + 1) * G::KBYTES);
+          fetch_x(xn, x + (K + 1) * G::KBYTES);
           __builtin_amdgcn_sched_barrier(0);
         }
         G::mma(ring[u % G::PU], xv, acc[j]);
-        if (u + G::PU < G::NACC * N) fetch_half(ring[u % G::PU], G::unit(W, u + G::PU));
+        if (u + G::PU < G::NACC * N) G::fetch_unit(ring[u % G::PU], W, u + G::PU);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
   } else {
     auto block = [&](int K, int k) {  // (k: K modulo PK, at compile time)
-      Blk2 xv;
-      fetch_half(xv, x + K * G::KBYTES);
+      Blk3 xv;
+      fetch_x(xv, x + K * G::KBYTES);
 #pragma unroll
       for (int j = 0; j < G::NACC; ++j) {
         G::mma(ring[G::NACC * k + j], xv, acc[j]);
-        fetch_half(ring[G::NACC * k + j], G::unit(W, G::NACC * min(K + G::PK, n - 1) + j));
+        G::fetch_unit(ring[G::NACC * k + j], W, G::NACC * min(K + G::PK, n - 1) + j);
         __builtin_amdgcn_sched_barrier(0);
       }
     };
@@ -236,39 +187,32 @@ __device__ inline void products(typename G::Acc (&acc)[G::NACC], Blk2 (&ring)[G:
   }
 }
 
-// Layer 2, in two chains over half of the inputs each: the first NL units from LDS (`own`, this lane's), the others through the ring, which holds the first of them.
+// Layer 2: the first NL units from LDS (`own`, this lane's), the others through the ring, which holds the first of them.
 template <class G>
-__device__ inline void products2(typename G::Acc (&acc)[G::NACC], Blk2 (&ring)[G::PU], const unsigned char *x, const u32x4 *own, const u32x4 *W) {
+__device__ inline void products2(typename G::Acc (&acc)[G::NACC], Blk3 (&ring)[G::PU], const unsigned char *x, const u32x4 *own, const u32x4 *W) {
   constexpr int NL = G::NL;
-  typename G::Acc first[G::NACC];
-  Blk2 xn, wn;
-  fetch_half(xn, x);
-  fetch_half(wn, own);
+  Blk3 xn, wn;
+  fetch_x(xn, x);
+  fetch_w(wn, own);
 #pragma unroll
   for (int K = 0; K < G::NK2; ++K) {
-    const Blk2 xv = xn;
+    const Blk3 xv = xn;
 #pragma unroll
     for (int j = 0; j < G::NACC; ++j) {
-      if (K == G::NK2 / 2) {
-        first[j] = acc[j];
-        G::clear(acc[j]);
-      }
       const int u = G::NACC * K + j, r = u - NL;
-      const Blk2 wv = r < 0 ? wn : ring[r < 0 ? 0 : r % G::PU];
-      if (j == 0 && K + 1 < G::NK2) fetch_half(xn, x + (K + 1) * G::KBYTES);
-      if (u + 1 < NL) fetch_half(wn, own + (u + 1) * 128);
+      const Blk3 wv = r < 0 ? wn : ring[r < 0 ? 0 : r % G::PU];
+      if (j == 0 && K + 1 < G::NK2) fetch_x(xn, x + (K + 1) * G::KBYTES);
+      if (u + 1 < NL) fetch_w(wn, own + (u + 1) * 192);
       __builtin_amdgcn_sched_barrier(0);
       G::mma(wv, xv, acc[j]);
-      if (r >= 0 && u + G::PU < G::NACC * G::NK2) fetch_half(ring[r % G::PU], G::unit(W, u + G::PU));
+      if (r >= 0 && u + G::PU < G::NACC * G::NK2) G::fetch_unit(ring[r % G::PU], W, u + G::PU);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-#pragma unroll
-  for (int j = 0; j < G::NACC; ++j) acc[j] += first[j];
 }
 
-// NH, NP: blocks of market and of portfolio columns (0: at run time)
-template <int E, int NH, int NP>
+// NK1, NH: blocks of layer 1, and how many of them hold market columns only (0: at run time)
+template <int E, int NK1, int NH>
 __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
   using G = Geometry<E>;
   using Tr = typename G::Tr;
@@ -279,39 +223,28 @@ __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n0 = (int)xcd_index(blockIdx.x, gridDim.x) * E;
   const size_t N = (size_t)d.N;
-  const int xpitch = half_pitch(a.market), ppitch = tile_pitch<false>(a.portfolio);
-  unsigned char *ldsX = lds, *ldsP = ldsX + E * xpitch;     // input tile: market columns, scaled and in fp16 parts, and portfolio
-  unsigned char *ldsH = ldsP + E * ppitch;                  // hidden tile, and in it the trades' scratch
-  float *planes = reinterpret_cast<float *>(ldsH + a.hidden_bytes);  // [NM][E][MUP] partial means
+  unsigned char *ldsX = lds, *ldsH = ldsX + E * a.xpitch;  // input tile; hidden tile, and in it the trades' scratch
+  float *planes = reinterpret_cast<float *>(ldsH + E * HP);  // [NM][E][MUP] partial means
   float *ldsBias = planes + NM * PLANE;                     // b1 | b2 | b3
-  float *ldsU = ldsBias + 2 * 256 + 32;                     // factors of the three layers' features
-  float *rowU = ldsU + 2 * 256 + 32;                        // [E] and of the market part of layer 1's rows
-  double *ldsTerms = reinterpret_cast<double *>(rowU + E);  // holdings' values, read while the hidden tile is in use
+  double *ldsTerms = reinterpret_cast<double *>(ldsBias + 2 * 256 + 32);  // holdings' values, read while the hidden tile is in use
   u32x4 *ldsW = reinterpret_cast<u32x4 *>(ldsTerms + E * 32);
-  const int agent = (n0 % d.N) / a.envs_per_agent;
-  const Net net = net_of(a.actor, agent);
-  auto half_w = [&](int l, int nkb, int nct) {
-    return reinterpret_cast<const u32x4 *>(static_cast<const unsigned char *>(a.actor.half_w[l]) + agent * halves_bytes(nkb, nct));
-  };
+  const Net net = net_of(a.actor, (n0 % d.N) / a.envs_per_agent);
 
-  for (int i = tid; i < E * (xpitch + ppitch) / 4; i += NT) reinterpret_cast<uint32_t *>(ldsX)[i] = 0u;  // (padded k columns stay so)
-  if (tid < 256) ldsU[tid] = a.actor.half_u[0][(size_t)agent * 256 + tid];
-  else ldsU[tid] = a.actor.half_u[1][(size_t)agent * 256 + tid - 256];
-  if (tid < 32) ldsU[512 + tid] = a.actor.half_u[2][(size_t)agent * 32 + tid];
+  for (int i = tid; i < E * a.xpitch / 4; i += NT) reinterpret_cast<uint32_t *>(ldsX)[i] = 0u;  // (padded k columns stay so)
   stage_net<NT>(net, ldsBias, nullptr, tid);
   __syncthreads();
 
   if (w < NM) {
     // ---------------------------------------------------------------- the network, features 64 w ..
-    const int nh = NH > 0 ? NH : (DK + D + G::KIN - 1) / G::KIN, np = NP > 0 ? NP : (D + G::KIN) / G::KIN;
+    const int nk1 = NK1 > 0 ? NK1 : (S + G::KIN - 1) / G::KIN, nh = NH > 0 ? NH : (DK + D) / G::KIN;
     const int row = G::row(lane), part = G::part(lane);
-    const unsigned char *xrow = ldsX + row * xpitch + 32 * part, *prow = ldsP + row * ppitch + O::HALF * part, *hrow = ldsH + row * HP + 32 * part;
-    Blk2 ring[PU];  // (for the portfolio part of layer 1 all of its blocks)
+    const unsigned char *xrow = ldsX + row * a.xpitch + O::HALF * part, *hrow = ldsH + row * HP + O::HALF * part;
+    Blk3 ring[PU];
     typename G::Acc acc[G::NACC];
     auto prime_range = [&](const u32x4 *W, int n) {
 #pragma unroll
       for (int u = 0; u < PU; ++u)
-        if (u / G::NACC < n) fetch_half(ring[u], G::unit(W, u));
+        if (u / G::NACC < n) G::fetch_unit(ring[u], W, u);
     };
     auto clear = [&]() {
 #pragma unroll
@@ -319,25 +252,22 @@ __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
     };
     // tanh of the sums, and between its operations, part by part, the ring is filled: all at once the
     // requests take longer to issue than they take to be answered (2 us for 24 KB a wavefront, the vector units idle)
-    auto activate = [&](int layer, auto unit_of_next) {
-      constexpr int PER = 2 * PU * 4 / (12 * G::NG);
-      static_assert(PER * 12 * G::NG == 2 * PU * 4, "");
+    auto activate = [&](const float *bias, auto unit_of_next) {
+      constexpr int PER = 3 * PU * 4 / (12 * G::NG);
 #pragma unroll
       for (int m0 = 0; m0 < G::NG; m0 += 4) {
         float z[16];
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
-          const int f = 256 * layer + 64 * w + G::feature(m0 + m, part);
-          const f32x4 b = *reinterpret_cast<const f32x4 *>(ldsBias + f), u = *reinterpret_cast<const f32x4 *>(ldsU + f);
+          const f32x4 b = *reinterpret_cast<const f32x4 *>(bias + 64 * w + G::feature(m0 + m, part));
 #pragma unroll
-          for (int i = 0; i < 4; ++i)  // (layer 1's sums have their factors already)
-            z[4 * m + i] = layer == 0 ? G::get(acc, m0 + m, i) + b[i] : fmaf(G::get(acc, m0 + m, i), u[i], b[i]);
+          for (int i = 0; i < 4; ++i) z[4 * m + i] = G::get(acc, m0 + m, i) + b[i];
         }
         tanh_accurate_16(z, [&](int stage) {
 #pragma unroll
           for (int k = 0; k < PER; ++k) {
             const int p = (stage + 3 * m0) * PER + k;
-            ring[p / 2].p[p % 2] = unit_of_next(p / 2)[64 * (p % 2)];
+            ring[p / 3].p[p % 3] = unit_of_next(p / 3)[64 * (p % 3)];
           }
         });
 #pragma unroll
@@ -345,53 +275,37 @@ __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
       }
     };
     int lane_s = lane;
-    const u32x4 *W1, *W1p, *W2;
+    const u32x4 *W1, *W2;
     auto addresses = [&]() {  // (opaque per step, or the addresses of all weight blocks are kept across the steps)
       asm volatile("" : "+v"(lane_s));
-      W1 = G::template base<128>(half_w(0, a.market, 8), w, lane_s);
-      W1p = G::template base<192>(net.W[0] + (size_t)a.market * (8 * 192), w, lane_s);
-      W2 = G::template base<128>(half_w(1, 16, 8), w, lane_s);
+      W1 = G::base(net.W[0], w, lane_s);
+      W2 = G::base(net.W[1], w, lane_s);
     };
-    // Market part of layer 1: its rows and weights are scaled, what it adds up is not any more.  Behind it the ring takes the
-    // weights of the portfolio part, three pieces a unit.
-    auto piece = [&](int i) -> u32x4 & { return ring[i / 2].p[i % 2]; };
-    static_assert(3 * G::NP * G::NACC <= 2 * PU, "");
     auto head = [&]() {
       clear();
       products<G, NH>(acc, ring, xrow, W1, nh);
-#pragma unroll
-      for (int u = 0; u < G::NP * G::NACC; ++u)
-        if (u / G::NACC < np)
-#pragma unroll
-          for (int i = 0; i < 3; ++i) piece(3 * u + i) = G::unit3(W1p, u)[64 * i];
-      const float ru = rowU[row];
-#pragma unroll
-      for (int m = 0; m < G::NG; ++m) {
-        const f32x4 u = *reinterpret_cast<const f32x4 *>(ldsU + 64 * w + G::feature(m, part));
-#pragma unroll
-        for (int i = 0; i < 4; ++i) G::put(acc, m, i, G::get(acc, m, i) * ru * u[i]);
-      }
+      prime_range(W1 + (size_t)nh * G::BLOCK, nk1 - nh);
     };
     addresses();
     // kept: the first units of layer 2 (LDS) and the output layer's weights (registers).  A lane of that layer's operand
     // takes the two halves of its piece from the places the order of its inputs has them in (see below).
-    u32x4 *own = ldsW + (size_t)w * (NL * 128) + lane;
+    u32x4 *own = ldsW + (size_t)w * (NL * 192) + lane;
 #pragma unroll
     for (int u = 0; u < NL; ++u) {
-      Blk2 b;
-      fetch_half(b, G::unit(W2, u));
+      Blk3 b;
+      G::fetch_unit(b, W2, u);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) own[u * 128 + 64 * i] = b.p[i];
+      for (int i = 0; i < 3; ++i) own[u * 192 + 64 * i] = b.p[i];
     }
-    const unsigned char *W3 = reinterpret_cast<const unsigned char *>(half_w(2, 16, 1) + (size_t)w * (4 * 128) + (E == 16 ? (part >> 1) * 32 : 0) + row) + 8 * (part & 1);
-    constexpr int W3K = E == 16 ? 2 * 128 : 128, W3H = E == 16 ? 128 : 32;  // pieces from block to block, and to the second half
-    Blk2 w3[G::N3][G::NC3];
+    const unsigned char *W3 = reinterpret_cast<const unsigned char *>(net.W[2] + (size_t)w * (4 * 192) + (E == 16 ? (part >> 1) * 32 : 0) + row) + 8 * (part & 1);
+    constexpr int W3K = E == 16 ? 2 * 192 : 192, W3H = E == 16 ? 192 : 32;  // pieces from block to block, and to the second half
+    Blk3 w3[G::N3][G::NC3];
 #pragma unroll
     for (int K = 0; K < G::N3; ++K)
 #pragma unroll
       for (int c = 0; c < G::NC3; ++c)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < 3; ++i) {
           const u32x2 lo = *reinterpret_cast<const u32x2 *>(W3 + (K * W3K + c * 16 + i * 64) * 16);
           const u32x2 hi = *reinterpret_cast<const u32x2 *>(W3 + (K * W3K + W3H + c * 16 + i * 64) * 16);
           w3[K][c].p[i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
@@ -407,48 +321,36 @@ __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
 #pragma unroll
         for (int j = 0; j < G::NACC; ++j) head_sums[j] = acc[j];
         clear();
-#pragma unroll
-        for (int K = 0; K < G::NP; ++K)
-          if (K < np) {
-            Blk3 xv;
-            fetch_x(xv, prow + K * G::PBYTES);
-#pragma unroll
-            for (int j = 0; j < G::NACC; ++j) {
-              const int u = 3 * (G::NACC * K + j);
-              const u32x4 wv[3] = {piece(u), piece(u + 1), piece(u + 2)};
-              G::mma3(wv, xv, acc[j]);
-            }
-          }
+        products<G, NK1 - NH>(acc, ring, xrow + nh * G::KBYTES, W1 + (size_t)nh * G::BLOCK, nk1 - nh);
 #pragma unroll
         for (int j = 0; j < G::NACC; ++j) acc[j] += head_sums[j];
       }
       addresses();
-      activate(0, [&](int u) { return G::unit(W2, NL + u); });
+      activate(ldsBias, [&](int u) { return G::unit(W2, NL + u); });
 #pragma unroll
       for (int m = 0; m < G::NG; ++m)
-      {
-        const float v[4] = {G::get(acc, m, 0), G::get(acc, m, 1), G::get(acc, m, 2), G::get(acc, m, 3)};
-        put_half4(ldsH + row * HP + half_off(64 * w + G::feature(m, part)), v);
-      }
+        O::store4<true>(ldsH + row * HP + O::off(64 * w + G::feature(m, part)), G::get(acc, m, 0), G::get(acc, m, 1), G::get(acc, m, 2),
+                        G::get(acc, m, 3));
       __syncthreads();  // first hidden layer complete, input tile free
       clear();
       products2<G>(acc, ring, hrow, own, W2);
       // Output layer, from registers: the eight values a lane holds of two groups of features are an operand of the
       // transposed product in another order of its inputs.  Each wavefront adds up its own features for all outputs.
-      const int last_head = nh - 1;
-      activate(1, [&](int u) { return G::unit(W1, NH > 0 ? u : G::NACC * min(u / G::NACC, last_head) + u % G::NACC); });
+      const int last_head = max(nh - 1, 0);
+      activate(ldsBias + 256, [&](int u) { return G::unit(W1, NH > 0 ? u : G::NACC * min(u / G::NACC, last_head) + u % G::NACC); });
       // (each block's sums start at zero and are added to the others afterwards: one chain over all leaves a larger error, 16
       // envs, 2-norm of the means 3.16e-7 for 3.06e-7)
       typename G::Acc o[G::NC3];
 #pragma unroll
       for (int K = 0; K < G::N3; ++K) {
-        Blk2 xv;
+        float v[8];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          uint32_t hi, lo;
-          split2_pair<true>(G::get(acc, 2 * K + (i >> 1), 2 * (i & 1)), G::get(acc, 2 * K + (i >> 1), 2 * (i & 1) + 1), hi, lo);
-          xv.p[0][i] = hi, xv.p[1][i] = lo;
-        }
+        for (int i = 0; i < 8; ++i) v[i] = G::get(acc, 2 * K + (i >> 2), i & 3);
+        bf16x8 xs[3];
+        split3<true>(v, xs);
+        Blk3 xv;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) xv.p[i] = __builtin_bit_cast(u32x4, xs[i]);
 #pragma unroll
         for (int c = 0; c < G::NC3; ++c) {
           typename G::Acc p;
@@ -476,7 +378,7 @@ __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
   trade.terms = ldsTerms;
   const int et = tid - 64 * NM, e = et / TPE, tl = et & (TPE - 1), ew = w - NM;
   const int n = n0 + e;
-  const float *lb3 = ldsBias + 2 * 256, *lu3 = ldsU + 2 * 256;
+  const float *lb3 = ldsBias + 2 * 256;
   int32_t tau = a.st.tau[n];
   const int32_t start = a.st.start[n];
   float cash = a.st.cash[n];
@@ -488,7 +390,7 @@ __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
 #pragma unroll
   for (int i = 0; i < ND; ++i) dd[i] = min(tl + TPE * i, D - 1);  // (stocks behind the last: that one again, not used)
   auto mine = [&](int i) { return tl + TPE * i < D; };
-  unsigned char *penv = ldsP + e * ppitch;
+  unsigned char *xenv = ldsX + e * a.xpitch;
   const int li = min(lane, (DK >> 2) - 1), lp = min(lane, D - 1);
   // market part of an observation: a row per instruction, prices and 16-byte groups of indicators (lanes beyond them, and
   // with few groups, repeat the last one)
@@ -507,41 +409,27 @@ __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
     for (int j = 0; j < ROWS; ++j) {
       const int er = ROWS * ew + j;
       float *orow = obs + (size_t)(n0 + er) * S;
-      unsigned char *x = ldsX + er * xpitch;
+      unsigned char *x = ldsX + er * a.xpitch;
       const float pv = r_p[j] * d.s_price;
       __builtin_nontemporal_store(pv, &orow[1 + lp]);
+      O::store1(x + O::off(DK + lp), pv);
       f32x4 v = r_i[j];
       v[0] *= d.s_ind, v[1] *= d.s_ind, v[2] *= d.s_ind, v[3] *= d.s_ind;
       // observation rows are 4-byte aligned only; a 16-byte store needs no more than that
       __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(orow + 1 + 2 * D) + li);
-      // The tile has the row over the power of two of its largest finite number, which goes to 2^14 .. 2^15.
-      auto finite = [](float f) { return fabsf(f) < __builtin_inff() ? fabsf(f) : 0.0f; };
-      const float m = wave_max(fmaxf(fmaxf(fmaxf(finite(v[0]), finite(v[1])), fmaxf(finite(v[2]), finite(v[3]))), finite(pv)));
-      const uint32_t me = min(max(__builtin_bit_cast(uint32_t, m > 0.0f ? m : 1.0f) >> 23, 15u), 254u);
-      const float scale = __builtin_bit_cast(float, (268u - me) << 23);
-      auto low = [&](float f, _Float16 h) { return (_Float16)(f * scale - (float)h); };
-      typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-      f16x4 hi, lo;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) hi[i] = half_of_nonzero(v[i] * scale, v[i]), lo[i] = low(v[i], hi[i]);
-      *reinterpret_cast<f16x4 *>(x + half_off(4 * li)) = hi;
-      *reinterpret_cast<f16x4 *>(x + half_off(4 * li) + 16) = lo;
-      const _Float16 ph = half_of_nonzero(pv * scale, pv);
-      *reinterpret_cast<_Float16 *>(x + half_off(DK + lp)) = ph;
-      *reinterpret_cast<_Float16 *>(x + half_off(DK + lp) + 16) = low(pv, ph);
-      if (lane == 0) rowU[er] = __builtin_bit_cast(float, (me - 14u) << 23);
+      O::store4(x + O::off(4 * li), v[0], v[1], v[2], v[3]);
     }
   };
   auto put_holding = [&](float *obs, int i) {
     const float v = (float)h[i] * d.s_hold;
     __builtin_nontemporal_store(v, &obs[(size_t)n * S + 1 + D + dd[i]]);
-    O::store1(penv + O::off(dd[i]), v);
+    O::store1(xenv + O::off(DK + D + dd[i]), v);
   };
   auto put_cash = [&](float *obs) {
     if (tl == 0) {
       const float v = cash * d.s_cash;
       __builtin_nontemporal_store(v, &obs[(size_t)n * S]);
-      O::store1(penv + O::off(D), v);
+      O::store1(xenv + O::off(DK + 2 * D), v);
     }
   };
   {
@@ -605,7 +493,7 @@ __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
       const float *m = planes + e * MUP + dd[i];
-      mu[i] = finish_out(((m[0] + m[PLANE]) + (m[2 * PLANE] + m[3 * PLANE])) * lu3[dd[i]], lb3[dd[i]], 1);
+      mu[i] = finish_out((m[0] + m[PLANE]) + (m[2 * PLANE] + m[3 * PLANE]), lb3[dd[i]], 1);
       a_raw[i] = mu[i] + d.sigma * eps[i];  // two roundings (contraction is off)
     }
     int32_t q[ND];
@@ -649,49 +537,44 @@ __global__ __launch_bounds__(NT, 2) void rollout_f32_kernel(F32Args a) {
 }
 
 template <int E>
-int hidden_bytes(int D) {
-  const size_t trades = trade_lds(E, true, D) - (size_t)E * ((D + 3) & ~3) * 8;  // (the terms have a place of their own)
-  return (int)((max(trades, (size_t)E * HP) + 15) & ~(size_t)15);
-}
-
-template <int E>
-size_t lds_bytes(int D, int K) {
+size_t lds_bytes(int S) {
   using G = Geometry<E>;
-  return (size_t)E * (half_pitch(f32_market_blocks(D, K)) + tile_pitch<false>(f32_portfolio_blocks(D))) + hidden_bytes<E>(D) +
-         ((size_t)NM * G::PLANE + 2 * (2 * 256 + 32) + E) * 4 + (size_t)E * 32 * 8 + (size_t)NM * G::NL * 2048;
+  return (size_t)E * (input_pitch<E>(S) + HP) + ((size_t)NM * G::PLANE + (2 * 256 + 32)) * 4 + (size_t)E * 32 * 8 + (size_t)NM * G::NL * 3072;
 }
 
-template <int E, int NH, int NP>
+template <int E, int NK1, int NH>
 hipError_t launch_inst(hipStream_t st, const F32Args &a, size_t lds) {
-  constexpr auto kern = rollout_f32_kernel<E, NH, NP>;
+  constexpr auto kern = rollout_f32_kernel<E, NK1, NH>;
   const hipError_t e = allow_full_lds<kern>();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)(a.d.N / E)), dim3(NT), lds, st, a);
   return hipGetLastError();
 }
 
-template <int E, int NH, int NP>
+template <int E, int NK1, int NH>
 hipError_t launch_geometry(hipStream_t st, F32Args a) {
   const EnvDims &d = a.d;
-  a.market = f32_market_blocks(d.D, d.K), a.portfolio = f32_portfolio_blocks(d.D), a.hidden_bytes = hidden_bytes<E>(d.D);
-  const size_t lds = lds_bytes<E>(d.D, d.K);
-  if (d.N % E || a.envs_per_agent % E || d.D > 32 || lds > (size_t)kMaxLdsBytes) return hipErrorInvalidValue;
+  a.xpitch = input_pitch<E>(d.S);
+  const size_t lds = lds_bytes<E>(d.S);
+  if (d.N % E || a.envs_per_agent % E || trade_lds(E, true, d.D) > (size_t)E * HP || lds > (size_t)kMaxLdsBytes) return hipErrorInvalidValue;
   constexpr int KIN = Geometry<E>::KIN;
-  // Layer 1 in straight-line code, each block's inputs read a block ahead, for the blocks of 30 stocks x 8 indicators (257 to
-  // 288 or 272 market columns).  us a step with numbers of blocks at run time and this: 16 envs, 1024 envs 6.64 and 6.57; 32
-  // envs, 8192 14.4 and 14.2, 65536 of 64 agents 114 and 110.
-  if ((d.D * d.K + d.D + KIN - 1) / KIN == NH && (d.D + KIN) / KIN == NP) return launch_inst<E, NH, NP>(st, a, lds);
+  // Layer 1 in straight-line code, each block's inputs read a block ahead, for the blocks of 30 stocks x 8 indicators (289 to
+  // 320 or 304 inputs, 256 to 287 or 271 of them market columns).  us a step with numbers of blocks at run time and this:
+  // 16 envs, where layer 1 is a third of the chain, 1024 envs 9.7 -> 8.0, 4096 12.2 -> 9.9; 32 envs 65536 of 64 agents 0.4
+  // and 1.2 % on two chips, 8192 and 16384 level.
+  if ((d.S + KIN - 1) / KIN == NK1 && (d.D * d.K + d.D) / KIN == NH) return launch_inst<E, NK1, NH>(st, a, lds);
   return launch_inst<E, 0, 0>(st, a, lds);
 }
 
 // 16 envs up to a workgroup for each of the 256 compute units; beyond, the weights streamed once for 32 envs are worth
-// more (301 inputs, per step: 4096 envs 7.9 us against 11.8; 8192 in two rounds of 16 would be 15.8 against 14.2).
+// more (301 inputs, per step: 4096 envs 10.9 us against 14.1, 1024 8.2 against 13.0; 8192 in two rounds 21 against 17.2).
 bool sixteen(int N) { return N <= 256 * 16; }
 
 }  // namespace
 
 size_t fused_f32_lds_bytes(const pr_config &c) {
-  return sixteen(c.n_envs) ? lds_bytes<16>(c.n_stocks, c.n_ind) : lds_bytes<32>(c.n_stocks, c.n_ind);
+  const int S = 1 + 2 * c.n_stocks + c.n_stocks * c.n_ind;
+  return sixteen(c.n_envs) ? lds_bytes<16>(S) : lds_bytes<32>(S);
 }
 
 hipError_t launch_rollout_fused_f32(hipStream_t st, const EnvDims &d, const EnvState &s, const float *price, const float *ind,
@@ -701,8 +584,8 @@ hipError_t launch_rollout_fused_f32(hipStream_t st, const EnvDims &d, const EnvS
   a.d = d, a.st = s, a.price = price, a.ind = ind, a.actor = actor, a.envs_per_agent = envs_per_agent, a.T = T;
   a.noise = noise, a.obs = out.obs, a.act_raw = out.act_raw, a.reward = out.reward, a.done = out.done, a.logp = out.logp;
   a.mu_out = out.mu, a.shares = out.shares;
-  if (actor.bf16 || !actor.half_w[0] || actor.nkb[1] != 16 || actor.nct[0] != 8 || actor.nct[2] != 1) return hipErrorInvalidValue;
-  return sixteen(d.N) ? launch_geometry<16, 9, 1>(st, a) : launch_geometry<32, 17, 2>(st, a);
+  if (actor.bf16 || actor.nkb[0] % 2 || actor.nkb[1] != 16 || actor.nct[0] != 8 || actor.nct[2] != 1) return hipErrorInvalidValue;
+  return sixteen(d.N) ? launch_geometry<16, 10, 8>(st, a) : launch_geometry<32, 19, 16>(st, a);
 }
 
 }  // namespace pod

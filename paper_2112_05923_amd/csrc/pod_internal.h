@@ -167,8 +167,8 @@ struct PackedNet {
                                   // activations (fp32 [hidden] or bf16 [layers_pitch(hidden)]), or null
   ObsShadow split_x;              // and, for bf16 networks, of its input
   int64_t split_rows;
-  void *half_w[3];                // layers in fp16 parts, and their factors, or null: of the critic its hidden layers, as scratch
-  float *half_u[3];               // of the value head over many rows; of the persistent rollout's actor all (layer 1's market part)
+  void *half_w[2];                // scratch for the fp32 value head over many rows: both hidden layers in fp16 parts, and
+  float *half_u[2];               // their factors; or null
 };
 // Rows the scratch of the layer-per-launch paths holds: all envs where a step's rows can take one of them (fewer 64-row
 // tiles than half the compute units), and always enough for a policy asked about a few; 0 for networks too narrow for them.
@@ -180,13 +180,13 @@ int padded_out(int out_dim);
 struct PackRun {
   int32_t at, row, count;
 };
-// One layer to pack, in nkb k-blocks: its rows in up to four runs, zeros elsewhere.
+// One layer to pack, in nkb k-blocks: its rows in up to three runs, zeros elsewhere.
 struct PackJob {
   const float *W, *b;  // [P, in_dim, out_dim], [P, out_dim]
   void *Wp;
   float *bp;
   int32_t in_dim, out_dim, nkb;
-  PackRun run[4];
+  PackRun run[3];
 };
 // three layers of two networks, and the actor's first layer in the rollout's order or both first layers in their parts
 constexpr int kMaxPackJobs = 10;
@@ -202,7 +202,7 @@ struct HalvesJob {
   int32_t nkb, nct, input_exp;
 };
 constexpr int kMaxHalvesJobs = 4;
-__host__ __device__ constexpr int64_t halves_bytes(int nkb, int nct) { return (int64_t)nkb * nct * 2048; }
+inline int64_t halves_bytes(int nkb, int nct) { return (int64_t)nkb * nct * 2048; }
 hipError_t launch_halves(hipStream_t st, const HalvesJob *jobs, int n, int P);
 // rows of X [rows, ldx] -> Y [rows, out_dim[2]]; row r uses agent ((r % N) / envs_per_agent).
 hipError_t launch_mlp(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx, float *Y,
@@ -248,9 +248,7 @@ hipError_t launch_rollout_fused(hipStream_t st, const pr_config &c, const EnvDim
                                 const float *price, const float *ind, const PackedNet &actor, int32_t envs_per_agent,
                                 int32_t T, const float *noise, const float *mu_forced, const pr_buffers &out);
 
-// The same with the actor for fp32 networks.  k-blocks of layer 1's market columns and of its portfolio columns there:
-inline int f32_market_blocks(int D, int K) { return 2 * ((D * K + D + 31) / 32); }
-inline int f32_portfolio_blocks(int D) { return 2 * ((D + 32) / 32); }
+// The same with the actor for fp32 networks.
 size_t fused_f32_lds_bytes(const pr_config &c);
 hipError_t launch_rollout_fused_f32(hipStream_t st, const EnvDims &d, const EnvState &s, const float *price, const float *ind,
                                     const PackedNet &actor, int32_t envs_per_agent, int32_t T, const float *noise,

@@ -1174,7 +1174,7 @@ __global__ __launch_bounds__(256) void pack_layers_kernel(PackArgs a) {
   float v[8];
   int first = -1;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 3; ++i)
     if (kb * 16 >= jb.run[i].at && kb * 16 + 16 <= jb.run[i].at + jb.run[i].count) first = kb * 16 - jb.run[i].at + jb.run[i].row;
   if (first >= 0) {
     const float *w = Wa + (size_t)(first + 8 * g) * jb.out_dim + min(col, jb.out_dim - 1);
@@ -1188,7 +1188,7 @@ __global__ __launch_bounds__(256) void pack_layers_kernel(PackArgs a) {
       const int k = kb * 16 + 8 * g + e;
       int ks = -1;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < 3; ++i)
         if ((unsigned)(k - jb.run[i].at) < (unsigned)jb.run[i].count) ks = k - jb.run[i].at + jb.run[i].row;
       v[e] = (ks >= 0 && col < jb.out_dim) ? Wa[(size_t)ks * jb.out_dim + col] : 0.0f;
     }
