@@ -27,9 +27,8 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK = {"hbm": (8000.0, "GB/s"), "mfma_bf16": (2500.0, "TFLOP/s"),
-        # fp32 networks run as three fp16 matrix instructions per fp32 product where operands are scaled (persistent rollout,
-        # value head), as six bf16 ones elsewhere
-        "mfma_fp32": (2500.0 / 3, "TFLOP/s")}
+        # fp32 networks run as six bf16 matrix instructions per fp32 product
+        "mfma_fp32": (2500.0 / 6, "TFLOP/s")}
 
 
 def kernel_sources_digest() -> str:

@@ -27,8 +27,6 @@ struct pr_handle {
   int32_t beside_steps;
   void *w_packed[2][3];   // device, per net and layer
   float *b_packed[2][3];
-  void *half_w[2];        // the critic's hidden layers in fp16 parts, and their factors (null: no value head takes them)
-  float *half_u[2];
   float *mu_scratch;      // [N, D]
   int32_t *start;         // [N] episode start rows (zeros unless a replay table is set)
   ObsShadow shadow;       // bf16 observations of the layer-per-launch actor, or null
@@ -70,7 +68,6 @@ struct Layout {
   size_t w1_rot, w1_beside, beside_h[2];
   size_t cash, tau, h, ep_ret, ep_sum, ep_sqsum, ep_cnt, mu, start, split[3], query[3];
   size_t table_w[2][2], table_p, tau0;
-  size_t half_w[2], half_u[2];
   size_t total;
 };
 
@@ -111,9 +108,6 @@ int rotated_blocks(const pr_config &c) {
 int table_blocks(const pr_config &c, int part) {
   return part == 0 ? table_market_blocks(c.n_stocks, c.n_ind) : table_portfolio_blocks(c.n_stocks);
 }
-
-// the value head over many rows takes the critic in fp16 parts
-bool value_in_halves(const pr_config &c) { return c.mlp_dtype == PR_MLP_F32 && c.hidden == 256; }
 
 int validate_config(const pr_config *c) {
   if (!c) return PR_EINVAL;
@@ -185,12 +179,6 @@ Layout make_layout(const pr_config &c) {
     L.table_p = take(table_scratch_bytes(c.n_envs));
     L.tau0 = take(N * 4);
   }
-  if (value_in_halves(c)) {
-    for (int l = 0; l < 2; ++l) {
-      L.half_w[l] = take((size_t)halves_bytes((in_dim[l] + 15) / 16, Hd / 32) * P);
-      L.half_u[l] = take((size_t)Hd * 4 * P);
-    }
-  }
   L.total = off;
   return L;
 }
@@ -230,7 +218,6 @@ void fill_net(PackedNet &pn, const pr_handle *h, int net) {
   pn.bf16 = bf;
   pn.out_tanh = net == 0 ? 1 : 0;
   pn.split_rows = split_scratch_rows(c.n_envs, Hd);
-  for (int l = 0; l < 2; ++l) pn.half_w[l] = net == 1 ? h->half_w[l] : nullptr, pn.half_u[l] = net == 1 ? h->half_u[l] : nullptr;
   set_scratch(pn, h->split);
   pn.split_x.pitch = layers_pitch(S);
   pn.split_x.cols = (S + 15) / 16 * 16;
@@ -376,9 +363,6 @@ int rollout_init(const pr_config *cfg, const pr_market *market, const pr_weights
     h->table_p = reinterpret_cast<float *>(ws + L.table_p);
     h->tau0 = reinterpret_cast<int32_t *>(ws + L.tau0);
   }
-
-  if (value_in_halves(*cfg))
-    for (int l = 0; l < 2; ++l) h->half_w[l] = ws + L.half_w[l], h->half_u[l] = reinterpret_cast<float *>(ws + L.half_u[l]);
 
   EnvDims &d = h->dims;
   d.N = cfg->n_envs;

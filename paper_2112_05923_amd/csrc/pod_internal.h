@@ -167,8 +167,6 @@ struct PackedNet {
                                   // activations (fp32 [hidden] or bf16 [layers_pitch(hidden)]), or null
   ObsShadow split_x;              // and, for bf16 networks, of its input
   int64_t split_rows;
-  void *half_w[2];                // scratch for the fp32 value head over many rows: both hidden layers in fp16 parts, and
-  float *half_u[2];               // their factors; or null
 };
 // Rows the scratch of the layer-per-launch paths holds: all envs where a step's rows can take one of them (fewer 64-row
 // tiles than half the compute units), and always enough for a policy asked about a few; 0 for networks too narrow for them.
@@ -191,24 +189,11 @@ struct PackJob {
 // three layers of two networks, and the actor's first layer in the rollout's order or both first layers in their parts
 constexpr int kMaxPackJobs = 10;
 hipError_t launch_pack_layers(hipStream_t st, const PackJob *jobs, int n, int P, int bf16);
-// A packed fp32 layer in two fp16 parts per weight (pod_half2.h): [kb][ct][part][lane], and per feature what a sum of products
-// is to be multiplied by: its scale's reciprocal, times 2^-input_exp.
-struct HalvesJob {
-  const void *W;     // as packed
-  int64_t w_stride;  // bytes between agents
-  void *H;
-  int64_t h_stride;
-  float *unscale;    // [P][32 nct]
-  int32_t nkb, nct, input_exp;
-};
-constexpr int kMaxHalvesJobs = 4;
-inline int64_t halves_bytes(int nkb, int nct) { return (int64_t)nkb * nct * 2048; }
-hipError_t launch_halves(hipStream_t st, const HalvesJob *jobs, int n, int P);
 // rows of X [rows, ldx] -> Y [rows, out_dim[2]]; row r uses agent ((r % N) / envs_per_agent).
 hipError_t launch_mlp(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx, float *Y,
                       int32_t N, int32_t envs_per_agent);
 // The fp32 value head with 256 hidden units over many dense rows, on `cus` compute units: with several agents whole steps
-// of N rows, whose envs per agent are a multiple of 32.  Takes net.half_w.
+// of N rows, whose envs per agent are a multiple of 32.
 bool value_rows_covers(int64_t rows, int32_t N, int32_t envs_per_agent);
 hipError_t launch_value_rows(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, float *Y, int32_t N,
                              int32_t envs_per_agent, int cus);

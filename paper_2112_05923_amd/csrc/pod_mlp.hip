@@ -1403,8 +1403,8 @@ static bool try_launch_value(hipStream_t st, const PackedNet &net, int64_t rows,
 }
 
 // The fp32 value head with 256 hidden units over dense rows: workgroups of 128 rows, a wavefront per 32 (pod_value.hip),
-// from the second 64-row tile per compute unit on, where the workgroups that share a tile take two passes (301 inputs: 17000
-// rows 43 us against 52, 65536 68 against 106; 49 inputs 30 against 33 and 46 against 71; 16384 rows, one pass, 43 against 31).
+// from the second 64-row tile per compute unit on, where the workgroups that share a tile take two passes (301 inputs: 20480
+// rows 49 us against 58, 65536 95 against 109, 98304 137 against 160; 16384 rows, one pass, 48 against 31).
 static bool try_launch_value_f32(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx,
                                  float *Y, int32_t N, int32_t envs_per_agent, hipError_t *err) {
   const int S = net.in_dim[0], Hd = net.out_dim[0];
@@ -1413,7 +1413,7 @@ static bool try_launch_value_f32(hipStream_t st, const PackedNet &net, int64_t r
   const int64_t ntiles = (rows + tile::BM - 1) / tile::BM;
   // (of several agents the whole steps; what is left begins at the first env again)
   const int64_t whole = envs_per_agent < N ? rows / N * N : rows;
-  if (net.half_w[0] && whole > (int64_t)tile::BM * compute_units() && value_rows_covers(whole, N, envs_per_agent)) {
+  if (whole > (int64_t)tile::BM * compute_units() && value_rows_covers(whole, N, envs_per_agent)) {
     *err = launch_value_rows(st, net, whole, X, Y, N, envs_per_agent, compute_units());
     if (*err == hipSuccess && whole < rows)
       *err = launch_mlp(st, net, rows - whole, X + whole * S, ldx, Y + whole, N, envs_per_agent);

@@ -572,6 +572,33 @@ def test_queries_side_by_side(base, N, rows, Hd, D, K):
         assert all(torch.equal(y, eager[i]) for i in range(2) for y in outs[i])
 
 
+# ... and so over the many rows that other kernels take, of either network: replayed before anything else has asked, and again
+@pytest.mark.parametrize("base,N,rows,Hd,D,K", [("dow30", 64, 16384 + 77, 256, 30, 8), ("dow30", 128, 20000, 256, 5, 2), ("dow30", 64, 16461, 128, 30, 8),
+                                                ("large", 64, 16461, 512, 30, 8), ("large", 64, 9000, 1024, 60, 2)])
+def test_captured_queries_of_many_rows(base, N, rows, Hd, D, K):
+    w = inputs.WORKLOADS[base].replace(n_envs=N, hidden=Hd, n_stocks=D, n_ind=K, steps=1)
+    d = inputs.make_all(w, horizon=1, n_market=1, steps=1)
+    X = np.random.default_rng(rows).standard_normal((rows, w.state_dim)).astype(np.float32)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        dev = lambda m: {k: _t(v) for k, v in m.items()}
+        ro = pr.Rollout(pr.make_config(w, horizon=1, n_market=1), _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+        x = _t(X)
+        for net, O in ((pr.PR_NET_CRITIC, 1), (pr.PR_NET_ACTOR, D)):
+            Y, graph = torch.full((rows, O), float("nan"), device=DEV), torch.cuda.CUDAGraph()
+            side.synchronize()
+            with torch.cuda.graph(graph, stream=side):
+                ro.mlp_forward(net, x, Y)
+            before = ro.workspace.clone()
+            for _ in range(3):
+                Y.fill_(float("nan"))
+                graph.replay()
+                side.synchronize()
+                assert torch.equal(ro.workspace, before)
+                got = parity.to_np(Y)[-70:]
+                parity.check_networks(w, d["actor"], d["critic"], X[-70:], **{"mu_rows" if O == D else "value_rows": got})
+
+
 # a small network over many envs, a last workgroup full or of one: the same rollout however it is cut
 @pytest.mark.parametrize("N", [8192, 8193])
 def test_small_networks_of_many_envs(N):
