@@ -26,20 +26,37 @@ struct QueryArgs {
   float *Y;        // [rows][out]
 };
 
-struct Sums {  // (fp32: the three smallest of the six products in a chain of their own)
-  f32x4 hi = {0.0f, 0.0f, 0.0f, 0.0f}, lo = {0.0f, 0.0f, 0.0f, 0.0f};
-};
+// A product of 16 features x 32 inputs x the 16 rows.  fp32: the three smallest of the six products go into a chain of their own.
 __device__ inline f32x4 mfma16(const u32x4 &w, const u32x4 &x, const f32x4 &c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c, 0, 0, 0);
 }
-__device__ inline void mma16(const u32x4 &w, const u32x4 &x, Sums &s) { s.hi = mfma16(w, x, s.hi); }
-__device__ inline void mma16(const tile::Blk3 &w, const tile::Blk3 &x, Sums &s) {
+__device__ inline void mma16(const u32x4 &w, const u32x4 &x, f32x4 &hi, f32x4 &) { hi = mfma16(w, x, hi); }
+__device__ inline void mma16(const tile::Blk3 &w, const tile::Blk3 &x, f32x4 &hi, f32x4 &lo) {
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
-    s.lo = mfma16(w.p[kSplitA[i]], x.p[kSplitB[i]], s.lo);
-    s.hi = mfma16(w.p[kSplitA[3 + i]], x.p[kSplitB[3 + i]], s.hi);
+    lo = mfma16(w.p[kSplitA[i]], x.p[kSplitB[i]], lo);
+    hi = mfma16(w.p[kSplitA[3 + i]], x.p[kSplitB[3 + i]], hi);
   }
 }
+
+// The sums of a feature tile: input step k goes to chain k % CH.  What a sum loses it loses in its longest chain of additions:
+// fp32, 301 inputs and 256 units, against 64 bits (2-norm, actor and critic, 24 networks of 1000 rows) one chain 2.2e-7 and
+// 2.1e-7, two 2.0e-7 and 1.8e-7, four 1.6e-7 and 1.5e-7; a launch per layer, whose eight wavefronts split the inputs, 1.8e-7 and
+// 1.7e-7.  bf16: what is lost there is far below the rounding of the operands, and two chains are as fast as one.
+template <bool BF16>
+struct Sums {
+  static constexpr int CH = BF16 ? 2 : 4;
+  f32x4 hi[CH], lo;
+  __device__ inline Sums() {
+#pragma unroll
+    for (int k = 0; k < CH; ++k) hi[k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    lo = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  }
+  __device__ inline f32x4 total() const {
+    const f32x4 v = hi[0] + hi[1];
+    return BF16 ? v : (v + (hi[2 % CH] + hi[3 % CH])) + lo;
+  }
+};
 
 template <bool BF16>
 __host__ __device__ constexpr int query_lds(int hd, int nks) {
@@ -106,22 +123,23 @@ __global__ __launch_bounds__(kThreads, 2) void query_kernel(QueryArgs a) {
 #pragma unroll
     for (int c = 0; c < FT; ++c) bias[c] = *reinterpret_cast<const f32x4 *>(b + 16 * (ft0 + c) + 4 * q4);
   };
-  Sums acc[FT];
-  auto multiply = [&](const Block(&b)[FT], const unsigned char *xk) {
+  static_assert(PD % Sums<BF16>::CH == 0, "");
+  Sums<BF16> acc[FT];
+  auto multiply = [&](const Block(&b)[FT], const unsigned char *xk, int chain) {
     Block v;
     fetch_x(v, xk);
 #pragma unroll
-    for (int c = 0; c < FT; ++c) mma16(b[c], v, acc[c]);
+    for (int c = 0; c < FT; ++c) mma16(b[c], v, acc[c].hi[chain], acc[c].lo);
   };
   auto put_hidden = [&](unsigned char *H) {
 #pragma unroll
     for (int c = 0; c < FT; ++c) {
-      f32x4 v = BF16 ? acc[c].hi : acc[c].hi + acc[c].lo;
+      f32x4 v = acc[c].total();
       v += bias[c];
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i] = BF16 ? tanh_from_scaled(v[i] * kTwoLog2e) : tanh_accurate(v[i]);
       if (active) O::template store4<true>(H + row * HP + O::off(16 * (ft0 + c) + 4 * q4), v[0], v[1], v[2], v[3]);
-      acc[c] = Sums{};
+      acc[c] = Sums<BF16>{};
     }
   };
 
@@ -133,19 +151,19 @@ __global__ __launch_bounds__(kThreads, 2) void query_kernel(QueryArgs a) {
   for (; i + PD <= last; i += PD) {
 #pragma unroll
     for (int s = 0; s < PD; ++s) {
-      multiply(ring[s], xop + 2 * (i + s) * O::KBYTES);
+      multiply(ring[s], xop + 2 * (i + s) * O::KBYTES, s % Sums<BF16>::CH);
       request(ring[s], net.W[0], nkb, min(i + s + PD, last));
       __builtin_amdgcn_sched_barrier(0);
     }
   }
 #pragma unroll
   for (int s = 0; s < PD; ++s) {
-    if (i + s < last) multiply(ring[s], xop + 2 * (i + s) * O::KBYTES);
+    if (i + s < last) multiply(ring[s], xop + 2 * (i + s) * O::KBYTES, s % Sums<BF16>::CH);
     if (i + s == last) {
 #pragma unroll
       for (int c = 0; c < FT; ++c)
         if (2 * last + (q4 >> 1) >= nkb) ring[s][c] = Block{};
-      multiply(ring[s], xop + 2 * last * O::KBYTES);
+      multiply(ring[s], xop + 2 * last * O::KBYTES, s % Sums<BF16>::CH);
     }
   }
   // -- layer 2
@@ -157,7 +175,7 @@ __global__ __launch_bounds__(kThreads, 2) void query_kernel(QueryArgs a) {
   const unsigned char *h1op = ldsH1 + row * HP + O::off(8 * q4), *h2op = ldsH2 + row * HP + O::off(8 * q4);
 #pragma unroll
   for (int k = 0; k < KS; ++k) {
-    multiply(ring[k % PD], h1op + 2 * k * O::KBYTES);
+    multiply(ring[k % PD], h1op + 2 * k * O::KBYTES, k % Sums<BF16>::CH);
     if (k + PD < KS) request(ring[k % PD], net.W[1], 2 * KS, k + PD);
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -171,14 +189,14 @@ __global__ __launch_bounds__(kThreads, 2) void query_kernel(QueryArgs a) {
   put_hidden(ldsH2);
   __syncthreads();
   if (mine) {
-    Sums s;
+    Sums<BF16> s;
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
       Block v;
       fetch_x(v, h2op + 2 * (kp * PER + p) * O::KBYTES);
-      mma16(w3[p], v, s);
+      mma16(w3[p], v, s.hi[p % Sums<BF16>::CH], s.lo);
     }
-    *reinterpret_cast<f32x4 *>(part + (kp * kRows + row) * kPartPitch + 16 * ot + 4 * q4) = BF16 ? s.hi : s.hi + s.lo;
+    *reinterpret_cast<f32x4 *>(part + (kp * kRows + row) * kPartPitch + 16 * ot + 4 * q4) = s.total();
   }
   __syncthreads();
   if (tl < out && row0 + e < a.rows) {

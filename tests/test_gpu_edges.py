@@ -696,6 +696,33 @@ def test_fp32_networks_are_as_precise_as_fp32_sums(N, rows, Hd, D, K, fused):
         assert err <= chain + 1e-7, (which, err, chain)
 
 
+# a few rows of fp32 networks: sums in chains of additions no longer than a launch per layer has them, whose eight wavefronts split
+# the inputs.  2-norm of the error against 64 bits in the mean over sixteen networks, actor and critic, in units of 1e-7, with 64,
+# 128 and 256 units: a launch per layer 1.40 and 1.26, 1.45 and 1.37, 1.80 and 1.71; four chains 1.33 and 1.19, 1.35 and 1.29,
+# 1.58 and 1.48; one chain, with 256 units, 2.24 and 2.08.  The limits lie above the first by what a mean of sixteen moves (5 %).
+@pytest.mark.parametrize("Hd,limits", [(64, (1.47e-7, 1.33e-7)), (128, (1.52e-7, 1.44e-7)), (256, (1.89e-7, 1.8e-7))])
+def test_sums_of_a_few_rows(Hd, limits):
+    w = inputs.WORKLOADS["dow30"].replace(n_envs=16, hidden=Hd, steps=1)
+    D, S, rows = w.n_stocks, w.state_dim, 600
+    err = np.zeros(2)
+    for seed in range(16):
+        d = inputs.make_all(w.replace(index=900 + seed), horizon=1, n_market=1, steps=1)
+        dev = lambda m: {k: _t(v) for k, v in m.items()}
+        ro = pr.Rollout(pr.make_config(w, horizon=1, n_market=1), _t(d["price"]), _t(d["ind"]), dev(d["actor"]), dev(d["critic"]))
+        rng = np.random.default_rng(seed)
+        X = rng.standard_normal((rows, S)).astype(np.float32)
+        X[:, 0] = rng.uniform(0, 1e6, rows) * w.obs_scale[0]
+        X[:, 1:1 + D] = 50 * np.exp(0.2 * X[:, 1:1 + D]) * w.obs_scale[1]
+        X[:, 1 + D:1 + 2 * D] = rng.integers(0, 600, (rows, D)) * w.obs_scale[2]
+        for i, (which, net) in enumerate(((pr.PR_NET_ACTOR, d["actor"]), (pr.PR_NET_CRITIC, d["critic"]))):
+            n = {k: v[0].astype(np.float64) for k, v in net.items()}
+            z = np.tanh(np.tanh(X.astype(np.float64) @ n["W1"] + n["b1"]) @ n["W2"] + n["b2"]) @ n["W3"] + n["b3"]
+            want = z if i else np.tanh(z)
+            got = parity.to_np(ro.mlp_forward(which, _t(X))).astype(np.float64)
+            err[i] += np.linalg.norm(got - want) / np.linalg.norm(want) / 16
+    assert (err <= limits).all(), err
+
+
 # the fp32 value head: tiles of 64 rows up to one per compute unit (9000 rows; 16384 = all of them), workgroups of 128 rows
 # beyond; ragged last tiles, runs of 32 rows behind the end, one k-block and an odd and an even number of them, inputs that
 # end inside a lane's eight, agents of fewer envs than a tile, rows left over behind the agents' last whole step; an infinite
