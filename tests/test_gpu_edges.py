@@ -347,7 +347,7 @@ def test_small_value_head(base, N, agents, Hd, D, K, T):
 # that are no multiple of four, one output and all 32, agents, and either side of the last row count that takes it
 @pytest.mark.parametrize("base,N,rows,agents,Hd,D,K", [("tiny", 16, 1, 1, 64, 1, 0), ("tiny", 16, 17, 1, 64, 32, 0), ("tiny", 192, 180, 3, 64, 5, 2),
                                                        ("tiny", 16, 31, 1, 128, 7, 0), ("tiny", 128, 100, 2, 256, 32, 16), ("tiny", 16, 300, 1, 256, 17, 9),
-                                                       ("large", 16, 15, 1, 64, 1, 1), ("large", 16, 33, 1, 128, 16, 4), ("large", 256, 250, 4, 256, 29, 17),
+                                                       ("tiny", 448, 440, 7, 256, 5, 2), ("large", 16, 15, 1, 64, 1, 1), ("large", 16, 33, 1, 128, 16, 4), ("large", 256, 250, 4, 256, 29, 17),
                                                        ("large", 16, 16, 1, 512, 30, 19), ("large", 128, 65, 2, 512, 3, 0), ("large", 8200, 8192, 1, 512, 12, 2),
                                                        ("large", 8200, 8193, 1, 512, 12, 2), ("tiny", 8200, 8192, 1, 64, 12, 2)])
 def test_networks_in_one_launch(base, N, rows, agents, Hd, D, K):
