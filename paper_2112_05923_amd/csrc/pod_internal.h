@@ -217,6 +217,8 @@ hipError_t launch_few_rows(hipStream_t st, const PackedNet &net, int64_t rows, c
                            int32_t N, int32_t envs_per_agent);
 // Few rows of networks whose weights pass through one compute unit quickly: all layers in one launch that keeps nothing.
 bool query_supported(int64_t rows, int S, int hidden, int outputs, int bf16, int32_t N, int32_t envs_per_agent);
+// and where a launch per layer, if there is scratch for it, is the faster one all the same
+bool query_outweighed(int64_t rows, int S, int hidden, int bf16, bool several);
 hipError_t launch_query(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx, float *Y, int32_t N,
                         int32_t envs_per_agent);
 // The output layer alone, on bf16 activations [rows][pitch].

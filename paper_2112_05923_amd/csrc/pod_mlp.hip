@@ -1532,7 +1532,10 @@ static bool try_launch_split(hipStream_t st, const PackedNet &net, int64_t rows,
 
 hipError_t launch_mlp(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx, float *Y,
                       int32_t N, int32_t envs_per_agent) {
-  if (query_supported(rows, net.in_dim[0], net.out_dim[0], net.out_dim[2], net.bf16, N, envs_per_agent) && !(reinterpret_cast<uintptr_t>(X) & 3u))
+  const bool per_layer = net.split_h[0] && rows <= net.split_rows &&
+                         query_outweighed(rows, net.in_dim[0], net.out_dim[0], net.bf16, envs_per_agent < N);
+  if (!per_layer && !(reinterpret_cast<uintptr_t>(X) & 3u) &&
+      query_supported(rows, net.in_dim[0], net.out_dim[0], net.out_dim[2], net.bf16, N, envs_per_agent))
     return launch_query(st, net, rows, X, ldx, Y, N, envs_per_agent);
   {
     hipError_t terr = hipSuccess;

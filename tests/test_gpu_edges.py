@@ -349,7 +349,10 @@ def test_small_value_head(base, N, agents, Hd, D, K, T):
                                                        ("tiny", 16, 31, 1, 128, 7, 0), ("tiny", 128, 100, 2, 256, 32, 16), ("tiny", 16, 300, 1, 256, 17, 9),
                                                        ("tiny", 448, 440, 7, 256, 5, 2), ("large", 16, 15, 1, 64, 1, 1), ("large", 16, 33, 1, 128, 16, 4), ("large", 256, 250, 4, 256, 29, 17),
                                                        ("large", 16, 16, 1, 512, 30, 19), ("large", 128, 65, 2, 512, 3, 0), ("large", 8200, 8192, 1, 512, 12, 2),
-                                                       ("large", 8200, 8193, 1, 512, 12, 2), ("tiny", 8200, 8192, 1, 64, 12, 2)])
+                                                       ("large", 8200, 8193, 1, 512, 12, 2), ("tiny", 8200, 8192, 1, 64, 12, 2),
+                                                       # (weights of a megabyte, either side of the row counts that keep a launch per layer)
+                                                       ("tiny", 16, 1024, 1, 256, 30, 11), ("tiny", 16, 1025, 1, 256, 30, 11), ("tiny", 256, 256, 4, 256, 17, 21),
+                                                       ("tiny", 384, 257, 6, 256, 17, 21), ("large", 16, 31, 1, 512, 32, 14), ("large", 16, 32, 1, 512, 32, 14)])
 def test_networks_in_one_launch(base, N, rows, agents, Hd, D, K):
     w = inputs.WORKLOADS[base].replace(n_envs=N, n_agents=agents, hidden=Hd, n_stocks=D, n_ind=K, steps=1)
     d = inputs.make_all(w, horizon=1, n_market=1, steps=1)
@@ -501,7 +504,8 @@ def test_learner_with_an_infinite_weight_of_the_last_input(B, D, K, Hd, layer):
 # queries of one handle from several sides at once: a captured query writes nothing but its output, so graphs replay beside
 # each other, eager queries and a captured rollout; launches of one call stay together when two threads ask
 @pytest.mark.parametrize("base,N,rows,Hd,D,K", [("large", 128, 48, 512, 30, 8), ("large", 16, 1000, 64, 5, 2), ("dow30", 128, 33, 256, 30, 8),
-                                                ("dow30", 1000, 1000, 512, 30, 4), ("large", 256, 200, 1024, 300, 2), ("dow30", 64, 1, 96, 3, 0)])
+                                                ("dow30", 1000, 1000, 512, 30, 4), ("large", 256, 200, 1024, 300, 2), ("dow30", 64, 1, 96, 3, 0),
+                                                ("large", 128, 20, 512, 30, 18), ("dow30", 64, 100, 256, 30, 12)])
 def test_queries_side_by_side(base, N, rows, Hd, D, K):
     import threading
     T = 6
