@@ -176,7 +176,7 @@ Layout make_layout(const pr_config &c) {
   if (table_supported(c)) {
     for (int net = 0; net < 2; ++net)
       for (int part = 0; part < 2; ++part) L.table_w[net][part] = take(packed_weight_bytes(16 * table_blocks(c, part), Hd, bf));
-    L.table_p = take(table_scratch_bytes(c.n_envs));
+    L.table_p = take(table_scratch_bytes(c.n_envs, c.horizon));
     L.tau0 = take(N * 4);
   }
   L.total = off;
@@ -450,7 +450,7 @@ int rollout_step_T(pr_handle *h, int32_t T, const float *noise, const pr_buffers
     const TableMarket m{h->market.price, h->market.ind, h->table_rows};
     POD_HIP(launch_rollout_table(h->stream, h->dims, h->st, m, table_net(h, 0), h->table_p, h->tau0, T, noise, *out, compute_units()));
     const int64_t rows = (int64_t)(T + 1) * (int64_t)N;
-    if (out->value && value_table_covers(rows, (int32_t)N, h->table_rows)) {
+    if (out->value && value_table_covers(rows, (int32_t)N, h->cfg.horizon, h->table_rows)) {
       POD_HIP(launch_value_table(h->stream, h->dims, h->st, m, table_net(h, 1), h->table_p, h->tau0, rows, out->obs, out->value,
                                  compute_units()));
       return PR_OK;

@@ -256,8 +256,8 @@ hipError_t launch_value_small(hipStream_t st, const PackedNet &critic, int64_t r
 bool table_supported(const pr_config &c);
 int table_market_blocks(int D, int K);
 int table_portfolio_blocks(int D);
-int64_t table_rows_kept(int64_t n_envs);
-size_t table_scratch_bytes(int64_t n_envs);
+int64_t table_rows_kept(int64_t n_envs, int64_t horizon);
+size_t table_scratch_bytes(int64_t n_envs, int64_t horizon);
 struct TableMarket {
   const float *price, *ind;
   int32_t rows;
@@ -271,7 +271,7 @@ struct TableNet {
 hipError_t launch_rollout_table(hipStream_t st, const EnvDims &d, const EnvState &s, const TableMarket &m, const TableNet &actor,
                                 float *P, int32_t *tau0, int32_t T, const float *noise, const pr_buffers &out, int cus);
 // The value head over the observations of such a rollout, where they are at least twice the table's rows.
-bool value_table_covers(int64_t rows, int32_t n_envs, int32_t table_rows);
+bool value_table_covers(int64_t rows, int32_t n_envs, int32_t horizon, int32_t table_rows);
 hipError_t launch_value_table(hipStream_t st, const EnvDims &d, const EnvState &s, const TableMarket &m, const TableNet &critic,
                               float *P, const int32_t *tau0, int64_t rows, const float *obs, float *Y, int cus);
 

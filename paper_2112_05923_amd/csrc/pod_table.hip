@@ -867,16 +867,18 @@ bool table_supported(const pr_config &c) {
 int table_market_blocks(int D, int K) { return (((D * K + 3) & ~3) + D + 15) / 16; }
 int table_portfolio_blocks(int D) { return portfolio_blocks(D); }
 
-// 128 MiB of rows, or one step's
-int64_t table_rows_kept(int64_t n_envs) {
-  const int64_t rows = ((int64_t)128 << 20) / (kPitch * 4);
-  return rows > n_envs ? rows : n_envs;
+// Rows of P: those of every env and step of two episodes, which no call of so many steps needs more of (a longer table's are formed
+// by env and step there); at least 8192 of them (17 MiB) and at most 128 MiB, or one step's.  16 envs over 100 rows: 17 MiB of
+// workspace, where every handle had 128.  Calls of more steps go in pieces if their table is longer than that too.
+int64_t table_rows_kept(int64_t n_envs, int64_t horizon) {
+  const int64_t most = ((int64_t)128 << 20) / (kPitch * 4);
+  return max(n_envs, min(most, max((int64_t)8192, 2 * n_envs * horizon)));
 }
-size_t table_scratch_bytes(int64_t n_envs) { return (size_t)table_rows_kept(n_envs) * kPitch * 4; }
+size_t table_scratch_bytes(int64_t n_envs, int64_t horizon) { return (size_t)table_rows_kept(n_envs, horizon) * kPitch * 4; }
 
 hipError_t launch_rollout_table(hipStream_t st, const EnvDims &d, const EnvState &s, const TableMarket &m, const TableNet &actor,
                                 float *P, int32_t *tau0, int32_t T, const float *noise, const pr_buffers &out, int cus) {
-  const int64_t kept = table_rows_kept(d.N);
+  const int64_t kept = table_rows_kept(d.N, d.H);
   const bool pairs = m.rows > kept || (int64_t)m.rows > (int64_t)T * d.N;
   const int32_t steps = pairs ? (int32_t)min((int64_t)T, kept / d.N) : T;
   TableArgs a;
@@ -911,8 +913,8 @@ hipError_t launch_rollout_table(hipStream_t st, const EnvDims &d, const EnvState
   return hipSuccess;
 }
 
-bool value_table_covers(int64_t rows, int32_t n_envs, int32_t table_rows) {
-  return table_rows <= table_rows_kept(n_envs) && 2 * (int64_t)table_rows <= rows;
+bool value_table_covers(int64_t rows, int32_t n_envs, int32_t horizon, int32_t table_rows) {
+  return table_rows <= table_rows_kept(n_envs, horizon) && 2 * (int64_t)table_rows <= rows;
 }
 
 hipError_t launch_value_table(hipStream_t st, const EnvDims &d, const EnvState &s, const TableMarket &m, const TableNet &critic,

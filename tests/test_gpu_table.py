@@ -27,6 +27,7 @@ CASES = [
     (16, 101, 5, 33, 32, 40),
     (1, 40, 8, 64, 8, 20),
     (1500, 35, 1, 64000, 64, 90),   # a table longer than the rows kept: in pieces of 42 steps
+    (200, 33, 1, 9000, 10, 50),     # and than those kept for few steps' envs: in pieces of 40
 ]
 
 

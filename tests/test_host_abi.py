@@ -71,6 +71,15 @@ def test_workspace_query_and_config_validation():
     assert pr.lib().rollout_workspace_bytes(None, None) == pr.PR_EINVAL
 
 
+def test_workspace_of_shared_table_rollouts_follows_their_size():
+    """Market sums of the rows of two episodes: a few envs need megabytes, many up to 128 MiB beside the rest."""
+    size = lambda n, horizon: _ws(pr.make_config(inputs.WORKLOADS["large"].replace(n_envs=n, n_stocks=40, hidden=512), horizon=horizon,
+                                                 n_market=1))[1]
+    assert size(16, 100) < 32 << 20
+    assert size(16, 100) < size(200, 100) < size(4096, 100)
+    assert size(4096, 100000) - size(4096, 100) < 1 << 20
+
+
 def test_persistent_kernel_lds_fits_the_compute_unit_for_every_shape_it_accepts():
     """The launch of the persistent kernel takes its LDS size from the same carve-up this query reads; every
     shape the schedule accepts must fit the 160 KiB of a compute unit, with and without the actor, and the
