@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kThreads, 2) void query_kernel(QueryArgs a) {
   constexpr int KP = KS >= 4 ? 4 : KS, PER = KS / KP;  // layer 3: its k-steps in KP parts
   extern __shared__ __align__(16) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t row0 = (int64_t)xcd_index(blockIdx.x, gridDim.x) * kRows;
+  const int64_t row0 = (int64_t)xcd_run(blockIdx.x, gridDim.x) * kRows;
   const Net net = net_of(a.net, (int)(row0 % a.N) / a.envs_per_agent);
   const int S = a.net.in_dim[0], nkb = net.nkb[0], nks = (nkb + 1) / 2, XP = tile_pitch<BF16>(2 * nks);
   unsigned char *ldsX = lds, *ldsH1 = ldsX + kRows * XP, *ldsH2 = ldsH1 + kRows * HP;
@@ -226,7 +226,7 @@ hipError_t launch_inst(hipStream_t st, const QueryArgs &a) {
 //   fp32, 256    14.3 -> 12.0  14.2 -> 12.6  23.0 -> 13.7  38.9 -> 24.4  40.3 -> 46.5
 //   bf16, 256    13.1 ->  7.5  12.8 ->  7.9  16.0 ->  7.6  24.8 -> 11.2  20.8 -> 18.8
 //   bf16, 512    13.4 -> 10.8  14.8 -> 11.3  25.0 -> 11.7  32.4 -> 21.2  28.1 -> 39.4
-// Several agents: an agent's workgroups stand on one XCD, so its weights cross from memory once (xcd_index; taken as they come, four
+// Several agents: an agent's workgroups stand on one XCD, so its weights cross from memory once (xcd_run; taken as they come, four
 // XCDs fetched the same 0.9 MB: 64 agents of 64 rows 23.7 -> 34 us).  us a call, a launch per layer -> this:
 //   agents x rows      8 x 64         32 x 64        64 x 64        4 x 1024
 //   fp32, 128       10.8 ->  7.6   12.0 ->  7.7   15.2 ->  8.0   13.9 ->  8.1

@@ -720,9 +720,11 @@ template <bool BF16>
 __host__ __device__ constexpr int tile_pitch(int nkb) { return nkb * Op<BF16>::KBYTES + 16; }
 inline int tile_pitch(int bf16, int nkb) { return bf16 ? tile_pitch<true>(nkb) : tile_pitch<false>(nkb); }
 
-// Workgroup b of n runs on XCD b % 8: the index that gives every XCD a run of consecutive tiles, so that the workgroups that
-// share an L2 stream the same agent's weights.
-__device__ inline unsigned xcd_index(unsigned b, unsigned n) {
+// Workgroup b runs on XCD b % 8: the index that gives every XCD a run of consecutive tiles, so that the workgroups that
+// share an L2 stream the same agent's weights.  xcd_run: for any number n of workgroups (a persistent rollout of one agent in 114
+// tiles takes 3.52 ms for 3.46 with it).
+__device__ inline unsigned xcd_index(unsigned b, unsigned n) { return n % 8 ? b : (b & 7) * (n / 8) + (b >> 3); }
+__device__ inline unsigned xcd_run(unsigned b, unsigned n) {
   const unsigned x = b & 7, more = n % 8;  // (the first `more` XCDs have one more)
   return x * (n / 8) + (x < more ? x : more) + (b >> 3);
 }
