@@ -13,6 +13,7 @@ namespace pod {
 namespace {
 
 using tile::f32x4;
+using tile::mma16;
 using tile::u32x4;
 typedef f32x4 f32x4u __attribute__((aligned(4)));
 
@@ -25,19 +26,6 @@ struct QueryArgs {
   int32_t N, envs_per_agent;
   float *Y;        // [rows][out]
 };
-
-// A product of 16 features x 32 inputs x the 16 rows.  fp32: the three smallest of the six products go into a chain of their own.
-__device__ inline f32x4 mfma16(const u32x4 &w, const u32x4 &x, const f32x4 &c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c, 0, 0, 0);
-}
-__device__ inline void mma16(const u32x4 &w, const u32x4 &x, f32x4 &hi, f32x4 &) { hi = mfma16(w, x, hi); }
-__device__ inline void mma16(const tile::Blk3 &w, const tile::Blk3 &x, f32x4 &hi, f32x4 &lo) {
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    lo = mfma16(w.p[kSplitA[i]], x.p[kSplitB[i]], lo);
-    hi = mfma16(w.p[kSplitA[3 + i]], x.p[kSplitB[3 + i]], hi);
-  }
-}
 
 // The sums of a feature tile: input step k goes to chain k % CH.  What a sum loses it loses in its longest chain of additions:
 // fp32, 301 inputs and 256 units, against 64 bits (2-norm, actor and critic, 24 networks of 1000 rows) one chain 2.2e-7 and

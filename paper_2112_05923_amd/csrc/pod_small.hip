@@ -55,22 +55,10 @@ struct SmallArgs {
   int32_t *shares;     // opt [T, N, D]
 };
 
-// A product of 16 features x 32 inputs x the 16 envs: lane l holds inputs 8 (l / 16) + 0..7 of feature (env) l % 16 and gets
-// the sums of features 4 (l / 16) + 0..3 of env l % 16.  fp32: the three largest of the six products in a chain of their own.
+// What a chain of products with the 16 envs adds up to; fp32: the three smallest of the six in a sum of their own (mma16).
 struct Sums {
   f32x4 hi = {0.0f, 0.0f, 0.0f, 0.0f}, lo = {0.0f, 0.0f, 0.0f, 0.0f};
 };
-__device__ inline f32x4 mfma16(const u32x4 &w, const u32x4 &x, const f32x4 &c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c, 0, 0, 0);
-}
-__device__ inline void mma16(const u32x4 &w, const u32x4 &x, Sums &s) { s.hi = mfma16(w, x, s.hi); }
-__device__ inline void mma16(const tile::Blk3 &w, const tile::Blk3 &x, Sums &s) {
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    s.lo = mfma16(w.p[kSplitA[i]], x.p[kSplitB[i]], s.lo);
-    s.hi = mfma16(w.p[kSplitA[3 + i]], x.p[kSplitB[3 + i]], s.hi);
-  }
-}
 
 template <int HD>
 struct Geometry {
@@ -247,7 +235,7 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
     for (int i = 0; i < NB; ++i) {
       Block b;
       fetch_x(b, x + 2 * i * O::KBYTES);
-      mma16(wb[i], b, s[i & 1]);
+      mma16(wb[i], b, s[i & 1].hi, s[i & 1].lo);
     }
     f32x4 v = NB > 1 ? s[0].hi + s[1].hi : s[0].hi;
     if (!BF16) v += NB > 1 ? s[0].lo + s[1].lo : s[0].lo;
@@ -529,7 +517,7 @@ __global__ __launch_bounds__(kEnvThreads, 2) void value_small_kernel(ValueSmallA
     for (int i = 0; i < NB; ++i) {
       Block b;
       fetch_x(b, x + 2 * i * O::KBYTES);
-      mma16(wb[i], b, s[i & 1]);
+      mma16(wb[i], b, s[i & 1].hi, s[i & 1].lo);
     }
     f32x4 v = s[0].hi + s[1].hi;
     if (!BF16) v += s[0].lo + s[1].lo;

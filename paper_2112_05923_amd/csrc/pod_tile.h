@@ -720,6 +720,20 @@ template <bool BF16>
 __host__ __device__ constexpr int tile_pitch(int nkb) { return nkb * Op<BF16>::KBYTES + 16; }
 inline int tile_pitch(int bf16, int nkb) { return bf16 ? tile_pitch<true>(nkb) : tile_pitch<false>(nkb); }
 
+// A product of 16 features x 32 inputs x 16 rows: lane l holds inputs 8 (l / 16) + 0..7 of feature (row) l % 16 and gets the sums
+// of features 4 (l / 16) + 0..3 of row l % 16.  fp32: the three smallest of the six products go into a chain of their own.
+__device__ inline f32x4 mfma16(const u32x4 &w, const u32x4 &x, const f32x4 &c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c, 0, 0, 0);
+}
+__device__ inline void mma16(const u32x4 &w, const u32x4 &x, f32x4 &hi, f32x4 &) { hi = mfma16(w, x, hi); }
+__device__ inline void mma16(const Blk3 &w, const Blk3 &x, f32x4 &hi, f32x4 &lo) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    lo = mfma16(w.p[kSplitA[i]], x.p[kSplitB[i]], lo);
+    hi = mfma16(w.p[kSplitA[3 + i]], x.p[kSplitB[3 + i]], hi);
+  }
+}
+
 // Workgroup b runs on XCD b % 8: the index that gives every XCD a run of consecutive tiles, so that the workgroups that
 // share an L2 stream the same agent's weights.  xcd_run: for any number n of workgroups (a persistent rollout of one agent in 114
 // tiles takes 3.52 ms for 3.46 with it).
