@@ -67,10 +67,11 @@ typedef struct pr_config {
                            activations rounded to bf16 (nearest-even),
                            fp32 accumulate, fp32 bias / tanh / outputs */
   int32_t schedule;     /* PR_SCHED_STEPWISE: actor and env launches for every
-                           step (networks of 64 or 128 hidden units on at most
-                           320 inputs and 32 stocks: one launch for all steps,
-                           but for more than 8192 envs with fp32 networks of 128
-                           units on more than 160 inputs);
+                           step, or one launch for all steps for networks of 64
+                           or 128 hidden units on at most 320 inputs and 32
+                           stocks, and for one agent's bf16 networks of 512
+                           units on 33 to 128 stocks that have indicators, if
+                           all envs share one market path (M = 1);
                            PR_SCHED_FUSED: one persistent launch that
                            keeps each env tile on one compute unit for all T
                            steps (bf16 networks with 256 or 512 hidden units,
@@ -129,7 +130,9 @@ typedef struct pr_state {
 typedef struct pr_handle pr_handle;
 
 /* Device bytes rollout_init needs in `workspace` for this config (packed
- * weights, env state, per-step scratch).  out: host pointer. */
+ * weights, env state, per-step scratch; where the stepwise schedule runs over one
+ * shared market path in one launch, 17 to 128 MiB of sums over market rows or one
+ * step's, by N and H).  out: host pointer. */
 int rollout_workspace_bytes(const pr_config *cfg, size_t *out);
 
 /* LDS bytes per workgroup the persistent rollout kernel (Sec. 4.2 worker, the
@@ -191,8 +194,8 @@ int rollout_step_forced(pr_handle *h, int32_t T, const float *mu, const float *n
 /* One network on its own: rows of X ([rows, S], row stride ldx floats) through
  * the actor (Y [rows, D]) or the critic (Y [rows]) of the agent that owns env
  * (row % N).  These are the kernels rollout_step_T uses for the critic and, in the
- * stepwise schedule of all but small networks, for the actor.  Several host threads may
- * ask one handle.  What a call on up to 8192 rows keeps between its launches lies in the
+ * stepwise schedule, for the actor, where the rollout has none of its own (its numbers
+ * then differ in the order of the sums).  Several host threads may ask one handle.  What a call on up to 8192 rows keeps between its launches lies in the
  * workspace, beside what a rollout keeps there, and the handle's stream orders it; a call
  * that is captured into a graph writes nothing but Y, so the graph can be replayed on any
  * stream, beside other work of the handle (on few rows it takes longer). */

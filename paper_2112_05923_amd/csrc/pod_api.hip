@@ -85,9 +85,10 @@ bool uses_rotated(const pr_config &c) { return c.schedule == PR_SCHED_FUSED || s
 
 // The value head's hidden layers run beside the actor's, step by step, on the bf16 rows the actor reads, instead of over the whole
 // record afterwards, where that fills compute units the actor's leave idle (or one round of taller tiles) and the inputs are too
-// many for the kernels that keep a tile's inputs in LDS.  Rollouts, us per step: 2048 envs x 300 stocks, 512 units 50.7 -> 46.1,
-// 1024 x 300 with 1024 units 49.7 -> 44.8, 600 x 500 56.7 -> 51.7, 1500 x 130, 512 units 35.9 -> 33.9; one round of tall
-// tiles, 2048 x 500 with 1024 units 84.4 -> 79.8 (the value head alone is bound by its weights there); with more tiles than that
+// many for the kernels that keep a tile's inputs in LDS.  Rollouts, us per step: 2048 envs x 300 stocks, 512 units 53.3 -> 48.2,
+// 1024 x 300 with 1024 units 52.1 -> 46.3, 600 x 500 56.5 -> 51.5, 1500 x 130, 512 units 35.7 -> 33.8.  One round of tall
+// tiles, 1665 to 2048 rows with 1024 units: 2048 x 500 82.2 -> 78.5, 1700 x 500 80.0 -> 76.1, 2048 x 300 67.6 -> 65.9, 1800 x 300 x 3
+// 64.6 -> 62.1, level at 150 stocks (50.8; 1700 x 150 x 2 47.0 -> 47.4).  With more tiles than that
 // it is slower: 1400 x 200 with 1024 units (352 tiles) 50.9 -> 52.9, 4000 x 100, 512 units (504) 48.8 -> 51.6.
 bool value_beside(const pr_config &c) { return uses_shadow(c) && state_dim(c) > 320 && layers_room_beside(c.n_envs, c.n_envs / c.n_agents, c.hidden); }
 // steps whose last activations are kept for one launch of the output layer: 32 MiB, or one step's

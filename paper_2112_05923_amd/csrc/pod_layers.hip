@@ -2,7 +2,8 @@
 // of a few thousand envs), bf16 operands: a small-batch GEMM with the bias and tanh in its epilogue.
 //
 // A kernel that carries a row tile through all three layers would leave most compute units idle at these sizes.  Here a
-// workgroup owns 64 rows x 128 output features of one layer, so 2048 rows x 1024 features are 256 workgroups.
+// workgroup owns 64 rows x 128 output features of one layer (128 x 128 where those are full rounds: tall_tiles), so 2048 rows x
+// 1024 features are 256 workgroups; a rollout's policy and critic stand side by side in a launch where that is one round.
 #include "pod_internal.h"
 
 #include "pod_tile.h"

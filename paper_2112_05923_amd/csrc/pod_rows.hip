@@ -1,5 +1,5 @@
 // One network layer per launch for the fewest rows of networks that pod_query.hip does not take (fp32 with 512 hidden units, 1024,
-// many inputs or outputs): a policy asked for actions on a handful of observations, the steps of a few hundred envs.
+// many inputs or outputs, few rows for a megabyte of weights): a policy asked for actions on a handful of observations, the steps of a few hundred envs.
 //
 // A kernel that carries a row tile through the network streams every weight through one compute unit: 8 MB of bf16 weights of 3001
 // inputs and 1024 hidden units would take 55 us at 150 GB/s.  Here a workgroup owns 32 output features of one layer and 32

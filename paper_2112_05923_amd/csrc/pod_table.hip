@@ -12,8 +12,15 @@
 // rows, values and advantages included: 7.97 -> 3.31 ms (four launches a step
 // 49.5 us -> 21 us; P of either network 30 us; value head 1.72 -> 0.6 ms).
 // 8192 envs x 120 stocks, 32 steps 2.89 -> 1.49 ms, 512 x 60 0.74 -> 0.53, 16
-// envs x 40, 64 steps 1.11 -> 0.67; calls of one step are level from 100 envs of
-// 40 stocks on (5000 x 100 138 -> 136 us), 200 x 100 60 -> 67 us.
+// envs x 40, 64 steps 1.11 -> 0.67.  Calls of two steps are level or faster from
+// 16 envs on; of one step only those of 2000 envs and more, or of 40 stocks: us
+// without values, launches per step -> this (11 to 14 of it the market sums)
+//   envs         16           200           1000          2000          5000
+//    40     20.0 -> 21.2  22.0 -> 22.4  24.5 -> 24.2  30.8 -> 27.0  40.8 -> 39.2
+//   100     24.1 -> 30.3  29.2 -> 33.2  34.1 -> 35.4  40.6 -> 38.4  58.0 -> 54.5
+//   128     26.2 -> 32.3  33.2 -> 35.4  40.0 -> 37.8  43.9 -> 40.7  64.2 -> 60.4
+// They are not sent back to those launches: layer 1's sums would have another
+// order, and a rollout gives the same bits however it is cut into calls.
 //
 // Compiled with floating-point contraction off (pod_trade.h); the network code
 // uses explicit fmaf.
