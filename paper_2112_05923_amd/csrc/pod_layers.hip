@@ -349,13 +349,36 @@ int32_t layers_pitch(int cols) { return (cols + 15) / 16 * 16 + 64; }
 
 namespace {
 
-// 128 rows a tile where there are more workgroups of 64 than compute units and those of 128 are full rounds, or nearly: two
-// thirds of the bytes for the same work, but one workgroup on a compute unit instead of two.  Rollouts with values, per step:
-// 8000 envs x 60 stocks x 8, 512 units (252 tiles) 63.6 -> 61.8 us, 6000 x 60 (188) 56.1 -> 57.0, 4500 x 128 (144) 59.1 -> 60.8.
+// An XCD's patch of tiles: the split of the eight XCDs that reads the fewest bytes (input rows and weight columns weigh the
+// same per k), among those that leave the fewest tiles on the busiest XCD, up to `slots` tiles counting the same.
+struct Patch {
+  int split_f, r, f;
+};
+Patch patch_of(int tiles_r, int tiles_f, int tile_rows, int slots) {
+  Patch best{};
+  int best_tiles = 0, best_bytes = 0;
+  for (int sf = 1; sf <= 8; sf *= 2) {
+    const int pr = (tiles_r + 8 / sf - 1) / (8 / sf), pf = (tiles_f + sf - 1) / sf;
+    const int tiles = pr * pf > slots ? pr * pf : slots, bytes = pr * tile_rows + pf * kFeatures;
+    if (best.split_f == 0 || tiles < best_tiles || (tiles == best_tiles && bytes < best_bytes))
+      best = {sf, pr, pf}, best_tiles = tiles, best_bytes = bytes;
+  }
+  return best;
+}
+
+// 128 rows a tile where there are more workgroups of 64 than compute units and those of 128 are one full round, or nearly: two
+// thirds of the bytes for the same work, but one workgroup on a compute unit instead of two.  Rollouts, per step, tiles of 64
+// rows -> this: 512 units, 7200 envs x 60 stocks (228 tiles) 47.4 -> 45.8 us, 7500 48.1 -> 46.6, 8000 49.6 -> 48.1, 7600 and 8192
+// level; 1024 units, 3500 x 130 (224) 55.0 -> 52.1, 4000 57.8 -> 55.4, 4096 56.6 -> 55.7.  Two rounds are slower (8192 x 130, 1024 units
+// 86.9 -> 90.4), fewer tiles too (6000 x 60, 512 units, 188 tiles 56.1 -> 57.0), and so are patches that hold a tile less on every
+// XCD but read half as much again (31 x 1 tiles for 8 x 4: 7800 x 60, 512 units 47.5 -> 49.5): up to 32 tiles of an XCD are the same.
+constexpr int kTallSlots = 32;  // compute units of an XCD
 bool tall_tiles(int64_t rows, int64_t tiles_f, int32_t N, int32_t envs_per_agent) {
   const int64_t tall = (rows + 127) / 128 * tiles_f;
   const bool one_agent = N == envs_per_agent || envs_per_agent % 128 == 0;  // (in a tile)
-  return one_agent && (rows + 63) / 64 * tiles_f > 256 && (tall - 1) % 256 >= 223;
+  if (!one_agent || (rows + 63) / 64 * tiles_f <= 256 || tall < 224 || tall > 256) return false;
+  const Patch p = patch_of((int)((rows + 127) / 128), (int)tiles_f, 128, kTallSlots);
+  return p.r * p.f <= kTallSlots;
 }
 
 // Layer l of `count` networks of one shape.  `move`: indicators beside it, where there is room.
@@ -381,17 +404,8 @@ hipError_t launch_one_layer(hipStream_t st, const PackedNet *const *nets, int co
   const bool tall = l < 2 && tall_tiles(rows, a.tiles_f, N, envs_per_agent);
   const int tile_rows = tall ? 128 : 64;
   a.tiles_r = (int32_t)((rows + tile_rows - 1) / tile_rows);
-  // an XCD's patch: the split of the eight XCDs that reads the fewest bytes (input rows and weight columns weigh the
-  // same per k), among those that leave the fewest tiles on the busiest XCD
-  int best = 0, best_tiles = 0, best_bytes = 0;
-  for (int sf = 1; sf <= 8; sf *= 2) {
-    const int pr = (a.tiles_r + 8 / sf - 1) / (8 / sf), pf = (a.tiles_f + sf - 1) / sf;
-    const int tiles = pr * pf, bytes = pr * tile_rows + pf * kFeatures;
-    if (best == 0 || tiles < best_tiles || (tiles == best_tiles && bytes < best_bytes))
-      best = sf, best_tiles = tiles, best_bytes = bytes;
-  }
-  a.split_f = best;
-  a.patch_r = (a.tiles_r + 8 / best - 1) / (8 / best), a.patch_f = (a.tiles_f + best - 1) / best;
+  const Patch patch = patch_of(a.tiles_r, a.tiles_f, tile_rows, tall ? kTallSlots : 1);
+  a.split_f = patch.split_f, a.patch_r = patch.r, a.patch_f = patch.f;
   const unsigned blocks = 8u * (unsigned)(a.patch_r * a.patch_f);
   const bool two = blocks > 256;  // more workgroups than compute units
   a.first_move = (int32_t)blocks;

@@ -285,7 +285,10 @@ def test_small_network_books(base, Hd, D, K):
 # policies over tiles of 128 rows: ragged rows, several agents, more steps than are kept for one launch of the output layer
 @pytest.mark.parametrize("N,agents,Hd,D,K,T", [(1030, 1, 512, 40, 8, 30), (1152, 2, 512, 37, 9, 3), (560, 1, 1024, 130, 2, 2),
                                                (2048, 1, 512, 33, 8, 2), (1100, 1, 544, 90, 3, 2), (4150, 1, 512, 40, 8, 2),
-                                               (4480, 5, 512, 40, 8, 2), (4480, 7, 512, 35, 10, 2)])
+                                               (4480, 5, 512, 40, 8, 2), (4480, 7, 512, 35, 10, 2),
+                                               # (tiles of 128 rows: both networks', one's in a round that is full or not, agents of nine)
+                                               (1700, 1, 1024, 55, 5, 2), (2048, 1, 1024, 36, 8, 3), (7815, 1, 512, 33, 9, 2), (4001, 1, 1024, 36, 8, 2),
+                                               (8064, 7, 512, 35, 10, 2)])
 def test_value_head_beside_the_policy(N, agents, Hd, D, K, T):
     H = 2
     w = inputs.WORKLOADS["large"].replace(n_envs=N, n_agents=agents, hidden=Hd, n_stocks=D, n_ind=K, steps=T, cash0=5e4)
