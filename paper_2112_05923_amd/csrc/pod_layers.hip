@@ -88,7 +88,8 @@ __device__ inline void move_indicators(const IndicatorMove &m, int n, int lane) 
 // registers a wavefront, for two networks together.
 // KI = 16: 128 registers of weights and rows in flight, one workgroup per compute unit; KI = 8: half of that and two
 // workgroups per compute unit, for launches with more workgroups than compute units.
-template <int KI, int RB, bool HIDDEN>
+// PAIR: of two networks (the choice at run time costs launches of one 0.2 us of 15 to 23).
+template <int KI, int RB, bool HIDDEN, bool PAIR>
 __global__ __launch_bounds__(kThreads, KI == 8 && RB == 2 ? 4 : 2) void layer_kernel(LayerArgs a, IndicatorMove move) {
   extern __shared__ __align__(16) unsigned char lds[];
   constexpr int kRows = 32 * RB;
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(kThreads, KI == 8 && RB == 2 ? 4 : 2) void layer_ke
   const int tr = (xcd / a.split_f) * a.patch_r + sr, tile_f = (xcd % a.split_f) * a.patch_f + sf;
   if (sr >= a.patch_r || tr >= a.tiles_r || tile_f >= a.tiles_f) return;
   // (both networks' pointers arrive with the other arguments: picked by an index they would be a round trip of their own)
-  const bool second = tile_f >= a.own_f;
+  const bool second = PAIR && tile_f >= a.own_f;
   const int tf = second ? tile_f - a.own_f : tile_f;
   auto own = [&](auto &two) { return second ? two[1] : two[0]; };
   const int row0 = tr * kRows;
@@ -326,9 +327,9 @@ __global__ __launch_bounds__(kThreads) void value_dot_kernel(const __bf16 *__res
   if (lane == 0) Y[r] = s + b[(size_t)agent * b_stride];
 }
 
-template <int KI, int RB, bool HIDDEN>
+template <int KI, int RB, bool HIDDEN, bool PAIR = false>
 hipError_t launch_layer(hipStream_t st, const LayerArgs &a, unsigned blocks, const IndicatorMove &move) {
-  constexpr auto kern = layer_kernel<KI, RB, HIDDEN>;
+  constexpr auto kern = layer_kernel<KI, RB, HIDDEN, PAIR>;
   constexpr int kRows = 32 * RB;
   const hipError_t e = allow_full_lds<kern>();
   if (e != hipSuccess) return e;
@@ -419,6 +420,10 @@ hipError_t launch_one_layer(hipStream_t st, const PackedNet *const *nets, int co
   if (l > 0 && move && !move->moved && (two ? blocks <= 384 : blocks <= 128 && a.nkb >= 64)) {
     move->moved = true;
     m = *move, all += (unsigned)((m.d.N + kThreads / 64 - 1) / (kThreads / 64));
+  }
+  if (count == 2) {
+    if (tall) return launch_layer<8, 4, true, true>(st, a, all, m);
+    return two ? launch_layer<8, 2, true, true>(st, a, all, m) : launch_layer<16, 2, true, true>(st, a, all, m);
   }
   if (tall) return launch_layer<8, 4, true>(st, a, all, m);
   if (l < 2) return two ? launch_layer<8, 2, true>(st, a, all, m) : launch_layer<16, 2, true>(st, a, all, m);
