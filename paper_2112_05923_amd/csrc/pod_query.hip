@@ -234,13 +234,13 @@ bool query_supported(int64_t rows, int S, int hidden, int outputs, int bf16, int
 //   fp32, 256, 361  11.3 -> 11.3  12.8 -> 11.6  13.9 -> 11.9  13.1 -> 12.0  16.1 -> 12.0
 //   fp32, 256, 421  11.0 -> 12.5  12.7 -> 12.9  13.6 -> 13.2  12.8 -> 13.3  16.4 -> 13.3  12.4 -> 13.1
 //   fp32, 256, 601  12.2 -> 14.2  13.6 -> 14.8  14.6 -> 15.1  13.7 -> 15.2  18.1 -> 15.2  13.4 -> 15.0
-//   bf16, 512, 481  10.8 -> 11.0  12.1 -> 11.4  13.0 -> 11.6
+//   bf16, 512, 481  10.8 -> 11.0  12.1 -> 11.4  13.0 -> 11.6   (16 rows 11.5 -> 11.3; a rollout's step of one env 15.0 -> 15.9)
 //   bf16, 512, 541  10.8 -> 11.1  11.8 -> 11.6  12.6 -> 11.9
 //   bf16, 512, 601  10.8 -> 12.4  12.4 -> 12.6  13.4 -> 13.0  15.0 -> 13.1  20.4 -> 13.1  12.0 -> 12.8
 // (the third column: inputs; more agents share no weights: 16 x 64 rows of 601 inputs 18.0 -> 15.2 and 15.1 -> 13.1)
 bool query_outweighed(int64_t rows, int S, int hidden, int bf16, bool several) {
   if (several) return rows <= 256 && S > (bf16 ? 512 : 384) && hidden == (bf16 ? 512 : 256);
-  return bf16 ? hidden == 512 && S > 512 && rows < 32 : hidden == 256 && S > 384 && rows <= 1024;
+  return bf16 ? hidden == 512 && S > 384 && rows < (S > 512 ? 32 : 16) : hidden == 256 && S > 384 && rows <= 1024;
 }
 
 hipError_t launch_query(hipStream_t st, const PackedNet &net, int64_t rows, const float *X, int64_t ldx, float *Y, int32_t N,
