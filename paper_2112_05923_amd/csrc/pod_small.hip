@@ -45,6 +45,7 @@ struct SmallArgs {
   const float *price, *ind;
   PackedNet net;  // layer 1 in the input order [indicators | cash | prices | holdings]
   int32_t envs_per_agent, T;
+  int32_t runs;        // an XCD takes a run of workgroups
   const float *noise;  // [T, N, D]
   float *obs;          // [T+1, N, S]
   float *act_raw;      // [T, N, D]
@@ -115,7 +116,7 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
   const bool trader = !APART || w < kWaves / 2, keeper = !APART || !trader;
   int e = trade.thread() / TPE, tl = tid & (TPE - 1);  // of either kind: its env, its lane of the env
   const int dd = min(tl, D - 1);
-  const int n0 = blockIdx.x * SE, n = min(n0 + e, d.N - 1);
+  const int n0 = (int)(a.runs ? xcd_run(blockIdx.x, gridDim.x) : blockIdx.x) * SE, n = min(n0 + e, d.N - 1);
   const bool live = n0 + e < d.N, own = live && tl < D;
   const size_t N = (size_t)d.N;
 
@@ -458,7 +459,7 @@ __global__ __launch_bounds__(kEnvThreads, 2) void value_small_kernel(ValueSmallA
 
   // tiles of an agent: its rows in each step; of a single one the rows as they are
   const bool several = a.envs_per_agent < a.N;
-  const int agent = blockIdx.x / a.per_agent, first = blockIdx.x - agent * a.per_agent;
+  const int block = (int)(several ? xcd_run(blockIdx.x, gridDim.x) : blockIdx.x), agent = block / a.per_agent, first = block - agent * a.per_agent;
   const int64_t in_step = several ? a.envs_per_agent / RR : 1;
   const int64_t tiles = several ? a.rows / a.N * in_step : (a.rows + RR - 1) / RR;
   auto row0_of = [&](int64_t k) {
@@ -606,6 +607,10 @@ hipError_t launch_rollout_small(hipStream_t st, const EnvDims &d, const EnvState
   a.d = d, a.st = s, a.price = price, a.ind = ind, a.net = actor, a.envs_per_agent = envs_per_agent, a.T = T, a.noise = noise;
   a.obs = out.obs, a.act_raw = out.act_raw, a.reward = out.reward, a.done = out.done, a.logp = out.logp, a.mu = out.mu;
   a.shares = out.shares;
+  // An agent's workgroups on one XCD, which then has its weights from memory once: fp32, 64 units, 301 inputs, us a call of one step
+  // with values, 64 agents of 64 envs 37.5 -> 27.7, 8 agents of 64 25.6 -> 24.0; bf16 21.5 -> 16.2.  One agent's envs of any number are
+  // slower in runs (65536 x 30 in bf16 187 -> 198), and so are many envs of bf16 networks, whose weights are few (64 agents 196 -> 201).
+  a.runs = envs_per_agent < d.N && (!actor.bf16 || d.N <= 1024 * SE);
   return actor.bf16 ? launch_dtype<true>(st, a) : launch_dtype<false>(st, a);
 }
 
