@@ -462,10 +462,11 @@ int rollout_step_T(pr_handle *h, int32_t T, const float *noise, const pr_buffers
   } else if (small_supported(h->cfg)) {
     POD_HIP(launch_rollout_small(h->stream, h->dims, h->st, h->market.price, h->market.ind, h->actor_rot, per_agent, T, noise,
                                  *out));
-    if (out->value)
-      POD_HIP(launch_value_small(h->stream, h->critic, (int64_t)(T + 1) * (int64_t)N, out->obs, h->S, out->value, (int32_t)N, per_agent,
-                                 compute_units()));
-    return PR_OK;
+    const int64_t rows = (int64_t)(T + 1) * (int64_t)N;
+    if (out->value && value_small_covers(h->critic, rows)) {
+      POD_HIP(launch_value_small(h->stream, h->critic, rows, out->obs, h->S, out->value, (int32_t)N, per_agent, compute_units()));
+      return PR_OK;
+    }
   } else {
     POD_HIP(launch_observe(h->stream, h->dims, h->st, h->market.price, h->market.ind, out->obs, h->shadow));
     const bool beside = out->value && h->critic_rot.W[0];

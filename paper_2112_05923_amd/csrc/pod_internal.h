@@ -248,6 +248,8 @@ hipError_t launch_rollout_small(hipStream_t st, const EnvDims &d, const EnvState
                                 const pr_buffers &out);
 
 // And the value head over the observations of such a rollout, whole steps of N rows, on `cus` compute units.
+// (the rows it is the fastest kernel for)
+bool value_small_covers(const PackedNet &critic, int64_t rows);
 hipError_t launch_value_small(hipStream_t st, const PackedNet &critic, int64_t rows, const float *X, int32_t S, float *Y, int32_t N,
                               int32_t envs_per_agent, int cus);
 

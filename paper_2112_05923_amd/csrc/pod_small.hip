@@ -589,7 +589,10 @@ hipError_t launch_value_dtype(hipStream_t st, const ValueSmallArgs &a, int cus) 
 
 // 64 or 128 hidden units, up to 320 inputs and 32 stocks: what eight wavefronts hold in registers.
 // A round of workgroups, one per compute unit, is 4096 envs, and the launches per step that would take over (query_kernel or
-// mlp_tiles_kernel, and an env step) never win.  Rollouts with values of 24 steps, 16 of 16384 envs and 6 of 65536; us, this and those:
+// mlp_tiles_kernel, and an env step) win only for calls of a step or a few of very many envs in fp32 with 128 units on more than 160 inputs,
+// where the start of a workgroup costs more than a step: 65536 envs x 30, one step 365 -> 508 us, two 298 -> 353 a step, four 264
+// -> 272, eight 246 -> 232, sixteen 236 -> 212; 16384 envs of 16 agents, one 114 -> 128, two 92 -> 86.  (All calls take the one launch:
+// a rollout gives the same bits however it is cut into calls.)  Rollouts with values of 24 steps, 16 of 16384 envs and 6 of 65536; us, this and those:
 //   envs                         512           4096          8192          16384          65536
 //   fp32, 128 units, 301     203 and 359   324 and 525   639 and 903   871 and 1166  1498 and 1629
 //   fp32, 128 units, 151     109 and 328   181 and 438   327 and 694   446 and 854    792 and 1204
@@ -612,6 +615,17 @@ hipError_t launch_rollout_small(hipStream_t st, const EnvDims &d, const EnvState
   // slower in runs (65536 x 30 in bf16 187 -> 198), and so are many envs of bf16 networks, whose weights are few (64 agents 196 -> 201).
   a.runs = envs_per_agent < d.N && (!actor.bf16 || d.N <= 1024 * SE);
   return actor.bf16 ? launch_dtype<true>(st, a) : launch_dtype<false>(st, a);
+}
+
+// Where other kernels of the forward pass are the faster value head.  Up to 4096 rows of more than 64 inputs: query_kernel, which starts
+// on the rows at once; us a step of calls of four steps, this -> that: fp32, 64 units, 301 inputs, 5 rows 8.05 -> 7.01, 500 9.2 -> 7.9,
+// 2000 9.3 -> 8.0, 4100 9.5 -> 9.6; 97 inputs 2000 rows 6.2 -> 5.9; bf16, 128 units, 301 inputs 500 rows 5.9 -> 5.5; 46 inputs level, 21
+// 4.7 -> 4.9.  Many rows in bf16 of more than 160 inputs, which pay for 320 here: 128 units, 301 inputs, 20480 rows 9.8 -> 8.7 the
+// other way round, 30000 14.2 -> 14.0, 81920 29.3 -> 27.8, 327680 131 -> 115 (161 inputs 101 -> 88), 64 units 163840 level, 327680 111 -> 108.
+bool value_small_covers(const PackedNet &critic, int64_t rows) {
+  const int nkb = critic.nkb[0], hidden = critic.out_dim[0];
+  if (nkb > 4 && rows <= 4096) return false;
+  return !(critic.bf16 && nkb > 10 && rows > (hidden == 64 ? 200000 : 24576));
 }
 
 hipError_t launch_value_small(hipStream_t st, const PackedNet &critic, int64_t rows, const float *X, int32_t S, float *Y, int32_t N,

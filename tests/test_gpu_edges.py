@@ -324,7 +324,11 @@ def test_value_head_beside_the_policy(N, agents, Hd, D, K, T):
 @pytest.mark.parametrize("base,N,agents,Hd,D,K,T", [("tiny", 16, 1, 64, 1, 0, 3), ("tiny", 1037, 1, 64, 5, 2, 15), ("tiny", 77, 1, 64, 20, 3, 5),
                                                     ("tiny", 192, 3, 64, 30, 8, 200), ("tiny", 33, 1, 128, 2, 0, 4), ("tiny", 128, 2, 128, 12, 9, 90),
                                                     ("tiny", 500, 1, 128, 31, 8, 12), ("large", 50, 1, 64, 13, 1, 2), ("large", 256, 4, 64, 32, 6, 70),
-                                                    ("large", 41, 1, 128, 8, 4, 9), ("large", 8250, 1, 128, 29, 8, 1)])
+                                                    ("large", 41, 1, 128, 8, 4, 9), ("large", 8250, 1, 128, 29, 8, 1),
+                                                    # (either side of the rows and inputs that other kernels take)
+                                                    ("tiny", 1024, 1, 64, 13, 3, 3), ("tiny", 1025, 1, 64, 13, 3, 3), ("tiny", 1024, 1, 64, 8, 5, 3), ("large", 512, 4, 128, 30, 8, 7),
+                                                    ("large", 576, 9, 128, 30, 8, 7), ("large", 8192, 1, 128, 20, 6, 2), ("large", 8193, 1, 128, 20, 6, 2), ("large", 8193, 1, 128, 19, 6, 2),
+                                                    ("large", 40001, 1, 64, 20, 6, 4)])
 def test_small_value_head(base, N, agents, Hd, D, K, T):
     w = inputs.WORKLOADS[base].replace(n_envs=N, n_agents=agents, hidden=Hd, n_stocks=D, n_ind=K, steps=T, cash0=5e4)
     d = inputs.make_all(w, horizon=2, n_market=1, steps=T)
