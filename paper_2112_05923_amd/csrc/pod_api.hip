@@ -451,7 +451,7 @@ int rollout_step_T(pr_handle *h, int32_t T, const float *noise, const pr_buffers
     const TableMarket m{h->market.price, h->market.ind, h->table_rows};
     POD_HIP(launch_rollout_table(h->stream, h->dims, h->st, m, table_net(h, 0), h->table_p, h->tau0, T, noise, *out, compute_units()));
     const int64_t rows = (int64_t)(T + 1) * (int64_t)N;
-    if (out->value && value_table_covers(rows, (int32_t)N, h->cfg.horizon, h->table_rows)) {
+    if (out->value && value_table_covers(rows, h->S, (int32_t)N, h->cfg.horizon, h->table_rows)) {
       POD_HIP(launch_value_table(h->stream, h->dims, h->st, m, table_net(h, 1), h->table_p, h->tau0, rows, out->obs, out->value,
                                  compute_units()));
       return PR_OK;

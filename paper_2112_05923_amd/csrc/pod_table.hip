@@ -920,8 +920,17 @@ hipError_t launch_rollout_table(hipStream_t st, const EnvDims &d, const EnvState
   return hipSuccess;
 }
 
-bool value_table_covers(int64_t rows, int32_t n_envs, int32_t horizon, int32_t table_rows) {
-  return table_rows <= table_rows_kept(n_envs, horizon) && 2 * (int64_t)table_rows <= rows;
+// Its two launches take 18 us over a short table's rows at the least and 26 over 3000, whatever the observations; for few of them the
+// kernels for any network are faster: query_kernel (up to 8192 rows of 640 inputs), or a launch per layer (1024 rows of more).  us of the
+// value head, this -> those, tables of 33 rows:
+//   rows            80            600           2000           3400           5000           7500
+//   161 inputs 18.1 ->  9.0  18.1 ->  9.1  18.2 ->  9.3  18.4 ->  9.6  18.4 -> 18.0  18.7 -> 18.2
+//   401        20.2 -> 11.5  20.1 -> 11.5  19.8 -> 11.5  20.3 -> 11.9  20.0 -> 23.1  20.8 -> 24.7
+//   1001       25.6 -> 13.5  25.8 -> 20.6  26.1 -> 57.4
+// and of 400 rows 161 inputs 5000 rows 21.3 -> 18.1, 401 inputs 24.8 -> 25.7; of 3000 rows 7500 rows 26.2 -> 19.1, 27.0 -> 24.1.
+bool value_table_covers(int64_t rows, int S, int32_t n_envs, int32_t horizon, int32_t table_rows) {
+  const int64_t few = S > 640 ? 1024 : table_rows > 256 ? 8192 : 4096;
+  return table_rows <= table_rows_kept(n_envs, horizon) && 2 * (int64_t)table_rows <= rows && rows > few;
 }
 
 hipError_t launch_value_table(hipStream_t st, const EnvDims &d, const EnvState &s, const TableMarket &m, const TableNet &critic,

@@ -85,3 +85,19 @@ def test_rollout_over_a_shared_table(N, D, K, rows, H, T):
         assert torch.equal(v, out[k]), k
     for k, v in ro.get_state().items():
         assert torch.equal(v, end[k]), k
+
+
+# Values of calls with few rows, on either side of the lines at which the head over table sums takes over from the kernels for any
+# network: 4096 rows over a short table (N (T + 1) = 4096, 4097), 8192 over a longer one, 1024 rows of more than 640 inputs.
+@pytest.mark.parametrize("N,D,K,rows,T", [(40, 40, 2, 33, 1), (2048, 50, 3, 33, 1), (241, 33, 1, 33, 16), (4096, 40, 2, 260, 1),
+                                          (2731, 61, 2, 260, 2), (512, 128, 4, 40, 1), (205, 100, 8, 40, 4)])
+def test_values_of_few_rows_over_a_shared_table(N, D, K, rows, T):
+    w, d, start, ro, noise = _setup(N, D, K, rows, 20, T)
+    out = ro.alloc_buffers(T, value=True, logp=False, mu=True)
+    ro.step_T(T, noise, out)
+    few = np.unique(np.concatenate([np.arange(min(N, 20)), np.arange(N - 20, N)]))
+    obs, mu, value = (parity.to_np(out[k]) for k in ("obs", "mu", "value"))
+    parity.check_networks(w, d["actor"], d["critic"], obs[:T][:, few].reshape(-1, w.state_dim), mu[:, few].reshape(-1, D),
+                          value[:T][:, few].reshape(-1))
+    again = parity.to_np(ro.mlp_forward(pr.PR_NET_CRITIC, out["obs"].view(-1, w.state_dim)))
+    parity.check_two_tier("value", value.reshape(1, -1), again.reshape(1, -1), True)
