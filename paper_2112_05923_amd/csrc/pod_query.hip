@@ -220,11 +220,15 @@ hipError_t launch_inst(hipStream_t st, const QueryArgs &a) {
 //   fp32, 128       10.8 ->  7.6   12.0 ->  7.7   15.2 ->  8.0   13.9 ->  8.1
 //   fp32, 256       12.0 -> 11.6   17.4 -> 12.2   23.9 -> 15.0   22.7 -> 12.1
 //   bf16, 512       10.8 -> 10.1   18.9 -> 10.6   27.4 -> 13.1   24.1 -> 10.6
-// Their line was drawn at 4096 rows before that; 8192 rows of 8 agents, fp32 with 256 units, would be 23 us for 41, and are not
+// A second round of workgroups with few fp32 inputs is slower than tiles of 32 or 64 rows, whose weights are read less often: 5000
+// rows, critic and actor, this -> those: 64 units, 41 inputs 9.9 -> 8.6 and 9.9 -> 9.1, 121 inputs 10.3 -> 9.7 and 10.5 -> 10.2, 181
+// 10.9 -> 11.4; 128 units, 41 inputs 11.5 -> 10.7 and 11.6 -> 11.2, 91 inputs 11.8 -> 11.4 and 11.9 -> 12.3, 121 12.1 -> 12.4.
+// Several agents' line was drawn at 4096 rows before that; 8192 rows of 8 agents, fp32 with 256 units, would be 23 us for 41, and are not
 // taken yet.  fp32 with 512 units is 2.6 MB of weights a workgroup; more than 32 outputs would be more tiles than wavefronts.
 bool query_supported(int64_t rows, int S, int hidden, int outputs, int bf16, int32_t N, int32_t envs_per_agent) {
   if (hidden != 64 && hidden != 128 && hidden != 256 && !(bf16 && hidden == 512)) return false;
   if (outputs > kMaxOut || S > 640 || (envs_per_agent < N && envs_per_agent % kRows != 0)) return false;
+  if (rows > 4096 && !bf16 && (hidden == 64 ? S <= 128 : hidden == 128 && S <= 96)) return false;
   return rows <= (envs_per_agent < N ? 4096 : 8192);
 }
 

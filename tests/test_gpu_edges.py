@@ -377,6 +377,13 @@ def test_networks_in_one_launch(base, N, rows, agents, Hd, D, K):
             parity.check_networks(w, d["actor"], d["critic"], X[pick][:, :w.state_dim], mu[pick], val[pick], agent=a)
 
 
+# Either side of the rows and inputs (128 of 64 units, 96 of 128) from which few inputs of fp32 networks go to another kernel than fewer rows
+@pytest.mark.parametrize("rows,Hd,D,K", [(4096, 64, 9, 12), (4097, 64, 9, 12), (4100, 64, 8, 14), (8192, 64, 5, 0), (4097, 128, 5, 17),
+                                         (5000, 128, 8, 10), (4160, 128, 7, 0)])
+def test_fp32_networks_of_few_inputs_on_many_rows(rows, Hd, D, K):
+    test_networks_in_one_launch("tiny", 8200, rows, 1, Hd, D, K)
+
+
 # fp32 networks with infinities, numbers next to the largest and NaN among inputs and weights: every kernel of the
 # forward pass and both rollouts that keep their input tile give what fp32 sums give (a saturated unit, or NaN)
 @pytest.mark.parametrize("N,rows,Hd,D,K,fused", [(16, 16, 32, 3, 1, False), (64, 64 * 260 + 40, 256, 30, 8, False),
