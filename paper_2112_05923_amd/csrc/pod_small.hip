@@ -68,6 +68,14 @@ struct Geometry {
   static constexpr int F = 4 / WT;            // features of a lane that its wavefront takes through tanh
   static constexpr int KS = HD / 32;          // k-steps of layers 2 and 3
 };
+// Which kernels do not request the k-blocks behind the last one.  The others request the last one in their place and replace it by
+// zeros, for which the weights are waited for before the state and the market's first row are requested: a call of one step, fp32, 64
+// units, us without values 16 envs x 12 stocks x 4 9.0 -> 8.6, 500 x 16 x 8 11.7 -> 10.6, 10000 x 20 x 7 35.4 -> 32.2; 128 units, 500 x 12 x 4
+// 10.8 -> 9.6; with values 4096 x 20 x 7, 64 units 26.3 -> 23.5.  But they have more registers to spill in fp32 with 128 units and more than
+// 160 inputs (4096 x 30 x 8, 32 steps 272 -> 294 us), and in bf16 it pays with many blocks only (4096 x 12 x 4, 128 units, 32 steps with
+// values 124 -> 127).
+constexpr bool skips_blocks(bool bf16, int hd, int ks1) { return bf16 ? ks1 == 10 : hd == 64 || ks1 < 10; }
+
 constexpr int kMeanPitch = 36, kSharePitch = 66;  // floats: partial means of an env; a wavefront's sums of a feature
 
 // What a step's trades need of a stock's price, in LDS.
@@ -128,8 +136,13 @@ __global__ __launch_bounds__(kEnvThreads, 2) void rollout_small_kernel(SmallArgs
   // (packed blocks are 32 features x 16 inputs)
   auto fetch = [&](Block &b, const u32x4 *W, int nct, int nkb, int tile, int ks) {
     const int kb = 2 * ks + (q4 >> 1);
-    fetch_w(b, W + ((size_t)min(kb, nkb - 1) * nct + (tile >> 1)) * NP + (tile & 1) * 16 + row + 32 * (q4 & 1));
-    if (kb >= nkb) b = Block{};
+    if constexpr (skips_blocks(BF16, HD, KS1)) {
+      b = Block{};
+      if (kb < nkb) fetch_w(b, W + ((size_t)kb * nct + (tile >> 1)) * NP + (tile & 1) * 16 + row + 32 * (q4 & 1));
+    } else {
+      fetch_w(b, W + ((size_t)min(kb, nkb - 1) * nct + (tile >> 1)) * NP + (tile & 1) * 16 + row + 32 * (q4 & 1));
+      if (kb >= nkb) b = Block{};
+    }
   };
   Block w1[B1], w2[KS], w3;
 #pragma unroll
@@ -471,8 +484,13 @@ __global__ __launch_bounds__(kEnvThreads, 2) void value_small_kernel(ValueSmallA
   const Net net = net_of(a.net, agent);
   auto fetch = [&](Block &b, const u32x4 *W, int nkb, int ks) {
     const int kb = 2 * ks + (q4 >> 1);
-    fetch_w(b, W + ((size_t)min(kb, nkb - 1) * NCT + (ft >> 1)) * NP + (ft & 1) * 16 + row + 32 * (q4 & 1));
-    if (kb >= nkb) b = Block{};
+    if constexpr (!BF16 || skips_blocks(BF16, HD, KS1)) {  // (few registers are held here)
+      b = Block{};
+      if (kb < nkb) fetch_w(b, W + ((size_t)kb * NCT + (ft >> 1)) * NP + (ft & 1) * 16 + row + 32 * (q4 & 1));
+    } else {
+      fetch_w(b, W + ((size_t)min(kb, nkb - 1) * NCT + (ft >> 1)) * NP + (ft & 1) * 16 + row + 32 * (q4 & 1));
+      if (kb >= nkb) b = Block{};
+    }
   };
   Block w1[KS1], w2[KS];
 #pragma unroll
