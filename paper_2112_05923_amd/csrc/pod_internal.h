@@ -272,7 +272,7 @@ struct TableNet {
 // tau0: [N], receives the cursors the call starts at.
 hipError_t launch_rollout_table(hipStream_t st, const EnvDims &d, const EnvState &s, const TableMarket &m, const TableNet &actor,
                                 float *P, int32_t *tau0, int32_t T, const float *noise, const pr_buffers &out, int cus);
-// The value head over the observations of such a rollout, where they are many and at least twice the table's rows.
+// The value head over the observations of such a rollout, where they are many for the table's rows.
 bool value_table_covers(int64_t rows, int S, int32_t n_envs, int32_t horizon, int32_t table_rows);
 hipError_t launch_value_table(hipStream_t st, const EnvDims &d, const EnvState &s, const TableMarket &m, const TableNet &critic,
                               float *P, const int32_t *tau0, int64_t rows, const float *obs, float *Y, int cus);

@@ -928,9 +928,13 @@ hipError_t launch_rollout_table(hipStream_t st, const EnvDims &d, const EnvState
 //   401        20.2 -> 11.5  20.1 -> 11.5  19.8 -> 11.5  20.3 -> 11.9  20.0 -> 23.1  20.8 -> 24.7
 //   1001       25.6 -> 13.5  25.8 -> 20.6  26.1 -> 57.4
 // and of 400 rows 161 inputs 5000 rows 21.3 -> 18.1, 401 inputs 24.8 -> 25.7; of 3000 rows 7500 rows 26.2 -> 19.1, 27.0 -> 24.1.
+// Tables of more than half the rows are worth their sums where those kernels are far slower: more than 640 inputs, calls of one step
+// with values, 100 stocks x 8, 600 envs over 2000 and 16384 rows 100 -> 68.5 and 101 -> 82, 8000 over 16384 137 -> 118; 86 x 6, 600 over 16384
+// 83 -> 72 (1000 envs x 100 x 8 over 3000 rows: 94.6 before there were table sums, 101 with them in the policy alone).
 bool value_table_covers(int64_t rows, int S, int32_t n_envs, int32_t horizon, int32_t table_rows) {
   const int64_t few = S > 640 ? 1024 : table_rows > 256 ? 8192 : 4096;
-  return table_rows <= table_rows_kept(n_envs, horizon) && 2 * (int64_t)table_rows <= rows && rows > few;
+  const int64_t most = max(rows / 2, (int64_t)(S > 640 ? 16384 : 0));
+  return table_rows <= min(most, table_rows_kept(n_envs, horizon)) && rows > few;
 }
 
 hipError_t launch_value_table(hipStream_t st, const EnvDims &d, const EnvState &s, const TableMarket &m, const TableNet &critic,

@@ -88,9 +88,11 @@ def test_rollout_over_a_shared_table(N, D, K, rows, H, T):
 
 
 # Values of calls with few rows, on either side of the lines at which the head over table sums takes over from the kernels for any
-# network: 4096 rows over a short table (N (T + 1) = 4096, 4097), 8192 over a longer one, 1024 rows of more than 640 inputs.
+# network: 4096 rows over a short table (N (T + 1) = 4096, 4097), 8192 over a longer one, 1024 rows of more than 640 inputs (there
+# also over tables longer than the rows).
 @pytest.mark.parametrize("N,D,K,rows,T", [(40, 40, 2, 33, 1), (2048, 50, 3, 33, 1), (241, 33, 1, 33, 16), (4096, 40, 2, 260, 1),
-                                          (2731, 61, 2, 260, 2), (512, 128, 4, 40, 1), (205, 100, 8, 40, 4)])
+                                          (2731, 61, 2, 260, 2), (512, 128, 4, 40, 1), (205, 100, 8, 40, 4),
+                                          (513, 128, 4, 3000, 1), (600, 128, 3, 8192, 1), (600, 80, 6, 601, 1)])
 def test_values_of_few_rows_over_a_shared_table(N, D, K, rows, T):
     w, d, start, ro, noise = _setup(N, D, K, rows, 20, T)
     out = ro.alloc_buffers(T, value=True, logp=False, mu=True)
