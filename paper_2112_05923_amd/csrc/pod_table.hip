@@ -13,12 +13,11 @@
 // 49.5 us -> 21 us; P of either network 30 us; value head 1.72 -> 0.6 ms).
 // 8192 envs x 120 stocks, 32 steps 2.89 -> 1.49 ms, 512 x 60 0.74 -> 0.53, 16
 // envs x 40, 64 steps 1.11 -> 0.67.  Calls of two steps are level or faster from
-// 16 envs on; of one step only those of 2000 envs and more, or of 40 stocks: us
-// without values, launches per step -> this (11 to 14 of it the market sums)
-//   envs         16           200           1000          2000          5000
-//    40     20.0 -> 21.2  22.0 -> 22.4  24.5 -> 24.2  30.8 -> 27.0  40.8 -> 39.2
-//   100     24.1 -> 30.3  29.2 -> 33.2  34.1 -> 35.4  40.6 -> 38.4  58.0 -> 54.5
-//   128     26.2 -> 32.3  33.2 -> 35.4  40.0 -> 37.8  43.9 -> 40.7  64.2 -> 60.4
+// 16 envs on; of one step only some: us without values over a table of 8000 rows, launches per step -> this (stocks x indicators)
+//   envs          1            32            200           1000          2500          4000
+//    40 x 2  17.3 -> 18.4  20.3 -> 19.5  21.0 -> 20.9  23.2 -> 24.0  29.9 -> 27.6  33.2 -> 32.1
+//   100 x 8  21.6 -> 26.8  26.6 -> 28.4  30.2 -> 30.0  35.1 -> 37.2  44.4 -> 42.2  48.8 -> 51.9
+//   128 x 4  21.1 -> 25.1  26.1 -> 26.8  28.3 -> 28.5  33.3 -> 34.5  41.7 -> 39.5  45.3 -> 46.9
 // They are not sent back to those launches: layer 1's sums would have another
 // order, and a rollout gives the same bits however it is cut into calls.
 //
@@ -103,18 +102,27 @@ struct MarketArgs {
 };
 
 constexpr int kChunk = 8;  // k-blocks staged at a time
+template <int I>
+using Int = std::integral_constant<int, I>;
 
 // 64 rows x 512 features per workgroup; the rows travel through two LDS buffers CKB k-blocks at a time, requested
 // behind the chunk before.  A sum is one chain over the k-blocks whichever rows share a tile, so a row's P is the same number in
-// either mode.  FEW: 128 features per workgroup, for launches of fewer than 64 tiles (a call of one step of 200
-// envs x 100 stocks 72 -> 66 us).
-template <bool PAIRS, bool FEW>
+// any mode.  FEW: 128 features per workgroup, for launches of fewer than 64 tiles (a call of one step of 200
+// envs x 100 stocks 72 -> 66 us).  FEWEST: 32 rows x 32 features per workgroup, one wavefront of which multiplies, up to a
+// workgroup per compute unit: four workgroups draw 64 rows and all weights through four compute units (12 us of 900 market inputs, and
+// 13 with requests as far ahead as here).  Calls of one step, 100 stocks x 8, 64 envs 34.1 -> 28.6 us, 400 36.4 -> 31.2, 600 37.2 -> 38.4
+// (which stay with FEW); 128 x 4, 200 envs 32.2 -> 28.5.
+enum Rows { MANY, FEW, FEWEST };
+template <bool PAIRS, Rows MODE>
 __global__ __launch_bounds__(NT, 2) void market_rows_kernel(MarketArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  constexpr int CT = FEW ? 1 : CTH, NBT = FEW ? 1 : 2, RD = 4;
-  constexpr int CKB = kChunk, PITCH = tile_pitch<true>(CKB), GR = 4 * CKB, NX = 64 * GR / NT;
-  const int row0 = blockIdx.x * 64, ct0 = FEW ? blockIdx.y * 4 + (w & 3) : w * CT, bt0 = FEW ? w >> 2 : 0;
+  constexpr int CT = MODE == MANY ? CTH : 1, NBT = MODE == MANY ? 2 : 1, RD = MODE == FEWEST ? 8 : 4;
+  constexpr int PC = MODE == FEWEST ? 4 : 1, RINGS = MODE == FEWEST ? 2 : 1;  // chunks of rows, and rings of weights, under way
+  constexpr int CKB = kChunk, PITCH = tile_pitch<true>(CKB), GR = 4 * CKB, ROWS = MODE == FEWEST ? 32 : 64, NX = ROWS * GR / NT;
+  const int row0 = blockIdx.x * ROWS, bt0 = MODE == FEW ? w >> 2 : 0;
+  const int ct0 = MODE == MANY ? w * CT : MODE == FEW ? blockIdx.y * 4 + (w & 3) : blockIdx.y;
+  const bool multiplies = MODE != FEWEST || w == 0;
   const int DK = a.DK, DK4 = (DK + 3) & ~3, nch = (a.nkb + CKB - 1) / CKB;
 
   // A thread stages four columns of NX rows.  Every request is made and lies inside its row: a group that reaches past the end
@@ -130,8 +138,9 @@ __global__ __launch_bounds__(NT, 2) void market_rows_kernel(MarketArgs a) {
     }
     row[i] = min(max(r, 0), a.table_rows - 1);
   }
-  f32x4 pre[NX];
-  auto fetch = [&](int ch) {
+  f32x4 pre[PC][NX];
+  auto fetch = [&](int ch, f32x4(&pre)[NX]) {
+    ch = min(ch, nch - 1);
     int l = threadIdx.x;
     asm volatile("" : "+v"(l));
     const int c = ch * (16 * CKB) + 4 * (l & (GR - 1));
@@ -141,7 +150,7 @@ __global__ __launch_bounds__(NT, 2) void market_rows_kernel(MarketArgs a) {
 #pragma unroll
     for (int i = 0; i < NX; ++i) pre[i] = *reinterpret_cast<const f32x4u *>(base + row[i] * pitch);
   };
-  auto stash = [&](int ch) {
+  auto stash = [&](int ch, const f32x4(&pre)[NX]) {
     int l = threadIdx.x;
     asm volatile("" : "+v"(l));
     const int c = ch * (16 * CKB) + 4 * (l & (GR - 1));
@@ -157,36 +166,67 @@ __global__ __launch_bounds__(NT, 2) void market_rows_kernel(MarketArgs a) {
         if (back & 2) v = f32x4{v[2], v[3], 0.0f, 0.0f};
         if (back >= 4) v = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
       }
-      Op<true>::store4(lds + (ch & 1) * (64 * PITCH) + (l / GR + NT / GR * i) * PITCH + 8 * (l & (GR - 1)), v[0], v[1], v[2], v[3]);
+      Op<true>::store4(lds + (ch & 1) * (ROWS * PITCH) + (l / GR + NT / GR * i) * PITCH + 8 * (l & (GR - 1)), v[0], v[1], v[2], v[3]);
     }
   };
 
-  fetch(0);
-  u32x4 ring[RD][CT];
-  prime<CT, RD>(ring, a.W, a.nkb, kTiles, ct0, lane);
   const u32x4 *wp[CT];
 #pragma unroll
   for (int c = 0; c < CT; ++c) wp[c] = a.W + (size_t)(ct0 + c) * 64 + lane;
+  u32x4 ring[RINGS][RD][CT];
+#pragma unroll
+  for (int j = 0; j < PC; ++j) {
+    fetch(j, pre[j]);
+    if (j < RINGS && multiplies) {
+#pragma unroll
+      for (int s = 0; s < RD; ++s)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) ring[j % RINGS][s][c] = wp[c][(size_t)min(j * RD + s, a.nkb - 1) * kTiles * 64];
+    }
+  }
   f32x16 acc[CT][NBT];
   bias_acc<CT, NBT>(acc, a.b, ct0, lane);
   const int nfull = a.nkb / CKB;
 #pragma unroll
-  for (int i = 0; i < NX; ++i) asm volatile("" : "+v"(pre[i]));  // (arrived: the loop's waits are for its own requests)
-  for (int ch = 0; ch < nfull; ++ch) {
-    unsigned char *x = lds + (ch & 1) * (64 * PITCH);
-    stash(ch);
+  for (int i = 0; i < NX; ++i) asm volatile("" : "+v"(pre[0][i]));  // (arrived: the loop's waits are for its own requests)
+  auto chunk = [&](int ch, auto place) {  // place: ch % PC
+    constexpr int j = decltype(place)::value;
+    unsigned char *x = lds + (ch & 1) * (ROWS * PITCH);
+    stash(ch, pre[j]);
     __syncthreads();  // chunk ch complete; everybody is done with the buffer chunk ch + 1 goes into
-    fetch(min(ch + 1, nch - 1));
+    fetch(ch + PC, pre[j]);
     asm volatile("" ::: "memory");  // (requested here: behind the weights they would be waited for with them)
     __builtin_amdgcn_sched_barrier(0);
-    mma_chunk<CT, NBT, RD, CKB>(acc, ring, x + bt0 * (32 * PITCH), PITCH, ch * CKB, a.nkb, wp, kTiles, lane);
-  }
-  if (nfull < nch) {
-    stash(nfull);
+    if (multiplies)
+      mma_chunk<CT, NBT, RD, CKB, RINGS * RD>(acc, ring[j % RINGS], x + bt0 * (32 * PITCH), PITCH, ch * CKB, a.nkb, wp, kTiles, lane);
+  };
+  auto last = [&](auto place) {
+    constexpr int j = decltype(place)::value;
+    stash(nfull, pre[j]);
     __syncthreads();
-    mma_layer_range<true, CT, NBT, RD>(acc, ring, lds + (nfull & 1) * (64 * PITCH), PITCH, nfull * CKB, a.nkb, a.nkb, a.W, kTiles, ct0, bt0,
-                                       lane);
+    if (multiplies)
+      mma_layer_range<true, CT, NBT, RD>(acc, ring[j % RINGS], lds + (nfull & 1) * (ROWS * PITCH), PITCH, nfull * CKB, a.nkb, a.nkb, a.W, kTiles,
+                                         ct0, bt0, lane);
+  };
+  int ch = 0;
+  if constexpr (PC == 4) {
+    for (; ch + 4 <= nfull; ch += 4) chunk(ch, Int<0>{}), chunk(ch + 1, Int<1>{}), chunk(ch + 2, Int<2>{}), chunk(ch + 3, Int<3>{});
+    if (ch < nfull) chunk(ch, Int<0>{});
+    if (ch + 1 < nfull) chunk(ch + 1, Int<1>{});
+    if (ch + 2 < nfull) chunk(ch + 2, Int<2>{});
+    if (nfull < nch) {
+      switch (nfull & 3) {
+        case 0: last(Int<0>{}); break;
+        case 1: last(Int<1>{}); break;
+        case 2: last(Int<2>{}); break;
+        case 3: last(Int<3>{}); break;
+      }
+    }
+  } else {
+    for (; ch < nfull; ++ch) chunk(ch, Int<0>{});
+    if (nfull < nch) last(Int<0>{});
   }
+  if (!multiplies) return;
 #pragma unroll
   for (int c = 0; c < CT; ++c)
 #pragma unroll
@@ -851,17 +891,18 @@ hipError_t launch_market_rows(hipStream_t st, const EnvDims &d, const EnvState &
   a.rows = rows, a.D = d.D, a.DK = d.D * d.K, a.nkb = table_market_blocks(d.D, d.K);
   a.s_price = d.s_price, a.s_ind = d.s_ind;
   a.tau = s.tau, a.start = s.start, a.N = d.N, a.H = d.H, a.table_rows = m.rows;
-  const unsigned tiles = (unsigned)((rows + 63) / 64);
-  auto launch = [&](auto p, auto few) {
-    constexpr auto kern = market_rows_kernel<decltype(p)::value, decltype(few)::value>;
+  auto launch = [&](auto p, auto mode) {
+    constexpr Rows MODE = (Rows)decltype(mode)::value;
+    constexpr auto kern = market_rows_kernel<decltype(p)::value, MODE>;
     const hipError_t err = allow_full_lds<kern>();
     if (err != hipSuccess) return err;
-    const size_t lds = 2 * (size_t)64 * tile_pitch<true>(kChunk);
-    hipLaunchKernelGGL(kern, dim3(tiles, decltype(few)::value ? kTiles / 4 : 1), dim3(NT), lds, st, a);
+    constexpr int ROWS = MODE == FEWEST ? 32 : 64;
+    const size_t lds = 2 * (size_t)ROWS * tile_pitch<true>(kChunk);
+    hipLaunchKernelGGL(kern, dim3((unsigned)((rows + ROWS - 1) / ROWS), MODE == MANY ? 1 : MODE == FEW ? kTiles / 4 : kTiles), dim3(NT), lds, st, a);
     return hipGetLastError();
   };
-  if (tiles < 64) return pairs ? launch(std::true_type{}, std::true_type{}) : launch(std::false_type{}, std::true_type{});
-  return pairs ? launch(std::true_type{}, std::false_type{}) : launch(std::false_type{}, std::false_type{});
+  auto launch_mode = [&](auto mode) { return pairs ? launch(std::true_type{}, mode) : launch(std::false_type{}, mode); };
+  return rows <= 512 ? launch_mode(Int<FEWEST>{}) : rows <= 63 * 64 ? launch_mode(Int<FEW>{}) : launch_mode(Int<MANY>{});
 }
 
 }  // namespace

@@ -282,8 +282,9 @@ __device__ inline void mma_layer_range(f32x16 (&acc)[CT][NBT], u32x4 (&ring)[PD]
   }
 }
 
-// A whole chunk of CKB k-blocks: straight-line code, the loop over the chunks is the caller's.
-template <int CT, int NBT, int PD, int CKB>
+// A whole chunk of CKB k-blocks: straight-line code, the loop over the chunks is the caller's.  AHEAD: the k-blocks of all of the
+// caller's rings, which its chunks take in turn.
+template <int CT, int NBT, int PD, int CKB, int AHEAD = PD>
 __device__ inline void mma_chunk(f32x16 (&acc)[CT][NBT], u32x4 (&ring)[PD][CT], const unsigned char *ldsX, int pitch, int kb_lo,
                                  int nkb, const u32x4 *const (&wp)[CT], int nct, int lane) {
   const unsigned char *xbase = ldsX + (size_t)(lane & 31) * pitch + 16 * (lane >> 5);
@@ -296,7 +297,7 @@ __device__ inline void mma_chunk(f32x16 (&acc)[CT][NBT], u32x4 (&ring)[PD][CT], 
     for (int c = 0; c < CT; ++c)
 #pragma unroll
       for (int t = 0; t < NBT; ++t) Op<true>::mma(ring[k % PD][c], x[t], acc[c][t]);
-    const size_t kn = min(kb_lo + k + PD, nkb - 1);
+    const size_t kn = min(kb_lo + k + AHEAD, nkb - 1);
 #pragma unroll
     for (int c = 0; c < CT; ++c) ring[k % PD][c] = wp[c][kn * nct * 64];
     __builtin_amdgcn_sched_barrier(0);

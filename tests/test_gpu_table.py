@@ -87,6 +87,13 @@ def test_rollout_over_a_shared_table(N, D, K, rows, H, T):
         assert torch.equal(v, end[k]), k
 
 
+# Calls of one step, whose market sums are formed by smaller workgroups on up to 512 rows, give the bits of longer ones: full and ragged
+# ones of 32 rows, the last row count, and inputs that end in each of the four places a chunk of them is requested in.
+@pytest.mark.parametrize("N,D,K,T", [(32, 47, 5, 24), (33, 33, 3, 24), (512, 34, 6, 9), (513, 64, 8, 9), (480, 90, 8, 9)])
+def test_market_sums_of_few_rows(N, D, K, T):
+    test_rollout_over_a_shared_table(N, D, K, 700, 9, T)  # (700 rows for the whole of it)
+
+
 # Values of calls with few rows, on either side of the lines at which the head over table sums takes over from the kernels for any
 # network: 4096 rows over a short table (N (T + 1) = 4096, 4097), 8192 over a longer one, 1024 rows of more than 640 inputs (there
 # also over tables longer than the rows).
