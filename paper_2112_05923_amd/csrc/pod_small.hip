@@ -636,9 +636,9 @@ hipError_t launch_rollout_small(hipStream_t st, const EnvDims &d, const EnvState
 }
 
 // Where other kernels of the forward pass are the faster value head.  Up to 4096 rows of more than 64 inputs: query_kernel, which starts
-// on the rows at once; us a step of calls of four steps, this -> that: fp32, 64 units, 301 inputs, 5 rows 8.05 -> 7.01, 500 9.2 -> 7.9,
-// 2000 9.3 -> 8.0, 4100 9.5 -> 9.6; 97 inputs 2000 rows 6.2 -> 5.9; bf16, 128 units, 301 inputs 500 rows 5.9 -> 5.5; 46 inputs level, 21
-// 4.7 -> 4.9.  Many rows in bf16 of more than 160 inputs, which pay for 320 here: 128 units, 301 inputs, 20480 rows 9.8 -> 8.7 the
+// on the rows at once; us of the head behind calls of four steps, this -> that: fp32, 64 units, 301 inputs, 5 rows 9.1 -> 6.2, 500 10.9 -> 6.9,
+// 4000 11.7 -> 8.5; 73 inputs 2000 rows 6.6 -> 6.0; bf16, 128 units, 301 inputs 500 rows 5.7 -> 4.5; up to 64 inputs level or the other way
+// round.  Many rows in bf16 of more than 160 inputs, which pay for 320 here: 128 units, 301 inputs, 20480 rows 9.8 -> 8.7 the
 // other way round, 30000 14.2 -> 14.0, 81920 29.3 -> 27.8, 327680 131 -> 115 (161 inputs 101 -> 88), 64 units 163840 level, 327680 111 -> 108.
 bool value_small_covers(const PackedNet &critic, int64_t rows) {
   const int nkb = critic.nkb[0], hidden = critic.out_dim[0];
